@@ -150,61 +150,61 @@ __device__ __forceinline__ void nearest_candidate(lds_i32* cand, lds_i32* ctok, 
 }
 
 // ------------------------------------------------------------------------------------------
-// After the density Gram pass, two independent jobs in one launch:
-//   blocks [0, REFINE_BLOCKS): the pairs the epilogue could not decide in fp32 - evaluate
-//       Eq. 5 in fp64 and clear the bit if the distance exceeds d_c (one wavefront per pair);
-//   the other blocks: Eq. 6 completed, rho_p = sum over the row blocks of the column
-//       partials (64 tokens x 4 slices per block).  With d_n = 2 every term is an fp32 value
-//       in [e^-1, 1], so these fp64 additions are exact whatever their order; for other d_n they
-//       are rounded, in an order that is fixed for a given shape (no atomics anywhere), and
-//       the order of close densities is settled in fp64 further down the line anyway.
-constexpr int REFINE_BLOCKS = 768;     // 3072 wavefronts: one pair each on the benchmark image (2 200 pairs), so that no
-                                       // wavefront evaluates two or three rows one after the other (256: 1.2 us longer)
+// After the density pass: the pairs its epilogue could not decide in fp32.  Eq. 5 in fp64, the bit
+// cleared where the distance exceeds d_c.  One wavefront per listed pair and turn, so that the pairs are
+// spread evenly (near d_c the pairs of a row come in clumps: settled by the wavefronts that build the rows'
+// lists, or by workgroups of 32 rows, they took 3 to 13 us longer); a wavefront's pairs, tokens and norms arrive in three
+// trips, then one trip per pair brings both rows (up to eight chunks of either per lane in flight: rows of
+// 7 KB took 57 us for 23 700 pairs when every chunk was a trip of its own).
+// grid (settle_blocks(), B), block 256.
+static int settle_blocks(int n_max) { return n_max >= 6144 ? 768 : n_max < 512 ? 64 : n_max / 8; }   // (the benchmark image: a pair per wavefront)
 
-template <int DT>
-__global__ __launch_bounds__(256) void post_gram_kernel(Batch bt, const char* __restrict__ keys, int dk,
-                                                         const int32_t* __restrict__ idx,
-                                                         const double* __restrict__ nn,
-                                                         const uint32_t* __restrict__ near_list,
-                                                         const int32_t* __restrict__ near_cnt,
-                                                         const uint32_t* __restrict__ far_bits, int far_words,
-                                                         uint64_t* adj, pact_report* rep,
-                                                         const double* __restrict__ rho_part,
-                                                         double* __restrict__ rho, double* rho_opt) {
-    __shared__ double s_p[4][64];
+template <int DT, int CH>
+__global__ __launch_bounds__(256) void settle_kernel(Batch bt, const char* __restrict__ keys, int dk,
+                                                     const int32_t* __restrict__ idx,
+                                                     const double* __restrict__ nn,
+                                                     const uint32_t* __restrict__ near_list,
+                                                     const int32_t* __restrict__ near_cnt,
+                                                     const uint32_t* __restrict__ far_bits, int far_words,
+                                                     uint64_t* adj, pact_report* rep) {
     const int b = blockIdx.y;
     const Seg sg = bt.s[b];
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
-    if (blockIdx.x < REFINE_BLOCKS) {
-        const int gw = blockIdx.x * 4 + wave;
-        const int nw = REFINE_BLOCKS * 4;
-        const uint32_t raw = (uint32_t)near_cnt[2 * b];
-        const int cnt = (int)min(raw, (uint32_t)NEAR_CAP);
-        if (gw == 0) {
-            // largest key distance: the wavefronts of the density pass each left the bits of their
-            // most negative exponent -(d / d_n) log2(e); negative floats order like those bits
-            uint32_t fb = 0u;
-            for (int k = lane; k < far_words; k += 64) fb = max(fb, far_bits[(size_t)b * far_words + k]);
+    const int gw = blockIdx.x * 4 + wave;
+    const int nw = gridDim.x * 4;
+    const uint32_t raw = (uint32_t)near_cnt[2 * b];
+    const int cnt = (int)min(raw, (uint32_t)NEAR_CAP);
+    if (gw == 0) {
+        // largest key distance: the wavefronts of the density pass each left the bits of their
+        // most negative exponent -(d / d_n) log2(e); negative floats order like those bits
+        uint32_t fb = 0u;
+        for (int k0 = lane; k0 < far_words; k0 += 16 * 64) {       // (16 words per lane and trip)
+            uint32_t v[16];
 #pragma unroll
-            for (int sft = 32; sft >= 1; sft >>= 1) fb = max(fb, (uint32_t)__shfl_xor((int)fb, sft, 64));
-            if (lane == 0) {
-                // (a listed pair that stands for both orders counts twice)
-                rep[b].dc_checked_pairs = raw > (uint32_t)NEAR_CAP ? cnt : near_cnt[2 * b + 1];
-                rep[b].refine_overflow = raw > (uint32_t)NEAR_CAP;
-                rep[b].max_key_distance = fb ? fminf(-__uint_as_float(fb) * sg.d_n * 0.6931471805599453f, 2.0f) : 0.0f;
-            }
+            for (int u = 0; u < 16; ++u) v[u] = k0 + 64 * u < far_words ? far_bits[(size_t)b * far_words + k0 + 64 * u] : 0u;
+#pragma unroll
+            for (int u = 0; u < 16; ++u) fb = max(fb, v[u]);
         }
-        const size_t row_bytes = (size_t)dk * Elem<DT>::BYTES;
-        const char* kb = keys + (size_t)sg.base * row_bytes;
-        const int32_t* ix = idx + sg.base;
-        const double* nnb = nn + sg.base;
-        const double d_c = (double)sg.d_c;
-        int ties = 0;
-        // lane l takes this wavefront's l-th pair (gw + l * nw): pair, tokens and norms of all of
-        // them arrive in three trips, whatever their number; then one trip per pair for the rows
-        static_assert(NEAR_CAP <= 64 * REFINE_BLOCKS * 4, "a wavefront's pairs fit its lanes");
-        const int my_e = gw + lane * nw;
+#pragma unroll
+        for (int sft = 32; sft >= 1; sft >>= 1) fb = max(fb, (uint32_t)__shfl_xor((int)fb, sft, 64));
+        if (lane == 0) {
+            // (a listed pair that stands for both orders counts twice)
+            rep[b].dc_checked_pairs = raw > (uint32_t)NEAR_CAP ? cnt : near_cnt[2 * b + 1];
+            rep[b].refine_overflow = raw > (uint32_t)NEAR_CAP;
+            rep[b].max_key_distance = fb ? fminf(-__uint_as_float(fb) * sg.d_n * 0.6931471805599453f, 2.0f) : 0.0f;
+        }
+    }
+    constexpr int EPL = Elem<DT>::EPL;
+    const size_t row_bytes = (size_t)dk * Elem<DT>::BYTES;
+    const char* kb = keys + (size_t)sg.base * row_bytes;
+    const int32_t* ix = idx + sg.base;
+    const double* nnb = nn + sg.base;
+    const double d_c = (double)sg.d_c;
+    int ties = 0;
+    for (int e0 = gw; e0 < cnt; e0 += 64 * nw) {
+        // lane l takes this wavefront's l-th pair (e0 + l * nw)
+        const int my_e = e0 + lane * nw;
         uint32_t my_pi = 0, my_pj = 0;
         int my_ti = 0, my_tj = 0;
         double my_ni = 0.0, my_nj = 0.0;
@@ -214,17 +214,36 @@ __global__ __launch_bounds__(256) void post_gram_kernel(Batch bt, const char* __
             my_ti = ix[my_pi & ~NEAR_MIRROR]; my_tj = ix[my_pj];
             my_ni = nnb[my_ti]; my_nj = nnb[my_tj];
         }
-        const int mine = (cnt > gw) ? (cnt - gw + nw - 1) / nw : 0;     // pairs of this wavefront
+        const int mine = min(64, (cnt - e0 + nw - 1) / nw);     // pairs of this wavefront
         for (int k = 0; k < mine; ++k) {
             // (k is the same in every lane: scalar lane reads)
             const uint32_t pi_raw = (uint32_t)__builtin_amdgcn_readlane((int)my_pi, k), pj = (uint32_t)__builtin_amdgcn_readlane((int)my_pj, k);
             const uint32_t pi = pi_raw & ~NEAR_MIRROR;
             const bool both = (pi_raw & NEAR_MIRROR) != 0;
-            const int ti = __builtin_amdgcn_readlane(my_ti, k), tj = __builtin_amdgcn_readlane(my_tj, k);
             double d = 0.0;
             if (pi != pj) {
-                const double dot = wave_dot64<DT>(kb + (size_t)ti * row_bytes, kb + (size_t)tj * row_bytes, dk, lane);
-                d = cos_dist64(dot, __shfl(my_ni, k, 64), __shfl(my_nj, k, 64));
+                const char* ri = kb + (size_t)__builtin_amdgcn_readlane(my_ti, k) * row_bytes;
+                const char* rj = kb + (size_t)__builtin_amdgcn_readlane(my_tj, k) * row_bytes;
+                double acc = 0.0;                        // (the order of operations of wave_dot64)
+                for (int c0 = lane * EPL; c0 < dk; c0 += CH * 64 * EPL) {
+                    uint4 va[CH], vb[CH];
+#pragma unroll
+                    for (int u = 0; u < CH; ++u) {
+                        const size_t o = (size_t)(c0 + u * 64 * EPL < dk ? c0 + u * 64 * EPL : c0) * Elem<DT>::BYTES;
+                        va[u] = *(const uint4*)(ri + o);
+                        vb[u] = *(const uint4*)(rj + o);
+                    }
+#pragma unroll
+                    for (int u = 0; u < CH; ++u)
+                        if (c0 + u * 64 * EPL < dk) {
+                            double a[8], x[8];
+                            Elem<DT>::widen(va[u], a);
+                            Elem<DT>::widen(vb[u], x);
+#pragma unroll
+                            for (int i = 0; i < EPL; ++i) acc = fma(a[i], x[i], acc);
+                        }
+                }
+                d = cos_dist64(wave_sum_f64(acc), __shfl(my_ni, k, 64), __shfl(my_nj, k, 64));
             }
             if (lane == 0) {
                 if (d > d_c) {
@@ -237,45 +256,8 @@ __global__ __launch_bounds__(256) void post_gram_kernel(Batch bt, const char* __
                 if (fabs(d - d_c) <= 1e-6) ties += both ? 2 : 1;
             }
         }
-        if (lane == 0 && ties) atomicAdd(&rep[b].dc_near_ties, ties);
-        return;
     }
-    const int p0 = (blockIdx.x - REFINE_BLOCKS) * 64;
-    const int p = p0 + lane;
-    // the first 32 rows of partials are requested before the number of kept tokens is known
-    // (they lie inside the workspace for any p < n_max; what is past the last row is masked)
-    const double* in = rho_part + (size_t)b * bt.W * bt.n_max + p;
-    double v0[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-        const int r = wave + 4 * u;
-        v0[u] = (p < bt.n_max && r < bt.W) ? in[(size_t)r * bt.n_max] : 0.0;
-    }
-    const int q = clamp_count(rep[b].n_kept, sg.n);
-    if (p0 >= q) return;
-    const int nrt = (q + GRAM_RHO_ROWS - 1) / GRAM_RHO_ROWS;
-    double acc = 0.0;
-    if (p < q) {
-#pragma unroll
-        for (int u = 0; u < 8; ++u) acc += (wave + 4 * u < nrt) ? v0[u] : 0.0;
-        for (int r0 = wave + 32; r0 < nrt; r0 += 32) {
-            double v[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int r = r0 + 4 * u;
-                v[u] = (r < nrt) ? in[(size_t)r * bt.n_max] : 0.0;
-            }
-#pragma unroll
-            for (int u = 0; u < 8; ++u) acc += v[u];
-        }
-    }
-    s_p[wave][lane] = acc;
-    __syncthreads();
-    if (wave == 0 && p < q) {
-        const double t = (s_p[0][lane] + s_p[1][lane]) + (s_p[2][lane] + s_p[3][lane]);
-        rho[(size_t)b * bt.n_max + p] = t;
-        if (rho_opt) rho_opt[sg.base + p] = t;
-    }
+    if (lane == 0 && ties) atomicAdd(&rep[b].dc_near_ties, ties);
 }
 
 // Optional output: position of every kept token in the density order, by enumeration.
@@ -346,73 +328,103 @@ __device__ __forceinline__ double recheck_band2(float d_n) {
 // bitmap row).  The first four slots are also written to the token's 8-byte head: most tokens
 // have at most three preceding neighbours, and the kernel that runs the rounds - a single
 // workgroup - then has 8 bytes per token to fetch instead of 32.
-// One wavefront per kept token p.  `odd` counts, wave-wide, the neighbours whose density is
-// too close to this token's: DETECT: inside the band above; otherwise (second pass, on fp64
-// densities): lower-numbered neighbours with a different density within 1e-11 of the sum.
+// GL lanes of a wavefront per token (16: four tokens per wavefront, most tokens have fewer
+// neighbours than that; 64: one).  Every lane of the wavefront takes part, with p < 0 for no token.
+// `odd` counts, per token, the neighbours whose density is too close to this token's: DETECT:
+// inside the band above; otherwise (second pass, on fp64 densities): lower-numbered neighbours with
+// a different density within 1e-11 of the sum.
 constexpr int HEAD_PREDS = 3;
-constexpr int PREDS_SPREAD = 256;      // set bits of 64 row words that are spread over the lanes through LDS
-template <bool DETECT>
+constexpr int PREDS_SPREAD = 256;      // set bits of a wavefront's row words that are spread over the lanes through LDS
+template <bool DETECT, int GL>
 __device__ __forceinline__ int preds_of_row(int p, int q, const double* r, const uint64_t* row, uint16_t* out,
-                                            uint16_t* head, volatile uint16_t* nb, int lane, double band2) {
-    const double rp = r[p];
+                                            uint16_t* head, volatile uint16_t* nb_wave, int lane, double band2) {
+    static_assert(GL == 16 || GL == 64, "a row of lanes or the wavefront");
+    constexpr int WPL = 64 / GL;                       // words per lane and turn
+    constexpr int CAP = PREDS_SPREAD / WPL;            // list entries per token
+    const int gl = lane & (GL - 1), gbase = lane & ~(GL - 1);
+    volatile uint16_t* nb = nb_wave + (lane / GL) * CAP;
+    const bool on = p >= 0;
+    const double rp = on ? r[p] : 0.0;
     const int Wq = (q + 63) >> 6;
     int total = 0, odd = 0;
-    auto too_close = [&](bool has, int j, double rj) __attribute__((always_inline)) {
-        const double d = rj - rp;
-        if constexpr (DETECT) return has && j < q && j != p && d * d <= band2 * fmax(rj, rp);
-        else return has && j < p && d != 0.0 && fabs(d) <= 1e-11 * (rj + rp);
+    auto group_bits = [&](bool v) __attribute__((always_inline)) {          // ballot of this token's lanes
+        const uint64_t m = __ballot(v);
+        return GL == 64 ? m : (m >> gbase) & ((1ull << (GL & 63)) - 1ull);
     };
+    auto group_scan = [&](int v) __attribute__((always_inline)) {           // inclusive prefix sum over them
+        v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);
+        v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);
+        v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);
+        v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);
+        if (GL == 64) {
+            v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);
+            v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);
+        }
+        return v;
+    };
+    auto last_of = [&](int v) __attribute__((always_inline)) { return GL == 64 ? lane63_of(v) : __shfl(v, gbase + GL - 1, 64); };
     // A token's neighbours are mostly close to it in the sequence, i.e. their bits sit in one or
     // two words of the row: lane by lane, a word's bits would be looked up one after the other,
     // each look-up (the neighbour's density) a trip to memory.  So the set bits of 64 words are
     // first spread over the lanes - the k-th set bit to lane k, through a small LDS list - and
-    // the densities of up to 64 neighbours are fetched in one trip.
+    // the densities of up to GL neighbours are fetched in one trip.
     for (int w0 = 0; w0 < Wq; w0 += 64) {
-        const int w = w0 + lane;
-        uint64_t word = (w < Wq) ? row[w] : 0ull;
-        const int cnt = __popcll(word);
-        const int inc = wave_scan_incl_i32(cnt);
-        const int nbits = lane63_of(inc);
-        if (nbits <= PREDS_SPREAD) {
+        uint64_t word[WPL];
+#pragma unroll
+        for (int u = 0; u < WPL; ++u) word[u] = on && w0 + gl + GL * u < Wq ? row[w0 + gl + GL * u] : 0ull;
+        while (true) {
+            // (all of a lane's bits; CAP / GL at a time where a token's words hold more than its list does)
+            int cnt = 0;
+#pragma unroll
+            for (int u = 0; u < WPL; ++u) cnt += __popcll(word[u]);
+            int inc = group_scan(cnt);
+            if (__any(last_of(inc) > CAP)) {
+                cnt = min(cnt, CAP / GL);
+                inc = group_scan(cnt);
+            }
+            const int nbits = last_of(inc);
+            if (__all(nbits == 0)) break;
             int at = inc - cnt;
-            while (word) {                                   // (no memory access in this loop)
-                nb[at++] = (uint16_t)((w << 6) + __builtin_ctzll(word));
-                word &= word - 1;
-            }
+#pragma unroll
+            for (int u = 0; u < WPL; ++u)
+                while (word[u] && at < inc) {                // (no memory access in this loop)
+                    const int bit = __builtin_ctzll(word[u]);
+                    nb[at++] = (uint16_t)(((w0 + gl + GL * u) << 6) + bit);
+                    word[u] &= word[u] - 1;
+                }
             __builtin_amdgcn_wave_barrier();
-            for (int k0 = 0; k0 < nbits; k0 += 64) {        // (wave-uniform trip count)
-                const int k = k0 + lane;
-                const bool has = k < nbits;
-                const int j = has ? nb[k] : p;
-                const double rj = r[j < q ? j : p];
-                const bool pre = has && j < q && precedes(rj, j, rp, p);
-                const uint64_t m = __ballot(pre);
-                const int slot = total + lanes_below(m, lane);
-                if (pre && slot < KP) out[1 + slot] = (uint16_t)j;
-                if (pre && slot < HEAD_PREDS) head[1 + slot] = (uint16_t)j;
-                total += __popcll(m);
-                odd += __popcll(__ballot(too_close(has, j, rj)));
+            // (wave-uniform trip count; the densities of WPL entries per lane arrive together)
+            for (int k0 = 0; __any(k0 < nbits); k0 += WPL * GL) {
+                int j[WPL];
+                double rj[WPL];
+                bool has[WPL];
+#pragma unroll
+                for (int u = 0; u < WPL; ++u) {
+                    const int k = k0 + gl + GL * u;
+                    has[u] = k < nbits;
+                    j[u] = has[u] ? nb[k] : 0;
+                    has[u] = has[u] && j[u] < q;
+                    rj[u] = has[u] ? r[j[u]] : rp;
+                }
+#pragma unroll
+                for (int u = 0; u < WPL; ++u) {
+                    if (u > 0 && !__any(k0 + GL * u < nbits)) break;
+                    const uint64_t m = group_bits(has[u] && precedes(rj[u], j[u], rp, p));
+                    const bool pre = (m >> gl) & 1ull;
+                    const int slot = total + __popcll(m & ((1ull << gl) - 1ull));
+                    if (pre && slot < KP) out[1 + slot] = (uint16_t)j[u];
+                    if (pre && slot < HEAD_PREDS) head[1 + slot] = (uint16_t)j[u];
+                    total += __popcll(m);
+                    const double d = rj[u] - rp;
+                    const bool close = DETECT ? j[u] != p && d * d <= band2 * fmax(rj[u], rp)
+                                              : j[u] < p && d != 0.0 && fabs(d) <= 1e-11 * (rj[u] + rp);
+                    odd += __popcll(group_bits(has[u] && close));
+                }
             }
-            __builtin_amdgcn_wave_barrier();                 // the list is rewritten for the next 64 words
-        } else {
-            // a very dense row: word by word, one bit per lane and turn
-            BitPop bp{word};
-            while (bp.any()) {
-                int bit;
-                const bool has = bp.pop(bit);
-                const int j = (w << 6) + bit;
-                const double rj = r[(has && j < q) ? j : p];
-                const bool pre = has && j < q && precedes(rj, j, rp, p);
-                const uint64_t m = __ballot(pre);
-                const int slot = total + lanes_below(m, lane);
-                if (pre && slot < KP) out[1 + slot] = (uint16_t)j;
-                if (pre && slot < HEAD_PREDS) head[1 + slot] = (uint16_t)j;
-                total += __popcll(m);
-                odd += __popcll(__ballot(too_close(has, j, rj)));
-            }
+            __builtin_amdgcn_wave_barrier();                 // the list is rewritten
         }
     }
-    if (lane == 0) {
+    if (gl == 0 && on) {
         const uint16_t c = (uint16_t)(total > KP ? KP + 1 : total);
         out[0] = c;
         head[0] = c;
@@ -420,33 +432,40 @@ __device__ __forceinline__ int preds_of_row(int p, int q, const double* r, const
     return odd;
 }
 
-// grid (ceil(n_max/4), B), block 256: one wavefront per kept token.  Tokens with a neighbour
+// grid (ceil(n_max * GL / 256), B), block 256: GL lanes per kept token (see launch_centres).  Tokens with a neighbour
 // inside the band are appended to the sample's list, as position | token << 16 (tie_cnt[4b]
 // counts them, also past the list's end: the re-evaluation is then skipped and reported).
+template <int GL>
 __global__ __launch_bounds__(256) void build_preds_kernel(Batch bt, const pact_report* __restrict__ rep,
                                                           const uint64_t* __restrict__ adj,
-                                                          const double* __restrict__ rho,
+                                                          const double* __restrict__ rho, double* __restrict__ rho_opt,
                                                           uint16_t* __restrict__ preds,
                                                           uint2* __restrict__ heads,
                                                           const int32_t* __restrict__ idx,
                                                           int32_t* __restrict__ tie_list,
                                                           int32_t* __restrict__ tie_cnt) {
-    const int b = blockIdx.y;
-    const int lane = threadIdx.x & 63;
-    const int p = blockIdx.x * 4 + (threadIdx.x >> 6);
-    const int q = clamp_count(rep[b].n_kept, bt.s[b].n);
-    if (p >= q) return;
     __shared__ uint16_t s_nb[4][PREDS_SPREAD];
-    const int odd = preds_of_row<true>(p, q, rho + (size_t)b * bt.n_max, adj + ((size_t)b * bt.n_max + p) * bt.W,
-                                       preds + ((size_t)b * bt.n_max + p) * PRED_CAP,
-                                       (uint16_t*)(heads + (size_t)b * bt.n_max + p), s_nb[threadIdx.x >> 6], lane,
-                                       recheck_band2(bt.s[b].d_n));
-    if (odd && lane == 0) {
+    const int b = blockIdx.y;
+    const Seg sg = bt.s[b];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    constexpr int TPW = 64 / GL;
+    const int pw = (blockIdx.x * 4 + wave) * TPW;          // the wavefront's first token
+    const int q = clamp_count(rep[b].n_kept, sg.n);
+    if (pw >= q) return;
+    const int p = pw + lane / GL < q ? pw + lane / GL : -1, pr = p < 0 ? pw : p;
+    const double* r = rho + (size_t)b * bt.n_max;
+    const int odd = preds_of_row<true, GL>(p, q, r, adj + ((size_t)b * bt.n_max + pr) * bt.W,
+                                           preds + ((size_t)b * bt.n_max + pr) * PRED_CAP,
+                                           (uint16_t*)(heads + (size_t)b * bt.n_max + pr), s_nb[wave], lane,
+                                           recheck_band2(sg.d_n));
+    if ((lane & (GL - 1)) != 0 || p < 0) return;
+    if (rho_opt) rho_opt[sg.base + p] = r[p];
+    if (odd) {
         // position and token in one word (both below 2^15), so that the re-evaluation finds the
         // token's key without another look-up
         static_assert(PACT_MAX_TOKENS <= 32768, "two 15-bit numbers per list entry");
         const int slot = atomicAdd(&tie_cnt[4 * b], 1);
-        if (slot < RHO_RECHECK_MAX) tie_list[(size_t)b * RHO_RECHECK_MAX + slot] = p | (idx[bt.s[b].base + p] << 16);
+        if (slot < RHO_RECHECK_MAX) tie_list[(size_t)b * RHO_RECHECK_MAX + slot] = p | (idx[sg.base + p] << 16);
     }
 }
 
@@ -477,7 +496,7 @@ __device__ __forceinline__ void finish_rechecked_densities(const Batch& bt, int 
     int fine = 0;
     for (int t = wave; t < T; t += nwaves) {
         const int p = min(list[t] & 0xFFFF, q - 1);
-        fine += preds_of_row<false>(p, q, rho_b, adj + ((size_t)b * bt.n_max + p) * bt.W,
+        fine += preds_of_row<false, 64>(p, q, rho_b, adj + ((size_t)b * bt.n_max + p) * bt.W,
                                     preds + ((size_t)b * bt.n_max + p) * PRED_CAP,
                                     (uint16_t*)(heads + (size_t)b * bt.n_max + p), nb, lane, 0.0);
     }
@@ -1453,16 +1472,24 @@ int launch_centres(const Batch& bt, const Ws& w, const void* keys, pact_dtype k_
                    int32_t* cluster_counts, pact_report* rep, double* rho_opt, int32_t* rank_opt,
                    int stat_words, bool assign_now, hipStream_t st) {
     const char* k = (const char*)keys;
-    dim3 gpost(REFINE_BLOCKS + (bt.n_max + 63) / 64, bt.B);
-    if (k_dt == PACT_BF16)
-        PACT_LAUNCH("post_gram", post_gram_kernel<PACT_BF16>, gpost, dim3(256), st, bt, k, dk, idx, w.nn,
-                    w.near_list, w.near_cnt, w.stat, stat_words, w.adj, rep, w.rho_part, w.rho, rho_opt);
+    dim3 gset(settle_blocks(bt.n_max), bt.B);
+    const bool wide = (size_t)dk * (k_dt == PACT_BF16 ? 2 : 4) > 2048;
+#define PACT_SETTLE(DT, CH)                                                                                           \
+    PACT_LAUNCH("settle", (settle_kernel<DT, CH>), gset, dim3(256), st, bt, k, dk, idx, w.nn, w.near_list, w.near_cnt, \
+                w.stat, stat_words, w.adj, rep)
+    if (k_dt == PACT_BF16) { if (wide) PACT_SETTLE(PACT_BF16, 8); else PACT_SETTLE(PACT_BF16, 2); }
+    else { if (wide) PACT_SETTLE(PACT_F32, 8); else PACT_SETTLE(PACT_F32, 2); }
+#undef PACT_SETTLE
+    // One wavefront per kept token while the chip holds them all at once (32 per CU); beyond that four
+    // tokens per wavefront (one image: 7.3 us against 9.5 us; 8 videos: 14.2 against 9.9 us).
+    long kept_est = 0;
+    for (int b = 0; b < bt.B; ++b) kept_est += bt.s[b].n - prune_rank(bt.s[b].lambda, bt.s[b].n);
+    if (kept_est <= 256 * 32)
+        PACT_LAUNCH("build_preds", build_preds_kernel<64>, dim3((bt.n_max + 3) / 4, bt.B), dim3(256), st, bt, rep, w.adj, w.rho,
+                    rho_opt, w.preds, w.heads, idx, w.tie_list, w.tie_cnt);
     else
-        PACT_LAUNCH("post_gram", post_gram_kernel<PACT_F32>, gpost, dim3(256), st, bt, k, dk, idx, w.nn,
-                    w.near_list, w.near_cnt, w.stat, stat_words, w.adj, rep, w.rho_part, w.rho, rho_opt);
-    dim3 gtok((bt.n_max + 3) / 4, bt.B);
-    PACT_LAUNCH("build_preds", build_preds_kernel, gtok, dim3(256), st, bt, rep, w.adj, w.rho, w.preds,
-                w.heads, idx, w.tie_list, w.tie_cnt);
+        PACT_LAUNCH("build_preds", build_preds_kernel<16>, dim3((bt.n_max + 15) / 16, bt.B), dim3(256), st, bt, rep, w.adj, w.rho,
+                    rho_opt, w.preds, w.heads, idx, w.tie_list, w.tie_cnt);
     // neighbours whose densities the fp32 terms cannot order: fp64 (a few tokens of an image)
     // (one sample: 2048 workgroups, a work item each for up to 32 listed tokens of a 4000-token sample -
     //  the chip holds 512 of them at a time, and 4096 took 0.8 us longer to dispatch; a batch: 8192
@@ -1478,8 +1505,6 @@ int launch_centres(const Batch& bt, const Ws& w, const void* keys, pact_dtype k_
     // (one kernel holding both versions behind a device-side choice ran each of them a quarter to a half
     // slower), so the host goes by the kept tokens it expects.
     const size_t recheck_row_bytes = (size_t)dk * (k_dt == PACT_BF16 ? 2 : 4);
-    long kept_est = 0;
-    for (int b = 0; b < bt.B; ++b) kept_est += bt.s[b].n - prune_rank(bt.s[b].lambda, bt.s[b].n);
     const bool quarters = recheck_row_bytes % 64 == 0 &&
                           (kept_est >= (bt.B == 1 ? 6000 : 20000) || recheck_row_bytes >= 4096);
     if (quarters && k_dt == PACT_BF16)
@@ -1519,7 +1544,7 @@ int launch_centres(const Batch& bt, const Ws& w, const void* keys, pact_dtype k_
     if (!assign_now) return PACT_OK;          // the caller runs it with the recovery (launch_reincorporate)
     NearArgs a;
     std::memset(&a, 0, sizeof(a));
-    a.rep = rep; a.keys = k; a.dk = dk; a.nn = w.nn; a.adj = w.adj; a.margin = (float)cos_margin(dk);
+    a.rep = rep; a.keys = k; a.dk = dk; a.nn = w.nn; a.adj = w.adj; a.margin = (float)cos_margin(dk, k_dt);
     a.cluster_id = cluster_id; a.cluster_counts = cluster_counts;
     a.idx = idx; a.cmask = w.cmask; a.status = w.status; a.cnum = w.cnum;
     a.assign_blocks = (bt.n_max + 3) / 4;
@@ -1541,7 +1566,7 @@ int launch_reincorporate(const Batch& bt, const Ws& w, const void* keys, pact_dt
     NearArgs a;
     std::memset(&a, 0, sizeof(a));
     a.rep = rep; a.keys = (const char*)keys; a.dk = dk; a.nn = w.nn; a.adj = w.adj;
-    a.margin = (float)cos_margin(dk);
+    a.margin = (float)cos_margin(dk, k_dt);
     a.cluster_id = cluster_id; a.cluster_counts = cluster_counts;
     a.pruned_idx = pruned_idx; a.center_idx = center_idx; a.cbest = w.cbest;
     if (kept_idx) {

@@ -18,11 +18,11 @@ namespace pact {
 struct PrepArgs {
     const char* keys; int32_t dk;
     const char* q; int32_t qcols;            // q == nullptr: no query pass
-    double* nn; float* rinv; uint64_t* adj; double* qg_part;
+    double* nn; float* rinv; uint64_t* adj; double* rho; double* qg_part;
     uint32_t* status; int32_t* ident; int32_t* near_cnt; int32_t* tie_cnt;
     pact_report* rep; int32_t* cluster_id; int32_t* cluster_counts;
     const int32_t* n_idx_dev; uint32_t* zeros;
-    uint16_t* ksplit;                        // fp32 keys only: [total][3][dk rounded up to 8] bf16 parts for the Gram passes
+    char* ksplit;                            // fp32 keys only: the int8 planes for the Gram passes
     int32_t mode; int32_t n_key_blocks; int32_t n_q_blocks;
 };
 
@@ -63,28 +63,40 @@ __global__ __launch_bounds__(256) void prep_kernel(Batch bt, PrepArgs a) {
         const size_t g = (size_t)sg.base + i;
         const char* row = a.keys + g * (size_t)a.dk * Elem<KDT>::BYTES;
         const double v = wave_dot64<KDT>(row, row, a.dk, lane);
+        double scale = 1.0;                                    // of the rows the Gram passes read
         if constexpr (KDT == PACT_F32) {
-            // x = hi + mid + lo, each the bf16 nearest to what the parts before it leave (the
-            // differences are exact in fp32); together they carry the 24 bits of x
-            const int dkp = (a.dk + 7) & ~7;                   // plane pitch: whole 16-byte chunks, zero-padded
-            uint16_t* sp = a.ksplit + g * (size_t)(3 * dkp);
-            for (int e = lane * 4; e < dkp; e += 256) {
+            // The row as 24-bit integers X = rint(x S) (S: its largest element becomes 8355711, or a power of
+            // four less for rows of more than 2^17 elements, whose order-0 sums would not fit an int32), split
+            // into three signed bytes; 64 elements are 64 bytes of each plane in turn, padded with zeros.
+            float top = 0.0f;
+            for (int e = lane * 4; e < a.dk; e += 256) {
+                const float4 x = *(const float4*)(row + (size_t)e * 4);
+                top = fmaxf(fmaxf(top, fmaxf(fabsf(x.x), fabsf(x.y))), fmaxf(fabsf(x.z), fabsf(x.w)));
+            }
+            top = group_max_f32<16>(top);
+            top = fmaxf(top, __shfl_xor(top, 16, 64));
+            top = fmaxf(top, __shfl_xor(top, 32, 64));
+            double most = 8355711.0;
+            for (int64_t d = a.dk; d > 131072; d >>= 2) most *= 0.5;
+            const double S = top > 0.0f ? most / (double)top : 0.0;
+            scale = S;
+            char* sp = a.ksplit + g * (size_t)((a.dk + 63) / 64 * 192);
+            for (int e = lane * 4; e < (a.dk + 63) / 64 * 64; e += 256) {
                 const float4 x4 = (e < a.dk) ? *(const float4*)(row + (size_t)e * 4) : make_float4(0.f, 0.f, 0.f, 0.f);
                 const float x[4] = {x4.x, x4.y, x4.z, x4.w};
-                uint32_t part[3][4];
+                uint32_t part[3] = {0u, 0u, 0u};
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    float r = x[i];
+                    int X = (int)rint((double)x[i] * S);
 #pragma unroll
-                    for (int pl = 0; pl < 3; ++pl) {
-                        part[pl][i] = f32_to_bf16_rne(r);
-                        r -= __uint_as_float(part[pl][i] << 16);
+                    for (int pl = 2; pl >= 0; --pl) {
+                        const int byte = (int)(int8_t)(X & 255);
+                        part[pl] |= (uint32_t)(byte & 255) << (8 * i);
+                        X = (X - byte) >> 8;
                     }
                 }
 #pragma unroll
-                for (int pl = 0; pl < 3; ++pl)
-                    *(uint2*)(sp + (size_t)pl * dkp + e) =
-                        make_uint2(part[pl][0] | (part[pl][1] << 16), part[pl][2] | (part[pl][3] << 16));
+                for (int pl = 0; pl < 3; ++pl) *(uint32_t*)(sp + (size_t)(e >> 6) * 192 + pl * 64 + (e & 63)) = part[pl];
             }
         }
         // The bitmap is used over (kept tokens) x (kept tokens).  In a full reduction that is
@@ -96,9 +108,11 @@ __global__ __launch_bounds__(256) void prep_kernel(Batch bt, PrepArgs a) {
         for (int k = lane; k < Wn; k += 64) arow[k] = 0ull;
         if (lane == 0) {
             a.nn[g] = v;
-            a.rinv[g] = v > 0.0 ? (float)(1.0 / sqrt(v)) : 0.0f;
+            // (fp32 keys: products of the integers in units of 65536)
+            a.rinv[g] = v > 0.0 ? (float)((KDT == PACT_F32 ? 256.0 / scale : 1.0) / sqrt(v)) : 0.0f;
             if (a.mode == INIT_REDUCE || a.mode == INIT_DBDPC_ALL || a.mode == INIT_DBDPC_SUBSET) {
                 a.status[(size_t)b * bt.n_max + i] = ST_UNKNOWN;
+                a.rho[(size_t)b * bt.n_max + i] = 0.0;
                 a.ident[g] = i;
                 a.cluster_id[g] = -1;
                 if (a.cluster_counts) a.cluster_counts[g] = 0;
@@ -812,7 +826,7 @@ int launch_prep(const Batch& bt, const Ws& w, const void* keys, pact_dtype k_dt,
     PrepArgs a;
     a.keys = (const char*)keys; a.dk = dk;
     a.q = (const char*)q; a.qcols = qcols;
-    a.nn = w.nn; a.rinv = w.rinv; a.adj = w.adj; a.qg_part = w.qg_part;
+    a.nn = w.nn; a.rinv = w.rinv; a.adj = w.adj; a.rho = w.rho; a.qg_part = w.qg_part;
     a.status = w.status; a.ident = w.ident; a.near_cnt = w.near_cnt; a.tie_cnt = w.tie_cnt;
     a.rep = rep; a.cluster_id = cluster_id; a.cluster_counts = cluster_counts; a.n_idx_dev = n_idx_dev;
     a.zeros = w.zeros; a.ksplit = w.ksplit;

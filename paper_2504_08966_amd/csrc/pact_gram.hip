@@ -10,23 +10,35 @@
 // The distance matrix itself is never written.
 //
 // Shape of the kernel (gfx950):
-//  * one workgroup of 8 wavefronts per CU owns a (64*MI) x 256 output tile, MI = 4 or 2: 256x256
-//    halves the L2 traffic per flop of 128x128 tiles (the L2 -> CU path is what limits this
-//    contraction at a key width of 512), 128x256 is for launches that would otherwise leave
-//    CUs without a tile; each wavefront computes (32*MI) x 64 of it as MI x 2
-//    v_mfma_f32_32x32x16_bf16 accumulators (fp32 keys: as three bf16 planes, six passes);
-//  * the key rows stream in 128-byte slices (whole cache lines: eight lanes fetch one row's
-//    line) straight from global memory into a ring of LDS stages (global_load_lds_dwordx4: no
-//    staging registers); waits on the ring are explicit (s_waitcnt vmcnt + s_barrier);
+//  * a workgroup of WR x WC wavefronts owns a (32*MI*WR) x (32*NJ*WC) output tile, each wavefront MI x NJ
+//    32 x 32 accumulators.  bf16 keys (v_mfma_f32_32x32x16_bf16): 256x256 by 8 wavefronts (halves
+//    the L2 traffic per flop of 128x128 tiles), 128x256 and 128x128 (4 wavefronts) for launches that would
+//    otherwise leave CUs without a tile.  fp32 keys (v_mfma_i32_32x32x32_i8): 128x128 by 8 wavefronts;
+//  * the key rows stream in slices straight from global memory into a ring of LDS stages
+//    (global_load_lds_dwordx4: no staging registers); waits on the ring are explicit (s_waitcnt
+//    vmcnt + s_barrier).  bf16: 128 bytes of each row (a whole cache line, fetched by eight lanes);
+//    fp32: 64 elements of the three int8 planes of a row, 192 contiguous bytes;
 //  * both operands are rows of the same key matrix, so a lane takes 16 contiguous bytes of
-//    "its" row per MFMA; the eight 16-byte chunks of a row slice are XOR-swizzled by the row
+//    "its" row per MFMA; the 16-byte chunks of a row slice are XOR-swizzled by the row
 //    number so that 16 consecutive rows read conflict-free; the fragments of the next k-group
 //    are read from LDS while the MFMAs of the current one run;
 //  * the grid is persistent (the tile count depends on counts only the device knows) and
 //    XCD-aware: each of the 8 XCDs (own L2) works on its own band of tile columns;
-//  * density pass of a sample with more 256 x 256 tiles than workgroups: d_ij = d_ji, so only the
+//  * density pass of a sample with more square tiles than workgroups: d_ij = d_ji, so only the
 //    tiles on and above the diagonal are computed, and a tile above it also leaves the row sums,
 //    the transposed bits and the flagged near-d_c pairs of its mirror image (template SYM).
+//
+// fp32 keys.  The first kernel of a call writes every row as 24-bit integers X = rint(x S),
+// S = 8355711 / max|x| (a row's largest element uses all 24 bits), split into three signed bytes,
+// X = 65536 s0 + 256 s1 + s2.  A dot product is then sums of byte products, exact in int32: order
+// 0 (s0 t0), order 1 (s0 t1 + s1 t0), order 2 (s0 t2 + s1 t1 + s2 t0) and, where it can matter, order 3
+// (s1 t2 + s2 t1), combined once per pair in fp32; s2 t2 is always left out.  Six byte products at twice
+// the bf16 rate cost three bf16 passes (eight: four), against six for a split into three bf16 parts, and
+// nothing is rounded on the way.  What is left out of a cosine: the rounding of the elements, at most
+// sqrt(dk) 2^-23, and the orders from 3 (or 4) on: with |X| >= 2^24.5 (dk / 512)^(1/4) in both rows the
+// order-3 terms have a standard deviation of at most 8e-8, less than the rounding of an fp32
+// accumulation of that width; samples that hold a row below that (one element far above all
+// others) get order 3 as well, whose successor is 256 times smaller.
 #include <type_traits>
 
 #include "pact_internal.h"
@@ -45,13 +57,14 @@ struct GramArgs {
     const char* zeros;         // >= 16 zero bytes (source of the slices past the key width)
     uint64_t* adj;             // [B][n_max][W]
     float* cbest;              // candidate pass: [B][W][n_max] largest cosine per (group of 64 centres, pruned token)
-    double* rho_part;          // [B][W][n_max], one row per GRAM_RHO_ROWS kept rows
+    double* rho;               // density pass: [B][n_max] densities (zeroed beforehand)
     uint32_t* near_list;       // [B][NEAR_CAP][2]
     int32_t* near_cnt;         // [B][2]: list slots taken, ordered pairs they stand for (8-byte aligned)
     uint32_t* stat;            // [B][stat_wgs * 8] per wavefront: bits of the most negative density exponent
                                // it saw (largest distance), or NULL when the statistic is not wanted
-    int32_t stat_wgs;          // workgroup slots per sample in `stat`
+    int32_t stat_wgs;          // workgroup slots per sample in `stat`, one word per wavefront
     float margin;              // worst-case fp32 error of a cosine
+    float rinv_low;            // fp32 keys: a reciprocal norm above this asks for the order-3 products
     // Batches (mapped != 0): a one-dimensional grid of GRAM_MAX_WORKGROUPS workgroups, shared out
     // among the samples by size; workgroup i serves sample wg_map[i] >> 8 as its workgroup number
     // wg_map[i] & 255 of wg_count[sample] (0xFFFF: a spare workgroup).
@@ -60,18 +73,29 @@ struct GramArgs {
     uint16_t wg_map[GRAM_MAX_WORKGROUPS];
 };
 
-constexpr int TILE_C = 256;
-constexpr int SLICE_BYTES = 128;           // bytes of each row per stage: 8 chunks of 16 B = one cache line
 constexpr int LDS_BUDGET = 160 * 1024 - 4096;
 
-template <int MI> struct Shape {
-    static constexpr int TILE_R = 64 * MI;                              // 2 wavefront rows x MI x 32
-    static constexpr int STAGE_BYTES = (TILE_R + TILE_C) * SLICE_BYTES; // A rows then B rows
-    static constexpr int NSTAGE = (LDS_BUDGET / STAGE_BYTES) < 4 ? (LDS_BUDGET / STAGE_BYTES) : 4;
-    static constexpr int AHEAD = NSTAGE - 1;                            // slices in flight besides the one being multiplied
-    static constexpr int NB = (TILE_R + TILE_C) / 64;                   // 1 KB blocks (8 rows) each wavefront brings per stage
-    static constexpr size_t LDS_BYTES = (size_t)NSTAGE * STAGE_BYTES + TILE_R * sizeof(float) + 4 * 64 * sizeof(double);
+// DT: PACT_BF16, or PACT_I8X3 for fp32 keys as three int8 planes.  STAGES: ring stages at most.
+template <int DT, int MI_, int NJ_, int WR_, int WC_, int STAGES> struct Shape {
+    static constexpr int MI = MI_, NJ = NJ_, WR = WR_, WC = WC_;
+    static constexpr int WAVES = WR * WC, THREADS = 64 * WAVES;
+    static constexpr int TILE_R = 32 * MI * WR, TILE_C = 32 * NJ * WC;
+    static constexpr bool I8 = DT == PACT_I8X3;
+    static constexpr int SLICE_BYTES = I8 ? 192 : 128;                   // bytes of each row per stage
+    static constexpr int STAGE_BYTES = (TILE_R + TILE_C) * SLICE_BYTES;  // A rows then B rows
+    static constexpr int NSTAGE = (LDS_BUDGET / STAGE_BYTES) < STAGES ? (LDS_BUDGET / STAGE_BYTES) : STAGES;
+    static constexpr int AHEAD = NSTAGE - 1;                             // slices in flight besides the one being multiplied
+    static constexpr int NB = STAGE_BYTES / 1024 / WAVES;                // 1 KB blocks each wavefront brings per stage
+    static constexpr int RINV_BYTES = TILE_R * sizeof(float);
     static_assert(NSTAGE >= 2, "the ring needs a slot to fill while another is multiplied");
+    static_assert(NB * 1024 * WAVES == STAGE_BYTES, "whole blocks per wavefront");
+    static_assert(!I8 || NB % 3 == 0, "16 rows of 192 bytes are three blocks");
+    static_assert((WAVES / 2) * NB * 1024 == TILE_R * SLICE_BYTES || !I8, "half of the wavefronts fetch the row operand");
+    // ring stages a launch needs: no more than there are slices (two at least: the epilogue uses one)
+    static size_t lds_bytes(int slices) {
+        const int st = slices < 2 ? 2 : slices < NSTAGE ? slices : NSTAGE;
+        return RINV_BYTES + (size_t)st * STAGE_BYTES;
+    }
 };
 
 typedef __attribute__((address_space(3))) char lds_char;
@@ -79,7 +103,6 @@ typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) u32x4_t lds_u32x4;
 typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
 typedef __attribute__((address_space(3))) u32x2_t lds_uint2;
-typedef __attribute__((address_space(3))) double lds_f64;
 constexpr int NEAR_BUF = 512;              // undecided pairs a wavefront buffers before reserving list slots (> 32)
 
 // 16 bytes per lane, global -> LDS at (lds_base + lane * 16); asynchronous, counted by vmcnt.
@@ -161,14 +184,14 @@ template <int N, int I = 0, class F> __device__ __forceinline__ void static_for(
     }
 }
 
-template <int DT> struct Mfma;
-template <> struct Mfma<PACT_BF16> {
-    __device__ static __forceinline__ void run(const u32x4_t& a, const u32x4_t& b, f32x16_t& c) {
-        c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, a),
-                                                    __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
-    }
-};
-template <> struct Mfma<PACT_F32X3> : Mfma<PACT_BF16> {};
+typedef __attribute__((ext_vector_type(4))) int i32x4_t;
+typedef __attribute__((ext_vector_type(16))) int i32x16_t;
+__device__ __forceinline__ void mfma_bf16(const u32x4_t& a, const u32x4_t& b, f32x16_t& c) {
+    c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
+}
+__device__ __forceinline__ void mfma_i8(const u32x4_t& a, const u32x4_t& b, i32x16_t& c) {
+    c = __builtin_amdgcn_mfma_i32_32x32x32_i8(__builtin_bit_cast(i32x4_t, a), __builtin_bit_cast(i32x4_t, b), c, 0, 0, 0);
+}
 
 // Density pass with t x t square tiles on g workgroups: do mirrored tiles (upper triangle only,
 // longer epilogue) save at least one turn in eight of a workgroup's tile loop?
@@ -177,12 +200,17 @@ __host__ __device__ __forceinline__ bool mirrored_tiles_pay(int t, int g) {
     return ((tri + g - 1) / g) * 9 < ((full + g - 1) / g) * 8;
 }
 
-template <int DT, int MODE, int MI, bool STAT, bool SYM>
-__global__ __launch_bounds__(512, 2) void gram_kernel(Batch bt, GramArgs ga) {
-    typedef Shape<MI> SH;
-    constexpr int TILE_R = SH::TILE_R, STAGE_BYTES = SH::STAGE_BYTES, NSTAGE = SH::NSTAGE;
-    constexpr int AHEAD = SH::AHEAD, NB = SH::NB, WROWS = 32 * MI;
-    extern __shared__ uint4 s_ring[];                         // NSTAGE stages, TILE_R floats, 256 doubles
+template <class SH, int MODE, bool STAT, bool SYM>
+__global__ __launch_bounds__(SH::THREADS, 2) void gram_kernel(Batch bt, GramArgs ga) {
+    constexpr int MI = SH::MI, NJ = SH::NJ, WC = SH::WC, WAVES = SH::WAVES;
+    constexpr int TILE_R = SH::TILE_R, TILE_C = SH::TILE_C, STAGE_BYTES = SH::STAGE_BYTES, NSTAGE = SH::NSTAGE;
+    constexpr int SLICE_BYTES = SH::SLICE_BYTES;
+    constexpr int AHEAD = SH::AHEAD, NB = SH::NB, WROWS = 32 * MI, WCOLS = 32 * NJ;
+    constexpr bool I8 = SH::I8;
+    static_assert(MODE == MODE_CAND || WCOLS == 64, "a wavefront's columns are one bitmap word");
+    static_assert(MODE == MODE_DENSITY || WROWS % 64 == 0, "a wavefront's rows are whole groups of 64 centres");
+    static_assert(!SYM || TILE_R == TILE_C, "mirrored tiles are square");
+    extern __shared__ uint4 s_ring[];                         // TILE_R floats, then the ring's stages
     // Which sample, which of its workgroups, and how many it has.  Batches: read from the map the
     // host made.  Workgroups are dealt to the 8 XCDs round-robin in launch order (XCD = workgroup
     // number mod 8) and every XCD has its own L2; the map gives a sample workgroups of one XCD
@@ -197,7 +225,8 @@ __global__ __launch_bounds__(512, 2) void gram_kernel(Batch bt, GramArgs ga) {
         G = ga.wg_count[b];
     }
     if (STAT && wg == 0)                                      // slots no workgroup of this sample writes
-        for (int k = threadIdx.x; k < (ga.stat_wgs - G) * 8; k += 512) ga.stat[((size_t)b * ga.stat_wgs + G) * 8 + k] = 0u;
+        for (int k = threadIdx.x; k < (ga.stat_wgs - G) * WAVES; k += SH::THREADS)
+            ga.stat[((size_t)b * ga.stat_wgs + G) * WAVES + k] = 0u;
     const Seg sg = bt.s[b];
     const int q_kept = clamp_count(ga.rep[b].n_kept, sg.n);
     // density pass: kept x kept; candidate pass: rows are the centres, columns the pruned tokens
@@ -206,7 +235,7 @@ __global__ __launch_bounds__(512, 2) void gram_kernel(Batch bt, GramArgs ga) {
     const int nB = (MODE == MODE_DENSITY) ? q_kept : clamp_count(ga.rep[b].n_pruned, sg.n - q_kept);
     if (nA <= 0 || nB <= 0) {
         if (STAT && (threadIdx.x & 63) == 0)
-            ga.stat[((size_t)b * ga.stat_wgs + wg) * 8 + (threadIdx.x >> 6)] = 0u;
+            ga.stat[((size_t)b * ga.stat_wgs + wg) * WAVES + (threadIdx.x >> 6)] = 0u;
         return;
     }
     const int tilesR = (nA + TILE_R - 1) / TILE_R;
@@ -215,31 +244,21 @@ __global__ __launch_bounds__(512, 2) void gram_kernel(Batch bt, GramArgs ga) {
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform: keep it scalar
-    const int wr = wave >> 2, wc = wave & 3;                      // 2 x 4 wavefronts of WROWS x 64
+    const int wr = wave / WC, wc = wave % WC;                     // WR x WC wavefronts of WROWS x WCOLS
 
-    lds_char* ring = (lds_char*)s_ring;
+    float* sRinv = (float*)s_ring;                                // [TILE_R]
+    lds_char* ring = (lds_char*)s_ring + SH::RINV_BYTES;
     const uint32_t ring_base = (uint32_t)(uintptr_t)ring;
-    float* sRinv = (float*)((char*)s_ring + NSTAGE * STAGE_BYTES);   // [TILE_R]
-    lds_f64* sRho = (lds_f64*)(ring + NSTAGE * STAGE_BYTES + TILE_R * sizeof(float));   // [4][64]
 
-    // A row is dk bf16 values; fp32 keys arrive as three such planes per token (hi, mid, lo:
-    // x = hi + mid + lo to 24 bits), each padded to whole 16-byte chunks.  Their product is then
-    // six passes over the key width, u.v = sum over the plane pairs below of plane_a(u).plane_b(v)
-    // (what is left out - mid.lo, lo.mid, lo.lo - is below 2^-23 |u||v|), smallest terms first:
-    // every fp32 rounding of the accumulator is relative to its size at that moment, so the
-    // five passes of small terms cost next to nothing in accuracy and the hi.hi pass at the end
-    // the same as a plain bf16 product.
-    constexpr bool SPLIT = DT == PACT_F32X3;
-    constexpr bool SHARE_RING = SPLIT && NSTAGE == 2;   // see the order of the slices below
-    const int row_bytes = SPLIT ? ((ga.dk + 7) & ~7) * 2 : ga.dk * Elem<PACT_BF16>::BYTES;   // of one plane
-    const int tok_bytes = SPLIT ? 3 * row_bytes : row_bytes;
-    const int spp = (row_bytes + SLICE_BYTES - 1) / SLICE_BYTES;                             // slices per plane
-    const int nSlices = SPLIT ? 6 * spp : spp;
+    // A row is dk bf16 values, or (fp32 keys) 192 bytes per 64 elements: 64 bytes of each of its three planes.
+    const int tok_bytes = I8 ? ((ga.dk + 63) >> 6) * 192 : ga.dk * Elem<PACT_BF16>::BYTES;
+    const int nSlices = (tok_bytes + SLICE_BYTES - 1) / SLICE_BYTES;
     const char* __restrict__ keys = ga.keys + (size_t)sg.base * tok_bytes;
     const int32_t* __restrict__ idxR = ga.idx_rows + sg.base;
     const int32_t* __restrict__ idxC = ga.idx_cols + sg.base;
     const float* __restrict__ rinv = ga.rinv + sg.base;
     uint64_t* adj = ga.adj + (size_t)b * bt.n_max * bt.W;
+    double* rho_b = (MODE == MODE_DENSITY) ? ga.rho + (size_t)b * bt.n_max : nullptr;
 
     // density constants: arg = cos * a - a = -(d / d_n) * log2(e); each of the two reciprocal norms
     // carries sqrt(a), so that the factor of a pair is the same product whichever token is the
@@ -250,9 +269,24 @@ __global__ __launch_bounds__(512, 2) void gram_kernel(Batch bt, GramArgs ga) {
     const float t_lo = (MODE == MODE_DENSITY) ? -(sg.d_c + ga.margin) * a_ : thr_cos - ga.margin;
     const float t_hi = -(sg.d_c - ga.margin) * a_;
 
-    // DMA roles: a stage is (TILE_R + 256) / 8 blocks of 1 KB (8 rows x 8 chunks), the A rows
-    // first; wavefront w brings blocks w*NB .. w*NB+NB-1.  Lane l of a block: row 8*blk + l/8,
-    // physical chunk l&7, which holds logical chunk (l&7) ^ ((row >> 1) & 7).
+    // fp32 keys: does a row of this sample need the order-3 products (see the head of this file)?
+    bool order3 = false;
+    if constexpr (I8) {
+        bool low = false;
+        for (int i = tid; i < sg.n; i += 8 * SH::THREADS) {
+            float v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = rinv[min(i + u * SH::THREADS, sg.n - 1)];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) low |= v[u] > ga.rinv_low;
+        }
+        order3 = __syncthreads_or(low);
+    }
+
+    // DMA roles: a stage is STAGE_BYTES / 1024 blocks of 1 KB, the A rows first; wavefront w brings
+    // blocks w*NB .. w*NB+NB-1.  bf16: a block is 8 rows x 8 chunks, lane l row 8*blk + l/8, physical
+    // chunk l&7, which holds logical chunk (l&7) ^ ((row >> 1) & 7).  fp32: three blocks are 16 rows x 12
+    // chunks; physical chunk c holds logical chunk c ^ ((row >> 2) & 3) (inside its plane's four).
     const uint32_t dma_lds0 = ring_base + (uint32_t)(wave * NB * 1024);
 
     // Tile order.  Workgroups are dealt to the 8 XCDs round-robin (XCD = workgroup id mod 8) and
@@ -290,11 +324,19 @@ __global__ __launch_bounds__(512, 2) void gram_kernel(Batch bt, GramArgs ga) {
         if constexpr (SYM) asm volatile("" : "+v"(tid_t));
         const int lane = tid_t & 63;
         const int l32_ = lane & 31, hh_ = lane >> 5;
-        const int dma_row0 = wave * NB * 8 + (lane >> 3);          // DMA: stage row of this lane in block k: + 8 * k
-        // fragment addressing: lane (l32, hh) reads chunk 2g+hh of row (its wave's row block) + l32
-        const int swz = (l32_ >> 1) & 7;
+        // stage row and logical chunk of this lane in block k
+        auto dma_row = [&](int k) __attribute__((always_inline)) {
+            if constexpr (I8) return (wave * (NB / 3) + k / 3) * 16 + ((k % 3) * 64 + lane) / 12;
+            else return wave * NB * 8 + (lane >> 3) + 8 * k;
+        };
+        auto dma_chunk = [&](int k) __attribute__((always_inline)) {
+            if constexpr (I8) return (((k % 3) * 64 + lane) % 12) ^ ((dma_row(k) >> 2) & 3);
+            else return (lane & 7) ^ ((dma_row(k) >> 1) & 7);
+        };
+        // fragment addressing: lane (l32, hh) reads chunks 2g+hh of row (its wave's row block) + l32
+        const int swz = I8 ? (l32_ >> 2) & 3 : (l32_ >> 1) & 7;
         const uint32_t fragA0 = (uint32_t)((wr * WROWS + l32_) * SLICE_BYTES);
-        const uint32_t fragB0 = (uint32_t)((TILE_R + wc * 64 + l32_) * SLICE_BYTES);
+        const uint32_t fragB0 = (uint32_t)((TILE_R + wc * WCOLS + l32_) * SLICE_BYTES);
 
         int tr = tl % tilesR, tc = tl / tilesR;
         if (patch) {
@@ -324,77 +366,51 @@ __global__ __launch_bounds__(512, 2) void gram_kernel(Batch bt, GramArgs ga) {
         uint32_t ro[NB];
 #pragma unroll
         for (int k = 0; k < NB; ++k) {
-            const int r = dma_row0 + 8 * k;
+            const int r = dma_row(k);
             const int tok = (r >= TILE_R) ? idxC[min(colBase + r - TILE_R, nB - 1)] : idxR[min(rowBase + r, nA - 1)];
-            // (with the lane's chunk: the swizzle term depends on the row only through
-            //  (row >> 1) & 7, and rows advance by 8 per block)
-            ro[k] = (uint32_t)tok * (uint32_t)tok_bytes + (uint32_t)(((lane & 7) ^ ((r >> 1) & 7)) * 16);
+            ro[k] = (uint32_t)tok * (uint32_t)tok_bytes + (uint32_t)(dma_chunk(k) * 16);
         }
         if (tid_t < TILE_R) sRinv[tid_t] = rinv[idxR[min(rowBase + tid_t, nA - 1)]] * sa_;
-        float rj_pre[2];                                    // 1/|u_j| of this lane's two columns (used in the epilogue)
+        float rj_pre[NJ];                                   // 1/|u_j| of this lane's columns (used in the epilogue)
 #pragma unroll
-        for (int j = 0; j < 2; ++j) rj_pre[j] = rinv[idxC[min(colBase + wc * 64 + j * 32 + l32_, nB - 1)]];
+        for (int j = 0; j < NJ; ++j) rj_pre[j] = rinv[idxC[min(colBase + wc * WCOLS + j * 32 + l32_, nB - 1)]];
 
-        // Order of the slices.  bf16 keys: along the key width.  fp32 keys (three planes): the five
-        // pairs of small terms first, then (hi,hi) along the key width (see above).  With two ring
-        // stages (256 x 256 tiles, where a wavefront fetches rows of one operand only) the small
-        // pairs of one slice of the key width follow each other so that each step changes one
-        // operand only - (hi,lo) (hi,mid) (mid,mid) (mid,hi) (lo,hi) - and the other half of the
-        // stage is reused instead of fetched again: the two halves of the ring then alternate
-        // independently (eight instead of twelve plane slices per slice of the key width).
-        constexpr bool SHARE = SHARE_RING;
-        static_assert(!SHARE || NB * 8 * 4 == TILE_R, "four wavefronts fetch the row operand, four the column operand");
-        int next_pass = 0, next_ks = 0;          // of the next slice to fetch (slices are fetched in order)
-        int slotA = 1, slotB = 1;                // SHARE: ring slot that holds the newest row / column operand
         auto issue = [&](int s) __attribute__((always_inline)) {      // slice s -> ring slot s % NSTAGE
-            const int pass = SPLIT ? next_pass : 0;   // SHARE: position in the group of five small pairs, 5 = (hi,hi)
-            const int ks = SPLIT ? next_ks : s;
-            uint32_t planeA, planeB;
-            bool fetchA = true, fetchB = true;
-            if constexpr (SHARE) {
-                planeA = (0x250u >> (2 * pass)) & 3;  planeB = (0x016u >> (2 * pass)) & 3;
-                fetchA = (0x35u >> pass) & 1;         fetchB = (0x2Bu >> pass) & 1;
-                if (pass == 5) { ++next_ks; }
-                else if (++next_pass == 5) { next_pass = 0; if (++next_ks == spp) { next_ks = 0; next_pass = 5; } }
-                slotA ^= fetchA ? 1 : 0;
-                slotB ^= fetchB ? 1 : 0;
-            } else {
-                // (hi,lo) (lo,hi) (mid,mid) (hi,mid) (mid,hi) (hi,hi), two bits per pass
-                planeA = (0x118u >> (2 * pass)) & 3;  planeB = (0x052u >> (2 * pass)) & 3;
-                if (SPLIT && ++next_ks == spp) { next_ks = 0; ++next_pass; }
-            }
-            const uint32_t offA = (uint32_t)(ks * SLICE_BYTES) + (SPLIT ? planeA * (uint32_t)row_bytes : 0u);
-            const uint32_t offB = (uint32_t)(ks * SLICE_BYTES) + (SPLIT ? planeB * (uint32_t)row_bytes : 0u);
-            const uint32_t ldsA = dma_lds0 + (uint32_t)((SHARE ? slotA : s % NSTAGE) * STAGE_BYTES);
-            const uint32_t ldsB = dma_lds0 + (uint32_t)((SHARE ? slotB : s % NSTAGE) * STAGE_BYTES);
-            if ((ks + 1) * SLICE_BYTES <= row_bytes) {
+            const uint32_t lds = dma_lds0 + (uint32_t)((s % NSTAGE) * STAGE_BYTES), off = (uint32_t)(s * SLICE_BYTES);
+            if (I8 || (s + 1) * SLICE_BYTES <= tok_bytes) {
                 // a whole slice: scalar base + (row offset + chunk) + slice offset, one add per block.
                 // (These instructions sit between the barrier and the first MFMA of every
                 //  wavefront, i.e. the matrix cores idle meanwhile: they are kept few.)
 #pragma unroll
-                for (int k = 0; k < NB; ++k) {
-                    const bool colRows = wave * NB * 8 + 8 * k >= TILE_R;          // (wave-uniform)
-                    if (colRows ? fetchB : fetchA)
-                        dma16_off(keys, ro[k] + (colRows ? offB : offA), (colRows ? ldsB : ldsA) + k * 1024);
-                }
+                for (int k = 0; k < NB; ++k) dma16_off(keys, ro[k] + off, lds + k * 1024);
             } else {
 #pragma unroll
                 for (int k = 0; k < NB; ++k) {
-                    const bool colRows = wave * NB * 8 + 8 * k >= TILE_R;
-                    const int chunk = (lane & 7) ^ (((dma_row0 + 8 * k) >> 1) & 7);
-                    const bool ok = ks * SLICE_BYTES + chunk * 16 < row_bytes;     // past the key width: zeros
-                    const char* src = ok ? keys + (ro[k] + (colRows ? offB : offA)) : ga.zeros;
-                    if (colRows ? fetchB : fetchA) dma16(src, (colRows ? ldsB : ldsA) + k * 1024);
+                    const bool ok = s * SLICE_BYTES + dma_chunk(k) * 16 < tok_bytes;     // past the key width: zeros
+                    const char* src = ok ? keys + (ro[k] + off) : ga.zeros;
+                    dma16(src, lds + k * 1024);
                 }
             }
         };
-        f32x16_t acc[MI][2];
+        f32x16_t acc[MI][NJ];
+        i32x16_t ord[I8 ? 4 : 1][MI][NJ];                   // fp32 keys: sums of the byte products, by order
+        if constexpr (I8) {
 #pragma unroll
-        for (int i = 0; i < MI; ++i)
+            for (int o = 0; o < 4; ++o)
 #pragma unroll
-            for (int j = 0; j < 2; ++j)
+                for (int i = 0; i < MI; ++i)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+                    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) ord[o][i][j][r] = 0;
+        } else {
+#pragma unroll
+            for (int i = 0; i < MI; ++i)
+#pragma unroll
+                for (int j = 0; j < NJ; ++j)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+        }
 
 #pragma unroll
         for (int s = 0; s < AHEAD; ++s)
@@ -406,51 +422,109 @@ __global__ __launch_bounds__(512, 2) void gram_kernel(Batch bt, GramArgs ga) {
             else wait_vmcnt<0>();
             __builtin_amdgcn_s_barrier();      // ... for every wavefront; and slot (s-1)%NSTAGE is free
 
-            // the fragments of k-group g+1 are read from LDS while the MFMAs of group g run
-            // (slotA / slotB still name the slots of this slice: the next fetch comes further down)
-            const lds_char* stA = ring + (SHARE ? slotA : s % NSTAGE) * STAGE_BYTES;
-            const lds_char* stB = ring + (SHARE ? slotB : s % NSTAGE) * STAGE_BYTES;
-            u32x4_t fa[2][MI], fb[2][2];
-            auto load_frags = [&](int g, int buf) __attribute__((always_inline)) {
-                const uint32_t co = (uint32_t)(((2 * g + hh_) ^ swz) << 4);
+            const lds_char* st = ring + (s % NSTAGE) * STAGE_BYTES;
+            if constexpr (I8) {
+                // two k-steps of 32 elements: the planes of MI + NJ fragment rows, then the byte products.
+                // (Eight wavefronts on four SIMDs: one reads while the other multiplies.)
+                if ((s & 511) == 511) {
+                    // rows of more than 32768 elements: carry into the higher orders before int32 can overflow (exact)
 #pragma unroll
-                for (int i = 0; i < MI; ++i) fa[buf][i] = *(const lds_u32x4*)(stA + fragA0 + i * 32 * SLICE_BYTES + co);
+                    for (int o = 3; o > 0; --o)
 #pragma unroll
-                for (int j = 0; j < 2; ++j) fb[buf][j] = *(const lds_u32x4*)(stB + fragB0 + j * 32 * SLICE_BYTES + co);
-            };
-            constexpr int MF = 1;                               // MFMA instructions per fragment pair
-            load_frags(0, 0);
-            __builtin_amdgcn_sched_group_barrier(0x100, MI + 2, 0);
-            // (the next fetches are issued while the first fragments are on their way from the LDS:
-            //  nothing else can fill the time between the barrier and the first MFMA)
-            if (s + AHEAD < nSlices) issue(s + AHEAD);
+                        for (int i = 0; i < MI; ++i)
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                if (g + 1 < 4) load_frags(g + 1, (g + 1) & 1);
+                            for (int j = 0; j < NJ; ++j)
 #pragma unroll
-                for (int i = 0; i < MI; ++i)
+                                for (int r = 0; r < 16; ++r) {
+                                    const int c = ord[o][i][j][r] >> 8;
+                                    ord[o][i][j][r] -= c * 256;
+                                    ord[o - 1][i][j][r] += c;
+                                }
+                }
 #pragma unroll
-                    for (int j = 0; j < 2; ++j) Mfma<DT>::run(fa[g & 1][i], fb[g & 1][j], acc[i][j]);
-                // issue order: the LDS reads of the next k-group go out one by one between the
-                // first MFMAs of this one (the scheduler would otherwise serialise read -> wait ->
-                // multiply on one set of fragment registers)
-                if (g + 1 < 4) {
+                for (int ks = 0; ks < 2; ++ks) {
+                    u32x4_t fa[MI][3], fb[NJ][3];
+                    const uint32_t co = (uint32_t)(((2 * ks + hh_) ^ swz) << 4);
 #pragma unroll
-                    for (int k = 0; k < MI + 2; ++k) {
-                        __builtin_amdgcn_sched_group_barrier(0x008, MF, 0);
-                        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+                    for (int pl = 0; pl < 3; ++pl) {
+#pragma unroll
+                        for (int i = 0; i < MI; ++i) fa[i][pl] = *(const lds_u32x4*)(st + fragA0 + i * 32 * SLICE_BYTES + pl * 64 + co);
+#pragma unroll
+                        for (int j = 0; j < NJ; ++j) fb[j][pl] = *(const lds_u32x4*)(st + fragB0 + j * 32 * SLICE_BYTES + pl * 64 + co);
                     }
-                    __builtin_amdgcn_sched_group_barrier(0x008, MF * (2 * MI - (MI + 2)), 0);
-                } else {
-                    __builtin_amdgcn_sched_group_barrier(0x008, MF * 2 * MI, 0);
+                    if (ks == 0 && s + AHEAD < nSlices) issue(s + AHEAD);
+#pragma unroll
+                    for (int o = 0; o < 3; ++o)
+#pragma unroll
+                        for (int pa = 0; pa <= o; ++pa)
+#pragma unroll
+                            for (int i = 0; i < MI; ++i)
+#pragma unroll
+                                for (int j = 0; j < NJ; ++j) mfma_i8(fa[i][pa], fb[j][o - pa], ord[o][i][j]);
+                    if (order3) {
+#pragma unroll
+                        for (int pa = 1; pa < 3; ++pa)
+#pragma unroll
+                            for (int i = 0; i < MI; ++i)
+#pragma unroll
+                                for (int j = 0; j < NJ; ++j) mfma_i8(fa[i][pa], fb[j][3 - pa], ord[3][i][j]);
+                    }
+                }
+            } else {
+                // the fragments of k-group g+1 are read from LDS while the MFMAs of group g run
+                u32x4_t fa[2][MI], fb[2][NJ];
+                auto load_frags = [&](int g, int buf) __attribute__((always_inline)) {
+                    const uint32_t co = (uint32_t)(((2 * g + hh_) ^ swz) << 4);
+#pragma unroll
+                    for (int i = 0; i < MI; ++i) fa[buf][i] = *(const lds_u32x4*)(st + fragA0 + i * 32 * SLICE_BYTES + co);
+#pragma unroll
+                    for (int j = 0; j < NJ; ++j) fb[buf][j] = *(const lds_u32x4*)(st + fragB0 + j * 32 * SLICE_BYTES + co);
+                };
+                load_frags(0, 0);
+                __builtin_amdgcn_sched_group_barrier(0x100, MI + NJ, 0);
+                // (the next fetches are issued while the first fragments are on their way from the LDS:
+                //  nothing else can fill the time between the barrier and the first MFMA)
+                if (s + AHEAD < nSlices) issue(s + AHEAD);
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    if (g + 1 < 4) load_frags(g + 1, (g + 1) & 1);
+#pragma unroll
+                    for (int i = 0; i < MI; ++i)
+#pragma unroll
+                        for (int j = 0; j < NJ; ++j) mfma_bf16(fa[g & 1][i], fb[g & 1][j], acc[i][j]);
+                    // issue order: the LDS reads of the next k-group go out one by one between the
+                    // first MFMAs of this one (the scheduler would otherwise serialise read -> wait ->
+                    // multiply on one set of fragment registers)
+                    if (g + 1 < 4) {
+#pragma unroll
+                        for (int k = 0; k < MI + NJ; ++k) {
+                            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+                        }
+                        if constexpr (NJ * MI > MI + NJ) __builtin_amdgcn_sched_group_barrier(0x008, NJ * MI - (MI + NJ), 0);
+                    } else {
+                        __builtin_amdgcn_sched_group_barrier(0x008, NJ * MI, 0);
+                    }
                 }
             }
         }
-        // LDS the epilogue may use for its buffers: the ring stage that the last slice did not
-        // occupy; where the two halves of the ring alternate independently the last slice may
-        // occupy halves of both, so there every wavefront finishes its reads first.
-        const int freeStage = SHARE_RING ? 0 : (nSlices % NSTAGE);
-        if constexpr (SHARE_RING) __builtin_amdgcn_s_barrier();
+        if constexpr (I8) {
+            // in units of 65536 (the reciprocal norms carry the scale); order 0 is exact in fp32 up to rows of 1040 elements
+#pragma unroll
+            for (int i = 0; i < MI; ++i)
+#pragma unroll
+                for (int j = 0; j < NJ; ++j)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) {
+                        float v = (float)ord[2][i][j][r];
+                        if (order3) v = fmaf((float)ord[3][i][j][r], 1.0f / 256.0f, v);
+                        v = fmaf((float)ord[1][i][j][r], 256.0f, v);
+                        acc[i][j][r] = fmaf((float)ord[0][i][j][r], 65536.0f, v);
+                    }
+        }
+        // LDS the epilogue may use for its buffers: a ring stage that the last slice did not occupy
+        // (one of the first two: a launch with few slices has no others)
+        const int freeStage = (nSlices - 1) % NSTAGE == 0 ? 1 : 0;
 
         // ------------------------------------------------------------------ epilogue
         // acc[i][j][r] holds row  rowBase + wr*WROWS + i*32 + 8*(r/4) + 4*hh + (r%4)
@@ -459,14 +533,14 @@ __global__ __launch_bounds__(512, 2) void gram_kernel(Batch bt, GramArgs ga) {
         //  arithmetic below is not hoisted out of the tile loop into long-lived registers)
         int l32 = l32_, hh = hh_;
         asm volatile("" : "+v"(l32), "+v"(hh));
-        const int colW = colBase + wc * 64;                 // first column of this wave, multiple of 64
+        const int colW = colBase + wc * WCOLS;              // first column of this wave (density pass: multiple of 64)
         const int wordIdx = colW >> 6;
         const int rowW = rowBase + wr * WROWS;
-        float rj[2];
-        int colP[2];
-        uint64_t laneOk[2];                                 // lanes whose column exists
+        float rj[NJ];
+        int colP[NJ];
+        uint64_t laneOk[NJ];                                // lanes whose column exists
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
+        for (int j = 0; j < NJ; ++j) {
             colP[j] = colW + j * 32 + l32;
             rj[j] = rj_pre[j] * sa_;
             laneOk[j] = __ballot(colP[j] < nB);
@@ -475,8 +549,6 @@ __global__ __launch_bounds__(512, 2) void gram_kernel(Batch bt, GramArgs ga) {
         // per-wavefront buffer of undecided pairs, in a ring slot no wavefront reads any more
         lds_uint2* nearBuf = (lds_uint2*)(ring + freeStage * STAGE_BYTES + wave * (NEAR_BUF * 8));
         int nearN = 0;
-        // mirrored tiles: the wavefronts' row sums (128 rows x 64 columns each), behind the pair buffers
-        lds_f64* rowBuf = (lds_f64*)(ring + freeStage * STAGE_BYTES + 8 * (NEAR_BUF * 8));
         auto flush_near = [&]() __attribute__((always_inline)) {
             int base_slot = 0;
             // (one 64-bit atomic: slots in the low word, ordered pairs in the high word)
@@ -515,7 +587,7 @@ __global__ __launch_bounds__(512, 2) void gram_kernel(Batch bt, GramArgs ga) {
                     for (int r = 0; r < 16; ++r)
                         rs[i2][r] = sRinv[wr * WROWS + gi * 64 + i2 * 32 + 8 * (r >> 2) + 4 * hh + (r & 3)];
 #pragma unroll
-                for (int j = 0; j < 2; ++j) {
+                for (int j = 0; j < NJ; ++j) {
                     float lb = -INFINITY;
 #pragma unroll
                     for (int i2 = 0; i2 < 2; ++i2)
@@ -608,7 +680,8 @@ __global__ __launch_bounds__(512, 2) void gram_kernel(Batch bt, GramArgs ga) {
                         d[0] += swizzle_xor<2>(d[0]);
                         d[0] += swizzle_xor<1>(d[0]);
                         // rows r4 .. r4+3 of this lane are rows 2 r4 + 4 hh + (0..3) of the block
-                        if ((l32 & 7) == 0) rowBuf[wave * 128 + i * 32 + 2 * r4 + 4 * hh + (l32 >> 3)] = d[0];
+                        const int gRow = rowI + 2 * r4 + 4 * hh + (l32 >> 3);
+                        if ((l32 & 7) == 0 && gRow < nA) unsafeAtomicAdd(&rho_b[gRow], d[0]);
                         if (r4 == 4) __builtin_amdgcn_sched_barrier(0);     // two groups at a time may overlap their exchanges
                     });
                 } else {
@@ -705,41 +778,22 @@ __global__ __launch_bounds__(512, 2) void gram_kernel(Batch bt, GramArgs ga) {
             }
         }
         }
-        if (MODE == MODE_DENSITY && nearN > 0) flush_near();
 
         if (MODE == MODE_DENSITY) {
-            // column sums over this wave's rows: combine the two half-waves; one row of partials
-            // covers GRAM_RHO_ROWS = 128 kept rows, i.e. one wavefront row (MI = 4) or both (MI = 2)
-            static_assert(GRAM_RHO_ROWS == 128, "the density partials are per 128 kept rows");
-            double tot[2];
+            // Column sums over this wave's rows: combine the two half-waves, then add them to the
+            // densities.  The fp64 additions of these fp32 terms are exact for d_n >= 0.21 (24 bits of a
+            // term down to exp(-2 / d_n), 2^15 of them), so their order does not matter; below that the
+            // last bit of a density may depend on it, far inside the band that is re-evaluated.
+            // (131 072 such additions, one image's, take 0.1 us more than as many plain stores of partial
+            // sums, which another kernel would have to add up.)
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
                 const double part = rho[j][0] + rho[j][1];
-                tot[j] = part + __shfl_xor(part, 32, 64);
+                const double tot = part + __shfl_xor(part, 32, 64);
+                if (hh == j && rowW < nA && colP[j] < nB) unsafeAtomicAdd(&rho_b[colP[j]], tot);
             }
-            if (MI == 2) {
-                if (wr == 1 && hh == 0) { sRho[wc * 64 + l32] = tot[0]; sRho[wc * 64 + 32 + l32] = tot[1]; }
-                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-                __builtin_amdgcn_s_barrier();
-                if (wr == 0 && hh == 0) { tot[0] += sRho[wc * 64 + l32]; tot[1] += sRho[wc * 64 + 32 + l32]; }
-            }
-            const int rt = (MI == 4) ? (rowBase / GRAM_RHO_ROWS) + wr : rowBase / GRAM_RHO_ROWS;
-            double* out = ga.rho_part + ((size_t)b * bt.W + rt) * bt.n_max;
-            const bool writer = hh == 0 && (MI == 4 ? rowW < nA : wr == 0);
-#pragma unroll
-            for (int j = 0; j < 2; ++j)
-                if (writer && colP[j] < nB) out[colP[j]] = tot[j];
         }
-        if (MODE == MODE_DENSITY && mirror) {
-            // row sums: two wavefronts side by side cover the 128 columns of one row of partials
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-            __builtin_amdgcn_s_barrier();
-            const int half = tid_t >> 8, pair = (tid_t >> 7) & 1, row = tid_t & 127;
-            const double v = rowBuf[(half * 4 + pair * 2) * 128 + row] + rowBuf[(half * 4 + pair * 2 + 1) * 128 + row];
-            const int gRow = rowBase + half * 128 + row;
-            if (gRow < nA && colBase + pair * 128 < nB)
-                ga.rho_part[((size_t)b * bt.W + colBase / GRAM_RHO_ROWS + pair) * bt.n_max + gRow] = v;
-        }
+        if (MODE == MODE_DENSITY && nearN > 0) flush_near();
         if (tl + t_step < l_hi) {
             // the ring and sRinv are rewritten by the next tile: every wavefront must be done with
             // them (and the slice loop's vmcnt arithmetic assumes nothing older is outstanding)
@@ -752,12 +806,12 @@ __global__ __launch_bounds__(512, 2) void gram_kernel(Batch bt, GramArgs ga) {
         // than the kernel); the kernel that finishes the densities takes the minimum
 #pragma unroll
         for (int sft = 32; sft >= 1; sft >>= 1) far = fminf(far, __shfl_xor(far, sft, 64));
-        if (lane == 0) ga.stat[((size_t)b * ga.stat_wgs + wg) * 8 + wave] = far < 0.0f ? __float_as_uint(far) : 0u;
+        if (lane == 0) ga.stat[((size_t)b * ga.stat_wgs + wg) * WAVES + wave] = far < 0.0f ? __float_as_uint(far) : 0u;
     }
 }
 
 // One sample: a workgroup per tile, at most one per CU, a multiple of the 8 XCDs (see the tile order).
-static int gram_grid_x(const Batch& bt, long tiles) {
+static int gram_grid_x(long tiles) {
     long grid_x = tiles;
     static_assert(GRAM_MAX_WORKGROUPS == 256, "one workgroup per CU, 256 CUs");
     if (grid_x > GRAM_MAX_WORKGROUPS) grid_x = GRAM_MAX_WORKGROUPS;
@@ -819,23 +873,23 @@ static int build_wg_map(int B, const long* tiles, GramArgs& ga) {
     return most;
 }
 
-template <int MODE, int MI, bool STAT, bool SYM>
-static int launch_gram_shape(const Batch& bt, const GramArgs& ga_in, pact_dtype k_dt, hipStream_t st,
-                             const char* name, int* grid_out) {
-    typedef Shape<MI> SH;
-    const int tilesR = (bt.n_max + SH::TILE_R - 1) / SH::TILE_R, tilesC = (bt.n_max + TILE_C - 1) / TILE_C;
+static long kept_estimate(const Seg& sg) { return sg.n - prune_rank(sg.lambda, sg.n); }
+
+template <class SH, int MODE, bool STAT, bool SYM>
+static int launch_gram_shape(const Batch& bt, const GramArgs& ga_in, hipStream_t st, const char* name, int* stat_words) {
+    const int tilesR = (bt.n_max + SH::TILE_R - 1) / SH::TILE_R, tilesC = (bt.n_max + SH::TILE_C - 1) / SH::TILE_C;
     GramArgs ga = ga_in;
-    int grid_x = gram_grid_x(bt, (long)tilesR * tilesC);
+    int grid_x = gram_grid_x((long)tilesR * tilesC);
     dim3 grid(grid_x, 1);
     ga.mapped = bt.B > 1;
     if (ga.mapped) {
         // tiles a sample is expected to have: kept tokens n - floor(lambda n); density pass
-        // kept x kept (square tiles: the triangle); candidate pass about kept / 2 centres x pruned
+        // kept x kept (mirrored: the triangle); candidate pass about kept / 2 centres x pruned
         long tiles[PACT_MAX_BATCH];
         for (int b = 0; b < bt.B; ++b) {
-            const long n = bt.s[b].n, q = n - (long)floorf(bt.s[b].lambda * (float)n);
+            const long n = bt.s[b].n, q = kept_estimate(bt.s[b]);
             const long rows = (MODE == MODE_DENSITY) ? q : (q + 1) / 2, cols = (MODE == MODE_DENSITY) ? q : n - q;
-            const long tr = (rows + SH::TILE_R - 1) / SH::TILE_R, tc = (cols + TILE_C - 1) / TILE_C;
+            const long tr = (rows + SH::TILE_R - 1) / SH::TILE_R, tc = (cols + SH::TILE_C - 1) / SH::TILE_C;
             tiles[b] = (MODE == MODE_DENSITY && SYM) ? tr * (tr + 1) / 2 : tr * tc;
             if (tiles[b] < 1) tiles[b] = 1;
         }
@@ -843,87 +897,93 @@ static int launch_gram_shape(const Batch& bt, const GramArgs& ga_in, pact_dtype 
         grid = dim3(GRAM_MAX_WORKGROUPS, 1);
     }
     ga.stat_wgs = grid_x;
-    if (grid_out) *grid_out = grid_x;
-    const size_t lds = SH::LDS_BYTES;
-    static bool raised[2] = {false, false};
-    const int di = k_dt == PACT_BF16 ? 1 : 0;
-    const void* fn = (k_dt == PACT_BF16) ? (const void*)gram_kernel<PACT_BF16, MODE, MI, STAT, SYM>
-                                         : (const void*)gram_kernel<PACT_F32X3, MODE, MI, STAT, SYM>;
-    if (!raised[di]) {
-        if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+    if (stat_words) *stat_words = STAT ? grid_x * SH::WAVES : 0;
+    const int tok_bytes = SH::I8 ? ((ga.dk + 63) / 64) * 192 : ga.dk * 2;
+    const size_t lds = SH::lds_bytes((tok_bytes + SH::SLICE_BYTES - 1) / SH::SLICE_BYTES);
+    static size_t raised = 0;
+    if (lds > raised) {
+        if (hipFuncSetAttribute((const void*)gram_kernel<SH, MODE, STAT, SYM>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                (int)SH::lds_bytes(1 << 20)) != hipSuccess)
             return PACT_ERR_HIP;
-        raised[di] = true;
+        raised = SH::lds_bytes(1 << 20);
     }
-    if (k_dt == PACT_BF16)
-        PACT_LAUNCH_SHMEM(name, (gram_kernel<PACT_BF16, MODE, MI, STAT, SYM>), grid, dim3(512), lds, st, bt, ga);
-    else
-        PACT_LAUNCH_SHMEM(name, (gram_kernel<PACT_F32X3, MODE, MI, STAT, SYM>), grid, dim3(512), lds, st, bt, ga);
+    PACT_LAUNCH_SHMEM(name, (gram_kernel<SH, MODE, STAT, SYM>), grid, dim3(SH::THREADS), lds, st, bt, ga);
     return PACT_OK;
 }
 
-// 256 x 256 tiles when there are enough of them to occupy the chip, else 128 x 256.
-// mirrored: the kernel build that can let the tiles above the diagonal stand for those below
-// (it decides per sample, from the count of kept tokens it finds, whether to do so).
-template <int MODE>
-static int launch_gram(const Batch& bt, const GramArgs& ga, pact_dtype k_dt, hipStream_t st,
-                       const char* name, long tiles256, bool mirrored, int* grid_out) {
+// The tiles.  256 x 256 has the best ratio of flops to bytes fetched, but its launch lasts as long as a
+// tile (23 us at a key width of 512) however few there are.
+typedef Shape<PACT_BF16, 4, 2, 2, 4, 2> Tile256;
+typedef Shape<PACT_BF16, 2, 2, 2, 4, 3> Tile128x256;
+typedef Shape<PACT_BF16, 2, 2, 2, 2, 4> Tile128;
+typedef Shape<PACT_I8X3, 1, 2, 4, 2, 3> TileI8;         // density pass
+typedef Shape<PACT_I8X3, 2, 1, 2, 4, 3> TileI8Cand;     // candidate pass (groups of 64 rows)
+
+template <class SH, int MODE>
+static int launch_gram(const Batch& bt, const GramArgs& ga, hipStream_t st, const char* name, bool mirrored, bool want_stat,
+                       int* stat_words) {
+    if constexpr (MODE == MODE_DENSITY) {
+        if constexpr (SH::TILE_R == SH::TILE_C) {
+            if (mirrored) return want_stat ? launch_gram_shape<SH, MODE, true, true>(bt, ga, st, name, stat_words)
+                                           : launch_gram_shape<SH, MODE, false, true>(bt, ga, st, name, stat_words);
+        }
+        if (want_stat) return launch_gram_shape<SH, MODE, true, false>(bt, ga, st, name, stat_words);
+    }
+    return launch_gram_shape<SH, MODE, false, false>(bt, ga, st, name, stat_words);
+}
+
+static int gram_args(GramArgs& ga, const Batch& bt, const Ws& w, const void* keys, pact_dtype k_dt, int32_t dk,
+                     const int32_t* idx_rows, const int32_t* idx_cols, const pact_report* rep) {
+    // (fp32 keys: their int8 planes)
+    ga.keys = (k_dt == PACT_F32) ? (const char*)w.ksplit : (const char*)keys;
+    ga.dk = dk; ga.idx_rows = idx_rows; ga.idx_cols = idx_cols; ga.rep = rep;
+    ga.rinv = w.rinv; ga.zeros = (const char*)w.zeros; ga.adj = w.adj;
+    ga.margin = (float)cos_margin(dk, k_dt);
+    ga.rinv_low = 256.0f / (23726566.0f * powf((float)dk / 512.0f, 0.25f));    // |X| = 2^24.5 (dk / 512)^(1/4)
     if (!ga.keys || !ga.idx_rows || !ga.idx_cols || !ga.rep || !ga.rinv || !ga.zeros || !ga.adj || ga.dk < 1)
         return PACT_ERR_NULL;                     // (an argument block that was not filled in completely)
     // the kernel addresses a sample's key rows with 32-bit byte offsets
-    const uint64_t tok_bytes = (k_dt == PACT_F32) ? 3ull * (((uint64_t)ga.dk + 7) & ~7ull) * 2 : (uint64_t)ga.dk * 2;
-    if ((uint64_t)bt.n_max * tok_bytes > 0xFFFFFFFFull) return PACT_ERR_SHAPE;
-    const bool big = tiles256 * bt.B >= 256;
-    if constexpr (MODE == MODE_DENSITY) {
-        if (ga.stat) {                            // with the key-distance statistic
-            if (big && mirrored) return launch_gram_shape<MODE, 4, true, true>(bt, ga, k_dt, st, name, grid_out);
-            if (big) return launch_gram_shape<MODE, 4, true, false>(bt, ga, k_dt, st, name, grid_out);
-            return launch_gram_shape<MODE, 2, true, false>(bt, ga, k_dt, st, name, grid_out);
-        }
-        if (big && mirrored) return launch_gram_shape<MODE, 4, false, true>(bt, ga, k_dt, st, name, grid_out);
-    }
-    if (big) return launch_gram_shape<MODE, 4, false, false>(bt, ga, k_dt, st, name, grid_out);
-    return launch_gram_shape<MODE, 2, false, false>(bt, ga, k_dt, st, name, grid_out);
+    if ((uint64_t)bt.n_max * gram_token_bytes(dk, k_dt) > 0xFFFFFFFFull) return PACT_ERR_SHAPE;
+    return PACT_OK;
 }
 
 int launch_gram_density(const Batch& bt, const Ws& w, const void* keys, pact_dtype k_dt, int32_t dk,
                         const int32_t* idx, pact_report* rep, bool want_stat, int* stat_words, hipStream_t st) {
     GramArgs ga = {};
-    // (fp32 keys: their three bf16 planes)
-    ga.keys = (k_dt == PACT_F32) ? (const char*)w.ksplit : (const char*)keys;
-    ga.dk = dk; ga.idx_rows = idx; ga.idx_cols = idx; ga.rep = rep;
-    ga.rinv = w.rinv; ga.zeros = (const char*)w.zeros; ga.adj = w.adj; ga.cbest = nullptr; ga.rho_part = w.rho_part;
-    ga.near_list = w.near_list; ga.near_cnt = w.near_cnt; ga.stat = want_stat ? w.stat : nullptr; ga.margin = (float)cos_margin(dk);
-    const long t1 = (bt.n_max + 255) / 256;
+    if (const int rc = gram_args(ga, bt, w, keys, k_dt, dk, idx, idx, rep)) return rc;
+    ga.rho = w.rho; ga.near_list = w.near_list; ga.near_cnt = w.near_cnt; ga.stat = want_stat ? w.stat : nullptr;
+    const char* name = "gram_density";
     // The count of kept tokens is known on the device only; what the percentile will leave
     // (n - floor(lambda n), more on ties) tells whether mirrored tiles are likely to pay for
     // some sample.  The kernel decides again from the real count, so a wrong guess costs time only.
     // (In a batch every sample has its own number of workgroups: the build that can mirror is
     //  used there whenever the tiles are square.)
-    bool mirrored = bt.B > 1;
-    const int gx = gram_grid_x(bt, t1 * t1);
-    for (int b = 0; b < bt.B; ++b) {
-        const int q_est = bt.s[b].n - (int)floorf(bt.s[b].lambda * (float)bt.s[b].n);
-        mirrored = mirrored || mirrored_tiles_pay((q_est + 255) / 256, gx);
-    }
-    int grid_x = 0;
-    const int rc = launch_gram<MODE_DENSITY>(bt, ga, k_dt, st, "gram_density", t1 * t1, mirrored, &grid_x);
-    if (stat_words) *stat_words = want_stat ? grid_x * 8 : 0;
-    return rc;
+    auto mirrored = [&](int tile) {
+        const long t = (bt.n_max + tile - 1) / tile;
+        bool m = bt.B > 1;
+        for (int b = 0; b < bt.B; ++b)
+            m = m || mirrored_tiles_pay((int)((kept_estimate(bt.s[b]) + tile - 1) / tile), gram_grid_x(t * t));
+        return m;
+    };
+    if (k_dt == PACT_F32) return launch_gram<TileI8, MODE_DENSITY>(bt, ga, st, name, mirrored(128), want_stat, stat_words);
+    const long t1 = (bt.n_max + 255) / 256;
+    if (t1 * t1 * bt.B >= 256) return launch_gram<Tile256, MODE_DENSITY>(bt, ga, st, name, mirrored(256), want_stat, stat_words);
+    return launch_gram<Tile128x256, MODE_DENSITY>(bt, ga, st, name, false, want_stat, stat_words);
 }
 
 int launch_gram_candidates(const Batch& bt, const Ws& w, const void* keys, pact_dtype k_dt, int32_t dk,
                            const int32_t* pruned_idx, const int32_t* center_idx, pact_report* rep,
                            hipStream_t st) {
     GramArgs ga = {};
-    ga.keys = (k_dt == PACT_F32) ? (const char*)w.ksplit : (const char*)keys;
-    ga.dk = dk; ga.idx_rows = center_idx; ga.idx_cols = pruned_idx;
-    ga.rep = rep; ga.rinv = w.rinv; ga.zeros = (const char*)w.zeros; ga.adj = w.adj; ga.cbest = w.cbest;
-    ga.rho_part = nullptr;
-    ga.near_list = nullptr; ga.near_cnt = nullptr; ga.stat = nullptr; ga.margin = (float)cos_margin(dk);
+    if (const int rc = gram_args(ga, bt, w, keys, k_dt, dk, center_idx, pruned_idx, rep)) return rc;
+    ga.cbest = w.cbest;
+    const char* name = "gram_candidates";
+    if (k_dt == PACT_F32) return launch_gram<TileI8Cand, MODE_CAND>(bt, ga, st, name, false, false, nullptr);
     // rows: the centres, columns: the pruned tokens; neither count is known on the host, a
     // typical split (half pruned, a third of the rest centres) sizes the choice
     const long tr = (bt.n_max / 6 + 255) / 256, tc = (bt.n_max / 2 + 255) / 256;
-    return launch_gram<MODE_CAND>(bt, ga, k_dt, st, "gram_candidates", tr * tc, false, nullptr);
+    if (tr * tc * bt.B >= 256) return launch_gram<Tile256, MODE_CAND>(bt, ga, st, name, false, false, nullptr);
+    return launch_gram<Tile128x256, MODE_CAND>(bt, ga, st, name, false, false, nullptr);
 }
 
 int plan_gram_workgroups(const int32_t* tiles, int32_t batch, uint16_t* wg_map, uint16_t* wg_count) {

@@ -4,6 +4,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <math.h>
 #include <stddef.h>
 #include <stdint.h>
 
@@ -34,7 +35,6 @@ struct Batch {
 constexpr int QG_CHUNKS = 512;        // row chunks of the global-query column sum
 constexpr int SCORE_TOK_PER_WG = 16;  // tokens (= wavefronts) per workgroup in the logits kernel
 constexpr int PRED_CAP = 64;          // 16-bit slots per kept token: slot 0 = count, then up to 63 preceding neighbours
-constexpr int GRAM_RHO_ROWS = 128;    // kept rows summed into one row of the density partials
 constexpr int GRAM_MAX_WORKGROUPS = 256; // workgroups of 8 wavefronts per sample in a Gram pass (one per CU)
 constexpr int NEAR_CAP = 1 << 16;     // near-threshold pairs kept for fp64 re-evaluation, per sample
 constexpr uint32_t NEAR_MIRROR = 0x80000000u;   // flag in a listed pair's row: the pair (col, row) is meant as well
@@ -55,10 +55,9 @@ struct WsLayout {
     size_t ident;                                      // identity index list (idx == NULL)
     size_t adj;                                        // [B][n_max][W] u64: rows < q adjacency; from row q on: candidate words [Wc][n_pruned]
     size_t cbest;                                      // [B][W][n_max] f32: largest cosine per (group of 64 centres, pruned token)
-    size_t rho_part;                                   // [B][W][n_max] f64
     size_t rho, rank, status, cnum, cmask;             // per sample, pitch n_max (cmask: W)
     size_t preds, heads;                               // [B][n_max][PRED_CAP] u16, [B][n_max] 4 x u16 (count + first 3)
-    size_t ksplit;                                     // [total][3][dk rounded up to 8] bf16: fp32 clustering keys as three bf16 parts
+    size_t ksplit;                                     // [total][dk/64 rounded up][3][64] int8: fp32 clustering keys as three int8 planes
     size_t near_list, near_cnt, stat;                  // refine list, counter; [B][workgroups * 8] most negative density exponent seen
     size_t tie_list, tie_cnt;                          // [B][RHO_RECHECK_MAX] kept positions whose density is re-evaluated; [B][4]: count, ticket
     size_t rho_fix;                                    // [B][min(RHO_RECHECK_MAX, n_max)][ceil(n_max / RHO_RECHECK_CHUNK)][2] f64 partial sums of those
@@ -73,8 +72,12 @@ inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 __host__ __device__ inline int64_t rho_fix_tokens(int64_t n_max) { return n_max < RHO_RECHECK_MAX ? n_max : RHO_RECHECK_MAX; }
 __host__ __device__ inline int64_t rho_fix_chunks(int64_t n_max) { return (n_max + RHO_RECHECK_CHUNK - 1) / RHO_RECHECK_CHUNK; }
 
+// Bytes of one token's clustering key as the Gram passes read it: bf16 as it is, fp32 as three int8
+// planes, 192 bytes per 64 elements (padded with zeros).
+inline size_t gram_token_bytes(int64_t dk, int k_dt) { return k_dt == PACT_F32 ? (size_t)((dk + 63) / 64) * 192 : (size_t)dk * 2; }
+
 // dk: width of the clustering keys (0 for calls that run no Gram pass); k_dt: their type (only
-// fp32 keys have a three-part bf16 copy)
+// fp32 keys have a copy)
 inline WsLayout make_layout(int64_t n_max, int64_t B, int64_t total, int64_t qcols, int64_t n_q, int64_t dk,
                             int k_dt) {
     WsLayout L;
@@ -92,7 +95,6 @@ inline WsLayout make_layout(int64_t n_max, int64_t B, int64_t total, int64_t qco
     L.ident = take(sizeof(int32_t) * total);
     L.adj = take(sizeof(uint64_t) * B * n_max * W);
     L.cbest = take(sizeof(float) * B * W * n_max);
-    L.rho_part = take(sizeof(double) * B * W * n_max);
     L.rho = take(sizeof(double) * B * n_max);
     L.rank = take(sizeof(int32_t) * B * n_max);
     L.status = take(sizeof(uint32_t) * B * n_max);
@@ -112,7 +114,7 @@ inline WsLayout make_layout(int64_t n_max, int64_t B, int64_t total, int64_t qco
     L.slots = take(sizeof(int32_t) * total * MERGE_SLOTS);
     L.worklist = take(n_max > RESOLVE_LDS_TOKENS ? 16 * B * n_max : 0);
     L.zeros = take(256);
-    L.ksplit = take(k_dt == PACT_F32 ? sizeof(uint16_t) * 3 * total * ((dk + 7) / 8 * 8) : 0);   // planes padded to whole 16-byte chunks
+    L.ksplit = take(k_dt == PACT_F32 ? total * gram_token_bytes(dk, k_dt) : 0);
     L.total = off;
     return L;
 }
@@ -121,10 +123,10 @@ inline WsLayout make_layout(int64_t n_max, int64_t B, int64_t total, int64_t qco
 struct Ws {
     double* qg_part; double* qg; double* logits; double* hnorm; double* sm_part;
     double* nn; float* rinv; int32_t* ident;
-    uint64_t* adj; float* cbest; double* rho_part; double* rho; int32_t* rank; uint32_t* status;
+    uint64_t* adj; float* cbest; double* rho; int32_t* rank; uint32_t* status;
     int32_t* cnum; uint64_t* cmask; uint16_t* preds; uint2* heads; uint32_t* near_list; int32_t* near_cnt; uint32_t* stat;
     int32_t* tie_list; int32_t* tie_cnt; double* rho_fix;
-    int32_t* offsets; int32_t* members; int32_t* big; int32_t* slots; uint2* worklist; uint32_t* zeros; uint16_t* ksplit;
+    int32_t* offsets; int32_t* members; int32_t* big; int32_t* slots; uint2* worklist; uint32_t* zeros; char* ksplit;
 };
 
 inline Ws resolve(void* base, const WsLayout& L) {
@@ -134,7 +136,7 @@ inline Ws resolve(void* base, const WsLayout& L) {
     w.logits = (double*)(p + L.logits); w.hnorm = (double*)(p + L.hnorm);
     w.sm_part = (double*)(p + L.sm_part);
     w.nn = (double*)(p + L.nn); w.rinv = (float*)(p + L.rinv); w.ident = (int32_t*)(p + L.ident);
-    w.adj = (uint64_t*)(p + L.adj); w.cbest = (float*)(p + L.cbest); w.rho_part = (double*)(p + L.rho_part);
+    w.adj = (uint64_t*)(p + L.adj); w.cbest = (float*)(p + L.cbest);
     w.rho = (double*)(p + L.rho); w.rank = (int32_t*)(p + L.rank);
     w.status = (uint32_t*)(p + L.status); w.cnum = (int32_t*)(p + L.cnum);
     w.preds = (uint16_t*)(p + L.preds); w.heads = (uint2*)(p + L.heads);
@@ -144,7 +146,7 @@ inline Ws resolve(void* base, const WsLayout& L) {
     w.rho_fix = (double*)(p + L.rho_fix);
     w.offsets = (int32_t*)(p + L.offsets); w.big = (int32_t*)(p + L.big);
     w.members = (int32_t*)(p + L.members); w.slots = (int32_t*)(p + L.slots); w.worklist = (uint2*)(p + L.worklist); w.zeros = (uint32_t*)(p + L.zeros);
-    w.ksplit = (uint16_t*)(p + L.ksplit);
+    w.ksplit = p + L.ksplit;
     return w;
 }
 
@@ -220,14 +222,17 @@ __host__ __device__ inline int prune_rank(float lambda, int n) {
 
 enum { INIT_REDUCE = 0, INIT_DBDPC_ALL = 1, INIT_DBDPC_SUBSET = 2, INIT_REINC = 3, INIT_SCORE = 4 };
 
-// Worst-case rounding error of an fp32-accumulated matrix-core cosine of two dk-long rows, plus
-// slack for the scaling multiplies and, for fp32 keys, for what their three-part bf16 form
-// leaves out (below 2^-22 of |u||v|); decisions closer than this to a threshold are re-made in fp64.
-inline double cos_margin(int dk) { return (double)(dk + 16) * (1.0 / 8388608.0) + 2.5e-6; }
+// Worst-case error of a cosine from the matrix passes.  bf16 keys: rounding of the fp32 accumulation of
+// dk products, plus slack for the scaling multiplies.  fp32 keys: the rounding of the elements to 24 bits
+// of the row's largest (sqrt(dk) 2^-23), the byte products left out (below dk 2^-23), the fp32 combination
+// of the rest.  Decisions closer than this to a threshold are re-made in fp64.
+inline double cos_margin(int dk, int k_dt) {
+    const double extra = k_dt == PACT_F32 ? sqrt((double)dk) : 0.0;
+    return ((double)dk + extra + 16.0) * (1.0 / 8388608.0) + 2.5e-6;
+}
 
-// Internal element type of the Gram kernel for fp32 keys: each value as the sum of three bf16
-// parts (hi + mid + lo, 24 significant bits), in three planes per token.
-enum { PACT_F32X3 = 2 };
+// Internal element type of the Gram kernel for fp32 keys: each row as 24-bit integers in three int8 planes.
+enum { PACT_I8X3 = 2 };
 
 }  // namespace pact
 
