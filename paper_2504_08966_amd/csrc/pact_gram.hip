@@ -75,8 +75,9 @@ struct GramArgs {
 
 constexpr int LDS_BUDGET = 160 * 1024 - 4096;
 
-// DT: PACT_BF16, or PACT_I8X3 for fp32 keys as three int8 planes.  STAGES: ring stages at most.
-template <int DT, int MI_, int NJ_, int WR_, int WC_, int STAGES> struct Shape {
+// DT: PACT_BF16, or PACT_I8X3 for fp32 keys as three int8 planes.  STAGES: ring stages at most.  TURNS: two groups
+// of wavefronts take turns at the matrix cores.
+template <int DT, int MI_, int NJ_, int WR_, int WC_, int STAGES, bool TURNS> struct Shape {
     static constexpr int MI = MI_, NJ = NJ_, WR = WR_, WC = WC_;
     static constexpr int WAVES = WR * WC, THREADS = 64 * WAVES;
     static constexpr int TILE_R = 32 * MI * WR, TILE_C = 32 * NJ * WC;
@@ -86,6 +87,10 @@ template <int DT, int MI_, int NJ_, int WR_, int WC_, int STAGES> struct Shape {
     static constexpr int NSTAGE = (LDS_BUDGET / STAGE_BYTES) < STAGES ? (LDS_BUDGET / STAGE_BYTES) : STAGES;
     static constexpr int AHEAD = NSTAGE - 1;                             // slices in flight besides the one being multiplied
     static constexpr int NB = STAGE_BYTES / 1024 / WAVES;                // 1 KB blocks each wavefront brings per stage
+    static constexpr bool PINGPONG = TURNS;
+    static_assert(!TURNS || WAVES == 8, "one wavefront of either group per SIMD");
+    // k-groups per slice; k-groups per turn
+    static constexpr int KG = I8 ? 2 : 4, HG = I8 || MI * NJ <= 4 ? KG : 2;
     static constexpr int RINV_BYTES = TILE_R * sizeof(float);
     static_assert(NSTAGE >= 2, "the ring needs a slot to fill while another is multiplied");
     static_assert(NB * 1024 * WAVES == STAGE_BYTES, "whole blocks per wavefront");
@@ -93,6 +98,7 @@ template <int DT, int MI_, int NJ_, int WR_, int WC_, int STAGES> struct Shape {
     static_assert((WAVES / 2) * NB * 1024 == TILE_R * SLICE_BYTES || !I8, "half of the wavefronts fetch the row operand");
     // ring stages a launch needs: no more than there are slices (two at least: the epilogue uses one)
     static size_t lds_bytes(int slices) {
+        if (I8) slices *= 2;                                             // (with the order-3 products they come twice)
         const int st = slices < 2 ? 2 : slices < NSTAGE ? slices : NSTAGE;
         return RINV_BYTES + (size_t)st * STAGE_BYTES;
     }
@@ -151,32 +157,33 @@ template <int L> __device__ __forceinline__ void file_ballots2(uint32_t& lo, uin
           "n"(L), "n"(L + 4));
 }
 // body(std::integral_constant<int, 0>{}) ... body(std::integral_constant<int, N-1>{})
-// value of the lane whose number differs by XOR (1, 2, 4, 8 or 16): a swizzle inside each
-// group of 32 lanes, which needs no address register
-template <int XOR> __device__ __forceinline__ double swizzle_xor(double v) {
-    static_assert(XOR >= 1 && XOR < 32, "within 32 lanes");
-    const uint64_t u = __builtin_bit_cast(uint64_t, v);
-    if constexpr (XOR < 16) {
-        // inside a row of 16 lanes the vector unit's own lane permutes do it (no trip through the LDS
-        // crossbar): quad permutes for 1 and 2, a rotation by 8 for 8, and for 4 a shift by 4 either
-        // way, each written to the banks of 4 lanes whose partner lies that way
-        auto half = [](int w) __attribute__((always_inline)) {
-            if constexpr (XOR == 1) return __builtin_amdgcn_update_dpp(w, w, 0xB1, 0xF, 0xF, false);
-            else if constexpr (XOR == 2) return __builtin_amdgcn_update_dpp(w, w, 0x4E, 0xF, 0xF, false);
-            else if constexpr (XOR == 8) return __builtin_amdgcn_update_dpp(w, w, 0x128, 0xF, 0xF, false);
-            else {
-                static_assert(XOR == 4, "1, 2, 4 or 8");
-                const int t = __builtin_amdgcn_update_dpp(w, w, 0x104, 0xF, 0x5, false);    // row_shl:4 -> banks 0, 2
-                return __builtin_amdgcn_update_dpp(t, w, 0x114, 0xF, 0xA, false);           // row_shr:4 -> banks 1, 3
-            }
-        };
-        const uint32_t lo = (uint32_t)half((int)(uint32_t)u), hi = (uint32_t)half((int)(uint32_t)(u >> 32));
-        return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
-    }
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_ds_swizzle((int)(uint32_t)u, (XOR << 10) | 0x1f);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_ds_swizzle((int)(uint32_t)(u >> 32), (XOR << 10) | 0x1f);
-    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+// Two values per lane, to be summed over pairs of lanes 16 apart: lanes with bit 4 clear get a's
+// sum, the others b's (v_permlane16_swap exchanges the odd rows of 16 lanes of one register with the even
+// rows of the other).
+__device__ __forceinline__ double halves16(double a, double b) {
+    const uint64_t ua = __builtin_bit_cast(uint64_t, a), ub = __builtin_bit_cast(uint64_t, b);
+    const auto lo = __builtin_amdgcn_permlane16_swap((uint32_t)ua, (uint32_t)ub, false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap((uint32_t)(ua >> 32), (uint32_t)(ub >> 32), false, false);
+    return __builtin_bit_cast(double, ((uint64_t)hi[0] << 32) | lo[0]) + __builtin_bit_cast(double, ((uint64_t)hi[1] << 32) | lo[1]);
 }
+// The same for lanes X = 8 or 4 apart (inside a row of 16), through the vector unit's lane permutes: a rotation by
+// 8, or a shift by 4 either way, each written to the banks of 4 lanes that want it.
+template <int X> __device__ __forceinline__ double halves_dpp(double a, double b) {
+    static_assert(X == 8 || X == 4, "inside a row");
+    constexpr int LOW = X == 8 ? 0x3 : 0x5, HIGH = X == 8 ? 0xC : 0xA;          // banks of the lanes that keep a / b
+    constexpr int FROM_HIGH = X == 8 ? 0x128 : 0x104, FROM_LOW = X == 8 ? 0x128 : 0x114;   // row_ror:8; row_shl:4, row_shr:4
+    const uint64_t ua = __builtin_bit_cast(uint64_t, a), ub = __builtin_bit_cast(uint64_t, b);
+    uint32_t own[2], other[2];
+#pragma unroll
+    for (int w = 0; w < 2; ++w) {
+        const int va = (int)(uint32_t)(ua >> (32 * w)), vb = (int)(uint32_t)(ub >> (32 * w));
+        own[w] = (uint32_t)__builtin_amdgcn_update_dpp(va, vb, 0xE4, 0xF, HIGH, false);       // quad_perm [0,1,2,3]
+        const int t = __builtin_amdgcn_update_dpp(va, va, FROM_HIGH, 0xF, LOW, false);
+        other[w] = (uint32_t)__builtin_amdgcn_update_dpp(t, vb, FROM_LOW, 0xF, HIGH, false);
+    }
+    return __builtin_bit_cast(double, ((uint64_t)own[1] << 32) | own[0]) + __builtin_bit_cast(double, ((uint64_t)other[1] << 32) | other[0]);
+}
+// body(std::integral_constant<int, 0>{}) ... body(std::integral_constant<int, N-1>{})
 template <int N, int I = 0, class F> __device__ __forceinline__ void static_for(F&& body) {
     if constexpr (I < N) {
         body(std::integral_constant<int, I>{});
@@ -308,6 +315,10 @@ __global__ __launch_bounds__(SH::THREADS, 2) void gram_kernel(Batch bt, GramArgs
     const long nTiles = sym ? nTri : nFull;
     const bool banded = !ga.mapped && nTiles >= 8 && (G & 7) == 0;        // (a sample kept on one XCD: one band)
     const bool patch = banded && !sym && (tilesR & 1) == 0 && (tilesC & 3) == 0;   // (patches of equal size only)
+    // Many tiles: the operands of 32 tiles of a column (a turn of an XCD's workgroups) do not fit its L2 and came from
+    // the last-level cache every turn; in squares of 6 x 6 tiles they are 12 operands instead of 33.
+    constexpr int SQ = 6;
+    const bool squares = !patch && tilesR >= 3 * SQ;
     const int pr0 = (xcd >> 2) * tilesR / 2, pnr = ((xcd >> 2) + 1) * tilesR / 2 - pr0;   // the XCD's patch
     const int pc0 = (xcd & 3) * tilesC / 4, pnc = ((xcd & 3) + 1) * tilesC / 4 - pc0;
     const int l_lo = patch ? 0 : banded ? (int)(xcd * nTiles / 8) : 0;
@@ -342,8 +353,30 @@ __global__ __launch_bounds__(SH::THREADS, 2) void gram_kernel(Batch bt, GramArgs
         if (patch) {
             tr = pr0 + tl % pnr;
             tc = pc0 + tl / pnr;
-        }
-        if (sym) {
+        } else if (squares) {
+            // columns in groups of SQ; above the diagonal (or over the full height) squares of SQ x SQ
+            // tiles, then (sym) the group's triangle on the diagonal
+            int c = sym ? (int)((sqrtf(8.0f * (float)tl + 1.0f) - 1.0f) * 0.5f) : tl / tilesR;
+            if (sym) {
+                while ((c + 1) * (c + 2) / 2 <= tl) ++c;
+                while (c * (c + 1) / 2 > tl) --c;
+            }
+            c -= c % SQ;                                     // first column of the group
+            const int w = min(SQ, tilesC - c), height = sym ? c : tilesR;
+            int rem = tl - (sym ? c * (c + 1) / 2 : c * tilesR);
+            if (rem < height * w) {
+                const int sr = rem / (SQ * w) * SQ, sh = min(SQ, height - sr);
+                rem -= sr * w;
+                tr = sr + rem % sh;
+                tc = c + rem / sh;
+            } else {
+                rem -= height * w;
+                int k = 0;
+                while (rem > k) rem -= ++k;
+                tr = c + rem;
+                tc = c + k;
+            }
+        } else if (sym) {
             // the tiles above the diagonal, column by column: tile tl is (tr, tc) with tr < tc,
             // tl = tc (tc - 1) / 2 + tr; then the tiles on the diagonal, whose epilogue is the
             // shorter one (the last turn of a workgroup's tile loop is then a short one)
@@ -375,8 +408,12 @@ __global__ __launch_bounds__(SH::THREADS, 2) void gram_kernel(Batch bt, GramArgs
 #pragma unroll
         for (int j = 0; j < NJ; ++j) rj_pre[j] = rinv[idxC[min(colBase + wc * WCOLS + j * 32 + l32_, nB - 1)]];
 
-        auto issue = [&](int s) __attribute__((always_inline)) {      // slice s -> ring slot s % NSTAGE
-            const uint32_t lds = dma_lds0 + (uint32_t)((s % NSTAGE) * STAGE_BYTES), off = (uint32_t)(s * SLICE_BYTES);
+        // The order-3 products take a sweep over the key width of their own, ahead of the others (in the
+        // registers of order 2, which they are a 256th of): the slices then come twice.
+        const int nSweep3 = I8 && order3 ? nSlices : 0, nSteps = nSweep3 + nSlices;
+        auto issue = [&](int step) __attribute__((always_inline)) {   // step's slice -> ring slot step % NSTAGE
+            const int s = I8 && step >= nSweep3 ? step - nSweep3 : step;
+            const uint32_t lds = dma_lds0 + (uint32_t)((step % NSTAGE) * STAGE_BYTES), off = (uint32_t)(s * SLICE_BYTES);
             if (I8 || (s + 1) * SLICE_BYTES <= tok_bytes) {
                 // a whole slice: scalar base + (row offset + chunk) + slice offset, one add per block.
                 // (These instructions sit between the barrier and the first MFMA of every
@@ -393,10 +430,10 @@ __global__ __launch_bounds__(SH::THREADS, 2) void gram_kernel(Batch bt, GramArgs
             }
         };
         f32x16_t acc[MI][NJ];
-        i32x16_t ord[I8 ? 4 : 1][MI][NJ];                   // fp32 keys: sums of the byte products, by order
+        i32x16_t ord[I8 ? 3 : 1][MI][NJ];                   // fp32 keys: sums of the byte products, by order
         if constexpr (I8) {
 #pragma unroll
-            for (int o = 0; o < 4; ++o)
+            for (int o = 0; o < 3; ++o)
 #pragma unroll
                 for (int i = 0; i < MI; ++i)
 #pragma unroll
@@ -414,63 +451,132 @@ __global__ __launch_bounds__(SH::THREADS, 2) void gram_kernel(Batch bt, GramArgs
 
 #pragma unroll
         for (int s = 0; s < AHEAD; ++s)
-            if (s < nSlices) issue(s);
+            if (s < nSteps) issue(s);
 
-        for (int s = 0; s < nSlices; ++s) {
+        auto arrive = [&](int s) __attribute__((always_inline)) {
             // slice s has landed once at most the younger slices' loads are outstanding
-            if (s + AHEAD - 1 < nSlices) wait_vmcnt<NB * (AHEAD - 1)>();
+            if (s + AHEAD - 1 < nSteps) wait_vmcnt<NB * (AHEAD - 1)>();
             else wait_vmcnt<0>();
             __builtin_amdgcn_s_barrier();      // ... for every wavefront; and slot (s-1)%NSTAGE is free
-
-            const lds_char* st = ring + (s % NSTAGE) * STAGE_BYTES;
-            if constexpr (I8) {
-                // two k-steps of 32 elements: the planes of MI + NJ fragment rows, then the byte products.
-                // (Eight wavefronts on four SIMDs: one reads while the other multiplies.)
-                if ((s & 511) == 511) {
-                    // rows of more than 32768 elements: carry into the higher orders before int32 can overflow (exact)
+            return (const lds_char*)(ring + (s % NSTAGE) * STAGE_BYTES);
+        };
+        auto carry = [&](int o) __attribute__((always_inline)) {     // exact: what exceeds a byte goes to the next higher order
 #pragma unroll
-                    for (int o = 3; o > 0; --o)
+            for (int i = 0; i < MI; ++i)
+#pragma unroll
+                for (int j = 0; j < NJ; ++j)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) {
+                        const int c = ord[o][i][j][r] >> 8;
+                        ord[o][i][j][r] -= c * 256;
+                        ord[o - 1][i][j][r] += c;
+                    }
+        };
+        if constexpr (I8) {
+            auto frag = [&](const lds_char* st, uint32_t row0, int blk, int pl, int ks) __attribute__((always_inline)) {
+                return *(const lds_u32x4*)(st + row0 + blk * 32 * SLICE_BYTES + pl * 64 + (uint32_t)(((2 * ks + hh_) ^ swz) << 4));
+            };
+            for (int s = 0; s < nSweep3; ++s) {
+                const lds_char* st = arrive(s);
+                if (s + AHEAD < nSteps) issue(s + AHEAD);
+#pragma unroll
+                for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+                    for (int pa = 1; pa < 3; ++pa)
 #pragma unroll
                         for (int i = 0; i < MI; ++i)
 #pragma unroll
                             for (int j = 0; j < NJ; ++j)
+                                mfma_i8(frag(st, fragA0, i, pa, ks), frag(st, fragB0, j, 3 - pa, ks), ord[2][i][j]);
+                if ((s & 511) == 511) carry(2);          // (rows of more than 32768 elements, see below; into order 1's registers)
+            }
+            if (nSweep3 > 0) {
 #pragma unroll
-                                for (int r = 0; r < 16; ++r) {
-                                    const int c = ord[o][i][j][r] >> 8;
-                                    ord[o][i][j][r] -= c * 256;
-                                    ord[o - 1][i][j][r] += c;
-                                }
+                for (int i = 0; i < MI; ++i)
+#pragma unroll
+                    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) {
+                            ord[2][i][j][r] = ((ord[2][i][j][r] + 128) >> 8) + ord[1][i][j][r];
+                            ord[1][i][j][r] = 0;
+                        }
+            }
+        }
+        // Multiply.  A SIMD holds two of the eight wavefronts, one of either group (wavefronts w and w + 4); the
+        // groups take turns, one multiplies while the other fetches its next fragments from the LDS, with a
+        // barrier between the turns, so that the matrix cores wait for no LDS read (all wavefronts reading
+        // after a common barrier left them idle for a third of the slice: a slice of 64 elements of
+        // 256 x 256 bf16 tiles took 1.53 us, of 128 x 128 fp32 tiles 1.28 us; its MFMAs 1.02 and 0.76 us).
+        // Group 1 is one turn behind.  Slice s + 1 has to be there, for every wavefront, before group 0 fetches
+        // from it: either group waits for its own part at the end of the turn before that.  A slot is
+        // refilled by group 0 in the turn after group 1 has read the last of it.
+        if constexpr (SH::PINGPONG) {
+            constexpr int KG = SH::KG, HG = SH::HG;
+            const bool second = wave >= 4;
+            auto turn = [&]() __attribute__((always_inline)) {
+                __builtin_amdgcn_sched_barrier(0);
+                __builtin_amdgcn_s_barrier();
+                __builtin_amdgcn_sched_barrier(0);
+            };
+            auto wait_slice = [&](int s) __attribute__((always_inline)) {     // (at most the younger slices outstanding)
+                if (s + AHEAD - 1 < nSteps) wait_vmcnt<NB * (AHEAD - 1)>();
+                else wait_vmcnt<0>();
+            };
+            wait_slice(nSweep3);
+            turn();
+            if (second) turn();
+            for (int s = nSweep3; s < nSteps; ++s) {
+                const lds_char* st = ring + (s % NSTAGE) * STAGE_BYTES;
+                if constexpr (I8) {
+                    if (((s - nSweep3) & 511) == 511) { carry(2); carry(1); }     // rows of more than 32768 elements: before int32 can overflow
                 }
 #pragma unroll
-                for (int ks = 0; ks < 2; ++ks) {
-                    u32x4_t fa[MI][3], fb[NJ][3];
-                    const uint32_t co = (uint32_t)(((2 * ks + hh_) ^ swz) << 4);
+                for (int g0 = 0; g0 < KG; g0 += HG) {
+                    constexpr int PL = I8 ? 3 : 1;
+                    u32x4_t fa[HG][MI][PL], fb[HG][NJ][PL];
 #pragma unroll
-                    for (int pl = 0; pl < 3; ++pl) {
+                    for (int g = 0; g < HG; ++g) {
+                        const uint32_t co = (uint32_t)(((2 * (g0 + g) + hh_) ^ swz) << 4);
 #pragma unroll
-                        for (int i = 0; i < MI; ++i) fa[i][pl] = *(const lds_u32x4*)(st + fragA0 + i * 32 * SLICE_BYTES + pl * 64 + co);
+                        for (int pl = 0; pl < PL; ++pl) {
 #pragma unroll
-                        for (int j = 0; j < NJ; ++j) fb[j][pl] = *(const lds_u32x4*)(st + fragB0 + j * 32 * SLICE_BYTES + pl * 64 + co);
+                            for (int i = 0; i < MI; ++i) fa[g][i][pl] = *(const lds_u32x4*)(st + fragA0 + i * 32 * SLICE_BYTES + pl * 64 + co);
+#pragma unroll
+                            for (int j = 0; j < NJ; ++j) fb[g][j][pl] = *(const lds_u32x4*)(st + fragB0 + j * 32 * SLICE_BYTES + pl * 64 + co);
+                        }
                     }
-                    if (ks == 0 && s + AHEAD < nSlices) issue(s + AHEAD);
+                    if (g0 == 0 && s + AHEAD < nSteps) issue(s + AHEAD);
+                    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                    if (g0 + HG == KG && second && s + 1 < nSteps) wait_slice(s + 1);
+                    turn();
+                    __builtin_amdgcn_s_setprio(1);
 #pragma unroll
-                    for (int o = 0; o < 3; ++o)
+                    for (int g = 0; g < HG; ++g) {
+                        if constexpr (I8) {
 #pragma unroll
-                        for (int pa = 0; pa <= o; ++pa)
+                            for (int o = 0; o < 3; ++o)
+#pragma unroll
+                                for (int pa = 0; pa <= o; ++pa)
+#pragma unroll
+                                    for (int i = 0; i < MI; ++i)
+#pragma unroll
+                                        for (int j = 0; j < NJ; ++j) mfma_i8(fa[g][i][pa], fb[g][j][o - pa], ord[o][i][j]);
+                        } else {
 #pragma unroll
                             for (int i = 0; i < MI; ++i)
 #pragma unroll
-                                for (int j = 0; j < NJ; ++j) mfma_i8(fa[i][pa], fb[j][o - pa], ord[o][i][j]);
-                    if (order3) {
-#pragma unroll
-                        for (int pa = 1; pa < 3; ++pa)
-#pragma unroll
-                            for (int i = 0; i < MI; ++i)
-#pragma unroll
-                                for (int j = 0; j < NJ; ++j) mfma_i8(fa[i][pa], fb[j][3 - pa], ord[3][i][j]);
+                                for (int j = 0; j < NJ; ++j) mfma_bf16(fa[g][i][0], fb[g][j][0], acc[i][j]);
+                        }
                     }
+                    __builtin_amdgcn_s_setprio(0);
+                    if (g0 + HG == KG && !second && s + 1 < nSteps) wait_slice(s + 1);
+                    turn();
                 }
-            } else {
+            }
+            if (!second) turn();
+        } else {
+            for (int s = 0; s < nSteps; ++s) {
+                const lds_char* st = arrive(s);
                 // the fragments of k-group g+1 are read from LDS while the MFMAs of group g run
                 u32x4_t fa[2][MI], fb[2][NJ];
                 auto load_frags = [&](int g, int buf) __attribute__((always_inline)) {
@@ -484,7 +590,7 @@ __global__ __launch_bounds__(SH::THREADS, 2) void gram_kernel(Batch bt, GramArgs
                 __builtin_amdgcn_sched_group_barrier(0x100, MI + NJ, 0);
                 // (the next fetches are issued while the first fragments are on their way from the LDS:
                 //  nothing else can fill the time between the barrier and the first MFMA)
-                if (s + AHEAD < nSlices) issue(s + AHEAD);
+                if (s + AHEAD < nSteps) issue(s + AHEAD);
 #pragma unroll
                 for (int g = 0; g < 4; ++g) {
                     if (g + 1 < 4) load_frags(g + 1, (g + 1) & 1);
@@ -517,14 +623,13 @@ __global__ __launch_bounds__(SH::THREADS, 2) void gram_kernel(Batch bt, GramArgs
 #pragma unroll
                     for (int r = 0; r < 16; ++r) {
                         float v = (float)ord[2][i][j][r];
-                        if (order3) v = fmaf((float)ord[3][i][j][r], 1.0f / 256.0f, v);
                         v = fmaf((float)ord[1][i][j][r], 256.0f, v);
                         acc[i][j][r] = fmaf((float)ord[0][i][j][r], 65536.0f, v);
                     }
         }
         // LDS the epilogue may use for its buffers: a ring stage that the last slice did not occupy
         // (one of the first two: a launch with few slices has no others)
-        const int freeStage = (nSlices - 1) % NSTAGE == 0 ? 1 : 0;
+        const int freeStage = (nSteps - 1) % NSTAGE == 0 ? 1 : 0;
 
         // ------------------------------------------------------------------ epilogue
         // acc[i][j][r] holds row  rowBase + wr*WROWS + i*32 + 8*(r/4) + 4*hh + (r%4)
@@ -538,12 +643,11 @@ __global__ __launch_bounds__(SH::THREADS, 2) void gram_kernel(Batch bt, GramArgs
         const int rowW = rowBase + wr * WROWS;
         float rj[NJ];
         int colP[NJ];
-        uint64_t laneOk[NJ];                                // lanes whose column exists
+        const bool edge = rowW + WROWS > nA || colW + WCOLS > nB;      // (the same in every lane)
 #pragma unroll
         for (int j = 0; j < NJ; ++j) {
             colP[j] = colW + j * 32 + l32;
             rj[j] = rj_pre[j] * sa_;
-            laneOk[j] = __ballot(colP[j] < nB);
         }
         double rho[2][2] = {{0.0, 0.0}, {0.0, 0.0}};
         // per-wavefront buffer of undecided pairs, in a ring slot no wavefront reads any more
@@ -625,72 +729,62 @@ __global__ __launch_bounds__(SH::THREADS, 2) void gram_kernel(Batch bt, GramArgs
             const int rowI = rowW + i * 32;                 // first row of this 32-row block
             // phase A1: cosines (scaled for the density exponent), left in place of the accumulators
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const bool pad = rowI + 8 * (r >> 2) + 4 * hh + (r & 3) >= nA;   // padded row: no term, no bit
+            for (int r = 0; r < 16; ++r)
 #pragma unroll
-                for (int j = 0; j < 2; ++j) {
-                    const float v = fmaf(acc[i][j][r], rs[r] * rj[j], -a_);
-                    acc[i][j][r] = pad ? -INFINITY : v;
+                for (int j = 0; j < 2; ++j) acc[i][j][r] = fmaf(acc[i][j][r], rs[r] * rj[j], -a_);
+            // d_ii = 0 exactly: only the blocks on the diagonal hold such elements
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+                if (rowI == colW + j * 32) {
+#pragma unroll
+                    for (int r = 0; r < 16; ++r)
+                        if (8 * (r >> 2) + 4 * hh + (r & 3) == l32) acc[i][j][r] = 0.0f;
+                }
+            // rows and columns past the last one: no term, no bit (only the last tiles have any)
+            if (edge) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const bool pad = rowI + 8 * (r >> 2) + 4 * hh + (r & 3) >= nA;
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) acc[i][j][r] = pad || colP[j] >= nB ? -INFINITY : acc[i][j][r];
                 }
             }
-            if (MODE == MODE_DENSITY) {
-                // d_ii = 0 exactly: only the blocks on the diagonal hold such elements
+            // phase A2: density terms
+            if (mirror) {
+                // ... which also belong to the densities of this tile's rows: sum them over
+                // the wavefront's 64 columns.  Eight rows x 2 columns per lane at a time; the 32
+                // lanes of a half-wave halve their row sets three times (a lane gives up half of its
+                // rows' sums and adds what it receives for those it keeps; rows of 16 lanes swap in one
+                // instruction) and are left with one row each, four neighbouring lanes with parts of the same one.
+                static_for<2>([&](auto r8_tag) __attribute__((always_inline)) {
+                    constexpr int r8 = 8 * decltype(r8_tag)::value;
+                    double d[8];
 #pragma unroll
-                for (int j = 0; j < 2; ++j)
-                    if (rowI == colW + j * 32) {
-#pragma unroll
-                        for (int r = 0; r < 16; ++r)
-                            if (8 * (r >> 2) + 4 * hh + (r & 3) == l32 && rowI + l32 < nA) acc[i][j][r] = 0.0f;
+                    for (int r = 0; r < 8; ++r) {
+                        const double e0 = (double)__builtin_amdgcn_exp2f(acc[i][0][r8 + r]);
+                        const double e1 = (double)__builtin_amdgcn_exp2f(acc[i][1][r8 + r]);
+                        rho[0][r & 1] += e0;
+                        rho[1][r & 1] += e1;
+                        d[r] = e0 + e1;
                     }
-                // phase A2: density terms
-                if (mirror) {
-                    // ... which also belong to the densities of this tile's rows: sum them over
-                    // the wavefront's 64 columns.  Each lane has 4 rows x 2 columns at a time; the 32
-                    // lanes of a half-wave halve their row sets twice (a lane sends the sums of the
-                    // rows it gives up and adds what it receives for those it keeps) and are left
-                    // with one row each, eight neighbouring lanes with parts of the same one.
-                    const bool ok0 = colP[0] < nB, ok1 = colP[1] < nB;      // clamped columns count nowhere
-                    static_for<4>([&](auto r4_tag) __attribute__((always_inline)) {   // four rows at a time: registers are tight
-                        constexpr int r4 = 4 * decltype(r4_tag)::value;
-                        double d[4];
 #pragma unroll
-                        for (int r = 0; r < 4; ++r) {
-                            const double e0 = (double)__builtin_amdgcn_exp2f(acc[i][0][r4 + r]);
-                            const double e1 = (double)__builtin_amdgcn_exp2f(acc[i][1][r4 + r]);
-                            rho[0][r & 1] += e0;
-                            rho[1][r & 1] += e1;
-                            d[r] = (ok0 ? e0 : 0.0) + (ok1 ? e1 : 0.0);
-                        }
-                        {
-                            const bool up = (l32 & 16) != 0;
+                    for (int k = 0; k < 4; ++k) d[k] = halves16(d[k], d[k + 4]);
 #pragma unroll
-                            for (int k = 0; k < 2; ++k) {
-                                const double keep = up ? d[k + 2] : d[k];
-                                const double send = up ? d[k] : d[k + 2];
-                                d[k] = keep + swizzle_xor<16>(send);
-                            }
-                        }
-                        {
-                            const bool up = (l32 & 8) != 0;
-                            const double keep = up ? d[1] : d[0];
-                            const double send = up ? d[0] : d[1];
-                            d[0] = keep + swizzle_xor<8>(send);
-                        }
-                        d[0] += swizzle_xor<4>(d[0]);
-                        d[0] += swizzle_xor<2>(d[0]);
-                        d[0] += swizzle_xor<1>(d[0]);
-                        // rows r4 .. r4+3 of this lane are rows 2 r4 + 4 hh + (0..3) of the block
-                        const int gRow = rowI + 2 * r4 + 4 * hh + (l32 >> 3);
-                        if ((l32 & 7) == 0 && gRow < nA) unsafeAtomicAdd(&rho_b[gRow], d[0]);
-                        if (r4 == 4) __builtin_amdgcn_sched_barrier(0);     // two groups at a time may overlap their exchanges
-                    });
-                } else {
+                    for (int k = 0; k < 2; ++k) d[k] = halves_dpp<8>(d[k], d[k + 2]);
+                    d[0] = halves_dpp<4>(d[0], d[1]);
+                    d[0] += dpp_f64<DPP_XOR2>(d[0]);
+                    d[0] += dpp_f64<DPP_XOR1>(d[0]);
+                    // this lane's row: bits 4, 3, 2 of l32 chose the upper half in turn
+                    const int gRow = rowI + 2 * r8 + 8 * (l32 >> 4) + 4 * hh + ((l32 >> 2) & 3);
+                    if ((l32 & 3) == 0 && gRow < nA) unsafeAtomicAdd(&rho_b[gRow], d[0]);
+                    __builtin_amdgcn_sched_barrier(0);     // registers are tight
+                });
+            } else {
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
 #pragma unroll
                     for (int j = 0; j < 2; ++j) rho[j][r & 1] += (double)__builtin_amdgcn_exp2f(acc[i][j][r]);
                     if ((r & 3) == 3) __builtin_amdgcn_sched_barrier(0);   // bound the live ranges: registers are tight
-                }
                 }
             }
             // phase B: one bit per pair; most 32 x 64 blocks have none set: test the block's maximum first
@@ -698,19 +792,17 @@ __global__ __launch_bounds__(SH::THREADS, 2) void gram_kernel(Batch bt, GramArgs
 #pragma unroll
             for (int r = 1; r < 16; ++r) mx = fmaxf(mx, fmaxf(acc[i][0][r], acc[i][1][r]));
             if (STAT) {
-                // the block's smallest exponent (largest distance); padded rows hold -inf and are
-                // left out (padded columns repeat a real column: harmless)
-                if (rowI + 32 <= nA) {
+                // the block's smallest exponent (largest distance); what is past the last row or column holds -inf
+                if (!edge) {
                     float mn = fminf(acc[i][0][0], acc[i][1][0]);
 #pragma unroll
                     for (int r = 1; r < 16; ++r) mn = fminf(mn, fminf(acc[i][0][r], acc[i][1][r]));
                     far = fminf(far, mn);
                 } else {
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) {
-                        const bool pad = rowI + 8 * (r >> 2) + 4 * hh + (r & 3) >= nA;
-                        far = fminf(far, pad ? 0.0f : fminf(acc[i][0][r], acc[i][1][r]));
-                    }
+                    for (int r = 0; r < 16; ++r)
+#pragma unroll
+                        for (int j = 0; j < 2; ++j) far = fminf(far, acc[i][j][r] == -INFINITY ? 0.0f : acc[i][j][r]);
                 }
             }
             if (__ballot(mx >= t_lo) == 0) continue;
@@ -737,10 +829,7 @@ __global__ __launch_bounds__(SH::THREADS, 2) void gram_kernel(Batch bt, GramArgs
                     file_ballots<k0>(wlo, whi, m0, m1);
                 }
             });
-            // the 32 words of this block, one store instruction (the bitmap was cleared beforehand;
-            // columns past the last one come from a clamped row: mask them)
-            wlo &= (uint32_t)laneOk[0];
-            whi &= (uint32_t)laneOk[1];
+            // the 32 words of this block, one store instruction (the bitmap was cleared beforehand)
             if (lane < 32 && (wlo | whi) != 0)
                 adj[(size_t)(rowI + lane) * bt.W + wordIdx] = ((uint64_t)whi << 32) | wlo;
             if (MODE == MODE_DENSITY && mirror) {
@@ -912,12 +1001,16 @@ static int launch_gram_shape(const Batch& bt, const GramArgs& ga_in, hipStream_t
 }
 
 // The tiles.  256 x 256 has the best ratio of flops to bytes fetched, but its launch lasts as long as a
-// tile (23 us at a key width of 512) however few there are.
-typedef Shape<PACT_BF16, 4, 2, 2, 4, 2> Tile256;
-typedef Shape<PACT_BF16, 2, 2, 2, 4, 3> Tile128x256;
-typedef Shape<PACT_BF16, 2, 2, 2, 2, 4> Tile128;
-typedef Shape<PACT_I8X3, 1, 2, 4, 2, 3> TileI8;         // density pass
-typedef Shape<PACT_I8X3, 2, 1, 2, 4, 3> TileI8Cand;     // candidate pass (groups of 64 rows)
+// tile (23 us at a key width of 512) however few there are.  bf16 tiles take turns at the matrix cores from key rows of
+// 2 KB on: the loop over a row of 7 KB got 5% shorter, over one of 1 KB the two turns' offset cost 0.8 us.
+// (Both are then near what the chip's power allows: a slice of random keys takes 1.45 us, of keys that
+// are mostly zeros 1.10 us, its MFMAs alone 1.02 us.)
+typedef Shape<PACT_BF16, 4, 2, 2, 4, 2, false> Tile256;
+typedef Shape<PACT_BF16, 4, 2, 2, 4, 2, true> Tile256Wide;
+typedef Shape<PACT_BF16, 2, 2, 2, 4, 3, false> Tile128x256;
+typedef Shape<PACT_I8X3, 1, 2, 4, 2, 3, true> TileI8;         // density pass
+typedef Shape<PACT_I8X3, 2, 1, 2, 4, 3, true> TileI8Cand;     // candidate pass (groups of 64 rows)
+constexpr int WIDE_KEYS = 1024;
 
 template <class SH, int MODE>
 static int launch_gram(const Batch& bt, const GramArgs& ga, hipStream_t st, const char* name, bool mirrored, bool want_stat,
@@ -967,7 +1060,10 @@ int launch_gram_density(const Batch& bt, const Ws& w, const void* keys, pact_dty
     };
     if (k_dt == PACT_F32) return launch_gram<TileI8, MODE_DENSITY>(bt, ga, st, name, mirrored(128), want_stat, stat_words);
     const long t1 = (bt.n_max + 255) / 256;
-    if (t1 * t1 * bt.B >= 256) return launch_gram<Tile256, MODE_DENSITY>(bt, ga, st, name, mirrored(256), want_stat, stat_words);
+    if (t1 * t1 * bt.B >= 256) {
+        if (dk >= WIDE_KEYS) return launch_gram<Tile256Wide, MODE_DENSITY>(bt, ga, st, name, mirrored(256), want_stat, stat_words);
+        return launch_gram<Tile256, MODE_DENSITY>(bt, ga, st, name, mirrored(256), want_stat, stat_words);
+    }
     return launch_gram<Tile128x256, MODE_DENSITY>(bt, ga, st, name, false, want_stat, stat_words);
 }
 
@@ -982,7 +1078,10 @@ int launch_gram_candidates(const Batch& bt, const Ws& w, const void* keys, pact_
     // rows: the centres, columns: the pruned tokens; neither count is known on the host, a
     // typical split (half pruned, a third of the rest centres) sizes the choice
     const long tr = (bt.n_max / 6 + 255) / 256, tc = (bt.n_max / 2 + 255) / 256;
-    if (tr * tc * bt.B >= 256) return launch_gram<Tile256, MODE_CAND>(bt, ga, st, name, false, false, nullptr);
+    if (tr * tc * bt.B >= 256) {
+        if (dk >= WIDE_KEYS) return launch_gram<Tile256Wide, MODE_CAND>(bt, ga, st, name, false, false, nullptr);
+        return launch_gram<Tile256, MODE_CAND>(bt, ga, st, name, false, false, nullptr);
+    }
     return launch_gram<Tile128x256, MODE_CAND>(bt, ga, st, name, false, false, nullptr);
 }
 

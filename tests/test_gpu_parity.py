@@ -763,6 +763,28 @@ def test_odd_sizes_and_key_widths(n, dk_heads, d_h, dtype):
     assert_same(gu.trim(o, n), oracle_reduce(s, d_c), s, f"n={n} dk={dk_heads * d_h} {dtype}")
 
 
+@pytest.mark.parametrize("n,dk,shift", [(130, 64, 0.0), (127, 64, 40.0), (257, 128, 40.0), (300, 192, 0.0), (385, 192, 40.0),
+                                        (129, 512, 300.0), (260, 4, 0.0), (96, 33024, 0.0), (96, 66048, 900.0)])
+def test_fp32_keys_as_integers(n, dk, shift):
+    # fp32 keys go through the matrix cores as 24-bit integers: one, two, three and more slices of 64 elements
+    # around the edges of 128 x 128 tiles; rows that one element dominates (shift), which take the additional
+    # products; rows of more than 32768 elements, whose sums are carried along
+    r = np.random.default_rng(n + dk)
+    cen = r.normal(size=(max(2, n // 12), dk))
+    u = cen[r.integers(0, cen.shape[0], n)] + 0.25 * r.normal(size=(n, dk))
+    u[:, dk // 3] += shift
+    u[5] = u[3]
+    u = u.astype(np.float32)
+    d_c = _gap_dc(u, frac=0.03)
+    ref = po.dbdpc(u.astype(np.float64), d_c, 2.0)
+    out = P.dbdpc_cluster(gu.dev(u, "f32"), d_c, 2.0, want_rho=True)
+    torch.cuda.synchronize()
+    rep = P.read_report(out["rep"])
+    np.testing.assert_allclose(out["rho"].cpu().numpy(), ref["rho"], rtol=1e-7, atol=0)
+    assert np.array_equal(out["center_idx"][: rep["n_centers"]].cpu().numpy(), ref["centers"])
+    assert np.array_equal(out["cluster_id"].cpu().numpy(), ref["labels"])
+
+
 # ------------------------------------------------------------------ mirrored tiles of the density pass
 # d_ij = d_ji: when a sample has more 256 x 256 tiles than it has workgroups, the density pass
 # computes the tiles above the diagonal only and lets them stand for their mirror images.
