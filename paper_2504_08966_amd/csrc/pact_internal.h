@@ -114,7 +114,9 @@ inline WsLayout make_layout(int64_t n_max, int64_t B, int64_t total, int64_t qco
     L.slots = take(sizeof(int32_t) * total * MERGE_SLOTS);
     L.worklist = take(n_max > RESOLVE_LDS_TOKENS ? 16 * B * n_max : 0);
     L.zeros = take(256);
-    L.ksplit = take(k_dt == PACT_F32 ? total * gram_token_bytes(dk, k_dt) : 0);
+    // (at least the six bytes per value that callers have been told to provide for)
+    const size_t key6 = (size_t)((dk + 7) / 8 * 8) * 6, keyI = gram_token_bytes(dk, k_dt);
+    L.ksplit = take(k_dt == PACT_F32 ? total * (keyI > key6 ? keyI : key6) : 0);
     L.total = off;
     return L;
 }
