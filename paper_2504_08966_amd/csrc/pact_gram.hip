@@ -65,12 +65,12 @@ struct GramArgs {
     int32_t stat_wgs;          // workgroup slots per sample in `stat`, one word per wavefront
     float margin;              // worst-case fp32 error of a cosine
     float rinv_low;            // fp32 keys: a reciprocal norm above this asks for the order-3 products
-    // Batches (mapped != 0): a one-dimensional grid of GRAM_MAX_WORKGROUPS workgroups, shared out
-    // among the samples by size; workgroup i serves sample wg_map[i] >> 8 as its workgroup number
-    // wg_map[i] & 255 of wg_count[sample] (0xFFFF: a spare workgroup).
+    // Batches (mapped != 0): a one-dimensional grid of 256 (512) workgroups, shared out
+    // among the samples by size; workgroup i serves sample wg_map[i] >> 8 (9) as its workgroup number
+    // wg_map[i] & 255 (511) of wg_count[sample] (0xFFFF: a spare workgroup).
     int32_t mapped;
     uint16_t wg_count[PACT_MAX_BATCH];
-    uint16_t wg_map[GRAM_MAX_WORKGROUPS];
+    uint16_t wg_map[2 * GRAM_MAX_WORKGROUPS];
 };
 
 constexpr int LDS_BUDGET = 160 * 1024 - 4096;
@@ -87,6 +87,9 @@ template <int DT, int MI_, int NJ_, int WR_, int WC_, int STAGES, bool TURNS> st
     static constexpr int NSTAGE = (LDS_BUDGET / STAGE_BYTES) < STAGES ? (LDS_BUDGET / STAGE_BYTES) : STAGES;
     static constexpr int AHEAD = NSTAGE - 1;                             // slices in flight besides the one being multiplied
     static constexpr int NB = STAGE_BYTES / 1024 / WAVES;                // 1 KB blocks each wavefront brings per stage
+    // workgroups of a launch: one per CU, or two where the registers and the ring leave room for them
+    static constexpr int SLOT_BITS = WAVES == 4 ? 9 : 8, SLOTS = 1 << SLOT_BITS;
+    static_assert(SLOTS * WAVES == GRAM_MAX_WORKGROUPS * 8, "a workgroup of eight wavefronts per CU, or two of four");
     static constexpr bool PINGPONG = TURNS;
     static_assert(!TURNS || WAVES == 8, "one wavefront of either group per SIMD");
     // k-groups per slice; k-groups per turn
@@ -227,14 +230,29 @@ __global__ __launch_bounds__(SH::THREADS, 2) void gram_kernel(Batch bt, GramArgs
     if (ga.mapped) {
         const uint32_t e = ga.wg_map[blockIdx.x];
         if (e == 0xFFFFu) return;
-        b = (int)(e >> 8);
-        wg = (int)(e & 255u);
+        b = (int)(e >> SH::SLOT_BITS);
+        wg = (int)(e & (SH::SLOTS - 1u));
         G = ga.wg_count[b];
     }
     if (STAT && wg == 0)                                      // slots no workgroup of this sample writes
         for (int k = threadIdx.x; k < (ga.stat_wgs - G) * WAVES; k += SH::THREADS)
             ga.stat[((size_t)b * ga.stat_wgs + G) * WAVES + k] = 0u;
     const Seg sg = bt.s[b];
+    // fp32 keys: does a row of this sample need the order-3 products (see the head of this file)?  (Requested
+    // before the counts are known.)
+    bool order3 = false;
+    if constexpr (I8) {
+        const float* __restrict__ rinv_b = ga.rinv + sg.base;
+        bool low = false;
+        for (int i = threadIdx.x; i < sg.n; i += 8 * SH::THREADS) {
+            float v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = rinv_b[min(i + u * SH::THREADS, sg.n - 1)];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) low |= v[u] > ga.rinv_low;
+        }
+        order3 = __syncthreads_or(low);
+    }
     const int q_kept = clamp_count(ga.rep[b].n_kept, sg.n);
     // density pass: kept x kept; candidate pass: rows are the centres, columns the pruned tokens
     // (what is wanted there is per pruned token, and a lane holds 16 rows of one column)
@@ -275,20 +293,6 @@ __global__ __launch_bounds__(SH::THREADS, 2) void gram_kernel(Batch bt, GramArgs
     const float thr_cos = (MODE == MODE_DENSITY) ? (1.0f - sg.d_c) : (1.0f - sg.alpha * sg.d_c);
     const float t_lo = (MODE == MODE_DENSITY) ? -(sg.d_c + ga.margin) * a_ : thr_cos - ga.margin;
     const float t_hi = -(sg.d_c - ga.margin) * a_;
-
-    // fp32 keys: does a row of this sample need the order-3 products (see the head of this file)?
-    bool order3 = false;
-    if constexpr (I8) {
-        bool low = false;
-        for (int i = tid; i < sg.n; i += 8 * SH::THREADS) {
-            float v[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) v[u] = rinv[min(i + u * SH::THREADS, sg.n - 1)];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) low |= v[u] > ga.rinv_low;
-        }
-        order3 = __syncthreads_or(low);
-    }
 
     // DMA roles: a stage is STAGE_BYTES / 1024 blocks of 1 KB, the A rows first; wavefront w brings
     // blocks w*NB .. w*NB+NB-1.  bf16: a block is 8 rows x 8 chunks, lane l row 8*blk + l/8, physical
@@ -900,32 +904,37 @@ __global__ __launch_bounds__(SH::THREADS, 2) void gram_kernel(Batch bt, GramArgs
 }
 
 // One sample: a workgroup per tile, at most one per CU, a multiple of the 8 XCDs (see the tile order).
-static int gram_grid_x(long tiles) {
+static int gram_grid_x(long tiles, int slots) {
     long grid_x = tiles;
     static_assert(GRAM_MAX_WORKGROUPS == 256, "one workgroup per CU, 256 CUs");
-    if (grid_x > GRAM_MAX_WORKGROUPS) grid_x = GRAM_MAX_WORKGROUPS;
+    if (grid_x > slots) grid_x = slots;
     if (grid_x >= 8) grid_x &= ~7L;
     return (int)grid_x;
 }
 
-// Batches: the chip's 256 workgroup slots are shared out among the samples by the number of
+// Fewest turns R of a workgroup's tile loop such that ceil(tiles[b] / R) workgroups per sample fit the slots.
+static long fewest_turns(int B, const long* tiles, int slots) {
+    long most_tiles = 1, all = 0;
+    for (int b = 0; b < B; ++b) { most_tiles = tiles[b] > most_tiles ? tiles[b] : most_tiles; all += tiles[b]; }
+    long R = (all + slots - 1) / slots;
+    for (R = R < 1 ? 1 : R;; ++R) {          // (R = most_tiles needs one workgroup per sample, B <= 64 < slots)
+        long need = 0;
+        for (int b = 0; b < B; ++b) need += (tiles[b] + R - 1) / R;
+        if (need <= slots || R >= most_tiles) return R;
+    }
+}
+
+// Batches: the chip's workgroup slots are shared out among the samples by the number of
 // tiles each is expected to have (tiles[b] >= 1): the fewest turns R of a workgroup's tile loop
 // such that ceil(tiles[b] / R) workgroups per sample fit, spare slots to the samples with the
 // most tiles per workgroup.  Each sample then gets slots of one XCD where it can (slot i belongs
 // to XCD i mod 8), the largest samples first.  The counts are estimates (the real ones are on the
 // device): a sample with more tiles than expected just takes more turns.
 // Fills ga.wg_map / ga.wg_count, returns the largest count.
-static int build_wg_map(int B, const long* tiles, GramArgs& ga) {
-    constexpr int S = GRAM_MAX_WORKGROUPS;
+static int build_wg_map(int B, const long* tiles, int slot_bits, GramArgs& ga) {
+    const int S = 1 << slot_bits;
     int g[PACT_MAX_BATCH], order[PACT_MAX_BATCH];
-    long most_tiles = 1;
-    for (int b = 0; b < B; ++b) most_tiles = tiles[b] > most_tiles ? tiles[b] : most_tiles;
-    long R = 1;
-    for (;; ++R) {                            // (R = most_tiles needs one workgroup per sample, B <= 64 < S)
-        long need = 0;
-        for (int b = 0; b < B; ++b) need += (tiles[b] + R - 1) / R;
-        if (need <= S || R >= most_tiles) break;
-    }
+    const long R = fewest_turns(B, tiles, S);
     int used = 0;
     for (int b = 0; b < B; ++b) { g[b] = (int)((tiles[b] + R - 1) / R); if (g[b] < 1) g[b] = 1; used += g[b]; }
     while (used < S) {
@@ -953,7 +962,7 @@ static int build_wg_map(int B, const long* tiles, GramArgs& ga) {
             const int take = left < freeSlots[x] ? left : freeSlots[x];
             for (int t = 0; t < take; ++t) {
                 const int slot = (S / 8 - freeSlots[x]) + t;       // this XCD's next unused slot
-                ga.wg_map[slot * 8 + x] = (uint16_t)((b << 8) | rank++);
+                ga.wg_map[slot * 8 + x] = (uint16_t)((b << slot_bits) | rank++);
             }
             freeSlots[x] -= take;
             left -= take;
@@ -963,27 +972,27 @@ static int build_wg_map(int B, const long* tiles, GramArgs& ga) {
 }
 
 static long kept_estimate(const Seg& sg) { return sg.n - prune_rank(sg.lambda, sg.n); }
+// Tiles a sample is expected to have: kept tokens n - floor(lambda n); density pass kept x kept
+// (mirrored: the triangle); candidate pass about kept / 2 centres x pruned.
+static long tiles_estimate(const Seg& sg, bool density, int tile_r, int tile_c, bool mirrored) {
+    const long q = kept_estimate(sg), rows = density ? q : (q + 1) / 2, cols = density ? q : sg.n - q;
+    const long tr = (rows + tile_r - 1) / tile_r, tc = (cols + tile_c - 1) / tile_c;
+    const long t = density && mirrored ? tr * (tr + 1) / 2 : tr * tc;
+    return t < 1 ? 1 : t;
+}
 
 template <class SH, int MODE, bool STAT, bool SYM>
 static int launch_gram_shape(const Batch& bt, const GramArgs& ga_in, hipStream_t st, const char* name, int* stat_words) {
     const int tilesR = (bt.n_max + SH::TILE_R - 1) / SH::TILE_R, tilesC = (bt.n_max + SH::TILE_C - 1) / SH::TILE_C;
     GramArgs ga = ga_in;
-    int grid_x = gram_grid_x((long)tilesR * tilesC);
+    int grid_x = gram_grid_x((long)tilesR * tilesC, SH::SLOTS);
     dim3 grid(grid_x, 1);
     ga.mapped = bt.B > 1;
     if (ga.mapped) {
-        // tiles a sample is expected to have: kept tokens n - floor(lambda n); density pass
-        // kept x kept (mirrored: the triangle); candidate pass about kept / 2 centres x pruned
         long tiles[PACT_MAX_BATCH];
-        for (int b = 0; b < bt.B; ++b) {
-            const long n = bt.s[b].n, q = kept_estimate(bt.s[b]);
-            const long rows = (MODE == MODE_DENSITY) ? q : (q + 1) / 2, cols = (MODE == MODE_DENSITY) ? q : n - q;
-            const long tr = (rows + SH::TILE_R - 1) / SH::TILE_R, tc = (cols + SH::TILE_C - 1) / SH::TILE_C;
-            tiles[b] = (MODE == MODE_DENSITY && SYM) ? tr * (tr + 1) / 2 : tr * tc;
-            if (tiles[b] < 1) tiles[b] = 1;
-        }
-        grid_x = build_wg_map(bt.B, tiles, ga);                // (from here on: the largest count of a sample)
-        grid = dim3(GRAM_MAX_WORKGROUPS, 1);
+        for (int b = 0; b < bt.B; ++b) tiles[b] = tiles_estimate(bt.s[b], MODE == MODE_DENSITY, SH::TILE_R, SH::TILE_C, SYM);
+        grid_x = build_wg_map(bt.B, tiles, SH::SLOT_BITS, ga);                // (from here on: the largest count of a sample)
+        grid = dim3(SH::SLOTS, 1);
     }
     ga.stat_wgs = grid_x;
     if (stat_words) *stat_words = STAT ? grid_x * SH::WAVES : 0;
@@ -1000,17 +1009,31 @@ static int launch_gram_shape(const Batch& bt, const GramArgs& ga_in, hipStream_t
     return PACT_OK;
 }
 
-// The tiles.  256 x 256 has the best ratio of flops to bytes fetched, but its launch lasts as long as a
-// tile (23 us at a key width of 512) however few there are.  bf16 tiles take turns at the matrix cores from key rows of
-// 2 KB on: the loop over a row of 7 KB got 5% shorter, over one of 1 KB the two turns' offset cost 0.8 us.
-// (Both are then near what the chip's power allows: a slice of random keys takes 1.45 us, of keys that
-// are mostly zeros 1.10 us, its MFMAs alone 1.02 us.)
+// The tiles.  256 x 256 has the best ratio of flops to bytes fetched; a launch lasts as many turns of 20 us (key
+// width 512) as its CUs have tiles.  Of the 128 x 128 tiles by four wavefronts a CU runs two at a time, one's
+// epilogue beside the other's multiplications: 11.4 us a turn for half the area, but a launch with
+// few tiles is over in 10, and the triangle of a sample divides better into turns.  gram_cost() has
+// what was measured (us, per turn and slice of 64 elements):
+//   4010 kept tokens 23 (256) / 25 (128), 1604: 18.5 / 11.4, 9012: 65 / 57, 8 x 3450: 81 / 69, 16 x 1604: 44 / 41
+// bf16 tiles of 256 take turns at the matrix cores from key rows of 2 KB on: the loop over a row of 7 KB got 5%
+// shorter, over one of 1 KB the two turns' offset cost 0.8 us.  (Both are then near what the chip's
+// power allows: a slice of random keys takes 1.45 us, of keys that are mostly zeros 1.10 us, its MFMAs alone 1.02 us.)
 typedef Shape<PACT_BF16, 4, 2, 2, 4, 2, false> Tile256;
 typedef Shape<PACT_BF16, 4, 2, 2, 4, 2, true> Tile256Wide;
-typedef Shape<PACT_BF16, 2, 2, 2, 4, 3, false> Tile128x256;
+typedef Shape<PACT_BF16, 2, 2, 2, 2, 2, false> Tile128;
 typedef Shape<PACT_I8X3, 1, 2, 4, 2, 3, true> TileI8;         // density pass
 typedef Shape<PACT_I8X3, 2, 1, 2, 4, 3, true> TileI8Cand;     // candidate pass (groups of 64 rows)
 constexpr int WIDE_KEYS = 1024;
+
+static double gram_cost(const Batch& bt, bool density, int tile, int dk, bool mirrored) {
+    const int slots = tile == 256 ? 256 : 512;
+    long tiles[PACT_MAX_BATCH], all = 0;
+    for (int b = 0; b < bt.B; ++b) all += tiles[b] = tiles_estimate(bt.s[b], density, tile, tile, mirrored);
+    const double slices = (dk + 63) / 64;
+    const long turns = fewest_turns(bt.B, tiles, slots);
+    if (tile == 256) return turns * (8.0 + 1.5 * slices);
+    return all <= 256 ? 6.5 + 0.5 * slices : 3.0 + turns * (5.0 + 0.8 * slices);
+}
 
 template <class SH, int MODE>
 static int launch_gram(const Batch& bt, const GramArgs& ga, hipStream_t st, const char* name, bool mirrored, bool want_stat,
@@ -1049,22 +1072,21 @@ int launch_gram_density(const Batch& bt, const Ws& w, const void* keys, pact_dty
     // The count of kept tokens is known on the device only; what the percentile will leave
     // (n - floor(lambda n), more on ties) tells whether mirrored tiles are likely to pay for
     // some sample.  The kernel decides again from the real count, so a wrong guess costs time only.
-    // (In a batch every sample has its own number of workgroups: the build that can mirror is
-    //  used there whenever the tiles are square.)
-    auto mirrored = [&](int tile) {
+    // (In a batch every sample has its own number of workgroups: the build that can mirror is used there.)
+    auto mirrored = [&](int tile, int slots) {
         const long t = (bt.n_max + tile - 1) / tile;
         bool m = bt.B > 1;
         for (int b = 0; b < bt.B; ++b)
-            m = m || mirrored_tiles_pay((int)((kept_estimate(bt.s[b]) + tile - 1) / tile), gram_grid_x(t * t));
+            m = m || mirrored_tiles_pay((int)((kept_estimate(bt.s[b]) + tile - 1) / tile), gram_grid_x(t * t, slots));
         return m;
     };
-    if (k_dt == PACT_F32) return launch_gram<TileI8, MODE_DENSITY>(bt, ga, st, name, mirrored(128), want_stat, stat_words);
-    const long t1 = (bt.n_max + 255) / 256;
-    if (t1 * t1 * bt.B >= 256) {
-        if (dk >= WIDE_KEYS) return launch_gram<Tile256Wide, MODE_DENSITY>(bt, ga, st, name, mirrored(256), want_stat, stat_words);
-        return launch_gram<Tile256, MODE_DENSITY>(bt, ga, st, name, mirrored(256), want_stat, stat_words);
-    }
-    return launch_gram<Tile128x256, MODE_DENSITY>(bt, ga, st, name, false, want_stat, stat_words);
+    if (k_dt == PACT_F32)
+        return launch_gram<TileI8, MODE_DENSITY>(bt, ga, st, name, mirrored(128, TileI8::SLOTS), want_stat, stat_words);
+    const bool m256 = mirrored(256, Tile256::SLOTS), m128 = mirrored(128, Tile128::SLOTS);
+    if (gram_cost(bt, true, 128, dk, m128) < gram_cost(bt, true, 256, dk, m256))
+        return launch_gram<Tile128, MODE_DENSITY>(bt, ga, st, name, m128, want_stat, stat_words);
+    if (dk >= WIDE_KEYS) return launch_gram<Tile256Wide, MODE_DENSITY>(bt, ga, st, name, m256, want_stat, stat_words);
+    return launch_gram<Tile256, MODE_DENSITY>(bt, ga, st, name, m256, want_stat, stat_words);
 }
 
 int launch_gram_candidates(const Batch& bt, const Ws& w, const void* keys, pact_dtype k_dt, int32_t dk,
@@ -1075,14 +1097,10 @@ int launch_gram_candidates(const Batch& bt, const Ws& w, const void* keys, pact_
     ga.cbest = w.cbest;
     const char* name = "gram_candidates";
     if (k_dt == PACT_F32) return launch_gram<TileI8Cand, MODE_CAND>(bt, ga, st, name, false, false, nullptr);
-    // rows: the centres, columns: the pruned tokens; neither count is known on the host, a
-    // typical split (half pruned, a third of the rest centres) sizes the choice
-    const long tr = (bt.n_max / 6 + 255) / 256, tc = (bt.n_max / 2 + 255) / 256;
-    if (tr * tc * bt.B >= 256) {
-        if (dk >= WIDE_KEYS) return launch_gram<Tile256Wide, MODE_CAND>(bt, ga, st, name, false, false, nullptr);
-        return launch_gram<Tile256, MODE_CAND>(bt, ga, st, name, false, false, nullptr);
-    }
-    return launch_gram<Tile128x256, MODE_CAND>(bt, ga, st, name, false, false, nullptr);
+    if (gram_cost(bt, false, 128, dk, false) < gram_cost(bt, false, 256, dk, false))
+        return launch_gram<Tile128, MODE_CAND>(bt, ga, st, name, false, false, nullptr);
+    if (dk >= WIDE_KEYS) return launch_gram<Tile256Wide, MODE_CAND>(bt, ga, st, name, false, false, nullptr);
+    return launch_gram<Tile256, MODE_CAND>(bt, ga, st, name, false, false, nullptr);
 }
 
 int plan_gram_workgroups(const int32_t* tiles, int32_t batch, uint16_t* wg_map, uint16_t* wg_count) {
@@ -1094,7 +1112,7 @@ int plan_gram_workgroups(const int32_t* tiles, int32_t batch, uint16_t* wg_map, 
         if (tiles[b] < 1) return PACT_ERR_SHAPE;
         t[b] = tiles[b];
     }
-    build_wg_map(batch, t, ga);
+    build_wg_map(batch, t, 8, ga);
     for (int i = 0; i < GRAM_MAX_WORKGROUPS; ++i) wg_map[i] = ga.wg_map[i];
     for (int b = 0; b < batch; ++b) wg_count[b] = ga.wg_count[b];
     return PACT_OK;
