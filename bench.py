@@ -38,12 +38,10 @@ def algorithmic_work(kernel: str, n, h, dk, q, C, n_reinc, key_bytes, hid_bytes,
         return "mfma", float(q) * q * dk, "flop"
     if kernel == "gram_candidates":
         return "mfma", 2.0 * (n - q) * C * dk, "flop"
-    if kernel == "qglobal_hnorm":         # read H once (norms) and the query partials, write norms and the global query
-        return "hbm", n * h * hid_bytes + 512 * n_q * d_h * 8 + n * 8 + n_q * d_h * 8, "B"
     if kernel == "merge_mean":            # read member rows once, write C merged rows
         return "hbm", (q + n_reinc) * h * hid_bytes + C * h * out_bytes, "B"
-    if kernel == "prep":                  # keys and queries read, the kept x kept bitmap cleared
-        return "hbm", n * dk * key_bytes + n * n_q * d_h * key_bytes + q * ((q + 63) // 64) * 8, "B"
+    if kernel == "front":                 # hidden states, keys and queries read once, norms written, the kept x kept bitmap cleared
+        return "hbm", n * h * hid_bytes + n * dk * key_bytes + n * n_q * d_h * key_bytes + n * 16 + q * ((q + 63) // 64) * 8, "B"
     return None, 0.0, ""
 
 
@@ -405,7 +403,7 @@ def main():
     # the bandwidth-bound stages: cold first (nothing of the inputs in any cache), then warm (inputs still in the
     # caches from the previous step)
     hbm_stages = {}
-    for k in ("qglobal_hnorm", "merge_mean", "prep"):
+    for k in ("front", "merge_mean"):
         bound, work, unit = algorithmic_work(k, n, h, dk, q_kept, C, n_re, 2, 2, 4, cfg.n_kv, cfg.d_h)
         if k not in per_launch_us:
             continue

@@ -48,7 +48,7 @@
  *    closer to the threshold than its worst-case rounding error, and always for the final
  *    nearest-centre choice, so those decisions are the fp64 ones.
  *  - Densities (Eq. 6) are fp64 sums of fp32 terms exp2-evaluated from matrix-core cosines
- *    (bf16 keys as they are; fp32 keys as three bf16 parts per value, all 24 bits of them).
+ *    (bf16 keys as they are; fp32 keys as 24-bit integers in three 8-bit planes).
  *    The density order (Alg. 2) only matters between tokens within d_c of each other; where
  *    two such tokens have densities closer than a band of about fifty standard errors of
  *    that fp32 sum, both densities are evaluated again entirely in fp64 (Eq. 5 and Eq. 6 as
@@ -147,7 +147,7 @@ typedef struct {
 #define PACT_MAX_RHO_RECHECK 1024
 
 /* Scratch bytes needed for one call on samples of at most n_max tokens each, `batch`
- * samples, clustering keys of width dk and type k_dt (fp32 keys need room for their three-part
+ * samples, clustering keys of width dk and type k_dt (fp32 keys need room for their integer
  * bf16 form), n_q query heads of width d_h.  0 if an argument is out of range. */
 size_t pact_workspace_bytes(int32_t n_max, int32_t batch, int32_t dk, pact_dtype k_dt, int32_t n_q, int32_t d_h);
 

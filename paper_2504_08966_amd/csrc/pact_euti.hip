@@ -7,564 +7,555 @@
 namespace pact {
 
 // ------------------------------------------------------------------------------------------
-// First kernel of a call.  Three independent jobs share one launch:
-//   blocks [nQ, nQ + nKeyBlocks)      : one wavefront per token: squared key norm (fp64),
-//                                       reciprocal norm (fp32), cleared bitmap row, and the
-//                                       per-token initial state (status, cluster id, counts);
-//   blocks [0, nQ)                    : Eq. 1 pass 1, column sums of one row chunk of Q; rows wider than
-//                                       1024 columns are shared out in groups of 1024 columns
-//                                       (nQ = QG_CHUNKS x groups, or 0 without a query pass).
-// grid (nKeyBlocks + nQ, B), block 256.
-struct PrepArgs {
+// First kernel of a call: everything that reads the inputs once and depends on nothing else.  Three
+// independent jobs share one launch, so that the small ones hide behind the stream of hidden states:
+//   blocks [0, n_q_blocks)            : Eq. 1 pass 1, column sums of one row chunk of Q and 128 bytes of
+//                                       its columns (32 row lanes x 8 lanes of 16 bytes; eight rows in
+//                                       flight per lane).  QG_CHUNKS chunks at most: the logits kernel
+//                                       adds them up again in every workgroup;
+//   blocks [.., + n_key_blocks)       : squared key norm (fp64), reciprocal norm (fp32), fp32 keys' int8
+//                                       planes, cleared bitmap row, per-token initial state (status,
+//                                       cluster id, counts); 16 to 64 lanes per token by the row's width;
+//   the other blocks                  : |h_i|_2 in fp64, one wavefront per token or, for rows of at most
+//                                       4 KB, several tokens per wavefront (eight loads in flight per lane).
+// Keys and hidden states are walked by token of the whole batch (no blocks for the tokens that
+// shorter samples do not have).  Bound by HBM: 7290 tokens of 3584 bf16 with 4 / 28 query heads 67 / 112 MB,
+// 8 x 6272 tokens 462 MB.  grid (blocks), block 256.
+struct FrontArgs {
     const char* keys; int32_t dk;
     const char* q; int32_t qcols;            // q == nullptr: no query pass
-    double* nn; float* rinv; uint64_t* adj; double* rho; double* qg_part;
+    const char* hidden; int32_t h; int32_t h_bf16; int32_t stream;   // hidden == nullptr: no norms
+    double* nn; float* rinv; uint64_t* adj; double* rho; double* qg_part; double* hnorm;
     uint32_t* status; int32_t* ident; int32_t* near_cnt; int32_t* tie_cnt;
     pact_report* rep; int32_t* cluster_id; int32_t* cluster_counts;
     const int32_t* n_idx_dev; uint32_t* zeros;
     char* ksplit;                            // fp32 keys only: the int8 planes for the Gram passes
-    int32_t mode; int32_t n_key_blocks; int32_t n_q_blocks;
+    int32_t mode; int32_t n_q_blocks, n_key_blocks, q_chunks, key_lanes;
 };
 
-template <int KDT, int QDT>
-__global__ __launch_bounds__(256) void prep_kernel(Batch bt, PrepArgs a) {
-    const int b = blockIdx.y;
+// Row chunks of the query sum: 8, or 4 for wide queries, which have blocks enough (every workgroup of the logits
+// kernel reads its columns of all chunks, 32 KB); fewer for short samples (128 rows a chunk).
+static int query_chunks(int n_max, int qcols) {
+    const int most = qcols > 1024 ? QG_CHUNKS / 2 : QG_CHUNKS, want = (n_max + 127) / 128;
+    return want < most ? want : most;
+}
+
+// |h_g|_2 in fp64 of TPW consecutive tokens by one wavefront, 8 / TPW independent 16-byte loads in flight per
+// lane and token.
+template <int HDT, int TPW>
+__device__ __forceinline__ void hnorm_rows(const char* __restrict__ hidden, int h, int g0, int total, int lane,
+                                           double* __restrict__ hnorm, bool stream) {
+    constexpr int HE = Elem<HDT>::EPL, U = 8 / TPW;
+    double ss[TPW][4];
+#pragma unroll
+    for (int t = 0; t < TPW; ++t)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) ss[t][k] = 0.0;
+    for (int e0 = lane * HE; e0 < h; e0 += U * 64 * HE) {
+        uint4 v[TPW][U];
+#pragma unroll
+        for (int t = 0; t < TPW; ++t) {
+            const char* hp = hidden + (size_t)min(g0 + t, total - 1) * (size_t)h * Elem<HDT>::BYTES;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int e = e0 + u * 64 * HE;
+                v[t][u] = (e >= h) ? make_uint4(0, 0, 0, 0)
+                        : stream ? load_once16(hp + (size_t)e * Elem<HDT>::BYTES)
+                                 : *(const uint4*)(hp + (size_t)e * Elem<HDT>::BYTES);
+            }
+        }
+#pragma unroll
+        for (int t = 0; t < TPW; ++t)
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                double x[8];
+                Elem<HDT>::widen(v[t][u], x);
+#pragma unroll
+                for (int k = 0; k < HE; ++k) ss[t][u & 3] = fma(x[k], x[k], ss[t][u & 3]);
+            }
+    }
+#pragma unroll
+    for (int t = 0; t < TPW; ++t) {
+        const double sst = wave_sum_f64((ss[t][0] + ss[t][1]) + (ss[t][2] + ss[t][3]));
+        if (lane == 0 && g0 + t < total) hnorm[g0 + t] = sqrt(sst);
+    }
+}
+// tokens per wavefront for a row of h elements
+__host__ __device__ inline int hnorm_tokens(int h, int elem_bytes) {
+    const int loads = (h * elem_bytes + 1023) / 1024;      // 16-byte loads per lane and row
+    return loads <= 2 ? 4 : loads <= 4 ? 2 : 1;
+}
+template <int HDT>
+__device__ __forceinline__ void hnorm_job(const FrontArgs& a, int wave_no, int total, int lane) {
+    const int tpw = hnorm_tokens(a.h, Elem<HDT>::BYTES), g0 = wave_no * tpw;
+    if (g0 >= total) return;
+    if (tpw == 4) hnorm_rows<HDT, 4>(a.hidden, a.h, g0, total, lane, a.hnorm, a.stream != 0);
+    else if (tpw == 2) hnorm_rows<HDT, 2>(a.hidden, a.h, g0, total, lane, a.hnorm, a.stream != 0);
+    else hnorm_rows<HDT, 1>(a.hidden, a.h, g0, total, lane, a.hnorm, a.stream != 0);
+}
+
+// Sample that token g of the batch belongs to (wave-uniform).
+__device__ __forceinline__ int sample_of(const Batch& bt, int g, int lane) {
+    if (bt.B == 1) return 0;
+    const uint64_t m = __ballot(lane < bt.B && bt.s[lane < bt.B ? lane : 0].base <= g);
+    return __builtin_amdgcn_readfirstlane(__popcll(m) - 1);
+}
+
+// One clustering key by KL lanes (16, 32 or 64; a row of at most KL 16-byte chunks for KL < 64): the
+// values are those of wave_dot64 whatever KL (the lanes it leaves out would add zeros).
+template <int KDT, int KL>
+__device__ __forceinline__ void key_job(const Batch& bt, const FrontArgs& a, int wave_no, int lane) {
+    constexpr int EPL = Elem<KDT>::EPL;
+    const int kl = lane & (KL - 1);
+    const int g0 = wave_no * (64 / KL);
+    if (g0 >= bt.total) return;
+    const int b0 = sample_of(bt, g0, lane);
+    const int gi = g0 + lane / KL;
+    if (gi >= bt.total) return;
+    // (the tokens of a wavefront may straddle samples)
+    int b = b0;
+    if (KL < 64) while (b + 1 < bt.B && bt.s[b + 1].base <= gi) ++b;
     const Seg sg = bt.s[b];
+    const size_t g = (size_t)gi;
+    const int i = gi - sg.base;
+    const char* row = a.keys + g * (size_t)a.dk * Elem<KDT>::BYTES;
+    // (the first two chunks per lane stay in registers: fp32 rows of up to 2 KB are read once for all three of their uses)
+    const uint4 none = make_uint4(0, 0, 0, 0);
+    const uint4 c0 = kl * EPL < a.dk ? *(const uint4*)(row + (size_t)kl * 16) : none;
+    const uint4 c1 = (kl + KL) * EPL < a.dk ? *(const uint4*)(row + (size_t)(kl + KL) * 16) : none;
+    auto chunk = [&](int e) __attribute__((always_inline)) {                 // at element e, a multiple of EPL
+        return e < KL * EPL ? c0 : e < 2 * KL * EPL ? c1 : e < a.dk ? *(const uint4*)(row + (size_t)e * Elem<KDT>::BYTES) : none;
+    };
+    double acc = 0.0;
+    for (int e = kl * EPL; e < a.dk; e += KL * EPL) {
+        double x[8];
+        Elem<KDT>::widen(chunk(e), x);
+#pragma unroll
+        for (int k = 0; k < EPL; ++k) acc = fma(x[k], x[k], acc);
+    }
+    const double v = group_sum_f64(acc, KL);
+    double scale = 1.0;                                    // of the rows the Gram passes read
+    if constexpr (KDT == PACT_F32) {
+        // The row as 24-bit integers X = rint(x S) (S: its largest element becomes 8355711, or a power of
+        // four less for rows of more than 2^17 elements, whose order-0 sums would not fit an int32), split
+        // into three signed bytes; 64 elements are 64 bytes of each plane in turn, padded with zeros.
+        float top = 0.0f;
+        for (int e = kl * 4; e < a.dk; e += 4 * KL) {
+            float x[8];
+            Elem<KDT>::widenf(chunk(e), x);
+            top = fmaxf(fmaxf(top, fmaxf(fabsf(x[0]), fabsf(x[1]))), fmaxf(fabsf(x[2]), fabsf(x[3])));
+        }
+        top = group_max_f32<16>(top);
+#pragma unroll
+        for (int sft = 16; sft < KL; sft <<= 1) top = fmaxf(top, __shfl_xor(top, sft, 64));
+        double most = 8355711.0;
+        for (int64_t d = a.dk; d > 131072; d >>= 2) most *= 0.5;
+        const double S = top > 0.0f ? most / (double)top : 0.0;
+        scale = S;
+        char* sp = a.ksplit + g * (size_t)((a.dk + 63) / 64 * 192);
+        for (int e = kl * 4; e < (a.dk + 63) / 64 * 64; e += 4 * KL) {
+            float x[8];
+            Elem<KDT>::widenf(chunk(e), x);                            // (zeros past the row's end)
+            uint32_t part[3] = {0u, 0u, 0u};
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                int X = (int)rint((double)x[k] * S);
+#pragma unroll
+                for (int pl = 2; pl >= 0; --pl) {
+                    const int byte = (int)(int8_t)(X & 255);
+                    part[pl] |= (uint32_t)(byte & 255) << (8 * k);
+                    X = (X - byte) >> 8;
+                }
+            }
+#pragma unroll
+            for (int pl = 0; pl < 3; ++pl) *(uint32_t*)(sp + (size_t)(e >> 6) * 192 + pl * 64 + (e & 63)) = part[pl];
+        }
+    }
+    // The bitmap is used over (kept tokens) x (kept tokens).  In a full reduction that is
+    // n - m rows and columns unless scores tie at the threshold (Eq. 3 / 4); the split
+    // clears the rest itself in that case.
+    uint64_t* arow = a.adj + ((size_t)b * bt.n_max + i) * bt.W;
+    const int side = (a.mode == INIT_REDUCE) ? sg.n - prune_rank(sg.lambda, sg.n) : sg.n;
+    const int Wn = (i < side) ? (side + 63) >> 6 : 0;
+    for (int k = kl; k < Wn; k += KL) arow[k] = 0ull;
+    if (kl == 0) {
+        a.nn[g] = v;
+        // (fp32 keys: products of the integers in units of 65536)
+        a.rinv[g] = v > 0.0 ? (float)((KDT == PACT_F32 ? 256.0 / scale : 1.0) / sqrt(v)) : 0.0f;
+        if (a.mode == INIT_REDUCE || a.mode == INIT_DBDPC_ALL || a.mode == INIT_DBDPC_SUBSET) {
+            a.status[(size_t)b * bt.n_max + i] = ST_UNKNOWN;
+            a.rho[(size_t)b * bt.n_max + i] = 0.0;
+            a.ident[g] = i;
+            a.cluster_id[g] = -1;
+            if (a.cluster_counts) a.cluster_counts[g] = 0;
+        }
+    }
+}
+
+template <int KDT, int QDT>
+__global__ __launch_bounds__(256) void front_kernel(Batch bt, FrontArgs a) {
     const int lane = threadIdx.x & 63;
-    const int n_q_blocks = a.n_q_blocks;             // the query chunks come first: they are the longer job
-    if ((int)blockIdx.x >= n_q_blocks) {
-        const int kblk = blockIdx.x - n_q_blocks;
-        if (kblk == 0 && b == 0 && threadIdx.x < 64) a.zeros[threadIdx.x] = 0u;
-        if (kblk == 0 && threadIdx.x == 0) {
-            a.near_cnt[2 * b] = 0; a.near_cnt[2 * b + 1] = 0;
-#pragma unroll
-            for (int k = 0; k < 4; ++k) a.tie_cnt[4 * b + k] = 0;
-            pact_report* rp = a.rep + b;
-            const int mode = a.mode;
-            if (mode == INIT_REDUCE || mode == INIT_DBDPC_ALL || mode == INIT_DBDPC_SUBSET) {
-                if (mode != INIT_REDUCE) {
-                    const int k = (mode == INIT_DBDPC_ALL) ? sg.n : min(max(*a.n_idx_dev, 0), sg.n);
-                    rp->n_kept = k;
-                    rp->n_pruned = (mode == INIT_DBDPC_ALL) ? 0 : sg.n - k;
-                }
-                rp->n_centers = 0; rp->rounds = 0; rp->dc_checked_pairs = 0; rp->dc_near_ties = 0;
-                rp->refine_overflow = 0; rp->n_reincorporated = 0; rp->n_dropped = 0;
-                rp->zero_norm_seen = 0;     // counted by the assignment kernels, which run later
-                rp->max_key_distance = 0.0f;
-                rp->rho_rechecked = 0; rp->rho_near_ties = 0;
-                // (a clustering call on a subset follows a split, whose two counters it adds to)
-                if (mode != INIT_DBDPC_SUBSET) { rp->score_near_ties = 0; rp->nonfinite_seen = 0; }
-                rp->reserved[0] = 0;
-            }
-            if (mode == INIT_REINC) { rp->n_reincorporated = 0; rp->n_dropped = 0; }
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    int blk = blockIdx.x;
+    if (blk >= a.n_q_blocks) {
+        blk -= a.n_q_blocks;
+        if (blk >= a.n_key_blocks) {
+            const int wave_no = (blk - a.n_key_blocks) * 4 + wave;
+            if (a.h_bf16) hnorm_job<PACT_BF16>(a, wave_no, bt.total, lane);
+            else hnorm_job<PACT_F32>(a, wave_no, bt.total, lane);
+            return;
         }
-        const int i = kblk * 4 + (threadIdx.x >> 6);
-        if (i >= sg.n) return;
-        const size_t g = (size_t)sg.base + i;
-        const char* row = a.keys + g * (size_t)a.dk * Elem<KDT>::BYTES;
-        const double v = wave_dot64<KDT>(row, row, a.dk, lane);
-        double scale = 1.0;                                    // of the rows the Gram passes read
-        if constexpr (KDT == PACT_F32) {
-            // The row as 24-bit integers X = rint(x S) (S: its largest element becomes 8355711, or a power of
-            // four less for rows of more than 2^17 elements, whose order-0 sums would not fit an int32), split
-            // into three signed bytes; 64 elements are 64 bytes of each plane in turn, padded with zeros.
-            float top = 0.0f;
-            for (int e = lane * 4; e < a.dk; e += 256) {
-                const float4 x = *(const float4*)(row + (size_t)e * 4);
-                top = fmaxf(fmaxf(top, fmaxf(fabsf(x.x), fabsf(x.y))), fmaxf(fabsf(x.z), fabsf(x.w)));
-            }
-            top = group_max_f32<16>(top);
-            top = fmaxf(top, __shfl_xor(top, 16, 64));
-            top = fmaxf(top, __shfl_xor(top, 32, 64));
-            double most = 8355711.0;
-            for (int64_t d = a.dk; d > 131072; d >>= 2) most *= 0.5;
-            const double S = top > 0.0f ? most / (double)top : 0.0;
-            scale = S;
-            char* sp = a.ksplit + g * (size_t)((a.dk + 63) / 64 * 192);
-            for (int e = lane * 4; e < (a.dk + 63) / 64 * 64; e += 256) {
-                const float4 x4 = (e < a.dk) ? *(const float4*)(row + (size_t)e * 4) : make_float4(0.f, 0.f, 0.f, 0.f);
-                const float x[4] = {x4.x, x4.y, x4.z, x4.w};
-                uint32_t part[3] = {0u, 0u, 0u};
+        if (blk == 0) {
+            if (threadIdx.x < 64) a.zeros[threadIdx.x] = 0u;
+            const int b = (int)threadIdx.x;
+            if (b < bt.B) {
+                a.near_cnt[2 * b] = 0; a.near_cnt[2 * b + 1] = 0;
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    int X = (int)rint((double)x[i] * S);
-#pragma unroll
-                    for (int pl = 2; pl >= 0; --pl) {
-                        const int byte = (int)(int8_t)(X & 255);
-                        part[pl] |= (uint32_t)(byte & 255) << (8 * i);
-                        X = (X - byte) >> 8;
+                for (int k = 0; k < 4; ++k) a.tie_cnt[4 * b + k] = 0;
+                pact_report* rp = a.rep + b;
+                const int mode = a.mode, n = bt.s[b].n;
+                if (mode == INIT_REDUCE || mode == INIT_DBDPC_ALL || mode == INIT_DBDPC_SUBSET) {
+                    if (mode != INIT_REDUCE) {
+                        const int k = (mode == INIT_DBDPC_ALL) ? n : min(max(*a.n_idx_dev, 0), n);
+                        rp->n_kept = k;
+                        rp->n_pruned = (mode == INIT_DBDPC_ALL) ? 0 : n - k;
                     }
+                    rp->n_centers = 0; rp->rounds = 0; rp->dc_checked_pairs = 0; rp->dc_near_ties = 0;
+                    rp->refine_overflow = 0; rp->n_reincorporated = 0; rp->n_dropped = 0;
+                    rp->zero_norm_seen = 0;     // counted by the assignment kernels, which run later
+                    rp->max_key_distance = 0.0f;
+                    rp->rho_rechecked = 0; rp->rho_near_ties = 0;
+                    // (a clustering call on a subset follows a split, whose two counters it adds to)
+                    if (mode != INIT_DBDPC_SUBSET) { rp->score_near_ties = 0; rp->nonfinite_seen = 0; }
+                    rp->reserved[0] = 0;
                 }
-#pragma unroll
-                for (int pl = 0; pl < 3; ++pl) *(uint32_t*)(sp + (size_t)(e >> 6) * 192 + pl * 64 + (e & 63)) = part[pl];
+                if (mode == INIT_REINC) { rp->n_reincorporated = 0; rp->n_dropped = 0; }
             }
         }
-        // The bitmap is used over (kept tokens) x (kept tokens).  In a full reduction that is
-        // n - m rows and columns unless scores tie at the threshold (Eq. 3 / 4); the split
-        // clears the rest itself in that case.
-        uint64_t* arow = a.adj + ((size_t)b * bt.n_max + i) * bt.W;
-        const int side = (a.mode == INIT_REDUCE) ? sg.n - prune_rank(sg.lambda, sg.n) : sg.n;
-        const int Wn = (i < side) ? (side + 63) >> 6 : 0;
-        for (int k = lane; k < Wn; k += 64) arow[k] = 0ull;
-        if (lane == 0) {
-            a.nn[g] = v;
-            // (fp32 keys: products of the integers in units of 65536)
-            a.rinv[g] = v > 0.0 ? (float)((KDT == PACT_F32 ? 256.0 / scale : 1.0) / sqrt(v)) : 0.0f;
-            if (a.mode == INIT_REDUCE || a.mode == INIT_DBDPC_ALL || a.mode == INIT_DBDPC_SUBSET) {
-                a.status[(size_t)b * bt.n_max + i] = ST_UNKNOWN;
-                a.rho[(size_t)b * bt.n_max + i] = 0.0;
-                a.ident[g] = i;
-                a.cluster_id[g] = -1;
-                if (a.cluster_counts) a.cluster_counts[g] = 0;
-            }
-        }
+        const int wave_no = blk * 4 + wave;
+        if (a.key_lanes == 16) key_job<KDT, 16>(bt, a, wave_no, lane);
+        else if (a.key_lanes == 32) key_job<KDT, 32>(bt, a, wave_no, lane);
+        else key_job<KDT, 64>(bt, a, wave_no, lane);
         return;
     }
     // ---- Eq. 1, pass 1
-    const int chunk = blockIdx.x % QG_CHUNKS, cgroup = blockIdx.x / QG_CHUNKS;
-    const int rows_per = (sg.n + QG_CHUNKS - 1) / QG_CHUNKS;
-    const int r0 = chunk * rows_per;
-    const int r1 = min(sg.n, r0 + rows_per);
-    const size_t row_bytes = (size_t)a.qcols * Elem<QDT>::BYTES;
-    double* out = a.qg_part + ((size_t)b * QG_CHUNKS + chunk) * a.qcols;
-    // Four columns per thread.  Rows of at most 512 (256) columns leave half (three quarters) of
-    // the threads without columns: they take every second (fourth) row of the chunk instead, and
-    // the row groups' sums meet in LDS.
-    const int RG = a.qcols <= 256 ? 4 : a.qcols <= 512 ? 2 : 1;
-    const int tpg = 256 / RG;
-    const int rg = threadIdx.x / tpg, ct = threadIdx.x % tpg;
-    __shared__ double s_part[192 * 4];
-    auto sum_rows = [&](int c, double (&acc)[4]) __attribute__((always_inline)) {
-        const char* base = a.q + (size_t)sg.base * row_bytes + (size_t)c * Elem<QDT>::BYTES;
-        for (int r = r0 + rg; r < r1; r += 8 * RG) {
-            float f[8][4];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const bool ok = r + u * RG < r1;
-                const char* p = base + (size_t)(ok ? r + u * RG : r0) * row_bytes;
-                if (QDT == PACT_BF16) {
-                    const uint2 v = *(const uint2*)p;
-                    f[u][0] = __uint_as_float(v.x << 16); f[u][1] = __uint_as_float(v.x & 0xFFFF0000u);
-                    f[u][2] = __uint_as_float(v.y << 16); f[u][3] = __uint_as_float(v.y & 0xFFFF0000u);
-                } else {
-                    const float4 v = *(const float4*)p;
-                    f[u][0] = v.x; f[u][1] = v.y; f[u][2] = v.z; f[u][3] = v.w;
-                }
-                if (!ok) { f[u][0] = f[u][1] = f[u][2] = f[u][3] = 0.0f; }
-            }
-#pragma unroll
-            for (int u = 0; u < 8; ++u)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) acc[i] += (double)f[u][i];
-        }
-    };
-    if (RG == 1) {
-        const int c = cgroup * 1024 + threadIdx.x * 4;
-        if (c < a.qcols) {
-            double acc[4] = {0.0, 0.0, 0.0, 0.0};
-            sum_rows(c, acc);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) out[c + i] = acc[i];
-        }
-        return;
-    }
-    const int c = ct * 4;
+    constexpr int EPL = Elem<QDT>::EPL, CW = 8 * EPL;            // columns of a block
+    __shared__ double s_part[32][CW];
+    const int ngroups = (a.qcols + CW - 1) / CW;
+    const int cgroup = blk % ngroups, bc = blk / ngroups;
+    const int b = bc / a.q_chunks, chunk = bc % a.q_chunks;
+    const Seg sg = bt.s[b];
+    const int rows_per = (sg.n + a.q_chunks - 1) / a.q_chunks;
+    const int r0 = chunk * rows_per, r1 = min(sg.n, r0 + rows_per);
+    const int rl = threadIdx.x >> 3, cl = threadIdx.x & 7;
+    const int c = cgroup * CW + cl * EPL;
     const bool act = c < a.qcols;
-    double acc[4] = {0.0, 0.0, 0.0, 0.0};
-    if (act) sum_rows(c, acc);
-    if (act && rg > 0) {
+    const size_t row_bytes = (size_t)a.qcols * Elem<QDT>::BYTES;
+    const char* base = a.q + (size_t)sg.base * row_bytes + (size_t)(act ? c : 0) * Elem<QDT>::BYTES;
+    double acc[EPL];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) s_part[((rg - 1) * tpg + ct) * 4 + i] = acc[i];
-    }
-    __syncthreads();
-    if (act && rg == 0) {
-        for (int g = 1; g < RG; ++g)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) acc[i] += s_part[((g - 1) * tpg + ct) * 4 + i];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) out[c + i] = acc[i];
-    }
-}
-
-// |h_g|_2 in fp64 by one wavefront (8 independent 16-byte loads in flight per lane).
-template <int HDT>
-__device__ __forceinline__ void hnorm_row(const char* __restrict__ hidden, int h, size_t g, int lane,
-                                          double* __restrict__ hnorm, bool stream) {
-    const char* hp = hidden + g * (size_t)h * Elem<HDT>::BYTES;
-    constexpr int HE = Elem<HDT>::EPL;
-    double ss[4] = {0.0, 0.0, 0.0, 0.0};
-    for (int e0 = lane * HE; e0 < h; e0 += 8 * 64 * HE) {
+    for (int k = 0; k < EPL; ++k) acc[k] = 0.0;
+    for (int r = r0 + rl; r < r1; r += 32 * 8) {
         uint4 v[8];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int e = e0 + u * 64 * HE;
-            v[u] = (e >= h) ? make_uint4(0, 0, 0, 0)
-                 : stream ? load_once16(hp + (size_t)e * Elem<HDT>::BYTES)
-                          : *(const uint4*)(hp + (size_t)e * Elem<HDT>::BYTES);
-        }
+        for (int u = 0; u < 8; ++u) v[u] = r + 32 * u < r1 ? *(const uint4*)(base + (size_t)(r + 32 * u) * row_bytes) : make_uint4(0, 0, 0, 0);
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
             double x[8];
-            Elem<HDT>::widen(v[u], x);
+            Elem<QDT>::widen(v[u], x);
 #pragma unroll
-            for (int k = 0; k < HE; ++k) ss[u & 3] = fma(x[k], x[k], ss[u & 3]);
+            for (int k = 0; k < EPL; ++k) acc[k] += x[k];
         }
     }
-    const double sst = wave_sum_f64((ss[0] + ss[1]) + (ss[2] + ss[3]));
-    if (lane == 0) hnorm[g] = sqrt(sst);
-}
-// The norms are split over two launches: tokens below hnorm_split(n, share) go with the global
-// query, the others with the logits (share in 256ths; a multiple of the 16 tokens of a block).
-__host__ __device__ __forceinline__ int hnorm_split(int n, int share) {
-    const int s = (((n * share) >> 8) + SCORE_TOK_PER_WG - 1) & ~(SCORE_TOK_PER_WG - 1);
-    return s < n ? s : n;
-}
-
-// Eq. 1, pass 2, and the hidden-state norms of Eq. 2, two independent jobs in one launch (the
-// first is a handful of blocks; the second streams H, the stage's one large read, which needs
-// neither the global query nor the logits and so need not wait for them):
-//   blocks [0, nq_blocks): the global query - the chunk partials summed in a fixed order and
-//       divided by n (64 columns x 16 slices of the chunk range per block), or, when the caller
-//       supplied the global query ([B, qcols]), its widening to fp64 (1024 columns per block);
-//   the other blocks: |h_i|_2 in fp64, one wavefront per token, 16 tokens per block.
-// grid (nq_blocks + ceil(n_max/16), B), block 1024.
-// Where column c of the global query goes.  The logits kernel for grouped-query heads wants it
-// laid out as its lanes read it (see there): element k of 16-byte chunk cc of query head
-// kvh * rep + r at ((r * epl + k) * n_kv + kvh) * lph + cc; rep == 0: as it is.
-struct QgLayout {
-    int rep, n_kv, d_h, lph, epl;
-    __device__ __forceinline__ int at(int c) const {
-        if (rep == 0) return c;
-        const int j = c / d_h, e = c - j * d_h;
-        return (((j % rep) * epl + (e % epl)) * n_kv + j / rep) * lph + e / epl;
+#pragma unroll
+    for (int k = 0; k < EPL; ++k) s_part[rl][cl * EPL + k] = acc[k];
+    __syncthreads();
+    const int oc = cgroup * CW + (int)threadIdx.x;
+    if ((int)threadIdx.x < CW && oc < a.qcols) {
+        double t = 0.0;
+#pragma unroll
+        for (int k = 0; k < 32; ++k) t += s_part[k][threadIdx.x];
+        a.qg_part[((size_t)b * QG_CHUNKS + chunk) * a.qcols + oc] = t;
     }
-};
-
-template <int HDT, int QDT>
-__global__ __launch_bounds__(1024) void qglobal_hnorm_kernel(Batch bt, int qcols, int q_per_token, int nq_blocks,
-                                                             QgLayout lay,
-                                                             const double* __restrict__ qg_part,
-                                                             const char* __restrict__ q_given,
-                                                             double* __restrict__ qg,
-                                                             const char* __restrict__ hidden, int h,
-                                                             double* __restrict__ hnorm, int hshare, int stream) {
-    __shared__ double s_p[16][64];
-    const int b = blockIdx.y;
-    const Seg sg = bt.s[b];
-    if ((int)blockIdx.x < nq_blocks) {
-        if (q_per_token) {
-            const int cl = threadIdx.x & 63, slice = threadIdx.x >> 6;
-            const int c = blockIdx.x * 64 + cl;
-            constexpr int PER = QG_CHUNKS / 16;
-            double acc = 0.0;
-            if (c < qcols) {
-                const double* in = qg_part + ((size_t)b * QG_CHUNKS + slice * PER) * qcols + c;
-                double v[PER];
-#pragma unroll
-                for (int k = 0; k < PER; ++k) v[k] = in[(size_t)k * qcols];
-#pragma unroll
-                for (int k = 0; k < PER; ++k) acc += v[k];
-            }
-            s_p[slice][cl] = acc;
-            __syncthreads();
-            if (slice == 0 && c < qcols) {
-                double t = 0.0;
-#pragma unroll
-                for (int k = 0; k < 16; ++k) t += s_p[k][cl];
-                qg[(size_t)b * qcols + lay.at(c)] = t / (double)sg.n;
-            }
-        } else {
-            const int c = blockIdx.x * 1024 + threadIdx.x;
-            if (c < qcols) {
-                const char* p = q_given + ((size_t)b * qcols + c) * Elem<QDT>::BYTES;
-                float f;
-                if (QDT == PACT_BF16) f = __uint_as_float((uint32_t)(*(const uint16_t*)p) << 16);
-                else f = *(const float*)p;
-                qg[(size_t)b * qcols + lay.at(c)] = (double)f;
-            }
-        }
-        return;
-    }
-    const int i = (blockIdx.x - nq_blocks) * SCORE_TOK_PER_WG + (threadIdx.x >> 6);
-    if (i >= hnorm_split(sg.n, hshare)) return;
-    hnorm_row<HDT>(hidden, h, (size_t)sg.base + i, threadIdx.x & 63, hnorm, stream != 0);
-}
-
-constexpr int LOGITS_MAX_REP = 8;        // query heads per key head that the grouped fast path handles
-constexpr int LOGITS_QG_LDS = 4096;      // columns of the global query that its LDS copy holds
-// key row of at most 1 KB, a power-of-two number of whole 16-byte chunks per head
-__host__ __device__ inline bool logits_shaped(int n_kv, int d_h, int elem_bytes) {
-    const int lph = d_h * elem_bytes / 16;
-    return (size_t)n_kv * d_h * elem_bytes <= 1024 && lph * 16 == d_h * elem_bytes && lph >= 1 && (lph & (lph - 1)) == 0;
-}
-__host__ __device__ inline bool logits_grouped(int n_kv, int n_q, int d_h, int elem_bytes) {
-    const int rep = n_q / n_kv;
-    return rep > 1 && rep <= LOGITS_MAX_REP && logits_shaped(n_kv, d_h, elem_bytes) && n_q * d_h <= LOGITS_QG_LDS;
 }
 
 // ------------------------------------------------------------------------------------------
-// Eq. 2, pass 1: one wavefront per token computes the n_q logits k_i^(g(j)) . Qg^(j); the
-// workgroup (SCORE_TOK_PER_WG tokens) then leaves one online-softmax partial (max, sum of exp)
-// per head.  grid (ceil(n_max/16), B), block 1024.
-template <int KDT, int HDT, bool GROUPED>
-__global__ __launch_bounds__(1024) void score_logits_kernel(Batch bt, const char* __restrict__ keys, int n_kv, int d_h,
-                                                            int n_q, const double* __restrict__ qg,
-                                                            double* __restrict__ logits,
-                                                            double* __restrict__ sm_part, int n_logit_blocks,
-                                                            const char* __restrict__ hidden, int h,
-                                                            double* __restrict__ hnorm, int hshare, int stream) {
-    __shared__ double s_l[SCORE_TOK_PER_WG][PACT_MAX_QHEADS];
-    __shared__ double s_qg[GROUPED ? LOGITS_QG_LDS : 1];
+// Eq. 1, pass 2 and Eq. 2, pass 1.  A workgroup takes SCORE_TOK tokens and one key head (BY_MFMA) or a group of
+// them: it adds up the chunk sums of its columns of the global query (or widens the one the caller
+// passed) into LDS, computes the logits k_i^(g(j)) . Qg^(j) and leaves, per query head, the largest logit of
+// its tokens, the sum of exp(logit - largest), and every token's exp(logit - largest).
+// BY_MFMA (three to 16 query heads per key head, heads of whole 64-byte quarters): 16 tokens x 16 query heads per
+// wavefront on v_mfma_f64_16x16x4_f64; lane l supplies token (query head) l % 16, elements of quarter l / 16
+// of the head.  The vector units spent four instructions on conversion, LDS and lane sums for every
+// multiplication (28 query heads over 4: 17.7 -> 13.2 us); with one query head per key head they are the faster way
+// (8 videos 27.6 against 23.6 us).
+// BY_LANES (one query head per key head, a power-of-two number of 16-byte chunks per head, at most 64): the
+// lanes that hold a token's keys of the group multiply by elements of the global query in their registers; 64 / LT tokens at a time.
+// BY_HEAD: any shape; a token per wavefront, one head after the other (and if a key head's columns do not fit
+// the LDS, the chunk sums are added up where they are used).
+// A launch of its own that added the chunk sums up cost 2.3 us and hid the norms' stream from the keys'.
+// grid (ceil(n_max / SCORE_TOK) x groups, B), block 256.
+constexpr int LOGITS_COLS_ANY = 15360;   // columns of the global query that fit the LDS
+constexpr int LOGITS_HEADS = 16;         // query heads of a workgroup, but for BY_HEAD
+enum { BY_HEAD = 0, BY_LANES = 1, BY_MFMA = 2 };
+struct LogitsArgs {
+    const char* keys; int32_t n_kv, d_h, n_q;
+    const double* qg_part; const char* q_given; int32_t q_bf16, q_chunks;     // q_given: the caller's global query
+    double* expl; double* sm_part;
+    int32_t kv_heads, qg_lds;            // key heads per group; whether their columns are in LDS
+};
+// Key heads per workgroup of BY_HEAD.
+static int logits_kv_heads_any(int n_kv, int n_q, int d_h) {
+    for (int k = n_kv; k > 1; --k)
+        if (n_kv % k == 0 && k * (n_q / n_kv) * d_h <= LOGITS_COLS_ANY) return k;
+    return 1;
+}
+static int logits_way(int n_kv, int n_q, int d_h, int elem_bytes) {
+    const int lph = d_h * elem_bytes / 16, rep = n_q / n_kv;
+    if (rep == 1 && lph * 16 == d_h * elem_bytes && lph >= 1 && lph <= 64 && (lph & (lph - 1)) == 0) return BY_LANES;
+    if (d_h * elem_bytes % 64 == 0 && rep <= LOGITS_HEADS && rep * (d_h + 8) <= LOGITS_COLS_ANY) return BY_MFMA;
+    return BY_HEAD;
+}
+
+// Key heads per workgroup of BY_LANES: as many as the lanes hold, but 512 workgroups where the call has them (one image:
+// 11.7 us with four heads a workgroup).
+static int logits_kv_heads_lanes(const Batch& bt, int n_kv, int lph) {
+    const long blocks = (bt.total + SCORE_TOK - 1) / SCORE_TOK;
+    int best = 1;
+    for (int k = 2; k <= n_kv && k <= LOGITS_HEADS && k * lph <= 64; ++k)
+        if (n_kv % k == 0 && blocks * (n_kv / k) >= 512) best = k;
+    return best;
+}
+
+template <int KDT, int WAY>
+__global__ __launch_bounds__(256) void score_logits_kernel(Batch bt, LogitsArgs a) {
+    constexpr int EPL = Elem<KDT>::EPL;
+    constexpr int HEADS = WAY == BY_HEAD ? PACT_MAX_QHEADS : LOGITS_HEADS;
+    extern __shared__ double s_qg[];     // BY_MFMA: [rep][4 quarters, padded]; otherwise [columns]
+    __shared__ double s_l[HEADS][SCORE_TOK + 1];
     const int b = blockIdx.y;
     const Seg sg = bt.s[b];
-    const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
-    if ((int)blockIdx.x >= n_logit_blocks) {
-        // the rest of the hidden-state norms (independent of the logits; rides in this launch)
-        const int i = hnorm_split(sg.n, hshare) + ((int)blockIdx.x - n_logit_blocks) * SCORE_TOK_PER_WG + wave;
-        if (i < sg.n) hnorm_row<HDT>(hidden, h, (size_t)sg.base + i, lane, hnorm, stream != 0);
-        return;
-    }
-    const int t0 = blockIdx.x * SCORE_TOK_PER_WG;
+    const int n_groups = a.n_kv / a.kv_heads;
+    const int tb = blockIdx.x / n_groups, kv0 = (blockIdx.x - tb * n_groups) * a.kv_heads;
+    const int t0 = tb * SCORE_TOK;
     if (t0 >= sg.n) return;
-    const int qcols = n_q * d_h;
-    const int rep = n_q / n_kv;
-    const double* qgb = qg + (size_t)b * qcols;
-    const size_t krow = (size_t)n_kv * d_h * Elem<KDT>::BYTES;
-
-    // Fast paths (the usual shapes: key row of at most 1 KB, a power-of-two number of 16-byte
-    // chunks per head): the whole key row is one load per lane and a head's logit is a reduction
-    // over the few lanes that hold it.  `fast`: one query head per key head.  GROUPED (its own
-    // build; the host checks logits_grouped()): up to LOGITS_MAX_REP query heads per key head
-    // (grouped-query attention); a lane then forms the partial logits of all query heads of its
-    // key head, against a copy of the global query in LDS.
-    const int lph = (int)((size_t)d_h * Elem<KDT>::BYTES / 16);      // lanes (chunks) per head
-    const bool fast = rep == 1 && logits_shaped(n_kv, d_h, Elem<KDT>::BYTES);
-    const int i = t0 + wave;
-    if constexpr (GROUPED) {
-        // The copy is laid out so that the lanes of a wavefront read neighbouring words: element k
-        // of chunk cc of query head kvh * rep + r sits at ((r * EPL + k) * n_kv + kvh) * lph + cc,
-        // i.e. at (r * EPL + k) * (lanes that hold the key row) + (the lane that needs it).
-        constexpr int EPL = Elem<KDT>::EPL;
-        const int klanes = n_kv * lph;
-        for (int c = threadIdx.x; c < qcols; c += 1024) s_qg[c] = qgb[c];      // (left in this order by the kernel before)
-        __syncthreads();
-        if (i < sg.n) {
-            const size_t g = (size_t)sg.base + i;
-            const bool klane = lane < klanes;
-            const int kvh = lane / lph;
-            double acc[LOGITS_MAX_REP];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int rep = a.n_q / a.n_kv, qcols = a.n_q * a.d_h;
+    const int j0 = kv0 * rep, heads = a.kv_heads * rep, cols = heads * a.d_h;     // this workgroup's query heads and columns
+    const size_t krow = (size_t)a.n_kv * a.d_h * Elem<KDT>::BYTES;
+    // this lane's first keys are requested ahead of the global query.  BY_MFMA: its quarter of its token's row (8 chunks of it);
+    // BY_LANES: its chunk of the rows of 8 tokens
+    const int l16 = lane & 15, quarter = lane >> 4;
+    const int qlen = a.d_h >> 2, qchunks = qlen / EPL;
+    const int LT = WAY == BY_LANES ? a.kv_heads * (a.d_h / EPL) : 64, tpp = 64 / LT, tin = lane / LT, lt = lane - tin * LT;
+    const char* kq = a.keys + ((size_t)sg.base + min(t0 + wave * 16 + l16, sg.n - 1)) * krow +
+                     (size_t)(kv0 * a.d_h + quarter * qlen) * Elem<KDT>::BYTES;
+    uint4 kv[8];
+    auto fetch = [&](int i0) __attribute__((always_inline)) {
 #pragma unroll
-            for (int r = 0; r < LOGITS_MAX_REP; ++r) acc[r] = 0.0;
-            if (klane) {
-                const uint4 kv = *(const uint4*)(keys + g * krow + (size_t)lane * 16);
-                double x[8];
-                Elem<KDT>::widen(kv, x);
-#pragma unroll
-                for (int r = 0; r < LOGITS_MAX_REP; ++r)
-                    if (r < rep) {
-#pragma unroll
-                        for (int k = 0; k < EPL; ++k) acc[r] = fma(x[k], s_qg[(r * EPL + k) * klanes + lane], acc[r]);
-                    }
-            }
-#pragma unroll
-            for (int r = 0; r < LOGITS_MAX_REP; ++r)
-                if (r < rep) acc[r] = group_sum_f64(acc[r], lph);
-            if (klane && (lane & (lph - 1)) == 0) {
-#pragma unroll
-                for (int r = 0; r < LOGITS_MAX_REP; ++r)
-                    if (r < rep) {
-                        logits[g * n_q + kvh * rep + r] = acc[r];
-                        s_l[wave][kvh * rep + r] = acc[r];
-                    }
+        for (int u = 0; u < 8; ++u) {
+            if constexpr (WAY == BY_MFMA) kv[u] = i0 + u < qchunks ? *(const uint4*)(kq + (i0 + u) * 16) : make_uint4(0, 0, 0, 0);
+            if constexpr (WAY == BY_LANES) {
+                const int t = t0 + wave * 16 + (i0 + u) * tpp + tin;
+                kv[u] = tin < tpp && (i0 + u) * tpp < 16 && t < sg.n
+                    ? *(const uint4*)(a.keys + ((size_t)sg.base + t) * krow + (size_t)(kv0 * a.d_h + lt * EPL) * Elem<KDT>::BYTES)
+                    : make_uint4(0, 0, 0, 0);
             }
         }
-    } else if (i < sg.n) {
-        const size_t g = (size_t)sg.base + i;
-        const char* kp = keys + g * krow;
-        if (fast) {
-            // lane l holds elements [l * EPL, (l + 1) * EPL) of the row, i.e. of head l / lph
-            const bool klane = (size_t)lane * 16 < krow;
-            double acc = 0.0;
-            if (klane) {
-                const uint4 kv = *(const uint4*)(kp + (size_t)lane * 16);
-                double x[8];
-                Elem<KDT>::widen(kv, x);
-                const double* qq = qgb + lane * Elem<KDT>::EPL;
+    };
+    fetch(0);
+    // column j0 d_h + c of the global query
+    auto query = [&](int c) __attribute__((always_inline)) {
+        if (a.q_given) {
+            const size_t at = (size_t)b * qcols + j0 * a.d_h + c;
+            return a.q_bf16 ? (double)__uint_as_float((uint32_t)((const uint16_t*)a.q_given)[at] << 16) : (double)((const float*)a.q_given)[at];
+        }
+        const double* in = a.qg_part + (size_t)b * QG_CHUNKS * qcols + j0 * a.d_h + c;
+        double p[QG_CHUNKS], v = 0.0;
 #pragma unroll
-                for (int k = 0; k < Elem<KDT>::EPL; ++k) acc = fma(x[k], qq[k], acc);
-            }
-            acc = group_sum_f64(acc, lph);
-            if (klane && (lane & (lph - 1)) == 0) {
-                const int j = lane / lph;
-                logits[g * n_q + j] = acc;
-                s_l[wave][j] = acc;
-            }
-        } else {
-            // per-head logits, one head after the other
-            for (int j = 0; j < n_q; ++j) {
-                const int kvh = j / rep;
-                double acc = 0.0;
-                for (int e = lane * Elem<KDT>::EPL; e < d_h; e += 64 * Elem<KDT>::EPL) {
-                    const uint4 v = *(const uint4*)(kp + (size_t)(kvh * d_h + e) * Elem<KDT>::BYTES);
-                    double x[8];
-                    Elem<KDT>::widen(v, x);
-                    const double* qq = qgb + j * d_h + e;
+        for (int k = 0; k < QG_CHUNKS; ++k) p[k] = k < a.q_chunks ? in[(size_t)k * qcols] : 0.0;
 #pragma unroll
-                    for (int k = 0; k < Elem<KDT>::EPL; ++k) acc = fma(x[k], qq[k], acc);
-                }
-                acc = wave_sum_f64(acc);
-                if (lane == 0) {
-                    logits[g * n_q + j] = acc;
-                    s_l[wave][j] = acc;
-                }
-            }
+        for (int k = 0; k < QG_CHUNKS; ++k) v += p[k];
+        return v / (double)sg.n;
+    };
+    // (a head's quarters one word apart from whole multiples of the LDS banks, the heads another: 64 different banks)
+    const int qpitch = qlen + 1, hpitch = 4 * qpitch + 1;
+    if (WAY != BY_HEAD || a.qg_lds) {
+#pragma unroll 2
+        for (int c = threadIdx.x; c < cols; c += 256) {
+            const double v = query(c);
+            if constexpr (WAY == BY_MFMA) {
+                const int r = c / a.d_h, e = c - r * a.d_h, qt = e / qlen;
+                s_qg[r * hpitch + qt * qpitch + (e - qt * qlen)] = v;
+            } else s_qg[c] = v;
         }
     }
     __syncthreads();
-    // the workgroup's softmax partial per head: thread (head j, token t) = 16 * j + t takes one
-    // exponential, the 16 lanes of a head combine (SCORE_TOK_PER_WG * PACT_MAX_QHEADS threads at most)
-    static_assert(SCORE_TOK_PER_WG == 16 && SCORE_TOK_PER_WG * PACT_MAX_QHEADS <= 1024, "one thread per (token, head)");
-    {
-        const int j = threadIdx.x >> 4, t = threadIdx.x & 15;
-        const int cnt = min(SCORE_TOK_PER_WG, sg.n - t0);
-        if (j < n_q) {                                             // (whole groups of 16 lanes take the branch)
-            const double v = t < cnt ? s_l[t][j] : -INFINITY;
-            double m = v;
-            m = group_max_f64<16>(m);
-            double e = t < cnt ? exp(v - m) : 0.0;
-            e = group_sum_f64(e, 16);
-            if (t == 0) {
-                const int smwg = (bt.n_max + SCORE_TOK_PER_WG - 1) / SCORE_TOK_PER_WG;
-                double* out = sm_part + (((size_t)b * smwg + blockIdx.x) * n_q + j) * 2;
-                out[0] = m;
-                out[1] = e;
+    if constexpr (WAY == BY_LANES) {
+        const int lph = a.d_h / EPL;
+        double qv[EPL];
+#pragma unroll
+        for (int k = 0; k < EPL; ++k) qv[k] = s_qg[lt * EPL + k];
+#pragma unroll 1
+        for (int i0 = 0; i0 * tpp < 16; i0 += 8) {
+            if (i0 > 0) fetch(i0);
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                if ((i0 + u) * tpp >= 16) break;                         // (uniform)
+                double x[8], acc = 0.0;
+                Elem<KDT>::widen(kv[u], x);
+#pragma unroll
+                for (int k = 0; k < EPL; ++k) acc = fma(x[k], qv[k], acc);
+                acc = group_sum_f64(acc, lph);
+                const int tl = (i0 + u) * tpp + tin;
+                if (tin < tpp && tl < 16 && (lt & (lph - 1)) == 0) s_l[lt / lph][wave * 16 + tl] = acc;
             }
         }
-    }
-}
-
-// (max, normaliser) of one head from the workgroup partials, by one wavefront: every lane
-// loads its (max, sum) pairs 8 at a time, then the usual two-step combine.
-__device__ __forceinline__ void combine_softmax_partials(const double* part, int nwg, int stride, int lane,
-                                                         double& M, double& Z) {
-    // the first 512 pairs stay in registers between the two steps (one fetch, not two)
-    double2 v0[8];
+    } else if constexpr (WAY == BY_MFMA) {
+        typedef double f64x4_t __attribute__((ext_vector_type(4)));
+        f64x4_t acc = {0.0, 0.0, 0.0, 0.0};
+        const double* qv = s_qg + min(l16, rep - 1) * hpitch + quarter * qpitch;
+        for (int c0 = 0; c0 < qchunks; c0 += 8) {
+            if (c0 > 0) fetch(c0);
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-        const int w = lane + 64 * u;
-        v0[u] = (w < nwg) ? *(const double2*)(part + (size_t)w * stride) : make_double2(-INFINITY, 0.0);
-    }
-    double m = -INFINITY;
+            for (int u = 0; u < 8; ++u) {
+                if (c0 + u >= qchunks) break;                            // (uniform)
+                double x[8];
+                Elem<KDT>::widen(kv[u], x);
 #pragma unroll
-    for (int u = 0; u < 8; ++u) m = fmax(m, v0[u].x);
-    for (int w0 = lane + 512; w0 < nwg; w0 += 512) {
-        double2 v[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int w = w0 + 64 * u;
-            v[u] = (w < nwg) ? *(const double2*)(part + (size_t)w * stride) : make_double2(-INFINITY, 0.0);
+                for (int k = 0; k < EPL; ++k)
+                    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(x[k], qv[(c0 + u) * EPL + k], acc, 0, 0, 0);
+            }
         }
+        // this lane's results: tokens 4 v + lane / 16 of the wavefront's sixteen, query head lane % 16
+        if (l16 < rep) {
 #pragma unroll
-        for (int u = 0; u < 8; ++u) m = fmax(m, v[u].x);
-    }
-    m = wave_max_f64(m);
-    double z = 0.0;
-#pragma unroll
-    for (int u = 0; u < 8; ++u) z += (v0[u].y != 0.0) ? v0[u].y * exp(v0[u].x - m) : 0.0;
-    for (int w0 = lane + 512; w0 < nwg; w0 += 512) {
-        double2 v[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int w = w0 + 64 * u;
-            v[u] = (w < nwg) ? *(const double2*)(part + (size_t)w * stride) : make_double2(-INFINITY, 0.0);
-        }
-#pragma unroll
-        for (int u = 0; u < 8; ++u) z += (v[u].y != 0.0) ? v[u].y * exp(v[u].x - m) : 0.0;
-    }
-    M = m;
-    Z = wave_sum_f64(z);
-}
-
-// ------------------------------------------------------------------------------------------
-// Eq. 2, pass 2 for many query heads, first half: (max, normaliser) of every head, once per sample
-// (left to every workgroup of the kernel below, the n_q * n / 16 exponentials of the combine are
-// most of that kernel's time from a dozen heads on).  mz: [B][n_q][2].  grid (n_q, B), block 64.
-__global__ __launch_bounds__(64) void softmax_combine_kernel(Batch bt, int n_q, const double* __restrict__ sm_part,
-                                                             double* __restrict__ mz) {
-    const int b = blockIdx.y, j = blockIdx.x;
-    const Seg sg = bt.s[b];
-    if (sg.n <= 0) return;
-    const int smwg = (bt.n_max + SCORE_TOK_PER_WG - 1) / SCORE_TOK_PER_WG;
-    const int nwg = (sg.n + SCORE_TOK_PER_WG - 1) / SCORE_TOK_PER_WG;
-    double m, z;
-    combine_softmax_partials(sm_part + ((size_t)b * smwg * n_q + j) * 2, nwg, n_q * 2, threadIdx.x, m, z);
-    if (threadIdx.x == 0) { mz[((size_t)b * n_q + j) * 2] = m; mz[((size_t)b * n_q + j) * 2 + 1] = z; }
-}
-
-// Eq. 2, pass 2: (max, normaliser) per head - combined here from the partials, or read from mz -
-// then s_i = |h_i| * (1/n_q) sum_j exp(l_ij - M_j) / Z_j.
-// A workgroup finishes TOK tokens with TOK * PARTS threads: thread (token, part) takes the heads
-// part, part + PARTS, ... of its token (and its wavefront the heads wave, wave + TOK * PARTS / 64,
-// ... of the combine); the parts of a token meet in LDS and are added in the order of their numbers.
-// grid (ceil(n_max/TOK), B), block TOK * PARTS.
-template <int TOK, int PARTS>
-__global__ __launch_bounds__(TOK * PARTS) void score_final_kernel(Batch bt, int n_q,
-                                                                  const double* __restrict__ logits,
-                                                                  const double* __restrict__ hnorm,
-                                                                  const double* __restrict__ sm_part,
-                                                                  const double* __restrict__ mz,
-                                                                  float* __restrict__ scores) {
-    __shared__ double s_M[PACT_MAX_QHEADS], s_Z[PACT_MAX_QHEADS];
-    __shared__ double s_acc[PARTS > 1 ? PARTS - 1 : 1][TOK];
-    const int b = blockIdx.y;
-    const Seg sg = bt.s[b];
-    if (blockIdx.x * TOK >= sg.n) return;
-    const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
-    const int tok = threadIdx.x % TOK, part = threadIdx.x / TOK;
-    const int smwg = (bt.n_max + SCORE_TOK_PER_WG - 1) / SCORE_TOK_PER_WG;
-    const int nwg = (sg.n + SCORE_TOK_PER_WG - 1) / SCORE_TOK_PER_WG;
-    // this thread's token: its norm and first logits are requested before the partials are
-    // combined (they do not depend on them)
-    const int i = blockIdx.x * TOK + tok;
-    const size_t g = (size_t)sg.base + min(i, sg.n - 1);
-    const double hn = hnorm[g];
-    double lg[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) lg[u] = (part + u * PARTS < n_q) ? logits[g * n_q + part + u * PARTS] : 0.0;
-    if (mz) {
-        if ((int)threadIdx.x < n_q) {
-            s_M[threadIdx.x] = mz[((size_t)b * n_q + threadIdx.x) * 2];
-            s_Z[threadIdx.x] = mz[((size_t)b * n_q + threadIdx.x) * 2 + 1];
+            for (int v = 0; v < 4; ++v) s_l[l16][wave * 16 + 4 * v + quarter] = acc[v];
         }
     } else {
-        for (int j = wave; j < n_q; j += TOK * PARTS / 64) {
-            double m, z;
-            combine_softmax_partials(sm_part + ((size_t)b * smwg * n_q + j) * 2, nwg, n_q * 2, lane, m, z);
-            if (lane == 0) { s_M[j] = m; s_Z[j] = z; }
+        for (int tl = wave; tl < SCORE_TOK && t0 + tl < sg.n; tl += 4) {
+            const char* kp = a.keys + ((size_t)sg.base + t0 + tl) * krow;
+            for (int jl = 0; jl < heads; ++jl) {
+                const int kvh = (j0 + jl) / rep;
+                double acc = 0.0;
+                for (int e = lane * EPL; e < a.d_h; e += 64 * EPL) {
+                    double x[8];
+                    Elem<KDT>::widen(*(const uint4*)(kp + (size_t)(kvh * a.d_h + e) * Elem<KDT>::BYTES), x);
+#pragma unroll
+                    for (int k = 0; k < EPL; ++k) {
+                        const int c = jl * a.d_h + e + k;
+                        acc = fma(x[k], a.qg_lds ? s_qg[c] : query(c), acc);
+                    }
+                }
+                acc = wave_sum_f64(acc);
+                if (lane == 0) s_l[jl][tl] = acc;
+            }
         }
     }
     __syncthreads();
-    // the two ablations of Eq. 2: without the norm; norm only (softmax term -> 1/n)
-    const bool norm_only = (sg.flags & PACT_FLAG_SCORE_NORM_ONLY) != 0;
+    static_assert(SCORE_TOK == 64, "a lane per token, 16 tokens per wavefront");
+    const bool have = t0 + lane < sg.n;
+    const size_t part0 = ((size_t)b * ((bt.n_max + SCORE_TOK - 1) / SCORE_TOK) + tb) * a.n_q + j0;
+    for (int jl = wave; jl < heads; jl += 4) {
+        const double l = have ? s_l[jl][lane] : -INFINITY;
+        const double m = wave_max_f64(l);
+        const double e = have ? exp(l - m) : 0.0;
+        const double z = wave_sum_f64(e);
+        // (transposed through the same LDS words, so that a token's heads are stored together)
+        s_l[jl][lane] = e;
+        if (lane == 0) *(double2*)(a.sm_part + (part0 + jl) * 2) = make_double2(m, z);
+    }
+    __syncthreads();
+    for (int k = threadIdx.x; k < heads * SCORE_TOK; k += 256) {
+        const int tl = k / heads, jl = k - tl * heads;
+        if (t0 + tl < sg.n) a.expl[((size_t)sg.base + t0 + tl) * a.n_q + j0 + jl] = s_l[jl][tl];
+    }
+}
+
+// ------------------------------------------------------------------------------------------
+// Eq. 2, pass 2: the softmax statistics of every head from the token blocks' partials, and from them the
+// factor exp(m_block - M) / Z of each (block, head); then s_i = |h_i| (1/n_q) sum_j e_ij factor_j.
+// Workgroup-wide helpers, 1024 threads.
+//   s_M, s_Z [PACT_MAX_QHEADS]; factors of blocks tb0 .. tb0 + nblk - 1: s_f[blk][n_q]
+__device__ __forceinline__ void softmax_factors(const Batch& bt, const Seg& sg, int b, int n_q, const double* __restrict__ sm_part,
+                                                int tb0, int nblk, double* s_M, double* s_Z, double* s_f, int tid) {
+    const int lane = tid & 63;
+    const int ntb_max = (bt.n_max + SCORE_TOK - 1) / SCORE_TOK, ntb = (sg.n + SCORE_TOK - 1) / SCORE_TOK;
+    const double* part = sm_part + (size_t)b * ntb_max * n_q * 2;
+    // 32 lanes per head; 8 partials per lane stay in registers between the two steps (16384 tokens)
+    const int l32 = lane & 31;
+    for (int j = tid >> 5; j < n_q; j += 32) {
+        double2 v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            v[u] = l32 + 32 * u < ntb ? *(const double2*)(part + ((size_t)(l32 + 32 * u) * n_q + j) * 2) : make_double2(-INFINITY, 0.0);
+        double m = v[0].x;
+#pragma unroll
+        for (int u = 1; u < 8; ++u) m = fmax(m, v[u].x);
+        for (int k = l32 + 256; k < ntb; k += 32) m = fmax(m, part[((size_t)k * n_q + j) * 2]);
+        m = group_max_f64<16>(m);
+        m = fmax(m, __shfl_xor(m, 16, 64));
+        double z = 0.0;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            if (32 * u >= ntb) break;                                // (uniform)
+            z += v[u].y != 0.0 ? v[u].y * exp(v[u].x - m) : 0.0;
+        }
+        for (int k = l32 + 256; k < ntb; k += 32) {
+            const double2 w = *(const double2*)(part + ((size_t)k * n_q + j) * 2);
+            z += w.y != 0.0 ? w.y * exp(w.x - m) : 0.0;
+        }
+        z = group_sum_f64(z, 32);
+        if (l32 == 0) { s_M[j] = m; s_Z[j] = z; }
+    }
+    __syncthreads();
+    for (int k = tid; k < nblk * n_q; k += 1024) {
+        const int blk = k / n_q, j = k - blk * n_q;
+        s_f[k] = tb0 + blk < ntb ? exp(part[((size_t)(tb0 + blk) * n_q + j) * 2] - s_M[j]) / s_Z[j] : 0.0;
+    }
+    __syncthreads();
+}
+// the two ablations of Eq. 2: without the norm; norm only (softmax term -> 1/n)
+__device__ __forceinline__ float finish_score(const Seg& sg, int n_q, double sum, double hn) {
+    const double p = (sg.flags & PACT_FLAG_SCORE_NORM_ONLY) ? 1.0 / (double)sg.n : sum / (double)n_q;
+    return (float)((sg.flags & PACT_FLAG_SCORE_NO_NORM) ? p : hn * p);
+}
+
+// grid (ceil(n_max/FINAL_TOK), B), block 1024: FINAL_PARTS threads per token (heads part, part + FINAL_PARTS, ...).
+// 256 tokens a workgroup, or 128 from nine query heads on (28 heads: 10.8 -> 8.6 us; with four heads it is 2.3 us longer for 8 videos).
+template <int FINAL_TOK>
+__global__ __launch_bounds__(1024) void score_final_kernel(Batch bt, int n_q, const double* __restrict__ expl,
+                                                           const double* __restrict__ hnorm,
+                                                           const double* __restrict__ sm_part,
+                                                           float* __restrict__ scores) {
+    constexpr int NBLK = FINAL_TOK / SCORE_TOK, FINAL_PARTS = 1024 / FINAL_TOK;
+    __shared__ double s_M[PACT_MAX_QHEADS], s_Z[PACT_MAX_QHEADS], s_f[NBLK * PACT_MAX_QHEADS];
+    __shared__ double s_acc[FINAL_PARTS - 1][FINAL_TOK];
+    const int b = blockIdx.y;
+    const Seg sg = bt.s[b];
+    if ((int)blockIdx.x * FINAL_TOK >= sg.n) return;
+    const int tid = threadIdx.x, tok = tid & (FINAL_TOK - 1), part = tid / FINAL_TOK;
+    const int i = blockIdx.x * FINAL_TOK + tok;
+    const size_t g = (size_t)sg.base + min(i, sg.n - 1);
+    // this thread's values are requested before the partials are combined (they do not depend on them)
+    const double hn = hnorm[g];
+    double e[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) e[u] = part + FINAL_PARTS * u < n_q ? expl[g * n_q + part + FINAL_PARTS * u] : 0.0;
+    softmax_factors(bt, sg, b, n_q, sm_part, blockIdx.x * NBLK, NBLK, s_M, s_Z, s_f, tid);
+    const double* f = s_f + (tok / SCORE_TOK) * n_q;
     double acc = 0.0;
-    if (!norm_only && i < sg.n) {
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
-            if (part + u * PARTS < n_q) acc += exp(lg[u] - s_M[part + u * PARTS]) / s_Z[part + u * PARTS];
-        for (int j = part + 4 * PARTS; j < n_q; j += PARTS) acc += exp(logits[g * n_q + j] - s_M[j]) / s_Z[j];
-    }
-    if (PARTS > 1) {
-        if (part > 0) s_acc[part - 1][tok] = acc;
-        __syncthreads();
-        if (part > 0) return;
+    for (int u = 0; u < 4; ++u)
+        if (part + FINAL_PARTS * u < n_q) acc = fma(e[u], f[part + FINAL_PARTS * u], acc);
+    for (int j = part + 4 * FINAL_PARTS; j < n_q; j += FINAL_PARTS) acc = fma(expl[g * n_q + j], f[j], acc);
+    if (part > 0) s_acc[part - 1][tok] = acc;
+    __syncthreads();
+    if (part > 0 || i >= sg.n) return;
 #pragma unroll
-        for (int k = 0; k + 1 < PARTS; ++k) acc += s_acc[k][tok];
-    }
-    if (i >= sg.n) return;
-    const double p = norm_only ? 1.0 / (double)sg.n : acc / (double)n_q;
-    scores[g] = (float)((sg.flags & PACT_FLAG_SCORE_NO_NORM) ? p : hn * p);
+    for (int k = 0; k < FINAL_PARTS - 1; ++k) acc += s_acc[k][tok];
+    scores[g] = finish_score(sg, n_q, acc, hn);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -572,15 +563,18 @@ __global__ __launch_bounds__(TOK * PARTS) void score_final_kernel(Batch bt, int 
 //   (a) the scores become order-preserving integer keys in LDS;
 //   (b) exact radix select of the (m+1)-th smallest key, m = min(floor(lambda n), n-1);
 //   (c) ordered compaction into the kept / pruned index lists.
-// (Finishing the scores here as well - one launch fewer - was slower: one compute unit then
-// evaluates all n * n_q fp64 exponentials.)
+// FINISH: samples of at most 1024 tokens finish their scores here as well (a thread per token; one launch
+// fewer).  More values per sample than FUSE_VALUES are too much for one compute unit to fetch: they have score_final_kernel.
 // Dynamic LDS: n_max * 4 bytes.
+constexpr int FUSE_TOKENS = 1024, FUSE_VALUES = 12288;
+struct FinishArgs { const double *expl, *hnorm, *sm_part; int32_t n_q; };
 __device__ __forceinline__ uint32_t ordered_key(float f) {
     const uint32_t u = __float_as_uint(f);
     return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
-__global__ __launch_bounds__(1024) void score_prune_kernel(Batch bt, const float* __restrict__ scores,
+template <bool FINISH>
+__global__ __launch_bounds__(1024) void score_prune_kernel(Batch bt, FinishArgs fin, float* scores,
                                                            uint64_t* __restrict__ adj,
                                                            int32_t* __restrict__ kept_idx,
                                                            int32_t* __restrict__ pruned_idx,
@@ -599,7 +593,7 @@ __global__ __launch_bounds__(1024) void score_prune_kernel(Batch bt, const float
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = tid >> 6;
-    const float* s = scores + sg.base;
+    float* s = scores + sg.base;
 
     // this thread's first keys stay in registers for the select (its passes then issue their
     // histogram updates back to back instead of waiting for an LDS read before each)
@@ -607,8 +601,34 @@ __global__ __launch_bounds__(1024) void score_prune_kernel(Batch bt, const float
     uint32_t kreg[KREG];
     {
         float sv[KREG];
+        if constexpr (FINISH) {
+            constexpr int NBLK = FUSE_TOKENS / SCORE_TOK;
+            __shared__ double s_M[PACT_MAX_QHEADS], s_Z[PACT_MAX_QHEADS], s_f[NBLK * PACT_MAX_QHEADS];
+            const int n_q = fin.n_q;
+            const size_t g = (size_t)sg.base + min(tid, n - 1);
+            const double hn = fin.hnorm[g];
+            double e[16];
 #pragma unroll
-        for (int u = 0; u < KREG; ++u) sv[u] = (tid + 1024 * u < n) ? s[tid + 1024 * u] : 0.0f;   // all in flight
+            for (int u = 0; u < 16; ++u) e[u] = u < n_q ? fin.expl[g * n_q + u] : 0.0;
+            softmax_factors(bt, sg, b, n_q, fin.sm_part, 0, NBLK, s_M, s_Z, s_f, tid);
+            const double* f = s_f + (tid / SCORE_TOK) * n_q;
+            double acc[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int u = 0; u < 16; ++u)
+                if (u < n_q) acc[u & 3] = fma(e[u], f[u], acc[u & 3]);
+            for (int j = 16; j < n_q; ++j) {
+                const double v = fin.expl[g * n_q + j] * f[j];
+                acc[0] += (j & 3) == 0 ? v : 0.0; acc[1] += (j & 3) == 1 ? v : 0.0;
+                acc[2] += (j & 3) == 2 ? v : 0.0; acc[3] += (j & 3) == 3 ? v : 0.0;
+            }
+#pragma unroll
+            for (int u = 0; u < KREG; ++u) sv[u] = 0.0f;
+            sv[0] = finish_score(sg, n_q, (acc[0] + acc[1]) + (acc[2] + acc[3]), hn);
+            if (tid < n) s[tid] = sv[0];
+        } else {
+#pragma unroll
+            for (int u = 0; u < KREG; ++u) sv[u] = (tid + 1024 * u < n) ? s[tid + 1024 * u] : 0.0f;   // all in flight
+        }
 #pragma unroll
         for (int u = 0; u < KREG; ++u) {
             kreg[u] = ordered_key(sv[u]);
@@ -812,115 +832,125 @@ static hipError_t raise_lds_limit(const void* fn, size_t bytes) {
 }
 
 template <int KDT>
-static int launch_prep_q(const Batch& bt, const PrepArgs& a, pact_dtype q_dt, dim3 grid, hipStream_t st) {
+static int launch_front_q(const Batch& bt, const FrontArgs& a, pact_dtype q_dt, dim3 grid, hipStream_t st) {
     if (q_dt == PACT_BF16)
-        PACT_LAUNCH("prep", (prep_kernel<KDT, PACT_BF16>), grid, dim3(256), st, bt, a);
+        PACT_LAUNCH("front", (front_kernel<KDT, PACT_BF16>), grid, dim3(256), st, bt, a);
     else
-        PACT_LAUNCH("prep", (prep_kernel<KDT, PACT_F32>), grid, dim3(256), st, bt, a);
+        PACT_LAUNCH("front", (front_kernel<KDT, PACT_F32>), grid, dim3(256), st, bt, a);
     return PACT_OK;
 }
 
-int launch_prep(const Batch& bt, const Ws& w, const void* keys, pact_dtype k_dt, int32_t dk,
-                const void* q, pact_dtype q_dt, int32_t qcols, pact_report* rep, int32_t* cluster_id,
-                int32_t* cluster_counts, int mode, const int32_t* n_idx_dev, hipStream_t st) {
-    PrepArgs a;
+int launch_front(const Batch& bt, const Ws& w, const void* keys, pact_dtype k_dt, int32_t dk,
+                 const ScoreIn* score, pact_report* rep, int32_t* cluster_id,
+                 int32_t* cluster_counts, int mode, const int32_t* n_idx_dev, hipStream_t st) {
+    FrontArgs a = {};
     a.keys = (const char*)keys; a.dk = dk;
-    a.q = (const char*)q; a.qcols = qcols;
-    a.nn = w.nn; a.rinv = w.rinv; a.adj = w.adj; a.rho = w.rho; a.qg_part = w.qg_part;
+    a.nn = w.nn; a.rinv = w.rinv; a.adj = w.adj; a.rho = w.rho; a.qg_part = w.qg_part; a.hnorm = w.hnorm;
     a.status = w.status; a.ident = w.ident; a.near_cnt = w.near_cnt; a.tie_cnt = w.tie_cnt;
     a.rep = rep; a.cluster_id = cluster_id; a.cluster_counts = cluster_counts; a.n_idx_dev = n_idx_dev;
     a.zeros = w.zeros; a.ksplit = w.ksplit;
-    a.mode = mode; a.n_key_blocks = keys ? (bt.n_max + 3) / 4 : 0;
-    a.n_q_blocks = q ? QG_CHUNKS * ((qcols + 1023) / 1024) : 0;
-    dim3 grid(a.n_key_blocks + a.n_q_blocks, bt.B);
-    return (k_dt == PACT_BF16) ? launch_prep_q<PACT_BF16>(bt, a, q_dt, grid, st)
-                               : launch_prep_q<PACT_F32>(bt, a, q_dt, grid, st);
+    a.mode = mode;
+    if (keys) {
+        const int chunks = dk * (k_dt == PACT_BF16 ? 2 : 4) / 16;
+        a.key_lanes = chunks <= 16 ? 16 : chunks <= 32 ? 32 : 64;
+        const int per_block = 4 * (64 / a.key_lanes);
+        a.n_key_blocks = (bt.total + per_block - 1) / per_block;
+    }
+    int h_blocks = 0;
+    pact_dtype q_dt = PACT_BF16;
+    if (score) {
+        const int hb = score->h_dt == PACT_BF16 ? 2 : 4, per_block = 4 * hnorm_tokens(score->h, hb);
+        a.hidden = (const char*)score->hidden; a.h = score->h; a.h_bf16 = score->h_dt == PACT_BF16;
+        a.stream = hidden_streams(bt.total, score->h, hb) ? 1 : 0;
+        h_blocks = (bt.total + per_block - 1) / per_block;
+        if (score->q_per_token) {
+            q_dt = score->q_dt;
+            a.q = (const char*)score->q; a.qcols = score->n_q * score->d_h;
+            a.q_chunks = query_chunks(bt.n_max, a.qcols);
+            const int cw = 128 / (q_dt == PACT_BF16 ? 2 : 4);
+            a.n_q_blocks = (a.qcols + cw - 1) / cw * a.q_chunks * bt.B;
+        }
+    }
+    dim3 grid(a.n_q_blocks + a.n_key_blocks + h_blocks);
+    return (k_dt == PACT_BF16) ? launch_front_q<PACT_BF16>(bt, a, q_dt, grid, st)
+                               : launch_front_q<PACT_F32>(bt, a, q_dt, grid, st);
 }
 
-// Share (in 256ths) of the hidden-state norms that go with the global query; the rest goes with
-// the logits.  For one image the norms are best left in one launch (split, the two launches
-// together took 1.5 us longer); for large batches, whose logits launch is long enough to hide
-// part of the read behind its arithmetic, a 144 : 112 split was 8 us (1.5%) faster on 8 x 6272.
-static int hnorm_share(const Batch& bt) { return bt.total >= 20000 ? 144 : 256; }
-
-template <int HDT>
-static int launch_qglobal_hnorm(const Batch& bt, const Ws& w, const ScoreIn& in, hipStream_t st) {
-    const int qcols = in.n_q * in.d_h;
-    const int nq_blocks = in.q_per_token ? (qcols + 63) / 64 : (qcols + 1023) / 1024;
-    const int share = hnorm_share(bt);
-    const int stream = hidden_streams(bt.total, in.h, Elem<HDT>::BYTES) ? 1 : 0;
-    dim3 grid(nq_blocks + (hnorm_split(bt.n_max, share) + SCORE_TOK_PER_WG - 1) / SCORE_TOK_PER_WG, bt.B);
-    const int kbytes = in.k_dt == PACT_BF16 ? 2 : 4;
-    QgLayout lay = {0, in.n_kv, in.d_h, in.d_h * kbytes / 16, 16 / kbytes};
-    if (logits_grouped(in.n_kv, in.n_q, in.d_h, kbytes)) lay.rep = in.n_q / in.n_kv;
-    if (in.q_dt == PACT_BF16)
-        PACT_LAUNCH("qglobal_hnorm", (qglobal_hnorm_kernel<HDT, PACT_BF16>), grid, dim3(1024), st, bt, qcols,
-                    in.q_per_token ? 1 : 0, nq_blocks, lay, w.qg_part, (const char*)in.q, w.qg, (const char*)in.hidden,
-                    in.h, w.hnorm, share, stream);
-    else
-        PACT_LAUNCH("qglobal_hnorm", (qglobal_hnorm_kernel<HDT, PACT_F32>), grid, dim3(1024), st, bt, qcols,
-                    in.q_per_token ? 1 : 0, nq_blocks, lay, w.qg_part, (const char*)in.q, w.qg, (const char*)in.hidden,
-                    in.h, w.hnorm, share, stream);
-    return PACT_OK;
-}
-
-template <int HDT>
-static int launch_logits_hnorm(const Batch& bt, const Ws& w, const ScoreIn& in, hipStream_t st) {
-    const int n_logit_blocks = (bt.n_max + SCORE_TOK_PER_WG - 1) / SCORE_TOK_PER_WG;
-    const int share = hnorm_share(bt);
-    const int stream = hidden_streams(bt.total, in.h, Elem<HDT>::BYTES) ? 1 : 0;
-    // tokens past the split: n - split(n) <= n - floor(n * share / 256), which grows with n
-    const int rest = bt.n_max - ((bt.n_max * share) >> 8);
-    dim3 grid(n_logit_blocks + (rest + SCORE_TOK_PER_WG - 1) / SCORE_TOK_PER_WG, bt.B);
-    const bool grouped = logits_grouped(in.n_kv, in.n_q, in.d_h, in.k_dt == PACT_BF16 ? 2 : 4);
-#define PACT_LOGITS(KDT, G)                                                                                          \
-    PACT_LAUNCH("score_logits", (score_logits_kernel<KDT, HDT, G>), grid, dim3(1024), st, bt,                        \
-                (const char*)in.keys_pre, in.n_kv, in.d_h, in.n_q, w.qg, w.logits, w.sm_part, n_logit_blocks,        \
-                (const char*)in.hidden, in.h, w.hnorm, share, stream)
-    if (in.k_dt == PACT_BF16) { if (grouped) PACT_LOGITS(PACT_BF16, true); else PACT_LOGITS(PACT_BF16, false); }
-    else { if (grouped) PACT_LOGITS(PACT_F32, true); else PACT_LOGITS(PACT_F32, false); }
+// Scores of every sample, up to the token blocks' softmax partials.  The first kernel (launch_front with `in`)
+// must have run.
+static int launch_logits(const Batch& bt, const Ws& w, const ScoreIn& in, hipStream_t st) {
+    LogitsArgs a = {};
+    a.keys = (const char*)in.keys_pre; a.n_kv = in.n_kv; a.d_h = in.d_h; a.n_q = in.n_q;
+    a.qg_part = w.qg_part; a.q_given = in.q_per_token ? nullptr : (const char*)in.q; a.q_bf16 = in.q_dt == PACT_BF16;
+    a.q_chunks = query_chunks(bt.n_max, in.n_q * in.d_h);
+    a.expl = w.logits; a.sm_part = w.sm_part;
+    const int way = logits_way(in.n_kv, in.n_q, in.d_h, in.k_dt == PACT_BF16 ? 2 : 4), r = in.n_q / in.n_kv;
+    a.kv_heads = way == BY_MFMA ? 1 : way == BY_LANES ? logits_kv_heads_lanes(bt, in.n_kv, in.d_h / (in.k_dt == PACT_BF16 ? 8 : 4))
+                                       : logits_kv_heads_any(in.n_kv, in.n_q, in.d_h);
+    const int cols = way == BY_MFMA ? r * (4 * (in.d_h / 4 + 1) + 1) : a.kv_heads * r * in.d_h;
+    a.qg_lds = cols <= LOGITS_COLS_ANY;
+    dim3 grid((bt.n_max + SCORE_TOK - 1) / SCORE_TOK * (in.n_kv / a.kv_heads), bt.B);
+    const size_t lds = a.qg_lds ? sizeof(double) * cols : 0;
+    if (lds > 24 * 1024) {
+        static size_t raised[6] = {};
+        const int di = (in.k_dt == PACT_BF16 ? 1 : 0) + 2 * way;
+        const void* fns[6] = {(const void*)score_logits_kernel<PACT_F32, BY_HEAD>, (const void*)score_logits_kernel<PACT_BF16, BY_HEAD>,
+                              (const void*)score_logits_kernel<PACT_F32, BY_LANES>, (const void*)score_logits_kernel<PACT_BF16, BY_LANES>,
+                              (const void*)score_logits_kernel<PACT_F32, BY_MFMA>, (const void*)score_logits_kernel<PACT_BF16, BY_MFMA>};
+        if (lds > raised[di]) {
+            if (raise_lds_limit(fns[di], lds) != hipSuccess) return PACT_ERR_HIP;
+            raised[di] = lds;
+        }
+    }
+#define PACT_LOGITS(KDT, WAY) PACT_LAUNCH_SHMEM("score_logits", (score_logits_kernel<KDT, WAY>), grid, dim3(256), lds, st, bt, a)
+    if (in.k_dt == PACT_BF16) {
+        if (way == BY_MFMA) PACT_LOGITS(PACT_BF16, BY_MFMA);
+        else if (way == BY_LANES) PACT_LOGITS(PACT_BF16, BY_LANES);
+        else PACT_LOGITS(PACT_BF16, BY_HEAD);
+    } else {
+        if (way == BY_MFMA) PACT_LOGITS(PACT_F32, BY_MFMA);
+        else if (way == BY_LANES) PACT_LOGITS(PACT_F32, BY_LANES);
+        else PACT_LOGITS(PACT_F32, BY_HEAD);
+    }
 #undef PACT_LOGITS
     return PACT_OK;
 }
 
-// Scores for every sample.  The per-token query pass (Eq. 1 pass 1) must already have run
-// (launch_prep with q != nullptr) when in.q_per_token is set.
-int launch_score(const Batch& bt, const Ws& w, const ScoreIn& in, hipStream_t st) {
-    int rc = (in.h_dt == PACT_BF16) ? launch_qglobal_hnorm<PACT_BF16>(bt, w, in, st)
-                                    : launch_qglobal_hnorm<PACT_F32>(bt, w, in, st);
-    if (rc) return rc;
-    return (in.h_dt == PACT_BF16) ? launch_logits_hnorm<PACT_BF16>(bt, w, in, st)
-                                  : launch_logits_hnorm<PACT_F32>(bt, w, in, st);
+static bool finish_in_prune(const Batch& bt, int n_q) {
+    return bt.n_max <= FUSE_TOKENS && (long)bt.n_max * n_q <= FUSE_VALUES;
 }
 
-int launch_score_only(const Batch& bt, const Ws& w, int n_q, float* scores, hipStream_t st) {
-    // Many query heads: the combine once per sample in a launch of its own (its result in the
-    // array of the query's chunk sums, which the global query has replaced by now), and sixteen
-    // threads per token.
-    if (n_q > 8) {
-        double* mz = w.qg_part;
-        PACT_LAUNCH("softmax_combine", softmax_combine_kernel, dim3(n_q, bt.B), dim3(64), st, bt, n_q, w.sm_part, mz);
-        PACT_LAUNCH("score_final", (score_final_kernel<64, 16>), dim3((bt.n_max + 63) / 64, bt.B), dim3(1024), st, bt,
-                    n_q, w.logits, w.hnorm, w.sm_part, (const double*)mz, scores);
-    } else {
-        PACT_LAUNCH("score_final", (score_final_kernel<256, 1>), dim3((bt.n_max + 255) / 256, bt.B), dim3(256), st, bt,
-                    n_q, w.logits, w.hnorm, w.sm_part, (const double*)nullptr, scores);
-    }
+// The scores themselves; with `prune_follows` small samples leave them to launch_score_prune.
+int launch_score(const Batch& bt, const Ws& w, const ScoreIn& in, float* scores, bool prune_follows, hipStream_t st) {
+    if (const int rc = launch_logits(bt, w, in, st)) return rc;
+    if (prune_follows && finish_in_prune(bt, in.n_q)) return PACT_OK;
+    if (in.n_q > 8)
+        PACT_LAUNCH("score_final", score_final_kernel<128>, dim3((bt.n_max + 127) / 128, bt.B), dim3(1024), st, bt,
+                    in.n_q, w.logits, w.hnorm, w.sm_part, scores);
+    else
+        PACT_LAUNCH("score_final", score_final_kernel<256>, dim3((bt.n_max + 255) / 256, bt.B), dim3(1024), st, bt,
+                    in.n_q, w.logits, w.hnorm, w.sm_part, scores);
     return PACT_OK;
 }
 
-// Splits the finished scores of every sample (Eq. 3 / 4).
-// adj: the samples' neighbour bitmaps as launch_prep(INIT_REDUCE) left them, or nullptr when no
+// Splits the scores of every sample (Eq. 3 / 4).  unfinished: what launch_score(prune_follows) left, or nullptr.
+// adj: the samples' neighbour bitmaps as launch_front(INIT_REDUCE) left them, or nullptr when no
 // clustering follows.
-int launch_score_prune(const Batch& bt, const float* scores, uint64_t* adj, int32_t* kept_idx,
+int launch_score_prune(const Batch& bt, const Ws* unfinished, int n_q, float* scores, uint64_t* adj, int32_t* kept_idx,
                        int32_t* pruned_idx, pact_report* rep, hipStream_t st) {
     const size_t lds = (size_t)((bt.n_max + 63) / 64 * 64) * sizeof(uint32_t);
+    if (unfinished && finish_in_prune(bt, n_q)) {
+        const FinishArgs fin{unfinished->logits, unfinished->hnorm, unfinished->sm_part, n_q};
+        PACT_LAUNCH_SHMEM("score_prune", score_prune_kernel<true>, dim3(bt.B), dim3(1024), lds, st, bt, fin, scores, adj,
+                          kept_idx, pruned_idx, rep);
+        return PACT_OK;
+    }
     static size_t raised = 0;
     if (lds > 48 * 1024 && lds > raised) {
-        if (raise_lds_limit((const void*)score_prune_kernel, lds) != hipSuccess) return PACT_ERR_HIP;
+        if (raise_lds_limit((const void*)score_prune_kernel<false>, lds) != hipSuccess) return PACT_ERR_HIP;
         raised = lds;
     }
-    PACT_LAUNCH_SHMEM("score_prune", score_prune_kernel, dim3(bt.B), dim3(1024), lds, st, bt, scores, adj,
+    PACT_LAUNCH_SHMEM("score_prune", score_prune_kernel<false>, dim3(bt.B), dim3(1024), lds, st, bt, FinishArgs{}, scores, adj,
                       kept_idx, pruned_idx, rep);
     return PACT_OK;
 }

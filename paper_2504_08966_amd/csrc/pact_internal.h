@@ -32,8 +32,8 @@ struct Batch {
 
 // ---------------------------------------------------------------------------------------
 // Workspace layout.  Offsets in bytes from the 256-aligned workspace base.
-constexpr int QG_CHUNKS = 512;        // row chunks of the global-query column sum
-constexpr int SCORE_TOK_PER_WG = 16;  // tokens (= wavefronts) per workgroup in the logits kernel
+constexpr int QG_CHUNKS = 8;          // row chunks of the global-query column sum, at most
+constexpr int SCORE_TOK = 64;         // tokens per workgroup in the logits kernel
 constexpr int PRED_CAP = 64;          // 16-bit slots per kept token: slot 0 = count, then up to 63 preceding neighbours
 constexpr int GRAM_MAX_WORKGROUPS = 256; // workgroups of 8 wavefronts per sample in a Gram pass (one per CU)
 constexpr int NEAR_CAP = 1 << 16;     // near-threshold pairs kept for fp64 re-evaluation, per sample
@@ -50,7 +50,7 @@ constexpr int RESOLVE_LDS_TOKENS = 8192;   // samples up to this size keep the w
 constexpr int32_t OVERFLOW_NEAR_LIST = 1, OVERFLOW_RHO_RECHECK = 2;   // bits of pact_report.refine_overflow
 
 struct WsLayout {
-    size_t qg_part, qg, logits, hnorm, sm_part;        // score
+    size_t qg_part, logits, hnorm, sm_part;            // score
     size_t nn, rinv;                                   // key norms, per token (global row index)
     size_t ident;                                      // identity index list (idx == NULL)
     size_t adj;                                        // [B][n_max][W] u64: rows < q adjacency; from row q on: candidate words [Wc][n_pruned]
@@ -84,9 +84,8 @@ inline WsLayout make_layout(int64_t n_max, int64_t B, int64_t total, int64_t qco
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes, 256); return o; };
     const int64_t W = (n_max + 63) / 64;
-    const int64_t smwg = (n_max + SCORE_TOK_PER_WG - 1) / SCORE_TOK_PER_WG;
+    const int64_t smwg = (n_max + SCORE_TOK - 1) / SCORE_TOK;
     L.qg_part = take(sizeof(double) * B * QG_CHUNKS * qcols);
-    L.qg = take(sizeof(double) * B * qcols);
     L.logits = take(sizeof(double) * total * n_q);
     L.hnorm = take(sizeof(double) * total);
     L.sm_part = take(sizeof(double) * B * smwg * n_q * 2);
@@ -123,7 +122,7 @@ inline WsLayout make_layout(int64_t n_max, int64_t B, int64_t total, int64_t qco
 
 // Resolved device pointers for one call.
 struct Ws {
-    double* qg_part; double* qg; double* logits; double* hnorm; double* sm_part;
+    double* qg_part; double* logits; double* hnorm; double* sm_part;
     double* nn; float* rinv; int32_t* ident;
     uint64_t* adj; float* cbest; double* rho; int32_t* rank; uint32_t* status;
     int32_t* cnum; uint64_t* cmask; uint16_t* preds; uint2* heads; uint32_t* near_list; int32_t* near_cnt; uint32_t* stat;
@@ -134,7 +133,7 @@ struct Ws {
 inline Ws resolve(void* base, const WsLayout& L) {
     char* p = (char*)base;
     Ws w;
-    w.qg_part = (double*)(p + L.qg_part); w.qg = (double*)(p + L.qg);
+    w.qg_part = (double*)(p + L.qg_part);
     w.logits = (double*)(p + L.logits); w.hnorm = (double*)(p + L.hnorm);
     w.sm_part = (double*)(p + L.sm_part);
     w.nn = (double*)(p + L.nn); w.rinv = (float*)(p + L.rinv); w.ident = (int32_t*)(p + L.ident);
@@ -181,14 +180,13 @@ struct ScoreIn {
     const void* q; pact_dtype q_dt; int32_t q_per_token; int32_t n_q;   // q_per_token: 1 = [total, ..], 0 = [B, ..]
 };
 
-// First kernel of every call: key norms, cleared bitmap rows, per-token initial state and
-// (q != nullptr) the first pass of Eq. 1.
-int launch_prep(const Batch& bt, const Ws& w, const void* keys, pact_dtype k_dt, int32_t dk,
-                const void* q, pact_dtype q_dt, int32_t qcols, pact_report* rep, int32_t* cluster_id,
-                int32_t* cluster_counts, int mode, const int32_t* n_idx_dev, hipStream_t st);
-int launch_score(const Batch& bt, const Ws& w, const ScoreIn& in, hipStream_t st);
-int launch_score_only(const Batch& bt, const Ws& w, int n_q, float* scores, hipStream_t st);
-int launch_score_prune(const Batch& bt, const float* scores, uint64_t* adj, int32_t* kept_idx,
+// First kernel of every call: key norms, cleared bitmap rows, per-token initial state and (score !=
+// nullptr) hidden-state norms and the first pass of Eq. 1.
+int launch_front(const Batch& bt, const Ws& w, const void* keys, pact_dtype k_dt, int32_t dk,
+                 const ScoreIn* score, pact_report* rep, int32_t* cluster_id,
+                 int32_t* cluster_counts, int mode, const int32_t* n_idx_dev, hipStream_t st);
+int launch_score(const Batch& bt, const Ws& w, const ScoreIn& in, float* scores, bool prune_follows, hipStream_t st);
+int launch_score_prune(const Batch& bt, const Ws* unfinished, int n_q, float* scores, uint64_t* adj, int32_t* kept_idx,
                        int32_t* pruned_idx, pact_report* rep, hipStream_t st);
 // want_stat: also record the largest key distance; *stat_words = words per sample the kernel
 // wrote to w.stat (0 if not wanted), to be handed to launch_centres.

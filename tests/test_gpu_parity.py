@@ -763,6 +763,36 @@ def test_odd_sizes_and_key_widths(n, dk_heads, d_h, dtype):
     assert_same(gu.trim(o, n), oracle_reduce(s, d_c), s, f"n={n} dk={dk_heads * d_h} {dtype}")
 
 
+@pytest.mark.parametrize("sizes,n_kv,n_q,d_h,hidden,dtype", [
+    ([64, 65, 1, 63, 129], 4, 4, 16, 40, "f32"),       # a lane per 16 bytes: tokens around a block of 64
+    ([70, 200], 16, 16, 32, 1024, "bf16"),             # ... 16 heads, 64 lanes
+    ([40, 65], 1, 1, 512, 520, "bf16"),                # ... one head on all 64 lanes
+    ([65, 128], 2, 32, 32, 2048, "bf16"),              # 16 query heads per key head: the matrix instruction
+    ([17, 64], 1, 3, 48, 4096, "f32"),                 # ... three, a head of three quarters of 64 bytes
+    ([66, 31], 1, 17, 32, 96, "bf16"),                 # 17: one head after the other
+    ([65, 30], 3, 3, 40, 96, "f32"),                   # a head of ten 16-byte chunks: likewise
+    ([33, 90], 1, 64, 320, 64, "f32"),                 # more columns than the LDS holds
+    ([1024, 7], 4, 12, 64, 256, "bf16"),               # the largest sample whose scores the prune launch finishes
+    ([1025, 7], 4, 4, 64, 256, "bf16"),                # and the first that it does not
+    ([1000], 1, 13, 64, 256, "bf16"),                  # more heads than it takes for 1000 tokens
+    ([255, 257, 512], 5, 10, 24, 264, "f32"),
+])
+def test_scores_by_every_shape_of_heads(sizes, n_kv, n_q, d_h, hidden, dtype):
+    parts = [_random_sample(31 + i, n, n_kv, n_q, d_h, hidden, 0.4, dtype) for i, n in enumerate(sizes)]
+    dev = lambda get: torch.cat([gu.dev(get(s).reshape(s.n, -1), dtype) for s in parts])
+    hid, ks, qs = dev(lambda s: s.hidden), dev(lambda s: s.keys), dev(lambda s: s.queries)
+    cu = np.cumsum([0] + sizes).tolist()
+    for b, s in enumerate(parts):
+        rows = slice(cu[b], cu[b + 1])
+        sc = P.pact_score(hid[rows], ks[rows], qs[rows], n_kv, d_h, n_q)
+        np.testing.assert_allclose(sc.cpu().numpy(), po.euti_scores(s.hidden, s.keys, s.queries), rtol=2e-7, atol=0)
+    dcs = [_gap_dc(s.keys.reshape(s.n, -1)) if s.n > 2 else 0.25 for s in parts]
+    o = P.pact_reduce_varlen(hid, ks, ks, qs, n_kv, d_h, n_q, cu, [P.PactParams(0.4, d, 2.0, 1.5) for d in dcs])
+    torch.cuda.synchronize()
+    for b, s in enumerate(parts):
+        assert_same(gu.trim(o, s.n, cu[b], b), oracle_reduce(s, dcs[b]), s, f"n={s.n} {n_kv}/{n_q} x {d_h} {dtype}")
+
+
 @pytest.mark.parametrize("n,dk,shift", [(130, 64, 0.0), (127, 64, 40.0), (257, 128, 40.0), (300, 192, 0.0), (385, 192, 40.0),
                                         (129, 512, 300.0), (260, 4, 0.0), (96, 33024, 0.0), (96, 66048, 900.0)])
 def test_fp32_keys_as_integers(n, dk, shift):
