@@ -120,9 +120,9 @@ typedef struct {
     int32_t n_centers;         /* C                                         (dbdpc_cluster) */
     int32_t n_reincorporated;  /* pruned tokens recovered by Eq. 8          (pact_reincorporate) */
     int32_t n_dropped;         /* pruned tokens not recovered                (pact_reincorporate) */
-    int32_t rounds;            /* parallel centre rounds run, the last one confirming that no token is left (a
-                                * round may use decisions other wavefronts took earlier in the same round, so
-                                * the count can differ by one or two between runs; the centres cannot) */
+    int32_t rounds;            /* looks at the undecided tokens until none was left, of the wavefront that took
+                                * the most (a look may use what others decided meanwhile, so the count differs
+                                * between runs; the centres cannot) */
     int32_t dc_checked_pairs;  /* ordered kept pairs re-evaluated in fp64 near d_c */
     int32_t dc_near_ties;      /* of those, pairs with |d - d_c| <= 1e-6 (each pair counted twice) */
     int32_t refine_overflow;   /* bit 0: the near-d_c list overflowed (those pairs keep their fp32 decision);
@@ -148,7 +148,7 @@ typedef struct {
 
 /* Scratch bytes needed for one call on samples of at most n_max tokens each, `batch`
  * samples, clustering keys of width dk and type k_dt (fp32 keys need room for their integer
- * bf16 form), n_q query heads of width d_h.  0 if an argument is out of range. */
+ * form), n_q query heads of width d_h.  0 if an argument is out of range. */
 size_t pact_workspace_bytes(int32_t n_max, int32_t batch, int32_t dk, pact_dtype k_dt, int32_t n_q, int32_t d_h);
 
 /* Eq. 1 + Eq. 2 (Alg. 1 steps 1-2): importance score of every token.

@@ -1,5 +1,5 @@
 // DBDPC after the Gram pass (Alg. 2): density order, centre selection under the bound d_c
-// done in parallel rounds (same centres as the sequential loop; cf. the recursive scheme of
+// done by parallel looks (same centres as the sequential loop; cf. the recursive scheme of
 // appendix D), nearest-centre assignment; and the recovery of pruned tokens (Eq. 8/9).
 //
 // Centre selection.  Token j "precedes" i when rho_j > rho_i, or rho_j == rho_i and j < i
@@ -327,7 +327,9 @@ __device__ __forceinline__ double recheck_band2(float d_n) {
 // the list length, or KP+1 if the list did not fit (the token is then evaluated from its
 // bitmap row).  The first four slots are also written to the token's 8-byte head: most tokens
 // have at most three preceding neighbours, and the kernel that runs the rounds - a single
-// workgroup - then has 8 bytes per token to fetch instead of 32.
+// workgroup - then has 8 bytes per token to fetch instead of 32.  The head of a longer list starts with the densest
+// neighbour instead (the first of the list as it is ordered by position): it is a centre more often than not, and
+// the token is then decided without its record.
 // GL lanes of a wavefront per token (16: four tokens per wavefront, most tokens have fewer
 // neighbours than that; 64: one).  Every lane of the wavefront takes part, with p < 0 for no token.
 // `odd` counts, per token, the neighbours whose density is too close to this token's: DETECT:
@@ -347,6 +349,8 @@ __device__ __forceinline__ int preds_of_row(int p, int q, const double* r, const
     const double rp = on ? r[p] : 0.0;
     const int Wq = (q + 63) >> 6;
     int total = 0, odd = 0;
+    float best = -1.0f;                                // densest predecessor this lane has seen, and its position
+    int best_j = 0;
     auto group_bits = [&](bool v) __attribute__((always_inline)) {          // ballot of this token's lanes
         const uint64_t m = __ballot(v);
         return GL == 64 ? m : (m >> gbase) & ((1ull << (GL & 63)) - 1ull);
@@ -415,6 +419,7 @@ __device__ __forceinline__ int preds_of_row(int p, int q, const double* r, const
                     if (pre && slot < KP) out[1 + slot] = (uint16_t)j[u];
                     if (pre && slot < HEAD_PREDS) head[1 + slot] = (uint16_t)j[u];
                     total += __popcll(m);
+                    if (pre && (float)rj[u] > best) { best = (float)rj[u]; best_j = j[u]; }
                     const double d = rj[u] - rp;
                     const bool close = DETECT ? j[u] != p && d * d <= band2 * fmax(rj[u], rp)
                                               : j[u] < p && d != 0.0 && fabs(d) <= 1e-11 * (rj[u] + rp);
@@ -423,6 +428,15 @@ __device__ __forceinline__ int preds_of_row(int p, int q, const double* r, const
             }
             __builtin_amdgcn_wave_barrier();                 // the list is rewritten
         }
+    }
+    if (__any(total > HEAD_PREDS)) {
+        float top = group_max_f32<16>(best);
+        if (GL == 64) {
+            top = fmaxf(top, __shfl_xor(top, 16, 64));
+            top = fmaxf(top, __shfl_xor(top, 32, 64));
+        }
+        const uint64_t m = group_bits(best == top);
+        if (total > HEAD_PREDS && gl == __builtin_ctzll(m)) head[1] = (uint16_t)best_j;
     }
     if (gl == 0 && on) {
         const uint16_t c = (uint16_t)(total > KP ? KP + 1 : total);
@@ -469,464 +483,280 @@ __global__ __launch_bounds__(256) void build_preds_kernel(Batch bt, const pact_r
     }
 }
 
-// Set-up step of the kernel that runs the centre rounds, for a sample with listed tokens: their
-// fp64 densities from the partial sums (one wavefront per token), written over the fp32-term
-// ones; then their predecessor lists again from the new values.  All wavefronts of the workgroup
-// call it; `nb` is a per-wavefront buffer of PREDS_SPREAD entries.
-__device__ __forceinline__ void finish_rechecked_densities(const Batch& bt, int b, int q, int T, int wave, int nwaves, int lane,
-                                                           const int32_t* list, const double* part_b, double* rho_b,
-                                                           double* rho_opt_b, const uint64_t* adj, uint16_t* preds,
-                                                           uint2* heads, volatile uint16_t* nb, pact_report* rep) {
-    const int nch = (q + RHO_RECHECK_CHUNK - 1) / RHO_RECHECK_CHUNK;
-    for (int t = wave; t < T; t += nwaves) {
-        double ah = 0.0, al = 0.0;
-        for (int c = lane; c < nch; c += 64) {
-            const double2 v = *(const double2*)(part_b + ((size_t)t * nch + c) * 2);
-            ah += v.x;
-            al += v.y;
-        }
-        const double acc = wave_sum_f64(ah) + wave_sum_f64(al);
-        if (lane == 0) {
-            const int p = min(list[t] & 0xFFFF, q - 1);
-            rho_b[p] = acc;
-            if (rho_opt_b) rho_opt_b[p] = acc;
-        }
-    }
-    __syncthreads();                                   // (the values are read back by this workgroup only)
-    int fine = 0;
-    for (int t = wave; t < T; t += nwaves) {
-        const int p = min(list[t] & 0xFFFF, q - 1);
-        fine += preds_of_row<false, 64>(p, q, rho_b, adj + ((size_t)b * bt.n_max + p) * bt.W,
-                                    preds + ((size_t)b * bt.n_max + p) * PRED_CAP,
-                                    (uint16_t*)(heads + (size_t)b * bt.n_max + p), nb, lane, 0.0);
-    }
-    if (lane == 0 && fine) atomicAdd(&rep[b].rho_near_ties, fine);
-    if (wave == 0 && lane == 0) rep[b].rho_rechecked = T;
-    __syncthreads();
-}
-
-// Status checks of the list positions 1..15 of a predecessor record held in two 16-byte
-// pieces; `pm` has bit s-1 set while the predecessor at position s is still undecided
-// (positions past the list length never are).  A centre among them blocks the token; the ones
-// found not to be centres are dropped from `pm`.
-__device__ __forceinline__ bool check_pending15(const uint4& v0, const uint4& v1, uint32_t& pm, lds_vu8* st) {
-    const uint32_t wv[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
-    bool blocked = false;
-#pragma unroll
-    for (int s = 1; s < 16; ++s) {
-        if (pm & (1u << (s - 1))) {
-            const int j = (wv[s >> 1] >> ((s & 1) * 16)) & 0xFFFF;
-            const unsigned char sj = st[j];
-            blocked |= (sj == ST_CENTER);
-            if (sj == ST_NOT) pm &= ~(1u << (s - 1));
-        }
-    }
-    return blocked;
-}
-
-// The same re-evaluation on the fp64 matrix instruction, for key rows of whole 64-byte quarters
-// (the usual widths).  A work item is (16 listed tokens, 64 kept tokens); each of the workgroup's four
-// wavefronts forms the 16 x 16 dot products of the listed tokens with 16 of the kept ones by
-// v_mfma_f64_16x16x4_f64: lane l supplies element k of row l % 16 of either operand, k running over
-// the quarter l / 16 of the key width (the order of the summands of a dot product is then the same
-// for every pair, which is all that the exactness argument above needs: equal rows give equal dot
-// products), and receives the products of listed tokens 4 v + l / 16, v = 0..3, with kept token
-// l % 16.  Norms are the per-token fp64 norms of the first kernel; everything after the dot product
-// is as above, and the partial sums have the same layout.
-// grid (blocks per sample, B), block 256.
-typedef double f64x4_t __attribute__((ext_vector_type(4)));
-template <int DT>
-__global__ __launch_bounds__(256) void rho_recheck_mfma_kernel(Batch bt, const char* keys, int dk, const int32_t* idx,
-                                                                const double* __restrict__ nn, pact_report* rep, double* part,
-                                                                const int32_t* tie_list, const int32_t* tie_cnt) {
-    __shared__ double s_hi[4][16], s_lo[4][16];
-    const int b = blockIdx.y;
-    const Seg sg = bt.s[b];
-    const int T = tie_cnt[4 * b];                      // (the same for every workgroup of the sample)
-    const int q = clamp_count(rep[b].n_kept, sg.n);
-    if (T <= 0) return;
-    if (T > RHO_RECHECK_MAX) {
-        if (blockIdx.x == 0 && threadIdx.x == 0) atomicOr(&rep[b].refine_overflow, OVERFLOW_RHO_RECHECK);
-        return;
-    }
-    constexpr int EPL = Elem<DT>::EPL;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int nch = (q + RHO_RECHECK_CHUNK - 1) / RHO_RECHECK_CHUNK;
-    const int nrt = (T + 15) >> 4;
-    const size_t row_bytes = (size_t)dk * Elem<DT>::BYTES;
-    const int qchunks = (int)(row_bytes / 64);          // 16-byte chunks per quarter of a row
-    const char* kb = keys + (size_t)sg.base * row_bytes;
-    const double* nnb = nn + sg.base;
-    const int32_t* ix = idx + sg.base;
-    const int32_t* list = tie_list + (size_t)b * RHO_RECHECK_MAX;
-    double* part_b = part + (size_t)b * 2 * rho_fix_tokens(bt.n_max) * rho_fix_chunks(bt.n_max);   // [T][nch][2]
-    const double d_n = (double)sg.d_n;
-    const int i16 = lane & 15, kq = lane >> 4;
-    for (int item = blockIdx.x; item < nrt * nch; item += gridDim.x) {
-        const int rt = item / nch, c = item - rt * nch;
-        // this lane's row of either operand: listed token 16 rt + i16, kept token 64 c + 16 wave + i16
-        const int t_mine = rt * 16 + i16;
-        const int ent = list[min(t_mine, T - 1)];
-        const int p_mine = min(ent & 0xFFFF, q - 1), tokA = min(max(ent >> 16, 0), sg.n - 1);
-        const int pk_mine = c * RHO_RECHECK_CHUNK + wave * 16 + i16;
-        const int tokB = ix[min(pk_mine, q - 1)];
-        const double nnA = nnb[tokA], nnB = nnb[tokB];
-        const char* ra = kb + (size_t)tokA * row_bytes + (size_t)kq * (row_bytes / 4);
-        const char* rb = kb + (size_t)tokB * row_bytes + (size_t)kq * (row_bytes / 4);
-        // eight chunks of either row per trip to memory, the next trip's requested before this one's are multiplied;
-        // four accumulators, so that an instruction does not wait for the one before it
-        constexpr int NBT = 8;
-        f64x4_t acc[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) acc[k] = f64x4_t{0.0, 0.0, 0.0, 0.0};
-        uint4 va0[NBT], vb0[NBT], va1[NBT], vb1[NBT];
-        auto fetch = [&](uint4 (&va)[NBT], uint4 (&vb)[NBT], int u0) __attribute__((always_inline)) {
-#pragma unroll
-            for (int u = 0; u < NBT; ++u) {
-                const size_t o = (size_t)min(u0 + u, qchunks - 1) * 16;
-                va[u] = *(const uint4*)(ra + o);
-                vb[u] = *(const uint4*)(rb + o);
-            }
-        };
-        auto multiply = [&](const uint4 (&va)[NBT], const uint4 (&vb)[NBT], int u0) __attribute__((always_inline)) {
-#pragma unroll
-            for (int u = 0; u < NBT; ++u) {
-                if (u0 + u < qchunks) {                     // (uniform)
-                    double a[8], x[8];
-                    Elem<DT>::widen(va[u], a);
-                    Elem<DT>::widen(vb[u], x);
-#pragma unroll
-                    for (int e = 0; e < EPL; ++e) acc[e & 3] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[e], x[e], acc[e & 3], 0, 0, 0);
-                }
-            }
-        };
-        fetch(va0, vb0, 0);
-#pragma unroll 1
-        for (int u0 = 0; u0 < qchunks; u0 += 2 * NBT) {
-            if (u0 + NBT < qchunks) fetch(va1, vb1, u0 + NBT);
-            multiply(va0, vb0, u0);
-            if (u0 + 2 * NBT < qchunks) fetch(va0, vb0, u0 + 2 * NBT);
-            if (u0 + NBT < qchunks) multiply(va1, vb1, u0 + NBT);
-        }
-        // products of listed token 4 v + kq (of this tile) with kept token i16: terms, split, sums over the 16 kept tokens
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int src = 4 * v + kq;                     // the lane that holds that listed token's entry
-            const int p_t = __shfl(p_mine, src, 64);
-            const double nn_t = __shfl(nnA, src, 64);
-            const double dot = (acc[0][v] + acc[1][v]) + (acc[2][v] + acc[3][v]);
-            const double d = cos_dist64(dot, nn_t, nnB);
-            const double term = pk_mine >= q ? 0.0 : (pk_mine == p_t ? 1.0 : exp(-d / d_n));
-            double hi = rint(term * 1073741824.0) * (1.0 / 1073741824.0);
-            double lo = term - hi;
-            hi = group_sum_f64(hi, 16);
-            lo = group_sum_f64(lo, 16);
-            if (i16 == 0) { s_hi[wave][src] = hi; s_lo[wave][src] = lo; }
-        }
-        __syncthreads();
-        if (tid < 16) {
-            const int t = rt * 16 + tid;
-            const double vh = (s_hi[0][tid] + s_hi[1][tid]) + (s_hi[2][tid] + s_hi[3][tid]);
-            const double vl = (s_lo[0][tid] + s_lo[1][tid]) + (s_lo[2][tid] + s_lo[3][tid]);
-            if (t < T) *(double2*)(part_b + ((size_t)t * nch + c) * 2) = make_double2(vh, vl);
-        }
-        __syncthreads();
-    }
-}
-
 // All rounds of the centre selection in one workgroup per sample, statuses in LDS; then the
 // centres are numbered in ascending token order and published.
 //  * The first round needs no look-ups: nothing is decided yet, so exactly the tokens without a
 //    preceding neighbour become centres.  It is folded into the set-up.
-//  * Tokens with one to HEAD_PREDS preceding neighbours (most of the others) go on a work list of
-//    8-byte entries (position and the predecessors that are still undecided).  A round reads the
-//    list, looks the predecessors' statuses up, decides what it can and appends the entries that
-//    stay undecided - without the predecessors found not to be centres - to the list of the next
-//    round (a ballot and one LDS atomic per wavefront): a round costs what is still undecided, not
-//    n, and the wavefronts beyond the list's end have nothing to do.  Two lists alternate; they
-//    live in LDS (WL_LDS, samples of up to RESOLVE_LDS_TOKENS tokens) or in the workspace.
-//  * Tokens with more preceding neighbours are collected in a list of their own; thread i keeps
-//    the first 32 bytes of the i-th listed token's record and a bit mask of the predecessors
-//    that are still undecided.
+//  * The second looks at the predecessors that the token's head names, still in registers: all of them for a token
+//    with one to HEAD_PREDS, the densest one and two others for the rest.
+//  * From then on there are no rounds: every wavefront looks at its undecided tokens again and again until
+//    all are decided, at statuses that the others change meanwhile.  (That ends: of the undecided tokens the first in
+//    the order has decided predecessors only, and its wavefront decides it at its next look.  What a token becomes does not
+//    depend on when it is looked at.)
+//  * Undecided tokens with more than HEAD_PREDS preceding neighbours are dealt out to groups of eight lanes, which keep
+//    a token's record and bit masks of the predecessors that may still be centres.
 //  * Tokens whose list overflowed the record are evaluated from their bitmap row by a whole
 //    wavefront.
-// grid (B), block 1024, dynamic LDS: (n_max + 64) bytes (status) + n_max * 2 bytes (token
-// lists: long lists from the front, overflowed from the back) + W * 4 bytes (centres per word)
-// [+ 2 * 8 * n_max bytes of work lists].
-constexpr int RESOLVE_CACHED = 4;
-constexpr int RESOLVE_LOOKS = 2;         // looks at a work-list entry's predecessors per round (7 -> 5 rounds on a 4000-token image; a third look gains nothing, and two looks at the long lists cost more than the round they save)
-typedef uint32_t wl_entry __attribute__((ext_vector_type(2)));      // position | predecessor << 16, two more predecessors (0xFFFF: none)
-typedef __attribute__((address_space(3))) wl_entry lds_wl_entry;
-template <bool WL_LDS> struct WorkList;
-template <> struct WorkList<true> { typedef lds_wl_entry* ptr; };
-template <> struct WorkList<false> { typedef wl_entry* ptr; };
+// Bound by chains of dependent accesses.  Rounds between barriers, with work lists of the undecided tokens, took 1.7 us
+// each, at least four of them; statuses were read one after the other, a long record by one lane. 4010 tokens: 18 -> 14 us
+// from the start to the end, 16384 tokens: 74 -> 33 us.
+// The code is loops rather than unrolled: it runs once, from a cold instruction cache.
+// dynamic LDS: rounds_lds below.
+// Tokens whose heads are kept in LDS, and whether the token numbers are.
+__host__ __device__ inline int lds_heads(int qpad) { return qpad <= 8192 ? qpad : qpad <= 16384 ? 8192 : 4096; }
+__host__ __device__ inline bool lds_tokens(int qpad) { return qpad <= 16384; }
+static size_t rounds_lds(int n_max, int W) {
+    const int qpad = (n_max + 63) / 64 * 64;
+    return (size_t)lds_heads(qpad) * 8 + ((size_t)W + 1) * 4 + (size_t)qpad * (lds_tokens(qpad) ? 5 : 3);
+}
 
-template <bool WL_LDS>
-__global__ __launch_bounds__(1024) void centre_resolve_kernel(Batch bt, pact_report* rep,
-                                                              const uint64_t* __restrict__ adj,
-                                                              double* rho, double* rho_opt,
-                                                              uint16_t* preds, uint2* heads,
-                                                              const int32_t* __restrict__ idx,
-                                                              const int32_t* __restrict__ tie_list,
-                                                              const int32_t* __restrict__ tie_cnt,
-                                                              const double* __restrict__ rho_fix,
-                                                              uint32_t* status, int32_t* cnum,
-                                                              uint64_t* cmask, int32_t* center_idx, uint2* worklist) {
-    extern __shared__ unsigned char s_raw[];
-    __shared__ int s_flag[3], s_cnt[3], s_nlong, s_nover;
-    __shared__ uint16_t s_nb[16][PREDS_SPREAD];
-    const int b = blockIdx.x;
+struct CentresArgs {
+    const char* keys; int32_t dk;
+    const int32_t* idx; const double* nn;
+    pact_report* rep;
+    const uint64_t* adj;
+    double* rho; double* rho_opt;
+    uint16_t* preds; uint2* heads;
+    const int32_t* tie_list; int32_t* tie_cnt;
+    double* rho_fix;
+    uint32_t* status; int32_t* cnum; uint64_t* cmask; int32_t* center_idx;
+    int32_t write_rho;                   // whether `rho` itself has to end with the fp64 densities
+};
+
+// The value again, by another name: what the compiler derives from it stays where it is used, instead of being kept in
+// registers across the parts of a kernel that takes all of them (the first version spilled 13).
+__device__ __forceinline__ int fresh_v(int v) { asm volatile("" : "+v"(v)); return v; }
+__device__ __forceinline__ int fresh_s(int v) { asm volatile("" : "+s"(v)); return v; }
+
+__device__ __forceinline__ void run_rounds(const Batch& bt, const CentresArgs& a, int b, unsigned char* s_raw,
+                                           int& s_nshort, int& s_nlong, int& s_looks) {
     const Seg sg = bt.s[b];
-    const int tid = threadIdx.x;
+    const int tid = fresh_v(threadIdx.x);
     const int lane = tid & 63;
     const int wave = tid >> 6;
-    // the heads of this thread's first tokens are requested before the number of kept tokens is
-    // known (they lie inside the workspace for any position below n_max): one trip less
-    uint2 h[RESOLVE_CACHED];
-#pragma unroll
-    for (int k = 0; k < RESOLVE_CACHED; ++k) {
-        const int p = tid + 1024 * k;
-        h[k] = (p < bt.n_max) ? heads[(size_t)b * bt.n_max + p] : make_uint2(0, 0);
-    }
-    const int T = tie_cnt[4 * b];
+    pact_report* rep = a.rep;
+    const int32_t* ix = a.idx + sg.base;
+    const uint2* hd = a.heads + (size_t)b * bt.n_max;
     const int q = clamp_count(rep[b].n_kept, sg.n);
-    if (T > 0 && T <= RHO_RECHECK_MAX) {
-        // tokens whose density was evaluated again in fp64: finish those sums and rebuild the
-        // lists they decide, then fetch the heads again (some of them are new)
-        finish_rechecked_densities(bt, b, q, T, wave, 16, lane, tie_list + (size_t)b * RHO_RECHECK_MAX,
-                                   rho_fix + (size_t)b * 2 * rho_fix_tokens(bt.n_max) * rho_fix_chunks(bt.n_max),
-                                   rho + (size_t)b * bt.n_max, rho_opt ? rho_opt + sg.base : nullptr, adj, preds, heads,
-                                   s_nb[wave], rep);
+    const int qpad = (bt.n_max + 63) / 64 * 64, Wq = (q + 63) >> 6, n_heads = lds_heads(qpad);
+    const bool tok_lds = lds_tokens(qpad);
+    typedef __attribute__((address_space(3))) unsigned char lds_u8;
+    typedef uint32_t head_t __attribute__((ext_vector_type(2)));
+    typedef __attribute__((address_space(3))) head_t lds_head;
+    lds_head* s_head = (lds_head*)s_raw;                         // [n_heads]
+    lds_i32* s_wcnt = (lds_i32*)(s_raw + (size_t)n_heads * 8); // [W + 1]
+    lds_u16* s_list = (lds_u16*)(s_wcnt + bt.W + 1);                               // [qpad] undecided tokens: short lists from the front, others from the back
+    lds_u16* s_ix = s_list + qpad;                               // [qpad] token numbers (tok_lds)
+    lds_vu8* s_st = (lds_vu8*)(tok_lds ? s_ix + qpad : s_ix);    // [qpad]
+    const lds_u8* s_rd = (const lds_u8*)s_st;                    // plain reads: independent look-ups go out together
+    const uint4* rec = (const uint4*)(a.preds + (size_t)b * bt.n_max * PRED_CAP);   // 8 pieces per token
+    if (tid == 0) { s_nshort = 0; s_nlong = 0; s_looks = 0; }
+    // round 1.  (The first heads and token numbers are requested before the number of kept tokens is known:
+    // they lie inside the workspace and the sample.)
+    for (int p0 = 0; p0 < sg.n; p0 += 4096) {
+        uint2 hv[4];
+        int tok[4];
 #pragma unroll
-        for (int k = 0; k < RESOLVE_CACHED; ++k) {
-            const int p = tid + 1024 * k;
-            h[k] = (p < bt.n_max) ? heads[(size_t)b * bt.n_max + p] : make_uint2(0, 0);
-        }
-    }
-    const int qpad = (bt.n_max + 63) / 64 * 64;
-    lds_vu8* s_st = (lds_vu8*)s_raw;                             // [qpad + 64]
-    lds_u16* s_list = (lds_u16*)(s_raw + qpad + 64);             // [n_max]
-    lds_i32* s_wcnt = (lds_i32*)(s_raw + qpad + 64 + (size_t)qpad * 2);   // [W + 1]
-    // the two work lists, n_max entries each
-    typedef typename WorkList<WL_LDS>::ptr wl_ptr;
-    wl_ptr wl[2];
-    if constexpr (WL_LDS) {
-        const size_t off = ((size_t)qpad + 64 + (size_t)qpad * 2 + ((size_t)bt.W + 1) * 4 + 7) & ~(size_t)7;
-        wl[0] = (wl_ptr)(s_raw + off);
-        wl[1] = wl[0] + bt.n_max;
-    } else {
-        wl[0] = (wl_ptr)worklist + (size_t)b * 2 * bt.n_max;
-        wl[1] = wl[0] + bt.n_max;
-    }
-    const double* r = rho + (size_t)b * bt.n_max;
-    const uint4* rec = (const uint4*)(preds + (size_t)b * bt.n_max * PRED_CAP);   // 8 pieces per token
-    const uint2* hd = heads + (size_t)b * bt.n_max;
-    const int Wq = (q + 63) >> 6;
-    const int last = bt.n_max - 1;                               // overflow list grows down from here
-
-    if (tid == 0) {
-        s_nlong = 0; s_nover = 0;
-        s_flag[0] = 0; s_flag[1] = 0; s_flag[2] = 0;
-        s_cnt[0] = 0; s_cnt[1] = 0; s_cnt[2] = 0;
-    }
-    __syncthreads();
-    // the token indices this thread will publish at the end (words wave, wave + 16, ...): fetched
-    // now, so that the last phase does not start with a trip to memory
-    const int32_t* ix = idx + sg.base;
-    int pub_ix[RESOLVE_CACHED];
+        for (int u = 0; u < 4; ++u) hv[u] = hd[min(p0 + 1024 * u + tid, sg.n - 1)];
 #pragma unroll
-    for (int k = 0; k < RESOLVE_CACHED; ++k) {
-        const int p = ((wave + 16 * k) << 6) + lane;
-        pub_ix[k] = (p < q) ? ix[p] : 0;
-    }
-    // set-up = round 1, and the three token lists (appended a wavefront at a time)
-    auto setup = [&](int p, uint2 hv) __attribute__((always_inline)) {
-        const int c = hv.x & 0xFFFF;
-        const bool in = p < q;
-        if (in) s_st[p] = (c == 0) ? ST_CENTER : ST_UNKNOWN;
-        const bool sht = in && c >= 1 && c <= HEAD_PREDS, lng = in && c > HEAD_PREDS && c <= KP, ovr = in && c > KP;
-        const uint64_t ms = __ballot(sht), ml = __ballot(lng), mo = __ballot(ovr);
-        if (ms) {
-            int base = 0;
-            if (lane == 0) base = atomicAdd(&s_cnt[1], __popcll(ms));
-            base = lane0_of(base);
-            if (sht) {
-                // (slots of the head past its count hold nothing)
-                const uint32_t j1 = c >= 2 ? (hv.y & 0xFFFFu) : 0xFFFFu, j2 = c >= 3 ? (hv.y >> 16) : 0xFFFFu;
-                wl[1][base + lanes_below(ms, lane)] = wl_entry{(uint32_t)p | (hv.x & 0xFFFF0000u), j1 | (j2 << 16)};
+        for (int u = 0; u < 4; ++u) tok[u] = ix[min(p0 + 1024 * u + tid, sg.n - 1)];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int p = p0 + 1024 * u + tid;
+            if (p < q) {
+                s_st[p] = (hv[u].x & 0xFFFFu) == 0 ? ST_CENTER : ST_UNKNOWN;
+                if (p < n_heads) s_head[p] = head_t{hv[u].x, hv[u].y};
             }
         }
-        if (ml) {
-            int base = 0;
-            if (lane == 0) base = atomicAdd(&s_nlong, __popcll(ml));
-            base = lane0_of(base);
-            if (lng) s_list[base + lanes_below(ml, lane)] = (uint16_t)p;
-        }
-        if (mo) {
-            int base = 0;
-            if (lane == 0) base = atomicAdd(&s_nover, __popcll(mo));
-            base = lane0_of(base);
-            if (ovr) s_list[last - (base + lanes_below(mo, lane))] = (uint16_t)p;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) if (tok_lds && p0 + 1024 * u + tid < q) s_ix[p0 + 1024 * u + tid] = (uint16_t)tok[u];
+        if (p0 + 4096 >= q) break;
+    }
+    __syncthreads();
+    auto head_of = [&](int p) __attribute__((always_inline)) {
+        if (p < n_heads) return (head_t)s_head[p];
+        const uint2 v = hd[p];
+        return head_t{v.x, v.y};
+    };
+    // one look at the up to three predecessors that a token's head names
+    auto look = [&](head_t hv, int c, bool& blocked, bool& pending) __attribute__((always_inline)) {
+        const uint32_t j[HEAD_PREDS] = {hv.x >> 16, hv.y & 0xFFFFu, hv.y >> 16};     // (slots past its count hold nothing)
+        unsigned char sj[HEAD_PREDS];
+#pragma unroll
+        for (int t = 0; t < HEAD_PREDS; ++t) sj[t] = s_rd[c > t ? j[t] : 0u];
+        blocked = pending = false;
+#pragma unroll
+        for (int t = 0; t < HEAD_PREDS; ++t) {
+            blocked |= c > t && sj[t] == ST_CENTER;
+            pending |= c > t && sj[t] == ST_UNKNOWN;
         }
     };
-#pragma unroll
-    for (int k = 0; k < RESOLVE_CACHED; ++k) setup(tid + 1024 * k, h[k]);
-    for (int p0 = 1024 * RESOLVE_CACHED; p0 < q; p0 += 1024) {      // (wave-uniform trip count)
+    auto decide = [&](int p, bool blocked, bool pending) __attribute__((always_inline)) {      // whether it stays undecided
+        if (blocked) s_st[p] = ST_NOT;
+        else if (!pending) s_st[p] = ST_CENTER;
+        return !blocked && pending;
+    };
+    // the positions of one counter's new entries, a wavefront at a time
+    auto slots_of = [&](uint64_t m, int* counter) __attribute__((always_inline)) {
+        int base = 0;
+        if (lane == 0) base = atomicAdd(counter, __popcll(m));
+        return lane0_of(base) + lanes_below(m, lane);
+    };
+    // the second, and the two token lists
+#pragma unroll 1
+    for (int p0 = 0; p0 < q; p0 += 1024) {                       // (wave-uniform trip count)
         const int p = p0 + tid;
-        setup(p, p < q ? hd[p] : make_uint2(0, 0));
+        bool shrt = false, lng = false;
+        if (p < q && s_st[p] != ST_CENTER) {
+            const head_t hv = head_of(p);
+            const int c = hv.x & 0xFFFF;
+            bool blocked, pending;
+            look(hv, c, blocked, pending);
+            if (c > HEAD_PREDS) { lng = !blocked; pending = true; }
+            shrt = decide(p, blocked, pending) && !lng;
+        }
+        const uint64_t ms = __ballot(shrt), ml = __ballot(lng);
+        if (ms) {
+            const int at = slots_of(ms, &s_nshort);
+            if (shrt) s_list[at] = (uint16_t)p;
+        }
+        if (ml) {
+            const int at = slots_of(ml, &s_nlong);
+            if (lng) s_list[qpad - 1 - at] = (uint16_t)p;
+        }
     }
     __syncthreads();
-    const int nlong = s_nlong, nover = s_nover;
-    int lp = -1, lc = 0;                                         // this thread's listed token
-    uint4 l0 = make_uint4(0, 0, 0, 0), l1 = l0;
-    uint32_t pml = 0;
-    if (tid < nlong) {
-        lp = s_list[tid];
-        l0 = rec[(size_t)lp * 8];
-        l1 = rec[(size_t)lp * 8 + 1];
-        lc = l0.x & 0xFFFF;
-        pml = (lc >= 15) ? 0x7FFFu : ((1u << lc) - 1u);
+    const int nshort = s_nshort, nlong = s_nlong;
+    // A long list's token, by eight lanes, a 16-byte piece of its record each.  Bit s of a lane's `pm`: position s of its piece is a
+    // predecessor not yet found to be no centre.  Whether the token stays undecided.
+    const int sub = lane & 7;
+    auto piece_mask = [&](int c) __attribute__((always_inline)) {              // of the positions 1 .. c
+        const int k = c - 8 * sub;
+        return (k >= 7 ? 0xFFu : k < 0 ? 0u : (2u << k) - 1u) & (sub == 0 ? 0xFEu : 0xFFu);
+    };
+    auto look_long = [&](const uint4& v, int p, uint32_t& pm) __attribute__((always_inline)) {
+        const uint32_t wv[4] = {v.x, v.y, v.z, v.w};
+        unsigned char sj[8];
+#pragma unroll
+        for (int t = 0; t < 8; ++t) sj[t] = s_rd[(pm >> t) & 1u ? (wv[t >> 1] >> ((t & 1) * 16)) & 0xFFFFu : 0u];
+        bool blocked = false;
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+            blocked |= ((pm >> t) & 1u) && sj[t] == ST_CENTER;
+            if (sj[t] == ST_NOT) pm &= ~(1u << t);
+        }
+        const bool b8 = ((__ballot(blocked) >> (lane & 56)) & 0xFFull) != 0, p8 = ((__ballot(pm != 0) >> (lane & 56)) & 0xFFull) != 0;
+        if (p >= 0 && sub == 0) decide(p, b8, p8);
+        return !b8 && p8;
+    };
+    // A token whose list overflowed the record, by the whole wavefront.
+    auto decide_row = [&](int p) __attribute__((always_inline)) {
+        const double* r = a.rho + (size_t)b * bt.n_max;
+        const double rp = r[p];
+        const uint64_t* row = a.adj + ((size_t)b * bt.n_max + p) * bt.W;
+        bool blocked = false, pending = false;
+        for (int w = lane; w < Wq; w += 64) {
+            uint64_t word = row[w];
+            while (word) {
+                const int bit = __builtin_ctzll(word);
+                word &= word - 1;
+                const int j = (w << 6) + bit;
+                if (j < q && precedes(r[j], j, rp, p)) {
+                    const unsigned char sj = s_st[j];
+                    blocked |= (sj == ST_CENTER);
+                    pending |= (sj == ST_UNKNOWN);
+                }
+            }
+        }
+        blocked = __any(blocked);
+        pending = __any(pending);
+        if (lane == 0 && (blocked || !pending)) s_st[p] = blocked ? ST_NOT : ST_CENTER;
+        return !blocked && pending;
+    };
+    // (tokens are dealt out to all wavefronts)
+    const int mine = lane * 16 + wave, mine8 = (lane >> 3) * 16 + wave;
+    int sp = -1, lp[2] = {-1, -1};                               // this thread's short-list token, its group's long-list tokens
+    bool over[2] = {false, false};                               // (one whose list overflowed)
+    head_t sh = {0, 0};
+    uint4 lv[2];
+    uint32_t pm[2] = {0, 0};
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        if (mine8 + 128 * k < nlong) {
+            lp[k] = s_list[qpad - 1 - (mine8 + 128 * k)];
+            lv[k] = rec[(size_t)lp[k] * 8 + sub];
+            const int c = head_of(lp[k]).x & 0xFFFF;
+            over[k] = c > KP;
+            pm[k] = over[k] ? 0u : piece_mask(c);
+        }
     }
-    int rounds = 1;
-    // One barrier per round: round r reads the work list r & 1 (s_cnt[r % 3] entries) and appends to the
-    // other one (s_cnt[(r + 1) % 3]); it raises s_flag[r % 3] if it leaves a token of the other kinds
-    // undecided, and clears the flag and the count of round r + 2 (last read before the previous
-    // barrier) on the way.
-    while (true) {
-        if (tid == 0) { s_flag[(rounds + 1) % 3] = 0; s_cnt[(rounds + 2) % 3] = 0; }
-        bool still = false;
-        auto decide = [&](int p, bool blocked, bool pending) __attribute__((always_inline)) {
-            if (blocked) s_st[p] = ST_NOT;
-            else if (!pending) s_st[p] = ST_CENTER;
-            else still = true;
-        };
-        // short lists: the work list
-        {
-            const int nA = s_cnt[rounds % 3];
-            const wl_ptr A = wl[rounds & 1], Bn = wl[(rounds + 1) & 1];
-            // (plain reads: the three look-ups of an entry go out together; a status that another
-            //  wavefront changes meanwhile is seen in the next round at the latest)
-            typedef __attribute__((address_space(3))) unsigned char lds_u8r;
-            const lds_u8r* s_rd = (const lds_u8r*)s_st;
-            for (int i0 = wave * 64; i0 < nA; i0 += 1024) {              // (wave-uniform trip count)
-                const int i = i0 + lane;
-                const bool have = i < nA;
-                wl_entry e = {0xFFFF0000u, 0xFFFFFFFFu};
-                if (have) e = A[i];
-                const uint32_t p = e.x & 0xFFFFu;
-                uint32_t j[HEAD_PREDS] = {e.x >> 16, e.y & 0xFFFFu, e.y >> 16};
-                bool blocked = false, done = !have;
-                uint32_t keep[HEAD_PREDS];
-                int nk = 0;
-                // (RESOLVE_LOOKS looks per round, each followed by what it decides: what the other
-                //  wavefronts decide in their first look is there for the second)
-#pragma unroll
-                for (int look = 0; look < RESOLVE_LOOKS; ++look) {
-                    nk = 0;
-#pragma unroll
-                    for (int t = 0; t < HEAD_PREDS; ++t) keep[t] = 0xFFFFu;
-#pragma unroll
-                    for (int t = 0; t < HEAD_PREDS; ++t) {
-                        const bool real = j[t] != 0xFFFFu;
-                        const unsigned char sj = look == 0 ? s_rd[real ? j[t] : 0u] : s_st[real ? j[t] : 0u];
-                        blocked |= real && sj == ST_CENTER;
-                        if (real && sj == ST_UNKNOWN) {                    // stays on the entry, moved to the front
-                            if (nk == 0) keep[0] = j[t];
-                            else if (nk == 1) keep[1] = j[t];
-                            else keep[2] = j[t];
-                            ++nk;
-                        }
-                    }
-#pragma unroll
-                    for (int t = 0; t < HEAD_PREDS; ++t) j[t] = keep[t];
-                    if (!done) {
-                        if (blocked) { s_st[p] = ST_NOT; done = true; }
-                        else if (nk == 0) { s_st[p] = ST_CENTER; done = true; }
-                    }
-                }
-                const bool stay = !done;
-                const uint64_t m = __ballot(stay);
-                if (m) {
-                    int base = 0;
-                    if (lane == 0) base = atomicAdd(&s_cnt[(rounds + 1) % 3], __popcll(m));
-                    base = lane0_of(base);
-                    if (stay) Bn[base + lanes_below(m, lane)] = wl_entry{p | (keep[0] << 16), keep[1] | (keep[2] << 16)};
-                }
-            }
-        }
-        // long lists: the first 15 positions from registers, the rest of the record from memory
-        if (lp >= 0 && s_st[lp] == ST_UNKNOWN) {
-            bool blocked = check_pending15(l0, l1, pml, s_st);
-            bool pending = pml != 0;
-            for (int piece = 2; piece * 8 <= lc && !blocked; ++piece) {
-                const uint4 v = rec[(size_t)lp * 8 + piece];
-                const uint32_t wv[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-                for (int t = 0; t < 8; ++t) {
-                    if (piece * 8 + t <= lc) {
-                        const unsigned char sj = s_st[(wv[t >> 1] >> ((t & 1) * 16)) & 0xFFFF];
-                        blocked |= (sj == ST_CENTER);
-                        pending |= (sj == ST_UNKNOWN);
-                    }
-                }
-            }
-            decide(lp, blocked, pending);
-        }
-        for (int i = tid + 1024; i < nlong; i += 1024) {                    // more listed tokens than threads
-            const int p = s_list[i];
-            if (s_st[p] != ST_UNKNOWN) continue;
-            const int c = rec[(size_t)p * 8].x & 0xFFFF;
-            bool blocked = false, pending = false;
-            for (int piece = 0; piece * 8 <= c && !blocked; ++piece) {
-                const uint4 v = rec[(size_t)p * 8 + piece];
-                const uint32_t wv[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-                for (int t = 0; t < 8; ++t) {
-                    const int pos = piece * 8 + t;
-                    if (pos >= 1 && pos <= c) {
-                        const unsigned char sj = s_st[(wv[t >> 1] >> ((t & 1) * 16)) & 0xFFFF];
-                        blocked |= (sj == ST_CENTER);
-                        pending |= (sj == ST_UNKNOWN);
-                    }
-                }
-            }
-            decide(p, blocked, pending);
-        }
-        for (int o = wave; o < nover; o += 16) {                 // overflowed lists (wave-uniform trip count)
-            const int p = s_list[last - o];
-            if (s_st[p] != ST_UNKNOWN) continue;
-            const double rp = r[p];
-            const uint64_t* row = adj + ((size_t)b * bt.n_max + p) * bt.W;
-            bool blocked = false, pending = false;
-            for (int w0 = 0; w0 < Wq; w0 += 64) {
-                const int w = w0 + lane;
-                uint64_t word = (w < Wq) ? row[w] : 0ull;
-                while (word) {
-                    const int bit = __builtin_ctzll(word);
-                    word &= word - 1;
-                    const int j = (w << 6) + bit;
-                    if (j < q && precedes(r[j], j, rp, p)) {
-                        const unsigned char sj = s_st[j];
-                        blocked |= (sj == ST_CENTER);
-                        pending |= (sj == ST_UNKNOWN);
-                    }
-                }
-            }
-            blocked = __any(blocked);
-            pending = __any(pending);
-            if (blocked) { if (lane == 0) s_st[p] = ST_NOT; }
-            else if (!pending) { if (lane == 0) s_st[p] = ST_CENTER; }
-            else still = true;
-        }
-        if (still) s_flag[rounds % 3] = 1;
-        __syncthreads();
-        const int more = s_flag[rounds % 3] | s_cnt[(rounds + 1) % 3];
-        ++rounds;
-        if (!more) break;
+    if (mine < nshort) {
+        sp = s_list[mine];
+        sh = head_of(sp);
     }
+    int looks = 2;
+    bool more_short = nshort > 1024, more_long = nlong > 256;
+    while (__any(sp >= 0 || lp[0] >= 0 || lp[1] >= 0 || more_short || more_long)) {
+        asm volatile("" ::: "memory");                           // (the statuses are read again)
+        ++looks;
+        if (sp >= 0) {
+            bool blocked, pending;
+            look(sh, sh.x & 0xFFFF, blocked, pending);
+            if (!decide(sp, blocked, pending)) sp = -1;
+        }
+        if (more_short) {
+            more_short = false;
+#pragma unroll 1
+            for (int i = tid + 1024; i < nshort; i += 1024) {
+                const int p = s_list[i];
+                if (s_st[p] != ST_UNKNOWN) continue;
+                const head_t hv = head_of(p);
+                bool blocked, pending;
+                look(hv, hv.x & 0xFFFF, blocked, pending);
+                more_short |= decide(p, blocked, pending);
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            if (__any(lp[k] >= 0)) {
+                const bool stays = look_long(lv[k], over[k] ? -1 : lp[k], pm[k]);
+                if (!over[k] && !stays) lp[k] = -1;
+                uint64_t mo = __ballot(lp[k] >= 0 && over[k] && sub == 0);
+                while (mo) {
+                    const int l = __builtin_ctzll(mo);
+                    mo &= mo - 1;
+                    if (!decide_row(__builtin_amdgcn_readlane(lp[k], l)) && (lane & 56) == l) lp[k] = -1;
+                }
+            }
+        }
+        if (__any(more_long)) {                                  // more of them than groups hold
+            more_long = false;
+#pragma unroll 1
+            for (int i0 = 256; i0 < nlong; i0 += 128) {          // (wave-uniform trip count)
+                const int i = i0 + mine8, p = i < nlong ? s_list[qpad - 1 - i] : 0;
+                const bool on = i < nlong && s_st[p] == ST_UNKNOWN;
+                if (!__any(on)) continue;
+                const uint4 v = rec[(size_t)p * 8 + sub];
+                const int c = on ? (int)(head_of(p).x & 0xFFFF) : 0;
+                const bool ov = c > KP;
+                uint32_t m = ov ? 0u : piece_mask(c);
+                const bool stays = look_long(v, on && !ov ? p : -1, m);
+                more_long |= on && !ov && stays;
+                uint64_t mo = __ballot(ov && sub == 0);
+                while (mo) {
+                    const int l = __builtin_ctzll(mo);
+                    mo &= mo - 1;
+                    more_long |= decide_row(__builtin_amdgcn_readlane(p, l));
+                }
+            }
+        }
+    }
+    if (lane == 0) atomicMax(&s_looks, looks);
+    __syncthreads();
     // Publish: one ballot per 64 tokens gives the centre mask word; the centres are numbered in
     // ascending p (= ascending token index) from the running sum of the words' popcounts.
-    uint64_t* cm = cmask + (size_t)b * bt.W;
+    uint64_t* cm = a.cmask + (size_t)b * bt.W;
+#pragma unroll 1
     for (int w = wave; w < Wq; w += 16) {
         const int p = (w << 6) + lane;
         const uint64_t m = __ballot(p < q && s_st[p] == ST_CENTER);
@@ -942,31 +772,312 @@ __global__ __launch_bounds__(1024) void centre_resolve_kernel(Batch bt, pact_rep
             if (w < Wq) s_wcnt[w] = run + inc - v;
             run += lane63_of(inc);
         }
-        if (lane == 0) s_wcnt[Wq] = run;
+        if (lane == 0) {
+            s_wcnt[Wq] = run;
+            rep[b].n_centers = run;
+            rep[b].rounds = s_looks;
+        }
     }
     __syncthreads();
-    uint32_t* st = status + (size_t)b * bt.n_max;
-    int32_t* cn = cnum + (size_t)b * bt.n_max;
-    int32_t* co = center_idx + sg.base;
-    auto publish_word = [&](int w, int tok, bool have_tok) __attribute__((always_inline)) {
-        const int p = (w << 6) + lane;
-        const unsigned char sv = (p < q) ? s_st[p] : (unsigned char)ST_NOT;
+    uint32_t* st = a.status + (size_t)b * bt.n_max;
+    int32_t* cn = a.cnum + (size_t)b * bt.n_max;
+    int32_t* co = a.center_idx + sg.base;
+#pragma unroll 1
+    for (int p0 = 0; p0 < q; p0 += 1024) {                       // (64 consecutive positions per wavefront)
+        const int p = p0 + tid;
+        const unsigned char sv = p < q ? s_st[p] : (unsigned char)ST_NOT;
         const bool isc = sv == ST_CENTER;
         const uint64_t m = __ballot(isc);
-        const int c = s_wcnt[w] + lanes_below(m, lane);
         if (p < q) {
+            const int c = s_wcnt[p >> 6] + lanes_below(m, lane);
             st[p] = sv;
             cn[p] = isc ? c : -1;
-            if (isc) co[c] = have_tok ? tok : ix[p];
+            if (isc) co[c] = tok_lds ? s_ix[p] : ix[p];
+        }
+    }
+}
+
+// Densities of the listed tokens again, entirely in fp64 (Eq. 5 and Eq. 6 as they are written: dot product, two
+// norms, one division, one exponential per pair, the term of the token itself exactly 1).
+// A work item is 16 listed tokens x 16 * tiles kept ones.  Wavefront w forms the 16 x 16 dot products with the kept
+// tokens of tile w % tiles over the w / tiles-th part of the 64-byte pieces of the rows, on v_mfma_f64_16x16x4_f64: lane l
+// supplies row l % 16 of either operand, the l / 16-th 16-byte chunk of the piece, and receives the products of listed
+// tokens 4 v + l / 16 with kept token l % 16.  (The order of the summands of a dot product is the same for every pair: equal rows give
+// equal dot products.)  The parts meet in LDS; a thread per pair takes them from there.  The next item's first rows are requested
+// before that.  Four tiles; two or one where a wavefront would have more than eight steps of 32 multiplications (bf16) to
+// do and the items are so few that every workgroup still gets at most one (3584-wide rows, 6 listed tokens: 40 -> 25 us; rows
+// of 1 KB are not worth the additional workgroups to count in).
+// The sums are exact, hence the same in any order and for any two tokens with the same terms (two tokens at
+// equal distances from everything else tie exactly, as they do for a correctly rounded sum, and the index
+// decides): every term t in (0, 1] is split into hi = t rounded to a multiple of 2^-30 and lo = t - hi; sums of at
+// most 32768 such hi, and of such lo as long as t >= 2^-17 (d_n >= 0.17), fit the 53 bits of an fp64 whatever
+// their order, and the density is hi_total + lo_total, rounded once.
+typedef double f64x4_t __attribute__((ext_vector_type(4)));
+constexpr int RECHECK_LDS = 4 * 16 * 64 * 8;
+template <int DT>
+__device__ __forceinline__ void recheck_items(const Batch& bt, const CentresArgs& a, int b, int T, int q, int from, int to,
+                                              int tiles, double* s_dot) {
+    constexpr int EPL = Elem<DT>::EPL, NBT = 4;
+    const Seg sg = bt.s[b];
+    const int tid = fresh_v(threadIdx.x), lane = tid & 63, wave = tid >> 6;
+    const int chunk = 16 * tiles, parts = 16 / tiles;
+    const int nch = (q + chunk - 1) / chunk;
+    const size_t row_bytes = (size_t)a.dk * Elem<DT>::BYTES;
+    const int nchunk = (int)(row_bytes / 16), steps = (nchunk + 4 * parts - 1) / (4 * parts);
+    const char* kb = a.keys + (size_t)sg.base * row_bytes;
+    const double* nnb = a.nn + sg.base;
+    const int32_t* ix = a.idx + sg.base;
+    const int32_t* list = a.tie_list + (size_t)b * RHO_RECHECK_MAX;
+    double* part_b = a.rho_fix + (size_t)b * 2 * rho_fix_tokens(bt.n_max) * rho_fix_chunks(bt.n_max);   // [T][nch][2]
+    const double d_n = (double)sg.d_n;
+    const int i16 = lane & 15, kq = lane >> 4, part = wave / tiles, tile = wave - part * tiles;
+    // this thread's rows of the products, and its pair of the second half (none beyond 16 x chunk threads)
+    const int te = tid / chunk, ke = tid - te * chunk;
+    int tokA, tokB, ent_end, tok_end;
+    auto tokens_of = [&](int item) __attribute__((always_inline)) {
+        const int rt = item / nch, c = item - rt * nch;
+        tokA = list[min(rt * 16 + i16, T - 1)] >> 16;
+        tokB = ix[min(c * chunk + tile * 16 + i16, q - 1)];
+        ent_end = list[min(rt * 16 + te, T - 1)];
+        tok_end = ix[min(c * chunk + ke, q - 1)];
+    };
+    uint4 va[NBT], vb[NBT];
+    const char *ra, *rb;
+    auto fetch = [&](int s0) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < NBT; ++u) {
+            const size_t o = (size_t)min(((s0 + u) * parts + part) * 4 + kq, nchunk - 1) * 16;
+            va[u] = *(const uint4*)(ra + o);
+            vb[u] = *(const uint4*)(rb + o);
         }
     };
+    auto begin = [&]() __attribute__((always_inline)) {
+        ra = kb + (size_t)min(max(tokA, 0), sg.n - 1) * row_bytes;
+        rb = kb + (size_t)tokB * row_bytes;
+        fetch(0);
+    };
+    tokens_of(from);
+    begin();
+    for (int item = from; item < to; ++item) {
+        const int rt = item / nch, c = item - rt * nch;
+        const int t_end = rt * 16 + te, pk_end = c * chunk + ke, p_end = ent_end & 0xFFFF;
+        const double nnA = nnb[min(max(ent_end >> 16, 0), sg.n - 1)], nnB = nnb[tok_end];
+        if (item + 1 < to) tokens_of(item + 1);
+        f64x4_t acc = {0.0, 0.0, 0.0, 0.0};                 // (four wavefronts share a matrix unit)
+#pragma unroll 1
+        for (int s0 = 0; s0 < steps; s0 += NBT) {
 #pragma unroll
-    for (int k = 0; k < RESOLVE_CACHED; ++k)
-        if (wave + 16 * k < Wq) publish_word(wave + 16 * k, pub_ix[k], true);
-    for (int w = wave + 16 * RESOLVE_CACHED; w < Wq; w += 16) publish_word(w, 0, false);
+            for (int u = 0; u < NBT; ++u) {
+                if (s0 + u < steps) {                       // (uniform)
+                    if (((s0 + u) * parts + part) * 4 + kq >= nchunk) va[u] = vb[u] = make_uint4(0, 0, 0, 0);
+                    double x[8], y[8];
+                    Elem<DT>::widen(va[u], x);
+                    Elem<DT>::widen(vb[u], y);
+#pragma unroll
+                    for (int e = 0; e < EPL; ++e) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(x[e], y[e], acc, 0, 0, 0);
+                }
+            }
+            if (s0 + NBT < steps) fetch(s0 + NBT);
+        }
+        if (item + 1 < to) begin();
+        __syncthreads();                                    // (the previous item's products have been read)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) s_dot[(part * 16 + 4 * v + kq) * chunk + tile * 16 + i16] = acc[v];
+        __syncthreads();
+        if (tid < 16 * chunk) {                             // (whole wavefronts)
+            double dot = 0.0;
+            for (int k = 0; k < parts; ++k) dot += s_dot[k * 16 * chunk + tid];
+            const double d = cos_dist64(dot, nnA, nnB);
+            const double term = pk_end >= q ? 0.0 : (pk_end == min(p_end, q - 1) ? 1.0 : exp(-d / d_n));
+            const double hi = rint(term * 1073741824.0) * (1.0 / 1073741824.0);
+            const double vh = group_sum_f64(hi, chunk), vl = group_sum_f64(term - hi, chunk);
+            if (ke == 0 && t_end < T) *(double2*)(part_b + ((size_t)t_end * nch + c) * 2) = make_double2(vh, vl);
+        }
+    }
+}
+
+// The fp64 densities of the listed tokens from their partial sums, and whether a pair of neighbours changes its order
+// by them: only listed tokens can (both tokens of a pair inside the band are listed), so all pairs of them are
+// looked at.  The densities are left in front of the partial sums.
+__device__ __forceinline__ bool order_changed(const Batch& bt, const CentresArgs& a, int b, int T, int q, int tiles,
+                                              unsigned char* s_raw, int* s_flag) {
+    const Seg sg = bt.s[b];
+    const int tid = fresh_v(threadIdx.x), lane = tid & 63, wave = tid >> 6;
+    double* s_new = (double*)s_raw;
+    double* s_old = s_new + RHO_RECHECK_MAX;
+    int* s_pos = (int*)(s_old + RHO_RECHECK_MAX);
+    const int32_t* list = a.tie_list + (size_t)b * RHO_RECHECK_MAX;
+    double* part_b = a.rho_fix + (size_t)b * 2 * rho_fix_tokens(bt.n_max) * rho_fix_chunks(bt.n_max);
+    const double* rho_b = a.rho + (size_t)b * bt.n_max;
+    const uint64_t* adj_b = a.adj + (size_t)b * bt.n_max * bt.W;
+    const int nch = (q + 16 * tiles - 1) / (16 * tiles);
+    static_assert(RHO_RECHECK_MAX <= 1024, "a listed token per thread");
+    __syncthreads();
+    if (tid == 0) s_flag[0] = s_flag[1] = fresh_v(0);
+    if (tid < T) {
+        const int p = min(list[tid] & 0xFFFF, q - 1);
+        s_pos[tid] = p;
+        s_old[tid] = rho_b[p];
+    }
+    for (int t0 = 0; t0 < T; t0 += 64) {                // 16 lanes per token
+        const int t = t0 + wave * 4 + (lane >> 4);
+        double ah = 0.0, al = 0.0;
+        if (t < T) {
+            for (int c = lane & 15; c < nch; c += 128) {
+                double2 v[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u)
+                    v[u] = c + 16 * u < nch ? *(const double2*)(part_b + ((size_t)t * nch + c + 16 * u) * 2) : make_double2(0.0, 0.0);
+#pragma unroll
+                for (int u = 0; u < 8; ++u) { ah += v[u].x; al += v[u].y; }
+            }
+        }
+        const double acc = group_sum_f64(ah, 16) + group_sum_f64(al, 16);
+        if (t < T && (lane & 15) == 0) s_new[t] = acc;
+    }
+    __syncthreads();
+    bool changed = false;
+    int fine = 0;
+    constexpr int UN = 4;
+    for (int e0 = tid; e0 < T * T; e0 += 1024 * UN) {
+        int i[UN], j[UN];
+        uint64_t word[UN];
+#pragma unroll
+        for (int u = 0; u < UN; ++u) {
+            const int e = min(e0 + 1024 * u, T * T - 1);
+            i[u] = e / T;
+            j[u] = e - i[u] * T;
+            word[u] = adj_b[(size_t)s_pos[i[u]] * bt.W + (s_pos[j[u]] >> 6)];
+        }
+#pragma unroll
+        for (int u = 0; u < UN; ++u) {
+            const int pi = s_pos[i[u]], pj = s_pos[j[u]];
+            if (e0 + 1024 * u >= T * T || pj >= pi || !((word[u] >> (pj & 63)) & 1ull)) continue;
+            const double ni = s_new[i[u]], nj = s_new[j[u]], d = nj - ni;
+            changed |= precedes(nj, pj, ni, pi) != precedes(s_old[j[u]], pj, s_old[i[u]], pi);
+            fine += d != 0.0 && fabs(d) <= 1e-11 * (nj + ni);
+        }
+    }
+    if (changed) s_flag[0] = 1;
+    if (fine) atomicAdd(&s_flag[1], fine);
+    if (tid < T) {
+        part_b[tid] = s_new[tid];
+        if (a.rho_opt) a.rho_opt[sg.base + s_pos[tid]] = s_new[tid];
+    }
+    __syncthreads();
     if (tid == 0) {
-        rep[b].n_centers = s_wcnt[Wq];
-        rep[b].rounds = rounds;
+        if (s_flag[1]) atomicAdd(&a.rep[b].rho_near_ties, s_flag[1]);
+        a.rep[b].rho_rechecked = T;
+    }
+    return lane0_of(s_flag[0]) != 0;
+}
+
+// The fp64 densities take their places; the predecessor lists of the listed tokens are made again from them.
+__device__ __forceinline__ void replace_densities(const Batch& bt, const CentresArgs& a, int b, int T, int q, bool lists,
+                                                  uint16_t* s_nb) {
+    const int tid = fresh_v(threadIdx.x), lane = tid & 63, wave = tid >> 6;
+    const int32_t* list = a.tie_list + (size_t)b * RHO_RECHECK_MAX;
+    const double* part_b = a.rho_fix + (size_t)b * 2 * rho_fix_tokens(bt.n_max) * rho_fix_chunks(bt.n_max);
+    double* rho_b = a.rho + (size_t)b * bt.n_max;
+    __syncthreads();
+    if (tid < T) rho_b[min(list[tid] & 0xFFFF, q - 1)] = part_b[tid];
+    __syncthreads();                                   // (the values are read back by this workgroup only)
+    if (!lists) return;
+    for (int t = wave; t < T; t += 16) {
+        const int p = min(list[t] & 0xFFFF, q - 1);
+        preds_of_row<false, 64>(p, q, rho_b, a.adj + ((size_t)b * bt.n_max + p) * bt.W, a.preds + ((size_t)b * bt.n_max + p) * PRED_CAP,
+                                (uint16_t*)(a.heads + (size_t)b * bt.n_max + p), s_nb + wave * PREDS_SPREAD, lane, 0.0);
+    }
+    __syncthreads();
+}
+
+// Centre rounds and fp64 densities side by side: workgroup b < B runs the rounds of sample b in the order of the
+// densities that it finds; the others share out the batch's work items of listed tokens, and the one that
+// finishes a sample's last item looks whether two neighbours change their order.  They hardly ever do (the band that lists tokens is
+// some fifty standard errors wide); if so, the later of that workgroup and the sample's first one puts the fp64
+// densities in place and runs the rounds again.  Nobody waits for anybody: counters say who is last.
+// As two launches, one after the other: 4010-token image 28 -> 18 us, 8 videos of 3450 tokens 43 -> 31 us, 7290 rows of 7 KB
+// 97 -> 37 us, 16384 tokens with fp32 keys 140 -> 67 us (the fp64 products of 70 listed tokens).
+// tie_cnt[4b]: listed tokens; [4b + 1]: work items done; [4b + 2]: 1 looked at, 2 changed, 4 rounds run.
+// grid (B + workers), block 1024, dynamic LDS: what run_rounds takes, at least RECHECK_LDS.
+template <int DT>
+__global__ __launch_bounds__(1024) void centres_kernel(Batch bt, CentresArgs a) {
+    extern __shared__ double s_dyn[];
+    __shared__ int s_flag[2], s_nshort, s_nlong, s_looks, s_got, s_tiles;
+    __shared__ int s_T[PACT_MAX_BATCH], s_q[PACT_MAX_BATCH], s_items[PACT_MAX_BATCH + 1];
+    static_assert(PACT_MAX_BATCH <= 64, "a sample per lane");
+    const bool resolver = (int)blockIdx.x < bt.B;
+    int item = 0, item_end = 0, b = blockIdx.x, T = 0, q = 0, tiles = 4;
+    if (!resolver) {
+        const int workers = gridDim.x - bt.B;
+        if (threadIdx.x < 64) {
+            const int k = threadIdx.x;
+            int Tk = 0, qk = 0;
+            if (k < bt.B) {
+                Tk = a.tie_cnt[4 * k];
+                qk = clamp_count(a.rep[k].n_kept, bt.s[k].n);
+                s_T[k] = Tk;
+                s_q[k] = qk;
+                if (Tk > RHO_RECHECK_MAX) Tk = 0;
+            }
+            // tiles of kept tokens per item; the room for partial sums is that of four tiles, for the most listed tokens
+            const int nchunk = a.dk * Elem<DT>::BYTES / 16;
+            int tiles = 4, inc = wave_scan_incl_i32(((Tk + 15) >> 4) * ((qk + 63) >> 6));
+            while (tiles > 1 && nchunk * tiles > 8 * 64) {
+                const int half = 8 * tiles, inc2 = wave_scan_incl_i32(((Tk + 15) >> 4) * ((qk + half - 1) / half));
+                if (lane63_of(inc2) > workers || __any(Tk * (64 / half) > rho_fix_tokens(bt.n_max))) break;
+                tiles >>= 1;
+                inc = inc2;
+            }
+            s_items[k + 1] = inc;
+            if (k == 0) { s_items[0] = 0; s_tiles = tiles; }
+        }
+        __syncthreads();
+        tiles = lane0_of(s_tiles);
+        const int total = lane0_of(s_items[bt.B]), w = (int)blockIdx.x - bt.B;
+        item = (int)((long)total * w / workers);
+        item_end = (int)((long)total * (w + 1) / workers);
+        b = 0;
+    }
+    auto meet = [&](int* counter, int add) __attribute__((always_inline)) {       // what was there before
+        __syncthreads();
+        if (threadIdx.x == 0) s_got = __hip_atomic_fetch_add(counter, add, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();
+        return lane0_of(s_got);
+    };
+    bool again = false, lists = false;
+    while (true) {
+        if (!resolver) {
+            if (item >= item_end) return;
+            while (item >= lane0_of(s_items[b + 1])) ++b;
+            const int from = lane0_of(s_items[b]), next = lane0_of(s_items[b + 1]), to = min(item_end, next), all = next - from, mine = to - item;
+            T = lane0_of(s_T[b]);
+            q = lane0_of(s_q[b]);
+            recheck_items<DT>(bt, a, fresh_s(b), fresh_s(T), fresh_s(q), fresh_s(item - from), fresh_s(to - from), tiles, s_dyn);
+            item = to;
+            if (meet(&a.tie_cnt[4 * b + 1], mine) != all - mine) continue;
+            lists = order_changed(bt, a, fresh_s(b), fresh_s(T), fresh_s(q), tiles, (unsigned char*)s_dyn, s_flag);
+            if (!(meet(&a.tie_cnt[4 * b + 2], lists ? 3 : 1) & 4)) continue;      // the rounds still run
+            again = lists || a.write_rho;
+            if (!again) continue;
+        }
+        const int bs = fresh_s(b);
+        if (again) replace_densities(bt, a, bs, T, q, lists, (uint16_t*)s_dyn);
+        if (!again || lists) run_rounds(bt, a, bs, (unsigned char*)s_dyn, s_nshort, s_nlong, s_looks);
+        if (!resolver) continue;
+        if (again) return;
+        T = a.tie_cnt[4 * bs];
+        if (T <= 0) return;
+        if (T > RHO_RECHECK_MAX) {
+            if (threadIdx.x == 0) atomicOr(&a.rep[bs].refine_overflow, OVERFLOW_RHO_RECHECK);
+            return;
+        }
+        q = clamp_count(a.rep[bs].n_kept, bt.s[bs].n);
+        const int seen = meet(&a.tie_cnt[4 * bs + 2], 4);
+        if (!(seen & 1)) return;                       // that workgroup will find the rounds run
+        lists = (seen & 2) != 0;
+        again = lists || a.write_rho;
+        if (!again) return;
     }
 }
 
@@ -1114,164 +1225,6 @@ __device__ __forceinline__ double group_dot64(const char* mine, const char* othe
         }
     }
     return group_sum_f64(acc, 16);
-}
-
-// Dot product in fp64 of two rows whose 16-byte chunks the 16 lanes of a group already hold (chunks
-// part, part + 16, .. of rows of at most 64 chunks; the first row widened to fp64 beforehand) and, in the
-// same pass and the same order of
-// operations, of the second row with itself: rows that are bit-identical then give bit-identical
-// dot products and norms, i.e. a cosine of exactly 1.  Every lane of the group gets both sums.
-template <int DT>
-__device__ __forceinline__ void chunk_dots64(const double (&a)[4][8], const uint4 (&vb)[4], int nchunk, int part,
-                                             double& dot, double& nn_other) {
-    constexpr int EPL = Elem<DT>::EPL;
-    double acc = 0.0, acc2 = 0.0;
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        if (part + 16 * u < nchunk) {
-            double x[8];
-            Elem<DT>::widen(vb[u], x);
-#pragma unroll
-            for (int i = 0; i < EPL; ++i) { acc = fma(a[u][i], x[i], acc); acc2 = fma(x[i], x[i], acc2); }
-        }
-    }
-    dot = group_sum_f64(acc, 16);
-    nn_other = group_sum_f64(acc2, 16);
-}
-
-// Densities of the listed tokens again, entirely in fp64 (Eq. 5 and Eq. 6 as they are written:
-// dot product, two norms - recomputed here by the routine that computes the dot product, so
-// that a copy of the token is at distance exactly 0 -, one division, one exponential per pair,
-// the term of the token itself exactly 1).  This kernel leaves partial sums; the kernel that
-// runs the centre rounds adds them up and rebuilds the predecessor lists of those tokens
-// (finish_rechecked_densities below) before it looks at any list.
-// Work items are (listed token, chunk of RHO_RECHECK_CHUNK kept tokens): one workgroup per item
-// and turn, 16 lanes per pair.  The sums are exact, hence the same in any order and for any two
-// tokens with the same terms (two tokens at equal distances from everything else tie exactly, as
-// they do for a correctly rounded sum, and the index decides): every term t in (0, 1] is split
-// into hi = t rounded to a multiple of 2^-30 and lo = t - hi; sums of at most 32768 such hi, and
-// of such lo as long as t >= 2^-17 (d_n >= 0.17), fit the 53 bits of an fp64 whatever their
-// order, and the density is hi_total + lo_total, rounded once.
-// grid (blocks per sample, B), block 256.
-template <int DT>
-__global__ __launch_bounds__(256) void rho_recheck_kernel(Batch bt, const char* keys, int dk, const int32_t* idx,
-                                                           pact_report* rep, double* part,
-                                                           const int32_t* tie_list, const int32_t* tie_cnt) {
-    __shared__ double s_hi[RHO_RECHECK_CHUNK], s_lo[RHO_RECHECK_CHUNK];
-    const int b = blockIdx.y;
-    const Seg sg = bt.s[b];
-    const int T = tie_cnt[4 * b];                      // (the same for every workgroup of the sample)
-    const int q = clamp_count(rep[b].n_kept, sg.n);
-    if (T <= 0) return;
-    if (T > RHO_RECHECK_MAX) {
-        if (blockIdx.x == 0 && threadIdx.x == 0) atomicOr(&rep[b].refine_overflow, OVERFLOW_RHO_RECHECK);
-        return;
-    }
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int nch = (q + RHO_RECHECK_CHUNK - 1) / RHO_RECHECK_CHUNK;
-    const size_t row_bytes = (size_t)dk * Elem<DT>::BYTES;
-    const int nchunk = (int)(row_bytes / 16);
-    const char* kb = keys + (size_t)sg.base * row_bytes;
-    const int32_t* ix = idx + sg.base;
-    const int32_t* list = tie_list + (size_t)b * RHO_RECHECK_MAX;
-    double* part_b = part + (size_t)b * 2 * rho_fix_tokens(bt.n_max) * rho_fix_chunks(bt.n_max);   // [T][nch][2], T <= q <= n_max
-    const double d_n = (double)sg.d_n;
-    const int g = tid >> 4, part16 = tid & 15;
-    constexpr int PER = RHO_RECHECK_CHUNK / 16;          // pairs per group of 16 lanes and item
-    static_assert(PER == 4, "a group's four rows are requested together");
-    for (int item = blockIdx.x; item < T * nch; item += gridDim.x) {
-        const int t = item / nch, c = item - t * nch;
-        // this group's kept tokens: lane s of the group fetches the s-th one's token (one trip for all)
-        const int pk_mine = c * RHO_RECHECK_CHUNK + (part16 & (PER - 1)) * 16 + g;
-        const int tk_mine = ix[min(pk_mine, q - 1)];
-        const int ent = list[t];
-        const int p = min(ent & 0xFFFF, q - 1), tok = min(max(ent >> 16, 0), sg.n - 1);
-        const char* mine = kb + (size_t)tok * row_bytes;
-        if (nchunk <= 64) {
-            // rows of at most 1 KB: a lane holds its (at most four) 16-byte chunks of the token's row and
-            // those of the group's four other rows, all requested together
-            uint4 vm[4], vk[PER][4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) vm[u] = *(const uint4*)(mine + (size_t)min(part16 + 16 * u, nchunk - 1) * 16);
-#pragma unroll
-            for (int s = 0; s < PER; ++s) {
-                const int tk = __shfl(tk_mine, (lane & ~15) + s, 64);
-#pragma unroll
-                for (int u = 0; u < 4; ++u)
-                    vk[s][u] = *(const uint4*)(kb + (size_t)tk * row_bytes + (size_t)min(part16 + 16 * u, nchunk - 1) * 16);
-            }
-            double am[4][8];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) Elem<DT>::widen(vm[u], am[u]);
-            double nnp, dd;
-            chunk_dots64<DT>(am, vm, nchunk, part16, dd, nnp);
-#pragma unroll
-            for (int s = 0; s < PER; ++s) {
-                const int pk = c * RHO_RECHECK_CHUNK + s * 16 + g;
-                double dot, nnk;
-                chunk_dots64<DT>(am, vk[s], nchunk, part16, dot, nnk);
-                const double d = cos_dist64(dot, nnp, nnk);
-                const double term = pk >= q ? 0.0 : (pk == p ? 1.0 : exp(-d / d_n));
-                const double hi = rint(term * 1073741824.0) * (1.0 / 1073741824.0);
-                if (part16 == 0) { s_hi[s * 16 + g] = hi; s_lo[s * 16 + g] = term - hi; }
-            }
-        } else {
-            // longer rows: the group's four pairs advance together, four chunks of the token's row
-            // and of each of the four other rows per trip (same order of operations per pair as above)
-            constexpr int EPL = Elem<DT>::EPL;
-            const char* rowk[PER];
-#pragma unroll
-            for (int s = 0; s < PER; ++s) rowk[s] = kb + (size_t)__shfl(tk_mine, (lane & ~15) + s, 64) * row_bytes;
-            double nnp = 0.0, dot[PER], nnk[PER];
-#pragma unroll
-            for (int s = 0; s < PER; ++s) dot[s] = nnk[s] = 0.0;
-#pragma unroll 1
-            for (int k0 = part16; k0 < nchunk; k0 += 64) {
-                uint4 vm[4], vk[PER][4];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const size_t o = (size_t)min(k0 + 16 * u, nchunk - 1) * 16;
-                    vm[u] = *(const uint4*)(mine + o);
-#pragma unroll
-                    for (int s = 0; s < PER; ++s) vk[s][u] = *(const uint4*)(rowk[s] + o);
-                }
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    if (k0 + 16 * u < nchunk) {
-                        double a[8], x[8];
-                        Elem<DT>::widen(vm[u], a);
-#pragma unroll
-                        for (int i = 0; i < EPL; ++i) nnp = fma(a[i], a[i], nnp);
-#pragma unroll
-                        for (int s = 0; s < PER; ++s) {
-                            Elem<DT>::widen(vk[s][u], x);
-#pragma unroll
-                            for (int i = 0; i < EPL; ++i) { dot[s] = fma(a[i], x[i], dot[s]); nnk[s] = fma(x[i], x[i], nnk[s]); }
-                        }
-                    }
-                }
-            }
-            nnp = group_sum_f64(nnp, 16);
-#pragma unroll
-            for (int s = 0; s < PER; ++s) { dot[s] = group_sum_f64(dot[s], 16); nnk[s] = group_sum_f64(nnk[s], 16); }
-#pragma unroll
-            for (int s = 0; s < PER; ++s) {
-                const int pk = c * RHO_RECHECK_CHUNK + s * 16 + g;
-                const double d = cos_dist64(dot[s], nnp, nnk[s]);
-                const double term = pk >= q ? 0.0 : (pk == p ? 1.0 : exp(-d / d_n));
-                const double hi = rint(term * 1073741824.0) * (1.0 / 1073741824.0);
-                if (part16 == 0) { s_hi[s * 16 + g] = hi; s_lo[s * 16 + g] = term - hi; }
-            }
-        }
-        __syncthreads();
-        if (tid < 64) {
-            static_assert(RHO_RECHECK_CHUNK == 64, "one term per lane");
-            const double vh = wave_sum_f64(s_hi[lane]);
-            const double vl = wave_sum_f64(s_lo[lane]);
-            if (lane == 0) *(double2*)(part_b + ((size_t)t * nch + c) * 2) = make_double2(vh, vl);
-        }
-        __syncthreads();
-    }
 }
 
 // Eq. 8/9: every pruned token joins the nearest centre iff its fp64 distance is below
@@ -1490,54 +1443,30 @@ int launch_centres(const Batch& bt, const Ws& w, const void* keys, pact_dtype k_
     else
         PACT_LAUNCH("build_preds", build_preds_kernel<16>, dim3((bt.n_max + 15) / 16, bt.B), dim3(256), st, bt, rep, w.adj, w.rho,
                     rho_opt, w.preds, w.heads, idx, w.tie_list, w.tie_cnt);
-    // neighbours whose densities the fp32 terms cannot order: fp64 (a few tokens of an image)
-    // (one sample: 2048 workgroups, a work item each for up to 32 listed tokens of a 4000-token sample -
-    //  the chip holds 512 of them at a time, and 4096 took 0.8 us longer to dispatch; a batch: 8192
-    //  shared out equally, since the listed tokens are not spread evenly over the samples)
-    const int rb = bt.B == 1 ? 2048 : 8192 / bt.B;
-    // Rows of whole 64-byte quarters can go through the fp64 matrix instruction.  A 16 x 16 tile of dot
-    // products is then one wavefront's chain of dk / 4 instructions (4 us at a key width of 512), against
-    // a couple of trips to memory per 64 pairs for the vector version.  With the handful of listed tokens
-    // of one image, or of a batch of small images, the vector version is the shorter one (4010 kept
-    // tokens: 12.3 against 14.9 us; 16 ragged images: 13.4 against 22.5 us); with many kept tokens or wide
-    // rows the matrix version (16384 kept tokens, 70 listed: 195 -> 58 us; 8 videos of 3450 kept tokens:
-    // 48 -> 29 us; 3584-wide rows: 82 -> 52 us).  How many tokens are listed is known on the device only
-    // (one kernel holding both versions behind a device-side choice ran each of them a quarter to a half
-    // slower), so the host goes by the kept tokens it expects.
-    const size_t recheck_row_bytes = (size_t)dk * (k_dt == PACT_BF16 ? 2 : 4);
-    const bool quarters = recheck_row_bytes % 64 == 0 &&
-                          (kept_est >= (bt.B == 1 ? 6000 : 20000) || recheck_row_bytes >= 4096);
-    if (quarters && k_dt == PACT_BF16)
-        PACT_LAUNCH("rho_recheck", rho_recheck_mfma_kernel<PACT_BF16>, dim3(rb, bt.B), dim3(256), st, bt, k, dk, idx,
-                    w.nn, rep, w.rho_fix, w.tie_list, w.tie_cnt);
-    else if (quarters)
-        PACT_LAUNCH("rho_recheck", rho_recheck_mfma_kernel<PACT_F32>, dim3(rb, bt.B), dim3(256), st, bt, k, dk, idx,
-                    w.nn, rep, w.rho_fix, w.tie_list, w.tie_cnt);
-    else if (k_dt == PACT_BF16)
-        PACT_LAUNCH("rho_recheck", rho_recheck_kernel<PACT_BF16>, dim3(rb, bt.B), dim3(256), st, bt, k, dk, idx,
-                    rep, w.rho_fix, w.tie_list, w.tie_cnt);
-    else
-        PACT_LAUNCH("rho_recheck", rho_recheck_kernel<PACT_F32>, dim3(rb, bt.B), dim3(256), st, bt, k, dk, idx,
-                    rep, w.rho_fix, w.tie_list, w.tie_cnt);
-    const size_t qpad = (size_t)((bt.n_max + 63) / 64 * 64);
-    const bool wl_lds = bt.n_max <= RESOLVE_LDS_TOKENS;       // the work lists fit beside the statuses
-    const size_t lds_base = (qpad + 64 + qpad * 2 + ((size_t)bt.W + 1) * 4 + 7) & ~(size_t)7;
-    const size_t lds = lds_base + (wl_lds ? (size_t)bt.n_max * 16 : 0);
-    static size_t raised[2] = {0, 0};
-    const void* fn = wl_lds ? (const void*)centre_resolve_kernel<true> : (const void*)centre_resolve_kernel<false>;
-    if (lds > 48 * 1024 && lds > raised[wl_lds ? 1 : 0]) {
+    const size_t lds_rounds = rounds_lds(bt.n_max, bt.W);
+    const size_t lds = lds_rounds > RECHECK_LDS ? lds_rounds : RECHECK_LDS;
+    CentresArgs ca;
+    std::memset(&ca, 0, sizeof(ca));
+    ca.keys = k; ca.dk = dk; ca.idx = idx; ca.nn = w.nn; ca.rep = rep; ca.adj = w.adj; ca.rho = w.rho; ca.rho_opt = rho_opt;
+    ca.preds = w.preds; ca.heads = w.heads; ca.tie_list = w.tie_list; ca.tie_cnt = w.tie_cnt; ca.rho_fix = w.rho_fix;
+    ca.status = w.status; ca.cnum = w.cnum; ca.cmask = w.cmask; ca.center_idx = center_idx;
+    ca.write_rho = rank_opt ? 1 : 0;
+    // at most a workgroup per CU in all; without a second turn up to four tiles of 16 listed tokens in each sample
+    long workers = 0;
+    for (int b = 0; b < bt.B; ++b) workers += (bt.s[b].n + 15) / 16;
+    if (workers > 256 - bt.B) workers = 256 - bt.B;
+    static size_t raised[2] = {};
+    const int di = k_dt == PACT_BF16 ? 1 : 0;
+    if (lds > 48 * 1024 && lds > raised[di]) {
+        const void* fn = di ? (const void*)centres_kernel<PACT_BF16> : (const void*)centres_kernel<PACT_F32>;
         if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
             return PACT_ERR_HIP;
-        raised[wl_lds ? 1 : 0] = lds;
+        raised[di] = lds;
     }
-    if (wl_lds)
-        PACT_LAUNCH_SHMEM("centre_resolve", centre_resolve_kernel<true>, dim3(bt.B), dim3(1024), lds, st, bt, rep,
-                          w.adj, w.rho, rho_opt, w.preds, w.heads, idx, w.tie_list, w.tie_cnt, w.rho_fix, w.status,
-                          w.cnum, w.cmask, center_idx, w.worklist);
+    if (k_dt == PACT_BF16)
+        PACT_LAUNCH_SHMEM("centres", centres_kernel<PACT_BF16>, dim3(bt.B + workers), dim3(1024), lds, st, bt, ca);
     else
-        PACT_LAUNCH_SHMEM("centre_resolve", centre_resolve_kernel<false>, dim3(bt.B), dim3(1024), lds, st, bt, rep,
-                          w.adj, w.rho, rho_opt, w.preds, w.heads, idx, w.tie_list, w.tie_cnt, w.rho_fix, w.status,
-                          w.cnum, w.cmask, center_idx, w.worklist);
+        PACT_LAUNCH_SHMEM("centres", centres_kernel<PACT_F32>, dim3(bt.B + workers), dim3(1024), lds, st, bt, ca);
     if (rank_opt)          // (after the fp64 densities are in place)
         PACT_LAUNCH("density_rank", rank_kernel, dim3((bt.n_max + 63) / 64, bt.B), dim3(1024), st, bt, rep,
                     w.rho, rank_opt);

@@ -793,6 +793,30 @@ def test_scores_by_every_shape_of_heads(sizes, n_kv, n_q, d_h, hidden, dtype):
         assert_same(gu.trim(o, s.n, cu[b], b), oracle_reduce(s, dcs[b]), s, f"n={s.n} {n_kv}/{n_q} x {d_h} {dtype}")
 
 
+@pytest.mark.parametrize("n,dk,frac,dtype", [
+    (1, 8, 0.0, "bf16"), (63, 16, 0.1, "f32"), (130, 520, 0.05, "bf16"),
+    (1100, 64, 0.03, "f32"),         # hundreds of lists of 4 to 63 neighbours and of more than a record holds
+    (1400, 64, 0.2, "bf16"),         # more of the latter than the threads keep
+    (700, 3584, 0.01, "bf16"),       # wide rows: smaller work items of the fp64 densities
+    (8200, 16, 0.0005, "f32"),       # more tokens than have their lists' heads in LDS
+])
+def test_centres_with_lists_of_every_length(n, dk, frac, dtype):
+    r = np.random.default_rng(n + dk)
+    cen = r.normal(size=(max(2, n // 12), dk))
+    u = cen[r.integers(0, cen.shape[0], n)] + 0.25 * r.normal(size=(n, dk))
+    half = n // 3
+    u[half:2 * half] = u[:half] + 1e-3 * r.normal(size=(half, dk))      # densities that fp32 terms cannot order
+    u = (gen.round_to_bf16(u) if dtype == "bf16" else u).astype(np.float32)
+    d_c = _gap_dc(u, frac=frac, window=min(300, max(2, n * (n - 1) // 8))) if n > 2 else 0.3
+    ref = po.dbdpc(u.astype(np.float64), d_c, 2.0)
+    out = P.dbdpc_cluster(gu.dev(u, dtype), d_c, 2.0, want_rho=True, want_rank=True)
+    torch.cuda.synchronize()
+    rep = P.read_report(out["rep"])
+    np.testing.assert_allclose(out["rho"].cpu().numpy(), ref["rho"], rtol=1e-7, atol=0)
+    assert np.array_equal(out["center_idx"][: rep["n_centers"]].cpu().numpy(), ref["centers"])
+    assert np.array_equal(out["cluster_id"].cpu().numpy(), ref["labels"])
+
+
 @pytest.mark.parametrize("n,dk,shift", [(130, 64, 0.0), (127, 64, 40.0), (257, 128, 40.0), (300, 192, 0.0), (385, 192, 40.0),
                                         (129, 512, 300.0), (260, 4, 0.0), (96, 33024, 0.0), (96, 66048, 900.0)])
 def test_fp32_keys_as_integers(n, dk, shift):
