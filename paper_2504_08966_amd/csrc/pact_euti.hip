@@ -94,11 +94,13 @@ __device__ __forceinline__ void hnorm_job(const FrontArgs& a, int wave_no, int t
     else hnorm_rows<HDT, 1>(a.hidden, a.h, g0, total, lane, a.hnorm, a.stream != 0);
 }
 
-// Sample that token g of the batch belongs to (wave-uniform).
-__device__ __forceinline__ int sample_of(const Batch& bt, int g, int lane) {
-    if (bt.B == 1) return 0;
-    const uint64_t m = __ballot(lane < bt.B && bt.s[lane < bt.B ? lane : 0].base <= g);
-    return __builtin_amdgcn_readfirstlane(__popcll(m) - 1);
+// Sample that token g of the batch belongs to (g the same for the wavefront: scalar loads, a vector load of an argument is a trip to memory).
+__device__ __forceinline__ int sample_of(const Batch& bt, int g) {
+    g = __builtin_amdgcn_readfirstlane(g);
+    int b = 0;
+    for (int step = PACT_MAX_BATCH / 2; step; step >>= 1)
+        if (b + step < bt.B && bt.s[b + step].base <= g) b += step;
+    return b;
 }
 
 // One clustering key by KL lanes (16, 32 or 64; a row of at most KL 16-byte chunks for KL < 64): the
@@ -109,7 +111,7 @@ __device__ __forceinline__ void key_job(const Batch& bt, const FrontArgs& a, int
     const int kl = lane & (KL - 1);
     const int g0 = wave_no * (64 / KL);
     if (g0 >= bt.total) return;
-    const int b0 = sample_of(bt, g0, lane);
+    const int b0 = sample_of(bt, g0);
     const int gi = g0 + lane / KL;
     if (gi >= bt.total) return;
     // (the tokens of a wavefront may straddle samples)

@@ -793,6 +793,28 @@ def test_scores_by_every_shape_of_heads(sizes, n_kv, n_q, d_h, hidden, dtype):
         assert_same(gu.trim(o, s.n, cu[b], b), oracle_reduce(s, dcs[b]), s, f"n={s.n} {n_kv}/{n_q} x {d_h} {dtype}")
 
 
+@pytest.mark.parametrize("h,dtype,out", [(8, "bf16", "f32"), (504, "bf16", "bf16"), (512, "f32", "f32"), (1032, "bf16", "f32"),
+                                         (1024, "f32", "bf16"), (2048, "bf16", "bf16"), (2056, "bf16", "f32")])
+def test_merge_by_every_row_width_and_cluster_size(h, dtype, out):
+    # rows of 1, 2, 4 and more KB; clusters of one row, of as many as are noted, one more, more than a wavefront's lanes,
+    # more than a list in LDS holds
+    sizes = [1, 2, 4, 9, 31, 32, 33, 64, 65, 130, 1024, 1025, 0, 3]
+    cid = np.repeat(np.arange(len(sizes)), sizes)
+    r = np.random.default_rng(h)
+    cid = np.concatenate([cid, np.full(40, -1)])[r.permutation(cid.size + 40)].astype(np.int32)
+    n = cid.size
+    hid = r.normal(size=(n, h)).astype(np.float32)
+    hid = (gen.round_to_bf16(hid) if dtype == "bf16" else hid).astype(np.float32)
+    rep = P.new_report(1)
+    rep[0, 2] = len(sizes)
+    merged, counts = P.pact_merge(gu.dev(hid, dtype), torch.from_numpy(cid).cuda(), rep,
+                                  out_dtype=torch.bfloat16 if out == "bf16" else torch.float32)
+    torch.cuda.synchronize()
+    assert counts[: len(sizes)].cpu().numpy().tolist() == sizes
+    ref = np.stack([hid[cid == c].astype(np.float64).mean(0) if m else np.zeros(h) for c, m in enumerate(sizes)])
+    np.testing.assert_allclose(merged[: len(sizes)].float().cpu().numpy(), ref, rtol=4e-3 if out == "bf16" else 2e-7, atol=1e-9)
+
+
 @pytest.mark.parametrize("n,dk,frac,dtype", [
     (1, 8, 0.0, "bf16"), (63, 16, 0.1, "f32"), (130, 520, 0.05, "bf16"),
     (1100, 64, 0.03, "f32"),         # hundreds of lists of 4 to 63 neighbours and of more than a record holds
