@@ -1112,88 +1112,6 @@ __device__ __forceinline__ void join_cluster(const NearArgs& a, pact_report* rp,
     }
 }
 
-// Alg. 2 last loop: every kept token joins the nearest centre.  Candidates are the centres
-// its bitmap row reaches (the nearest centre is within d_c, hence one of them; it need not
-// precede the token); with one candidate no distance is needed, otherwise Eq. 5 is
-// evaluated (fp32 screen, fp64 where it matters).  One wavefront per kept token, 4 per block.
-template <int DT>
-__device__ __forceinline__ void assign_body(const Batch& bt, const NearArgs& a, int blk, lds_i32* cand,
-                                            lds_i32* ctok, lds_f32* ccos) {
-    pact_report* rep = a.rep;
-    const char* keys = a.keys;
-    const int dk = a.dk;
-    const int32_t* idx = a.idx;
-    const double* nn = a.nn;
-    const uint64_t* adj = a.adj;
-    const uint64_t* cmask = a.cmask;
-    const uint32_t* status = a.status;
-    const int32_t* cnum = a.cnum;
-    const float margin = a.margin;
-    int32_t* cluster_id = a.cluster_id;
-    int32_t* cluster_counts = a.cluster_counts;
-    const int b = blockIdx.y;
-    const Seg sg = bt.s[b];
-    const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
-    const int p = blk * 4 + wave;
-    const int q = clamp_count(rep[b].n_kept, sg.n);
-    if (p >= q) return;
-    const int32_t* ix = idx + sg.base;
-    const int32_t* cn = cnum + (size_t)b * bt.n_max;
-    const uint32_t* st = status + (size_t)b * bt.n_max;
-    const double* nnb = nn + sg.base;
-    const uint64_t* row = adj + ((size_t)b * bt.n_max + p) * bt.W;
-    const uint64_t* cm = cmask + (size_t)b * bt.W;
-    const int tok = ix[p];
-    const uint32_t stp = st[p];
-    const int cnp = cn[p];
-    // (the first 64 words of the row and of the centre mask go out with them, before the status
-    //  is looked at: a trip less for the tokens that are not centres)
-    const uint64_t first = (lane < bt.W) ? (row[lane] & cm[lane]) : 0ull;
-    int cid;
-    if (stp == ST_CENTER) {
-        cid = cnp;
-    } else {
-        const size_t row_bytes = (size_t)dk * Elem<DT>::BYTES;
-        const char* kb = keys + (size_t)sg.base * row_bytes;
-        const char* mine = kb + (size_t)tok * row_bytes;
-        const double nnp = nnb[tok];
-        double best = INFINITY;
-        int bestj = 0x7FFFFFFF;
-        auto tok_of = [&](int j) { return ix[j]; };
-        const int Wq = (q + 63) >> 6;
-        int nbuf = 0, ntot = 0;
-        for (int w0 = 0; w0 < Wq; w0 += 64) {
-            const int w = w0 + lane;
-            BitPop bp{(w < Wq) ? (w0 == 0 ? first : (row[w] & cm[w])) : 0ull};
-            while (bp.any()) {
-                int bit;
-                const bool has = bp.pop(bit);
-                const int j = (w << 6) + bit;
-                const bool ok = has && j < q;
-                const uint64_t m = __ballot(ok);
-                if (ok) cand[nbuf + lanes_below(m, lane)] = j;
-                nbuf += __popcll(m);
-                ntot += __popcll(m);
-                if (nbuf > CAND_BUF - 64) {
-                    nearest_candidate<DT>(cand, ctok, ccos, nbuf, false, mine, nnp, kb, row_bytes, nnb, dk,
-                                          lane, INFINITY, margin, tok_of, best, bestj);
-                    nbuf = 0;
-                }
-            }
-        }
-        if (ntot == 1) bestj = cand[0];                 // a single centre in reach: no distance needed
-        else if (nbuf) nearest_candidate<DT>(cand, ctok, ccos, nbuf, nbuf == ntot, mine, nnp, kb, row_bytes, nnb,
-                                             dk, lane, INFINITY, margin, tok_of, best, bestj);
-        cid = bestj != 0x7FFFFFFF ? cn[bestj] : -1;
-    }
-    if (lane == 0) {
-        cluster_id[sg.base + tok] = cid;
-        if (cid >= 0 && cluster_counts) join_cluster(a, rep + b, sg.base, cid, tok);
-        note_odd_norm(rep + b, nnb[tok]);
-    }
-}
-
 // Dot product in fp64 of the rows `mine` and `other` by the 16 lanes part = 0..15 of a group
 // (lane `part` takes the 16-byte chunks part, part + 16, ...; four chunks of either row in
 // flight per lane).  Every lane of the group gets the sum.
@@ -1213,18 +1131,225 @@ __device__ __forceinline__ double group_dot64(const char* mine, const char* othe
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             if (k0 + 16 * u < nchunk) {
-                // (the chunk is tied to the running sum so that the conversions of all chunks are
-                //  not hoisted ahead of the additions: registers decide this kernel's occupancy)
+                // (each word is tied to the running sum, so that conversions are not hoisted ahead of the
+                //  additions: registers decide this kernel's occupancy)
                 asm volatile("" : "+v"(va[u].x), "+v"(vb[u].x) : "v"(acc));
-                double a[8], x[8];
-                Elem<DT>::widen(va[u], a);
-                Elem<DT>::widen(vb[u], x);
+                if constexpr (DT == PACT_BF16) {
+                    const uint32_t wa[4] = {va[u].x, va[u].y, va[u].z, va[u].w}, wb[4] = {vb[u].x, vb[u].y, vb[u].z, vb[u].w};
 #pragma unroll
-                for (int i = 0; i < EPL; ++i) acc = fma(a[i], x[i], acc);
+                    for (int i = 0; i < 4; ++i) {
+                        uint32_t p = wa[i], r = wb[i];
+                        asm volatile("" : "+v"(p), "+v"(r) : "v"(acc));
+                        acc = fma((double)__uint_as_float(p << 16), (double)__uint_as_float(r << 16), acc);
+                        acc = fma((double)__uint_as_float(p & 0xFFFF0000u), (double)__uint_as_float(r & 0xFFFF0000u), acc);
+                    }
+                } else {
+                    double a[8], x[8];
+                    Elem<DT>::widen(va[u], a);
+                    Elem<DT>::widen(vb[u], x);
+#pragma unroll
+                    for (int i = 0; i < EPL; ++i) acc = fma(a[i], x[i], acc);
+                }
             }
         }
     }
     return group_sum_f64(acc, 16);
+}
+
+// 16 lanes per token.  The set bits of words wb + part + 16 u (lane `part` of the group holds word[u]) as numbers from 64 wb on: those
+// from the skip-th to the LIST_TURN - 1 after it into the token's list in LDS, n of them; ntot counts all.
+constexpr int LIST_TURN = 16;
+__device__ __forceinline__ void list_bits(const uint64_t (&word)[4], int wb, int lane, int skip, lds_i32* list, int& n, int& ntot) {
+    const int part = lane & 15, gbase = lane & ~15;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        uint32_t who = (uint32_t)(__ballot(word[u] != 0) >> gbase) & 0xFFFFu;
+        while (who) {
+            const int src = __builtin_ctz(who);
+            who &= who - 1;
+            uint64_t bits = __shfl(word[u], gbase + src, 64);
+            const int cbase = (wb + src + 16 * u) << 6;
+            while (bits) {
+                const int c = cbase + __builtin_ctzll(bits);
+                bits &= bits - 1;
+                if (ntot >= skip && n < LIST_TURN) {
+                    if (part == 0) list[n] = c;
+                    ++n;
+                }
+                ++ntot;
+            }
+        }
+    }
+}
+// fp64 for the n listed candidates (token_of[c]: a candidate's token): their tokens and norms in one trip, then row by row.
+template <int DT>
+__device__ __forceinline__ void nearest_listed(const lds_i32* list, int n, int lane, const char* mine, double nnp, const char* kb,
+                                               size_t row_bytes, const double* nnb, const int32_t* token_of, double thr,
+                                               double& best, int& bestc) {
+    const int part = lane & 15, gbase = lane & ~15, nchunk = (int)(row_bytes / 16);
+    int ctk = 0, cid = 0;
+    double cnn = 0.0;
+    if (part < n) {
+        cid = list[part];
+        ctk = token_of[cid];
+        cnn = nnb[ctk];
+    }
+#pragma unroll 1
+    for (int k = 0; k < n; ++k) {
+        const int c = __shfl(cid, gbase + k, 64);
+        const int tc = __shfl(ctk, gbase + k, 64);
+        const double nc = __shfl(cnn, gbase + k, 64);
+        const double d = cos_dist64(group_dot64<DT>(mine, kb + (size_t)tc * row_bytes, nchunk, part), nnp, nc);
+        if (d < thr && (d < best || (d == best && c < bestc))) { best = d; bestc = c; }
+    }
+}
+
+// Alg. 2 last loop: every kept token joins the nearest centre.  Candidates are the centres
+// its bitmap row reaches (the nearest centre is within d_c, hence one of them; it need not
+// precede the token); with one candidate no distance is needed, otherwise Eq. 5 is
+// evaluated (fp32 screen, fp64 where it matters).
+// TPW tokens per wavefront, 64 / TPW lanes each, as long as they look for their candidates: one while the chip holds a wavefront for
+// each token, four beyond that.  Up to four candidates of a token are then compared in fp64 by its 16 lanes, row by row; more take
+// the whole wavefront, token by token (fp32 cosines of eight candidates at a time, fp64 for those that are left).
+// 27 600 kept tokens of 8 videos 31 -> 21 us, 18 200 of 16 ragged images 29 -> 26 us.
+template <int DT, int TPW>
+__device__ __forceinline__ void assign_body(const Batch& bt, const NearArgs& a, int blk, lds_i32* cand,
+                                            lds_i32* ctok, lds_f32* ccos, lds_i32* s_c) {
+    constexpr int GL = 64 / TPW, WPL = 64 / GL;            // lanes per token, bitmap words per lane and turn
+    pact_report* rep = a.rep;
+    const int dk = a.dk;
+    const double* nn = a.nn;
+    const uint64_t* cmask = a.cmask;
+    const int b = blockIdx.y;
+    const Seg sg = bt.s[b];
+    const int lane = threadIdx.x & 63, gl = lane & (GL - 1);
+    const int wave = threadIdx.x >> 6;
+    const int pw = (blk * 4 + wave) * TPW;
+    const int q = clamp_count(rep[b].n_kept, sg.n);
+    if (pw >= q) return;
+    const int p = pw + lane / GL;
+    const bool on = p < q;
+    const int32_t* ix = a.idx + sg.base;
+    const int32_t* cn = a.cnum + (size_t)b * bt.n_max;
+    const uint32_t* st = a.status + (size_t)b * bt.n_max;
+    const double* nnb = nn + sg.base;
+    const uint64_t* row = a.adj + ((size_t)b * bt.n_max + min(p, q - 1)) * bt.W;
+    const uint64_t* cm = cmask + (size_t)b * bt.W;
+    const int tok = ix[min(p, q - 1)];
+    const uint32_t stp = st[min(p, q - 1)];
+    const int cnp = cn[min(p, q - 1)];
+    // (the first 64 words of the row and of the centre mask go out with them, before the status
+    //  is looked at: a trip less for the tokens that are not centres)
+    uint64_t first[WPL];
+#pragma unroll
+    for (int u = 0; u < WPL; ++u) {
+        const int w = gl + GL * u;
+        first[u] = w < bt.W ? row[w] & cm[w] : 0ull;
+    }
+    const int Wq = (q + 63) >> 6;
+    const bool centre = stp == ST_CENTER;
+    // the number of candidates (at most one per lane counts), and the first lane's that has one
+    int cid = cnp, some = 0, j1 = -1;
+    if (!centre) {
+#pragma unroll
+        for (int u = 0; u < WPL; ++u) {
+            const int w = gl + GL * u;
+            if (w == Wq - 1 && (q & 63)) first[u] &= (1ull << (q & 63)) - 1ull;
+            if (w >= Wq) first[u] = 0ull;
+            if (first[u] && j1 < 0) j1 = (w << 6) + __builtin_ctzll(first[u]);
+            some += __popcll(first[u]);
+        }
+        for (int w = 64 + gl; w < Wq; w += GL) {
+            uint64_t word = row[w] & cm[w];
+            if (w == Wq - 1 && (q & 63)) word &= (1ull << (q & 63)) - 1ull;
+            if (word && j1 < 0) j1 = (w << 6) + __builtin_ctzll(word);
+            some += __popcll(word);
+        }
+    }
+    const uint64_t gmask = GL == 64 ? ~0ull : ((1ull << (GL & 63)) - 1ull) << (lane & ~(GL - 1));
+    const uint64_t have = __ballot(some > 0) & gmask, many = __ballot(some > 1) & gmask;
+    const bool several = !centre && (many != 0 || (have & (have - 1)) != 0);
+    if (!centre) {
+        const int j = __shfl(j1, have ? __builtin_ctzll(have) : lane, 64);
+        cid = have && !several ? cn[j] : -1;               // a single centre in reach: no distance needed
+    }
+    const size_t row_bytes = (size_t)dk * Elem<DT>::BYTES;
+    const char* kb = a.keys + (size_t)sg.base * row_bytes;
+    const bool few = TPW > 1 && group_sum_f32<16>((float)min(some, 1024)) <= 4.0f;
+    if constexpr (TPW == 4) {
+        if (several && few && on) {                        // (the same for a token's lanes)
+            lds_i32* list = s_c + (threadIdx.x >> 4) * LIST_TURN;
+            double best = INFINITY;
+            int bestj = 0x7FFFFFFF;
+            int n = 0, ntot = 0;
+            list_bits(first, 0, lane, 0, list, n, ntot);
+#pragma unroll 1
+            for (int wb = 64; wb < Wq; wb += 64) {
+                uint64_t word[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int w = wb + gl + 16 * u;
+                    word[u] = w < Wq ? row[w] & cm[w] : 0ull;
+                    if (w == Wq - 1 && (q & 63)) word[u] &= (1ull << (q & 63)) - 1ull;
+                }
+                list_bits(word, wb, lane, 0, list, n, ntot);
+            }
+            nearest_listed<DT>(list, n, lane, kb + (size_t)tok * row_bytes, nnb[tok], kb, row_bytes, nnb, ix, INFINITY, best, bestj);
+            cid = bestj;
+        }
+    }
+    uint64_t todo = __ballot(several && on && gl == 0 && !(TPW > 1 && few));
+    while (todo) {
+        const int l0 = __builtin_ctzll(todo);
+        todo &= todo - 1;
+        const bool mine_g = (lane & ~(GL - 1)) == l0;
+        const int pa = pw + l0 / GL, toka = __builtin_amdgcn_readlane(tok, l0);
+        const uint64_t* rowa = a.adj + ((size_t)b * bt.n_max + pa) * bt.W;
+        const char* mine = kb + (size_t)toka * row_bytes;
+        const double nnp = nnb[toka];
+        double best = INFINITY;
+        int bestj = 0x7FFFFFFF;
+        auto tok_of = [&](int j) { return ix[j]; };
+        int nbuf = 0, ntot = 0;
+        auto list = [&](uint64_t word, int w) __attribute__((always_inline)) {
+            BitPop bp{word};
+            while (bp.any()) {
+                int bit;
+                const bool ok = bp.pop(bit);
+                const uint64_t m = __ballot(ok);
+                if (ok) cand[nbuf + lanes_below(m, lane)] = (w << 6) + bit;
+                nbuf += __popcll(m);
+                ntot += __popcll(m);
+                if (nbuf > CAND_BUF - 64) {
+                    nearest_candidate<DT>(cand, ctok, ccos, nbuf, false, mine, nnp, kb, row_bytes, nnb, dk,
+                                          lane, INFINITY, a.margin, tok_of, best, bestj);
+                    nbuf = 0;
+                }
+            }
+        };
+#pragma unroll 1
+        for (int u = 0; u < WPL; ++u) {
+            list(mine_g ? first[0] : 0ull, gl + GL * u);
+#pragma unroll
+            for (int v = 0; v + 1 < WPL; ++v) if (mine_g) first[v] = first[v + 1];
+        }
+#pragma unroll 1
+        for (int w0 = 64; w0 < Wq; w0 += 64) {
+            const int w = w0 + lane;
+            uint64_t word = w < Wq ? rowa[w] & cm[w] : 0ull;
+            if (w == Wq - 1 && (q & 63)) word &= (1ull << (q & 63)) - 1ull;
+            list(word, w);
+        }
+        if (nbuf) nearest_candidate<DT>(cand, ctok, ccos, nbuf, nbuf == ntot, mine, nnp, kb, row_bytes, nnb,
+                                        dk, lane, INFINITY, a.margin, tok_of, best, bestj);
+        if (mine_g) cid = bestj;                           // (a position; its cluster below, for all tokens at once)
+    }
+    if (several && on) cid = cid >= 0 && cid != 0x7FFFFFFF ? cn[cid] : -1;
+    if (gl == 0 && on) {
+        a.cluster_id[sg.base + tok] = cid;
+        if (cid >= 0 && a.cluster_counts) join_cluster(a, rep + b, sg.base, cid, tok);
+        note_odd_norm(rep + b, nnb[tok]);
+    }
 }
 
 // Eq. 8/9: every pruned token joins the nearest centre iff its fp64 distance is below
@@ -1238,8 +1363,7 @@ __device__ __forceinline__ double group_dot64(const char* mine, const char* othe
 // What a token costs is its chain of dependent memory accesses, so 16 lanes work on one token
 // (16 tokens per block and turn): the values and words of 64 groups arrive in one trip and are
 // kept for the listing, a candidate row in another.  Blocks blk = 0 .. nblk-1, 256 threads.
-// s_c: [16][RECOVER_LIST] candidate ids per token slot.
-constexpr int RECOVER_LIST = 16;
+// s_c: [16][LIST_TURN] candidate ids per token slot.
 template <int DT>
 __device__ __forceinline__ void recover_body(const Batch& bt, const NearArgs& a, int blk, int nblk, lds_i32* s_c) {
     pact_report* rep = a.rep;
@@ -1251,7 +1375,6 @@ __device__ __forceinline__ void recover_body(const Batch& bt, const NearArgs& a,
     const int q = clamp_count(rep[b].n_kept, sg.n), np = clamp_count(rep[b].n_pruned, sg.n - q),
               C = clamp_count(rep[b].n_centers, q);
     const size_t row_bytes = (size_t)a.dk * Elem<DT>::BYTES;
-    const int nchunk = (int)(row_bytes / 16);
     const char* kb = a.keys + (size_t)sg.base * row_bytes;
     const double* nnb = a.nn + sg.base;
     const int32_t* co = a.center_idx + sg.base;
@@ -1265,8 +1388,8 @@ __device__ __forceinline__ void recover_body(const Batch& bt, const NearArgs& a,
     const int Wc = (C + 63) >> 6;
     const float* cb = a.cbest + (size_t)b * bt.W * bt.n_max;        // [W][n_max]
     const uint64_t* cw = a.adj + ((size_t)b * bt.n_max + q) * bt.W; // [Wc][np]
-    const int part = tid & 15, ts = tid >> 4, gbase = lane & ~15;
-    lds_i32* list = s_c + ts * RECOVER_LIST;
+    const int part = tid & 15, ts = tid >> 4;
+    lds_i32* list = s_c + ts * LIST_TURN;
     for (int t = t_first; t < np; t += nblk * 16) {
         const int tok = pruned[t];
         int res = -1;                                               // -1: no centre in reach
@@ -1295,59 +1418,27 @@ __device__ __forceinline__ void recover_body(const Batch& bt, const NearArgs& a,
                 double best = INFINITY;
                 int bestc = 0x7FFFFFFF;
                 bool first_batch_loaded = true;
-                // The candidates are listed in the token's LDS slots, RECOVER_LIST per turn (one
+                // The candidates are listed in the token's LDS slots, LIST_TURN per turn (one
                 // turn unless the token is degenerate); all control flow from here on is uniform
                 // within the 16 lanes of a token.
 #pragma unroll 1
-                for (int skip = 0;; skip += RECOVER_LIST) {
+                for (int skip = 0;; skip += LIST_TURN) {
                     int n = 0, ntot = 0;
 #pragma unroll 1
                     for (int wb = 0; wb < Wc; wb += 64) {
                         if (!first_batch_loaded) load_batch(wb);     // (the first turn starts with the values already here)
                         first_batch_loaded = false;
+                        uint64_t within[4];
 #pragma unroll
-                        for (int u = 0; u < 4; ++u) {
-                            const uint64_t wv = (v[u] >= floor32) ? word[u] : 0ull;
-                            uint32_t who = (uint32_t)(__ballot(wv != 0) >> gbase) & 0xFFFFu;
-                            while (who) {
-                                const int src = __builtin_ctz(who);
-                                who &= who - 1;
-                                uint64_t bits = __shfl(wv, gbase + src, 64);
-                                const int cbase = (wb + src + 16 * u) << 6;
-                                while (bits) {
-                                    const int c = cbase + __builtin_ctzll(bits);
-                                    bits &= bits - 1;
-                                    if (ntot >= skip && n < RECOVER_LIST) {
-                                        if (part == 0) list[n] = c;
-                                        ++n;
-                                    }
-                                    ++ntot;
-                                }
-                            }
-                        }
+                        for (int u = 0; u < 4; ++u) within[u] = (v[u] >= floor32) ? word[u] : 0ull;
+                        list_bits(within, wb, lane, skip, list, n, ntot);
                     }
                     if (ntot == 1 && clear) {                          // decided by the fp32 screen alone
                         bestc = list[0];
                         break;
                     }
-                    // fp64 for the n listed candidates: their tokens and norms in one trip, then row by row
-                    int ctk = 0, cid = 0;
-                    double cnn = 0.0;
-                    if (part < n) {
-                        cid = list[part];
-                        ctk = co[cid];
-                        cnn = nnb[ctk];
-                    }
-                    const double nnp = nnb[tok];
-#pragma unroll 1
-                    for (int k = 0; k < n; ++k) {
-                        const int c = __shfl(cid, gbase + k, 64);
-                        const int tc = __shfl(ctk, gbase + k, 64);
-                        const double nc = __shfl(cnn, gbase + k, 64);
-                        const double d = cos_dist64(group_dot64<DT>(mine, kb + (size_t)tc * row_bytes, nchunk, part), nnp, nc);
-                        if (d < thr && (d < best || (d == best && c < bestc))) { best = d; bestc = c; }
-                    }
-                    if (skip + RECOVER_LIST >= ntot) break;
+                    nearest_listed<DT>(list, n, lane, mine, nnb[tok], kb, row_bytes, nnb, co, thr, best, bestc);
+                    if (skip + LIST_TURN >= ntot) break;
                 }
                 res = bestc != 0x7FFFFFFF ? bestc : -1;
             }
@@ -1369,35 +1460,40 @@ __device__ __forceinline__ void recover_body(const Batch& bt, const NearArgs& a,
 // PART: NEAREST_BOTH, or a build that holds one of the two searches only (the assignment alone
 // needs fewer registers and runs four wavefronts per SIMD instead of three).
 enum { NEAREST_BOTH = 0, NEAREST_ASSIGN = 1, NEAREST_RECOVER = 2 };
-template <int DT, int PART>
-__global__ __launch_bounds__(256) void nearest_centre_kernel(Batch bt, NearArgs a) {
+template <int DT, int PART, int TPW>
+__global__ __launch_bounds__(256, 4) void nearest_centre_kernel(Batch bt, NearArgs a) {
     __shared__ int s_cand[4][CAND_BUF], s_ctok[4][CAND_BUF];
     __shared__ float s_ccos[4][CAND_BUF];
-    __shared__ int s_list[16 * RECOVER_LIST];
+    __shared__ int s_list[16 * LIST_TURN];
     const int wave = threadIdx.x >> 6;
     lds_i32* cand = (lds_i32*)s_cand[wave];
     lds_i32* ctok = (lds_i32*)s_ctok[wave];
     lds_f32* ccos = (lds_f32*)s_ccos[wave];
-    if constexpr (PART == NEAREST_ASSIGN) assign_body<DT>(bt, a, blockIdx.x, cand, ctok, ccos);
+    if constexpr (PART == NEAREST_ASSIGN) assign_body<DT, TPW>(bt, a, blockIdx.x, cand, ctok, ccos, (lds_i32*)s_list);
     else if constexpr (PART == NEAREST_RECOVER) recover_body<DT>(bt, a, blockIdx.x, gridDim.x, (lds_i32*)s_list);
     else if ((int)blockIdx.x >= (int)gridDim.x - a.assign_blocks)
-        assign_body<DT>(bt, a, blockIdx.x - (gridDim.x - a.assign_blocks), cand, ctok, ccos);
+        assign_body<DT, TPW>(bt, a, blockIdx.x - (gridDim.x - a.assign_blocks), cand, ctok, ccos, (lds_i32*)s_list);
     else recover_body<DT>(bt, a, blockIdx.x, gridDim.x - a.assign_blocks, (lds_i32*)s_list);
 }
 
-template <int PART>
+template <int PART, int TPW>
 static int launch_nearest_part(const Batch& bt, const NearArgs& a, int blocks, pact_dtype k_dt, const char* name,
                                hipStream_t st) {
     dim3 grid(blocks, bt.B);
-    if (k_dt == PACT_BF16) PACT_LAUNCH(name, (nearest_centre_kernel<PACT_BF16, PART>), grid, dim3(256), st, bt, a);
-    else PACT_LAUNCH(name, (nearest_centre_kernel<PACT_F32, PART>), grid, dim3(256), st, bt, a);
+    if (k_dt == PACT_BF16) PACT_LAUNCH(name, (nearest_centre_kernel<PACT_BF16, PART, TPW>), grid, dim3(256), st, bt, a);
+    else PACT_LAUNCH(name, (nearest_centre_kernel<PACT_F32, PART, TPW>), grid, dim3(256), st, bt, a);
     return PACT_OK;
 }
-static int launch_nearest(const Batch& bt, const NearArgs& a, int recover_blocks, pact_dtype k_dt, const char* name,
+// a.assign_blocks: whether the assignment takes part.
+static int launch_nearest(const Batch& bt, NearArgs a, int recover_blocks, pact_dtype k_dt, const char* name,
                           hipStream_t st) {
-    if (recover_blocks == 0) return launch_nearest_part<NEAREST_ASSIGN>(bt, a, a.assign_blocks, k_dt, name, st);
-    if (a.assign_blocks == 0) return launch_nearest_part<NEAREST_RECOVER>(bt, a, recover_blocks, k_dt, name, st);
-    return launch_nearest_part<NEAREST_BOTH>(bt, a, a.assign_blocks + recover_blocks, k_dt, name, st);
+    if (a.assign_blocks == 0) return launch_nearest_part<NEAREST_RECOVER, 1>(bt, a, recover_blocks, k_dt, name, st);
+    const bool four = recover_blocks == 0 && kept_estimate(bt) > 8192;            // (see assign_body)
+    a.assign_blocks = (bt.n_max + (four ? 15 : 3)) / (four ? 16 : 4);
+    if (recover_blocks == 0)
+        return four ? launch_nearest_part<NEAREST_ASSIGN, 4>(bt, a, a.assign_blocks, k_dt, name, st)
+                    : launch_nearest_part<NEAREST_ASSIGN, 1>(bt, a, a.assign_blocks, k_dt, name, st);
+    return launch_nearest_part<NEAREST_BOTH, 1>(bt, a, a.assign_blocks + recover_blocks, k_dt, name, st);
 }
 
 // Stand-alone pact_reincorporate: totals of recovered / dropped tokens (the fused path gets
@@ -1435,9 +1531,7 @@ int launch_centres(const Batch& bt, const Ws& w, const void* keys, pact_dtype k_
 #undef PACT_SETTLE
     // One wavefront per kept token while the chip holds them all at once (32 per CU); beyond that four
     // tokens per wavefront (one image: 7.3 us against 9.5 us; 8 videos: 14.2 against 9.9 us).
-    long kept_est = 0;
-    for (int b = 0; b < bt.B; ++b) kept_est += bt.s[b].n - prune_rank(bt.s[b].lambda, bt.s[b].n);
-    if (kept_est <= 256 * 32)
+    if (kept_estimate(bt) <= 256 * 32)
         PACT_LAUNCH("build_preds", build_preds_kernel<64>, dim3((bt.n_max + 3) / 4, bt.B), dim3(256), st, bt, rep, w.adj, w.rho,
                     rho_opt, w.preds, w.heads, idx, w.tie_list, w.tie_cnt);
     else
@@ -1476,7 +1570,7 @@ int launch_centres(const Batch& bt, const Ws& w, const void* keys, pact_dtype k_
     a.rep = rep; a.keys = k; a.dk = dk; a.nn = w.nn; a.adj = w.adj; a.margin = (float)cos_margin(dk, k_dt);
     a.cluster_id = cluster_id; a.cluster_counts = cluster_counts;
     a.idx = idx; a.cmask = w.cmask; a.status = w.status; a.cnum = w.cnum;
-    a.assign_blocks = (bt.n_max + 3) / 4;
+    a.assign_blocks = 1;
     return launch_nearest(bt, a, 0, k_dt, "assign", st);
 }
 
@@ -1500,7 +1594,7 @@ int launch_reincorporate(const Batch& bt, const Ws& w, const void* keys, pact_dt
     a.pruned_idx = pruned_idx; a.center_idx = center_idx; a.cbest = w.cbest;
     if (kept_idx) {
         a.idx = kept_idx; a.cmask = w.cmask; a.status = w.status; a.cnum = w.cnum;
-        a.assign_blocks = (bt.n_max + 3) / 4;
+        a.assign_blocks = 1;
         a.slots = w.slots; a.big = w.big;     // (a full reduction: the merge follows)
     }
     if (kept_idx && bt.total >= 20000) {

@@ -217,6 +217,12 @@ __host__ __device__ inline int prune_rank(float lambda, int n) {
     if (m > n - 1) m = n - 1;
     return m < 0 ? 0 : m;
 }
+// Tokens that a call will keep, of all samples (the exact number of a sample is known on the device only: ties).
+inline long kept_estimate(const Batch& bt) {
+    long n = 0;
+    for (int b = 0; b < bt.B; ++b) n += bt.s[b].n - prune_rank(bt.s[b].lambda, bt.s[b].n);
+    return n;
+}
 
 enum { INIT_REDUCE = 0, INIT_DBDPC_ALL = 1, INIT_DBDPC_SUBSET = 2, INIT_REINC = 3, INIT_SCORE = 4 };
 

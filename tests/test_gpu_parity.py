@@ -793,6 +793,23 @@ def test_scores_by_every_shape_of_heads(sizes, n_kv, n_q, d_h, hidden, dtype):
         assert_same(gu.trim(o, s.n, cu[b], b), oracle_reduce(s, dcs[b]), s, f"n={s.n} {n_kv}/{n_q} x {d_h} {dtype}")
 
 
+@pytest.mark.parametrize("n,frac,dtype", [(8197, 0.0003, "f32"), (8320, 0.002, "bf16")])
+def test_assignment_of_more_tokens_than_wavefronts(n, frac, dtype):
+    # four tokens per wavefront: tokens with no more than four centres in reach, and (wide cutoff) with dozens; more than 64 words
+    # of bitmap, a last group of one token
+    r = np.random.default_rng(n)
+    cen = r.normal(size=(n // 8, 16))
+    u = cen[r.integers(0, cen.shape[0], n)] + 0.2 * r.normal(size=(n, 16))
+    u = (gen.round_to_bf16(u) if dtype == "bf16" else u).astype(np.float32)
+    d_c = _gap_dc(u, frac=frac)
+    ref = po.dbdpc(u.astype(np.float64), d_c, 2.0)
+    out = P.dbdpc_cluster(gu.dev(u, dtype), d_c, 2.0)
+    torch.cuda.synchronize()
+    rep = P.read_report(out["rep"])
+    assert np.array_equal(out["center_idx"][: rep["n_centers"]].cpu().numpy(), ref["centers"])
+    assert np.array_equal(out["cluster_id"].cpu().numpy(), ref["labels"])
+
+
 @pytest.mark.parametrize("h,dtype,out", [(8, "bf16", "f32"), (504, "bf16", "bf16"), (512, "f32", "f32"), (1032, "bf16", "f32"),
                                          (1024, "f32", "bf16"), (2048, "bf16", "bf16"), (2056, "bf16", "f32")])
 def test_merge_by_every_row_width_and_cluster_size(h, dtype, out):
