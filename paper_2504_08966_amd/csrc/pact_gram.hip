@@ -88,8 +88,10 @@ template <int DT, int MI_, int NJ_, int WR_, int WC_, int STAGES, bool TURNS> st
     static constexpr int AHEAD = NSTAGE - 1;                             // slices in flight besides the one being multiplied
     static constexpr int NB = STAGE_BYTES / 1024 / WAVES;                // 1 KB blocks each wavefront brings per stage
     // workgroups of a launch: one per CU, or two where the registers and the ring leave room for them
-    static constexpr int SLOT_BITS = WAVES == 4 ? 9 : 8, SLOTS = 1 << SLOT_BITS;
-    static_assert(SLOTS * WAVES == GRAM_MAX_WORKGROUPS * 8, "a workgroup of eight wavefronts per CU, or two of four");
+    static constexpr bool PAIRED = WAVES == 4 && MI * NJ <= 4;
+    static constexpr int SLOT_BITS = PAIRED ? 9 : 8, SLOTS = 1 << SLOT_BITS;
+    static constexpr int WAVES_PER_SIMD = PAIRED || WAVES == 8 ? 2 : 1;
+    static_assert(SLOTS * WAVES <= GRAM_MAX_WORKGROUPS * 8, "a workgroup of eight wavefronts per CU, or two of four");
     static constexpr bool PINGPONG = TURNS;
     static_assert(!TURNS || WAVES == 8, "one wavefront of either group per SIMD");
     // k-groups per slice; k-groups per turn
@@ -211,13 +213,13 @@ __host__ __device__ __forceinline__ bool mirrored_tiles_pay(int t, int g) {
 }
 
 template <class SH, int MODE, bool STAT, bool SYM>
-__global__ __launch_bounds__(SH::THREADS, 2) void gram_kernel(Batch bt, GramArgs ga) {
+__global__ __launch_bounds__(SH::THREADS, SH::WAVES_PER_SIMD) void gram_kernel(Batch bt, GramArgs ga) {
     constexpr int MI = SH::MI, NJ = SH::NJ, WC = SH::WC, WAVES = SH::WAVES;
     constexpr int TILE_R = SH::TILE_R, TILE_C = SH::TILE_C, STAGE_BYTES = SH::STAGE_BYTES, NSTAGE = SH::NSTAGE;
     constexpr int SLICE_BYTES = SH::SLICE_BYTES;
     constexpr int AHEAD = SH::AHEAD, NB = SH::NB, WROWS = 32 * MI, WCOLS = 32 * NJ;
     constexpr bool I8 = SH::I8;
-    static_assert(MODE == MODE_CAND || WCOLS == 64, "a wavefront's columns are one bitmap word");
+    static_assert(MODE == MODE_CAND || NJ == 2 || NJ == 3, "a wavefront's columns are one bitmap word, or three halves");
     static_assert(MODE == MODE_DENSITY || WROWS % 64 == 0, "a wavefront's rows are whole groups of 64 centres");
     static_assert(!SYM || TILE_R == TILE_C, "mirrored tiles are square");
     extern __shared__ uint4 s_ring[];                         // TILE_R floats, then the ring's stages
@@ -653,7 +655,9 @@ __global__ __launch_bounds__(SH::THREADS, 2) void gram_kernel(Batch bt, GramArgs
             colP[j] = colW + j * 32 + l32;
             rj[j] = rj_pre[j] * sa_;
         }
-        double rho[2][2] = {{0.0, 0.0}, {0.0, 0.0}};
+        double rho[NJ][2];
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) rho[j][0] = rho[j][1] = 0.0;
         // per-wavefront buffer of undecided pairs, in a ring slot no wavefront reads any more
         lds_uint2* nearBuf = (lds_uint2*)(ring + freeStage * STAGE_BYTES + wave * (NEAR_BUF * 8));
         int nearN = 0;
@@ -735,10 +739,10 @@ __global__ __launch_bounds__(SH::THREADS, 2) void gram_kernel(Batch bt, GramArgs
 #pragma unroll
             for (int r = 0; r < 16; ++r)
 #pragma unroll
-                for (int j = 0; j < 2; ++j) acc[i][j][r] = fmaf(acc[i][j][r], rs[r] * rj[j], -a_);
+                for (int j = 0; j < NJ; ++j) acc[i][j][r] = fmaf(acc[i][j][r], rs[r] * rj[j], -a_);
             // d_ii = 0 exactly: only the blocks on the diagonal hold such elements
 #pragma unroll
-            for (int j = 0; j < 2; ++j)
+            for (int j = 0; j < NJ; ++j)
                 if (rowI == colW + j * 32) {
 #pragma unroll
                     for (int r = 0; r < 16; ++r)
@@ -750,13 +754,13 @@ __global__ __launch_bounds__(SH::THREADS, 2) void gram_kernel(Batch bt, GramArgs
                 for (int r = 0; r < 16; ++r) {
                     const bool pad = rowI + 8 * (r >> 2) + 4 * hh + (r & 3) >= nA;
 #pragma unroll
-                    for (int j = 0; j < 2; ++j) acc[i][j][r] = pad || colP[j] >= nB ? -INFINITY : acc[i][j][r];
+                    for (int j = 0; j < NJ; ++j) acc[i][j][r] = pad || colP[j] >= nB ? -INFINITY : acc[i][j][r];
                 }
             }
             // phase A2: density terms
             if (mirror) {
                 // ... which also belong to the densities of this tile's rows: sum them over
-                // the wavefront's 64 columns.  Eight rows x 2 columns per lane at a time; the 32
+                // the wavefront's columns.  Eight rows x NJ columns per lane at a time; the 32
                 // lanes of a half-wave halve their row sets three times (a lane gives up half of its
                 // rows' sums and adds what it receives for those it keeps; rows of 16 lanes swap in one
                 // instruction) and are left with one row each, four neighbouring lanes with parts of the same one.
@@ -765,11 +769,13 @@ __global__ __launch_bounds__(SH::THREADS, 2) void gram_kernel(Batch bt, GramArgs
                     double d[8];
 #pragma unroll
                     for (int r = 0; r < 8; ++r) {
-                        const double e0 = (double)__builtin_amdgcn_exp2f(acc[i][0][r8 + r]);
-                        const double e1 = (double)__builtin_amdgcn_exp2f(acc[i][1][r8 + r]);
-                        rho[0][r & 1] += e0;
-                        rho[1][r & 1] += e1;
-                        d[r] = e0 + e1;
+                        d[r] = 0.0;
+#pragma unroll
+                        for (int j = 0; j < NJ; ++j) {
+                            const double e = (double)__builtin_amdgcn_exp2f(acc[i][j][r8 + r]);
+                            rho[j][r & 1] += e;
+                            d[r] += e;
+                        }
                     }
 #pragma unroll
                     for (int k = 0; k < 4; ++k) d[k] = halves16(d[k], d[k + 4]);
@@ -787,26 +793,29 @@ __global__ __launch_bounds__(SH::THREADS, 2) void gram_kernel(Batch bt, GramArgs
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
 #pragma unroll
-                    for (int j = 0; j < 2; ++j) rho[j][r & 1] += (double)__builtin_amdgcn_exp2f(acc[i][j][r]);
+                    for (int j = 0; j < NJ; ++j) rho[j][r & 1] += (double)__builtin_amdgcn_exp2f(acc[i][j][r]);
                     if ((r & 3) == 3) __builtin_amdgcn_sched_barrier(0);   // bound the live ranges: registers are tight
                 }
             }
-            // phase B: one bit per pair; most 32 x 64 blocks have none set: test the block's maximum first
-            float mx = fmaxf(acc[i][0][0], acc[i][1][0]);
+            // phase B: one bit per pair; most blocks have none set: test the block's maximum first
+            auto over_block = [&](auto&& f) __attribute__((always_inline)) {        // f over a lane's elements of the block, two at a time
+                float v = acc[i][0][0];
 #pragma unroll
-            for (int r = 1; r < 16; ++r) mx = fmaxf(mx, fmaxf(acc[i][0][r], acc[i][1][r]));
+                for (int j = 0; j < NJ; j += 2)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) v = f(v, j + 1 < NJ ? f(acc[i][j][r], acc[i][j + 1 < NJ ? j + 1 : j][r]) : acc[i][j][r]);
+                return v;
+            };
+            const float mx = over_block([](float x, float y) { return fmaxf(x, y); });
             if (STAT) {
                 // the block's smallest exponent (largest distance); what is past the last row or column holds -inf
                 if (!edge) {
-                    float mn = fminf(acc[i][0][0], acc[i][1][0]);
-#pragma unroll
-                    for (int r = 1; r < 16; ++r) mn = fminf(mn, fminf(acc[i][0][r], acc[i][1][r]));
-                    far = fminf(far, mn);
+                    far = fminf(far, over_block([](float x, float y) { return fminf(x, y); }));
                 } else {
 #pragma unroll
                     for (int r = 0; r < 16; ++r)
 #pragma unroll
-                        for (int j = 0; j < 2; ++j) far = fminf(far, acc[i][j][r] == -INFINITY ? 0.0f : acc[i][j][r]);
+                        for (int j = 0; j < NJ; ++j) far = fminf(far, acc[i][j][r] == -INFINITY ? 0.0f : acc[i][j][r]);
                 }
             }
             if (__ballot(mx >= t_lo) == 0) continue;
@@ -819,36 +828,40 @@ __global__ __launch_bounds__(SH::THREADS, 2) void gram_kernel(Batch bt, GramArgs
             // Straight-line code per element is kept to compares and lane writes: this part is
             // unrolled 16 * MI times, and blocks that reach it are the minority, so its
             // instructions are rarely in the instruction cache when they are needed.
-            uint32_t wlo = 0, whi = 0, hlo = 0, hhi = 0;
+            uint32_t wlo = 0, whi = 0, hlo = 0, hhi = 0, w2 = 0, h2 = 0;      // (w2, h2: the third 32 columns)
             static_for<16>([&](auto r_tag) __attribute__((always_inline)) {
                 constexpr int r = decltype(r_tag)::value;
                 constexpr int k0 = 8 * (r >> 2) + (r & 3);            // row of the lanes with hh = 0; hh = 1: k0 + 4
                 const uint64_t m0 = __ballot(acc[i][0][r] >= t_lo);
                 const uint64_t m1 = __ballot(acc[i][1][r] >= t_lo);
-                if (MODE == MODE_DENSITY) {
-                    const uint64_t h0 = __ballot(acc[i][0][r] >= t_hi);
-                    const uint64_t h1 = __ballot(acc[i][1][r] >= t_hi);
-                    file_ballots2<k0>(wlo, whi, hlo, hhi, m0, m1, h0, h1);
-                } else {
-                    file_ballots<k0>(wlo, whi, m0, m1);
-                }
+                const uint64_t h0 = __ballot(acc[i][0][r] >= t_hi);
+                const uint64_t h1 = __ballot(acc[i][1][r] >= t_hi);
+                file_ballots2<k0>(wlo, whi, hlo, hhi, m0, m1, h0, h1);
+                if constexpr (NJ == 3) file_ballots<k0>(w2, h2, __ballot(acc[i][2][r] >= t_lo), __ballot(acc[i][2][r] >= t_hi));
             });
             // the 32 words of this block, one store instruction (the bitmap was cleared beforehand)
-            if (lane < 32 && (wlo | whi) != 0)
-                adj[(size_t)(rowI + lane) * bt.W + wordIdx] = ((uint64_t)whi << 32) | wlo;
+            if constexpr (NJ == 2) {
+                if (lane < 32 && (wlo | whi) != 0)
+                    adj[(size_t)(rowI + lane) * bt.W + wordIdx] = ((uint64_t)whi << 32) | wlo;
+            } else if (lane < 32) {
+                uint32_t* halves = (uint32_t*)adj + (size_t)(rowI + lane) * bt.W * 2 + (colW >> 5);
+                if (wlo) halves[0] = wlo;
+                if (whi) halves[1] = whi;
+                if (w2) halves[2] = w2;
+            }
             if (MODE == MODE_DENSITY && mirror) {
                 // the same bits for the mirror image: 32 rows of this block are 32 columns (half a
                 // bitmap word) of the rows that are this tile's columns; assembled in the lane
                 // from its 16 rows and completed by the lane 32 further on
 #pragma unroll
-                for (int j = 0; j < 2; ++j) {
+                for (int j = 0; j < NJ; ++j) {
                     uint32_t bits = 0u;
 #pragma unroll
                     for (int r = 0; r < 16; ++r)
                         bits |= (acc[i][j][r] >= t_lo) ? (1u << (8 * (r >> 2) + (r & 3))) : 0u;
                     bits <<= 4 * hh;
                     bits |= (uint32_t)__shfl_xor((int)bits, 32, 64);
-                    if (hh == j && colP[j] < nB && bits != 0u)
+                    if (hh == (j & 1) && colP[j] < nB && bits != 0u)
                         ((uint32_t*)adj)[((size_t)colP[j] * bt.W + (rowI >> 6)) * 2 + ((rowI >> 5) & 1)] = bits;
                 }
             }
@@ -856,18 +869,22 @@ __global__ __launch_bounds__(SH::THREADS, 2) void gram_kernel(Batch bt, GramArgs
                 // Undecided pairs: queue them for the fp64 check.  They collect in this wavefront's
                 // LDS buffer, every lane adding one pair of its row per turn; one atomic reserves
                 // list slots for a whole buffer (an atomic per pair would cost a memory round trip).
-                uint64_t band = ((uint64_t)(whi & ~hhi) << 32) | (wlo & ~hlo);   // zero in lanes 32..63
-                uint64_t has;
-                while ((has = __ballot(band != 0)) != 0) {
-                    if (band != 0) {
-                        const int c = __builtin_ctzll(band);
-                        band &= band - 1;
-                        nearBuf[nearN + __popcll(has & ((1ull << lane) - 1ull))] =
-                            u32x2_t{(uint32_t)(rowI + lane) | (mirror ? NEAR_MIRROR : 0u), (uint32_t)(colW + c)};
+                // (`band`: the row's undecided columns from column `col` on; zero in lanes 32..63)
+                auto queue = [&](uint64_t band, int col) __attribute__((always_inline)) {
+                    uint64_t has;
+                    while ((has = __ballot(band != 0)) != 0) {
+                        if (band != 0) {
+                            const int c = __builtin_ctzll(band);
+                            band &= band - 1;
+                            nearBuf[nearN + __popcll(has & ((1ull << lane) - 1ull))] =
+                                u32x2_t{(uint32_t)(rowI + lane) | (mirror ? NEAR_MIRROR : 0u), (uint32_t)(col + c)};
+                        }
+                        nearN += __popcll(has);
+                        if (nearN > NEAR_BUF - 32) flush_near();
                     }
-                    nearN += __popcll(has);
-                    if (nearN > NEAR_BUF - 32) flush_near();
-                }
+                };
+                queue(((uint64_t)(whi & ~hhi) << 32) | (wlo & ~hlo), colW);
+                if constexpr (NJ == 3) queue(w2 & ~h2, colW + 64);
             }
         }
         }
@@ -880,10 +897,10 @@ __global__ __launch_bounds__(SH::THREADS, 2) void gram_kernel(Batch bt, GramArgs
             // (131 072 such additions, one image's, take 0.1 us more than as many plain stores of partial
             // sums, which another kernel would have to add up.)
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
+            for (int j = 0; j < NJ; ++j) {
                 const double part = rho[j][0] + rho[j][1];
                 const double tot = part + __shfl_xor(part, 32, 64);
-                if (hh == j && rowW < nA && colP[j] < nB) unsafeAtomicAdd(&rho_b[colP[j]], tot);
+                if (hh == (j & 1) && rowW < nA && colP[j] < nB) unsafeAtomicAdd(&rho_b[colP[j]], tot);
             }
         }
         if (MODE == MODE_DENSITY && nearN > 0) flush_near();
@@ -1012,27 +1029,35 @@ static int launch_gram_shape(const Batch& bt, const GramArgs& ga_in, hipStream_t
 // The tiles.  256 x 256 has the best ratio of flops to bytes fetched; a launch lasts as many turns of 20 us (key
 // width 512) as its CUs have tiles.  Of the 128 x 128 tiles by four wavefronts a CU runs two at a time, one's
 // epilogue beside the other's multiplications: 11.4 us a turn for half the area, but a launch with
-// few tiles is over in 10, and the triangle of a sample divides better into turns.  gram_cost() has
-// what was measured (us, per turn and slice of 64 elements):
-//   4010 kept tokens 23 (256) / 25 (128), 1604: 18.5 / 11.4, 9012: 65 / 57, 8 x 3450: 81 / 69, 16 x 1604: 44 / 41
+// few tiles is over in 10, and the triangle of a sample divides better into turns.  192 x 192, four wavefronts of 3 x 3 blocks (one
+// per SIMD: 1.05 us a slice of 0.56 the area), for the samples whose triangle is then one turn: 3800 to 4224 kept tokens.
+// gram_cost() has what was measured (us, per turn and slice of 64 elements), key width 512 unless stated, 256 / 192 / 128:
+//   1600 kept tokens 23 / 20 / 11, 3600: 24 / 21 / 15, 4010: 24 / 21 / 24, 4600: 24 / 37 / 23, 6000: 45 / 54 / 32, 9012: 68 / 85 / 65;
+//   of width 3584 4010: 93 / 65 / 112, 7290: 173 / 187 / 191; of width 128 4010: 14 / 16 / 16, 6000: 31 / 37 / 22
 // bf16 tiles of 256 take turns at the matrix cores from key rows of 2 KB on: the loop over a row of 7 KB got 5%
 // shorter, over one of 1 KB the two turns' offset cost 0.8 us.  (Both are then near what the chip's
 // power allows: a slice of random keys takes 1.45 us, of keys that are mostly zeros 1.10 us, its MFMAs alone 1.02 us.)
 typedef Shape<PACT_BF16, 4, 2, 2, 4, 2, false> Tile256;
 typedef Shape<PACT_BF16, 4, 2, 2, 4, 2, true> Tile256Wide;
 typedef Shape<PACT_BF16, 2, 2, 2, 2, 2, false> Tile128;
+typedef Shape<PACT_BF16, 3, 3, 2, 2, 3, false> Tile192;        // density pass
 typedef Shape<PACT_I8X3, 1, 2, 4, 2, 3, true> TileI8;         // density pass
 typedef Shape<PACT_I8X3, 2, 1, 2, 4, 3, true> TileI8Cand;     // candidate pass (groups of 64 rows)
 constexpr int WIDE_KEYS = 1024;
 
 static double gram_cost(const Batch& bt, bool density, int tile, int dk, bool mirrored) {
-    const int slots = tile == 256 ? 256 : 512;
+    const int slots = tile == 128 ? 512 : 256;
     long tiles[PACT_MAX_BATCH], all = 0;
     for (int b = 0; b < bt.B; ++b) all += tiles[b] = tiles_estimate(bt.s[b], density, tile, tile, mirrored);
     const double slices = (dk + 63) / 64;
     const long turns = fewest_turns(bt.B, tiles, slots);
-    if (tile == 256) return turns * (8.0 + 1.5 * slices);
-    return all <= 256 ? 6.5 + 0.5 * slices : 3.0 + turns * (5.0 + 0.8 * slices);
+    if (!density) {
+        if (tile == 256) return turns * (8.0 + 1.5 * slices);
+        return all <= 256 ? 6.5 + 0.5 * slices : 3.0 + turns * (5.0 + 0.8 * slices);
+    }
+    if (tile == 256) return 2.5 + turns * (mirrored ? 12.2 + 1.25 * slices : 8.0 + 1.55 * slices);
+    if (tile == 192) return 2.8 + turns * (10.8 + 0.9 * slices);
+    return all <= 256 ? 6.2 + 0.6 * slices : turns == 1 ? 9.0 + 0.7 * slices : 0.8 + turns * (5.4 + 0.73 * slices);
 }
 
 template <class SH, int MODE>
@@ -1082,8 +1107,11 @@ int launch_gram_density(const Batch& bt, const Ws& w, const void* keys, pact_dty
     };
     if (k_dt == PACT_F32)
         return launch_gram<TileI8, MODE_DENSITY>(bt, ga, st, name, mirrored(128, TileI8::SLOTS), want_stat, stat_words);
-    const bool m256 = mirrored(256, Tile256::SLOTS), m128 = mirrored(128, Tile128::SLOTS);
-    if (gram_cost(bt, true, 128, dk, m128) < gram_cost(bt, true, 256, dk, m256))
+    const bool m256 = mirrored(256, Tile256::SLOTS), m192 = mirrored(192, Tile192::SLOTS), m128 = mirrored(128, Tile128::SLOTS);
+    const double c256 = gram_cost(bt, true, 256, dk, m256), c192 = gram_cost(bt, true, 192, dk, m192), c128 = gram_cost(bt, true, 128, dk, m128);
+    if (c192 < c128 && c192 < c256)
+        return launch_gram<Tile192, MODE_DENSITY>(bt, ga, st, name, m192, want_stat, stat_words);
+    if (c128 < c256)
         return launch_gram<Tile128, MODE_DENSITY>(bt, ga, st, name, m128, want_stat, stat_words);
     if (dk >= WIDE_KEYS) return launch_gram<Tile256Wide, MODE_DENSITY>(bt, ga, st, name, m256, want_stat, stat_words);
     return launch_gram<Tile256, MODE_DENSITY>(bt, ga, st, name, m256, want_stat, stat_words);

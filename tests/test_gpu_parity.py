@@ -838,6 +838,7 @@ def test_merge_by_every_row_width_and_cluster_size(h, dtype, out):
     (1400, 64, 0.2, "bf16"),         # more of the latter than the threads keep
     (700, 3584, 0.01, "bf16"),       # wide rows: smaller work items of the fp64 densities
     (8200, 16, 0.0005, "f32"),       # more tokens than have their lists' heads in LDS
+    (4033, 512, 0.002, "bf16"), (4224, 512, 0.002, "bf16"),   # tiles of 192: one token in the last ones, none missing
 ])
 def test_centres_with_lists_of_every_length(n, dk, frac, dtype):
     r = np.random.default_rng(n + dk)
