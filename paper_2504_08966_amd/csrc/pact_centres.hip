@@ -896,10 +896,15 @@ __device__ __forceinline__ void recheck_items(const Batch& bt, const CentresArgs
     }
 }
 
-// The fp64 densities of the listed tokens from their partial sums, and whether a pair of neighbours changes its order
-// by them: only listed tokens can (both tokens of a pair inside the band are listed), so all pairs of them are
-// looked at.  The densities are left in front of the partial sums.
-__device__ __forceinline__ bool order_changed(const Batch& bt, const CentresArgs& a, int b, int T, int q, int tiles,
+// The fp64 densities of the listed tokens from their partial sums, and what they change: ORDER_PAIRS where two listed
+// neighbours change their order, ORDER_BAND where a listed token moves by more than the band.  A neighbour that is not listed
+// is further away than the band at the larger of the two densities, hence on the same side of a token that moves by no more than the
+// band at its own: without ORDER_BAND only pairs of listed tokens can change.  With it any list of the sample may be out of date; a
+// list that still names a neighbour which by now follows the token would let the two wait for each other for good.  (The band is
+// a statistical bound, and tokens that are nearly all alike pass it: their terms share the rounding of the
+// token's reciprocal norm.)  The densities are left in front of the partial sums.
+enum { ORDER_PAIRS = 2, ORDER_BAND = 8 };
+__device__ __forceinline__ int order_changed(const Batch& bt, const CentresArgs& a, int b, int T, int q, int tiles,
                                               unsigned char* s_raw, int* s_flag) {
     const Seg sg = bt.s[b];
     const int tid = fresh_v(threadIdx.x), lane = tid & 63, wave = tid >> 6;
@@ -936,8 +941,12 @@ __device__ __forceinline__ bool order_changed(const Batch& bt, const CentresArgs
         if (t < T && (lane & 15) == 0) s_new[t] = acc;
     }
     __syncthreads();
-    bool changed = false;
+    bool changed = false, far = false;
     int fine = 0;
+    if (tid < T) {
+        const double d = s_new[tid] - s_old[tid];
+        far = !(d * d <= recheck_band2(sg.d_n) * s_old[tid]);           // (the comparison that lists tokens)
+    }
     constexpr int UN = 4;
     for (int e0 = tid; e0 < T * T; e0 += 1024 * UN) {
         int i[UN], j[UN];
@@ -958,7 +967,8 @@ __device__ __forceinline__ bool order_changed(const Batch& bt, const CentresArgs
             fine += d != 0.0 && fabs(d) <= 1e-11 * (nj + ni);
         }
     }
-    if (changed) s_flag[0] = 1;
+    if (changed) atomicOr(&s_flag[0], (int)ORDER_PAIRS);
+    if (far) atomicOr(&s_flag[0], (int)ORDER_BAND);
     if (fine) atomicAdd(&s_flag[1], fine);
     if (tid < T) {
         part_b[tid] = s_new[tid];
@@ -969,11 +979,12 @@ __device__ __forceinline__ bool order_changed(const Batch& bt, const CentresArgs
         if (s_flag[1]) atomicAdd(&a.rep[b].rho_near_ties, s_flag[1]);
         a.rep[b].rho_rechecked = T;
     }
-    return lane0_of(s_flag[0]) != 0;
+    return lane0_of(s_flag[0]);
 }
 
-// The fp64 densities take their places; the predecessor lists of the listed tokens are made again from them.
-__device__ __forceinline__ void replace_densities(const Batch& bt, const CentresArgs& a, int b, int T, int q, bool lists,
+// The fp64 densities take their places; the predecessor lists are made again from them: those of the listed tokens, or all of
+// the sample's (`changed`: what order_changed found).
+__device__ __forceinline__ void replace_densities(const Batch& bt, const CentresArgs& a, int b, int T, int q, int changed,
                                                   uint16_t* s_nb) {
     const int tid = fresh_v(threadIdx.x), lane = tid & 63, wave = tid >> 6;
     const int32_t* list = a.tie_list + (size_t)b * RHO_RECHECK_MAX;
@@ -982,9 +993,11 @@ __device__ __forceinline__ void replace_densities(const Batch& bt, const Centres
     __syncthreads();
     if (tid < T) rho_b[min(list[tid] & 0xFFFF, q - 1)] = part_b[tid];
     __syncthreads();                                   // (the values are read back by this workgroup only)
-    if (!lists) return;
-    for (int t = wave; t < T; t += 16) {
-        const int p = min(list[t] & 0xFFFF, q - 1);
+    if (!changed) return;
+    const bool all = (changed & ORDER_BAND) != 0;
+    const int n_lists = all ? q : T;
+    for (int t = wave; t < n_lists; t += 16) {
+        const int p = all ? t : min(list[t] & 0xFFFF, q - 1);
         preds_of_row<false, 64>(p, q, rho_b, a.adj + ((size_t)b * bt.n_max + p) * bt.W, a.preds + ((size_t)b * bt.n_max + p) * PRED_CAP,
                                 (uint16_t*)(a.heads + (size_t)b * bt.n_max + p), s_nb + wave * PREDS_SPREAD, lane, 0.0);
     }
@@ -998,7 +1011,7 @@ __device__ __forceinline__ void replace_densities(const Batch& bt, const Centres
 // densities in place and runs the rounds again.  Nobody waits for anybody: counters say who is last.
 // As two launches, one after the other: 4010-token image 28 -> 18 us, 8 videos of 3450 tokens 43 -> 31 us, 7290 rows of 7 KB
 // 97 -> 37 us, 16384 tokens with fp32 keys 140 -> 67 us (the fp64 products of 70 listed tokens).
-// tie_cnt[4b]: listed tokens; [4b + 1]: work items done; [4b + 2]: 1 looked at, 2 changed, 4 rounds run.
+// tie_cnt[4b]: listed tokens; [4b + 1]: work items done; [4b + 2]: 1 looked at, ORDER_PAIRS, ORDER_BAND, 4 rounds run.
 // grid (B + workers), block 1024, dynamic LDS: what run_rounds takes, at least RECHECK_LDS.
 template <int DT>
 __global__ __launch_bounds__(1024) void centres_kernel(Batch bt, CentresArgs a) {
@@ -1045,7 +1058,8 @@ __global__ __launch_bounds__(1024) void centres_kernel(Batch bt, CentresArgs a) 
         __syncthreads();
         return lane0_of(s_got);
     };
-    bool again = false, lists = false;
+    bool again = false;
+    int changed = 0;
     while (true) {
         if (!resolver) {
             if (item >= item_end) return;
@@ -1056,14 +1070,14 @@ __global__ __launch_bounds__(1024) void centres_kernel(Batch bt, CentresArgs a) 
             recheck_items<DT>(bt, a, fresh_s(b), fresh_s(T), fresh_s(q), fresh_s(item - from), fresh_s(to - from), tiles, s_dyn);
             item = to;
             if (meet(&a.tie_cnt[4 * b + 1], mine) != all - mine) continue;
-            lists = order_changed(bt, a, fresh_s(b), fresh_s(T), fresh_s(q), tiles, (unsigned char*)s_dyn, s_flag);
-            if (!(meet(&a.tie_cnt[4 * b + 2], lists ? 3 : 1) & 4)) continue;      // the rounds still run
-            again = lists || a.write_rho;
+            changed = order_changed(bt, a, fresh_s(b), fresh_s(T), fresh_s(q), tiles, (unsigned char*)s_dyn, s_flag);
+            if (!(meet(&a.tie_cnt[4 * b + 2], changed | 1) & 4)) continue;        // the rounds still run
+            again = changed || a.write_rho;
             if (!again) continue;
         }
         const int bs = fresh_s(b);
-        if (again) replace_densities(bt, a, bs, T, q, lists, (uint16_t*)s_dyn);
-        if (!again || lists) run_rounds(bt, a, bs, (unsigned char*)s_dyn, s_nshort, s_nlong, s_looks);
+        if (again) replace_densities(bt, a, bs, T, q, changed, (uint16_t*)s_dyn);
+        if (!again || changed) run_rounds(bt, a, bs, (unsigned char*)s_dyn, s_nshort, s_nlong, s_looks);
         if (!resolver) continue;
         if (again) return;
         T = a.tie_cnt[4 * bs];
@@ -1075,8 +1089,8 @@ __global__ __launch_bounds__(1024) void centres_kernel(Batch bt, CentresArgs a) 
         q = clamp_count(a.rep[bs].n_kept, bt.s[bs].n);
         const int seen = meet(&a.tie_cnt[4 * bs + 2], 4);
         if (!(seen & 1)) return;                       // that workgroup will find the rounds run
-        lists = (seen & 2) != 0;
-        again = lists || a.write_rho;
+        changed = seen & (ORDER_PAIRS | ORDER_BAND);
+        again = changed || a.write_rho;
         if (!again) return;
     }
 }

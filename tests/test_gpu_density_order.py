@@ -1,0 +1,93 @@
+"""The density order behind the centre selection (Alg. 2): the densities that decide it, what happens where
+the fp32-term sums had it wrong, and that a call's densities are the same on every run."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2504_08966_amd as P
+from oracle import pact_oracle as po
+
+pytestmark = pytest.mark.gpu
+LOG2E = 1.4426950408889634
+
+
+def _alike_with_copies(n, triples, d_n, seed):
+    """64-wide bf16 keys that are nearly all alike, and among them `triples` times three parallel keys v c, 2 v c and v c', whose true
+    densities are equal: the density pass's factor of the first two, 1/|v c| sqrt(log2(e) / d_n) in fp32, is rounded up by more than
+    the band stands for (all terms of a token share it), that of the third hardly.  (v holds integers up to 15 and c is at most 17, so
+    that the products are bf16 numbers.)"""
+    r = np.random.default_rng(seed)
+    base = r.standard_normal(64)
+    base *= 10.0 / np.abs(base).max()
+    v = np.clip(np.rint(base + r.standard_normal((n, 64))), -15, 15)
+    scales = np.arange(1, 18, 2, dtype=np.float64)
+    a = np.float32(LOG2E) / np.float32(d_n)
+    inv = 1.0 / (np.linalg.norm(v, axis=1)[:, None] * scales)
+    err = (inv.astype(np.float32) * np.sqrt(a)).astype(np.float64) / (inv * np.sqrt(np.float64(a))) - 1.0
+    u = v[:400] / np.linalg.norm(v[:400], axis=1)[:, None]
+    term = np.exp(-(1.0 - np.mean(u @ u.T)) / d_n)                       # of a typical pair
+    band = 2.0 ** -20 * (1.0 + 4.0 * LOG2E / d_n) * np.sqrt(n * term)
+    need = band / (0.9 * n * term / d_n)
+    level = np.where((err > 1e-9) & (err < 1e-8), scales, 0.0).max(axis=1)
+    pick = np.flatnonzero((err.max(axis=1) > need + 1.2e-8) & (level > 0))[:triples]
+    assert pick.size == triples
+    up = scales[np.argmax(err, axis=1)][pick, None]
+    x = v * r.choice(scales, n)[:, None]
+    x[pick] = v[pick] * up
+    twin, third = np.setdiff1d(np.arange(n), pick)[:2 * triples].reshape(2, triples)
+    x[twin], x[third] = 2.0 * v[pick] * up, v[pick] * level[pick, None]
+    at = r.permutation(n)                                                # token i goes to row at[i]
+    out = np.empty((n, 64), dtype=np.float32)
+    out[at] = x
+    return out, at[np.stack([pick, twin, third])]
+
+
+def _distances(x):
+    """Eq. 5 in fp64 (plain torch, on the GPU)."""
+    u = x.double()
+    u = u / u.norm(dim=1, keepdim=True)
+    d = (1.0 - u @ u.T).clamp_(0.0, 2.0)
+    d.fill_diagonal_(0.0)
+    return d
+
+
+def _centres_of(near, rho):
+    """Alg. 2's loop on given densities (equal ones by index)."""
+    blocked, centres = np.zeros(rho.size, dtype=bool), []
+    for i in po.density_order(rho):
+        if not blocked[i]:
+            centres.append(int(i))
+            blocked |= near[i]
+    return np.array(sorted(centres))
+
+
+@pytest.mark.parametrize("n,d_n", [(8000, 0.3), (8000, 0.4)])
+def test_tokens_that_move_past_the_band_leave_one_order(n, d_n):
+    # Of three parallel keys two are evaluated again, since their sums are equal, and the third is not: its sum is further away than the
+    # band.  The two fp64 densities then fall behind the third one: its list of predecessors, which names them, has to be
+    # made again with theirs, which name it (otherwise the three wait for each other for good).
+    keys, role = _alike_with_copies(n, 100, d_n, 3)
+    x = torch.from_numpy(keys).cuda().to(torch.bfloat16)
+    d_c = 1e-6                                                  # parallel keys are the only neighbours
+    # the fp32-term sums: with one of the three there are no neighbours, hence nothing is evaluated again; each of the other two adds 1
+    sums = np.zeros(n)
+    for k in range(3):
+        idx = np.setdiff1d(np.arange(n), np.delete(role, k, axis=0))
+        o = P.dbdpc_cluster(x, d_c, d_n, idx=torch.from_numpy(idx).int().cuda(),
+                            n_idx_dev=torch.tensor([idx.size], dtype=torch.int32, device="cuda"), want_rho=True)
+        assert P.read_report(o["rep"])["rho_rechecked"] == 0
+        sums[idx] = o["rho"].cpu().numpy()[:idx.size] + 2.0
+    o = P.dbdpc_cluster(x, d_c, d_n, want_rho=True, want_rank=True)
+    torch.cuda.synchronize()
+    rep, rho, rank = P.read_report(o["rep"]), o["rho"].cpu().numpy(), o["rank"].cpu().numpy()
+    first, third = role[0], role[2]
+    passed = (sums[first] > sums[third]) & (rho[first] < rho[third])
+    print(f"n={n} d_n={d_n}: listed {rep['rho_rechecked']}, passed {passed.sum()}, centres {rep['n_centers']}")
+    assert rep["rho_rechecked"] >= 200 and rep["refine_overflow"] == 0 and passed.sum() >= 20
+    d = _distances(x)
+    exact = torch.exp(-d / float(np.float32(d_n))).sum(1).cpu().numpy()
+    assert np.max(np.abs(rho[first] - exact[first])) <= 1e-10 * exact.max()          # those are the fp64 values
+    order = np.empty(n, dtype=np.int64)
+    order[rank] = np.arange(n)
+    assert np.array_equal(order, po.density_order(rho))
+    assert np.array_equal(o["center_idx"][:rep["n_centers"]].cpu().numpy(), _centres_of((d <= d_c).cpu().numpy(), rho))
