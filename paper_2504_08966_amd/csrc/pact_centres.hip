@@ -1052,7 +1052,10 @@ __global__ __launch_bounds__(1024) void centres_kernel(Batch bt, CentresArgs a) 
         item_end = (int)((long)total * (w + 1) / workers);
         b = 0;
     }
-    auto meet = [&](int* counter, int add) __attribute__((always_inline)) {       // what was there before
+    // Counts the workgroup in; what was there before.  Every wavefront waits for its own stores before the barrier: the one that
+    // counts releases what has reached the L2, and a workgroup barrier alone does not wait for that.
+    auto meet = [&](int* counter, int add) __attribute__((always_inline)) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
         if (threadIdx.x == 0) s_got = __hip_atomic_fetch_add(counter, add, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
         __syncthreads();
