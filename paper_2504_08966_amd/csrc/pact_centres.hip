@@ -166,9 +166,13 @@ __global__ __launch_bounds__(256) void settle_kernel(Batch bt, const char* __res
                                                      const uint32_t* __restrict__ near_list,
                                                      const int32_t* __restrict__ near_cnt,
                                                      const uint32_t* __restrict__ far_bits, int far_words,
+                                                     double* __restrict__ rho, const double* __restrict__ rho_lo,
                                                      uint64_t* adj, pact_report* rep) {
     const int b = blockIdx.y;
     const Seg sg = bt.s[b];
+    if (sg.d_n < EXACT_SUMS_D_N)                               // densities that came in two parts (add_density)
+        for (int p = blockIdx.x * 256 + threadIdx.x; p < sg.n; p += gridDim.x * 256)
+            rho[(size_t)b * bt.n_max + p] += rho_lo[(size_t)b * bt.n_max + p];
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
     const int gw = blockIdx.x * 4 + wave;
@@ -1542,7 +1546,7 @@ int launch_centres(const Batch& bt, const Ws& w, const void* keys, pact_dtype k_
     const bool wide = (size_t)dk * (k_dt == PACT_BF16 ? 2 : 4) > 2048;
 #define PACT_SETTLE(DT, CH)                                                                                           \
     PACT_LAUNCH("settle", (settle_kernel<DT, CH>), gset, dim3(256), st, bt, k, dk, idx, w.nn, w.near_list, w.near_cnt, \
-                w.stat, stat_words, w.adj, rep)
+                w.stat, stat_words, w.rho, w.rho_lo, w.adj, rep)
     if (k_dt == PACT_BF16) { if (wide) PACT_SETTLE(PACT_BF16, 8); else PACT_SETTLE(PACT_BF16, 2); }
     else { if (wide) PACT_SETTLE(PACT_F32, 8); else PACT_SETTLE(PACT_F32, 2); }
 #undef PACT_SETTLE

@@ -25,7 +25,7 @@ struct FrontArgs {
     const char* keys; int32_t dk;
     const char* q; int32_t qcols;            // q == nullptr: no query pass
     const char* hidden; int32_t h; int32_t h_bf16; int32_t stream;   // hidden == nullptr: no norms
-    double* nn; float* rinv; uint64_t* adj; double* rho; double* qg_part; double* hnorm;
+    double* nn; float* rinv; uint64_t* adj; double* rho; double* rho_lo; double* qg_part; double* hnorm;
     uint32_t* status; int32_t* ident; int32_t* near_cnt; int32_t* tie_cnt;
     pact_report* rep; int32_t* cluster_id; int32_t* cluster_counts;
     const int32_t* n_idx_dev; uint32_t* zeros;
@@ -187,6 +187,7 @@ __device__ __forceinline__ void key_job(const Batch& bt, const FrontArgs& a, int
         if (a.mode == INIT_REDUCE || a.mode == INIT_DBDPC_ALL || a.mode == INIT_DBDPC_SUBSET) {
             a.status[(size_t)b * bt.n_max + i] = ST_UNKNOWN;
             a.rho[(size_t)b * bt.n_max + i] = 0.0;
+            if (sg.d_n < EXACT_SUMS_D_N) a.rho_lo[(size_t)b * bt.n_max + i] = 0.0;
             a.ident[g] = i;
             a.cluster_id[g] = -1;
             if (a.cluster_counts) a.cluster_counts[g] = 0;
@@ -847,7 +848,7 @@ int launch_front(const Batch& bt, const Ws& w, const void* keys, pact_dtype k_dt
                  int32_t* cluster_counts, int mode, const int32_t* n_idx_dev, hipStream_t st) {
     FrontArgs a = {};
     a.keys = (const char*)keys; a.dk = dk;
-    a.nn = w.nn; a.rinv = w.rinv; a.adj = w.adj; a.rho = w.rho; a.qg_part = w.qg_part; a.hnorm = w.hnorm;
+    a.nn = w.nn; a.rinv = w.rinv; a.adj = w.adj; a.rho = w.rho; a.rho_lo = w.rho_lo; a.qg_part = w.qg_part; a.hnorm = w.hnorm;
     a.status = w.status; a.ident = w.ident; a.near_cnt = w.near_cnt; a.tie_cnt = w.tie_cnt;
     a.rep = rep; a.cluster_id = cluster_id; a.cluster_counts = cluster_counts; a.n_idx_dev = n_idx_dev;
     a.zeros = w.zeros; a.ksplit = w.ksplit;

@@ -57,7 +57,7 @@ struct GramArgs {
     const char* zeros;         // >= 16 zero bytes (source of the slices past the key width)
     uint64_t* adj;             // [B][n_max][W]
     float* cbest;              // candidate pass: [B][W][n_max] largest cosine per (group of 64 centres, pruned token)
-    double* rho;               // density pass: [B][n_max] densities (zeroed beforehand)
+    double* rho; double* rho_lo;   // density pass: [B][n_max] densities, and their low parts (d_n below EXACT_SUMS_D_N); zeroed beforehand
     uint32_t* near_list;       // [B][NEAR_CAP][2]
     int32_t* near_cnt;         // [B][2]: list slots taken, ordered pairs they stand for (8-byte aligned)
     uint32_t* stat;            // [B][stat_wgs * 8] per wavefront: bits of the most negative density exponent
@@ -205,6 +205,22 @@ __device__ __forceinline__ void mfma_i8(const u32x4_t& a, const u32x4_t& b, i32x
     c = __builtin_amdgcn_mfma_i32_32x32x32_i8(__builtin_bit_cast(i32x4_t, a), __builtin_bit_cast(i32x4_t, b), c, 0, 0, 0);
 }
 
+// A partial sum of a density, added by whichever wavefront gets there: the total must not depend on the order.
+// Its terms are fp32 values down to exp(-2 / d_n).  From d_n = 0.21 on their last bit is worth 2^-37 or more, and 2^15 of them
+// fit the 53 bits of an fp64: every addition is exact.  Below that (`split`) the sum v goes in two parts, hi = v rounded to a multiple of
+// 2^-37 and lo = v - hi, rounded to a multiple of 2^-80: hi parts up to 2^15 and the at most 2^11 lo parts of a density (|lo| <= 2^-38) add up
+// exactly again, what is dropped is below 2^-70, and the next kernel leaves hi + lo, rounded once.
+// (131 072 such additions, one image's, take 0.1 us more than as many plain stores of partial
+// sums, which another kernel would have to add up.)
+__device__ __forceinline__ void add_density(double* rho, double* rho_lo, double v, bool split) {
+    if (split) {
+        const double hi = rint(v * 0x1p37) * 0x1p-37;
+        unsafeAtomicAdd(rho_lo, rint((v - hi) * 0x1p80) * 0x1p-80);
+        v = hi;
+    }
+    unsafeAtomicAdd(rho, v);
+}
+
 // Density pass with t x t square tiles on g workgroups: do mirrored tiles (upper triangle only,
 // longer epilogue) save at least one turn in eight of a workgroup's tile loop?
 __host__ __device__ __forceinline__ bool mirrored_tiles_pay(int t, int g) {
@@ -286,6 +302,8 @@ __global__ __launch_bounds__(SH::THREADS, SH::WAVES_PER_SIMD) void gram_kernel(B
     const float* __restrict__ rinv = ga.rinv + sg.base;
     uint64_t* adj = ga.adj + (size_t)b * bt.n_max * bt.W;
     double* rho_b = (MODE == MODE_DENSITY) ? ga.rho + (size_t)b * bt.n_max : nullptr;
+    double* rho_lo_b = (MODE == MODE_DENSITY) ? ga.rho_lo + (size_t)b * bt.n_max : nullptr;
+    const bool split = sg.d_n < EXACT_SUMS_D_N;               // (see add_density)
 
     // density constants: arg = cos * a - a = -(d / d_n) * log2(e); each of the two reciprocal norms
     // carries sqrt(a), so that the factor of a pair is the same product whichever token is the
@@ -786,7 +804,7 @@ __global__ __launch_bounds__(SH::THREADS, SH::WAVES_PER_SIMD) void gram_kernel(B
                     d[0] += dpp_f64<DPP_XOR1>(d[0]);
                     // this lane's row: bits 4, 3, 2 of l32 chose the upper half in turn
                     const int gRow = rowI + 2 * r8 + 8 * (l32 >> 4) + 4 * hh + ((l32 >> 2) & 3);
-                    if ((l32 & 3) == 0 && gRow < nA) unsafeAtomicAdd(&rho_b[gRow], d[0]);
+                    if ((l32 & 3) == 0 && gRow < nA) add_density(rho_b + gRow, rho_lo_b + gRow, d[0], split);
                     __builtin_amdgcn_sched_barrier(0);     // registers are tight
                 });
             } else {
@@ -890,17 +908,12 @@ __global__ __launch_bounds__(SH::THREADS, SH::WAVES_PER_SIMD) void gram_kernel(B
         }
 
         if (MODE == MODE_DENSITY) {
-            // Column sums over this wave's rows: combine the two half-waves, then add them to the
-            // densities.  The fp64 additions of these fp32 terms are exact for d_n >= 0.21 (24 bits of a
-            // term down to exp(-2 / d_n), 2^15 of them), so their order does not matter; below that the
-            // last bit of a density may depend on it, far inside the band that is re-evaluated.
-            // (131 072 such additions, one image's, take 0.1 us more than as many plain stores of partial
-            // sums, which another kernel would have to add up.)
+            // Column sums over this wave's rows: combine the two half-waves, then add them to the densities.
 #pragma unroll
             for (int j = 0; j < NJ; ++j) {
                 const double part = rho[j][0] + rho[j][1];
                 const double tot = part + __shfl_xor(part, 32, 64);
-                if (hh == (j & 1) && rowW < nA && colP[j] < nB) unsafeAtomicAdd(&rho_b[colP[j]], tot);
+                if (hh == (j & 1) && rowW < nA && colP[j] < nB) add_density(rho_b + colP[j], rho_lo_b + colP[j], tot, split);
             }
         }
         if (MODE == MODE_DENSITY && nearN > 0) flush_near();
@@ -1092,7 +1105,7 @@ int launch_gram_density(const Batch& bt, const Ws& w, const void* keys, pact_dty
                         const int32_t* idx, pact_report* rep, bool want_stat, int* stat_words, hipStream_t st) {
     GramArgs ga = {};
     if (const int rc = gram_args(ga, bt, w, keys, k_dt, dk, idx, idx, rep)) return rc;
-    ga.rho = w.rho; ga.near_list = w.near_list; ga.near_cnt = w.near_cnt; ga.stat = want_stat ? w.stat : nullptr;
+    ga.rho = w.rho; ga.rho_lo = w.rho_lo; ga.near_list = w.near_list; ga.near_cnt = w.near_cnt; ga.stat = want_stat ? w.stat : nullptr;
     const char* name = "gram_density";
     // The count of kept tokens is known on the device only; what the percentile will leave
     // (n - floor(lambda n), more on ties) tells whether mirrored tiles are likely to pay for

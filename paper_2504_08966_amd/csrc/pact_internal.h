@@ -38,6 +38,7 @@ constexpr int PRED_CAP = 64;          // 16-bit slots per kept token: slot 0 = c
 constexpr int GRAM_MAX_WORKGROUPS = 256; // workgroups of 8 wavefronts per sample in a Gram pass (one per CU)
 constexpr int NEAR_CAP = 1 << 16;     // near-threshold pairs kept for fp64 re-evaluation, per sample
 constexpr uint32_t NEAR_MIRROR = 0x80000000u;   // flag in a listed pair's row: the pair (col, row) is meant as well
+constexpr float EXACT_SUMS_D_N = 0.21f;      // from this d_n on the density sums are exact in any order (see add_density)
 constexpr uint32_t ST_UNKNOWN = 0, ST_CENTER = 1, ST_NOT = 2;
 constexpr int RHO_RECHECK_MAX = PACT_MAX_RHO_RECHECK;   // tokens per sample whose density is evaluated again in fp64
 constexpr int RHO_RECHECK_CHUNK = 64;                   // kept tokens per partial sum of such an evaluation (16 or 32 where few are listed)
@@ -55,7 +56,8 @@ struct WsLayout {
     size_t adj;                                        // [B][n_max][W] u64: rows < q adjacency; from row q on: candidate words [Wc][n_pruned]
     size_t cbest;                                      // [B][W][n_max] f32: largest cosine per (group of 64 centres, pruned token)
     size_t rho, rank, status, cnum, cmask;             // per sample, pitch n_max (cmask: W)
-    size_t preds, heads;                               // [B][n_max][PRED_CAP] u16, [B][n_max] 4 x u16 (count + first 3)
+    size_t preds, heads;                               // [B][n_max][PRED_CAP] u16, [B][n_max] 4 x u16 (count + first 3; until those are
+                                                       // built, the low parts of the densities: see add_density)
     size_t ksplit;                                     // [total][dk/64 rounded up][3][64] int8: fp32 clustering keys as three int8 planes
     size_t near_list, near_cnt, stat;                  // refine list, counter; [B][workgroups * 8] most negative density exponent seen
     size_t tie_list, tie_cnt;                          // [B][RHO_RECHECK_MAX] kept positions whose density is re-evaluated; [B][4]: count, ticket
@@ -123,7 +125,7 @@ struct Ws {
     double* qg_part; double* logits; double* hnorm; double* sm_part;
     double* nn; float* rinv; int32_t* ident;
     uint64_t* adj; float* cbest; double* rho; int32_t* rank; uint32_t* status;
-    int32_t* cnum; uint64_t* cmask; uint16_t* preds; uint2* heads; uint32_t* near_list; int32_t* near_cnt; uint32_t* stat;
+    int32_t* cnum; uint64_t* cmask; uint16_t* preds; uint2* heads; double* rho_lo; uint32_t* near_list; int32_t* near_cnt; uint32_t* stat;
     int32_t* tie_list; int32_t* tie_cnt; double* rho_fix;
     int32_t* offsets; int32_t* members; int32_t* big; int32_t* slots; uint32_t* zeros; char* ksplit;
 };
@@ -138,7 +140,7 @@ inline Ws resolve(void* base, const WsLayout& L) {
     w.adj = (uint64_t*)(p + L.adj); w.cbest = (float*)(p + L.cbest);
     w.rho = (double*)(p + L.rho); w.rank = (int32_t*)(p + L.rank);
     w.status = (uint32_t*)(p + L.status); w.cnum = (int32_t*)(p + L.cnum);
-    w.preds = (uint16_t*)(p + L.preds); w.heads = (uint2*)(p + L.heads);
+    w.preds = (uint16_t*)(p + L.preds); w.heads = (uint2*)(p + L.heads); w.rho_lo = (double*)(p + L.heads);
     w.cmask = (uint64_t*)(p + L.cmask); w.near_list = (uint32_t*)(p + L.near_list);
     w.near_cnt = (int32_t*)(p + L.near_cnt); w.stat = (uint32_t*)(p + L.stat);
     w.tie_list = (int32_t*)(p + L.tie_list); w.tie_cnt = (int32_t*)(p + L.tie_cnt);

@@ -91,3 +91,19 @@ def test_tokens_that_move_past_the_band_leave_one_order(n, d_n):
     order[rank] = np.arange(n)
     assert np.array_equal(order, po.density_order(rho))
     assert np.array_equal(o["center_idx"][:rep["n_centers"]].cpu().numpy(), _centres_of((d <= d_c).cpu().numpy(), rho))
+
+
+@pytest.mark.parametrize("n,dk,dtype,d_n", [(1500, 512, torch.bfloat16, 0.05), (4500, 128, torch.bfloat16, 0.02), (2700, 64, torch.float32, 0.1),
+                                            (2048, 1024, torch.bfloat16, 0.2), (2048, 1024, torch.bfloat16, 0.21)])
+def test_densities_do_not_depend_on_the_order_of_the_additions(n, dk, dtype, d_n):
+    # Below d_n = 0.21 the terms span more binades than an fp64 sum holds: wavefronts add their parts in whatever order they get there.
+    r = np.random.default_rng(n)
+    x = r.standard_normal((12, dk))[r.integers(0, 12, n)] * 3.0 + r.standard_normal((n, dk))
+    x = torch.from_numpy(x.astype(np.float32)).cuda().to(dtype)
+    ws = P.alloc_workspace(n, 1, dk, 1, 1, key_dtype=dtype)
+    runs = [P.dbdpc_cluster(x, 0.0, d_n, ws=ws, want_rho=True)["rho"] for _ in range(12)]
+    for k in runs[1:]:
+        assert torch.equal(k, runs[0]), f"{int((k != runs[0]).sum())} densities differ between two runs"
+    # and they are the sums: a term's error is that of its exponent, (dk + 16) 2^-24 / d_n at the very most and mostly far less
+    exact = torch.exp(-_distances(x) / float(np.float32(d_n))).sum(1)
+    assert float(((runs[0] - exact).abs() / exact).max()) <= (dk + 16) * 2.0 ** -24 / d_n
