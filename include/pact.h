@@ -48,7 +48,7 @@
  *    closer to the threshold than its worst-case rounding error, and always for the final
  *    nearest-centre choice, so those decisions are the fp64 ones.
  *  - Densities (Eq. 6) are fp64 sums of fp32 terms exp2-evaluated from matrix-core cosines
- *    (bf16 keys as they are; fp32 keys as 24-bit integers in three 8-bit planes).  The sums do not
+ *    (bf16 keys as they are; fp32 keys as 32-bit integers in four 8-bit planes).  The sums do not
  *    depend on the order in which they are formed: the same call gives the same densities, bit for bit.
  *    The density order (Alg. 2) only matters between tokens within d_c of each other; where
  *    two such tokens have densities closer than a band of about fifty standard errors of

@@ -136,11 +136,13 @@ __device__ __forceinline__ void key_job(const Batch& bt, const FrontArgs& a, int
         for (int k = 0; k < EPL; ++k) acc = fma(x[k], x[k], acc);
     }
     const double v = group_sum_f64(acc, KL);
-    double scale = 1.0;                                    // of the rows the Gram passes read
+    float rinv = v > 0.0 ? (float)(1.0 / sqrt(v)) : 0.0f;
     if constexpr (KDT == PACT_F32) {
-        // The row as 24-bit integers X = rint(x S) (S: its largest element becomes 8355711, or a power of
+        // The row as 32-bit integers X = rint(x S) (S: its largest element becomes 2139062143 = 0x7F7F7F7F, or a power of
         // four less for rows of more than 2^17 elements, whose order-0 sums would not fit an int32), split
-        // into three signed bytes; 64 elements are 64 bytes of each plane in turn, padded with zeros.
+        // into four signed bytes: the upper three in turn, 64 elements of each, then all of the lowest; padded with zeros.
+        // The Gram passes' products are in units of 2^24, so that the reciprocal norm is 4096 / |X|.  It is rounded up to fp32 and S is
+        // taken from what that is the reciprocal of: it is then exact.
         float top = 0.0f;
         for (int e = kl * 4; e < a.dk; e += 4 * KL) {
             float x[8];
@@ -150,20 +152,25 @@ __device__ __forceinline__ void key_job(const Batch& bt, const FrontArgs& a, int
         top = group_max_f32<16>(top);
 #pragma unroll
         for (int sft = 16; sft < KL; sft <<= 1) top = fmaxf(top, __shfl_xor(top, sft, 64));
-        double most = 8355711.0;
+        double most = 2139062143.0;
         for (int64_t d = a.dk; d > 131072; d >>= 2) most *= 0.5;
-        const double S = top > 0.0f ? most / (double)top : 0.0;
-        scale = S;
-        char* sp = a.ksplit + g * (size_t)((a.dk + 63) / 64 * 192);
-        for (int e = kl * 4; e < (a.dk + 63) / 64 * 64; e += 4 * KL) {
+        double S = top > 0.0f ? most / (double)top : 0.0;
+        if (v > 0.0) {
+            const double len = sqrt(v);
+            rinv = __double2float_ru(4096.0 / (S * len));
+            if (v < INFINITY) S = 4096.0 / ((double)rinv * len);
+        }
+        const int groups = (a.dk + 63) / 64;
+        char* sp = a.ksplit + g * (size_t)groups * 256;
+        for (int e = kl * 4; e < groups * 64; e += 4 * KL) {
             float x[8];
             Elem<KDT>::widenf(chunk(e), x);                            // (zeros past the row's end)
-            uint32_t part[3] = {0u, 0u, 0u};
+            uint32_t part[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 int X = (int)rint((double)x[k] * S);
 #pragma unroll
-                for (int pl = 2; pl >= 0; --pl) {
+                for (int pl = 3; pl >= 0; --pl) {
                     const int byte = (int)(int8_t)(X & 255);
                     part[pl] |= (uint32_t)(byte & 255) << (8 * k);
                     X = (X - byte) >> 8;
@@ -171,6 +178,7 @@ __device__ __forceinline__ void key_job(const Batch& bt, const FrontArgs& a, int
             }
 #pragma unroll
             for (int pl = 0; pl < 3; ++pl) *(uint32_t*)(sp + (size_t)(e >> 6) * 192 + pl * 64 + (e & 63)) = part[pl];
+            *(uint32_t*)(sp + (size_t)groups * 192 + e) = part[3];
         }
     }
     // The bitmap is used over (kept tokens) x (kept tokens).  In a full reduction that is
@@ -182,8 +190,7 @@ __device__ __forceinline__ void key_job(const Batch& bt, const FrontArgs& a, int
     for (int k = kl; k < Wn; k += KL) arow[k] = 0ull;
     if (kl == 0) {
         a.nn[g] = v;
-        // (fp32 keys: products of the integers in units of 65536)
-        a.rinv[g] = v > 0.0 ? (float)((KDT == PACT_F32 ? 256.0 / scale : 1.0) / sqrt(v)) : 0.0f;
+        a.rinv[g] = rinv;
         if (a.mode == INIT_REDUCE || a.mode == INIT_DBDPC_ALL || a.mode == INIT_DBDPC_SUBSET) {
             a.status[(size_t)b * bt.n_max + i] = ST_UNKNOWN;
             a.rho[(size_t)b * bt.n_max + i] = 0.0;

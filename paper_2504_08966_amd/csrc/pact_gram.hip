@@ -17,7 +17,7 @@
 //  * the key rows stream in slices straight from global memory into a ring of LDS stages
 //    (global_load_lds_dwordx4: no staging registers); waits on the ring are explicit (s_waitcnt
 //    vmcnt + s_barrier).  bf16: 128 bytes of each row (a whole cache line, fetched by eight lanes);
-//    fp32: 64 elements of the three int8 planes of a row, 192 contiguous bytes;
+//    fp32: 64 elements of the upper three int8 planes of a row, 192 contiguous bytes;
 //  * both operands are rows of the same key matrix, so a lane takes 16 contiguous bytes of
 //    "its" row per MFMA; the 16-byte chunks of a row slice are XOR-swizzled by the row
 //    number so that 16 consecutive rows read conflict-free; the fragments of the next k-group
@@ -28,17 +28,22 @@
 //    tiles on and above the diagonal are computed, and a tile above it also leaves the row sums,
 //    the transposed bits and the flagged near-d_c pairs of its mirror image (template SYM).
 //
-// fp32 keys.  The first kernel of a call writes every row as 24-bit integers X = rint(x S),
-// S = 8355711 / max|x| (a row's largest element uses all 24 bits), split into three signed bytes,
-// X = 65536 s0 + 256 s1 + s2.  A dot product is then sums of byte products, exact in int32: order
-// 0 (s0 t0), order 1 (s0 t1 + s1 t0), order 2 (s0 t2 + s1 t1 + s2 t0) and, where it can matter, order 3
-// (s1 t2 + s2 t1), combined once per pair in fp32; s2 t2 is always left out.  Six byte products at twice
-// the bf16 rate cost three bf16 passes (eight: four), against six for a split into three bf16 parts, and
-// nothing is rounded on the way.  What is left out of a cosine: the rounding of the elements, at most
-// sqrt(dk) 2^-23, and the orders from 3 (or 4) on: with |X| >= 2^24.5 (dk / 512)^(1/4) in both rows the
-// order-3 terms have a standard deviation of at most 8e-8, less than the rounding of an fp32
-// accumulation of that width; samples that hold a row below that (one element far above all
-// others) get order 3 as well, whose successor is 256 times smaller.
+// fp32 keys.  The first kernel of a call writes every row as 32-bit integers X = rint(x S),
+// S = 2139062143 / max|x| or slightly less, split into four signed bytes,
+// X = 2^24 s0 + 2^16 s1 + 2^8 s2 + s3.  A dot product is then sums of byte products, exact in int32: order
+// 0 (s0 t0), order 1 (s0 t1 + s1 t0), order 2 (s0 t2 + s1 t1 + s2 t0), order 3.
+//  * Density pass: orders 0 to 2 and of order 3 the part s1 t2 + s2 t1, eight byte products at twice the bf16 rate: four bf16
+//    passes' worth against six for a split into three bf16 parts, and nothing is rounded on the way.  The other part of order 3,
+//    s0 t3 + s3 t0, is what the lowest byte is worth: its standard deviation in a cosine is 105 / |X| for two rows of that
+//    length, 1.4e-8 at |X| = 3.5 max|X|.  Tiles with a row or column below that (one element larger than that part of
+//    the row's length) get it too, in a sweep of its own.  Left out always: order 4 on (standard deviation 3e-9 where one element is
+//    all there is of 512-wide rows, 1e-10 ordinarily).
+//    Errors of single cosines against 64 bits, rms in 1e-8 (2.5 of it is the rounding of the exponent that follows), tokens of
+//    512-wide images with cosines near 0 / neighbours near 0.7: 2.8 / 7.4; with the six products of orders 0 to 2 alone 3.6 / 8.6 and
+//    8.8 where the largest element is 8 times the rms (now 2.7); as three bf16 parts 3.0 / 12.7.  16384 tokens, 512 wide: 519 us
+//    against 426 us with six products, all pairs of tiles with the lowest byte 750 us.
+//  * Candidate pass: orders 0 to 2.  Its cosines decide nothing by themselves (what is within the margin of a threshold or of
+//    the largest is evaluated in fp64), and the margin holds the rest at its worst.
 #include <type_traits>
 
 #include "pact_internal.h"
@@ -64,7 +69,7 @@ struct GramArgs {
                                // it saw (largest distance), or NULL when the statistic is not wanted
     int32_t stat_wgs;          // workgroup slots per sample in `stat`, one word per wavefront
     float margin;              // worst-case fp32 error of a cosine
-    float rinv_low;            // fp32 keys: a reciprocal norm above this asks for the order-3 products
+    float rinv_low;            // fp32 keys: a reciprocal norm above this asks for the lowest byte as well
     // Batches (mapped != 0): a one-dimensional grid of 256 (512) workgroups, shared out
     // among the samples by size; workgroup i serves sample wg_map[i] >> 8 (9) as its workgroup number
     // wg_map[i] & 255 (511) of wg_count[sample] (0xFFFF: a spare workgroup).
@@ -75,13 +80,13 @@ struct GramArgs {
 
 constexpr int LDS_BUDGET = 160 * 1024 - 4096;
 
-// DT: PACT_BF16, or PACT_I8X3 for fp32 keys as three int8 planes.  STAGES: ring stages at most.  TURNS: two groups
+// DT: PACT_BF16, or PACT_I8X4 for fp32 keys as int8 planes.  STAGES: ring stages at most.  TURNS: two groups
 // of wavefronts take turns at the matrix cores.
 template <int DT, int MI_, int NJ_, int WR_, int WC_, int STAGES, bool TURNS> struct Shape {
     static constexpr int MI = MI_, NJ = NJ_, WR = WR_, WC = WC_;
     static constexpr int WAVES = WR * WC, THREADS = 64 * WAVES;
     static constexpr int TILE_R = 32 * MI * WR, TILE_C = 32 * NJ * WC;
-    static constexpr bool I8 = DT == PACT_I8X3;
+    static constexpr bool I8 = DT == PACT_I8X4;
     static constexpr int SLICE_BYTES = I8 ? 192 : 128;                   // bytes of each row per stage
     static constexpr int STAGE_BYTES = (TILE_R + TILE_C) * SLICE_BYTES;  // A rows then B rows
     static constexpr int NSTAGE = (LDS_BUDGET / STAGE_BYTES) < STAGES ? (LDS_BUDGET / STAGE_BYTES) : STAGES;
@@ -96,20 +101,21 @@ template <int DT, int MI_, int NJ_, int WR_, int WC_, int STAGES, bool TURNS> st
     static_assert(!TURNS || WAVES == 8, "one wavefront of either group per SIMD");
     // k-groups per slice; k-groups per turn
     static constexpr int KG = I8 ? 2 : 4, HG = I8 || MI * NJ <= 4 ? KG : 2;
-    static constexpr int RINV_BYTES = TILE_R * sizeof(float);
+    static constexpr int RINV_BYTES = TILE_R * sizeof(float) + (I8 ? 128 : 0);     // (fp32 keys: and a flag)
     static_assert(NSTAGE >= 2, "the ring needs a slot to fill while another is multiplied");
     static_assert(NB * 1024 * WAVES == STAGE_BYTES, "whole blocks per wavefront");
     static_assert(!I8 || NB % 3 == 0, "16 rows of 192 bytes are three blocks");
     static_assert((WAVES / 2) * NB * 1024 == TILE_R * SLICE_BYTES || !I8, "half of the wavefronts fetch the row operand");
     // ring stages a launch needs: no more than there are slices (two at least: the epilogue uses one)
     static size_t lds_bytes(int slices) {
-        if (I8) slices *= 2;                                             // (with the order-3 products they come twice)
+        if (I8) slices *= 2;                                             // (with the lowest byte they come twice)
         const int st = slices < 2 ? 2 : slices < NSTAGE ? slices : NSTAGE;
         return RINV_BYTES + (size_t)st * STAGE_BYTES;
     }
 };
 
 typedef __attribute__((address_space(3))) char lds_char;
+typedef __attribute__((address_space(3))) volatile int lds_vi32;
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) u32x4_t lds_u32x4;
 typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
@@ -235,6 +241,8 @@ __global__ __launch_bounds__(SH::THREADS, SH::WAVES_PER_SIMD) void gram_kernel(B
     constexpr int SLICE_BYTES = SH::SLICE_BYTES;
     constexpr int AHEAD = SH::AHEAD, NB = SH::NB, WROWS = 32 * MI, WCOLS = 32 * NJ;
     constexpr bool I8 = SH::I8;
+    constexpr bool LOWEST = I8 && MODE == MODE_DENSITY;      // fp32 keys: orders 0 to 3 and, where it matters, the lowest byte; otherwise 0 to 2
+    constexpr int ORDERS = LOWEST ? 4 : 3;
     static_assert(MODE == MODE_CAND || NJ == 2 || NJ == 3, "a wavefront's columns are one bitmap word, or three halves");
     static_assert(MODE == MODE_DENSITY || WROWS % 64 == 0, "a wavefront's rows are whole groups of 64 centres");
     static_assert(!SYM || TILE_R == TILE_C, "mirrored tiles are square");
@@ -256,21 +264,6 @@ __global__ __launch_bounds__(SH::THREADS, SH::WAVES_PER_SIMD) void gram_kernel(B
         for (int k = threadIdx.x; k < (ga.stat_wgs - G) * WAVES; k += SH::THREADS)
             ga.stat[((size_t)b * ga.stat_wgs + G) * WAVES + k] = 0u;
     const Seg sg = bt.s[b];
-    // fp32 keys: does a row of this sample need the order-3 products (see the head of this file)?  (Requested
-    // before the counts are known.)
-    bool order3 = false;
-    if constexpr (I8) {
-        const float* __restrict__ rinv_b = ga.rinv + sg.base;
-        bool low = false;
-        for (int i = threadIdx.x; i < sg.n; i += 8 * SH::THREADS) {
-            float v[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) v[u] = rinv_b[min(i + u * SH::THREADS, sg.n - 1)];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) low |= v[u] > ga.rinv_low;
-        }
-        order3 = __syncthreads_or(low);
-    }
     const int q_kept = clamp_count(ga.rep[b].n_kept, sg.n);
     // density pass: kept x kept; candidate pass: rows are the centres, columns the pruned tokens
     // (what is wanted there is per pruned token, and a lane holds 16 rows of one column)
@@ -291,11 +284,20 @@ __global__ __launch_bounds__(SH::THREADS, SH::WAVES_PER_SIMD) void gram_kernel(B
 
     float* sRinv = (float*)s_ring;                                // [TILE_R]
     lds_char* ring = (lds_char*)s_ring + SH::RINV_BYTES;
+    // fp32 keys: number of the last of this workgroup's tiles that had a row or column which needs the lowest byte
+    lds_vi32* sLow = (lds_vi32*)((lds_char*)s_ring + TILE_R * sizeof(float));
+    int tileNo = 0;
+    if constexpr (LOWEST) {
+        if (tid == 0) *sLow = 0;
+        __syncthreads();
+    }
     const uint32_t ring_base = (uint32_t)(uintptr_t)ring;
 
-    // A row is dk bf16 values, or (fp32 keys) 192 bytes per 64 elements: 64 bytes of each of its three planes.
-    const int tok_bytes = I8 ? ((ga.dk + 63) >> 6) * 192 : ga.dk * Elem<PACT_BF16>::BYTES;
-    const int nSlices = (tok_bytes + SLICE_BYTES - 1) / SLICE_BYTES;
+    // A row is dk bf16 values, or (fp32 keys) int8 planes: 192 bytes per 64 elements, 64 of each of the upper three, then
+    // the lowest plane, 64 bytes per 64 elements.
+    const int groups = (ga.dk + 63) >> 6;
+    const int tok_bytes = I8 ? groups * 256 : ga.dk * Elem<PACT_BF16>::BYTES;
+    const int nSlices = I8 ? groups : (tok_bytes + SLICE_BYTES - 1) / SLICE_BYTES;
     const char* __restrict__ keys = ga.keys + (size_t)sg.base * tok_bytes;
     const int32_t* __restrict__ idxR = ga.idx_rows + sg.base;
     const int32_t* __restrict__ idxC = ga.idx_cols + sg.base;
@@ -352,11 +354,11 @@ __global__ __launch_bounds__(SH::THREADS, SH::WAVES_PER_SIMD) void gram_kernel(B
 
     float far = 0.0f;              // most negative density exponent seen = largest distance (density pass)
     for (int tl = t_first; tl < l_hi; tl += t_step) {
-        // Per-lane constants of a tile.  (The build with mirrored tiles has no register to spare
+        // Per-lane constants of a tile.  (The builds with mirrored tiles and those for fp32 keys have no register to spare
         // in its epilogue: there they are derived anew for every tile from a laundered thread
         // number, so that they do not occupy registers from one tile to the next.)
         int tid_t = tid;
-        if constexpr (SYM) asm volatile("" : "+v"(tid_t));
+        if constexpr (SYM || I8) asm volatile("" : "+v"(tid_t));
         const int lane = tid_t & 63;
         const int l32_ = lane & 31, hh_ = lane >> 5;
         // stage row and logical chunk of this lane in block k
@@ -427,17 +429,35 @@ __global__ __launch_bounds__(SH::THREADS, SH::WAVES_PER_SIMD) void gram_kernel(B
             const int tok = (r >= TILE_R) ? idxC[min(colBase + r - TILE_R, nB - 1)] : idxR[min(rowBase + r, nA - 1)];
             ro[k] = (uint32_t)tok * (uint32_t)tok_bytes + (uint32_t)(dma_chunk(k) * 16);
         }
-        if (tid_t < TILE_R) sRinv[tid_t] = rinv[idxR[min(rowBase + tid_t, nA - 1)]] * sa_;
+        float ri_pre = 0.0f;
+        if (tid_t < TILE_R) {
+            ri_pre = rinv[idxR[min(rowBase + tid_t, nA - 1)]];
+            sRinv[tid_t] = ri_pre * sa_;
+        }
         float rj_pre[NJ];                                   // 1/|u_j| of this lane's columns (used in the epilogue)
 #pragma unroll
         for (int j = 0; j < NJ; ++j) rj_pre[j] = rinv[idxC[min(colBase + wc * WCOLS + j * 32 + l32_, nB - 1)]];
+        if constexpr (LOWEST) {
+            // (ahead of the first barrier of the tile, so that it is there for all wavefronts behind it)
+            ++tileNo;
+            bool low = ri_pre > ga.rinv_low;
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) low |= rj_pre[j] > ga.rinv_low;
+            if (__any(low)) *sLow = tileNo;
+        }
 
-        // The order-3 products take a sweep over the key width of their own, ahead of the others (in the
-        // registers of order 2, which they are a 256th of): the slices then come twice.
-        const int nSweep3 = I8 && order3 ? nSlices : 0, nSteps = nSweep3 + nSlices;
+        // The lowest byte's products take a sweep over the key width of their own, behind the others: steps from nSlices on, in which a
+        // stage holds the uppermost plane where that belongs and the lowest in the place of the second.
+        int nSteps = nSlices;
         auto issue = [&](int step) __attribute__((always_inline)) {   // step's slice -> ring slot step % NSTAGE
-            const int s = I8 && step >= nSweep3 ? step - nSweep3 : step;
+            const int s = LOWEST && step >= nSlices ? step - nSlices : step;
             const uint32_t lds = dma_lds0 + (uint32_t)((step % NSTAGE) * STAGE_BYTES), off = (uint32_t)(s * SLICE_BYTES);
+            if (LOWEST && step >= nSlices) {
+                const uint32_t off3 = (uint32_t)(groups * 192 - 64 + s * 64);
+#pragma unroll
+                for (int k = 0; k < NB; ++k) dma16_off(keys, ro[k] + ((dma_chunk(k) >> 2) == 1 ? off3 : off), lds + k * 1024);
+                return;
+            }
             if (I8 || (s + 1) * SLICE_BYTES <= tok_bytes) {
                 // a whole slice: scalar base + (row offset + chunk) + slice offset, one add per block.
                 // (These instructions sit between the barrier and the first MFMA of every
@@ -454,10 +474,10 @@ __global__ __launch_bounds__(SH::THREADS, SH::WAVES_PER_SIMD) void gram_kernel(B
             }
         };
         f32x16_t acc[MI][NJ];
-        i32x16_t ord[I8 ? 3 : 1][MI][NJ];                   // fp32 keys: sums of the byte products, by order
+        i32x16_t ord[I8 ? ORDERS : 1][MI][NJ];                   // fp32 keys: sums of the byte products, by order
         if constexpr (I8) {
 #pragma unroll
-            for (int o = 0; o < 3; ++o)
+            for (int o = 0; o < ORDERS; ++o)
 #pragma unroll
                 for (int i = 0; i < MI; ++i)
 #pragma unroll
@@ -496,36 +516,6 @@ __global__ __launch_bounds__(SH::THREADS, SH::WAVES_PER_SIMD) void gram_kernel(B
                         ord[o - 1][i][j][r] += c;
                     }
         };
-        if constexpr (I8) {
-            auto frag = [&](const lds_char* st, uint32_t row0, int blk, int pl, int ks) __attribute__((always_inline)) {
-                return *(const lds_u32x4*)(st + row0 + blk * 32 * SLICE_BYTES + pl * 64 + (uint32_t)(((2 * ks + hh_) ^ swz) << 4));
-            };
-            for (int s = 0; s < nSweep3; ++s) {
-                const lds_char* st = arrive(s);
-                if (s + AHEAD < nSteps) issue(s + AHEAD);
-#pragma unroll
-                for (int ks = 0; ks < 2; ++ks)
-#pragma unroll
-                    for (int pa = 1; pa < 3; ++pa)
-#pragma unroll
-                        for (int i = 0; i < MI; ++i)
-#pragma unroll
-                            for (int j = 0; j < NJ; ++j)
-                                mfma_i8(frag(st, fragA0, i, pa, ks), frag(st, fragB0, j, 3 - pa, ks), ord[2][i][j]);
-                if ((s & 511) == 511) carry(2);          // (rows of more than 32768 elements, see below; into order 1's registers)
-            }
-            if (nSweep3 > 0) {
-#pragma unroll
-                for (int i = 0; i < MI; ++i)
-#pragma unroll
-                    for (int j = 0; j < NJ; ++j)
-#pragma unroll
-                        for (int r = 0; r < 16; ++r) {
-                            ord[2][i][j][r] = ((ord[2][i][j][r] + 128) >> 8) + ord[1][i][j][r];
-                            ord[1][i][j][r] = 0;
-                        }
-            }
-        }
         // Multiply.  A SIMD holds two of the eight wavefronts, one of either group (wavefronts w and w + 4); the
         // groups take turns, one multiplies while the other fetches its next fragments from the LDS, with a
         // barrier between the turns, so that the matrix cores wait for no LDS read (all wavefronts reading
@@ -546,13 +536,23 @@ __global__ __launch_bounds__(SH::THREADS, SH::WAVES_PER_SIMD) void gram_kernel(B
                 if (s + AHEAD - 1 < nSteps) wait_vmcnt<NB * (AHEAD - 1)>();
                 else wait_vmcnt<0>();
             };
-            wait_slice(nSweep3);
+            wait_slice(0);
+            if constexpr (LOWEST) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // (the flag's store)
             turn();
+            if constexpr (LOWEST) {
+                asm volatile("" ::: "memory");
+                if (__builtin_amdgcn_readfirstlane(*sLow) == tileNo) {
+                    nSteps = 2 * nSlices;
+#pragma unroll
+                    for (int s = 1; s < AHEAD; ++s)                      // (fewer slices than are kept in flight)
+                        if (s >= nSlices && s < nSteps) issue(s);
+                }
+            }
             if (second) turn();
-            for (int s = nSweep3; s < nSteps; ++s) {
+            for (int s = 0; s < nSlices; ++s) {
                 const lds_char* st = ring + (s % NSTAGE) * STAGE_BYTES;
                 if constexpr (I8) {
-                    if (((s - nSweep3) & 511) == 511) { carry(2); carry(1); }     // rows of more than 32768 elements: before int32 can overflow
+                    if ((s & 511) == 511) { if constexpr (LOWEST) carry(3); carry(2); carry(1); }     // rows of more than 32768 elements: before int32 can overflow
                 }
 #pragma unroll
                 for (int g0 = 0; g0 < KG; g0 += HG) {
@@ -578,9 +578,9 @@ __global__ __launch_bounds__(SH::THREADS, SH::WAVES_PER_SIMD) void gram_kernel(B
                     for (int g = 0; g < HG; ++g) {
                         if constexpr (I8) {
 #pragma unroll
-                            for (int o = 0; o < 3; ++o)
+                            for (int o = 0; o < ORDERS; ++o)
 #pragma unroll
-                                for (int pa = 0; pa <= o; ++pa)
+                                for (int pa = o < 3 ? 0 : 1; pa <= o && pa < 3; ++pa)
 #pragma unroll
                                     for (int i = 0; i < MI; ++i)
 #pragma unroll
@@ -598,6 +598,33 @@ __global__ __launch_bounds__(SH::THREADS, SH::WAVES_PER_SIMD) void gram_kernel(B
                 }
             }
             if (!second) turn();
+            if constexpr (LOWEST) {
+                if (nSteps > nSlices) carry(3);
+#pragma unroll 1
+                for (int s = nSlices; s < nSteps; ++s) {
+                    const lds_char* st = arrive(s);
+                    if (s + AHEAD < nSteps) issue(s + AHEAD);
+#pragma unroll
+                    for (int ks = 0; ks < 2; ++ks) {
+                        const uint32_t co = (uint32_t)(((2 * ks + hh_) ^ swz) << 4);
+                        u32x4_t fa[MI][2], fb[NJ][2];
+#pragma unroll
+                        for (int pl = 0; pl < 2; ++pl) {
+#pragma unroll
+                            for (int i = 0; i < MI; ++i) fa[i][pl] = *(const lds_u32x4*)(st + fragA0 + i * 32 * SLICE_BYTES + pl * 64 + co);
+#pragma unroll
+                            for (int j = 0; j < NJ; ++j) fb[j][pl] = *(const lds_u32x4*)(st + fragB0 + j * 32 * SLICE_BYTES + pl * 64 + co);
+                        }
+#pragma unroll
+                        for (int pl = 0; pl < 2; ++pl)
+#pragma unroll
+                            for (int i = 0; i < MI; ++i)
+#pragma unroll
+                                for (int j = 0; j < NJ; ++j) mfma_i8(fa[i][pl], fb[j][1 - pl], ord[3][i][j]);
+                    }
+                    if (((s - nSlices) & 511) == 511) carry(3);
+                }
+            }
         } else {
             for (int s = 0; s < nSteps; ++s) {
                 const lds_char* st = arrive(s);
@@ -639,16 +666,17 @@ __global__ __launch_bounds__(SH::THREADS, SH::WAVES_PER_SIMD) void gram_kernel(B
             }
         }
         if constexpr (I8) {
-            // in units of 65536 (the reciprocal norms carry the scale); order 0 is exact in fp32 up to rows of 1040 elements
+            // in units of 2^24 (the reciprocal norms carry the scale); order 0 is exact in fp32 up to rows of 1040 elements
 #pragma unroll
             for (int i = 0; i < MI; ++i)
 #pragma unroll
                 for (int j = 0; j < NJ; ++j)
 #pragma unroll
                     for (int r = 0; r < 16; ++r) {
-                        float v = (float)ord[2][i][j][r];
-                        v = fmaf((float)ord[1][i][j][r], 256.0f, v);
-                        acc[i][j][r] = fmaf((float)ord[0][i][j][r], 65536.0f, v);
+                        float v = LOWEST ? (float)ord[ORDERS - 1][i][j][r] : 0.0f;
+                        v = fmaf((float)ord[2][i][j][r], 256.0f, v);
+                        v = fmaf((float)ord[1][i][j][r], 65536.0f, v);
+                        acc[i][j][r] = fmaf((float)ord[0][i][j][r], 16777216.0f, v);
                     }
         }
         // LDS the epilogue may use for its buffers: a ring stage that the last slice did not occupy
@@ -1026,8 +1054,7 @@ static int launch_gram_shape(const Batch& bt, const GramArgs& ga_in, hipStream_t
     }
     ga.stat_wgs = grid_x;
     if (stat_words) *stat_words = STAT ? grid_x * SH::WAVES : 0;
-    const int tok_bytes = SH::I8 ? ((ga.dk + 63) / 64) * 192 : ga.dk * 2;
-    const size_t lds = SH::lds_bytes((tok_bytes + SH::SLICE_BYTES - 1) / SH::SLICE_BYTES);
+    const size_t lds = SH::lds_bytes(SH::I8 ? (ga.dk + 63) / 64 : (ga.dk * 2 + SH::SLICE_BYTES - 1) / SH::SLICE_BYTES);
     static size_t raised = 0;
     if (lds > raised) {
         if (hipFuncSetAttribute((const void*)gram_kernel<SH, MODE, STAT, SYM>, hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -1054,8 +1081,8 @@ typedef Shape<PACT_BF16, 4, 2, 2, 4, 2, false> Tile256;
 typedef Shape<PACT_BF16, 4, 2, 2, 4, 2, true> Tile256Wide;
 typedef Shape<PACT_BF16, 2, 2, 2, 2, 2, false> Tile128;
 typedef Shape<PACT_BF16, 3, 3, 2, 2, 3, false> Tile192;        // density pass
-typedef Shape<PACT_I8X3, 1, 2, 4, 2, 3, true> TileI8;         // density pass
-typedef Shape<PACT_I8X3, 2, 1, 2, 4, 3, true> TileI8Cand;     // candidate pass (groups of 64 rows)
+typedef Shape<PACT_I8X4, 1, 2, 4, 2, 3, true> TileI8;         // density pass
+typedef Shape<PACT_I8X4, 2, 1, 2, 4, 3, true> TileI8Cand;     // candidate pass (groups of 64 rows)
 constexpr int WIDE_KEYS = 1024;
 
 static double gram_cost(const Batch& bt, bool density, int tile, int dk, bool mirrored) {
@@ -1093,7 +1120,7 @@ static int gram_args(GramArgs& ga, const Batch& bt, const Ws& w, const void* key
     ga.dk = dk; ga.idx_rows = idx_rows; ga.idx_cols = idx_cols; ga.rep = rep;
     ga.rinv = w.rinv; ga.zeros = (const char*)w.zeros; ga.adj = w.adj;
     ga.margin = (float)cos_margin(dk, k_dt);
-    ga.rinv_low = 256.0f / (23726566.0f * powf((float)dk / 512.0f, 0.25f));    // |X| = 2^24.5 (dk / 512)^(1/4)
+    ga.rinv_low = 4096.0f / (3.5f * 2139062143.0f);                            // |X| = 3.5 max|X|
     if (!ga.keys || !ga.idx_rows || !ga.idx_cols || !ga.rep || !ga.rinv || !ga.zeros || !ga.adj || ga.dk < 1)
         return PACT_ERR_NULL;                     // (an argument block that was not filled in completely)
     // the kernel addresses a sample's key rows with 32-bit byte offsets

@@ -58,7 +58,7 @@ struct WsLayout {
     size_t rho, rank, status, cnum, cmask;             // per sample, pitch n_max (cmask: W)
     size_t preds, heads;                               // [B][n_max][PRED_CAP] u16, [B][n_max] 4 x u16 (count + first 3; until those are
                                                        // built, the low parts of the densities: see add_density)
-    size_t ksplit;                                     // [total][dk/64 rounded up][3][64] int8: fp32 clustering keys as three int8 planes
+    size_t ksplit;                                     // [total]: fp32 clustering keys as int8 planes, [dk/64 rounded up][3][64] and [dk/64 rounded up][64]
     size_t near_list, near_cnt, stat;                  // refine list, counter; [B][workgroups * 8] most negative density exponent seen
     size_t tie_list, tie_cnt;                          // [B][RHO_RECHECK_MAX] kept positions whose density is re-evaluated; [B][4]: count, ticket
     size_t rho_fix;                                    // [B][min(RHO_RECHECK_MAX, n_max)][ceil(n_max / RHO_RECHECK_CHUNK)][2] f64 partial sums of those
@@ -72,9 +72,9 @@ inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 __host__ __device__ inline int64_t rho_fix_tokens(int64_t n_max) { return n_max < RHO_RECHECK_MAX ? n_max : RHO_RECHECK_MAX; }
 __host__ __device__ inline int64_t rho_fix_chunks(int64_t n_max) { return (n_max + RHO_RECHECK_CHUNK - 1) / RHO_RECHECK_CHUNK; }
 
-// Bytes of one token's clustering key as the Gram passes read it: bf16 as it is, fp32 as three int8
-// planes, 192 bytes per 64 elements (padded with zeros).
-inline size_t gram_token_bytes(int64_t dk, int k_dt) { return k_dt == PACT_F32 ? (size_t)((dk + 63) / 64) * 192 : (size_t)dk * 2; }
+// Bytes of one token's clustering key as the Gram passes read it: bf16 as it is, fp32 as four int8 planes (padded with zeros to a
+// multiple of 64 elements): the upper three interleaved, 192 bytes per 64 elements, then the lowest, 64 bytes per 64 elements.
+inline size_t gram_token_bytes(int64_t dk, int k_dt) { return k_dt == PACT_F32 ? (size_t)((dk + 63) / 64) * 256 : (size_t)dk * 2; }
 
 // dk: width of the clustering keys (0 for calls that run no Gram pass); k_dt: their type (only
 // fp32 keys have a copy)
@@ -229,16 +229,16 @@ inline long kept_estimate(const Batch& bt) {
 enum { INIT_REDUCE = 0, INIT_DBDPC_ALL = 1, INIT_DBDPC_SUBSET = 2, INIT_REINC = 3, INIT_SCORE = 4 };
 
 // Worst-case error of a cosine from the matrix passes.  bf16 keys: rounding of the fp32 accumulation of
-// dk products, plus slack for the scaling multiplies.  fp32 keys: the rounding of the elements to 24 bits
-// of the row's largest (sqrt(dk) 2^-23), the byte products left out (below dk 2^-23), the fp32 combination
-// of the rest.  Decisions closer than this to a threshold are re-made in fp64.
+// dk products, plus slack for the scaling multiplies.  fp32 keys: bytes left out of the elements (at most
+// sqrt(dk) 2^-23: all below 2^-24 of a row's largest), byte products left out (below dk 2^-23: order 3), the fp32
+// combination of the rest.  Decisions closer than this to a threshold are re-made in fp64.
 inline double cos_margin(int dk, int k_dt) {
     const double extra = k_dt == PACT_F32 ? sqrt((double)dk) : 0.0;
     return ((double)dk + extra + 16.0) * (1.0 / 8388608.0) + 2.5e-6;
 }
 
-// Internal element type of the Gram kernel for fp32 keys: each row as 24-bit integers in three int8 planes.
-enum { PACT_I8X3 = 2 };
+// Internal element type of the Gram kernel for fp32 keys: each row as 32-bit integers in four int8 planes.
+enum { PACT_I8X4 = 2 };
 
 }  // namespace pact
 
