@@ -75,7 +75,8 @@ def test_tokens_that_move_past_the_band_leave_one_order(n, d_n):
         idx = np.setdiff1d(np.arange(n), np.delete(role, k, axis=0))
         o = P.dbdpc_cluster(x, d_c, d_n, idx=torch.from_numpy(idx).int().cuda(),
                             n_idx_dev=torch.tensor([idx.size], dtype=torch.int32, device="cuda"), want_rho=True)
-        assert P.read_report(o["rep"])["rho_rechecked"] == 0
+        rep = P.read_report(o["rep"])
+        assert rep["rho_rechecked"] == 0 and rep["refine_overflow"] == 0, rep
         sums[idx] = o["rho"].cpu().numpy()[:idx.size] + 2.0
     o = P.dbdpc_cluster(x, d_c, d_n, want_rho=True, want_rank=True)
     torch.cuda.synchronize()
@@ -107,3 +108,77 @@ def test_densities_do_not_depend_on_the_order_of_the_additions(n, dk, dtype, d_n
     # and they are the sums: a term's error is that of its exponent, (dk + 16) 2^-24 / d_n at the very most and mostly far less
     exact = torch.exp(-_distances(x) / float(np.float32(d_n))).sum(1)
     assert float(((runs[0] - exact).abs() / exact).max()) <= (dk + 16) * 2.0 ** -24 / d_n
+
+
+def _twins(n, dk, spread, seed):
+    """fp32 keys of which the last half of the tokens `spread` names are the first half again, off by one part in 10^6: densities that differ
+    by less than the fp32 terms can tell."""
+    r = np.random.default_rng(seed)
+    first, second = spread
+    x = r.standard_normal((max(2, n // 12), dk))[r.integers(0, max(2, n // 12), n)] + 0.25 * r.standard_normal((n, dk))
+    x[second] = x[first] + 1e-6 * r.standard_normal((len(first), dk))
+    return x.astype(np.float32)
+
+
+def _order_of_sums(x, d_n, idx=None):
+    """Densities as the fp32 terms leave them (no neighbours within 0: nothing is evaluated again) and in fp64."""
+    n = x.shape[0]
+    kw = {} if idx is None else dict(idx=torch.from_numpy(idx).int().cuda(), n_idx_dev=torch.tensor([idx.size], dtype=torch.int32, device="cuda"))
+    o = P.dbdpc_cluster(x, 0.0, d_n, want_rho=True, **kw)
+    rep = P.read_report(o["rep"])
+    assert rep["rho_rechecked"] == 0 and rep["refine_overflow"] == 0, rep
+    u = x if idx is None else x[torch.from_numpy(idx).cuda()]
+    d = _distances(u)
+    return o["rho"].cpu().numpy()[:n if idx is None else idx.size], torch.exp(-d / float(np.float32(d_n))).sum(1).cpu().numpy(), d
+
+
+def _check_reordered(x, d_c, d_n, idx, sums, exact, d, first, second):
+    """The call's centres are those of the fp64 order, which the fp32-term sums get wrong for some pairs (first[k], second[k])."""
+    kw = {} if idx is None else dict(idx=torch.from_numpy(idx).int().cuda(), n_idx_dev=torch.tensor([idx.size], dtype=torch.int32, device="cuda"))
+    wrong = np.sign(sums[first] - sums[second]) != np.sign(exact[first] - exact[second])
+    near = (d <= float(np.float32(d_c))).cpu().numpy()
+    assert wrong.sum() >= 1 and near[first, second].all()
+    for _ in range(3):
+        o = P.dbdpc_cluster(x, d_c, d_n, want_rho=True, **kw)
+        torch.cuda.synchronize()
+        rep, rho = P.read_report(o["rep"]), o["rho"].cpu().numpy()[:exact.size]
+        assert rep["rho_rechecked"] >= 2 and rep["refine_overflow"] == 0
+        assert np.max(np.abs(rho[first] - exact[first])) <= 1e-11 * exact.max()
+        centres = _centres_of(near, rho)
+        tokens = centres if idx is None else idx[centres]
+        assert np.array_equal(o["center_idx"][:rep["n_centers"]].cpu().numpy(), tokens)
+        assert not np.array_equal(centres, _centres_of(near, sums))           # (the selection before the re-evaluation had others)
+    print(f"{wrong.sum()} of {first.size} pairs in the wrong order, listed {rep['rho_rechecked']}, rounds {rep['rounds']}")
+
+
+@pytest.mark.parametrize("n,pairs,dk", [(960, 480, 4096), (1000, 300, 512)])
+def test_selection_runs_again_when_the_fp64_densities_are_the_last_to_come(n, pairs, dk):
+    # hundreds of listed tokens with long rows: the re-evaluation ends long after the selection, whose order it changes
+    # (a build that noted which workgroup ran it again: one of the re-evaluation's, in all calls)
+    first, second = np.arange(pairs), np.arange(n - pairs, n)
+    x = torch.from_numpy(_twins(n, dk, (first, second), n)).cuda()
+    sums, exact, d = _order_of_sums(x, 2.0)
+    _check_reordered(x, 1e-5, 2.0, None, sums, exact, d, first, second)
+
+
+def test_selection_runs_again_when_it_is_the_last_to_come():
+    # Two listed tokens, and a selection that has to go along a chain: tokens on an arc, densest at one end. Of the twins one pair whose order the
+    # fp32-term sums get wrong is left in.  (The same build: the selection's own workgroup.)
+    n, arc, dk, d_c = 2620, 2000, 64, 2e-3
+    r = np.random.default_rng(5)
+    first, second = np.arange(n - 120, n - 60), np.arange(n - 60, n)
+    x = _twins(n, dk, (first, second), 5)
+    x[first] = r.standard_normal((60, dk))                                    # (no neighbours but their twins)
+    x[second] = x[first] + 1e-6 * r.standard_normal((60, dk))
+    theta = np.concatenate([np.linspace(0.0, 2.5, arc), 0.4 * r.random(n - 120 - arc)])
+    x[:n - 120] = 1e-4 * r.standard_normal((n - 120, dk))
+    x[:n - 120, 0] += np.cos(theta)
+    x[:n - 120, 1] += np.sin(theta)
+    x = torch.from_numpy(x.astype(np.float32)).cuda()
+    for k in range(60):
+        idx = np.concatenate([np.arange(n - 60), second[k:k + 1]])
+        sums, exact, d = _order_of_sums(x, 2.0, idx)
+        a, b = n - 120 + k, n - 60                                            # their positions in the subset
+        if np.sign(sums[a] - sums[b]) != np.sign(exact[a] - exact[b]):
+            return _check_reordered(x, d_c, 2.0, idx, sums, exact, d, np.array([a]), np.array([b]))
+    pytest.fail("no pair whose order the sums get wrong")
