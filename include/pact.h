@@ -236,7 +236,7 @@ int pact_reduce(const void* hidden, pact_dtype h_dt, int32_t n, int32_t h,
  * that is part of the library's device code (each GPU the library runs on holds its own copy
  * until the process ends).  The call makes no allocation of any kind.
  *  - A call that would need more scratch than that (pact_workspace_bytes(n, 1, n_kv*d_h, k_dt,
- *    n_q, d_h) tells) returns PACT_ERR_WORKSPACE; every single image of up to 8748 tokens with
+ *    n_q, d_h) tells) returns PACT_ERR_WORKSPACE; every single image of up to 14500 tokens with
  *    512-wide bf16 keys and 28 query heads fits.
  *  - All calls on one GPU share that GPU's array: they must be ordered on one stream (or
  *    otherwise serialised); calls that overlap on one GPU race.  The array keeps the last call's

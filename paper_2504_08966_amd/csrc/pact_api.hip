@@ -52,8 +52,9 @@ static int check_tensor(const void* p, int dt, int64_t cols) {
     if (!aligned16(p) || (cols * esize(dt)) % 16 != 0) return PACT_ERR_ALIGN;
     return PACT_OK;
 }
-// The matrix passes address a sample's clustering keys with 32-bit byte offsets (fp32 keys in
-// their three-part bf16 form, 6 bytes per value).
+// The matrix passes address a sample's clustering keys with 32-bit byte offsets.  fp32 keys: the limit that pact.h states is 6
+// bytes per value; their integer form takes 4, padded to 64 values (gram_token_bytes), which that limit covers from 48 values
+// a row on, and below that no sample is large enough.
 static int check_key_extent(int64_t n_max, int64_t dk, int k_dt) {
     const uint64_t tok_bytes = (k_dt == PACT_F32) ? 3ull * (((uint64_t)dk + 7) & ~7ull) * 2 : (uint64_t)dk * 2;
     return (uint64_t)n_max * tok_bytes > 0xFFFFFFFFull ? PACT_ERR_SHAPE : PACT_OK;

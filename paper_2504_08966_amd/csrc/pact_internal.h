@@ -55,7 +55,7 @@ struct WsLayout {
     size_t ident;                                      // identity index list (idx == NULL)
     size_t adj;                                        // [B][n_max][W] u64: rows < q adjacency; from row q on: candidate words [Wc][n_pruned]
     size_t cbest;                                      // [B][W][n_max] f32: largest cosine per (group of 64 centres, pruned token)
-    size_t rho, rank, status, cnum, cmask;             // per sample, pitch n_max (cmask: W)
+    size_t rho, status, cnum, cmask;                   // per sample, pitch n_max (cmask: W)
     size_t preds, heads;                               // [B][n_max][PRED_CAP] u16, [B][n_max] 4 x u16 (count + first 3; until those are
                                                        // built, the low parts of the densities: see add_density)
     size_t ksplit;                                     // [total]: fp32 clustering keys as int8 planes, [dk/64 rounded up][3][64] and [dk/64 rounded up][64]
@@ -63,7 +63,7 @@ struct WsLayout {
     size_t tie_list, tie_cnt;                          // [B][RHO_RECHECK_MAX] kept positions whose density is re-evaluated; [B][4]: count, ticket
     size_t rho_fix;                                    // [B][min(RHO_RECHECK_MAX, n_max)][ceil(n_max / RHO_RECHECK_CHUNK)][2] f64 partial sums of those
     size_t offsets, members, big;                      // merge CSR (global row index); ids of the large clusters
-    size_t slots;                                      // [total][MERGE_SLOTS] i32: first members of each cluster, in the order they joined
+    size_t slots;                                      // [total][MERGE_SLOTS] i32: first members of each cluster, in the order they joined (in the place of preds)
     size_t zeros;                                      // 256 zero bytes
     size_t total;
 };
@@ -95,7 +95,6 @@ inline WsLayout make_layout(int64_t n_max, int64_t B, int64_t total, int64_t qco
     L.adj = take(sizeof(uint64_t) * B * n_max * W);
     L.cbest = take(sizeof(float) * B * W * n_max);
     L.rho = take(sizeof(double) * B * n_max);
-    L.rank = take(sizeof(int32_t) * B * n_max);
     L.status = take(sizeof(uint32_t) * B * n_max);
     L.cnum = take(sizeof(int32_t) * B * n_max);
     L.cmask = take(sizeof(uint64_t) * B * W);
@@ -110,12 +109,11 @@ inline WsLayout make_layout(int64_t n_max, int64_t B, int64_t total, int64_t qco
     L.offsets = take(sizeof(int32_t) * (total + B));
     L.members = take(sizeof(int32_t) * total);
     L.big = take(sizeof(int32_t) * total);
-    L.slots = take(sizeof(int32_t) * total * MERGE_SLOTS);
-    take(n_max > 8192 ? 16 * B * n_max : 0);             // (nothing: the size that callers have been told stays)
+    // (the selection is over with the lists when the first member joins a cluster)
+    static_assert(sizeof(int32_t) * MERGE_SLOTS == sizeof(uint16_t) * PRED_CAP, "a token's list and a cluster's slots take the same room");
+    L.slots = L.preds;
     L.zeros = take(256);
-    // (at least the six bytes per value that callers have been told to provide for)
-    const size_t key6 = (size_t)((dk + 7) / 8 * 8) * 6, keyI = gram_token_bytes(dk, k_dt);
-    L.ksplit = take(k_dt == PACT_F32 ? total * (keyI > key6 ? keyI : key6) : 0);
+    L.ksplit = take(k_dt == PACT_F32 ? total * gram_token_bytes(dk, k_dt) : 0);
     L.total = off;
     return L;
 }
@@ -124,7 +122,7 @@ inline WsLayout make_layout(int64_t n_max, int64_t B, int64_t total, int64_t qco
 struct Ws {
     double* qg_part; double* logits; double* hnorm; double* sm_part;
     double* nn; float* rinv; int32_t* ident;
-    uint64_t* adj; float* cbest; double* rho; int32_t* rank; uint32_t* status;
+    uint64_t* adj; float* cbest; double* rho; uint32_t* status;
     int32_t* cnum; uint64_t* cmask; uint16_t* preds; uint2* heads; double* rho_lo; uint32_t* near_list; int32_t* near_cnt; uint32_t* stat;
     int32_t* tie_list; int32_t* tie_cnt; double* rho_fix;
     int32_t* offsets; int32_t* members; int32_t* big; int32_t* slots; uint32_t* zeros; char* ksplit;
@@ -138,7 +136,7 @@ inline Ws resolve(void* base, const WsLayout& L) {
     w.sm_part = (double*)(p + L.sm_part);
     w.nn = (double*)(p + L.nn); w.rinv = (float*)(p + L.rinv); w.ident = (int32_t*)(p + L.ident);
     w.adj = (uint64_t*)(p + L.adj); w.cbest = (float*)(p + L.cbest);
-    w.rho = (double*)(p + L.rho); w.rank = (int32_t*)(p + L.rank);
+    w.rho = (double*)(p + L.rho);
     w.status = (uint32_t*)(p + L.status); w.cnum = (int32_t*)(p + L.cnum);
     w.preds = (uint16_t*)(p + L.preds); w.heads = (uint2*)(p + L.heads); w.rho_lo = (double*)(p + L.heads);
     w.cmask = (uint64_t*)(p + L.cmask); w.near_list = (uint32_t*)(p + L.near_list);
