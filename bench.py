@@ -18,6 +18,7 @@ against the HBM peak, and the CPU oracle timed on this machine's host cores on the s
 from __future__ import annotations
 
 import argparse
+import hashlib
 import json
 import os
 import re
@@ -45,34 +46,56 @@ def algorithmic_work(kernel: str, n, h, dk, q, C, n_reinc, key_bytes, hid_bytes,
     return None, 0.0, ""
 
 
-def _profile_table(name):
-    """Rows `| kernel | a | b | ...` of a committed rocprofv3 summary under profiles/ -> {kernel: [cells]}."""
-    path = os.path.join(ROOT, "profiles", name)
+def source_digest(csrc=None):
+    """Digest of the library's sources without comments and white space: what a committed measurement was taken of."""
+    csrc = csrc or os.path.join(ROOT, "paper_2504_08966_amd", "csrc")
+    h = hashlib.sha256()
+    for fn in sorted(os.listdir(csrc)):
+        if fn.endswith((".hip", ".h")):
+            text = re.sub(r"//[^\n]*", "", open(os.path.join(csrc, fn)).read())
+            h.update(fn.encode() + re.sub(r"\s+", "", text).encode())
+    return h.hexdigest()[:16]
+
+
+def _profile_table(name, folder=None):
+    """Rows `| kernel | a | b | ...` of a committed rocprofv3 summary under profiles/ -> {kernel: [cells]}; empty where the
+    summary was not taken of these sources (its line `Sources: <digest>` says of which)."""
+    path = os.path.join(folder or os.path.join(ROOT, "profiles"), name)
     rows = {}
     if os.path.exists(path):
-        for ln in open(path):
+        text = open(path).read()
+        of = re.search(r"^Sources: ([0-9a-f]{16})$", text, re.M)
+        if not of or of.group(1) != source_digest():
+            return rows
+        for ln in text.splitlines():
             cells = [c.strip() for c in ln.strip().strip("|").split("|")]
             if len(cells) >= 3 and re.fullmatch(r"[a-z_]+", cells[0] or ""):
                 rows[cells[0]] = cells[1:]
     return rows
 
 
-def measured_traffic(kernel: str):
-    """HBM bytes per launch of `kernel` (read + write) from the committed rocprofv3 --pmc summary."""
-    cells = _profile_table("pact_reduce_img7b_hbm_traffic.md").get(kernel)
+def _profile_number(name, kernel, *columns):
+    """Sum of the given columns of a kernel's row in a committed summary, or None."""
+    cells = _profile_table(name).get(kernel)
     try:
-        return float(cells[0]) + float(cells[1])
+        return sum(float(cells[c]) for c in columns)
     except (TypeError, ValueError, IndexError):
         return None
+
+
+def measured_traffic(kernel: str):
+    """HBM bytes per launch of `kernel` (read + write) from the committed rocprofv3 --pmc summary."""
+    return _profile_number("pact_reduce_img7b_hbm_traffic.md", kernel, 0, 1)
 
 
 def rocprof_us(kernel: str):
     """Average duration of `kernel` in the committed rocprofv3 kernel trace of this command (us)."""
-    cells = _profile_table("pact_reduce_img7b_kernel_stats.md").get(kernel)
-    try:
-        return float(cells[1])
-    except (TypeError, ValueError, IndexError):
-        return None
+    return _profile_number("pact_reduce_img7b_kernel_stats.md", kernel, 1)
+
+
+def executed_gflop(kernel: str):
+    """GFLOP that `kernel` issues to the matrix cores per launch, from the committed counters."""
+    return _profile_number("pact_reduce_img7b_mfma_counters.md", kernel, 0)
 
 
 def kernel_times(P, torch, fn, steps):
@@ -118,8 +141,8 @@ def other_configs(P, gen, torch, np, only=None, steps_override=None):
         return (time.perf_counter() - t0) / steps * 1e6
 
     def fractions(kus, reps, ns, h, dk):
-        """density pass: unique pairs of all samples against the bf16 matrix-core peak (fp32 keys run on the
-        bf16 instruction as three parts, six passes: their algorithmic flops are still q^2 dk); merge: member
+        """density pass: unique pairs of all samples against the bf16 matrix-core peak (fp32 keys run on the int8
+        instruction, eight byte products a pair: their algorithmic flops are still q^2 dk); merge: member
         rows read + merged rows written against the HBM peak."""
         out = {}
         if "gram_density" in kus:
@@ -394,10 +417,11 @@ def main():
         if rp:
             roof["us_per_launch_rocprof"] = rp
             roof["frac_rocprof"] = round(work / (rp * 1e-6) / (1e12 if bound == "mfma" else 1e9) / peak, 4)
-        if k == "gram_density":
-            # the kernel computes the full (symmetric) matrix: executed flops are twice the algorithmic ones
-            roof["executed_flop_per_launch"] = 2.0 * work
-            roof["frac_executed"] = round(2.0 * ach / peak, 4)
+        # what it issues to the matrix cores (tiles on the diagonal are computed whole, the last ones are padded)
+        ex = executed_gflop(k)
+        if ex:
+            roof["executed_flop_per_launch"] = ex * 1e9
+            roof["frac_executed"] = round(ex * 1e9 / sec / 1e12 / peak, 4)
         break
 
     # the bandwidth-bound stages: cold first (nothing of the inputs in any cache), then warm (inputs still in the
