@@ -51,9 +51,12 @@
  *    (bf16 keys as they are; fp32 keys as 32-bit integers in four 8-bit planes).  The sums do not
  *    depend on the order in which they are formed: the same call gives the same densities, bit for bit.
  *    The density order (Alg. 2) only matters between tokens within d_c of each other; where
- *    two such tokens have densities closer than a band of about fifty standard errors of
+ *    two such tokens have densities closer than a band of twenty to a hundred standard errors of
  *    that fp32 sum, both densities are evaluated again entirely in fp64 (Eq. 5 and Eq. 6 as
- *    written) and those decide (pact_report.rho_rechecked, rho_near_ties).
+ *    written) and those decide (pact_report.rho_rechecked, rho_near_ties).  The band is measured, not
+ *    a worst case: where nearly all tokens of a sample are alike, a token's terms share the
+ *    rounding of its norm and the sum can be off by more, so that two neighbours may be ordered by their
+ *    sums although fp64 would order them the other way round.
  *  - Ties: equal scores at the percentile are all kept; equal densities are processed in
  *    ascending token index; equal distances pick the centre with the lower token index.
  *  - A zero-norm key has cosine 0 (distance 1) to every other token; d_ii = 0.

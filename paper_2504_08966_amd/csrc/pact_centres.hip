@@ -1,5 +1,5 @@
 // DBDPC after the Gram pass (Alg. 2): density order, centre selection under the bound d_c
-// done by parallel looks (same centres as the sequential loop; cf. the recursive scheme of
+// by parallel looks (same centres as the sequential loop; cf. the recursive scheme of
 // appendix D), nearest-centre assignment; and the recovery of pruned tokens (Eq. 8/9).
 //
 // Centre selection.  Token j "precedes" i when rho_j > rho_i, or rho_j == rho_i and j < i
@@ -8,9 +8,9 @@
 // every token can evaluate on its own from its list of preceding neighbours:
 //     a preceding neighbour is a centre            -> i is not a centre
 //     every preceding neighbour is known not to be -> i is a centre
-// A round evaluates this for all undecided tokens at once; the densest undecided token is
-// always decided, so the rounds terminate, and the result does not depend on how stale the
-// statuses read within a round are.
+// Every wavefront evaluates this for its undecided tokens again and again, on statuses that the others
+// change meanwhile.  The lists come from one order of the tokens, so the densest undecided token can always
+// be decided and the looks end; what a token becomes does not depend on how stale the statuses are that were read.
 #include <cstring>
 
 #include "pact_internal.h"
@@ -155,7 +155,7 @@ __device__ __forceinline__ void nearest_candidate(lds_i32* cand, lds_i32* ctok, 
 // spread evenly (near d_c the pairs of a row come in clumps: settled by the wavefronts that build the rows'
 // lists, or by workgroups of 32 rows, they took 3 to 13 us longer); a wavefront's pairs, tokens and norms arrive in three
 // trips, then one trip per pair brings both rows (up to eight chunks of either per lane in flight: rows of
-// 7 KB took 57 us for 23 700 pairs when every chunk was a trip of its own).
+// 7 KB took 57 us for 23 700 pairs when every chunk was a trip of its own, 52 to 55 us now: they are 340 MB).
 // grid (settle_blocks(), B), block 256.
 static int settle_blocks(int n_max) { return n_max >= 6144 ? 768 : n_max < 512 ? 64 : n_max / 8; }   // (the benchmark image: a pair per wavefront)
 
@@ -312,14 +312,21 @@ struct BitPop {
 // (matrix-core accumulation, scaling products, one fused multiply-add; a = log2(e) / d_n is the
 // factor that turns a cosine error into an exponent error) and of the hardware exponential,
 // independent from term to term, so the error of a sum grows like the square root of the number
-// of terms that matter.  Measured against fp64 on 7290-token images: standard error of the
-// difference of two neighbours' densities 2.1e-6 at d_n = 2 (rho = 2 400), 4.9e-6 at d_n = 0.5
-// (rho = 570), 1.6e-6 at d_n = 8; largest seen 8e-6 / 3.2e-5 / 1.2e-5.  Two neighbours whose
-// sums differ by less than
-//     2^-20 (1 + 4a) sqrt(max(rho_i, rho_j))          (1.8e-4 / 2.8e-4 / 9.8e-5 for those cases)
+// of terms that matter.  Two neighbours whose sums differ by less than
+//     2^-20 (1 + 4a) sqrt(max(rho_i, rho_j))
 // are both listed, and their densities are evaluated again entirely in fp64 before the order
-// between them is used.  This is a statistical bound (fifty and more standard errors), not a
-// worst-case one: the worst-case error of an fp32 cosine would list half the tokens of an image.
+// between them is used.  Measured against fp64, difference of two neighbours' sums, standard error / largest seen /
+// the band, bf16 keys and fp32 keys, 512 wide:
+//   4010 tokens of an image   d_n = 0.25  1.4e-5 / 7.5e-5 / 2.6e-4   9.4e-6 / 4.7e-5 / 2.6e-4   (rho = 120)
+//                             d_n = 0.5   7.0e-6 / 3.5e-5 / 2.9e-4   4.2e-6 / 2.1e-5 / 2.9e-4   (rho = 590)
+//                             d_n = 2     2.5e-6 / 1.1e-5 / 1.8e-4   2.2e-6 / 0.9e-5 / 1.8e-4   (rho = 2450)
+//                             d_n = 8     1.7e-6 / 0.7e-5 / 9.8e-5   1.7e-6 / 0.7e-5 / 9.8e-5   (rho = 3540)
+//   8000 of a video           d_n = 2     2.8e-6 / 1.3e-5 / 2.6e-4   2.8e-6 / 1.3e-5 / 2.6e-4   (rho = 4980)
+// i.e. a band of twenty to a hundred standard errors.  It is a statistical bound, not a worst-case one (that of an fp32 cosine would list
+// half the tokens of an image), and it does not hold everywhere: the rounding of a token's reciprocal norm is shared by all
+// its terms, and where nearly all tokens are alike (cosines near 1) the errors add up.  Half of 4010 tokens nearly alike: largest error 0.9 of
+// the band at d_n = 2, 1.5 at 0.25; all of 7290: 2.4 and 3.0 (more than 1024 tokens are listed there, which is reported).  The
+// order between two such neighbours may then be that of the sums; whatever it is, it is one order (order_changed).
 __device__ __forceinline__ double recheck_band2(float d_n) {
     const double a = 1.4426950408889634 / (double)d_n;
     const double c = (1.0 / 1048576.0) * (1.0 + 4.0 * a);
@@ -502,8 +509,7 @@ __global__ __launch_bounds__(256) void build_preds_kernel(Batch bt, const pact_r
 //  * Tokens whose list overflowed the record are evaluated from their bitmap row by a whole
 //    wavefront.
 // Bound by chains of dependent accesses.  Rounds between barriers, with work lists of the undecided tokens, took 1.7 us
-// each, at least four of them; statuses were read one after the other, a long record by one lane. 4010 tokens: 18 -> 14 us
-// from the start to the end, 16384 tokens: 74 -> 33 us.
+// each, at least four of them; statuses were read one after the other, a long record by one lane.  (The times are at the kernel.)
 // The code is loops rather than unrolled: it runs once, from a cold instruction cache.
 // dynamic LDS: rounds_lds below.
 // Tokens whose heads are kept in LDS, and whether the token numbers are.
@@ -1011,10 +1017,12 @@ __device__ __forceinline__ void replace_densities(const Batch& bt, const Centres
 // Centre rounds and fp64 densities side by side: workgroup b < B runs the rounds of sample b in the order of the
 // densities that it finds; the others share out the batch's work items of listed tokens, and the one that
 // finishes a sample's last item looks whether two neighbours change their order.  They hardly ever do (the band that lists tokens is
-// some fifty standard errors wide); if so, the later of that workgroup and the sample's first one puts the fp64
+// twenty and more standard errors wide); if so, the later of that workgroup and the sample's first one puts the fp64
 // densities in place and runs the rounds again.  Nobody waits for anybody: counters say who is last.
-// As two launches, one after the other: 4010-token image 28 -> 18 us, 8 videos of 3450 tokens 43 -> 31 us, 7290 rows of 7 KB
-// 97 -> 37 us, 16384 tokens with fp32 keys 140 -> 67 us (the fp64 products of 70 listed tokens).
+// As two launches, rounds with barriers after the re-evaluation (event brackets, of which either launch has 2.5 us): 4010-token
+// image 29 -> 20 us, 8 videos of 3450 tokens 48 -> 42 us, 16 ragged images 34 -> 21 us, 7290 rows of 7 KB 96 -> 36 us, 16384 tokens with fp32
+// keys 151 -> 77 us (the fp64 products of 70 listed tokens).  Bound by the selection of a sample on one CU, for the videos and the long
+// rows by the fp64 matrix products of the listed tokens.
 // tie_cnt[4b]: listed tokens; [4b + 1]: work items done; [4b + 2]: 1 looked at, ORDER_PAIRS, ORDER_BAND, 4 rounds run.
 // grid (B + workers), block 1024, dynamic LDS: what run_rounds takes, at least RECHECK_LDS.
 template <int DT>
@@ -1232,7 +1240,7 @@ __device__ __forceinline__ void nearest_listed(const lds_i32* list, int n, int l
 // TPW tokens per wavefront, 64 / TPW lanes each, as long as they look for their candidates: one while the chip holds a wavefront for
 // each token, four beyond that.  Up to four candidates of a token are then compared in fp64 by its 16 lanes, row by row; more take
 // the whole wavefront, token by token (fp32 cosines of eight candidates at a time, fp64 for those that are left).
-// 27 600 kept tokens of 8 videos 31 -> 21 us, 18 200 of 16 ragged images 29 -> 26 us.
+// Event brackets: 27 600 kept tokens of 8 videos 29 -> 19 us, 18 200 of 16 ragged images 27 -> 24 us, 12 800 of 32 crops 17 us either way.
 template <int DT, int TPW>
 __device__ __forceinline__ void assign_body(const Batch& bt, const NearArgs& a, int blk, lds_i32* cand,
                                             lds_i32* ctok, lds_f32* ccos, lds_i32* s_c) {

@@ -11,9 +11,10 @@
 //
 // Shape of the kernel (gfx950):
 //  * a workgroup of WR x WC wavefronts owns a (32*MI*WR) x (32*NJ*WC) output tile, each wavefront MI x NJ
-//    32 x 32 accumulators.  bf16 keys (v_mfma_f32_32x32x16_bf16): 256x256 by 8 wavefronts (halves
-//    the L2 traffic per flop of 128x128 tiles), 128x256 and 128x128 (4 wavefronts) for launches that would
-//    otherwise leave CUs without a tile.  fp32 keys (v_mfma_i32_32x32x32_i8): 128x128 by 8 wavefronts;
+//    32 x 32 accumulators.  bf16 keys (v_mfma_f32_32x32x16_bf16): 128x128 by 4 wavefronts, two workgroups per CU;
+//    256x256 by 8 wavefronts (half the L2 traffic per flop) where the turns come out better; density pass also
+//    192x192 by 4 wavefronts, where the triangle of one sample is then a single turn of the chip (see gram_cost()).
+//    fp32 keys (v_mfma_i32_32x32x32_i8): 128x128 by 8 wavefronts;
 //  * the key rows stream in slices straight from global memory into a ring of LDS stages
 //    (global_load_lds_dwordx4: no staging registers); waits on the ring are explicit (s_waitcnt
 //    vmcnt + s_barrier).  bf16: 128 bytes of each row (a whole cache line, fetched by eight lanes);
@@ -24,9 +25,9 @@
 //    are read from LDS while the MFMAs of the current one run;
 //  * the grid is persistent (the tile count depends on counts only the device knows) and
 //    XCD-aware: each of the 8 XCDs (own L2) works on its own band of tile columns;
-//  * density pass of a sample with more square tiles than workgroups: d_ij = d_ji, so only the
-//    tiles on and above the diagonal are computed, and a tile above it also leaves the row sums,
-//    the transposed bits and the flagged near-d_c pairs of its mirror image (template SYM).
+//  * density pass of a sample that saves turns by it: d_ij = d_ji, so only the tiles on and above the
+//    diagonal are computed, and a tile above it also leaves the row sums, the transposed bits and
+//    the flagged near-d_c pairs of its mirror image (template SYM, mirrored_tiles_pay()).
 //
 // fp32 keys.  The first kernel of a call writes every row as 32-bit integers X = rint(x S),
 // S = 2139062143 / max|x| or slightly less, split into four signed bytes,
@@ -136,7 +137,6 @@ template <int N> __device__ __forceinline__ void wait_vmcnt() {
     asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory");
 }
 
-// v = value in lane `l` of a wavefront-wide register (value and lane are wave-uniform)
 // Files the two halves of two ballots (m0: columns 0-31 of rows L and L+4, m1: columns 32-63)
 // under lanes L and L+4 of `lo` / `hi`.  (The compiler cannot see into the asm to pad the
 // distance a VALU-written scalar needs before another VALU instruction reads it, hence the s_nop.)
@@ -167,7 +167,6 @@ template <int L> __device__ __forceinline__ void file_ballots2(uint32_t& lo, uin
           "s"((uint32_t)h0), "s"((uint32_t)(h0 >> 32)), "s"((uint32_t)h1), "s"((uint32_t)(h1 >> 32)),
           "n"(L), "n"(L + 4));
 }
-// body(std::integral_constant<int, 0>{}) ... body(std::integral_constant<int, N-1>{})
 // Two values per lane, to be summed over pairs of lanes 16 apart: lanes with bit 4 clear get a's
 // sum, the others b's (v_permlane16_swap exchanges the odd rows of 16 lanes of one register with the even
 // rows of the other).
@@ -520,7 +519,7 @@ __global__ __launch_bounds__(SH::THREADS, SH::WAVES_PER_SIMD) void gram_kernel(B
         // groups take turns, one multiplies while the other fetches its next fragments from the LDS, with a
         // barrier between the turns, so that the matrix cores wait for no LDS read (all wavefronts reading
         // after a common barrier left them idle for a third of the slice: a slice of 64 elements of
-        // 256 x 256 bf16 tiles took 1.53 us, of 128 x 128 fp32 tiles 1.28 us; its MFMAs 1.02 and 0.76 us).
+        // 256 x 256 bf16 tiles took 1.53 us, of 128 x 128 fp32 tiles with six products 1.28 us; its MFMAs 1.02 and 0.76 us).
         // Group 1 is one turn behind.  Slice s + 1 has to be there, for every wavefront, before group 0 fetches
         // from it: either group waits for its own part at the end of the turn before that.  A slot is
         // refilled by group 0 in the turn after group 1 has read the last of it.
@@ -1066,14 +1065,21 @@ static int launch_gram_shape(const Batch& bt, const GramArgs& ga_in, hipStream_t
     return PACT_OK;
 }
 
-// The tiles.  256 x 256 has the best ratio of flops to bytes fetched; a launch lasts as many turns of 20 us (key
-// width 512) as its CUs have tiles.  Of the 128 x 128 tiles by four wavefronts a CU runs two at a time, one's
+// The tiles of the bf16 passes.  256 x 256 has the best ratio of flops to bytes fetched; a launch lasts as many turns of
+// 20 us (key width 512) as its CUs have tiles.  Of the 128 x 128 tiles by four wavefronts a CU runs two at a time, one's
 // epilogue beside the other's multiplications: 11.4 us a turn for half the area, but a launch with
 // few tiles is over in 10, and the triangle of a sample divides better into turns.  192 x 192, four wavefronts of 3 x 3 blocks (one
-// per SIMD: 1.05 us a slice of 0.56 the area), for the samples whose triangle is then one turn: 3800 to 4224 kept tokens.
-// gram_cost() has what was measured (us, per turn and slice of 64 elements), key width 512 unless stated, 256 / 192 / 128:
-//   1600 kept tokens 23 / 20 / 11, 3600: 24 / 21 / 15, 4010: 24 / 21 / 24, 4600: 24 / 37 / 23, 6000: 45 / 54 / 32, 9012: 68 / 85 / 65;
-//   of width 3584 4010: 93 / 65 / 112, 7290: 173 / 187 / 191; of width 128 4010: 14 / 16 / 16, 6000: 31 / 37 / 22
+// per SIMD: 1.05 us a slice of 0.56 the area), is the best where one sample's triangle just fits one turn of it and no longer one of
+// 128s: 3969 to 4224 kept tokens (more than 31, no more than 33 tiles of 128).  Nowhere else does gram_cost() choose it, nor is it the fastest.
+// All three, event brackets in us, dbdpc_cluster on random keys and equal batches (256 / 192 / 128):
+//   width 512    800 tokens 21 / 20 / 13, 2000: 22 / 21 / 13, 3600: 24 / 21 / 17, 3968: 24 / 21 / 17, 4010: 24 / 21 / 26, 4224: 25 / 21 / 24,
+//                4300: 25 / 36 / 24, 5000: 25 / 35 / 27, 5632: 25 / 35 / 28, 6000: 44 / 49 / 33, 7290: 46 / 51 / 43, 9012: 64 / 79 / 60,
+//                12000: 104 / 118 / 101, 16384: 177 / 217 / 182;  2 x 3450: 25 / 37 / 29, 8 x 3450: 75 / 87 / 69, 16 x 1000: 24 / 36 / 28,
+//                16 x 2900: 101 / 134 / 99, 32 x 1450: 63 / 81 / 59
+//   width 3584   2000: 80 / 63 / 43, 4010: 95 / 65 / 112, 4600: 80 / 121 / 93, 6000: 166 / 180 / 141, 7290: 177 / 187 / 190, 8192: 259 / 244 / 239
+//   width 128    2000: 15 / 16 / 10, 4010: 17 / 17 / 18, 6000: 29 / 33 / 23, 8192: 37 / 41 / 33
+// gram_cost()'s choice is the fastest of the three within 1 us but where the triangle of 128s nearly fills its second turn (5000 to 5632
+// tokens, 2 x 3450, 16 x 1000 and the like): it then takes 128 and is 2 to 4 us off.
 // bf16 tiles of 256 take turns at the matrix cores from key rows of 2 KB on: the loop over a row of 7 KB got 5%
 // shorter, over one of 1 KB the two turns' offset cost 0.8 us.  (Both are then near what the chip's
 // power allows: a slice of random keys takes 1.45 us, of keys that are mostly zeros 1.10 us, its MFMAs alone 1.02 us.)

@@ -860,9 +860,9 @@ def test_centres_with_lists_of_every_length(n, dk, frac, dtype):
 @pytest.mark.parametrize("n,dk,shift", [(130, 64, 0.0), (127, 64, 40.0), (257, 128, 40.0), (300, 192, 0.0), (385, 192, 40.0),
                                         (129, 512, 300.0), (260, 4, 0.0), (96, 33024, 0.0), (96, 66048, 900.0)])
 def test_fp32_keys_as_integers(n, dk, shift):
-    # fp32 keys go through the matrix cores as 24-bit integers: one, two, three and more slices of 64 elements
-    # around the edges of 128 x 128 tiles; rows that one element dominates (shift), which take the additional
-    # products; rows of more than 32768 elements, whose sums are carried along
+    # fp32 keys go through the matrix cores as integers, a byte at a time: one, two, three and more slices of 64 elements
+    # around the edges of 128 x 128 tiles; rows that one element dominates (shift), which take the lowest
+    # byte as well; rows of more than 32768 elements, whose sums are carried along
     r = np.random.default_rng(n + dk)
     cen = r.normal(size=(max(2, n // 12), dk))
     u = cen[r.integers(0, cen.shape[0], n)] + 0.25 * r.normal(size=(n, dk))
