@@ -48,7 +48,7 @@ def test_static_scratch_entry_point_equals_pact_reduce():
     assert got1["rep"]["n_centers"] == gu.manifest()[gu.sample_key(s1)]["C"]
     s2, ref2, got2 = _both("tiny_bf16", 2, torch.bfloat16)          # smaller input, the array holds the first call's data
     _same(ref2, got2, "second call (392 tokens)")
-    s3, ref3, got3 = _both("img_0p5b", 1)                           # fp32 keys: the three-part copy lives in the array too
+    s3, ref3, got3 = _both("img_0p5b", 1)                           # fp32 keys: their integer form lives in the array too
     _same(ref3, got3, "third call (729 tokens, fp32 keys)")
 
 
