@@ -13,8 +13,9 @@
 //  * a workgroup of WR x WC wavefronts owns a (32*MI*WR) x (32*NJ*WC) output tile, each wavefront MI x NJ
 //    32 x 32 accumulators.  bf16 keys (v_mfma_f32_32x32x16_bf16): 128x128 by 4 wavefronts, two workgroups per CU;
 //    256x256 by 8 wavefronts (half the L2 traffic per flop) where the turns come out better; density pass also
-//    192x192 by 4 wavefronts, where the triangle of one sample is then a single turn of the chip (see gram_cost()).
-//    fp32 keys (v_mfma_i32_32x32x32_i8): 128x128 by 8 wavefronts;
+//    192x192 by 4 wavefronts, where the triangle of one sample is then a single turn of the chip (see gram_cost()); 64x128 (candidate
+//    pass 128x64) by 4 wavefronts where all tiles are one turn.
+//    fp32 keys (v_mfma_i32_32x32x32_i8): the same halves by 4 wavefronts, two workgroups per CU, or 128x128 by 8 wavefronts;
 //  * the key rows stream in slices straight from global memory into a ring of LDS stages
 //    (global_load_lds_dwordx4: no staging registers); waits on the ring are explicit (s_waitcnt
 //    vmcnt + s_barrier).  bf16: 128 bytes of each row (a whole cache line, fetched by eight lanes);
@@ -25,7 +26,7 @@
 //    are read from LDS while the MFMAs of the current one run;
 //  * the grid is persistent (the tile count depends on counts only the device knows) and
 //    XCD-aware: each of the 8 XCDs (own L2) works on its own band of tile columns;
-//  * density pass of a sample that saves turns by it: d_ij = d_ji, so only the tiles on and above the
+//  * density pass of a sample that saves turns by it: d_ij = d_ji, so only the tiles (squares of two halves) on and above the
 //    diagonal are computed, and a tile above it also leaves the row sums, the transposed bits and
 //    the flagged near-d_c pairs of its mirror image (template SYM, mirrored_tiles_pay()).
 //
@@ -106,7 +107,8 @@ template <int DT, int MI_, int NJ_, int WR_, int WC_, int STAGES, bool TURNS> st
     static_assert(NSTAGE >= 2, "the ring needs a slot to fill while another is multiplied");
     static_assert(NB * 1024 * WAVES == STAGE_BYTES, "whole blocks per wavefront");
     static_assert(!I8 || NB % 3 == 0, "16 rows of 192 bytes are three blocks");
-    static_assert((WAVES / 2) * NB * 1024 == TILE_R * SLICE_BYTES || !I8, "half of the wavefronts fetch the row operand");
+    // mirrored tiles: row tiles per column tile
+    static constexpr int RPC = TILE_C % TILE_R == 0 ? TILE_C / TILE_R : 1;
     // ring stages a launch needs: no more than there are slices (two at least: the epilogue uses one)
     static size_t lds_bytes(int slices) {
         if (I8) slices *= 2;                                             // (with the lowest byte they come twice)
@@ -226,10 +228,10 @@ __device__ __forceinline__ void add_density(double* rho, double* rho_lo, double 
     unsafeAtomicAdd(rho, v);
 }
 
-// Density pass with t x t square tiles on g workgroups: do mirrored tiles (upper triangle only,
+// Density pass with t x t squares of rpc tiles each on g workgroups: do mirrored tiles (upper triangle only,
 // longer epilogue) save at least one turn in eight of a workgroup's tile loop?
-__host__ __device__ __forceinline__ bool mirrored_tiles_pay(int t, int g) {
-    const long full = (long)t * t, tri = (long)t * (t + 1) / 2;
+__host__ __device__ __forceinline__ bool mirrored_tiles_pay(int t, int rpc, int g) {
+    const long full = (long)t * t * rpc, tri = (long)t * (t + 1) / 2 * rpc;
     return ((tri + g - 1) / g) * 9 < ((full + g - 1) / g) * 8;
 }
 
@@ -244,7 +246,8 @@ __global__ __launch_bounds__(SH::THREADS, SH::WAVES_PER_SIMD) void gram_kernel(B
     constexpr int ORDERS = LOWEST ? 4 : 3;
     static_assert(MODE == MODE_CAND || NJ == 2 || NJ == 3, "a wavefront's columns are one bitmap word, or three halves");
     static_assert(MODE == MODE_DENSITY || WROWS % 64 == 0, "a wavefront's rows are whole groups of 64 centres");
-    static_assert(!SYM || TILE_R == TILE_C, "mirrored tiles are square");
+    constexpr int RPC = SH::RPC;
+    static_assert(!SYM || TILE_R * RPC == TILE_C, "mirrored tiles are squares, or whole parts of one");
     extern __shared__ uint4 s_ring[];                         // TILE_R floats, then the ring's stages
     // Which sample, which of its workgroups, and how many it has.  Batches: read from the map the
     // host made.  Workgroups are dealt to the 8 XCDs round-robin in launch order (XCD = workgroup
@@ -334,16 +337,16 @@ __global__ __launch_bounds__(SH::THREADS, SH::WAVES_PER_SIMD) void gram_kernel(B
     // when they save at least one turn in eight of the workgroups' tile loop.
     const int xcd = wg & 7;
     const long nFull = (long)tilesR * tilesC;
-    const long nTri = (long)tilesR * (tilesR + 1) / 2;
+    const long nTri = (long)tilesC * (tilesC + 1) / 2 * RPC;              // (squares of TILE_C, each RPC tiles)
     bool sym = false;
-    if constexpr (SYM) sym = mirrored_tiles_pay(tilesR, G);
+    if constexpr (SYM) sym = mirrored_tiles_pay(tilesC, RPC, G);
     const long nTiles = sym ? nTri : nFull;
     const bool banded = !ga.mapped && nTiles >= 8 && (G & 7) == 0;        // (a sample kept on one XCD: one band)
     const bool patch = banded && !sym && (tilesR & 1) == 0 && (tilesC & 3) == 0;   // (patches of equal size only)
     // Many tiles: the operands of 32 tiles of a column (a turn of an XCD's workgroups) do not fit its L2 and came from
     // the last-level cache every turn; in squares of 6 x 6 tiles they are 12 operands instead of 33.
     constexpr int SQ = 6;
-    const bool squares = !patch && tilesR >= 3 * SQ;
+    const bool squares = !patch && (sym ? tilesC : tilesR) >= 3 * SQ;
     const int pr0 = (xcd >> 2) * tilesR / 2, pnr = ((xcd >> 2) + 1) * tilesR / 2 - pr0;   // the XCD's patch
     const int pc0 = (xcd & 3) * tilesC / 4, pnc = ((xcd & 3) + 1) * tilesC / 4 - pc0;
     const int l_lo = patch ? 0 : banded ? (int)(xcd * nTiles / 8) : 0;
@@ -374,6 +377,7 @@ __global__ __launch_bounds__(SH::THREADS, SH::WAVES_PER_SIMD) void gram_kernel(B
         const uint32_t fragA0 = (uint32_t)((wr * WROWS + l32_) * SLICE_BYTES);
         const uint32_t fragB0 = (uint32_t)((TILE_R + wc * WCOLS + l32_) * SLICE_BYTES);
 
+        const int ts = SYM && sym ? tl / RPC : tl;           // (mirrored tiles: the square, then its part)
         int tr = tl % tilesR, tc = tl / tilesR;
         if (patch) {
             tr = pr0 + tl % pnr;
@@ -381,14 +385,14 @@ __global__ __launch_bounds__(SH::THREADS, SH::WAVES_PER_SIMD) void gram_kernel(B
         } else if (squares) {
             // columns in groups of SQ; above the diagonal (or over the full height) squares of SQ x SQ
             // tiles, then (sym) the group's triangle on the diagonal
-            int c = sym ? (int)((sqrtf(8.0f * (float)tl + 1.0f) - 1.0f) * 0.5f) : tl / tilesR;
+            int c = sym ? (int)((sqrtf(8.0f * (float)ts + 1.0f) - 1.0f) * 0.5f) : ts / tilesR;
             if (sym) {
-                while ((c + 1) * (c + 2) / 2 <= tl) ++c;
-                while (c * (c + 1) / 2 > tl) --c;
+                while ((c + 1) * (c + 2) / 2 <= ts) ++c;
+                while (c * (c + 1) / 2 > ts) --c;
             }
             c -= c % SQ;                                     // first column of the group
             const int w = min(SQ, tilesC - c), height = sym ? c : tilesR;
-            int rem = tl - (sym ? c * (c + 1) / 2 : c * tilesR);
+            int rem = ts - (sym ? c * (c + 1) / 2 : c * tilesR);
             if (rem < height * w) {
                 const int sr = rem / (SQ * w) * SQ, sh = min(SQ, height - sr);
                 rem -= sr * w;
@@ -402,22 +406,28 @@ __global__ __launch_bounds__(SH::THREADS, SH::WAVES_PER_SIMD) void gram_kernel(B
                 tc = c + k;
             }
         } else if (sym) {
-            // the tiles above the diagonal, column by column: tile tl is (tr, tc) with tr < tc,
-            // tl = tc (tc - 1) / 2 + tr; then the tiles on the diagonal, whose epilogue is the
+            // the squares above the diagonal, column by column: square ts is (tr, tc) with tr < tc,
+            // ts = tc (tc - 1) / 2 + tr; then those on the diagonal, whose epilogue is the
             // shorter one (the last turn of a workgroup's tile loop is then a short one)
-            const int nOff = tilesR * (tilesR - 1) / 2;
-            if (tl < nOff) {
-                tc = (int)((sqrtf(8.0f * (float)tl + 1.0f) + 1.0f) * 0.5f);
-                while ((tc + 1) * tc / 2 <= tl) ++tc;
-                while (tc * (tc - 1) / 2 > tl) --tc;
-                tr = tl - tc * (tc - 1) / 2;
+            const int nOff = tilesC * (tilesC - 1) / 2;
+            if (ts < nOff) {
+                tc = (int)((sqrtf(8.0f * (float)ts + 1.0f) + 1.0f) * 0.5f);
+                while ((tc + 1) * tc / 2 <= ts) ++tc;
+                while (tc * (tc - 1) / 2 > ts) --tc;
+                tr = ts - tc * (tc - 1) / 2;
             } else {
-                tr = tc = tl - nOff;
+                tr = tc = ts - nOff;
+            }
+        }
+        if constexpr (SYM && RPC > 1) {
+            if (sym) {
+                tr = tr * RPC + (tl - ts * RPC);
+                if (tr >= tilesR) continue;                  // (the last square's lower part has no rows)
             }
         }
         const int rowBase = tr * TILE_R;
         const int colBase = tc * TILE_C;
-        const bool mirror = SYM && sym && tr != tc;  // this tile also stands for tile (tc, tr)
+        const bool mirror = SYM && sym && tr / RPC != tc;    // this tile also stands for its mirror image
 
         // byte offsets of this lane's 16 bytes in the first slice of its NB DMA rows; rows past the
         // end are clamped to the last one (their products are discarded in the epilogue)
@@ -515,6 +525,27 @@ __global__ __launch_bounds__(SH::THREADS, SH::WAVES_PER_SIMD) void gram_kernel(B
                         ord[o - 1][i][j][r] += c;
                     }
         };
+        // one k-group's byte products of the orders wanted
+        auto products = [&](const u32x4_t (&fa)[MI][3], const u32x4_t (&fb)[NJ][3]) __attribute__((always_inline)) {
+#pragma unroll
+            for (int o = 0; o < ORDERS; ++o)
+#pragma unroll
+                for (int pa = o < 3 ? 0 : 1; pa <= o && pa < 3; ++pa)
+#pragma unroll
+                    for (int i = 0; i < MI; ++i)
+#pragma unroll
+                        for (int j = 0; j < NJ; ++j) mfma_i8(fa[i][pa], fb[j][o - pa], ord[o][i][j]);
+        };
+        // (behind the tile's first barrier) whether its rows or columns ask for the lowest byte as well
+        auto lowest_too = [&]() __attribute__((always_inline)) {
+            asm volatile("" ::: "memory");
+            if (__builtin_amdgcn_readfirstlane(*sLow) == tileNo) {
+                nSteps = 2 * nSlices;
+#pragma unroll
+                for (int s = 1; s < AHEAD; ++s)                      // (fewer slices than are kept in flight)
+                    if (s >= nSlices && s < nSteps) issue(s);
+            }
+        };
         // Multiply.  A SIMD holds two of the eight wavefronts, one of either group (wavefronts w and w + 4); the
         // groups take turns, one multiplies while the other fetches its next fragments from the LDS, with a
         // barrier between the turns, so that the matrix cores wait for no LDS read (all wavefronts reading
@@ -538,15 +569,7 @@ __global__ __launch_bounds__(SH::THREADS, SH::WAVES_PER_SIMD) void gram_kernel(B
             wait_slice(0);
             if constexpr (LOWEST) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // (the flag's store)
             turn();
-            if constexpr (LOWEST) {
-                asm volatile("" ::: "memory");
-                if (__builtin_amdgcn_readfirstlane(*sLow) == tileNo) {
-                    nSteps = 2 * nSlices;
-#pragma unroll
-                    for (int s = 1; s < AHEAD; ++s)                      // (fewer slices than are kept in flight)
-                        if (s >= nSlices && s < nSteps) issue(s);
-                }
-            }
+            if constexpr (LOWEST) lowest_too();
             if (second) turn();
             for (int s = 0; s < nSlices; ++s) {
                 const lds_char* st = ring + (s % NSTAGE) * STAGE_BYTES;
@@ -576,14 +599,7 @@ __global__ __launch_bounds__(SH::THREADS, SH::WAVES_PER_SIMD) void gram_kernel(B
 #pragma unroll
                     for (int g = 0; g < HG; ++g) {
                         if constexpr (I8) {
-#pragma unroll
-                            for (int o = 0; o < ORDERS; ++o)
-#pragma unroll
-                                for (int pa = o < 3 ? 0 : 1; pa <= o && pa < 3; ++pa)
-#pragma unroll
-                                    for (int i = 0; i < MI; ++i)
-#pragma unroll
-                                        for (int j = 0; j < NJ; ++j) mfma_i8(fa[g][i][pa], fb[g][j][o - pa], ord[o][i][j]);
+                            products(fa[g], fb[g]);
                         } else {
 #pragma unroll
                             for (int i = 0; i < MI; ++i)
@@ -597,32 +613,29 @@ __global__ __launch_bounds__(SH::THREADS, SH::WAVES_PER_SIMD) void gram_kernel(B
                 }
             }
             if (!second) turn();
-            if constexpr (LOWEST) {
-                if (nSteps > nSlices) carry(3);
-#pragma unroll 1
-                for (int s = nSlices; s < nSteps; ++s) {
-                    const lds_char* st = arrive(s);
-                    if (s + AHEAD < nSteps) issue(s + AHEAD);
+        } else if constexpr (I8) {
+            // two workgroups share a CU, each SIMD holds a wavefront of either: one's LDS reads, fetches, conversions and
+            // epilogue run beside the other's products
+            if constexpr (LOWEST) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // (the flag's store, ahead of the first barrier)
+            for (int s = 0; s < nSlices; ++s) {
+                if ((s & 511) == 511) { if constexpr (LOWEST) carry(3); carry(2); carry(1); }     // (as above)
+                const lds_char* st = arrive(s);
+                if constexpr (LOWEST) { if (s == 0) lowest_too(); }
+                u32x4_t fa[2][MI][3], fb[2][NJ][3];
 #pragma unroll
-                    for (int ks = 0; ks < 2; ++ks) {
-                        const uint32_t co = (uint32_t)(((2 * ks + hh_) ^ swz) << 4);
-                        u32x4_t fa[MI][2], fb[NJ][2];
+                for (int g = 0; g < 2; ++g) {
+                    const uint32_t co = (uint32_t)(((2 * g + hh_) ^ swz) << 4);
 #pragma unroll
-                        for (int pl = 0; pl < 2; ++pl) {
+                    for (int pl = 0; pl < 3; ++pl) {
 #pragma unroll
-                            for (int i = 0; i < MI; ++i) fa[i][pl] = *(const lds_u32x4*)(st + fragA0 + i * 32 * SLICE_BYTES + pl * 64 + co);
+                        for (int i = 0; i < MI; ++i) fa[g][i][pl] = *(const lds_u32x4*)(st + fragA0 + i * 32 * SLICE_BYTES + pl * 64 + co);
 #pragma unroll
-                            for (int j = 0; j < NJ; ++j) fb[j][pl] = *(const lds_u32x4*)(st + fragB0 + j * 32 * SLICE_BYTES + pl * 64 + co);
-                        }
-#pragma unroll
-                        for (int pl = 0; pl < 2; ++pl)
-#pragma unroll
-                            for (int i = 0; i < MI; ++i)
-#pragma unroll
-                                for (int j = 0; j < NJ; ++j) mfma_i8(fa[i][pl], fb[j][1 - pl], ord[3][i][j]);
+                        for (int j = 0; j < NJ; ++j) fb[g][j][pl] = *(const lds_u32x4*)(st + fragB0 + j * 32 * SLICE_BYTES + pl * 64 + co);
                     }
-                    if (((s - nSlices) & 511) == 511) carry(3);
+                    if (g == 0 && s + AHEAD < nSteps) issue(s + AHEAD);
                 }
+#pragma unroll
+                for (int g = 0; g < 2; ++g) products(fa[g], fb[g]);
             }
         } else {
             for (int s = 0; s < nSteps; ++s) {
@@ -662,6 +675,33 @@ __global__ __launch_bounds__(SH::THREADS, SH::WAVES_PER_SIMD) void gram_kernel(B
                         __builtin_amdgcn_sched_group_barrier(0x008, NJ * MI, 0);
                     }
                 }
+            }
+        }
+        if constexpr (LOWEST) {
+            if (nSteps > nSlices) carry(3);
+#pragma unroll 1
+            for (int s = nSlices; s < nSteps; ++s) {
+                const lds_char* st = arrive(s);
+                if (s + AHEAD < nSteps) issue(s + AHEAD);
+#pragma unroll
+                for (int ks = 0; ks < 2; ++ks) {
+                    const uint32_t co = (uint32_t)(((2 * ks + hh_) ^ swz) << 4);
+                    u32x4_t fa[MI][2], fb[NJ][2];
+#pragma unroll
+                    for (int pl = 0; pl < 2; ++pl) {
+#pragma unroll
+                        for (int i = 0; i < MI; ++i) fa[i][pl] = *(const lds_u32x4*)(st + fragA0 + i * 32 * SLICE_BYTES + pl * 64 + co);
+#pragma unroll
+                        for (int j = 0; j < NJ; ++j) fb[j][pl] = *(const lds_u32x4*)(st + fragB0 + j * 32 * SLICE_BYTES + pl * 64 + co);
+                    }
+#pragma unroll
+                    for (int pl = 0; pl < 2; ++pl)
+#pragma unroll
+                        for (int i = 0; i < MI; ++i)
+#pragma unroll
+                            for (int j = 0; j < NJ; ++j) mfma_i8(fa[i][pl], fb[j][1 - pl], ord[3][i][j]);
+                }
+                if (((s - nSlices) & 511) == 511) carry(3);
             }
         }
         if constexpr (I8) {
@@ -1034,7 +1074,7 @@ static long kept_estimate(const Seg& sg) { return sg.n - prune_rank(sg.lambda, s
 static long tiles_estimate(const Seg& sg, bool density, int tile_r, int tile_c, bool mirrored) {
     const long q = kept_estimate(sg), rows = density ? q : (q + 1) / 2, cols = density ? q : sg.n - q;
     const long tr = (rows + tile_r - 1) / tile_r, tc = (cols + tile_c - 1) / tile_c;
-    const long t = density && mirrored ? tr * (tr + 1) / 2 : tr * tc;
+    const long t = density && mirrored ? tc * (tc + 1) / 2 * (tile_c / tile_r) : tr * tc;
     return t < 1 ? 1 : t;
 }
 
@@ -1080,6 +1120,17 @@ static int launch_gram_shape(const Batch& bt, const GramArgs& ga_in, hipStream_t
 //   width 128    2000: 15 / 16 / 10, 4010: 17 / 17 / 18, 6000: 29 / 33 / 23, 8192: 37 / 41 / 33
 // gram_cost()'s choice is the fastest of the three within 1 us but where the triangle of 128s nearly fills its second turn (5000 to 5632
 // tokens, 2 x 3450, 16 x 1000 and the like): it then takes 128 and is 2 to 4 us off.
+// 64 x 128 (candidate pass 128 x 64), four wavefronts of one row (column) block: a small sample is twice as many workgroups, and a
+// wavefront's epilogue, which nothing overlaps there, is half as long.  Density / candidate pass, brackets in us, 128s -> halves, images at
+// lambda = 0.45, width 512: 729 tokens 13.1 / 11.8 -> 11.2 / 10.4, 1458: 14.2 / 12.7 -> 13.3 / 10.9, 4374: 18.7 / 13.0 -> 16.9 / 11.8;
+// width 128: 196: 10.1 / 8.2 -> 8.7 / 7.1, 5103: 12.5 / 9.4 -> 12.0 / 8.5, 16 x 729: 13.2 / 9.7 -> 11.8 / 8.4.  More than one turn
+// of them is never better (5832: 19.4 / 14.3 -> 25.2 / 17.7), nor, at width 512, a full square of 257 to 512 (2915: 15.8 -> 16.2).
+// fp32 keys: the halves are two workgroups of four wavefronts per CU instead of one of eight that takes turns at the matrix cores; what
+// each SIMD holds is the same.  Density pass, whole tiles -> halves: width 512, 729 tokens 18.7 -> 15.7, 2915: 22.6 -> 23.0, 5832: 39.6 -> 33.9,
+// 7290: 54.1 -> 46.7, 12000: 103.7 -> 97.1, 16384 at lambda = 0.45: 172.6 -> 175.7, at lambda = 0: 493 -> 515, 32 x 729: 48.0 -> 45.7;
+// width 128, 729: 13.7 -> 11.6, 7290: 35.1 -> 30.3.  Large samples are bound by the power of the matrix cores and of what feeds them
+// (a slice is then at 54% of the dense peak, as are the largest bf16 products of the libraries): there the halves' 1.5 times the fetches from the L2
+// cost more than the overlapped epilogue gives, and a sample of eight turns of whole tiles and more takes those.
 // bf16 tiles of 256 take turns at the matrix cores from key rows of 2 KB on: the loop over a row of 7 KB got 5%
 // shorter, over one of 1 KB the two turns' offset cost 0.8 us.  (Both are then near what the chip's
 // power allows: a slice of random keys takes 1.45 us, of keys that are mostly zeros 1.10 us, its MFMAs alone 1.02 us.)
@@ -1087,30 +1138,40 @@ typedef Shape<PACT_BF16, 4, 2, 2, 4, 2, false> Tile256;
 typedef Shape<PACT_BF16, 4, 2, 2, 4, 2, true> Tile256Wide;
 typedef Shape<PACT_BF16, 2, 2, 2, 2, 2, false> Tile128;
 typedef Shape<PACT_BF16, 3, 3, 2, 2, 3, false> Tile192;        // density pass
+typedef Shape<PACT_BF16, 1, 2, 2, 2, 2, false> Tile64;         // density pass: 64 x 128
+typedef Shape<PACT_BF16, 2, 1, 2, 2, 2, false> Tile64Cand;     // candidate pass: 128 x 64 (groups of 64 rows)
 typedef Shape<PACT_I8X4, 1, 2, 4, 2, 3, true> TileI8;         // density pass
-typedef Shape<PACT_I8X4, 2, 1, 2, 4, 3, true> TileI8Cand;     // candidate pass (groups of 64 rows)
+typedef Shape<PACT_I8X4, 2, 1, 2, 4, 3, true> TileI8Cand;     // candidate pass
+typedef Shape<PACT_I8X4, 1, 2, 2, 2, 2, false> TileI8Half;     // density pass: 64 x 128
+typedef Shape<PACT_I8X4, 2, 1, 2, 2, 2, false> TileI8CandHalf; // candidate pass: 128 x 64
 constexpr int WIDE_KEYS = 1024;
 
 static double gram_cost(const Batch& bt, bool density, int tile, int dk, bool mirrored) {
-    const int slots = tile == 128 ? 512 : 256;
+    const int slots = tile <= 128 ? 512 : 256;
+    const int tile_r = tile == 64 && !density ? 128 : tile, tile_c = tile == 64 && density ? 128 : tile;
     long tiles[PACT_MAX_BATCH], all = 0;
-    for (int b = 0; b < bt.B; ++b) all += tiles[b] = tiles_estimate(bt.s[b], density, tile, tile, mirrored);
+    for (int b = 0; b < bt.B; ++b) all += tiles[b] = tiles_estimate(bt.s[b], density, tile_r, tile_c, mirrored);
     const double slices = (dk + 63) / 64;
     const long turns = fewest_turns(bt.B, tiles, slots);
+    if (tile == 64) {
+        if (turns > 1) return 1e9;
+        if (!density) return 4.9 + 0.5 * slices;
+        return all <= 256 ? 4.7 + 0.6 * slices : 4.9 + 0.85 * slices;
+    }
     if (!density) {
         if (tile == 256) return turns * (8.0 + 1.5 * slices);
         return all <= 256 ? 6.5 + 0.5 * slices : 3.0 + turns * (5.0 + 0.8 * slices);
     }
     if (tile == 256) return 2.5 + turns * (mirrored ? 12.2 + 1.25 * slices : 8.0 + 1.55 * slices);
     if (tile == 192) return 2.8 + turns * (10.8 + 0.9 * slices);
-    return all <= 256 ? 6.2 + 0.6 * slices : turns == 1 ? 9.0 + 0.7 * slices : 0.8 + turns * (5.4 + 0.73 * slices);
+    return all <= 256 ? 6.2 + 0.6 * slices + (mirrored && bt.B == 1 ? 2.0 : 0.0) : turns == 1 ? 9.0 + 0.7 * slices : 0.8 + turns * (5.4 + 0.73 * slices);
 }
 
 template <class SH, int MODE>
 static int launch_gram(const Batch& bt, const GramArgs& ga, hipStream_t st, const char* name, bool mirrored, bool want_stat,
                        int* stat_words) {
     if constexpr (MODE == MODE_DENSITY) {
-        if constexpr (SH::TILE_R == SH::TILE_C) {
+        if constexpr (SH::TILE_R * SH::RPC == SH::TILE_C) {
             if (mirrored) return want_stat ? launch_gram_shape<SH, MODE, true, true>(bt, ga, st, name, stat_words)
                                            : launch_gram_shape<SH, MODE, false, true>(bt, ga, st, name, stat_words);
         }
@@ -1144,17 +1205,27 @@ int launch_gram_density(const Batch& bt, const Ws& w, const void* keys, pact_dty
     // (n - floor(lambda n), more on ties) tells whether mirrored tiles are likely to pay for
     // some sample.  The kernel decides again from the real count, so a wrong guess costs time only.
     // (In a batch every sample has its own number of workgroups: the build that can mirror is used there.)
-    auto mirrored = [&](int tile, int slots) {
+    auto mirrored = [&](int tile, int rpc, int slots) {
         const long t = (bt.n_max + tile - 1) / tile;
         bool m = bt.B > 1;
         for (int b = 0; b < bt.B; ++b)
-            m = m || mirrored_tiles_pay((int)((kept_estimate(bt.s[b]) + tile - 1) / tile), gram_grid_x(t * t, slots));
+            m = m || mirrored_tiles_pay((int)((kept_estimate(bt.s[b]) + tile - 1) / tile), rpc, gram_grid_x(t * t * rpc, slots));
         return m;
     };
-    if (k_dt == PACT_F32)
-        return launch_gram<TileI8, MODE_DENSITY>(bt, ga, st, name, mirrored(128, TileI8::SLOTS), want_stat, stat_words);
-    const bool m256 = mirrored(256, Tile256::SLOTS), m192 = mirrored(192, Tile192::SLOTS), m128 = mirrored(128, Tile128::SLOTS);
+    if (k_dt == PACT_F32) {
+        // whole tiles from eight turns of the chip on (see there)
+        const bool m = mirrored(128, 1, TileI8::SLOTS);
+        long tiles = 0;
+        for (int b = 0; b < bt.B; ++b) tiles += tiles_estimate(bt.s[b], true, 128, 128, m);
+        if (tiles > 8 * TileI8::SLOTS) return launch_gram<TileI8, MODE_DENSITY>(bt, ga, st, name, m, want_stat, stat_words);
+        return launch_gram<TileI8Half, MODE_DENSITY>(bt, ga, st, name, mirrored(128, 2, TileI8Half::SLOTS), want_stat, stat_words);
+    }
+    const bool m256 = mirrored(256, 1, Tile256::SLOTS), m192 = mirrored(192, 1, Tile192::SLOTS), m128 = mirrored(128, 1, Tile128::SLOTS);
+    const bool m64 = mirrored(128, 2, Tile64::SLOTS);
     const double c256 = gram_cost(bt, true, 256, dk, m256), c192 = gram_cost(bt, true, 192, dk, m192), c128 = gram_cost(bt, true, 128, dk, m128);
+    const double c64 = gram_cost(bt, true, 64, dk, m64);
+    if (c64 < c128 && c64 < c192 && c64 < c256)
+        return launch_gram<Tile64, MODE_DENSITY>(bt, ga, st, name, m64, want_stat, stat_words);
     if (c192 < c128 && c192 < c256)
         return launch_gram<Tile192, MODE_DENSITY>(bt, ga, st, name, m192, want_stat, stat_words);
     if (c128 < c256)
@@ -1170,7 +1241,23 @@ int launch_gram_candidates(const Batch& bt, const Ws& w, const void* keys, pact_
     if (const int rc = gram_args(ga, bt, w, keys, k_dt, dk, center_idx, pruned_idx, rep)) return rc;
     ga.cbest = w.cbest;
     const char* name = "gram_candidates";
-    if (k_dt == PACT_F32) return launch_gram<TileI8Cand, MODE_CAND>(bt, ga, st, name, false, false, nullptr);
+    if (k_dt == PACT_F32) {
+        // event brackets less what all launches have: a + turns x (b + c slices) of either (512 wide 11 to 13.5 / 16.7 us where the
+        // halves are at most 256 / 512, whole tiles 13.5 to 15.8; two turns of whole tiles 27 to 29, of halves 25 to 30; 128 wide
+        // halves 8.0 to 8.8, 10, 15, whole tiles 9.2 to 10.5, 16)
+        long whole[PACT_MAX_BATCH], half[PACT_MAX_BATCH], all = 0;
+        for (int b = 0; b < bt.B; ++b) {
+            whole[b] = tiles_estimate(bt.s[b], false, 128, 128, false);
+            all += half[b] = tiles_estimate(bt.s[b], false, 128, 64, false);
+        }
+        const double slices = (dk + 63) / 64;
+        const double cw = 4.7 + fewest_turns(bt.B, whole, TileI8Cand::SLOTS) * (3.6 + 0.95 * slices);
+        const double ch = all <= 256 ? 6.5 + 0.75 * slices : 5.0 + fewest_turns(bt.B, half, TileI8CandHalf::SLOTS) * (2.0 + 1.4 * slices);
+        if (ch < cw) return launch_gram<TileI8CandHalf, MODE_CAND>(bt, ga, st, name, false, false, nullptr);
+        return launch_gram<TileI8Cand, MODE_CAND>(bt, ga, st, name, false, false, nullptr);
+    }
+    if (gram_cost(bt, false, 64, dk, false) < gram_cost(bt, false, 128, dk, false))
+        return launch_gram<Tile64Cand, MODE_CAND>(bt, ga, st, name, false, false, nullptr);
     if (gram_cost(bt, false, 128, dk, false) < gram_cost(bt, false, 256, dk, false))
         return launch_gram<Tile128, MODE_CAND>(bt, ga, st, name, false, false, nullptr);
     if (dk >= WIDE_KEYS) return launch_gram<Tile256Wide, MODE_CAND>(bt, ga, st, name, false, false, nullptr);

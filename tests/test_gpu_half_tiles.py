@@ -1,0 +1,45 @@
+"""The matrix passes in tiles of 64 x 128 (candidates: 128 x 64), at the edges of such tiles: single samples around one, two and
+several of them, mirrored and not, key rows of less than one slice to several, fp32 keys with and without the lowest byte's sweep."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2504_08966_amd as P
+from oracle import pact_oracle as po
+from tests import gpu_util as gu
+from tests.test_gpu_parity import _gap_dc, _random_sample, assert_same, oracle_reduce
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("n,dk", [(2, 64), (63, 8), (64, 64), (65, 128), (127, 72), (128, 512), (129, 64), (191, 128), (192, 520), (193, 64),
+                                  (255, 128), (257, 512), (449, 64), (1025, 128), (2369, 64)])
+def test_clustering_around_the_tiles_edges(n, dk, dtype):
+    # 2369 tokens: 38 x 19 tiles, more than 512: mirrored, the last square has no lower part
+    s = _random_sample(7000 + n, n, 1, 1, dk, 64, 0.0, dtype)
+    U = s.keys.reshape(n, -1).astype(np.float64)
+    if dtype == "f32" and n % 2:                         # rows dominated by one element: the sweep with the lowest byte
+        U[:: 9, dk // 2] *= 64.0
+        U = U.astype(np.float32).astype(np.float64)
+    d_c = _gap_dc(U, frac=0.02 if n < 1000 else 0.002) if n > 2 else 0.3
+    out = P.dbdpc_cluster(gu.dev(U, dtype), d_c, 2.0, want_rho=True)
+    torch.cuda.synchronize()
+    rep = P.read_report(out["rep"])
+    ref = po.dbdpc(U, float(np.float32(d_c)), 2.0)
+    # (a term's exponent of up to 1.45 is rounded to 2^-24, the cosine is within (dk + 16) 2^-23 at worst)
+    np.testing.assert_allclose(out["rho"].cpu().numpy(), ref["rho"], rtol=1e-7 + (dk + 16) * 2.0 ** -26, atol=0)
+    assert np.array_equal(out["center_idx"][: rep["n_centers"]].cpu().numpy(), ref["centers"])
+    assert np.array_equal(out["cluster_id"].cpu().numpy(), ref["labels"])
+    assert abs(rep["max_key_distance"] - po.max_pairwise_distance(U)) <= (dk + 16) / 2.0 ** 23 + 3e-6
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("n,lam,d_h", [(9, 0.9, 64), (130, 0.5, 64), (257, 0.5, 512), (640, 0.3, 72), (1500, 0.45, 128), (3000, 0.9, 64)])
+def test_reduction_around_the_tiles_edges(n, lam, d_h, dtype):
+    s = _random_sample(7100 + n, n, 1, 1, d_h, 64, lam, dtype)
+    d_c = _gap_dc(s.keys.reshape(n, -1), frac=0.02 if n < 1000 else 0.002) if n > 9 else 0.3
+    hid, ks, qs = (gu.dev(x.reshape(n, -1), dtype) for x in (s.hidden, s.keys, s.queries))
+    o = P.pact_reduce(hid, ks, ks, qs, 1, d_h, 1, P.PactParams(lam, d_c, 2.0, 1.5))
+    torch.cuda.synchronize()
+    assert_same(gu.trim(o, n), oracle_reduce(s, d_c), s, f"n={n} d_h={d_h} {dtype}")
