@@ -527,7 +527,7 @@ struct CentresArgs {
     const uint64_t* adj;
     double* rho; double* rho_opt;
     uint16_t* preds; uint2* heads;
-    const int32_t* tie_list; int32_t* tie_cnt;
+    int32_t* tie_list; int32_t* tie_cnt;
     double* rho_fix;
     uint32_t* status; int32_t* cnum; uint64_t* cmask; int32_t* center_idx;
     int32_t write_rho;                   // whether `rho` itself has to end with the fp64 densities
@@ -1111,6 +1111,395 @@ __global__ __launch_bounds__(1024) void centres_kernel(Batch bt, CentresArgs a) 
 }
 
 // ------------------------------------------------------------------------------------------
+// Samples of at most SMALL_TOKENS: settling, order and selection in one launch.  One workgroup per sample, the sample's bitmap in LDS
+// (1024 tokens: 139 KB, rows an odd number of words apart):
+//  1. the undecided pairs are evaluated as settle_kernel does it, by groups of lanes that hold a row in one 16-byte chunk each where it has
+//     at most 64; bits are cleared in LDS, and in memory, where the assignment reads them;
+//  2. one to eight threads per kept token go through the set bits of its row, 32 at a time, and leave those of preceding neighbours.
+//     Densities are compared in fp32 where that decides, near-ties are listed;
+//  3. a thread per token, every wavefront looks at its undecided tokens until none is left.  Its 64 tokens are one word of the masks of
+//     centres and of undecided tokens, so it alone writes that word, centres ahead of undecided; whoever reads the other
+//     way round never misses a centre.  Two words of predecessors are in registers.
+// Listed tokens (a tenth of the samples have two; all where tokens are copies of each other): their fp64 densities are work items that the
+// launch's other workgroups wait for and take by ticket, and so does the sample's own workgroup once its selection is
+// through: a worker's wait is bounded, and without workers the items are done all the same.  What follows from them is
+// as in centres_kernel.
+// tie_cnt[4b + 1]: work items done; [4b + 2]: as in centres_kernel; [4b + 3]: tickets taken | listed tokens << 16 | READY.
+constexpr int SMALL_TOKENS = 1024, SMALL_READY = 1 << 30, SMALL_POLLS = 1 << 12;
+struct SmallArgs {
+    const uint32_t* near_list; const int32_t* near_cnt;
+    const uint32_t* far_bits; int32_t far_words;
+    const double* rho_lo;
+};
+static size_t small_lds(int W) { return (size_t)W * 64 * (((W | 1) + 1) * sizeof(uint64_t) + sizeof(float)); }
+
+typedef __attribute__((address_space(3))) uint64_t lds_u64;
+typedef __attribute__((address_space(3))) volatile uint64_t lds_vu64;
+typedef __attribute__((address_space(3))) uint32_t lds_u32;
+typedef __attribute__((address_space(3))) double lds_f64;
+struct SmallShared {
+    uint64_t centre[16], open[16], odd[16];  // masks of centres, of undecided tokens, of tokens with a near-tie
+    uint32_t far[16];
+    int looks, near_ties, got;
+    int flag[2];
+    uint16_t tok[SMALL_TOKENS];
+};
+
+// The selection of sample b.  first: with the settling and the list of near-ties; otherwise on the bitmap and the densities as they
+// are by now.  Returns the number of listed tokens (first).
+template <int DT>
+__device__ __forceinline__ int select_sample(const Batch& bt, const CentresArgs& a, const SmallArgs& sa, int b, bool first,
+                                             unsigned char* s_raw, SmallShared& sh) {
+    const Seg sg = bt.s[b];
+    const int tid = fresh_v(threadIdx.x), lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int W = bt.W, pitch = W | 1;
+    lds_u64* s_row = (lds_u64*)s_raw;                            // [64 W][pitch]
+    lds_f64* s_rho = (lds_f64*)(s_row + (size_t)W * 64 * pitch); // [64 W]
+    lds_f32* s_rho32 = (lds_f32*)(s_rho + (size_t)W * 64);       // [64 W]
+    pact_report* rep = a.rep + b;
+    uint64_t* adj = (uint64_t*)a.adj + (size_t)b * bt.n_max * W;
+    double* rho = a.rho + (size_t)b * bt.n_max;
+    const int32_t* ix = a.idx + sg.base;
+    const double* nnb = a.nn + sg.base;
+    constexpr int U = 2;                                         // pairs in flight per group of lanes
+    const int nchunk = a.dk * Elem<DT>::BYTES / 16;
+    const int lpp = nchunk <= 16 ? 16 : nchunk <= 32 ? 32 : 64, ng = 1024 / lpp, g = tid / lpp, gl = tid & (lpp - 1);
+    const uint2* pairs = (const uint2*)(sa.near_list + (size_t)b * NEAR_CAP * 2);
+    // ---- everything whose address depends on the thread's position only goes out before the first count is read
+    const int pc = min(tid, sg.n - 1), r0 = tid >> 4, w0 = tid & 15;
+    const int tok = ix[pc];
+    double r = rho[pc];
+    const bool split = first && sg.d_n < EXACT_SUMS_D_N;         // densities that came in two parts (add_density)
+    const double r_lo = split ? sa.rho_lo[(size_t)b * bt.n_max + pc] : 0.0;
+    uint64_t word[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) word[k] = r0 + 64 * k < sg.n && w0 < W ? adj[(size_t)(r0 + 64 * k) * W + w0] : 0ull;
+    uint2 pr[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) pr[u] = first ? pairs[u * ng + g] : make_uint2(0, 0);      // (garbage beyond the count, never used)
+    const uint32_t raw = first ? (uint32_t)sa.near_cnt[2 * b] : 0u;
+    const int checked = first ? sa.near_cnt[2 * b + 1] : 0;
+    const int q = clamp_count(rep->n_kept, sg.n), Wq = (q + 63) >> 6;
+    const int cnt = (int)min(raw, (uint32_t)NEAR_CAP);
+    if (first && sa.far_words > 0) {
+        uint32_t fb = 0u;                                        // (see settle_kernel)
+        for (int k = tid; k < sa.far_words; k += 1024) fb = max(fb, sa.far_bits[(size_t)b * sa.far_words + k]);
+#pragma unroll
+        for (int sft = 32; sft >= 1; sft >>= 1) fb = max(fb, (uint32_t)__shfl_xor((int)fb, sft, 64));
+        if (lane == 0) sh.far[wave] = fb;
+    }
+    if (split) {
+        r += r_lo;
+        if (tid < q) rho[tid] = r;
+    }
+    __syncthreads();                                             // (again: the LDS of before is free)
+    if (tid == 0) { sh.looks = 0; sh.near_ties = 0; }
+    if (tid < 16) sh.odd[tid] = 0ull;
+    sh.tok[tid] = (uint16_t)tok;
+    if (tid < 64 * W) { s_rho[tid] = r; s_rho32[tid] = (float)r; }
+    const uint64_t last = q & 63 ? (1ull << (q & 63)) - 1ull : ~0ull;
+    auto put = [&](int k0) __attribute__((always_inline)) {
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const int row = r0 + 64 * (k0 + k);
+            if (row < q && w0 < Wq) s_row[row * pitch + w0] = w0 == Wq - 1 ? word[k] & last : word[k];
+        }
+    };
+    put(0);
+    if (q > 512) {
+#pragma unroll
+        for (int k = 0; k < 8; ++k) word[k] = r0 + 64 * (k + 8) < q && w0 < W ? adj[(size_t)(r0 + 64 * (k + 8)) * W + w0] : 0ull;
+        put(8);
+    }
+    __syncthreads();
+    // ---- 1. the pairs that fp32 could not decide (the order of operations of wave_dot64)
+    if (cnt > 0) {
+        constexpr int EPL = Elem<DT>::EPL;
+        const char* kb = a.keys + (size_t)sg.base * ((size_t)nchunk * 16);
+        const double d_c = (double)sg.d_c;
+        auto clear = [&](int i, int j) __attribute__((always_inline)) {
+            __hip_atomic_fetch_and((lds_u32*)(s_row + i * pitch) + (j >> 5), ~(1u << (j & 31)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            atomicAnd((unsigned long long*)&adj[(size_t)i * W + (j >> 6)], ~(1ull << (j & 63)));
+        };
+#pragma unroll 1
+        for (int e0 = 0; e0 < cnt; e0 += ng * U) {               // (uniform)
+            const char *ri[U], *rj[U];
+            double acc[U], ni[U], nj[U];
+            const bool two = e0 + ng < cnt;                      // (uniform) whether any group has a second pair
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int e = e0 + u * ng + g;
+                if (e0 > 0) pr[u] = pairs[min(e, cnt - 1)];
+                if (e >= cnt) pr[u] = make_uint2(0, 0);
+                const int ti = sh.tok[min((int)(pr[u].x & ~NEAR_MIRROR), q - 1)], tj = sh.tok[min((int)pr[u].y, q - 1)];
+                ri[u] = kb + (size_t)ti * nchunk * 16;
+                rj[u] = kb + (size_t)tj * nchunk * 16;
+                ni[u] = nnb[ti];
+                nj[u] = nnb[tj];
+                acc[u] = 0.0;
+            }
+#pragma unroll 1
+            for (int c0 = 0; c0 < nchunk; c0 += lpp) {           // (uniform)
+                uint4 va[U], vb[U];
+                const size_t o = (size_t)min(c0 + gl, nchunk - 1) * 16;
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    if (u > 0 && !two) break;
+                    va[u] = *(const uint4*)(ri[u] + o);
+                    vb[u] = *(const uint4*)(rj[u] + o);
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    if (u > 0 && !two) break;
+                    if (c0 + gl < nchunk) {
+                        double x[8], y[8];
+                        Elem<DT>::widen(va[u], x);
+                        Elem<DT>::widen(vb[u], y);
+#pragma unroll
+                        for (int i = 0; i < EPL; ++i) acc[u] = fma(x[i], y[i], acc[u]);
+                    }
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (u > 0 && !two) break;
+                const int pi = (int)(pr[u].x & ~NEAR_MIRROR), pj = (int)pr[u].y;
+                const bool both = (pr[u].x & NEAR_MIRROR) != 0;
+                const double dot = group_sum_f64(acc[u], lpp);
+                const double d = pi != pj ? cos_dist64(dot, ni[u], nj[u]) : 0.0;
+                if (gl == 0 && e0 + u * ng + g < cnt && pi < q && pj < q) {
+                    if (d > d_c) {
+                        clear(pi, pj);
+                        if (both) clear(pj, pi);
+                    }
+                    if (fabs(d - d_c) <= 1e-6) atomicAdd(&sh.near_ties, both ? 2 : 1);
+                }
+            }
+        }
+        __syncthreads();
+    }
+    // ---- 2. the bits of preceding neighbours, in the place of the row's.  GL threads per token, every GL-th half word each
+    {
+        const int gsh = q <= 128 ? 3 : q <= 256 ? 2 : q <= 512 ? 1 : 0;
+        const int p = tid >> gsh;
+        if (p < q) {
+            lds_u32* half = (lds_u32*)(s_row + p * pitch);
+            const float fp = s_rho32[p];
+            // a difference of the fp32 densities beyond `far` is one of the fp64 ones, and beyond the band c sqrt(rj) of the larger
+            // density rj (inside it sqrt(rj) <= sqrt(rp) + c); the roundings to fp32 are 2^-23 of the larger density
+            const float c = 0x1p-20f * (1.0f + 4.0f * 1.4426950f / sg.d_n), w = c * __builtin_amdgcn_sqrtf(fp) + c * c;
+            const float far = 1.001f * (w + 0x1p-21f * (fp + w));
+            bool odd = false;
+#pragma unroll 1
+            for (int h = tid & ((1 << gsh) - 1); h < 2 * Wq; h += 1 << gsh) {
+                const uint32_t has = half[h], others = h == p >> 5 ? has & ~(1u << (p & 31)) : has;
+                uint32_t pre = 0u;
+                bool near = false;
+#pragma unroll 1
+                for (uint32_t bits = others; bits; bits &= bits - 1) {
+                    const int k = __builtin_ctz(bits);
+                    const float d = s_rho32[32 * h + k] - fp;
+                    pre |= (d > far ? 1u : 0u) << k;
+                    near |= !(fabsf(d) > far);
+                }
+                if (near) {                                      // again, in fp64
+                    const double rp = s_rho[p], band2 = recheck_band2(sg.d_n);
+                    pre = 0u;
+#pragma unroll 1
+                    for (uint32_t bits = others; bits; bits &= bits - 1) {
+                        const int k = __builtin_ctz(bits), j = 32 * h + k;
+                        const double x = s_rho[j], d = x - rp;
+                        pre |= (precedes(x, j, rp, p) ? 1u : 0u) << k;
+                        odd |= d * d <= band2 * fmax(x, rp);
+                    }
+                }
+                if (has) half[h] = pre;
+            }
+            if (first && odd) atomicOr((unsigned long long*)&sh.odd[p >> 6], 1ull << (p & 63));
+        }
+    }
+    __syncthreads();
+    const bool on = tid < q;
+    int listed = 0;
+    if (first) {
+        if (on && a.rho_opt) a.rho_opt[sg.base + tid] = r;
+        const int pop = lane < 16 ? __popcll(sh.odd[lane]) : 0, inc = wave_scan_incl_i32(pop);
+        listed = __builtin_amdgcn_readlane(inc, 15);
+        const int at = __builtin_amdgcn_readlane(inc - pop, wave);           // (ahead of the branch: all lanes have to take part)
+        if (listed) {
+            static_assert(SMALL_TOKENS <= RHO_RECHECK_MAX && PACT_MAX_TOKENS <= 32768, "all may be listed; two 15-bit numbers per entry");
+            const uint64_t odd = sh.odd[wave];
+            if ((odd >> lane) & 1ull)
+                a.tie_list[(size_t)b * RHO_RECHECK_MAX + at + lanes_below(odd, lane)] = tid | (tok << 16);
+            // (the list, the bits and the densities are to be where the workers look for them)
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __syncthreads();
+        }
+        if (tid == 1023) {                                       // (of the wavefront that has a selection of its own least often)
+            __hip_atomic_fetch_add(&a.tie_cnt[4 * b + 3], SMALL_READY | (listed << 16), __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+            // (a listed pair that stands for both orders counts twice)
+            rep->dc_checked_pairs = raw > (uint32_t)NEAR_CAP ? cnt : checked;
+            rep->refine_overflow = raw > (uint32_t)NEAR_CAP ? OVERFLOW_NEAR_LIST : 0;
+            rep->dc_near_ties = sh.near_ties;
+            uint32_t fb = 0u;
+            if (sa.far_words > 0)
+                for (int k = 0; k < 16; ++k) fb = max(fb, sh.far[k]);
+            rep->max_key_distance = fb ? fminf(-__uint_as_float(fb) * sg.d_n * 0.6931471805599453f, 2.0f) : 0.0f;
+        }
+    }
+    // ---- 3. the selection.  Two words of predecessors in registers, others from LDS
+    const lds_u64* mine = s_row + tid * pitch;
+    uint32_t left = 0u;
+    if (on) {
+#pragma unroll 4
+        for (int w = 0; w < Wq; ++w) left |= (mine[w] != 0ull ? 1u : 0u) << w;
+    }
+    uint64_t m[2];
+    int wn[2];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        wn[k] = left ? __builtin_ctz(left) : 0;
+        m[k] = left ? mine[wn[k]] : 0ull;
+        left &= left - 1 + (left == 0u);
+    }
+    lds_vu64* s_centre = (lds_vu64*)sh.centre;
+    lds_vu64* s_open = (lds_vu64*)sh.open;
+    uint64_t open = __ballot(on), centre = 0ull;
+    if (lane == 0) { s_open[wave] = open; s_centre[wave] = 0ull; }
+    __syncthreads();
+    bool todo = on;
+    int looks = 0;
+    while (open) {                                               // (the same in all lanes)
+        ++looks;
+        bool blocked = false, pending = false;
+        if (todo) {
+            uint64_t o = 0ull, c = 0ull;
+#pragma unroll
+            for (int k = 0; k < 2; ++k) o |= s_open[wn[k]] & m[k];
+            for (uint32_t rest = left; rest; rest &= rest - 1) { const int w = __builtin_ctz(rest); o |= s_open[w] & mine[w]; }
+#pragma unroll
+            for (int k = 0; k < 2; ++k) c |= s_centre[wn[k]] & m[k];
+            for (uint32_t rest = left; rest; rest &= rest - 1) { const int w = __builtin_ctz(rest); c |= s_centre[w] & mine[w]; }
+            blocked = c != 0ull;
+            pending = o != 0ull;
+        }
+        const uint64_t up = __ballot(todo && !blocked && !pending), down = __ballot(todo && blocked);
+        if (up | down) {
+            centre |= up;
+            open &= ~(up | down);
+            if (lane == 0) { s_centre[wave] = centre; s_open[wave] = open; }     // (in this order)
+            todo = todo && !blocked && pending;
+        }
+    }
+    if (lane == 0) atomicMax(&sh.looks, looks);
+    __syncthreads();
+    // ---- the centres, numbered in ascending token order
+    const int pop = lane < 16 ? __popcll(s_centre[lane]) : 0, inc = wave_scan_incl_i32(pop);
+    const int before = __builtin_amdgcn_readlane(inc - pop, wave), n_centres = __builtin_amdgcn_readlane(inc, 15);
+    if (lane == 0 && wave < Wq) a.cmask[(size_t)b * W + wave] = centre;
+    if (on) {
+        const bool isc = (centre >> lane) & 1ull;
+        const int c = before + lanes_below(centre, lane);
+        a.status[(size_t)b * bt.n_max + tid] = isc ? ST_CENTER : ST_NOT;
+        a.cnum[(size_t)b * bt.n_max + tid] = isc ? c : -1;
+        if (isc) a.center_idx[sg.base + c] = tok;
+    }
+    if (tid == 0) {
+        rep->n_centers = n_centres;
+        rep->rounds = sh.looks;
+    }
+    return listed;
+}
+
+// grid (B + workers), block 1024, dynamic LDS: small_lds, at least RECHECK_LDS.
+template <int DT>
+__global__ __launch_bounds__(1024) void select_small_kernel(Batch bt, CentresArgs a, SmallArgs sa) {
+    extern __shared__ double s_dyn[];
+    __shared__ SmallShared sh;
+    // Counts the workgroup in (see centres_kernel).
+    auto meet = [&](int* counter, int add) __attribute__((always_inline)) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        if (threadIdx.x == 0) sh.got = __hip_atomic_fetch_add(counter, add, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();
+        return lane0_of(sh.got);
+    };
+    fetch_arguments<sizeof(Batch) + sizeof(CentresArgs) + sizeof(SmallArgs)>(min((int)blockIdx.x, PACT_MAX_BATCH - 1));
+    const bool resolver = (int)blockIdx.x < bt.B;
+    const int workers = gridDim.x - bt.B, b = resolver ? blockIdx.x : ((int)blockIdx.x - bt.B) % bt.B;
+    int T = 0, ticket = -1, changed = 0;
+    bool select = resolver, first = true;
+    if (!resolver) {
+        if (threadIdx.x == 0) {
+            int v = 0;
+            for (int k = 0; k < SMALL_POLLS; ++k) {              // (some milliseconds at most)
+                v = __hip_atomic_load(&a.tie_cnt[4 * b + 3], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (v & SMALL_READY) break;
+                __builtin_amdgcn_s_sleep(8);
+            }
+            if (v & SMALL_READY && (v >> 16) & 0x7FF) v = __hip_atomic_fetch_add(&a.tie_cnt[4 * b + 3], 1, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT);
+            sh.got = v;
+        }
+        __syncthreads();
+        const int v = lane0_of(sh.got);
+        T = v & SMALL_READY ? (v >> 16) & 0x7FF : 0;
+        ticket = v & 0xFFFF;
+        if (T == 0) return;
+    }
+    while (true) {
+        if (select) {
+            const int listed = select_sample<DT>(bt, a, sa, fresh_s(b), first, (unsigned char*)s_dyn, sh);
+            if (!first || listed == 0) return;
+            T = listed;
+        }
+        const int q = clamp_count(a.rep[b].n_kept, bt.s[b].n);
+        const int nchunk = a.dk * Elem<DT>::BYTES / 16, rows = (T + 15) >> 4;
+        int tiles = 4;                                           // (see centres_kernel)
+        while (tiles > 1 && nchunk * tiles > 8 * 64) {
+            const int half = 8 * tiles;
+            if (rows * ((q + half - 1) / half) > workers / bt.B || T * (64 / half) > rho_fix_tokens(bt.n_max)) break;
+            tiles >>= 1;
+        }
+        const int total = rows * ((q + 16 * tiles - 1) / (16 * tiles));
+        bool again = false;
+        if (select) {
+            const int seen = meet(&a.tie_cnt[4 * b + 2], 4);
+            if (seen & 1) {                                      // all items are done
+                changed = seen & (ORDER_PAIRS | ORDER_BAND);
+                again = changed || a.write_rho;
+                if (!again) return;
+            }
+        }
+        while (!again) {
+            if (ticket < 0) {
+                __syncthreads();
+                if (threadIdx.x == 0) sh.got = __hip_atomic_fetch_add(&a.tie_cnt[4 * b + 3], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & 0xFFFF;
+                __syncthreads();
+                ticket = lane0_of(sh.got);
+            }
+            const int item = ticket;
+            ticket = -1;
+            if (item >= total) return;
+            recheck_items<DT>(bt, a, fresh_s(b), fresh_s(T), fresh_s(q), fresh_s(item), fresh_s(item + 1), tiles, s_dyn);
+            if (meet(&a.tie_cnt[4 * b + 1], 1) != total - 1) continue;
+            changed = order_changed(bt, a, fresh_s(b), fresh_s(T), fresh_s(q), tiles, (unsigned char*)s_dyn, sh.flag);
+            if (!(meet(&a.tie_cnt[4 * b + 2], changed | 1) & 4)) return;          // the selection still runs
+            if (!changed && !a.write_rho) return;
+            again = true;
+        }
+        // the fp64 densities take their places
+        const int32_t* list = a.tie_list + (size_t)b * RHO_RECHECK_MAX;
+        const double* part_b = a.rho_fix + (size_t)b * 2 * rho_fix_tokens(bt.n_max) * rho_fix_chunks(bt.n_max);
+        if ((int)threadIdx.x < T) a.rho[(size_t)b * bt.n_max + min(list[threadIdx.x] & 0xFFFF, q - 1)] = part_b[threadIdx.x];
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();                                         // (read back by this workgroup only)
+        if (!changed) return;
+        select = true;
+        first = false;
+    }
+}
+
+// ------------------------------------------------------------------------------------------
 constexpr int CAND_BUF = 128;
 
 // The two nearest-centre searches share one kernel (below): the assignment of the kept tokens
@@ -1550,46 +1939,55 @@ int launch_centres(const Batch& bt, const Ws& w, const void* keys, pact_dtype k_
                    int32_t* cluster_counts, pact_report* rep, double* rho_opt, int32_t* rank_opt,
                    int stat_words, bool assign_now, hipStream_t st) {
     const char* k = (const char*)keys;
-    dim3 gset(settle_blocks(bt.n_max), bt.B);
-    const bool wide = (size_t)dk * (k_dt == PACT_BF16 ? 2 : 4) > 2048;
-#define PACT_SETTLE(DT, CH)                                                                                           \
-    PACT_LAUNCH("settle", (settle_kernel<DT, CH>), gset, dim3(256), st, bt, k, dk, idx, w.nn, w.near_list, w.near_cnt, \
-                w.stat, stat_words, w.rho, w.rho_lo, w.adj, rep)
-    if (k_dt == PACT_BF16) { if (wide) PACT_SETTLE(PACT_BF16, 8); else PACT_SETTLE(PACT_BF16, 2); }
-    else { if (wide) PACT_SETTLE(PACT_F32, 8); else PACT_SETTLE(PACT_F32, 2); }
-#undef PACT_SETTLE
-    // One wavefront per kept token while the chip holds them all at once (32 per CU); beyond that four
-    // tokens per wavefront (one image: 7.3 us against 9.5 us; 8 videos: 14.2 against 9.9 us).
-    if (kept_estimate(bt) <= 256 * 32)
-        PACT_LAUNCH("build_preds", build_preds_kernel<64>, dim3((bt.n_max + 3) / 4, bt.B), dim3(256), st, bt, rep, w.adj, w.rho,
-                    rho_opt, w.preds, w.heads, idx, w.tie_list, w.tie_cnt);
-    else
-        PACT_LAUNCH("build_preds", build_preds_kernel<16>, dim3((bt.n_max + 15) / 16, bt.B), dim3(256), st, bt, rep, w.adj, w.rho,
-                    rho_opt, w.preds, w.heads, idx, w.tie_list, w.tie_cnt);
-    const size_t lds_rounds = rounds_lds(bt.n_max, bt.W);
-    const size_t lds = lds_rounds > RECHECK_LDS ? lds_rounds : RECHECK_LDS;
     CentresArgs ca;
     std::memset(&ca, 0, sizeof(ca));
     ca.keys = k; ca.dk = dk; ca.idx = idx; ca.nn = w.nn; ca.rep = rep; ca.adj = w.adj; ca.rho = w.rho; ca.rho_opt = rho_opt;
     ca.preds = w.preds; ca.heads = w.heads; ca.tie_list = w.tie_list; ca.tie_cnt = w.tie_cnt; ca.rho_fix = w.rho_fix;
     ca.status = w.status; ca.cnum = w.cnum; ca.cmask = w.cmask; ca.center_idx = center_idx;
     ca.write_rho = rank_opt ? 1 : 0;
-    // at most a workgroup per CU in all; without a second turn up to four tiles of 16 listed tokens in each sample
-    long workers = 0;
-    for (int b = 0; b < bt.B; ++b) workers += (bt.s[b].n + 15) / 16;
-    if (workers > 256 - bt.B) workers = 256 - bt.B;
-    static size_t raised[2] = {};
-    const int di = k_dt == PACT_BF16 ? 1 : 0;
-    if (lds > 48 * 1024 && lds > raised[di]) {
-        const void* fn = di ? (const void*)centres_kernel<PACT_BF16> : (const void*)centres_kernel<PACT_F32>;
-        if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
-            return PACT_ERR_HIP;
-        raised[di] = lds;
+    // at most a workgroup per CU in all
+    auto launch_selection = [&](const char* name, auto kernel, size_t& raised, size_t lds, int tokens_per_worker, auto... more) -> int {
+        long workers = 0;
+        for (int b = 0; b < bt.B; ++b) workers += (bt.s[b].n + tokens_per_worker - 1) / tokens_per_worker;
+        if (workers > 256 - bt.B) workers = 256 - bt.B;
+        if (lds < RECHECK_LDS) lds = RECHECK_LDS;
+        if (lds > 48 * 1024 && lds > raised) {
+            if (hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+                return PACT_ERR_HIP;
+            raised = lds;
+        }
+        PACT_LAUNCH_SHMEM(name, kernel, dim3(bt.B + workers), dim3(1024), lds, st, bt, ca, more...);
+        return PACT_OK;
+    };
+    static size_t raised[4] = {};
+    if (bt.n_max <= SMALL_TOKENS) {
+        SmallArgs sa{w.near_list, w.near_cnt, w.stat, stat_words, w.rho_lo};
+        const int rc = k_dt == PACT_BF16 ? launch_selection("centres", select_small_kernel<PACT_BF16>, raised[0], small_lds(bt.W), 32, sa)
+                                         : launch_selection("centres", select_small_kernel<PACT_F32>, raised[1], small_lds(bt.W), 32, sa);
+        if (rc) return rc;
+    } else {
+        dim3 gset(settle_blocks(bt.n_max), bt.B);
+        const bool wide = (size_t)dk * (k_dt == PACT_BF16 ? 2 : 4) > 2048;
+#define PACT_SETTLE(DT, CH)                                                                                           \
+        PACT_LAUNCH("settle", (settle_kernel<DT, CH>), gset, dim3(256), st, bt, k, dk, idx, w.nn, w.near_list, w.near_cnt, \
+                    w.stat, stat_words, w.rho, w.rho_lo, w.adj, rep)
+        if (k_dt == PACT_BF16) { if (wide) PACT_SETTLE(PACT_BF16, 8); else PACT_SETTLE(PACT_BF16, 2); }
+        else { if (wide) PACT_SETTLE(PACT_F32, 8); else PACT_SETTLE(PACT_F32, 2); }
+#undef PACT_SETTLE
+        // One wavefront per kept token while the chip holds them all at once (32 per CU); beyond that four
+        // tokens per wavefront (one image: 7.3 us against 9.5 us; 8 videos: 14.2 against 9.9 us).
+        if (kept_estimate(bt) <= 256 * 32)
+            PACT_LAUNCH("build_preds", build_preds_kernel<64>, dim3((bt.n_max + 3) / 4, bt.B), dim3(256), st, bt, rep, w.adj, w.rho,
+                        rho_opt, w.preds, w.heads, idx, w.tie_list, w.tie_cnt);
+        else
+            PACT_LAUNCH("build_preds", build_preds_kernel<16>, dim3((bt.n_max + 15) / 16, bt.B), dim3(256), st, bt, rep, w.adj, w.rho,
+                        rho_opt, w.preds, w.heads, idx, w.tie_list, w.tie_cnt);
+        // (without a second turn up to four tiles of 16 listed tokens in each sample)
+        const size_t lds = rounds_lds(bt.n_max, bt.W);
+        const int rc = k_dt == PACT_BF16 ? launch_selection("centres", centres_kernel<PACT_BF16>, raised[2], lds, 16)
+                                         : launch_selection("centres", centres_kernel<PACT_F32>, raised[3], lds, 16);
+        if (rc) return rc;
     }
-    if (k_dt == PACT_BF16)
-        PACT_LAUNCH_SHMEM("centres", centres_kernel<PACT_BF16>, dim3(bt.B + workers), dim3(1024), lds, st, bt, ca);
-    else
-        PACT_LAUNCH_SHMEM("centres", centres_kernel<PACT_F32>, dim3(bt.B + workers), dim3(1024), lds, st, bt, ca);
     if (rank_opt)          // (after the fp64 densities are in place)
         PACT_LAUNCH("density_rank", rank_kernel, dim3((bt.n_max + 63) / 64, bt.B), dim3(1024), st, bt, rep,
                     w.rho, rank_opt);

@@ -1,0 +1,89 @@
+"""Settling, order and selection of samples up to 1024 tokens in one launch, against the oracle and against the three launches that larger
+samples take (a sample of 1100 tokens in the same call makes all of them take those)."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2504_08966_amd as P
+from oracle import pact_oracle as po
+from tests import gpu_util as gu
+from tests.test_gpu_parity import _gap_dc, _random_sample, assert_same, oracle_reduce
+
+pytestmark = pytest.mark.gpu
+_VARY = ("rounds",)                                   # (depends on how the wavefronts interleave)
+
+
+def _both_ways(s, d_c, d_n, dtype, flags=0):
+    n, dk, h = s.n, s.keys.shape[1] * s.keys.shape[2], s.hidden.shape[1]
+    big = _random_sample(3, 1100, 1, 1, dk, h, 0.4, dtype)
+    prm = P.PactParams(s.lam, d_c, d_n, 1.5, 10, flags)
+    one = lambda t: gu.dev(t.reshape(t.shape[0], -1), dtype)
+    alone = P.pact_reduce(one(s.hidden), one(s.keys), one(s.keys), one(s.queries), 1, dk, 1, prm)
+    two = lambda x, y: one(np.concatenate([x.reshape(len(x), -1), y.reshape(len(y), -1)]))
+    k = two(s.keys, big.keys)
+    both = P.pact_reduce_varlen(two(s.hidden, big.hidden), k, k, two(s.queries, big.queries), 1, dk, 1, [0, n, n + 1100],
+                                [prm, P.PactParams(0.4, d_c, 2.0, 1.5)])
+    torch.cuda.synchronize()
+    a, b = gu.trim(alone, n), gu.trim(both, n)
+    for key in ("scores", "kept_idx", "pruned_idx", "center_idx", "cluster_id", "merged", "counts"):
+        assert np.array_equal(a[key], b[key]), key
+    ra, rb = ({f: v for f, v in r["rep"].items() if f not in _VARY} for r in (a, b))
+    assert ra == rb
+    return a
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("n,dk,lam", [(1, 8, 0.0), (2, 64, 0.0), (64, 128, 0.0), (65, 136, 0.0), (128, 256, 0.0), (129, 512, 0.0), (256, 128, 0.0),
+                                      (257, 520, 0.0), (512, 64, 0.0), (513, 128, 0.0), (1000, 1032, 0.2), (1024, 64, 0.0), (1024, 128, 0.3),
+                                      (960, 2048, 0.45)])
+def test_small_samples_both_ways_and_the_oracle(n, dk, lam, dtype):
+    # kept tokens at the edges of the words, of the threads per token and of what one pass over the bitmap loads; rows of one chunk a
+    # lane and of several
+    s = _random_sample(8000 + n + dk, n, 1, 1, dk, 64, lam, dtype)
+    d_c = _gap_dc(s.keys.reshape(n, -1), frac=0.01) if n > 64 else 0.3
+    g = _both_ways(s, d_c, 2.0, dtype, P.PACT_FLAG_KEY_STATS)
+    assert_same(g, oracle_reduce(s, d_c), s, f"n={n} dk={dk} {dtype}")
+
+
+@pytest.mark.parametrize("d_n", [0.05, 0.5, 8.0])
+@pytest.mark.parametrize("kind", ["alike", "pairs", "dense", "edge"])
+def test_small_samples_with_ties_and_undecided_pairs(kind, d_n):
+    # all tokens copies of a few (every one listed, ties decided by the index); copies in pairs; a cutoff that takes in half of all
+    # pairs (rows with predecessors in every word); a cutoff that many pairs' distances equal (more undecided pairs than groups of lanes)
+    n, dk, r = 700, 64, np.random.default_rng(17)
+    s = _random_sample(91, n, 1, 1, dk, 64, 0.25, "f32")
+    k = s.keys.reshape(n, dk)
+    if kind == "alike":
+        k = k[r.integers(0, 5, n)]
+    elif kind == "pairs":
+        k = k[np.arange(n) // 2]
+    elif kind == "edge":
+        k = np.eye(dk, dtype=np.float32)[r.integers(0, dk, n)] + np.eye(dk, dtype=np.float32)[r.integers(0, dk, n)]
+    s.keys[...] = k.reshape(s.keys.shape)
+    D = po.cosine_distance_matrix(k.astype(np.float64))
+    d_c = {"alike": 0.1, "pairs": 0.3, "dense": float(np.float32(np.median(D))), "edge": 0.5}[kind]
+    g = _both_ways(s, d_c, d_n, "f32")
+    if kind in ("alike", "pairs"):                    # (decided by exact ties)
+        assert g["rep"]["rho_rechecked"] > 100
+    if kind == "edge":
+        assert g["rep"]["dc_checked_pairs"] > 10000
+    # (no oracle here: its sums break exact ties by their rounding)
+
+
+def test_a_batch_of_small_samples_with_listed_tokens_in_each():
+    # every sample has copies, so that its densities are evaluated again by the workgroups that wait for the lists
+    samples = []
+    for b in range(40):
+        s = _random_sample(600 + b, 150 + 17 * b, 1, 1, 64, 64, 0.3, "bf16")
+        s.keys[1::7] = s.keys[0::7][: len(s.keys[1::7])]
+        samples.append(s)
+    cat = lambda f: gu.dev(np.concatenate([f(s).reshape(s.n, -1) for s in samples]), "bf16")
+    cu = np.concatenate([[0], np.cumsum([s.n for s in samples])]).tolist()
+    dcs = [_gap_dc(s.keys.reshape(s.n, -1), frac=0.02) for s in samples]
+    k = cat(lambda s: s.keys)
+    o = P.pact_reduce_varlen(cat(lambda s: s.hidden), k, k, cat(lambda s: s.queries), 1, 64, 1, cu, [P.PactParams(0.3, d, 2.0, 1.5) for d in dcs])
+    torch.cuda.synchronize()
+    for b, s in enumerate(samples):
+        g = gu.trim(o, s.n, base=cu[b], b=b)
+        assert g["rep"]["rho_rechecked"] > 0
+        assert_same(g, oracle_reduce(s, dcs[b]), s, f"sample {b}")

@@ -1,0 +1,31 @@
+"""The hand-over between workgroups in the one-launch selection of small samples, read from the assembly of the kernel: list and
+densities are stored by all wavefronts, one of them says that they are there.  CPU only (hipcc, no GPU)."""
+import os
+import re
+import subprocess
+
+import pytest
+
+from paper_2504_08966_amd import build as B
+
+
+def test_every_wavefront_waits_for_its_stores_before_they_are_announced(tmp_path):
+    out = str(tmp_path / "centres.s")
+    cmd = [B._hipcc(), *B.FLAGS, "--cuda-device-only", "-S", os.path.join(B.CSRC, "pact_centres.hip"), "-o", out]
+    try:
+        r = subprocess.run(cmd, capture_output=True, text=True, timeout=300)
+    except FileNotFoundError:
+        pytest.skip("no hipcc")
+    assert r.returncode == 0, r.stderr
+    kernels = re.findall(r"^(_ZN4pact19select_small_kernel\w+):(.*?)^\.Lfunc_end", open(out).read(), re.S | re.M)
+    assert len(kernels) == 2                                        # bf16 and fp32 keys
+    for name, text in kernels:
+        lines = [ln.strip() for ln in text.splitlines() if ln.strip() and not ln.strip().startswith(";")]
+        releases = [i for i, ln in enumerate(lines) if ln.startswith("buffer_wbl2")]
+        assert len(releases) == 4, name                             # the list; selection run; an item done; looked at
+        for i in releases:
+            barrier = max(k for k in range(i) if lines[k].startswith("s_barrier"))
+            for ln in reversed(lines[:barrier]):
+                if ln.startswith("s_waitcnt") and "vmcnt(0)" in ln:
+                    break
+                assert not re.match(r"(global|buffer|flat|scratch)_|s_barrier|s_c?branch|\.LBB", ln), (name, lines[barrier - 8:barrier + 1])
