@@ -1124,6 +1124,9 @@ __global__ __launch_bounds__(1024) void centres_kernel(Batch bt, CentresArgs a) 
 // launch's other workgroups wait for and take by ticket, and so does the sample's own workgroup once its selection is
 // through: a worker's wait is bounded, and without workers the items are done all the same.  What follows from them is
 // as in centres_kernel.
+// Bound by its chain: arguments, one trip for everything, one for the undecided pairs' rows (3 + 1.4 us), then instructions of few wavefronts (lists
+// 2 to 3, selection 2 us).  The three launches of larger samples were mostly their beginnings and ends; event brackets: one frame of 196
+// tokens 5.5 + 7.5 + 10.9 -> 12.7 us, a crop of 729 with fp32 keys 6 + 7 + 9.6 -> 14.8, 32 crops 7.3 + 8.6 + 16.4 -> 25 (ten of which are the listed tokens').
 // tie_cnt[4b + 1]: work items done; [4b + 2]: as in centres_kernel; [4b + 3]: tickets taken | listed tokens << 16 | READY.
 constexpr int SMALL_TOKENS = 1024, SMALL_READY = 1 << 30, SMALL_POLLS = 1 << 12;
 struct SmallArgs {
@@ -1424,7 +1427,6 @@ __global__ __launch_bounds__(1024) void select_small_kernel(Batch bt, CentresArg
         __syncthreads();
         return lane0_of(sh.got);
     };
-    fetch_arguments<sizeof(Batch) + sizeof(CentresArgs) + sizeof(SmallArgs)>(min((int)blockIdx.x, PACT_MAX_BATCH - 1));
     const bool resolver = (int)blockIdx.x < bt.B;
     const int workers = gridDim.x - bt.B, b = resolver ? blockIdx.x : ((int)blockIdx.x - bt.B) % bt.B;
     int T = 0, ticket = -1, changed = 0;

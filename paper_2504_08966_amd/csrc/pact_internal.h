@@ -257,31 +257,6 @@ typedef __attribute__((ext_vector_type(16))) float f32x16_t;
 
 __device__ __forceinline__ float bf16_bits_to_f32(uint32_t hi16) { return __uint_as_float(hi16 << 16); }
 
-// Kernel arguments are read through the scalar data cache, 64 bytes at a time, and a compiled kernel reads them where it first needs
-// them: every line is a trip to memory of its own, one after the other.  One read of every line that it will need, at the start
-// and all together, makes the later ones hits.  `bytes`: of all arguments; the batch description comes first, of which a kernel needs
-// the beginning and sample b's line.
-template <int BYTES> __device__ __forceinline__ void fetch_arguments(int b) {
-    typedef const __attribute__((address_space(4))) char* kptr;
-    constexpr int FIRST = (int)sizeof(Batch) / 64 * 64, LINES = (BYTES - FIRST + 63) / 64;
-    const kptr k = (kptr)__builtin_amdgcn_kernarg_segment_ptr(), ks = k + 16 + 32 * b;
-    int t;
-    if constexpr (LINES <= 1)
-        asm volatile("s_load_dword %0, %1, 0x0\n\ts_load_dword %0, %2, 0x0\n\ts_load_dword %0, %1, %3\n\ts_waitcnt lgkmcnt(0)"
-                     : "=&s"(t) : "s"(k), "s"(ks), "n"(FIRST));
-    else if constexpr (LINES == 2)
-        asm volatile("s_load_dword %0, %1, 0x0\n\ts_load_dword %0, %2, 0x0\n\ts_load_dword %0, %1, %3\n\ts_load_dword %0, %1, %4\n\ts_waitcnt lgkmcnt(0)"
-                     : "=&s"(t) : "s"(k), "s"(ks), "n"(FIRST), "n"(FIRST + 64));
-    else if constexpr (LINES == 3)
-        asm volatile("s_load_dword %0, %1, 0x0\n\ts_load_dword %0, %2, 0x0\n\ts_load_dword %0, %1, %3\n\ts_load_dword %0, %1, %4\n\t"
-                     "s_load_dword %0, %1, %5\n\ts_waitcnt lgkmcnt(0)"
-                     : "=&s"(t) : "s"(k), "s"(ks), "n"(FIRST), "n"(FIRST + 64), "n"(FIRST + 128));
-    else
-        asm volatile("s_load_dword %0, %1, 0x0\n\ts_load_dword %0, %2, 0x0\n\ts_load_dword %0, %1, %3\n\ts_load_dword %0, %1, %4\n\t"
-                     "s_load_dword %0, %1, %5\n\ts_load_dword %0, %1, %6\n\ts_waitcnt lgkmcnt(0)"
-                     : "=&s"(t) : "s"(k), "s"(ks), "n"(FIRST), "n"(FIRST + 64), "n"(FIRST + 128), "n"(FIRST + 192));
-}
-
 // Counts read back from a device-side report are clamped to the sample size, so that a report
 // the caller never initialised cannot send a kernel out of bounds.
 __device__ __forceinline__ int clamp_count(int v, int n) { return v < 0 ? 0 : (v > n ? n : v); }
