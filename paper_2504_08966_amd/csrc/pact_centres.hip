@@ -1113,8 +1113,8 @@ __global__ __launch_bounds__(1024) void centres_kernel(Batch bt, CentresArgs a) 
 // ------------------------------------------------------------------------------------------
 // Samples of at most SMALL_TOKENS: settling, order and selection in one launch.  One workgroup per sample, the sample's bitmap in LDS
 // (1024 tokens: 139 KB, rows an odd number of words apart):
-//  1. the undecided pairs are evaluated as settle_kernel does it, by groups of lanes that hold a row in one 16-byte chunk each where it has
-//     at most 64; bits are cleared in LDS, and in memory, where the assignment reads them;
+//  1. the undecided pairs are evaluated as settle_kernel does it, by groups of lanes that hold a row in one 16-byte chunk each (wide rows: by
+//     settle_kernel, ahead); bits are cleared in LDS, and in memory, where the assignment reads them;
 //  2. one to eight threads per kept token go through the set bits of its row, 32 at a time, and leave those of preceding neighbours.
 //     Densities are compared in fp32 where that decides, near-ties are listed;
 //  3. a thread per token, every wavefront looks at its undecided tokens until none is left.  Its 64 tokens are one word of the masks of
@@ -1130,10 +1130,24 @@ __global__ __launch_bounds__(1024) void centres_kernel(Batch bt, CentresArgs a) 
 // tie_cnt[4b + 1]: work items done; [4b + 2]: as in centres_kernel; [4b + 3]: tickets taken | listed tokens << 16 | READY.
 constexpr int SMALL_TOKENS = 1024, SMALL_READY = 1 << 30, SMALL_POLLS = 1 << 12;
 struct SmallArgs {
-    const uint32_t* near_list; const int32_t* near_cnt;
+    const uint32_t* near_list; const int32_t* near_cnt;          // near_list == nullptr: settle_kernel has run
     const uint32_t* far_bits; int32_t far_words;
     const double* rho_lo;
 };
+// Rows of more than 512 bytes are left to settle_kernel: one compute unit would fetch them for 5 us and more (835 tokens, fp32 keys 512
+// wide, 158 pairs: event bracket 30 us).
+constexpr int SMALL_SETTLE_CHUNKS = 32;
+// Where one launch is the faster way: up to 512 kept tokens, and where settle_kernel has to come first up to 256 of a single sample.  Settling to
+// selection, brackets without their 2.5 us a launch, three launches -> here, nothing listed / two tokens listed in a sample: width
+// 128, images of 160 tokens 15.8 / - -> 9.0 / -, 300: 16.2 -> 11.4, 729: 16.6 / 20.1 -> 14.0 / 21.2, 1000 (550 kept): 17.2 -> 19.7; 8 of 300 18.3 / 21.2 -> 11.6 /
+// 19; 8 of 729 18.3 / 21 -> 14.7 / 23; 32 of 729 25 -> 23; width 512: 160: 14.0 -> 11.0, 300: 15.5 / 23.3 -> 12.8 / 25.2, 729: 15.2 / 24.4 -> 14.8 / 27.2,
+// 8 of 729 - / 24.5 -> - / 28.5.
+static bool selects_in_one(const Batch& bt, bool settle_there) {
+    if (bt.n_max > SMALL_TOKENS || (!settle_there && bt.B > 1)) return false;
+    for (int b = 0; b < bt.B; ++b)
+        if (bt.s[b].n - prune_rank(bt.s[b].lambda, bt.s[b].n) > (settle_there ? 512 : 256)) return false;
+    return true;
+}
 static size_t small_lds(int W) { return (size_t)W * 64 * (((W | 1) + 1) * sizeof(uint64_t) + sizeof(float)); }
 
 typedef __attribute__((address_space(3))) uint64_t lds_u64;
@@ -1165,26 +1179,27 @@ __device__ __forceinline__ int select_sample(const Batch& bt, const CentresArgs&
     const int32_t* ix = a.idx + sg.base;
     const double* nnb = a.nn + sg.base;
     constexpr int U = 2;                                         // pairs in flight per group of lanes
-    const int nchunk = a.dk * Elem<DT>::BYTES / 16;
-    const int lpp = nchunk <= 16 ? 16 : nchunk <= 32 ? 32 : 64, ng = 1024 / lpp, g = tid / lpp, gl = tid & (lpp - 1);
+    const bool settle = first && sa.near_list != nullptr;
+    const int nchunk = a.dk * Elem<DT>::BYTES / 16;              // (settle: SMALL_SETTLE_CHUNKS at most)
+    const int lpp = nchunk <= 16 ? 16 : 32, ng = 1024 / lpp, g = tid / lpp, gl = tid & (lpp - 1);
     const uint2* pairs = (const uint2*)(sa.near_list + (size_t)b * NEAR_CAP * 2);
     // ---- everything whose address depends on the thread's position only goes out before the first count is read
     const int pc = min(tid, sg.n - 1), r0 = tid >> 4, w0 = tid & 15;
     const int tok = ix[pc];
     double r = rho[pc];
-    const bool split = first && sg.d_n < EXACT_SUMS_D_N;         // densities that came in two parts (add_density)
+    const bool split = settle && sg.d_n < EXACT_SUMS_D_N;         // densities that came in two parts (add_density)
     const double r_lo = split ? sa.rho_lo[(size_t)b * bt.n_max + pc] : 0.0;
     uint64_t word[8];
 #pragma unroll
     for (int k = 0; k < 8; ++k) word[k] = r0 + 64 * k < sg.n && w0 < W ? adj[(size_t)(r0 + 64 * k) * W + w0] : 0ull;
     uint2 pr[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) pr[u] = first ? pairs[u * ng + g] : make_uint2(0, 0);      // (garbage beyond the count, never used)
-    const uint32_t raw = first ? (uint32_t)sa.near_cnt[2 * b] : 0u;
-    const int checked = first ? sa.near_cnt[2 * b + 1] : 0;
+    for (int u = 0; u < U; ++u) pr[u] = settle ? pairs[u * ng + g] : make_uint2(0, 0);      // (garbage beyond the count, never used)
+    const uint32_t raw = settle ? (uint32_t)sa.near_cnt[2 * b] : 0u;
+    const int checked = settle ? sa.near_cnt[2 * b + 1] : 0;
     const int q = clamp_count(rep->n_kept, sg.n), Wq = (q + 63) >> 6;
     const int cnt = (int)min(raw, (uint32_t)NEAR_CAP);
-    if (first && sa.far_words > 0) {
+    if (settle && sa.far_words > 0) {
         uint32_t fb = 0u;                                        // (see settle_kernel)
         for (int k = tid; k < sa.far_words; k += 1024) fb = max(fb, sa.far_bits[(size_t)b * sa.far_words + k]);
 #pragma unroll
@@ -1241,26 +1256,23 @@ __device__ __forceinline__ int select_sample(const Batch& bt, const CentresArgs&
                 nj[u] = nnb[tj];
                 acc[u] = 0.0;
             }
-#pragma unroll 1
-            for (int c0 = 0; c0 < nchunk; c0 += lpp) {           // (uniform)
-                uint4 va[U], vb[U];
-                const size_t o = (size_t)min(c0 + gl, nchunk - 1) * 16;
+            uint4 va[U], vb[U];
+            const size_t o = (size_t)min(gl, nchunk - 1) * 16;
 #pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    if (u > 0 && !two) break;
-                    va[u] = *(const uint4*)(ri[u] + o);
-                    vb[u] = *(const uint4*)(rj[u] + o);
-                }
+            for (int u = 0; u < U; ++u) {
+                if (u > 0 && !two) break;
+                va[u] = *(const uint4*)(ri[u] + o);
+                vb[u] = *(const uint4*)(rj[u] + o);
+            }
 #pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    if (u > 0 && !two) break;
-                    if (c0 + gl < nchunk) {
-                        double x[8], y[8];
-                        Elem<DT>::widen(va[u], x);
-                        Elem<DT>::widen(vb[u], y);
+            for (int u = 0; u < U; ++u) {
+                if (u > 0 && !two) break;
+                if (gl < nchunk) {
+                    double x[8], y[8];
+                    Elem<DT>::widen(va[u], x);
+                    Elem<DT>::widen(vb[u], y);
 #pragma unroll
-                        for (int i = 0; i < EPL; ++i) acc[u] = fma(x[i], y[i], acc[u]);
-                    }
+                    for (int i = 0; i < EPL; ++i) acc[u] = fma(x[i], y[i], acc[u]);
                 }
             }
 #pragma unroll
@@ -1340,14 +1352,16 @@ __device__ __forceinline__ int select_sample(const Batch& bt, const CentresArgs&
         }
         if (tid == 1023) {                                       // (of the wavefront that has a selection of its own least often)
             __hip_atomic_fetch_add(&a.tie_cnt[4 * b + 3], SMALL_READY | (listed << 16), __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-            // (a listed pair that stands for both orders counts twice)
-            rep->dc_checked_pairs = raw > (uint32_t)NEAR_CAP ? cnt : checked;
-            rep->refine_overflow = raw > (uint32_t)NEAR_CAP ? OVERFLOW_NEAR_LIST : 0;
-            rep->dc_near_ties = sh.near_ties;
-            uint32_t fb = 0u;
-            if (sa.far_words > 0)
-                for (int k = 0; k < 16; ++k) fb = max(fb, sh.far[k]);
-            rep->max_key_distance = fb ? fminf(-__uint_as_float(fb) * sg.d_n * 0.6931471805599453f, 2.0f) : 0.0f;
+            if (settle) {
+                // (a listed pair that stands for both orders counts twice)
+                rep->dc_checked_pairs = raw > (uint32_t)NEAR_CAP ? cnt : checked;
+                rep->refine_overflow = raw > (uint32_t)NEAR_CAP ? OVERFLOW_NEAR_LIST : 0;
+                rep->dc_near_ties = sh.near_ties;
+                uint32_t fb = 0u;
+                if (sa.far_words > 0)
+                    for (int k = 0; k < 16; ++k) fb = max(fb, sh.far[k]);
+                rep->max_key_distance = fb ? fminf(-__uint_as_float(fb) * sg.d_n * 0.6931471805599453f, 2.0f) : 0.0f;
+            }
         }
     }
     // ---- 3. the selection.  Two words of predecessors in registers, others from LDS
@@ -1962,12 +1976,8 @@ int launch_centres(const Batch& bt, const Ws& w, const void* keys, pact_dtype k_
         return PACT_OK;
     };
     static size_t raised[4] = {};
-    if (bt.n_max <= SMALL_TOKENS) {
-        SmallArgs sa{w.near_list, w.near_cnt, w.stat, stat_words, w.rho_lo};
-        const int rc = k_dt == PACT_BF16 ? launch_selection("centres", select_small_kernel<PACT_BF16>, raised[0], small_lds(bt.W), 32, sa)
-                                         : launch_selection("centres", select_small_kernel<PACT_F32>, raised[1], small_lds(bt.W), 32, sa);
-        if (rc) return rc;
-    } else {
+    const bool narrow = dk * (k_dt == PACT_BF16 ? 2 : 4) <= SMALL_SETTLE_CHUNKS * 16, small = selects_in_one(bt, narrow);
+    if (!small || !narrow) {
         dim3 gset(settle_blocks(bt.n_max), bt.B);
         const bool wide = (size_t)dk * (k_dt == PACT_BF16 ? 2 : 4) > 2048;
 #define PACT_SETTLE(DT, CH)                                                                                           \
@@ -1976,6 +1986,13 @@ int launch_centres(const Batch& bt, const Ws& w, const void* keys, pact_dtype k_
         if (k_dt == PACT_BF16) { if (wide) PACT_SETTLE(PACT_BF16, 8); else PACT_SETTLE(PACT_BF16, 2); }
         else { if (wide) PACT_SETTLE(PACT_F32, 8); else PACT_SETTLE(PACT_F32, 2); }
 #undef PACT_SETTLE
+    }
+    if (small) {
+        SmallArgs sa{narrow ? w.near_list : nullptr, w.near_cnt, w.stat, stat_words, w.rho_lo};
+        const int rc = k_dt == PACT_BF16 ? launch_selection("centres", select_small_kernel<PACT_BF16>, raised[0], small_lds(bt.W), 32, sa)
+                                         : launch_selection("centres", select_small_kernel<PACT_F32>, raised[1], small_lds(bt.W), 32, sa);
+        if (rc) return rc;
+    } else {
         // One wavefront per kept token while the chip holds them all at once (32 per CU); beyond that four
         // tokens per wavefront (one image: 7.3 us against 9.5 us; 8 videos: 14.2 against 9.9 us).
         if (kept_estimate(bt) <= 256 * 32)

@@ -34,15 +34,27 @@ def _both_ways(s, d_c, d_n, dtype, flags=0):
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("n,dk,lam", [(1, 8, 0.0), (2, 64, 0.0), (64, 128, 0.0), (65, 136, 0.0), (128, 256, 0.0), (129, 512, 0.0), (256, 128, 0.0),
-                                      (257, 520, 0.0), (512, 64, 0.0), (513, 128, 0.0), (1000, 1032, 0.2), (1024, 64, 0.0), (1024, 128, 0.3),
-                                      (960, 2048, 0.45)])
+                                      (257, 120, 0.0), (512, 64, 0.0), (513, 128, 0.0), (1024, 64, 0.5), (1024, 128, 0.5), (1024, 72, 0.51),
+                                      (255, 1032, 0.0), (960, 2048, 0.75)])
 def test_small_samples_both_ways_and_the_oracle(n, dk, lam, dtype):
-    # kept tokens at the edges of the words, of the threads per token and of what one pass over the bitmap loads; rows of one chunk a
-    # lane and of several
+    # kept tokens at the edges of the words, of the threads per token and of the rule; rows of one chunk a lane and of several
     s = _random_sample(8000 + n + dk, n, 1, 1, dk, 64, lam, dtype)
     d_c = _gap_dc(s.keys.reshape(n, -1), frac=0.01) if n > 64 else 0.3
     g = _both_ways(s, d_c, 2.0, dtype, P.PACT_FLAG_KEY_STATS)
     assert_same(g, oracle_reduce(s, d_c), s, f"n={n} dk={dk} {dtype}")
+
+
+def test_more_tokens_kept_than_the_percentile_alone_would_leave():
+    # equal scores: all of 1024 are kept where 512 were expected
+    n, dk = 1024, 64
+    s = _random_sample(77, n, 1, 1, dk, 64, 0.5, "f32")
+    s.hidden[...] = s.hidden[0]
+    s.keys[...] = s.keys / np.linalg.norm(s.keys, axis=2, keepdims=True)
+    s.queries[...] = 0.0                              # (equal logits)
+    d_c = _gap_dc(s.keys.reshape(n, -1), frac=0.01)
+    g = _both_ways(s, d_c, 2.0, "f32")
+    assert g["rep"]["n_kept"] == n
+    assert_same(g, oracle_reduce(s, d_c), s, "ties")
 
 
 @pytest.mark.parametrize("d_n", [0.05, 0.5, 8.0])
@@ -51,7 +63,7 @@ def test_small_samples_with_ties_and_undecided_pairs(kind, d_n):
     # all tokens copies of a few (every one listed, ties decided by the index); copies in pairs; a cutoff that takes in half of all
     # pairs (rows with predecessors in every word); a cutoff that many pairs' distances equal (more undecided pairs than groups of lanes)
     n, dk, r = 700, 64, np.random.default_rng(17)
-    s = _random_sample(91, n, 1, 1, dk, 64, 0.25, "f32")
+    s = _random_sample(91, n, 1, 1, dk, 64, 0.3, "f32")
     k = s.keys.reshape(n, dk)
     if kind == "alike":
         k = k[r.integers(0, 5, n)]
@@ -74,14 +86,14 @@ def test_a_batch_of_small_samples_with_listed_tokens_in_each():
     # every sample has copies, so that its densities are evaluated again by the workgroups that wait for the lists
     samples = []
     for b in range(40):
-        s = _random_sample(600 + b, 150 + 17 * b, 1, 1, 64, 64, 0.3, "bf16")
+        s = _random_sample(600 + b, 150 + 17 * b, 1, 1, 64, 64, 0.4, "bf16")
         s.keys[1::7] = s.keys[0::7][: len(s.keys[1::7])]
         samples.append(s)
     cat = lambda f: gu.dev(np.concatenate([f(s).reshape(s.n, -1) for s in samples]), "bf16")
     cu = np.concatenate([[0], np.cumsum([s.n for s in samples])]).tolist()
     dcs = [_gap_dc(s.keys.reshape(s.n, -1), frac=0.02) for s in samples]
     k = cat(lambda s: s.keys)
-    o = P.pact_reduce_varlen(cat(lambda s: s.hidden), k, k, cat(lambda s: s.queries), 1, 64, 1, cu, [P.PactParams(0.3, d, 2.0, 1.5) for d in dcs])
+    o = P.pact_reduce_varlen(cat(lambda s: s.hidden), k, k, cat(lambda s: s.queries), 1, 64, 1, cu, [P.PactParams(0.4, d, 2.0, 1.5) for d in dcs])
     torch.cuda.synchronize()
     for b, s in enumerate(samples):
         g = gu.trim(o, s.n, base=cu[b], b=b)
