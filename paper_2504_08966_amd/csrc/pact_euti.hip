@@ -487,9 +487,9 @@ __global__ __launch_bounds__(256) void score_logits_kernel(Batch bt, LogitsArgs 
 // Eq. 2, pass 2: the softmax statistics of every head from the token blocks' partials, and from them the
 // factor exp(m_block - M) / Z of each (block, head); then s_i = |h_i| (1/n_q) sum_j e_ij factor_j.
 // Workgroup-wide helpers, 1024 threads.
-//   s_M, s_Z [PACT_MAX_QHEADS]; factors of blocks tb0 .. tb0 + nblk - 1: s_f[blk][n_q]
+//   factors of blocks tb0 .. tb0 + nblk - 1: s_f[blk][n_q].  (Of the exponentials that Z is summed from, a lane holds its blocks'.)
 __device__ __forceinline__ void softmax_factors(const Batch& bt, const Seg& sg, int b, int n_q, const double* __restrict__ sm_part,
-                                                int tb0, int nblk, double* s_M, double* s_Z, double* s_f, int tid) {
+                                                int tb0, int nblk, double* s_f, int tid) {
     const int lane = tid & 63;
     const int ntb_max = (bt.n_max + SCORE_TOK - 1) / SCORE_TOK, ntb = (sg.n + SCORE_TOK - 1) / SCORE_TOK;
     const double* part = sm_part + (size_t)b * ntb_max * n_q * 2;
@@ -510,19 +510,22 @@ __device__ __forceinline__ void softmax_factors(const Batch& bt, const Seg& sg, 
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
             if (32 * u >= ntb) break;                                // (uniform)
-            z += v[u].y != 0.0 ? v[u].y * exp(v[u].x - m) : 0.0;
+            const double e = exp(v[u].x - m);
+            z += v[u].y != 0.0 ? v[u].y * e : 0.0;
+            v[u].x = e;
         }
         for (int k = l32 + 256; k < ntb; k += 32) {
             const double2 w = *(const double2*)(part + ((size_t)k * n_q + j) * 2);
             z += w.y != 0.0 ? w.y * exp(w.x - m) : 0.0;
         }
         z = group_sum_f64(z, 32);
-        if (l32 == 0) { s_M[j] = m; s_Z[j] = z; }
-    }
-    __syncthreads();
-    for (int k = tid; k < nblk * n_q; k += 1024) {
-        const int blk = k / n_q, j = k - blk * n_q;
-        s_f[k] = tb0 + blk < ntb ? exp(part[((size_t)(tb0 + blk) * n_q + j) * 2] - s_M[j]) / s_Z[j] : 0.0;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int blk = l32 + 32 * u - tb0;
+            if (blk >= 0 && blk < nblk) s_f[blk * n_q + j] = blk + tb0 < ntb ? v[u].x / z : 0.0;
+        }
+        for (int k = l32 + 256; k < tb0 + nblk; k += 32)
+            if (k >= tb0) s_f[(k - tb0) * n_q + j] = k < ntb ? exp(part[((size_t)k * n_q + j) * 2] - m) / z : 0.0;
     }
     __syncthreads();
 }
@@ -540,7 +543,7 @@ __global__ __launch_bounds__(1024) void score_final_kernel(Batch bt, int n_q, co
                                                            const double* __restrict__ sm_part,
                                                            float* __restrict__ scores) {
     constexpr int NBLK = FINAL_TOK / SCORE_TOK, FINAL_PARTS = 1024 / FINAL_TOK;
-    __shared__ double s_M[PACT_MAX_QHEADS], s_Z[PACT_MAX_QHEADS], s_f[NBLK * PACT_MAX_QHEADS];
+    __shared__ double s_f[NBLK * PACT_MAX_QHEADS];
     __shared__ double s_acc[FINAL_PARTS - 1][FINAL_TOK];
     const int b = blockIdx.y;
     const Seg sg = bt.s[b];
@@ -553,7 +556,7 @@ __global__ __launch_bounds__(1024) void score_final_kernel(Batch bt, int n_q, co
     double e[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) e[u] = part + FINAL_PARTS * u < n_q ? expl[g * n_q + part + FINAL_PARTS * u] : 0.0;
-    softmax_factors(bt, sg, b, n_q, sm_part, blockIdx.x * NBLK, NBLK, s_M, s_Z, s_f, tid);
+    softmax_factors(bt, sg, b, n_q, sm_part, blockIdx.x * NBLK, NBLK, s_f, tid);
     const double* f = s_f + (tok / SCORE_TOK) * n_q;
     double acc = 0.0;
 #pragma unroll
@@ -570,30 +573,51 @@ __global__ __launch_bounds__(1024) void score_final_kernel(Batch bt, int n_q, co
 
 // ------------------------------------------------------------------------------------------
 // Eq. 3/4, one workgroup of 1024 per sample, on the finished fp32 scores:
-//   (a) the scores become order-preserving integer keys in LDS;
-//   (b) exact radix select of the (m+1)-th smallest key, m = min(floor(lambda n), n-1);
+//   (a) the scores become order-preserving integer keys, in registers: wavefront w owns a contiguous range of tokens, 64 KREG at most;
+//   (b) exact selection of the (m+1)-th smallest key, m = min(floor(lambda n), n-1);
 //   (c) ordered compaction into the kept / pruned index lists.
 // FINISH: samples of at most 1024 tokens finish their scores here as well (a thread per token; one launch
 // fewer).  More values per sample than FUSE_VALUES are too much for one compute unit to fetch: they have score_final_kernel.
-// Dynamic LDS: n_max * 4 bytes.
+// Bound by its chain of barriers and LDS trips, on one CU.  The keys of a token stay in one lane from the scores to the lists (they were in LDS, the lists'
+// order another one than the selection's); maxima and sums over wavefronts are lane permutes instead of shuffles and loops (event
+// brackets, us): 196 tokens with FINISH 11.4 -> 8.8, 2915 tokens 10.4 -> 7.8, 7290 12.8 -> 10.4, 16384 21.5 -> 16.1.
 constexpr int FUSE_TOKENS = 1024, FUSE_VALUES = 12288;
 struct FinishArgs { const double *expl, *hnorm, *sm_part; int32_t n_q; };
 __device__ __forceinline__ uint32_t ordered_key(float f) {
     const uint32_t u = __float_as_uint(f);
     return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
+// Largest value of a row of 16 lanes, in all of them / of the wavefront.
+__device__ __forceinline__ uint32_t row_max_u32(uint32_t v) {
+    auto step = [&](uint32_t x) { v = max(v, x); };
+    step((uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, DPP_XOR1, 0xF, 0xF, true));
+    step((uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, DPP_XOR2, 0xF, 0xF, true));
+    step((uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, DPP_HALF_MIRROR, 0xF, 0xF, true));
+    step((uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, DPP_MIRROR, 0xF, 0xF, true));
+    return v;
+}
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
+    v = row_max_u32(v);
+    auto at = [&](int l) { return (uint32_t)__builtin_amdgcn_readlane((int)v, l); };
+    return max(max(at(0), at(16)), max(at(32), at(48)));
+}
+// Sums of 16 wavefronts' counts in LDS: of all of them; of those before wavefront `wave` (scalar).
+__device__ __forceinline__ int counts_before(const int* s_cnt, int lane, int wave, int& all) {
+    const int own = lane < 16 ? s_cnt[lane] : 0, inc = wave_scan_incl_i32(own);
+    all = __builtin_amdgcn_readlane(inc, 15);
+    return __builtin_amdgcn_readlane(inc - own, wave);
+}
 
-template <bool FINISH>
+template <bool FINISH, int KREG>
 __global__ __launch_bounds__(1024) void score_prune_kernel(Batch bt, FinishArgs fin, float* scores,
                                                            uint64_t* __restrict__ adj,
                                                            int32_t* __restrict__ kept_idx,
                                                            int32_t* __restrict__ pruned_idx,
                                                            pact_report* __restrict__ rep) {
-    extern __shared__ uint32_t s_key[];
     __shared__ int s_hist[256 * 16];
     __shared__ int s_bin[256];
     __shared__ int s_sel[2][2];
-    __shared__ int s_wtot[16];
+    __shared__ int s_wtot[2][16];
     __shared__ int s_odd[2];             // scores next to the threshold without being equal to it; non-finite scores
     __shared__ uint32_t s_mm[2][16], s_cand[64];
     __shared__ int s_ncand;
@@ -602,25 +626,27 @@ __global__ __launch_bounds__(1024) void score_prune_kernel(Batch bt, FinishArgs 
     const int n = sg.n;
     const int tid = threadIdx.x;
     const int lane = tid & 63;
-    const int wave = tid >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     float* s = scores + sg.base;
 
-    // this thread's first keys stay in registers for the select (its passes then issue their
-    // histogram updates back to back instead of waiting for an LDS read before each)
-    constexpr int KREG = 8;
+    // this thread's tokens: i0 + 64 u + lane, below i1
+    const int per_wave = ((n + 15) / 16 + 63) / 64 * 64;
+    const int i0 = min(n, wave * per_wave), i1 = min(n, i0 + per_wave);
     uint32_t kreg[KREG];
+    auto have = [&](int u) __attribute__((always_inline)) { return i0 + 64 * u + lane < i1; };
     {
         float sv[KREG];
         if constexpr (FINISH) {
+            static_assert(KREG == 1, "a thread per token");
             constexpr int NBLK = FUSE_TOKENS / SCORE_TOK;
-            __shared__ double s_M[PACT_MAX_QHEADS], s_Z[PACT_MAX_QHEADS], s_f[NBLK * PACT_MAX_QHEADS];
+            __shared__ double s_f[NBLK * PACT_MAX_QHEADS];
             const int n_q = fin.n_q;
             const size_t g = (size_t)sg.base + min(tid, n - 1);
             const double hn = fin.hnorm[g];
             double e[16];
 #pragma unroll
             for (int u = 0; u < 16; ++u) e[u] = u < n_q ? fin.expl[g * n_q + u] : 0.0;
-            softmax_factors(bt, sg, b, n_q, fin.sm_part, 0, NBLK, s_M, s_Z, s_f, tid);
+            softmax_factors(bt, sg, b, n_q, fin.sm_part, 0, NBLK, s_f, tid);
             const double* f = s_f + (tid / SCORE_TOK) * n_q;
             double acc[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
@@ -631,21 +657,14 @@ __global__ __launch_bounds__(1024) void score_prune_kernel(Batch bt, FinishArgs 
                 acc[0] += (j & 3) == 0 ? v : 0.0; acc[1] += (j & 3) == 1 ? v : 0.0;
                 acc[2] += (j & 3) == 2 ? v : 0.0; acc[3] += (j & 3) == 3 ? v : 0.0;
             }
-#pragma unroll
-            for (int u = 0; u < KREG; ++u) sv[u] = 0.0f;
             sv[0] = finish_score(sg, n_q, (acc[0] + acc[1]) + (acc[2] + acc[3]), hn);
             if (tid < n) s[tid] = sv[0];
         } else {
 #pragma unroll
-            for (int u = 0; u < KREG; ++u) sv[u] = (tid + 1024 * u < n) ? s[tid + 1024 * u] : 0.0f;   // all in flight
+            for (int u = 0; u < KREG; ++u) sv[u] = have(u) ? s[i0 + 64 * u + lane] : 0.0f;   // all in flight
         }
 #pragma unroll
-        for (int u = 0; u < KREG; ++u) {
-            kreg[u] = ordered_key(sv[u]);
-            if (tid + 1024 * u < n) s_key[tid + 1024 * u] = kreg[u];
-        }
-        for (int i = tid + 1024 * KREG; i < n; i += 1024) s_key[i] = ordered_key(s[i]);
-        __syncthreads();
+        for (int u = 0; u < KREG; ++u) kreg[u] = ordered_key(sv[u]);
     }
 
     const int m_rank = prune_rank(sg.lambda, n);
@@ -654,49 +673,40 @@ __global__ __launch_bounds__(1024) void score_prune_kernel(Batch bt, FinishArgs 
     // Selection in one histogram where that works: the keys of a sample share their leading bits
     // (scores of one image lie within a few binades), so the 4096 bins are laid over the range the
     // keys actually span, [smallest, largest]; the bin that holds rank k then has a handful of keys,
-    // and one wavefront finds the wanted one among them by counting.  More than 64 keys in that bin
+    // among which every wavefront finds the wanted one.  More than 64 keys in that bin
     // (ties, non-finite values that stretch the range): the radix select below does the whole job.
-    bool selected = false;
+    bool selected = false, finite;
     {
-        uint32_t kmin = 0xFFFFFFFFu, kmax = 0u;
+        uint32_t kinv = 0u, kmax = 0u;                                       // (largest complement: the smallest key)
 #pragma unroll
         for (int r = 0; r < KREG; ++r)
-            if (tid + 1024 * r < n) { kmin = min(kmin, kreg[r]); kmax = max(kmax, kreg[r]); }
-        for (int i = tid + 1024 * KREG; i < n; i += 1024) { const uint32_t u = s_key[i]; kmin = min(kmin, u); kmax = max(kmax, u); }
-#pragma unroll
-        for (int sft = 32; sft >= 1; sft >>= 1) {
-            kmin = min(kmin, (uint32_t)__shfl_xor((int)kmin, sft, 64));
-            kmax = max(kmax, (uint32_t)__shfl_xor((int)kmax, sft, 64));
-        }
-        if (lane == 0) { s_mm[0][wave] = kmin; s_mm[1][wave] = kmax; }
-        for (int i = tid; i < 256 * 16; i += 1024) s_hist[i] = 0;
-        if (tid == 0) s_ncand = 0;
+            if (have(r)) { kinv = max(kinv, ~kreg[r]); kmax = max(kmax, kreg[r]); }
+        kinv = wave_max_u32(kinv);
+        kmax = wave_max_u32(kmax);
+        if (lane == 0) { s_mm[0][wave] = kinv; s_mm[1][wave] = kmax; }
+        *(int4*)&s_hist[4 * tid] = make_int4(0, 0, 0, 0);
+        if (tid == 0) { s_ncand = 0; s_odd[0] = 0; s_odd[1] = 0; }
         __syncthreads();
-        kmin = s_mm[0][lane & 15];
-        kmax = s_mm[1][lane & 15];
-#pragma unroll
-        for (int sft = 8; sft >= 1; sft >>= 1) {
-            kmin = min(kmin, (uint32_t)__shfl_xor((int)kmin, sft, 64));
-            kmax = max(kmax, (uint32_t)__shfl_xor((int)kmax, sft, 64));
-        }
+        const uint32_t kmin = ~(uint32_t)lane0_of((int)row_max_u32(s_mm[0][lane & 15]));
+        kmax = (uint32_t)lane0_of((int)row_max_u32(s_mm[1][lane & 15]));
+        finite = kmin > ordered_key(-INFINITY) && kmax < ordered_key(INFINITY);        // (NaN is beyond either)
         const uint32_t range = kmax - kmin;
         const int nbits = range ? 32 - __builtin_clz(range) : 0;
         const int bshift = nbits > 12 ? nbits - 12 : 0;                  // (key - kmin) >> bshift < 4096
 #pragma unroll
         for (int r = 0; r < KREG; ++r)
-            if (tid + 1024 * r < n) atomicAdd(&s_hist[(kreg[r] - kmin) >> bshift], 1);
-        for (int i = tid + 1024 * KREG; i < n; i += 1024) atomicAdd(&s_hist[(s_key[i] - kmin) >> bshift], 1);
+            if (have(r)) atomicAdd(&s_hist[(kreg[r] - kmin) >> bshift], 1);
         __syncthreads();
         // exclusive scan over the bins, four per thread
-        const int c0 = s_hist[4 * tid], c1 = s_hist[4 * tid + 1], c2 = s_hist[4 * tid + 2], c3 = s_hist[4 * tid + 3];
-        const int loc = c0 + c1 + c2 + c3;
+        const int4 c4 = *(const int4*)&s_hist[4 * tid];
+        const int c[4] = {c4.x, c4.y, c4.z, c4.w};
+        const int loc = c4.x + c4.y + c4.z + c4.w;
         const int inc = wave_scan_incl_i32(loc);
-        if (lane == 63) s_wtot[wave] = inc;
+        if (lane == 63) s_wtot[0][wave] = inc;
         __syncthreads();
-        int e = inc - loc;
-        for (int w = 0; w < wave; ++w) e += s_wtot[w];
-        {
-            const int c[4] = {c0, c1, c2, c3};
+        int all;
+        int e = counts_before(s_wtot[0], lane, wave, all) + inc - loc;
+        if (k >= e && k < e + loc) {
 #pragma unroll
             for (int t = 0; t < 4; ++t) {
                 if (k >= e && k < e + c[t]) { s_sel[0][0] = 4 * tid + t; s_sel[0][1] = k - e; s_sel[1][0] = c[t]; }
@@ -704,31 +714,24 @@ __global__ __launch_bounds__(1024) void score_prune_kernel(Batch bt, FinishArgs 
             }
         }
         __syncthreads();
-        const int sel = s_sel[0][0], kk = s_sel[0][1], ncand = s_sel[1][0];
+        const int sel = lane0_of(s_sel[0][0]), kk = lane0_of(s_sel[0][1]), ncand = lane0_of(s_sel[1][0]);
         if (ncand <= 64) {                                                   // (uniform)
 #pragma unroll
             for (int r = 0; r < KREG; ++r)
-                if (tid + 1024 * r < n && (int)((kreg[r] - kmin) >> bshift) == sel) s_cand[atomicAdd(&s_ncand, 1)] = kreg[r];
-            for (int i = tid + 1024 * KREG; i < n; i += 1024) {
-                const uint32_t u = s_key[i];
-                if ((int)((u - kmin) >> bshift) == sel) s_cand[atomicAdd(&s_ncand, 1)] = u;
-            }
+                if (have(r) && (int)((kreg[r] - kmin) >> bshift) == sel) s_cand[atomicAdd(&s_ncand, 1)] = kreg[r];
             __syncthreads();
-            if (wave == 0) {
-                const uint32_t v = lane < ncand ? s_cand[lane] : 0xFFFFFFFFu;
-                int below = 0, equal = 0;
-                for (int j = 0; j < ncand; ++j) {
-                    const uint32_t u = s_cand[j];
-                    below += u < v;
-                    equal += u == v;
-                }
-                if (lane < ncand && below <= kk && kk < below + equal) s_mm[0][0] = v;   // (the same value from every lane that qualifies)
+            // (counted one by one: by the bits in which they can differ, a ballot each, took 1.3 us longer for 3 candidates and 0.4 less for 40)
+            const uint32_t v = lane < ncand ? s_cand[lane] : 0xFFFFFFFFu;
+            int below = 0, equal = 0;
+            for (int j = 0; j < ncand; ++j) {
+                const uint32_t u = (uint32_t)__builtin_amdgcn_readlane((int)v, j);
+                below += u < v;
+                equal += u == v;
             }
-            __syncthreads();
-            prefix = s_mm[0][0];
+            const uint64_t found = __ballot(lane < ncand && below <= kk && kk < below + equal);      // (lanes of the same value)
+            prefix = (uint32_t)__builtin_amdgcn_readlane((int)v, found ? __builtin_ctzll(found) : 0);
             selected = true;
-        }
-        __syncthreads();                   // (s_hist, s_sel and s_wtot are used again below)
+        } else __syncthreads();            // (s_hist and s_sel are used again below)
     }
     if (!selected) {
     // Radix select, 8 bits per pass from the top.  Scores of one image share their leading bits,
@@ -741,12 +744,8 @@ __global__ __launch_bounds__(1024) void score_prune_kernel(Batch bt, FinishArgs 
 #pragma unroll
         for (int r = 0; r < KREG; ++r) {
             const uint32_t u = kreg[r];
-            if (tid + 1024 * r < n && (u & mask) == prefix)
+            if (have(r) && (u & mask) == prefix)
                 atomicAdd(&s_hist[(((u >> shift) & 255) << 4) + (lane & 15)], 1);
-        }
-        for (int i = tid + 1024 * KREG; i < n; i += 1024) {
-            const uint32_t u = s_key[i];
-            if ((u & mask) == prefix) atomicAdd(&s_hist[(((u >> shift) & 255) << 4) + (lane & 15)], 1);
         }
         __syncthreads();
         if (tid < 256) {                   // sum the 16 copies of a bin and leave them cleared for the next pass
@@ -781,33 +780,25 @@ __global__ __launch_bounds__(1024) void score_prune_kernel(Batch bt, FinishArgs 
     }
     const uint32_t tau = prefix;
 
-    // Ordered split (Eq. 3 / 4): wavefront w owns a contiguous range of tokens; a ballot per 64
-    // tokens gives each its place, so both index lists are written in coalesced runs.
-    const int per_wave = ((n + 15) / 16 + 63) / 64 * 64;
-    const int i0 = min(n, wave * per_wave), i1 = min(n, i0 + per_wave);
+    // Ordered split (Eq. 3 / 4): a ballot per 64 tokens gives each its place, so both index lists are written in coalesced runs.
     int cnt = 0;
-    for (int i = i0; i < i1; i += 64) {
-        const int t = i + lane;
-        cnt += __popcll(__ballot(t < i1 && s_key[t] >= tau));
-    }
-    if (lane == 0) s_wtot[wave] = cnt;
-    if (tid == 0) { s_odd[0] = 0; s_odd[1] = 0; }
+#pragma unroll
+    for (int r = 0; r < KREG; ++r) cnt += __popcll(__ballot(have(r) && kreg[r] >= tau));
+    if (lane == 0) s_wtot[1][wave] = cnt;
     __syncthreads();
     // the threshold as a score again (inverse of ordered_key), for the two counters of the report
     const float tau_f = __uint_as_float((tau & 0x80000000u) ? (tau & 0x7FFFFFFFu) : ~tau);
     const double tau_band = 1e-6 * fabs((double)tau_f);
-    int n_near = 0, n_bad = 0;
-    int kp = 0, total = 0;
-    for (int w = 0; w < 16; ++w) {
-        if (w < wave) kp += s_wtot[w];
-        total += s_wtot[w];
-    }
+    int n_near = 0, n_bad = 0, total;
+    int kp = counts_before(s_wtot[1], lane, wave, total);
     int32_t* ko = kept_idx + sg.base;
     int32_t* po = pruned_idx + sg.base;
-    for (int i = i0; i < i1; i += 64) {
-        const int t = i + lane;
-        const bool in = t < i1;
-        const uint32_t key = in ? s_key[t] : tau;
+#pragma unroll
+    for (int r = 0; r < KREG; ++r) {
+        if (i0 + 64 * r >= i1) break;                            // (uniform)
+        const int t = i0 + 64 * r + lane;
+        const bool in = have(r);
+        const uint32_t key = in ? kreg[r] : tau;
         const bool keep = in && key >= tau;
         const uint64_t m = __ballot(keep);
         const int below = __popcll(m & ((1ull << lane) - 1ull));
@@ -815,8 +806,10 @@ __global__ __launch_bounds__(1024) void score_prune_kernel(Batch bt, FinishArgs 
         else if (in) po[t - (kp + below)] = t;
         kp += __popcll(m);
         const float f = __uint_as_float((key & 0x80000000u) ? (key & 0x7FFFFFFFu) : ~key);
-        n_near += __popcll(__ballot(key != tau && fabs((double)f - (double)tau_f) <= tau_band));
-        n_bad += __popcll(__ballot(in && !isfinite(f)));
+        // (the band in fp32 with something to spare first: hardly any score is inside it)
+        const bool maybe = key != tau && !(fabsf(f - tau_f) > 1.01e-6f * fabsf(tau_f));
+        if (__any(maybe)) n_near += __popcll(__ballot(maybe && fabs((double)f - (double)tau_f) <= tau_band));
+        if (!finite) n_bad += __popcll(__ballot(in && !isfinite(f)));
     }
     if (lane == 0 && (n_near | n_bad)) { atomicAdd(&s_odd[0], n_near); atomicAdd(&s_odd[1], n_bad); }
     __syncthreads();
@@ -948,20 +941,21 @@ int launch_score(const Batch& bt, const Ws& w, const ScoreIn& in, float* scores,
 // clustering follows.
 int launch_score_prune(const Batch& bt, const Ws* unfinished, int n_q, float* scores, uint64_t* adj, int32_t* kept_idx,
                        int32_t* pruned_idx, pact_report* rep, hipStream_t st) {
-    const size_t lds = (size_t)((bt.n_max + 63) / 64 * 64) * sizeof(uint32_t);
+#define PACT_PRUNE(FINISH, KREG, fin)                                                                                          \
+    PACT_LAUNCH("score_prune", (score_prune_kernel<FINISH, KREG>), dim3(bt.B), dim3(1024), st, bt, fin, scores, adj, kept_idx, \
+                pruned_idx, rep)
     if (unfinished && finish_in_prune(bt, n_q)) {
         const FinishArgs fin{unfinished->logits, unfinished->hnorm, unfinished->sm_part, n_q};
-        PACT_LAUNCH_SHMEM("score_prune", score_prune_kernel<true>, dim3(bt.B), dim3(1024), lds, st, bt, fin, scores, adj,
-                          kept_idx, pruned_idx, rep);
+        PACT_PRUNE(true, 1, fin);
         return PACT_OK;
     }
-    static size_t raised = 0;
-    if (lds > 48 * 1024 && lds > raised) {
-        if (raise_lds_limit((const void*)score_prune_kernel<false>, lds) != hipSuccess) return PACT_ERR_HIP;
-        raised = lds;
-    }
-    PACT_LAUNCH_SHMEM("score_prune", score_prune_kernel<false>, dim3(bt.B), dim3(1024), lds, st, bt, FinishArgs{}, scores, adj,
-                      kept_idx, pruned_idx, rep);
+    const FinishArgs none{};
+    static_assert(PACT_MAX_TOKENS <= 1024 * 32, "a sample's keys in the registers of one workgroup");
+    if (bt.n_max <= 1024 * 4) PACT_PRUNE(false, 4, none);
+    else if (bt.n_max <= 1024 * 8) PACT_PRUNE(false, 8, none);
+    else if (bt.n_max <= 1024 * 16) PACT_PRUNE(false, 16, none);
+    else PACT_PRUNE(false, 32, none);
+#undef PACT_PRUNE
     return PACT_OK;
 }
 
