@@ -169,6 +169,21 @@ template <int L> __device__ __forceinline__ void file_ballots2(uint32_t& lo, uin
           "s"((uint32_t)h0), "s"((uint32_t)(h0 >> 32)), "s"((uint32_t)h1), "s"((uint32_t)(h1 >> 32)),
           "n"(L), "n"(L + 4));
 }
+// bits = bits * 16 + (a >= t) * 8 + (b >= t) * 4 + (c >= t) * 2 + (d >= t): two instructions a comparison, the bit coming in as a carry.
+// (The comparisons go ahead of the additions: a scalar written by a vector instruction is not to be read by the next two.)
+__device__ __forceinline__ void shift_in_ge(uint32_t& bits, float a, float b, float c, float d, float t) {
+    uint64_t ca, cb, cc, cd;
+    asm("v_cmp_ge_f32 %1, %5, %9\n\t"
+        "v_cmp_ge_f32 %2, %6, %9\n\t"
+        "v_cmp_ge_f32 %3, %7, %9\n\t"
+        "v_cmp_ge_f32 %4, %8, %9\n\t"
+        "v_addc_co_u32 %0, vcc, %0, %0, %1\n\t"
+        "v_addc_co_u32 %0, vcc, %0, %0, %2\n\t"
+        "v_addc_co_u32 %0, vcc, %0, %0, %3\n\t"
+        "v_addc_co_u32 %0, vcc, %0, %0, %4"
+        : "+v"(bits), "=&s"(ca), "=&s"(cb), "=&s"(cc), "=&s"(cd)
+        : "v"(a), "v"(b), "v"(c), "v"(d), "v"(t) : "vcc");
+}
 // Two values per lane, to be summed over pairs of lanes 16 apart: lanes with bit 4 clear get a's
 // sum, the others b's (v_permlane16_swap exchanges the odd rows of 16 lanes of one register with the even
 // rows of the other).
@@ -783,29 +798,50 @@ __global__ __launch_bounds__(SH::THREADS, SH::WAVES_PER_SIMD) void gram_kernel(B
 #pragma unroll
                     for (int r = 0; r < 16; ++r)
                         rs[i2][r] = sRinv[wr * WROWS + gi * 64 + i2 * 32 + 8 * (r >> 2) + 4 * hh + (r & 3)];
-#pragma unroll
-                for (int j = 0; j < NJ; ++j) {
-                    float lb = -INFINITY;
+                if (rowG + 64 > nA) {                                      // (the last group only)
 #pragma unroll
                     for (int i2 = 0; i2 < 2; ++i2)
 #pragma unroll
                         for (int r = 0; r < 16; ++r) {
                             const bool pad = rowG + i2 * 32 + 8 * (r >> 2) + 4 * hh + (r & 3) >= nA;
-                            const float v = pad ? -INFINITY : acc[2 * gi + i2][j][r] * rs[i2][r] * rj[j];
-                            acc[2 * gi + i2][j][r] = v;
-                            lb = fmaxf(lb, v);
+#pragma unroll
+                            for (int j = 0; j < NJ; ++j) acc[2 * gi + i2][j][r] = pad ? -INFINITY : acc[2 * gi + i2][j][r];
+                            rs[i2][r] = pad ? 1.0f : rs[i2][r];
                         }
-                    lb = fmaxf(lb, __shfl_xor(lb, 32, 64));
-                    const float cut = fmaxf(lb - two_m, t_lo);
+                }
+#pragma unroll
+                for (int j = 0; j < NJ; ++j) {
+                    // The column's own factor is left out of the 32 products: the largest cosine is the largest of them times it (a rounded
+                    // product is monotonic), and the lower bound is divided by it, with more to spare than the roundings take: a
+                    // bit more there is one more look in fp64.  (8 videos 57.5 -> 53 us, 16 ragged images 52.5 -> 49, the image 16.3 -> 15.1: half of
+                    // the epilogue's instructions; the scaling of the column, the test for the last row and a three-instruction bit are gone.)
+                    float top = -INFINITY;
+#pragma unroll
+                    for (int i2 = 0; i2 < 2; ++i2)
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) {
+                            acc[2 * gi + i2][j][r] *= rs[i2][r];
+                            top = fmaxf(top, acc[2 * gi + i2][j][r]);
+                        }
+                    const auto tops = __builtin_amdgcn_permlane32_swap(__float_as_uint(top), __float_as_uint(top), false, false);
+                    const float lb = fmaxf(fmaxf(__uint_as_float(tops[0]), __uint_as_float(tops[1])) * rj[j], -INFINITY);      // (no NaN)
+                    const float cut = fmaxf(lb - two_m, t_lo), inv = __builtin_amdgcn_rcpf(rj[j]), at = cut * inv;
+                    float cutv = at - fmaxf(fabsf(at) * 0x1p-20f, inv * 1e-37f);
+                    if (!(fabsf(cutv) < INFINITY)) cutv = -INFINITY;       // (a zero vector, or nearly infinite ones: all are candidates)
                     uint32_t w32[2];
 #pragma unroll
                     for (int i2 = 0; i2 < 2; ++i2) {
+                        // the 16 comparisons shift into a word, the last row first; then four bits to every other nibble
                         uint32_t bits = 0u;
 #pragma unroll
-                        for (int r = 0; r < 16; ++r)
-                            bits |= (acc[2 * gi + i2][j][r] >= cut) ? (1u << (8 * (r >> 2) + (r & 3))) : 0u;
-                        bits <<= 4 * hh;
-                        w32[i2] = bits | (uint32_t)__shfl_xor((int)bits, 32, 64);
+                        for (int r = 12; r >= 0; r -= 4) {
+                            const f32x16_t& v = acc[2 * gi + i2][j];
+                            shift_in_ge(bits, v[r + 3], v[r + 2], v[r + 1], v[r], cutv);
+                        }
+                        bits = (bits | (bits << 8)) & 0x00FF00FFu;
+                        bits = ((bits | (bits << 4)) & 0x0F0F0F0Fu) << (4 * hh);
+                        const auto both = __builtin_amdgcn_permlane32_swap(bits, bits, false, false);
+                        w32[i2] = both[0] | both[1];
                     }
                     if (hh == j && colP[j] < nB) {
                         cb[(size_t)(rowG >> 6) * bt.n_max + colP[j]] = lb;
