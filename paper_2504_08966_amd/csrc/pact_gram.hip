@@ -13,7 +13,7 @@
 //  * a workgroup of WR x WC wavefronts owns a (32*MI*WR) x (32*NJ*WC) output tile, each wavefront MI x NJ
 //    32 x 32 accumulators.  bf16 keys (v_mfma_f32_32x32x16_bf16): 128x128 by 4 wavefronts, two workgroups per CU;
 //    256x256 by 8 wavefronts (half the L2 traffic per flop) where the turns come out better; density pass also
-//    192x192 by 4 wavefronts, where the triangle of one sample is then a single turn of the chip (see gram_cost()); 64x128 (candidate
+//    192x192 by 12 wavefronts, where the triangle of one sample is then a single turn of the chip (see gram_cost()); 64x128 (candidate
 //    pass 128x64) by 4 wavefronts where all tiles are one turn.
 //    fp32 keys (v_mfma_i32_32x32x32_i8): the same halves by 4 wavefronts, two workgroups per CU, or 128x128 by 8 wavefronts;
 //  * the key rows stream in slices straight from global memory into a ring of LDS stages
@@ -95,10 +95,11 @@ template <int DT, int MI_, int NJ_, int WR_, int WC_, int STAGES, bool TURNS> st
     static constexpr int AHEAD = NSTAGE - 1;                             // slices in flight besides the one being multiplied
     static constexpr int NB = STAGE_BYTES / 1024 / WAVES;                // 1 KB blocks each wavefront brings per stage
     // workgroups of a launch: one per CU, or two where the registers and the ring leave room for them
-    static constexpr bool PAIRED = WAVES == 4 && MI * NJ <= 4;
+    static constexpr bool PAIRED = (WAVES == 4 && MI * NJ <= 4) || (WAVES == 8 && MI * NJ <= 2 && !TURNS);
     static constexpr int SLOT_BITS = PAIRED ? 9 : 8, SLOTS = 1 << SLOT_BITS;
-    static constexpr int WAVES_PER_SIMD = PAIRED || WAVES == 8 ? 2 : 1;
-    static_assert(SLOTS * WAVES <= GRAM_MAX_WORKGROUPS * 8, "a workgroup of eight wavefronts per CU, or two of four");
+    static constexpr int WAVES_PER_SIMD = PAIRED ? WAVES / 2 : WAVES / 4;
+    // words of the distance statistic per workgroup: one per wavefront, or per several
+    static constexpr int STAT_WORDS = GRAM_MAX_WORKGROUPS * 8 / SLOTS < WAVES ? GRAM_MAX_WORKGROUPS * 8 / SLOTS : WAVES;
     static constexpr bool PINGPONG = TURNS;
     static_assert(!TURNS || WAVES == 8, "one wavefront of either group per SIMD");
     // k-groups per slice; k-groups per turn
@@ -118,6 +119,7 @@ template <int DT, int MI_, int NJ_, int WR_, int WC_, int STAGES, bool TURNS> st
 };
 
 typedef __attribute__((address_space(3))) char lds_char;
+typedef __attribute__((address_space(3))) uint32_t lds_u32;
 typedef __attribute__((address_space(3))) volatile int lds_vi32;
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) u32x4_t lds_u32x4;
@@ -278,8 +280,8 @@ __global__ __launch_bounds__(SH::THREADS, SH::WAVES_PER_SIMD) void gram_kernel(B
         G = ga.wg_count[b];
     }
     if (STAT && wg == 0)                                      // slots no workgroup of this sample writes
-        for (int k = threadIdx.x; k < (ga.stat_wgs - G) * WAVES; k += SH::THREADS)
-            ga.stat[((size_t)b * ga.stat_wgs + G) * WAVES + k] = 0u;
+        for (int k = threadIdx.x; k < (ga.stat_wgs - G) * SH::STAT_WORDS; k += SH::THREADS)
+            ga.stat[((size_t)b * ga.stat_wgs + G) * SH::STAT_WORDS + k] = 0u;
     const Seg sg = bt.s[b];
     const int q_kept = clamp_count(ga.rep[b].n_kept, sg.n);
     // density pass: kept x kept; candidate pass: rows are the centres, columns the pruned tokens
@@ -287,8 +289,7 @@ __global__ __launch_bounds__(SH::THREADS, SH::WAVES_PER_SIMD) void gram_kernel(B
     const int nA = (MODE == MODE_DENSITY) ? q_kept : clamp_count(ga.rep[b].n_centers, q_kept);
     const int nB = (MODE == MODE_DENSITY) ? q_kept : clamp_count(ga.rep[b].n_pruned, sg.n - q_kept);
     if (nA <= 0 || nB <= 0) {
-        if (STAT && (threadIdx.x & 63) == 0)
-            ga.stat[((size_t)b * ga.stat_wgs + wg) * WAVES + (threadIdx.x >> 6)] = 0u;
+        if (STAT && threadIdx.x < SH::STAT_WORDS) ga.stat[((size_t)b * ga.stat_wgs + wg) * SH::STAT_WORDS + threadIdx.x] = 0u;
         return;
     }
     const int tilesR = (nA + TILE_R - 1) / TILE_R;
@@ -1032,7 +1033,19 @@ __global__ __launch_bounds__(SH::THREADS, SH::WAVES_PER_SIMD) void gram_kernel(B
         // than the kernel); the kernel that finishes the densities takes the minimum
 #pragma unroll
         for (int sft = 32; sft >= 1; sft >>= 1) far = fminf(far, __shfl_xor(far, sft, 64));
-        if (lane == 0) ga.stat[((size_t)b * ga.stat_wgs + wg) * WAVES + wave] = far < 0.0f ? __float_as_uint(far) : 0u;
+        const uint32_t word = far < 0.0f ? __float_as_uint(far) : 0u;
+        if constexpr (SH::STAT_WORDS == WAVES) {
+            if (lane == 0) ga.stat[((size_t)b * ga.stat_wgs + wg) * WAVES + wave] = word;
+        } else {
+            __syncthreads();
+            if (lane == 0) ((lds_u32*)s_ring)[wave] = word;
+            __syncthreads();
+            if (tid < SH::STAT_WORDS) {
+                uint32_t most = 0u;                                      // (negative floats order like their bits)
+                for (int w = tid; w < WAVES; w += SH::STAT_WORDS) most = max(most, ((const lds_u32*)s_ring)[w]);
+                ga.stat[((size_t)b * ga.stat_wgs + wg) * SH::STAT_WORDS + tid] = most;
+            }
+        }
     }
 }
 
@@ -1128,7 +1141,7 @@ static int launch_gram_shape(const Batch& bt, const GramArgs& ga_in, hipStream_t
         grid = dim3(SH::SLOTS, 1);
     }
     ga.stat_wgs = grid_x;
-    if (stat_words) *stat_words = STAT ? grid_x * SH::WAVES : 0;
+    if (stat_words) *stat_words = STAT ? grid_x * SH::STAT_WORDS : 0;
     const size_t lds = SH::lds_bytes(SH::I8 ? (ga.dk + 63) / 64 : (ga.dk * 2 + SH::SLICE_BYTES - 1) / SH::SLICE_BYTES);
     static size_t raised = 0;
     if (lds > raised) {
@@ -1144,18 +1157,23 @@ static int launch_gram_shape(const Batch& bt, const GramArgs& ga_in, hipStream_t
 // The tiles of the bf16 passes.  256 x 256 has the best ratio of flops to bytes fetched; a launch lasts as many turns of
 // 20 us (key width 512) as its CUs have tiles.  Of the 128 x 128 tiles by four wavefronts a CU runs two at a time, one's
 // epilogue beside the other's multiplications: 11.4 us a turn for half the area, but a launch with
-// few tiles is over in 10, and the triangle of a sample divides better into turns.  192 x 192, four wavefronts of 3 x 3 blocks (one
-// per SIMD: 1.05 us a slice of 0.56 the area), is the best where one sample's triangle just fits one turn of it and no longer one of
-// 128s: 3969 to 4224 kept tokens (more than 31, no more than 33 tiles of 128).  Nowhere else does gram_cost() choose it, nor is it the fastest.
-// All three, event brackets in us, dbdpc_cluster on random keys and equal batches (256 / 192 / 128):
+// few tiles is over in 10, and the triangle of a sample divides better into turns.  192 x 192, twelve wavefronts of 1 x 3 blocks (three
+// per SIMD), is the best where one sample's triangle just fits one turn of it and no longer one of 128s: 3969 to 4224 kept tokens (more than 31, no
+// more than 33 tiles of 128).  Its epilogue was 11 of 21 us with four wavefronts of 3 x 3 blocks, one per SIMD, of which an instruction takes five clocks
+// and more; three side by side take 2.4 times the LDS reads, but 2 to 3 us less.
+// The first three, event brackets in us, dbdpc_cluster on random keys and equal batches (256 / 192 by four wavefronts / 128):
 //   width 512    800 tokens 21 / 20 / 13, 2000: 22 / 21 / 13, 3600: 24 / 21 / 17, 3968: 24 / 21 / 17, 4010: 24 / 21 / 26, 4224: 25 / 21 / 24,
 //                4300: 25 / 36 / 24, 5000: 25 / 35 / 27, 5632: 25 / 35 / 28, 6000: 44 / 49 / 33, 7290: 46 / 51 / 43, 9012: 64 / 79 / 60,
 //                12000: 104 / 118 / 101, 16384: 177 / 217 / 182;  2 x 3450: 25 / 37 / 29, 8 x 3450: 75 / 87 / 69, 16 x 1000: 24 / 36 / 28,
 //                16 x 2900: 101 / 134 / 99, 32 x 1450: 63 / 81 / 59
 //   width 3584   2000: 80 / 63 / 43, 4010: 95 / 65 / 112, 4600: 80 / 121 / 93, 6000: 166 / 180 / 141, 7290: 177 / 187 / 190, 8192: 259 / 244 / 239
 //   width 128    2000: 15 / 16 / 10, 4010: 17 / 17 / 18, 6000: 29 / 33 / 23, 8192: 37 / 41 / 33
-// gram_cost()'s choice is the fastest of the three within 1 us but where the triangle of 128s nearly fills its second turn (5000 to 5632
+// 192 by four -> by twelve wavefronts: image of 7290 tokens (4010 kept) 512 wide 26.1 -> 23.9, 128 wide 19.8 -> 16.6; 4010 random keys 256 wide 19.0 ->
+// 16.8, 1024: 30.2 -> 27.8, 3584: 68.2 -> 68.0.
+// gram_cost()'s choice is the fastest within 1 us but where the triangle of 128s nearly fills its second turn (5000 to 5632
 // tokens, 2 x 3450, 16 x 1000 and the like): it then takes 128 and is 2 to 4 us off.
+// Rows of up to 128 elements: 128 x 128 by eight wavefronts of 1 x 2 blocks, four per SIMD: the epilogue is most of such a tile (9000
+// tokens 21.0 -> 20.1, 16384: 43.9 -> 40.5, 8 x 6272: 55.3 -> 51.2; 512 wide 8 x 6272: 85.2 -> 88.8).
 // 64 x 128 (candidate pass 128 x 64), four wavefronts of one row (column) block: a small sample is twice as many workgroups, and a
 // wavefront's epilogue, which nothing overlaps there, is half as long.  Density / candidate pass, brackets in us, 128s -> halves, images at
 // lambda = 0.45, width 512: 729 tokens 13.1 / 11.8 -> 11.2 / 10.4, 1458: 14.2 / 12.7 -> 13.3 / 10.9, 4374: 18.7 / 13.0 -> 16.9 / 11.8;
@@ -1173,14 +1191,15 @@ static int launch_gram_shape(const Batch& bt, const GramArgs& ga_in, hipStream_t
 typedef Shape<PACT_BF16, 4, 2, 2, 4, 2, false> Tile256;
 typedef Shape<PACT_BF16, 4, 2, 2, 4, 2, true> Tile256Wide;
 typedef Shape<PACT_BF16, 2, 2, 2, 2, 2, false> Tile128;
-typedef Shape<PACT_BF16, 3, 3, 2, 2, 3, false> Tile192;        // density pass
+typedef Shape<PACT_BF16, 1, 2, 4, 2, 2, false> Tile128Narrow;  // density pass, short rows
+typedef Shape<PACT_BF16, 1, 3, 6, 2, 3, false> Tile192;        // density pass
 typedef Shape<PACT_BF16, 1, 2, 2, 2, 2, false> Tile64;         // density pass: 64 x 128
 typedef Shape<PACT_BF16, 2, 1, 2, 2, 2, false> Tile64Cand;     // candidate pass: 128 x 64 (groups of 64 rows)
 typedef Shape<PACT_I8X4, 1, 2, 4, 2, 3, true> TileI8;         // density pass
 typedef Shape<PACT_I8X4, 2, 1, 2, 4, 3, true> TileI8Cand;     // candidate pass
 typedef Shape<PACT_I8X4, 1, 2, 2, 2, 2, false> TileI8Half;     // density pass: 64 x 128
 typedef Shape<PACT_I8X4, 2, 1, 2, 2, 2, false> TileI8CandHalf; // candidate pass: 128 x 64
-constexpr int WIDE_KEYS = 1024;
+constexpr int WIDE_KEYS = 1024, NARROW_KEYS = 128;
 
 static double gram_cost(const Batch& bt, bool density, int tile, int dk, bool mirrored) {
     const int slots = tile <= 128 ? 512 : 256;
@@ -1199,7 +1218,7 @@ static double gram_cost(const Batch& bt, bool density, int tile, int dk, bool mi
         return all <= 256 ? 6.5 + 0.5 * slices : 3.0 + turns * (5.0 + 0.8 * slices);
     }
     if (tile == 256) return 2.5 + turns * (mirrored ? 12.2 + 1.25 * slices : 8.0 + 1.55 * slices);
-    if (tile == 192) return 2.8 + turns * (10.8 + 0.9 * slices);
+    if (tile == 192) return 2.8 + turns * (8.2 + 0.95 * slices);
     return all <= 256 ? 6.2 + 0.6 * slices + (mirrored && bt.B == 1 ? 2.0 : 0.0) : turns == 1 ? 9.0 + 0.7 * slices : 0.8 + turns * (5.4 + 0.73 * slices);
 }
 
@@ -1264,6 +1283,8 @@ int launch_gram_density(const Batch& bt, const Ws& w, const void* keys, pact_dty
         return launch_gram<Tile64, MODE_DENSITY>(bt, ga, st, name, m64, want_stat, stat_words);
     if (c192 < c128 && c192 < c256)
         return launch_gram<Tile192, MODE_DENSITY>(bt, ga, st, name, m192, want_stat, stat_words);
+    if (c128 < c256 && dk <= NARROW_KEYS)
+        return launch_gram<Tile128Narrow, MODE_DENSITY>(bt, ga, st, name, m128, want_stat, stat_words);
     if (c128 < c256)
         return launch_gram<Tile128, MODE_DENSITY>(bt, ga, st, name, m128, want_stat, stat_words);
     if (dk >= WIDE_KEYS) return launch_gram<Tile256Wide, MODE_DENSITY>(bt, ga, st, name, m256, want_stat, stat_words);
