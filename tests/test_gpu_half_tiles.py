@@ -1,5 +1,6 @@
 """The matrix passes in tiles of 64 x 128 (candidates: 128 x 64), at the edges of such tiles: single samples around one, two and
-several of them, mirrored and not, key rows of less than one slice to several, fp32 keys with and without the lowest byte's sweep."""
+several of them, mirrored and not, key rows of less than one slice to several, fp32 keys with and without the lowest byte's sweep.
+The density pass in tiles of 192 x 192 and, with short rows, of 128 x 128 by eight wavefronts."""
 import numpy as np
 import pytest
 import torch
@@ -17,6 +18,16 @@ pytestmark = pytest.mark.gpu
                                   (255, 128), (257, 512), (449, 64), (1025, 128), (2369, 64)])
 def test_clustering_around_the_tiles_edges(n, dk, dtype):
     # 2369 tokens: 38 x 19 tiles, more than 512: mirrored, the last square has no lower part
+    _check_clustering(n, dk, dtype)
+
+
+# short rows: 26 tiles of 128 with one token in the last, none missing, two turns of them, width 136: no longer short; 192: likewise
+@pytest.mark.parametrize("n,dk", [(3201, 8), (3201, 128), (3328, 72), (5400, 64), (3201, 136), (3969, 64), (4033, 128), (4224, 72)])
+def test_clustering_with_more_wavefronts_a_tile(n, dk):
+    _check_clustering(n, dk, "bf16")
+
+
+def _check_clustering(n, dk, dtype):
     s = _random_sample(7000 + n, n, 1, 1, dk, 64, 0.0, dtype)
     U = s.keys.reshape(n, -1).astype(np.float64)
     if dtype == "f32" and n % 2:                         # rows dominated by one element: the sweep with the lowest byte
