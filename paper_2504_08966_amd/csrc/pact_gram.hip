@@ -799,14 +799,15 @@ __global__ __launch_bounds__(SH::THREADS, SH::WAVES_PER_SIMD) void gram_kernel(B
 #pragma unroll
                     for (int r = 0; r < 16; ++r)
                         rs[i2][r] = sRinv[wr * WROWS + gi * 64 + i2 * 32 + 8 * (r >> 2) + 4 * hh + (r & 3)];
-                if (rowG + 64 > nA) {                                      // (the last group only)
+                // (the last group only; NaN: neither the largest nor, whatever the cut, a candidate)
+                if (rowG + 64 > nA) {
 #pragma unroll
                     for (int i2 = 0; i2 < 2; ++i2)
 #pragma unroll
                         for (int r = 0; r < 16; ++r) {
                             const bool pad = rowG + i2 * 32 + 8 * (r >> 2) + 4 * hh + (r & 3) >= nA;
 #pragma unroll
-                            for (int j = 0; j < NJ; ++j) acc[2 * gi + i2][j][r] = pad ? -INFINITY : acc[2 * gi + i2][j][r];
+                            for (int j = 0; j < NJ; ++j) acc[2 * gi + i2][j][r] = pad ? __builtin_nanf("") : acc[2 * gi + i2][j][r];
                             rs[i2][r] = pad ? 1.0f : rs[i2][r];
                         }
                 }
