@@ -1533,6 +1533,8 @@ struct NearArgs {
     const int32_t* idx; const uint64_t* cmask; const uint32_t* status; const int32_t* cnum; int assign_blocks;
     // recovery of pruned tokens (Eq. 8/9): the blocks before the assignment ones
     const int32_t* pruned_idx; const int32_t* center_idx; const float* cbest;
+    // small samples, which look for their candidates here: reciprocal norms, fp32 keys' byte planes
+    const float* rinv; const char* planes;
 };
 
 // Token `tok` joins cluster c (both local to the sample): the cluster's size goes up and, where
@@ -1786,6 +1788,121 @@ __device__ __forceinline__ void assign_body(const Batch& bt, const NearArgs& a, 
     }
 }
 
+// What the matrix-core pass over centres x pruned tokens leaves (MODE_CAND of gram_kernel: the same byte products, cut and margin), for 16
+// pruned tokens and in LDS: a wavefront per group of 64 centres and turn, v_mfma 16x16 straight from the key rows, 16 (fp32 keys: 12)
+// 16-byte chunks of centres in flight per lane.  Bound by its chain: lists, rows and norms, products, 100 instructions of one wavefront.  (The lists were
+// requested once their lengths were known at first: 3 us longer.)
+// tokB: this lane's token (lanes 16 apart the same), first: the centre 64 wavefront + lane, if there is such a one.
+// s_cb, s_cw: [group][16]; s_rs: [4 wavefronts][64].
+typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+typedef int i32x4_t __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) f32x4_t lds_f32x4;
+template <int DT>
+__device__ __forceinline__ void candidates_16(const NearArgs& a, const Seg& sg, int tokB, int first, int C, lds_f32* s_cb, lds_u64* s_cw,
+                                              lds_f32* s_rs) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15, kg = lane >> 4;
+    const int32_t* co = a.center_idx + sg.base;
+    const float* rinv = a.rinv + sg.base;
+    const int groups = (a.dk + 63) / 64;
+    const size_t row = DT == PACT_BF16 ? (size_t)a.dk * 2 : (size_t)groups * 256;
+    const char* kb = (DT == PACT_BF16 ? a.keys : a.planes) + (size_t)sg.base * row;
+    const float rj = rinv[tokB], t_lo = (1.0f - sg.alpha * sg.d_c) - a.margin;
+    const char* rowB = kb + (size_t)tokB * row;
+    lds_f32* rs = s_rs + wave * 64;
+    for (int c0 = wave * 64; c0 < C; c0 += 4 * 64) {
+        const int tokA = c0 + lane >= C ? 0 : c0 == wave * 64 ? first : co[c0 + lane];
+        rs[lane] = rinv[tokA];
+        const char* rowA[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) rowA[k] = kb + (size_t)__shfl(tokA, 16 * k + l16, 64) * row;
+        f32x4_t acc[4];
+        if constexpr (DT == PACT_BF16) {
+            const int nchunk = a.dk / 8;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) acc[k] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+            for (int s0 = 0; s0 < nchunk; s0 += 16) {                    // (four steps of 32 elements in flight)
+                uint4 va[4][4], vb[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int e = s0 + 4 * u + kg;
+                    const size_t o = e < nchunk ? (size_t)e * 16 : 0;
+                    vb[u] = *(const uint4*)(rowB + o);
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) va[k][u] = *(const uint4*)(rowA[k] + o);
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const bool in = s0 + 4 * u + kg < nchunk;
+                    const uint4 none = make_uint4(0, 0, 0, 0);
+#pragma unroll
+                    for (int k = 0; k < 4; ++k)
+                        acc[k] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, in ? va[k][u] : none),
+                                                                         __builtin_bit_cast(bf16x8_t, in ? vb[u] : none), acc[k], 0, 0, 0);
+                }
+            }
+        } else {
+            i32x4_t ord[3][4];
+#pragma unroll
+            for (int o = 0; o < 3; ++o)
+#pragma unroll
+                for (int k = 0; k < 4; ++k) ord[o][k] = i32x4_t{0, 0, 0, 0};
+            for (int g = 0; g < groups; ++g) {
+                i32x4_t va[4][3], vb[3];
+#pragma unroll
+                for (int pl = 0; pl < 3; ++pl) {
+                    const size_t o = (size_t)g * 192 + pl * 64 + kg * 16;
+                    vb[pl] = *(const i32x4_t*)(rowB + o);
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) va[k][pl] = *(const i32x4_t*)(rowA[k] + o);
+                }
+#pragma unroll
+                for (int o = 0; o < 3; ++o)
+#pragma unroll
+                    for (int pl = 0; pl <= o; ++pl)
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) ord[o][k] = __builtin_amdgcn_mfma_i32_16x16x64_i8(va[k][pl], vb[o - pl], ord[o][k], 0, 0, 0);
+            }
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    acc[k][r] = fmaf((float)ord[0][k][r], 16777216.0f, fmaf((float)ord[1][k][r], 65536.0f, (float)ord[2][k][r] * 256.0f));
+        }
+        // acc[k][r]: centre c0 + 16 k + 4 kg + r, token t0 + l16
+        __builtin_amdgcn_wave_barrier();                                 // (the wavefront's own part of LDS)
+        float top = -INFINITY;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const f32x4_t f = *(const lds_f32x4*)(rs + 16 * k + 4 * kg);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                acc[k][r] = c0 + 16 * k + 4 * kg + r < C ? acc[k][r] * f[r] : __builtin_nanf("");
+                top = fmaxf(top, acc[k][r]);
+            }
+        }
+        top = fmaxf(top, __shfl_xor(top, 16, 64));
+        top = fmaxf(top, __shfl_xor(top, 32, 64));
+        const float lb = fmaxf(top * rj, -INFINITY);                     // (no NaN)
+        const float cut = fmaxf(lb - 2.0f * a.margin, t_lo), inv = __builtin_amdgcn_rcpf(rj), at = cut * inv;
+        float cutv = at - fmaxf(fabsf(at) * 0x1p-20f, inv * 1e-37f);
+        if (!(fabsf(cutv) < INFINITY)) cutv = -INFINITY;
+        uint32_t lo = 0u, hi = 0u;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            lo |= (acc[0][r] >= cutv ? 1u : 0u) << r | (acc[1][r] >= cutv ? 1u : 0u) << (16 + r);
+            hi |= (acc[2][r] >= cutv ? 1u : 0u) << r | (acc[3][r] >= cutv ? 1u : 0u) << (16 + r);
+        }
+        uint64_t word = ((uint64_t)hi << 32 | lo) << (4 * kg);
+        word |= __shfl_xor(word, 16, 64);
+        word |= __shfl_xor(word, 32, 64);
+        if (kg == 0) {
+            s_cb[(c0 >> 6) * 16 + l16] = lb;
+            s_cw[(c0 >> 6) * 16 + l16] = word;
+        }
+    }
+}
+
 // Eq. 8/9: every pruned token joins the nearest centre iff its fp64 distance is below
 // alpha*d_c.  The matrix-core pass left, per pruned token t and group w of 64 centres, the
 // group's largest fp32 cosine cbest[w][t] and a word of candidates (bits of the centres within
@@ -1798,14 +1915,22 @@ __device__ __forceinline__ void assign_body(const Batch& bt, const NearArgs& a, 
 // (16 tokens per block and turn): the values and words of 64 groups arrive in one trip and are
 // kept for the listing, a candidate row in another.  Blocks blk = 0 .. nblk-1, 256 threads.
 // s_c: [16][LIST_TURN] candidate ids per token slot.
-template <int DT>
-__device__ __forceinline__ void recover_body(const Batch& bt, const NearArgs& a, int blk, int nblk, lds_i32* s_c) {
+// HERE: the candidates are found by candidates_16 (SMALL_TOKENS at most).
+template <int DT, bool HERE>
+__device__ __forceinline__ void recover_body(const Batch& bt, const NearArgs& a, int blk, int nblk, lds_i32* s_c, lds_f32* s_cb = nullptr,
+                                             lds_u64* s_cw = nullptr, lds_f32* s_rs = nullptr) {
     pact_report* rep = a.rep;
     const int b = blockIdx.y;
     const Seg sg = bt.s[b];
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int t_first = blk * 16 + (tid >> 4);
+    // (in a full reduction the lists have room for n: they go out before their lengths are known)
+    int tokB = 0, first = 0;
+    if (HERE && a.idx) {
+        tokB = a.pruned_idx[sg.base + min(blk * 16 + (tid & 15), sg.n - 1)];
+        first = a.center_idx[sg.base + min(tid, sg.n - 1)];
+    }
     const int q = clamp_count(rep[b].n_kept, sg.n), np = clamp_count(rep[b].n_pruned, sg.n - q),
               C = clamp_count(rep[b].n_centers, q);
     const size_t row_bytes = (size_t)a.dk * Elem<DT>::BYTES;
@@ -1824,8 +1949,19 @@ __device__ __forceinline__ void recover_body(const Batch& bt, const NearArgs& a,
     const uint64_t* cw = a.adj + ((size_t)b * bt.n_max + q) * bt.W; // [Wc][np]
     const int part = tid & 15, ts = tid >> 4;
     lds_i32* list = s_c + ts * LIST_TURN;
-    for (int t = t_first; t < np; t += nblk * 16) {
-        const int tok = pruned[t];
+    for (int t = t_first; HERE ? t - ts < np : t < np; t += nblk * 16) {
+        if constexpr (HERE) {
+            if (!a.idx || t != t_first) {
+                tokB = pruned[min(t - ts + part, np - 1)];
+                if (C > 0) first = co[min(tid, C - 1)];
+            }
+            if (t - ts + part >= np) tokB = 0;
+            __syncthreads();                                        // (the values of the turn before have been read)
+            if (thr > 0.0 && C > 0) candidates_16<DT>(a, sg, tokB, first, C, s_cb, s_cw, s_rs);
+            __syncthreads();
+            if (t >= np) continue;
+        }
+        const int tok = HERE ? __shfl(tokB, (lane & 48) + ts, 64) : pruned[t];
         int res = -1;                                               // -1: no centre in reach
         if (thr > 0.0 && C > 0) {
             // groups part, part + 16, .. of the first 64 with their candidate words (a word is
@@ -1837,8 +1973,13 @@ __device__ __forceinline__ void recover_body(const Batch& bt, const NearArgs& a,
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
                     const int w = wb + part + 16 * u;
-                    v[u] = w < Wc ? cb[(size_t)w * bt.n_max + t] : -INFINITY;
-                    word[u] = w < Wc ? cw[(size_t)w * np + t] : 0ull;
+                    if constexpr (HERE) {
+                        v[u] = w < Wc ? s_cb[w * 16 + ts] : -INFINITY;
+                        word[u] = w < Wc ? s_cw[w * 16 + ts] : 0ull;
+                    } else {
+                        v[u] = w < Wc ? cb[(size_t)w * bt.n_max + t] : -INFINITY;
+                        word[u] = w < Wc ? cw[(size_t)w * np + t] : 0ull;
+                    }
                 }
             };
             load_batch(0);
@@ -1892,10 +2033,10 @@ __device__ __forceinline__ void recover_body(const Batch& bt, const NearArgs& a,
 // chip holds, the last ones idle: their number is sized by n, not by the kept tokens) they
 // started 3 us late.
 // PART: NEAREST_BOTH, or a build that holds one of the two searches only (the assignment alone
-// needs fewer registers and runs four wavefronts per SIMD instead of three).
-enum { NEAREST_BOTH = 0, NEAREST_ASSIGN = 1, NEAREST_RECOVER = 2 };
+// needs fewer registers and runs four wavefronts per SIMD instead of three).  _HERE: the recovery finds its candidates itself (three per SIMD).
+enum { NEAREST_BOTH = 0, NEAREST_ASSIGN = 1, NEAREST_RECOVER = 2, NEAREST_BOTH_HERE = 3, NEAREST_RECOVER_HERE = 4 };
 template <int DT, int PART, int TPW>
-__global__ __launch_bounds__(256, 4) void nearest_centre_kernel(Batch bt, NearArgs a) {
+__global__ __launch_bounds__(256, PART >= NEAREST_BOTH_HERE ? 3 : 4) void nearest_centre_kernel(Batch bt, NearArgs a) {
     __shared__ int s_cand[4][CAND_BUF], s_ctok[4][CAND_BUF];
     __shared__ float s_ccos[4][CAND_BUF];
     __shared__ int s_list[16 * LIST_TURN];
@@ -1903,11 +2044,16 @@ __global__ __launch_bounds__(256, 4) void nearest_centre_kernel(Batch bt, NearAr
     lds_i32* cand = (lds_i32*)s_cand[wave];
     lds_i32* ctok = (lds_i32*)s_ctok[wave];
     lds_f32* ccos = (lds_f32*)s_ccos[wave];
+    constexpr bool HERE = PART == NEAREST_BOTH_HERE || PART == NEAREST_RECOVER_HERE;
+    __shared__ uint64_t s_cw[HERE ? SMALL_TOKENS / 4 : 1];
+    __shared__ float s_cb[HERE ? SMALL_TOKENS / 4 : 1];
+    __shared__ f32x4_t s_rs[HERE ? 64 : 1];
     if constexpr (PART == NEAREST_ASSIGN) assign_body<DT, TPW>(bt, a, blockIdx.x, cand, ctok, ccos, (lds_i32*)s_list);
-    else if constexpr (PART == NEAREST_RECOVER) recover_body<DT>(bt, a, blockIdx.x, gridDim.x, (lds_i32*)s_list);
+    else if constexpr (PART == NEAREST_RECOVER || PART == NEAREST_RECOVER_HERE)
+        recover_body<DT, HERE>(bt, a, blockIdx.x, gridDim.x, (lds_i32*)s_list, (lds_f32*)s_cb, (lds_u64*)s_cw, (lds_f32*)s_rs);
     else if ((int)blockIdx.x >= (int)gridDim.x - a.assign_blocks)
         assign_body<DT, TPW>(bt, a, blockIdx.x - (gridDim.x - a.assign_blocks), cand, ctok, ccos, (lds_i32*)s_list);
-    else recover_body<DT>(bt, a, blockIdx.x, gridDim.x - a.assign_blocks, (lds_i32*)s_list);
+    else recover_body<DT, HERE>(bt, a, blockIdx.x, gridDim.x - a.assign_blocks, (lds_i32*)s_list, (lds_f32*)s_cb, (lds_u64*)s_cw, (lds_f32*)s_rs);
 }
 
 template <int PART, int TPW>
@@ -1921,13 +2067,16 @@ static int launch_nearest_part(const Batch& bt, const NearArgs& a, int blocks, p
 // a.assign_blocks: whether the assignment takes part.
 static int launch_nearest(const Batch& bt, NearArgs a, int recover_blocks, pact_dtype k_dt, const char* name,
                           hipStream_t st) {
-    if (a.assign_blocks == 0) return launch_nearest_part<NEAREST_RECOVER, 1>(bt, a, recover_blocks, k_dt, name, st);
+    if (a.assign_blocks == 0)
+        return a.rinv ? launch_nearest_part<NEAREST_RECOVER_HERE, 1>(bt, a, recover_blocks, k_dt, name, st)
+                      : launch_nearest_part<NEAREST_RECOVER, 1>(bt, a, recover_blocks, k_dt, name, st);
     const bool four = recover_blocks == 0 && kept_estimate(bt) > 8192;            // (see assign_body)
     a.assign_blocks = (bt.n_max + (four ? 15 : 3)) / (four ? 16 : 4);
     if (recover_blocks == 0)
         return four ? launch_nearest_part<NEAREST_ASSIGN, 4>(bt, a, a.assign_blocks, k_dt, name, st)
                     : launch_nearest_part<NEAREST_ASSIGN, 1>(bt, a, a.assign_blocks, k_dt, name, st);
-    return launch_nearest_part<NEAREST_BOTH, 1>(bt, a, a.assign_blocks + recover_blocks, k_dt, name, st);
+    return a.rinv ? launch_nearest_part<NEAREST_BOTH_HERE, 1>(bt, a, a.assign_blocks + recover_blocks, k_dt, name, st)
+                  : launch_nearest_part<NEAREST_BOTH, 1>(bt, a, a.assign_blocks + recover_blocks, k_dt, name, st);
 }
 
 // Stand-alone pact_reincorporate: totals of recovered / dropped tokens (the fused path gets
@@ -2024,13 +2173,32 @@ int launch_gram_candidates(const Batch& bt, const Ws& w, const void* keys, pact_
                            const int32_t* pruned_idx, const int32_t* center_idx, pact_report* rep,
                            hipStream_t st);
 
+// Where the recovery finds its candidates itself (candidates_16).  A workgroup fetches the rows of all centres - at most the kept tokens' - for
+// its 16 pruned tokens: the launch saved is 5 to 6 us, and 384 KB by one compute unit or 16 MB by all of them take about that long.
+// Calls, us, candidate pass -> here: width 128, 196 tokens 53.5 -> 46.5, 300: 58.1 -> 51.9, 729: 59.1 -> 55.1, 1000: 66.9 -> 59.9, 8 of 300 64.3 -> 58.2;
+// fp32 keys 56.6 -> 50.6, 59.5 -> 54.4, 71.4 -> 68.5, 71.0 -> 66.4, 70.0 -> 65.0; width 512, 196: 68.9 -> 63.0, 300: 70.3 -> 66.1, 8 of 300 104.9 -> 100.9.
+// Beyond the limits: width 512, 1000 tokens 82.0 -> 84.0, 8 of 729 119.7 -> 129.6, 32 of 729 234 -> 247; width 128, 8 of 729 79.3 -> 78.4, 32 of 729
+// 124.8 -> 123.7, with fp32 keys 94.4 -> 96.1 and 164.1 -> 164.2.
+static bool finds_candidates_there(const Batch& bt, int dk, int k_dt) {
+    if (bt.n_max > SMALL_TOKENS) return false;
+    const long row = k_dt == PACT_F32 ? (dk + 63) / 64 * 192l : dk * 2l;
+    long all = 0;
+    for (int b = 0; b < bt.B; ++b) {
+        const long pruned = prune_rank(bt.s[b].lambda, bt.s[b].n), fetched = (bt.s[b].n - pruned) * row;
+        if (fetched > 384 * 1024) return false;
+        all += (pruned + 15) / 16 * fetched;
+    }
+    return all <= 16 * 1024 * 1024;
+}
+
 // kept_idx != nullptr: the assignment of the kept tokens (deferred by launch_centres) runs in the
 // same launch as the recovery.
 int launch_reincorporate(const Batch& bt, const Ws& w, const void* keys, pact_dtype k_dt, int32_t dk,
                          const int32_t* pruned_idx, const int32_t* center_idx, int32_t* cluster_id,
                          int32_t* cluster_counts, pact_report* rep, bool count_totals,
                          const int32_t* kept_idx, hipStream_t st) {
-    int rc = launch_gram_candidates(bt, w, keys, k_dt, dk, pruned_idx, center_idx, rep, st);
+    const bool here = finds_candidates_there(bt, dk, k_dt);
+    int rc = here ? PACT_OK : launch_gram_candidates(bt, w, keys, k_dt, dk, pruned_idx, center_idx, rep, st);
     if (rc != PACT_OK) return rc;
     NearArgs a;
     std::memset(&a, 0, sizeof(a));
@@ -2038,6 +2206,7 @@ int launch_reincorporate(const Batch& bt, const Ws& w, const void* keys, pact_dt
     a.margin = (float)cos_margin(dk, k_dt);
     a.cluster_id = cluster_id; a.cluster_counts = cluster_counts;
     a.pruned_idx = pruned_idx; a.center_idx = center_idx; a.cbest = w.cbest;
+    if (here) { a.rinv = w.rinv; a.planes = w.ksplit; }
     if (kept_idx) {
         a.idx = kept_idx; a.cmask = w.cmask; a.status = w.status; a.cnum = w.cnum;
         a.assign_blocks = 1;

@@ -1,0 +1,52 @@
+"""Small samples, whose recovery finds its candidates itself: pruned tokens around multiples of 16, centres around multiples of 64 and of
+the 256 that four wavefronts take in a turn, key rows of less than one product's width to several; against the oracle, in one call and
+by the stand-alone one."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2504_08966_amd as P
+from tests import gpu_util as gu
+from tests.test_gpu_parity import _random_sample, assert_same, oracle_reduce
+
+pytestmark = pytest.mark.gpu
+
+
+def _sample(seed, n, d_h, lam, dtype):
+    """Every third token a copy of another one (several nearest centres, lowest index wins), every eleventh with a key of norm zero."""
+    s = _random_sample(seed, n, 1, 1, d_h, 64, lam, dtype)
+    s.keys[2::3] = s.keys[: len(s.keys[2::3])]
+    s.keys[10::11] = 0.0
+    return s
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("n,lam,d_h,d_c", [
+    (2, 0.5, 8, 0.3), (17, 0.9, 24, 0.1), (32, 0.5, 32, 0.01), (34, 0.5, 40, 0.01), (130, 0.5, 64, 0.9), (160, 0.6, 72, 1e-4),
+    (196, 0.45, 128, 0.02), (400, 0.35, 136, 1e-4), (405, 0.36, 256, 1e-4), (729, 0.7, 512, 0.05), (1000, 0.2, 128, 1e-5), (1024, 0.5, 8, 0.02),
+    (1024, 0.75, 128, 0.9)])
+def test_recovery_of_small_samples(n, lam, d_h, d_c, dtype):
+    s = _sample(7400 + n, n, d_h, lam, dtype)
+    o = oracle_reduce(s, d_c, lam=lam)
+    hid, ks, qs = (gu.dev(x.reshape(n, -1), dtype) for x in (s.hidden, s.keys, s.queries))
+    g = P.pact_reduce(hid, ks, ks, qs, 1, d_h, 1, P.PactParams(lam, d_c, 2.0, 1.5))
+    torch.cuda.synchronize()
+    assert_same(gu.trim(g, n), o, s, f"n={n} d_h={d_h} {dtype}")
+    # the stand-alone call on the same split and centres
+    cid = g["cluster_id"].clone()
+    cid[g["pruned_idx"][: len(o["pruned_idx"])].long()] = -1
+    P.pact_reincorporate(ks, g["pruned_idx"], g["center_idx"], d_c, 1.5, cid, g["rep"])
+    torch.cuda.synchronize()
+    assert np.array_equal(cid.cpu().numpy(), o["cluster_id"])
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("kept", [1, 63, 64, 65, 255, 256, 257, 512])
+def test_every_kept_token_a_centre(kept, dtype):
+    s = _random_sample(7500 + kept, 2 * kept, 1, 1, 64, 64, 0.5, dtype)
+    o = oracle_reduce(s, 1e-6, alpha=2e5)                             # (recovered from 0.2)
+    assert len(o["center_idx"]) == kept
+    hid, ks, qs = (gu.dev(x.reshape(2 * kept, -1), dtype) for x in (s.hidden, s.keys, s.queries))
+    g = P.pact_reduce(hid, ks, ks, qs, 1, 64, 1, P.PactParams(0.5, 1e-6, 2.0, 2e5))
+    torch.cuda.synchronize()
+    assert_same(gu.trim(g, 2 * kept), o, s, f"{kept} centres {dtype}")
