@@ -2173,20 +2173,22 @@ int launch_gram_candidates(const Batch& bt, const Ws& w, const void* keys, pact_
                            const int32_t* pruned_idx, const int32_t* center_idx, pact_report* rep,
                            hipStream_t st);
 
-// Where the recovery finds its candidates itself (candidates_16).  A workgroup fetches the rows of all centres - at most the kept tokens' - for
-// its 16 pruned tokens: the launch saved is 5 to 6 us, and 384 KB by one compute unit or 16 MB by all of them take about that long.
-// Calls, us, candidate pass -> here: width 128, 196 tokens 53.5 -> 46.5, 300: 58.1 -> 51.9, 729: 59.1 -> 55.1, 1000: 66.9 -> 59.9, 8 of 300 64.3 -> 58.2;
-// fp32 keys 56.6 -> 50.6, 59.5 -> 54.4, 71.4 -> 68.5, 71.0 -> 66.4, 70.0 -> 65.0; width 512, 196: 68.9 -> 63.0, 300: 70.3 -> 66.1, 8 of 300 104.9 -> 100.9.
-// Beyond the limits: width 512, 1000 tokens 82.0 -> 84.0, 8 of 729 119.7 -> 129.6, 32 of 729 234 -> 247; width 128, 8 of 729 79.3 -> 78.4, 32 of 729
-// 124.8 -> 123.7, with fp32 keys 94.4 -> 96.1 and 164.1 -> 164.2.
+// Where the recovery finds its candidates itself (candidates_16).  That saves a launch, 5 to 6 us; a turn of 256 centres - half of the kept tokens and
+// more are centres - costs 3, the rows of all of them by one compute unit 2 to 4.  So up to 416 kept tokens and 192 KB of rows, with fp32 keys 256
+// and 96 KB, and 16 MB over all workgroups.  Calls, us, candidate pass -> here, lambda = 0.45 where nothing else is said:
+//   width 128, 196 tokens 49.7 -> 45.6, 300: 54.7 -> 51.1, 729: 56.7 -> 54.9, 1000 at 0.6: 58.9 -> 58.4, 8 of 300 61.7 -> 58.5, 4 of 729 72.1 -> 70.2;
+//   fp32 keys 196: 52.6 -> 50.9, 300: 56.3 -> 54.4, 8 of 300 67.6 -> 64.8; width 512, 196: 65.9 -> 62.4, 300: 67.7 -> 65.5, 8 of 300 105.0 -> 100.0;
+//   beyond the limits: 729 at 0.3 53.7 -> 54.8, fp32 keys 58.7 -> 61.1, 1000: 65.6 -> 66.5; width 512, 500 at 0.6 64.2 -> 64.1, fp32 keys 196: 74.1 -> 75.5,
+//   4 of 300 100.7 -> 103.5; 8 of 729 77.8 -> 77.6.
 static bool finds_candidates_there(const Batch& bt, int dk, int k_dt) {
     if (bt.n_max > SMALL_TOKENS) return false;
-    const long row = k_dt == PACT_F32 ? (dk + 63) / 64 * 192l : dk * 2l;
+    const bool f32 = k_dt == PACT_F32;
+    const long row = f32 ? (dk + 63) / 64 * 192l : dk * 2l;
     long all = 0;
     for (int b = 0; b < bt.B; ++b) {
-        const long pruned = prune_rank(bt.s[b].lambda, bt.s[b].n), fetched = (bt.s[b].n - pruned) * row;
-        if (fetched > 384 * 1024) return false;
-        all += (pruned + 15) / 16 * fetched;
+        const long pruned = prune_rank(bt.s[b].lambda, bt.s[b].n), kept = bt.s[b].n - pruned;
+        if (kept > (f32 ? 256 : 416) || kept * row > (f32 ? 96 : 192) * 1024) return false;
+        all += (pruned + 15) / 16 * kept * row;
     }
     return all <= 16 * 1024 * 1024;
 }
