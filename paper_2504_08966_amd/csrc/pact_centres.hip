@@ -2064,19 +2064,26 @@ static int launch_nearest_part(const Batch& bt, const NearArgs& a, int blocks, p
     else PACT_LAUNCH(name, (nearest_centre_kernel<PACT_F32, PART, TPW>), grid, dim3(256), st, bt, a);
     return PACT_OK;
 }
-// a.assign_blocks: whether the assignment takes part.
+// a.assign_blocks: whether the assignment takes part.  Four tokens per wavefront in it from 8192 kept ones on (see assign_body), beside the recovery
+// from 20 000: its wavefronts then start behind the recovery's and one each is the shorter way up to that.  Both searches are always one launch.
+// Batches as two launches (with their gap left out) / one / one with four tokens per wavefront, us: width 128, 32 of 729 (12 800 kept) 21.2 / 17.3 / 18.3, 5 of
+// 5000 (13 700) 23.3 / 18.7 / 21.7, 2 of 16384 at lambda 0.5 (16 400) 30.2 / 26.5 / 31.9, 16 ragged images (21 500) 33.0 / 34.7 / 29.1, 8 of 6272 (27 600)
+// 35.1 / 34.5 / 31.0, 40 of 2915 (64 000) 57.9 / 70.0 / 54.5; width 512: 29.1 / 22.1 / 23.1, 29.2 / 23.4 / 23.2, 36.0 / 32.5 / 36.1, 46.5 / 41.2 / 40.5,
+// 46.1 / 43.3 / 40.1, 75.0 / 90.6 / 69.1; fp32 keys 33.5 / 24.4 / 25.3 to 97.7 / 102.8 / 88.2.
 static int launch_nearest(const Batch& bt, NearArgs a, int recover_blocks, pact_dtype k_dt, const char* name,
                           hipStream_t st) {
     if (a.assign_blocks == 0)
         return a.rinv ? launch_nearest_part<NEAREST_RECOVER_HERE, 1>(bt, a, recover_blocks, k_dt, name, st)
                       : launch_nearest_part<NEAREST_RECOVER, 1>(bt, a, recover_blocks, k_dt, name, st);
-    const bool four = recover_blocks == 0 && kept_estimate(bt) > 8192;            // (see assign_body)
+    const bool four = !a.rinv && kept_estimate(bt) > (recover_blocks == 0 ? 8192 : 20000);
     a.assign_blocks = (bt.n_max + (four ? 15 : 3)) / (four ? 16 : 4);
     if (recover_blocks == 0)
         return four ? launch_nearest_part<NEAREST_ASSIGN, 4>(bt, a, a.assign_blocks, k_dt, name, st)
                     : launch_nearest_part<NEAREST_ASSIGN, 1>(bt, a, a.assign_blocks, k_dt, name, st);
-    return a.rinv ? launch_nearest_part<NEAREST_BOTH_HERE, 1>(bt, a, a.assign_blocks + recover_blocks, k_dt, name, st)
-                  : launch_nearest_part<NEAREST_BOTH, 1>(bt, a, a.assign_blocks + recover_blocks, k_dt, name, st);
+    const int blocks = a.assign_blocks + recover_blocks;
+    if (a.rinv) return launch_nearest_part<NEAREST_BOTH_HERE, 1>(bt, a, blocks, k_dt, name, st);
+    return four ? launch_nearest_part<NEAREST_BOTH, 4>(bt, a, blocks, k_dt, name, st)
+                : launch_nearest_part<NEAREST_BOTH, 1>(bt, a, blocks, k_dt, name, st);
 }
 
 // Stand-alone pact_reincorporate: totals of recovered / dropped tokens (the fused path gets
@@ -2214,15 +2221,7 @@ int launch_reincorporate(const Batch& bt, const Ws& w, const void* keys, pact_dt
         a.assign_blocks = 1;
         a.slots = w.slots; a.big = w.big;     // (a full reduction: the merge follows)
     }
-    if (kept_idx && bt.total >= 20000) {
-        // Large batches are bound by how many wavefronts of these searches the chip holds: the two
-        // searches then go out as two launches, the assignment in its leaner build.  (One image:
-        // one launch, the second launch floor would cost more than the occupancy gives.)
-        NearArgs only = a;
-        only.assign_blocks = 0;
-        if ((rc = launch_nearest(bt, a, 0, k_dt, "assign", st))) return rc;
-        if ((rc = launch_nearest(bt, only, (bt.n_max + 15) / 16, k_dt, "reincorporate", st))) return rc;
-    } else if ((rc = launch_nearest(bt, a, (bt.n_max + 15) / 16, k_dt, "reinc_assign", st))) return rc;
+    if ((rc = launch_nearest(bt, a, (bt.n_max + 15) / 16, k_dt, "reinc_assign", st))) return rc;
     if (count_totals)
         PACT_LAUNCH("count_recovered", count_recovered_kernel, dim3(bt.B), dim3(1024), st, bt, rep,
                     pruned_idx, cluster_id);
