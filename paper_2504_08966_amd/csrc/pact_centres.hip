@@ -2182,11 +2182,12 @@ int launch_gram_candidates(const Batch& bt, const Ws& w, const void* keys, pact_
 
 // Where the recovery finds its candidates itself (candidates_16).  That saves a launch, 5 to 6 us; a turn of 256 centres - half of the kept tokens and
 // more are centres - costs 3, the rows of all of them by one compute unit 2 to 4.  So up to 416 kept tokens and 192 KB of rows, with fp32 keys 256
-// and 96 KB, and 16 MB over all workgroups.  Calls, us, candidate pass -> here, lambda = 0.45 where nothing else is said:
+// and 96 KB, and 12 MB over all workgroups.  Calls, us, candidate pass -> here, lambda = 0.45 where nothing else is said:
 //   width 128, 196 tokens 49.7 -> 45.6, 300: 54.7 -> 51.1, 729: 56.7 -> 54.9, 1000 at 0.6: 58.9 -> 58.4, 8 of 300 61.7 -> 58.5, 4 of 729 72.1 -> 70.2;
 //   fp32 keys 196: 52.6 -> 50.9, 300: 56.3 -> 54.4, 8 of 300 67.6 -> 64.8; width 512, 196: 65.9 -> 62.4, 300: 67.7 -> 65.5, 8 of 300 105.0 -> 100.0;
 //   beyond the limits: 729 at 0.3 53.7 -> 54.8, fp32 keys 58.7 -> 61.1, 1000: 65.6 -> 66.5; width 512, 500 at 0.6 64.2 -> 64.1, fp32 keys 196: 74.1 -> 75.5,
-//   4 of 300 100.7 -> 103.5; 8 of 729 77.8 -> 77.6.
+//   4 of 300 100.7 -> 103.5; 8 of 729 77.8 -> 77.6; the two passes alone, 16 of 729
+//   17.3 -> 19.6, 64 of 300 22.1 -> 24.2, 64 of 200 19.0 -> 18.3 (10 MB), with fp32 keys 18.4 -> 21.0 (15 MB).
 static bool finds_candidates_there(const Batch& bt, int dk, int k_dt) {
     if (bt.n_max > SMALL_TOKENS) return false;
     const bool f32 = k_dt == PACT_F32;
@@ -2197,7 +2198,7 @@ static bool finds_candidates_there(const Batch& bt, int dk, int k_dt) {
         if (kept > (f32 ? 256 : 416) || kept * row > (f32 ? 96 : 192) * 1024) return false;
         all += (pruned + 15) / 16 * kept * row;
     }
-    return all <= 16 * 1024 * 1024;
+    return all <= 12 * 1024 * 1024;
 }
 
 // kept_idx != nullptr: the assignment of the kept tokens (deferred by launch_centres) runs in the
