@@ -54,6 +54,9 @@ namespace pact {
 
 enum { MODE_DENSITY = 0, MODE_CAND = 1 };
 
+// Elements of a wide / a short key row.
+constexpr int WIDE_KEYS = 1024, NARROW_KEYS = 128;
+
 struct GramArgs {
     const char* keys;          // [total, dk]
     int32_t dk;
@@ -355,7 +358,7 @@ __global__ __launch_bounds__(SH::THREADS, SH::WAVES_PER_SIMD) void gram_kernel(B
     const long nFull = (long)tilesR * tilesC;
     const long nTri = (long)tilesC * (tilesC + 1) / 2 * RPC;              // (squares of TILE_C, each RPC tiles)
     bool sym = false;
-    if constexpr (SYM) sym = mirrored_tiles_pay(tilesC, RPC, G);
+    if constexpr (SYM) sym = mirrored_tiles_pay(tilesC, RPC, ga.dk >= WIDE_KEYS ? min(G, GRAM_MAX_WORKGROUPS) : G);
     const long nTiles = sym ? nTri : nFull;
     const bool banded = !ga.mapped && nTiles >= 8 && (G & 7) == 0;        // (a sample kept on one XCD: one band)
     const bool patch = banded && !sym && (tilesR & 1) == 0 && (tilesC & 3) == 0;   // (patches of equal size only)
@@ -1050,12 +1053,13 @@ __global__ __launch_bounds__(SH::THREADS, SH::WAVES_PER_SIMD) void gram_kernel(B
     }
 }
 
-// One sample: a workgroup per tile, at most one per CU, a multiple of the 8 XCDs (see the tile order).
+// One sample: a workgroup per tile, as many as there are slots at most, rounded up to a multiple of the 8 XCDs (see the tile order; rounded down, 28 tiles
+// were a second turn for four workgroups: clustering 400 tokens 512 wide 15.5 -> 10.9 us, with fp32 keys 23.8 -> 15.2).
 static int gram_grid_x(long tiles, int slots) {
     long grid_x = tiles;
     static_assert(GRAM_MAX_WORKGROUPS == 256, "one workgroup per CU, 256 CUs");
-    if (grid_x > slots) grid_x = slots;
-    if (grid_x >= 8) grid_x &= ~7L;
+    if (grid_x >= 8) grid_x = (grid_x + 7) & ~7L;
+    if (grid_x > slots) grid_x = slots;                      // (a multiple of 8)
     return (int)grid_x;
 }
 
@@ -1200,7 +1204,6 @@ typedef Shape<PACT_I8X4, 1, 2, 4, 2, 3, true> TileI8;         // density pass
 typedef Shape<PACT_I8X4, 2, 1, 2, 4, 3, true> TileI8Cand;     // candidate pass
 typedef Shape<PACT_I8X4, 1, 2, 2, 2, 2, false> TileI8Half;     // density pass: 64 x 128
 typedef Shape<PACT_I8X4, 2, 1, 2, 2, 2, false> TileI8CandHalf; // candidate pass: 128 x 64
-constexpr int WIDE_KEYS = 1024, NARROW_KEYS = 128;
 
 static double gram_cost(const Batch& bt, bool density, int tile, int dk, bool mirrored) {
     const int slots = tile <= 128 ? 512 : 256;
@@ -1265,16 +1268,22 @@ int launch_gram_density(const Batch& bt, const Ws& w, const void* keys, pact_dty
         const long t = (bt.n_max + tile - 1) / tile;
         bool m = bt.B > 1;
         for (int b = 0; b < bt.B; ++b)
-            m = m || mirrored_tiles_pay((int)((kept_estimate(bt.s[b]) + tile - 1) / tile), rpc, gram_grid_x(t * t * rpc, slots));
+            m = m || mirrored_tiles_pay((int)((kept_estimate(bt.s[b]) + tile - 1) / tile), rpc,
+                                        gram_grid_x(t * t * rpc, dk >= WIDE_KEYS ? GRAM_MAX_WORKGROUPS : slots));
         return m;
     };
     if (k_dt == PACT_F32) {
-        // whole tiles from eight turns of the chip on (see there)
-        const bool m = mirrored(128, 1, TileI8::SLOTS);
-        long tiles = 0;
-        for (int b = 0; b < bt.B; ++b) tiles += tiles_estimate(bt.s[b], true, 128, 128, m);
-        if (tiles > 8 * TileI8::SLOTS) return launch_gram<TileI8, MODE_DENSITY>(bt, ga, st, name, m, want_stat, stat_words);
-        return launch_gram<TileI8Half, MODE_DENSITY>(bt, ga, st, name, mirrored(128, 2, TileI8Half::SLOTS), want_stat, stat_words);
+        // whole tiles from eight turns of the chip on (see there), and where they are one turn but the halves more than one per CU (single samples of 1458
+        // tokens, halves / whole: 512 wide 20.3 / 19.7 us, 896: 29.0 / 26.5)
+        const bool m = mirrored(128, 1, TileI8::SLOTS), mh = mirrored(128, 2, TileI8Half::SLOTS);
+        long whole = 0, half = 0;
+        for (int b = 0; b < bt.B; ++b) {
+            whole += tiles_estimate(bt.s[b], true, 128, 128, m);
+            half += tiles_estimate(bt.s[b], true, 64, 128, mh);
+        }
+        if (whole > 8 * TileI8::SLOTS || (whole <= TileI8::SLOTS && half > TileI8::SLOTS && bt.B == 1))
+            return launch_gram<TileI8, MODE_DENSITY>(bt, ga, st, name, m, want_stat, stat_words);
+        return launch_gram<TileI8Half, MODE_DENSITY>(bt, ga, st, name, mh, want_stat, stat_words);
     }
     const bool m256 = mirrored(256, 1, Tile256::SLOTS), m192 = mirrored(192, 1, Tile192::SLOTS), m128 = mirrored(128, 1, Tile128::SLOTS);
     const bool m64 = mirrored(128, 2, Tile64::SLOTS);

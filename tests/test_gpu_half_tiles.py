@@ -27,6 +27,13 @@ def test_clustering_with_more_wavefronts_a_tile(n, dk):
     _check_clustering(n, dk, "bf16")
 
 
+# numbers of tiles that are no multiple of 8, or one more than a turn: 28, 66, 276 halves; wide rows, of which a turn is one tile per CU
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("n,dk", [(400, 64), (702, 128), (1458, 64), (1458, 1032), (2400, 1024)])
+def test_clustering_with_a_workgroup_for_every_tile(n, dk, dtype):
+    _check_clustering(n, dk, dtype)
+
+
 def _check_clustering(n, dk, dtype):
     s = _random_sample(7000 + n, n, 1, 1, dk, 64, 0.0, dtype)
     U = s.keys.reshape(n, -1).astype(np.float64)
