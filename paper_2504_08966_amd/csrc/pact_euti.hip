@@ -19,8 +19,10 @@ namespace pact {
 //   the other blocks                  : |h_i|_2 in fp64, one wavefront per token or, for rows of at most
 //                                       4 KB, several tokens per wavefront (eight loads in flight per lane).
 // Keys and hidden states are walked by token of the whole batch (no blocks for the tokens that
-// shorter samples do not have).  Bound by HBM: 7290 tokens of 3584 bf16 with 4 / 28 query heads 67 / 112 MB,
-// 8 x 6272 tokens 462 MB.  grid (blocks), block 256.
+// shorter samples do not have).  Bound by HBM, and nearly by the vector units (conversions to fp64): 7290 tokens of 3584 bf16 with 4 / 28 query
+// heads 67 / 112 MB, 14.7 -> 12.7 / 25.2 -> 22.9 us; 16 x 2688 tokens 396 MB in 64 us, 8 x 6272 462 MB, 89.5 -> 81 (a plain read of as much: 71); 32 x 729 of 896
+// 90 MB, 19.4 -> 18.2; 16384 of 3584 with fp32 keys 185 MB, 54.4 -> 44.8 (before: a key row at a time, longer query chunks).
+// grid (blocks), block 256.
 struct FrontArgs {
     const char* keys; int32_t dk;
     const char* q; int32_t qcols;            // q == nullptr: no query pass
@@ -30,14 +32,23 @@ struct FrontArgs {
     pact_report* rep; int32_t* cluster_id; int32_t* cluster_counts;
     const int32_t* n_idx_dev; uint32_t* zeros;
     char* ksplit;                            // fp32 keys only: the int8 planes for the Gram passes
-    int32_t mode; int32_t n_q_blocks, n_key_blocks, q_chunks, key_lanes;
+    int32_t mode; int32_t n_q_blocks, n_key_blocks, q_chunks, key_lanes, four_keys;
+    uint32_t key_share;                      // key blocks among the blocks behind the query's, in units of 2^-32, rounded up; 0: all of them first
 };
 
 // Row chunks of the query sum: 8, or 4 for wide queries, which have blocks enough (every workgroup of the logits
-// kernel reads its columns of all chunks, 32 KB); fewer for short samples (128 rows a chunk).
+// kernel reads its columns of all chunks, 32 KB); fewer for short samples (128 rows a chunk); more for long ones with narrow queries, whose few
+// blocks would each be a chain of trips of 256 rows (16384 tokens, 512 fp32 columns: 8 chunks of 2048 rows were 128 blocks of 8 trips, 22 us for 34 MB
+// and the end of a launch of 54 us; 32 chunks: 45 us; 7290 tokens 13.2 -> 12.7).
 static int query_chunks(int n_max, int qcols) {
+    if (qcols <= 1024 && n_max > 512 * QG_CHUNKS) return (n_max + 511) / 512;
     const int most = qcols > 1024 ? QG_CHUNKS / 2 : QG_CHUNKS, want = (n_max + 127) / 128;
     return want < most ? want : most;
+}
+// Where the chunks' sums are: more than QG_CHUNKS of them in the place of the predecessor lists, which are made after the sums' last use.
+static double* query_sums(const Ws& w, int chunks) {
+    static_assert(8 * 1024 / 512 <= 2 * PRED_CAP, "the sums of 512 tokens of 1024 columns take less than the tokens' lists");
+    return chunks > QG_CHUNKS ? (double*)w.preds : w.qg_part;
 }
 
 // |h_g|_2 in fp64 of TPW consecutive tokens by one wavefront, 8 / TPW independent 16-byte loads in flight per
@@ -101,6 +112,30 @@ __device__ __forceinline__ int sample_of(const Batch& bt, int g) {
     for (int step = PACT_MAX_BATCH / 2; step; step >>= 1)
         if (b + step < bt.B && bt.s[b + step].base <= g) b += step;
     return b;
+}
+
+// The bitmap is used over (kept tokens) x (kept tokens).  In a full reduction that is
+// n - m rows and columns unless scores tie at the threshold (Eq. 3 / 4); the split
+// clears the rest itself in that case.  Token i of sample b, by KL lanes.
+template <int KL>
+__device__ __forceinline__ void clear_bits(const Batch& bt, const FrontArgs& a, int b, const Seg& sg, int i, int kl) {
+    uint64_t* arow = a.adj + ((size_t)b * bt.n_max + i) * bt.W;
+    const int side = (a.mode == INIT_REDUCE) ? sg.n - prune_rank(sg.lambda, sg.n) : sg.n;
+    const int Wn = (i < side) ? (side + 63) >> 6 : 0;
+    for (int k = kl; k < Wn; k += KL) arow[k] = 0ull;
+}
+__device__ __forceinline__ void start_token(const Batch& bt, const FrontArgs& a, int b, const Seg& sg, int i, double v, float rinv) {
+    const size_t g = (size_t)sg.base + i;
+    a.nn[g] = v;
+    a.rinv[g] = rinv;
+    if (a.mode == INIT_REDUCE || a.mode == INIT_DBDPC_ALL || a.mode == INIT_DBDPC_SUBSET) {
+        a.status[(size_t)b * bt.n_max + i] = ST_UNKNOWN;
+        a.rho[(size_t)b * bt.n_max + i] = 0.0;
+        if (sg.d_n < EXACT_SUMS_D_N) a.rho_lo[(size_t)b * bt.n_max + i] = 0.0;
+        a.ident[g] = i;
+        a.cluster_id[g] = -1;
+        if (a.cluster_counts) a.cluster_counts[g] = 0;
+    }
 }
 
 // One clustering key by KL lanes (16, 32 or 64; a row of at most KL 16-byte chunks for KL < 64): the
@@ -181,24 +216,90 @@ __device__ __forceinline__ void key_job(const Batch& bt, const FrontArgs& a, int
             *(uint32_t*)(sp + (size_t)groups * 192 + e) = part[3];
         }
     }
-    // The bitmap is used over (kept tokens) x (kept tokens).  In a full reduction that is
-    // n - m rows and columns unless scores tie at the threshold (Eq. 3 / 4); the split
-    // clears the rest itself in that case.
-    uint64_t* arow = a.adj + ((size_t)b * bt.n_max + i) * bt.W;
-    const int side = (a.mode == INIT_REDUCE) ? sg.n - prune_rank(sg.lambda, sg.n) : sg.n;
-    const int Wn = (i < side) ? (side + 63) >> 6 : 0;
-    for (int k = kl; k < Wn; k += KL) arow[k] = 0ull;
-    if (kl == 0) {
-        a.nn[g] = v;
-        a.rinv[g] = rinv;
-        if (a.mode == INIT_REDUCE || a.mode == INIT_DBDPC_ALL || a.mode == INIT_DBDPC_SUBSET) {
-            a.status[(size_t)b * bt.n_max + i] = ST_UNKNOWN;
-            a.rho[(size_t)b * bt.n_max + i] = 0.0;
-            if (sg.d_n < EXACT_SUMS_D_N) a.rho_lo[(size_t)b * bt.n_max + i] = 0.0;
-            a.ident[g] = i;
-            a.cluster_id[g] = -1;
-            if (a.cluster_counts) a.cluster_counts[g] = 0;
+    clear_bits<KL>(bt, a, b, sg, i, kl);
+    if (kl == 0) start_token(bt, a, b, sg, i, v, rinv);
+}
+
+// Values of four rows per lane (v[t]: row t), each summed over KL lanes as group_sum_f64 does it (neighbours, then pairs 2, 4, 8, 16 and 32
+// apart; the same pairs, so the same bits): a lane gives up half of its rows at each of the first two steps and is left with row
+// lane & 3.  Half the instructions of four sums.
+template <int KL> __device__ __forceinline__ double four_sums(const double (&v)[4], int lane) {
+    auto halve = [&](double a, double b, bool low, auto other) __attribute__((always_inline)) {
+        const double own = low ? a : b;
+        return own + other(low ? b : a);
+    };
+    const bool e1 = (lane & 1) == 0, e2 = (lane & 2) == 0;
+    auto x1 = [](double d) __attribute__((always_inline)) { return dpp_f64<DPP_XOR1>(d); };
+    auto x2 = [](double d) __attribute__((always_inline)) { return dpp_f64<DPP_XOR2>(d); };
+    const double s0 = halve(v[0], v[1], e1, x1), s1 = halve(v[2], v[3], e1, x1);
+    double s = halve(s0, s1, e2, x2);
+    s += dpp_xor4_f64(s);
+    s += dpp_f64<0x128>(s);                                          // row_ror:8
+#pragma unroll
+    for (int sft = 16; sft < KL; sft <<= 1) s += __shfl_xor(s, sft, 64);
+    return s;
+}
+
+// bf16 keys of up to two 16-byte chunks a lane: four rows per group of KL lanes, whose chunks are requested together, and what is one value per row -
+// the square root, the reciprocal, the stores - is done for all of them at once, a row per lane.  (Row by row that is 150
+// instructions of a whole wavefront for each token, as much as the hidden states' part of the wavefronts beside it: 8 x 6272 tokens 512 wide, keys and hidden states
+// 77.5 -> 65 us, one image 13.8 -> 11.7.  fp32 keys, whose split into bytes is most of the work, and wide rows are the shorter a row at a time.)
+template <int KL>
+__device__ __forceinline__ void four_keys_job(const Batch& bt, const FrontArgs& a, int wave_no, int lane) {
+    constexpr int EPL = 8, ROWS = 64 / KL;
+    const int kl = lane & (KL - 1);
+    const int g0 = wave_no * (ROWS * 4);
+    if (g0 >= bt.total) return;
+    const int grp = KL < 64 ? lane / KL : 0;                         // this group's rows: g0 + grp + ROWS t
+    const uint4 none = make_uint4(0, 0, 0, 0);
+    uint4 c[4][2];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        const char* row = a.keys + (size_t)min(g0 + grp + ROWS * t, bt.total - 1) * (size_t)a.dk * 2;
+#pragma unroll
+        for (int u = 0; u < 2; ++u) c[t][u] = (u * KL + kl) * EPL < a.dk ? *(const uint4*)(row + (size_t)(u * KL + kl) * 16) : none;
+    }
+    const int b0 = sample_of(bt, g0);
+    double acc[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        acc[t] = 0.0;
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            if (u * KL * EPL >= a.dk) break;                         // (uniform)
+            double x[8];
+            Elem<PACT_BF16>::widen(c[t][u], x);
+#pragma unroll
+            for (int k = 0; k < EPL; ++k) acc[t] = fma(x[k], x[k], acc[t]);
         }
+    }
+    const double v = four_sums<KL>(acc, lane);                       // from here on a lane has row lane & 3 of its group's
+    const float rinv = v > 0.0 ? (float)(1.0 / sqrt(v)) : 0.0f;
+    const int mine = g0 + grp + ROWS * (lane & 3);
+    const int end = b0 + 1 < bt.B ? bt.s[b0 + 1].base : bt.total;
+    if (g0 + ROWS * 4 <= end) {                                      // all of one sample (uniform)
+        const Seg sg = bt.s[b0];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) clear_bits<KL>(bt, a, b0, sg, g0 + grp + ROWS * t - sg.base, kl);
+        if (kl < 4) start_token(bt, a, b0, sg, mine - sg.base, v, rinv);
+        return;
+    }
+    auto sample_from = [&](int g) __attribute__((always_inline)) {
+        int b = b0;
+        while (b + 1 < bt.B && bt.s[b + 1].base <= g) ++b;
+        return b;
+    };
+#pragma unroll 1
+    for (int t = 0; t < 4; ++t) {
+        const int g = g0 + grp + ROWS * t;
+        if (g < bt.total) {
+            const int b = sample_from(g);
+            clear_bits<KL>(bt, a, b, bt.s[b], g - bt.s[b].base, kl);
+        }
+    }
+    if (kl < 4 && mine < bt.total) {
+        const int b = sample_from(mine);
+        start_token(bt, a, b, bt.s[b], mine - bt.s[b].base, v, rinv);
     }
 }
 
@@ -208,13 +309,21 @@ __global__ __launch_bounds__(256) void front_kernel(Batch bt, FrontArgs a) {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int blk = blockIdx.x;
     if (blk >= a.n_q_blocks) {
-        blk -= a.n_q_blocks;
-        if (blk >= a.n_key_blocks) {
-            const int wave_no = (blk - a.n_key_blocks) * 4 + wave;
+        // key blocks: ahead of those of the hidden states, or evenly among them (see launch_front)
+        const uint32_t at = (uint32_t)(blk - a.n_q_blocks);
+        uint32_t key_no = min(at, (uint32_t)a.n_key_blocks);
+        bool keys_here = at < (uint32_t)a.n_key_blocks;
+        if (a.key_share) {
+            key_no = __umulhi(at, a.key_share);
+            keys_here = __umulhi(at + 1, a.key_share) != key_no;
+        }
+        if (!keys_here) {
+            const int wave_no = (int)(at - key_no) * 4 + wave;
             if (a.h_bf16) hnorm_job<PACT_BF16>(a, wave_no, bt.total, lane);
             else hnorm_job<PACT_F32>(a, wave_no, bt.total, lane);
             return;
         }
+        blk = (int)key_no;
         if (blk == 0) {
             if (threadIdx.x < 64) a.zeros[threadIdx.x] = 0u;
             const int b = (int)threadIdx.x;
@@ -243,7 +352,12 @@ __global__ __launch_bounds__(256) void front_kernel(Batch bt, FrontArgs a) {
             }
         }
         const int wave_no = blk * 4 + wave;
-        if (a.key_lanes == 16) key_job<KDT, 16>(bt, a, wave_no, lane);
+        if (KDT == PACT_BF16 && a.four_keys) {
+            if (a.key_lanes == 16) four_keys_job<16>(bt, a, wave_no, lane);
+            else if (a.key_lanes == 32) four_keys_job<32>(bt, a, wave_no, lane);
+            else four_keys_job<64>(bt, a, wave_no, lane);
+        }
+        else if (a.key_lanes == 16) key_job<KDT, 16>(bt, a, wave_no, lane);
         else if (a.key_lanes == 32) key_job<KDT, 32>(bt, a, wave_no, lane);
         else key_job<KDT, 64>(bt, a, wave_no, lane);
         return;
@@ -285,7 +399,7 @@ __global__ __launch_bounds__(256) void front_kernel(Batch bt, FrontArgs a) {
         double t = 0.0;
 #pragma unroll
         for (int k = 0; k < 32; ++k) t += s_part[k][threadIdx.x];
-        a.qg_part[((size_t)b * QG_CHUNKS + chunk) * a.qcols + oc] = t;
+        a.qg_part[((size_t)b * a.q_chunks + chunk) * a.qcols + oc] = t;
     }
 }
 
@@ -381,12 +495,16 @@ __global__ __launch_bounds__(256) void score_logits_kernel(Batch bt, LogitsArgs 
             const size_t at = (size_t)b * qcols + j0 * a.d_h + c;
             return a.q_bf16 ? (double)__uint_as_float((uint32_t)((const uint16_t*)a.q_given)[at] << 16) : (double)((const float*)a.q_given)[at];
         }
-        const double* in = a.qg_part + (size_t)b * QG_CHUNKS * qcols + j0 * a.d_h + c;
-        double p[QG_CHUNKS], v = 0.0;
+        const double* in = a.qg_part + (size_t)b * a.q_chunks * qcols + j0 * a.d_h + c;
+        double v = 0.0;
+#pragma unroll 1
+        for (int k0 = 0; k0 < a.q_chunks; k0 += QG_CHUNKS) {
+            double p[QG_CHUNKS];
 #pragma unroll
-        for (int k = 0; k < QG_CHUNKS; ++k) p[k] = k < a.q_chunks ? in[(size_t)k * qcols] : 0.0;
+            for (int k = 0; k < QG_CHUNKS; ++k) p[k] = k0 + k < a.q_chunks ? in[(size_t)(k0 + k) * qcols] : 0.0;
 #pragma unroll
-        for (int k = 0; k < QG_CHUNKS; ++k) v += p[k];
+            for (int k = 0; k < QG_CHUNKS; ++k) v += p[k];
+        }
         return v / (double)sg.n;
     };
     // (a head's quarters one word apart from whole multiples of the LDS banks, the heads another: 64 different banks)
@@ -848,7 +966,7 @@ int launch_front(const Batch& bt, const Ws& w, const void* keys, pact_dtype k_dt
                  int32_t* cluster_counts, int mode, const int32_t* n_idx_dev, hipStream_t st) {
     FrontArgs a = {};
     a.keys = (const char*)keys; a.dk = dk;
-    a.nn = w.nn; a.rinv = w.rinv; a.adj = w.adj; a.rho = w.rho; a.rho_lo = w.rho_lo; a.qg_part = w.qg_part; a.hnorm = w.hnorm;
+    a.nn = w.nn; a.rinv = w.rinv; a.adj = w.adj; a.rho = w.rho; a.rho_lo = w.rho_lo; a.hnorm = w.hnorm;
     a.status = w.status; a.ident = w.ident; a.near_cnt = w.near_cnt; a.tie_cnt = w.tie_cnt;
     a.rep = rep; a.cluster_id = cluster_id; a.cluster_counts = cluster_counts; a.n_idx_dev = n_idx_dev;
     a.zeros = w.zeros; a.ksplit = w.ksplit;
@@ -856,7 +974,11 @@ int launch_front(const Batch& bt, const Ws& w, const void* keys, pact_dtype k_dt
     if (keys) {
         const int chunks = dk * (k_dt == PACT_BF16 ? 2 : 4) / 16;
         a.key_lanes = chunks <= 16 ? 16 : chunks <= 32 ? 32 : 64;
-        const int per_block = 4 * (64 / a.key_lanes);
+        // Four rows per group of lanes: beside hidden states but for the smallest calls (512 wide, a row at a time / by fours: 230 tokens 4.0 / 4.4 us, 1458:
+        // 5.3 / 5.1; 2000 128 wide 4.5 / 4.1), and where one row each is more wavefronts than the chip holds (keys alone, 512 wide, 4655 tokens: 4.8 / 5.7;
+        // 7290: 6.7 / 6.2; 16384: 11.7 / 10.3).
+        a.four_keys = k_dt == PACT_BF16 && chunks <= 128 && (long)bt.total * a.key_lanes / 64 >= (score ? 400 : 6144);
+        const int per_block = 4 * (64 / a.key_lanes) * (a.four_keys ? 4 : 1);
         a.n_key_blocks = (bt.total + per_block - 1) / per_block;
     }
     int h_blocks = 0;
@@ -870,10 +992,15 @@ int launch_front(const Batch& bt, const Ws& w, const void* keys, pact_dtype k_dt
             q_dt = score->q_dt;
             a.q = (const char*)score->q; a.qcols = score->n_q * score->d_h;
             a.q_chunks = query_chunks(bt.n_max, a.qcols);
+            a.qg_part = query_sums(w, a.q_chunks);
             const int cw = 128 / (q_dt == PACT_BF16 ? 2 : 4);
             a.n_q_blocks = (a.qcols + cw - 1) / cw * a.q_chunks * bt.B;
         }
     }
+    // Long streams of hidden states: bf16 keys' blocks evenly among theirs, whose loads keep the memory busy beside the keys' arithmetic (16 x 2688 tokens 67.0 ->
+    // 64.1 us, 4 x 6272 40.9 -> 39.7); otherwise first, since their chains would be the launch's end (7290 tokens 13.2 -> 13.8, 16384 with fp32 keys 44.9 -> 46.5).
+    const uint64_t rest = (uint64_t)a.n_key_blocks + h_blocks;
+    a.key_share = k_dt == PACT_BF16 && h_blocks > 5000 ? (uint32_t)((((uint64_t)a.n_key_blocks << 32) + rest - 1) / rest) : 0u;
     dim3 grid(a.n_q_blocks + a.n_key_blocks + h_blocks);
     return (k_dt == PACT_BF16) ? launch_front_q<PACT_BF16>(bt, a, q_dt, grid, st)
                                : launch_front_q<PACT_F32>(bt, a, q_dt, grid, st);
@@ -884,8 +1011,9 @@ int launch_front(const Batch& bt, const Ws& w, const void* keys, pact_dtype k_dt
 static int launch_logits(const Batch& bt, const Ws& w, const ScoreIn& in, hipStream_t st) {
     LogitsArgs a = {};
     a.keys = (const char*)in.keys_pre; a.n_kv = in.n_kv; a.d_h = in.d_h; a.n_q = in.n_q;
-    a.qg_part = w.qg_part; a.q_given = in.q_per_token ? nullptr : (const char*)in.q; a.q_bf16 = in.q_dt == PACT_BF16;
+    a.q_given = in.q_per_token ? nullptr : (const char*)in.q; a.q_bf16 = in.q_dt == PACT_BF16;
     a.q_chunks = query_chunks(bt.n_max, in.n_q * in.d_h);
+    a.qg_part = query_sums(w, a.q_chunks);
     a.expl = w.logits; a.sm_part = w.sm_part;
     const int way = logits_way(in.n_kv, in.n_q, in.d_h, in.k_dt == PACT_BF16 ? 2 : 4), r = in.n_q / in.n_kv;
     a.kv_heads = way == BY_MFMA ? 1 : way == BY_LANES ? logits_kv_heads_lanes(bt, in.n_kv, in.d_h / (in.k_dt == PACT_BF16 ? 8 : 4))

@@ -320,6 +320,18 @@ template <int CTRL> __device__ __forceinline__ double dpp_f64(double v) {
     const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp((int)(uint32_t)(u >> 32), (int)(uint32_t)(u >> 32), CTRL, 0xF, 0xF, true);
     return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
 }
+// the value of the lane 4 apart, inside a row of 16: from above for the lanes with bit 2 clear (banks of four 0 and 2), from below for the others
+__device__ __forceinline__ double dpp_xor4_f64(double v) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+    uint32_t r[2];
+#pragma unroll
+    for (int w = 0; w < 2; ++w) {
+        const int x = (int)(uint32_t)(u >> (32 * w));
+        const int t = __builtin_amdgcn_update_dpp(x, x, 0x104, 0xF, 0x5, false);      // row_shl:4
+        r[w] = (uint32_t)__builtin_amdgcn_update_dpp(t, x, 0x114, 0xF, 0xA, false);   // row_shr:4
+    }
+    return __builtin_bit_cast(double, ((uint64_t)r[1] << 32) | r[0]);
+}
 constexpr int DPP_XOR1 = 0xB1, DPP_XOR2 = 0x4E, DPP_HALF_MIRROR = 0x141, DPP_MIRROR = 0x140;   // quad_perm [1,0,3,2], [2,3,0,1], row_half_mirror, row_mirror
 __device__ __forceinline__ double group_sum_f64(double v, int width) {
     if (width > 1) v += dpp_f64<DPP_XOR1>(v);

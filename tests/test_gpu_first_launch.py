@@ -1,0 +1,47 @@
+"""The first launch of a call: norms of four bf16 key rows per group of lanes (calls of enough rows, samples that start inside such a group), and
+the query sums of long samples, which come in more chunks.  Against a call of one sample, whose rows are taken one at a time, and the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2504_08966_amd as P
+from oracle import pact_oracle as O
+from tests import gpu_util as gu
+from tests.test_gpu_parity import _random_sample
+
+pytestmark = pytest.mark.gpu
+
+
+# 16, 32 and 64 lanes a row, one and two chunks a lane; keys alone take four rows from 6144 (64 lanes each) on, a sample of its own here never does
+@pytest.mark.parametrize("dk,n_b", [(8, 70), (128, 70), (136, 60), (256, 60), (264, 30), (512, 30), (1024, 20)])
+@pytest.mark.parametrize("d_n", [2.0, 0.1])
+def test_rows_by_fours_as_one_at_a_time(dk, n_b, d_n):
+    lens = [n_b + k % 5 for k in range(31)] + [1, 2, 3]
+    assert sum(lens) * (16 if dk <= 128 else 32 if dk <= 256 else 64) / 64 >= 400 > max(lens)
+    ss = [_random_sample(9100 + k, n, 1, 1, dk, 64, 0.3, "bf16") for k, n in enumerate(lens)]
+    hid, ks, qs = (gu.dev(np.concatenate([x(s).reshape(s.n, -1) for s in ss]), "bf16") for x in (lambda s: s.hidden, lambda s: s.keys, lambda s: s.queries))
+    ks[5] = 0                                              # a zero vector
+    off = np.concatenate([[0], np.cumsum(lens)]).astype(int)
+    prm = [P.PactParams(0.3, 0.06, d_n, 1.5) for _ in lens]
+    o = P.pact_reduce_varlen(hid, ks, ks, qs, 1, dk, 1, off.tolist(), prm)
+    torch.cuda.synchronize()
+    reps = P.read_report(o["rep"])
+    for k in range(len(lens)):
+        a, b = off[k], off[k + 1]
+        g = P.pact_reduce(hid[a:b], ks[a:b], ks[a:b], qs[a:b], 1, dk, 1, prm[k])
+        torch.cuda.synchronize()
+        rep = P.read_report(g["rep"])
+        assert all(reps[k][f] == rep[f] for f in ("n_kept", "n_centers", "n_reincorporated", "zero_norm_seen")), k
+        for name, m in (("scores", b - a), ("cluster_id", b - a), ("center_idx", rep["n_centers"]), ("merged", rep["n_centers"])):
+            assert torch.equal(o[name][a:a + m], g[name][:m]), (k, name)
+
+
+# one token more than eight chunks take, a last chunk of a few rows, and the widest queries that come in more chunks
+@pytest.mark.parametrize("n,n_kv,n_q,d_h,dtype", [(4097, 1, 1, 64, "bf16"), (4097, 2, 2, 64, "f32"), (5121, 1, 8, 128, "bf16"), (8200, 1, 4, 32, "f32")])
+def test_query_sums_of_long_samples(n, n_kv, n_q, d_h, dtype):
+    s = _random_sample(31, n, n_kv, n_q, d_h, 64, 0.4, dtype)
+    hid, ks, qs = (gu.dev(x.reshape(n, -1), dtype) for x in (s.hidden, s.keys, s.queries))
+    got = P.pact_score(hid, ks, qs, n_kv, d_h, n_q)
+    torch.cuda.synchronize()
+    want = O.euti_scores(s.hidden, s.keys, s.queries)
+    np.testing.assert_allclose(got[:n].cpu().numpy(), want, rtol=2e-7)          # one rounding to fp32: 6e-8, and the sums in fp64
