@@ -334,16 +334,17 @@ __device__ __forceinline__ double recheck_band2(float d_n) {
 // have at most three preceding neighbours, and the kernel that runs the rounds - a single
 // workgroup - then has 8 bytes per token to fetch instead of 32.  The head of a longer list starts with the densest
 // neighbour instead (the first of the list as it is ordered by position): it is a centre more often than not, and
-// the token is then decided without its record.
+// the token is then decided without its record.  Slots of a head that nothing names hold `pad`, the position behind the last one (see run_rounds).
 // GL lanes of a wavefront per token (16: four tokens per wavefront, most tokens have fewer
 // neighbours than that; 64: one).  Every lane of the wavefront takes part, with p < 0 for no token.
 // `odd` counts, per token, the neighbours whose density is too close to this token's: DETECT:
 // inside the band above; otherwise (second pass, on fp64 densities): lower-numbered neighbours with
 // a different density within 1e-11 of the sum.
 constexpr int HEAD_PREDS = 3;
+__host__ __device__ inline int positions(int n_max) { return (n_max + 63) / 64 * 64; }
 constexpr int PREDS_SPREAD = 256;      // set bits of a wavefront's row words that are spread over the lanes through LDS
 template <bool DETECT, int GL>
-__device__ __forceinline__ int preds_of_row(int p, int q, const double* r, const uint64_t* row, uint16_t* out,
+__device__ __forceinline__ int preds_of_row(int p, int q, int pad, const double* r, const uint64_t* row, uint16_t* out,
                                             uint16_t* head, volatile uint16_t* nb_wave, int lane, double band2) {
     static_assert(GL == 16 || GL == 64, "a row of lanes or the wavefront");
     constexpr int WPL = 64 / GL;                       // words per lane and turn
@@ -443,6 +444,7 @@ __device__ __forceinline__ int preds_of_row(int p, int q, const double* r, const
         const uint64_t m = group_bits(best == top);
         if (total > HEAD_PREDS && gl == __builtin_ctzll(m)) head[1] = (uint16_t)best_j;
     }
+    if (on && gl < HEAD_PREDS && gl >= total) head[1 + gl] = (uint16_t)pad;
     if (gl == 0 && on) {
         const uint16_t c = (uint16_t)(total > KP ? KP + 1 : total);
         out[0] = c;
@@ -473,7 +475,7 @@ __global__ __launch_bounds__(256) void build_preds_kernel(Batch bt, const pact_r
     if (pw >= q) return;
     const int p = pw + lane / GL < q ? pw + lane / GL : -1, pr = p < 0 ? pw : p;
     const double* r = rho + (size_t)b * bt.n_max;
-    const int odd = preds_of_row<true, GL>(p, q, r, adj + ((size_t)b * bt.n_max + pr) * bt.W,
+    const int odd = preds_of_row<true, GL>(p, q, positions(bt.n_max), r, adj + ((size_t)b * bt.n_max + pr) * bt.W,
                                            preds + ((size_t)b * bt.n_max + pr) * PRED_CAP,
                                            (uint16_t*)(heads + (size_t)b * bt.n_max + pr), s_nb[wave], lane,
                                            recheck_band2(sg.d_n));
@@ -499,10 +501,11 @@ __global__ __launch_bounds__(256) void build_preds_kernel(Batch bt, const pact_r
 //    the order has decided predecessors only, and its wavefront decides it at its next look.  What a token becomes does not
 //    depend on when it is looked at.)
 //  * Undecided tokens with more than HEAD_PREDS preceding neighbours are dealt out to groups of eight lanes, which keep
-//    a token's record and bit masks of the predecessors that may still be centres.
+//    their records.
 //  * Tokens whose list overflowed the record are evaluated from their bitmap row by a whole
 //    wavefront.
-// Bound by chains of dependent accesses.  Rounds between barriers, with work lists of the undecided tokens, took 1.7 us
+// Bound by the instructions of one compute unit and chains of dependent accesses: 4010 / 7290 / 16384 kept tokens 12.4 / 24 / 29 us from the kernel's first instruction,
+// of which the second look 2.0 / 3.9 / 8.7 and the later ones 2.3 / 7.4 / 2.3 (a comparison and a mask for every predecessor: 14.3 / 30.6 / 36 us).  Rounds between barriers, with work lists of the undecided tokens, took 1.7 us
 // each, at least four of them; statuses were read one after the other, a long record by one lane.  (The times are at the kernel.)
 // The code is loops rather than unrolled: it runs once, from a cold instruction cache.
 // dynamic LDS: rounds_lds below.
@@ -510,8 +513,8 @@ __global__ __launch_bounds__(256) void build_preds_kernel(Batch bt, const pact_r
 __host__ __device__ inline int lds_heads(int qpad) { return qpad <= 8192 ? qpad : qpad <= 16384 ? 8192 : 4096; }
 __host__ __device__ inline bool lds_tokens(int qpad) { return qpad <= 16384; }
 static size_t rounds_lds(int n_max, int W) {
-    const int qpad = (n_max + 63) / 64 * 64;
-    return (size_t)lds_heads(qpad) * 8 + ((size_t)W + 1) * 4 + (size_t)qpad * (lds_tokens(qpad) ? 5 : 3);
+    const int qpad = positions(n_max);
+    return (size_t)lds_heads(qpad) * 8 + ((size_t)W + 1) * 4 + (size_t)qpad * (lds_tokens(qpad) ? 5 : 3) + 4;
 }
 
 struct CentresArgs {
@@ -547,7 +550,7 @@ __device__ __forceinline__ int count_in(int* counter, int add, int& s_got) {
 }
 
 __device__ __forceinline__ void run_rounds(const Batch& bt, const CentresArgs& a, int b, unsigned char* s_raw,
-                                           int& s_nshort, int& s_nlong, int& s_looks) {
+                                           int& s_count, int& s_looks) {
     const Seg sg = bt.s[b];
     const int tid = fresh_v(threadIdx.x);
     const int lane = tid & 63;
@@ -556,7 +559,7 @@ __device__ __forceinline__ void run_rounds(const Batch& bt, const CentresArgs& a
     const int32_t* ix = a.idx + sg.base;
     const uint2* hd = a.heads + (size_t)b * bt.n_max;
     const int q = clamp_count(rep[b].n_kept, sg.n);
-    const int qpad = (bt.n_max + 63) / 64 * 64, Wq = (q + 63) >> 6, n_heads = lds_heads(qpad);
+    const int qpad = positions(bt.n_max), Wq = (q + 63) >> 6, n_heads = lds_heads(qpad);
     const bool tok_lds = lds_tokens(qpad);
     typedef __attribute__((address_space(3))) unsigned char lds_u8;
     typedef uint32_t head_t __attribute__((ext_vector_type(2)));
@@ -565,10 +568,14 @@ __device__ __forceinline__ void run_rounds(const Batch& bt, const CentresArgs& a
     lds_i32* s_wcnt = (lds_i32*)(s_raw + (size_t)n_heads * 8); // [W + 1]
     lds_u16* s_list = (lds_u16*)(s_wcnt + bt.W + 1);                               // [qpad] undecided tokens: short lists from the front, others from the back
     lds_u16* s_ix = s_list + qpad;                               // [qpad] token numbers (tok_lds)
-    lds_vu8* s_st = (lds_vu8*)(tok_lds ? s_ix + qpad : s_ix);    // [qpad]
+    // [qpad + 1] 1: undecided, 2: centre, 0: not one, as is the position behind the last, which stands for no predecessor: the statuses of several joined by OR say
+    // whether one is a centre and whether one is undecided.  (One compute unit does all of this, and is bound by its instructions: with a comparison
+    // for each predecessor the second look took 3 us for 4000 tokens, a later one 0.5.)
+    lds_vu8* s_st = (lds_vu8*)(tok_lds ? s_ix + qpad : s_ix);
+    constexpr unsigned char OPEN = 1, CENTRE = 2, NONE = 0;
     const lds_u8* s_rd = (const lds_u8*)s_st;                    // plain reads: independent look-ups go out together
     const uint4* rec = (const uint4*)(a.preds + (size_t)b * bt.n_max * PRED_CAP);   // 8 pieces per token
-    if (tid == 0) { s_nshort = 0; s_nlong = 0; s_looks = 0; }
+    if (tid == 0) { s_count = 0; s_looks = 0; s_st[qpad] = NONE; }
     // round 1.  (The first heads are requested before the number of kept tokens is known: they lie inside the workspace.  So are the token
     // numbers, and again where the list may end with the last kept one.)
     for (int p0 = 0; p0 < sg.n; p0 += 4096) {
@@ -582,7 +589,7 @@ __device__ __forceinline__ void run_rounds(const Batch& bt, const CentresArgs& a
         for (int u = 0; u < 4; ++u) {
             const int p = p0 + 1024 * u + tid;
             if (p < q) {
-                s_st[p] = (hv[u].x & 0xFFFFu) == 0 ? ST_CENTER : ST_UNKNOWN;
+                s_st[p] = (hv[u].x & 0xFFFFu) == 0 ? CENTRE : OPEN;
                 if (p < n_heads) s_head[p] = head_t{hv[u].x, hv[u].y};
             }
         }
@@ -601,74 +608,67 @@ __device__ __forceinline__ void run_rounds(const Batch& bt, const CentresArgs& a
         return head_t{v.x, v.y};
     };
     // one look at the up to three predecessors that a token's head names
-    auto look = [&](head_t hv, int c, bool& blocked, bool& pending) __attribute__((always_inline)) {
-        const uint32_t j[HEAD_PREDS] = {hv.x >> 16, hv.y & 0xFFFFu, hv.y >> 16};     // (slots past its count hold nothing)
-        unsigned char sj[HEAD_PREDS];
-#pragma unroll
-        for (int t = 0; t < HEAD_PREDS; ++t) sj[t] = s_rd[c > t ? j[t] : 0u];
-        blocked = pending = false;
-#pragma unroll
-        for (int t = 0; t < HEAD_PREDS; ++t) {
-            blocked |= c > t && sj[t] == ST_CENTER;
-            pending |= c > t && sj[t] == ST_UNKNOWN;
-        }
+    auto look = [&](head_t hv) __attribute__((always_inline)) {
+        return (uint32_t)s_rd[hv.x >> 16] | s_rd[hv.y & 0xFFFFu] | s_rd[hv.y >> 16];
     };
-    auto decide = [&](int p, bool blocked, bool pending) __attribute__((always_inline)) {      // whether it stays undecided
-        if (blocked) s_st[p] = ST_NOT;
-        else if (!pending) s_st[p] = ST_CENTER;
-        return !blocked && pending;
+    auto decide = [&](int p, uint32_t seen) __attribute__((always_inline)) {      // whether it stays undecided
+        if (seen != OPEN) s_st[p] = seen & CENTRE ? NONE : CENTRE;
+        return seen == OPEN;
     };
-    // the positions of one counter's new entries, a wavefront at a time
-    auto slots_of = [&](uint64_t m, int* counter) __attribute__((always_inline)) {
-        int base = 0;
-        if (lane == 0) base = atomicAdd(counter, __popcll(m));
-        return lane0_of(base) + lanes_below(m, lane);
-    };
-    // the second, and the two token lists
+    // the second, and the two token lists (a wavefront's entries at once)
 #pragma unroll 1
-    for (int p0 = 0; p0 < q; p0 += 1024) {                       // (wave-uniform trip count)
-        const int p = p0 + tid;
-        bool shrt = false, lng = false;
-        if (p < q && s_st[p] != ST_CENTER) {
-            const head_t hv = head_of(p);
-            const int c = hv.x & 0xFFFF;
-            bool blocked, pending;
-            look(hv, c, blocked, pending);
-            if (c > HEAD_PREDS) { lng = !blocked; pending = true; }
-            shrt = decide(p, blocked, pending) && !lng;
+    for (int p0 = 0; p0 < q; p0 += 2048) {                       // (wave-uniform trip count)
+        uint64_t ms[2], ml[2];
+        int n = 0;                                               // short ones, long ones << 16
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int p = p0 + 1024 * u + tid;
+            const head_t hv = head_of(min(p, q - 1));
+            const int c = p < q ? hv.x & 0xFFFF : 0;
+            const uint32_t seen = look(hv);
+            const bool lng = c > HEAD_PREDS && !(seen & CENTRE);
+            bool shrt = false;
+            if (c > 0 && !lng) shrt = decide(p, seen);
+            ms[u] = __ballot(shrt);
+            ml[u] = __ballot(lng);
+            n += __popcll(ms[u]) + (__popcll(ml[u]) << 16);
         }
-        const uint64_t ms = __ballot(shrt), ml = __ballot(lng);
-        if (ms) {
-            const int at = slots_of(ms, &s_nshort);
-            if (shrt) s_list[at] = (uint16_t)p;
-        }
-        if (ml) {
-            const int at = slots_of(ml, &s_nlong);
-            if (lng) s_list[qpad - 1 - at] = (uint16_t)p;
+        if (n == 0) continue;
+        int at = 0;
+        if (lane == 0) at = atomicAdd(&s_count, n);
+        at = lane0_of(at);
+        int at_s = at & 0xFFFF, at_l = (int)((uint32_t)at >> 16);
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int p = p0 + 1024 * u + tid;
+            if ((ms[u] >> lane) & 1ull) s_list[at_s + lanes_below(ms[u], lane)] = (uint16_t)p;
+            if ((ml[u] >> lane) & 1ull) s_list[qpad - 1 - (at_l + lanes_below(ml[u], lane))] = (uint16_t)p;
+            at_s += __popcll(ms[u]);
+            at_l += __popcll(ml[u]);
         }
     }
     __syncthreads();
-    const int nshort = s_nshort, nlong = s_nlong;
-    // A long list's token, by eight lanes, a 16-byte piece of its record each.  Bit s of a lane's `pm`: position s of its piece is a
-    // predecessor not yet found to be no centre.  Whether the token stays undecided.
+    const int nshort = s_count & 0xFFFF, nlong = (int)((uint32_t)s_count >> 16);
+    // A long list's token, by eight lanes, a 16-byte piece of its record each, in which the position behind the last stands where there is no predecessor.
+    // Whether the token stays undecided.
     const int sub = lane & 7;
-    auto piece_mask = [&](int c) __attribute__((always_inline)) {              // of the positions 1 .. c
-        const int k = c - 8 * sub;
-        return (k >= 7 ? 0xFFu : k < 0 ? 0u : (2u << k) - 1u) & (sub == 0 ? 0xFEu : 0xFFu);
-    };
-    auto look_long = [&](const uint4& v, int p, uint32_t& pm) __attribute__((always_inline)) {
+    auto piece_of = [&](const uint4& v, int c) __attribute__((always_inline)) {      // of the positions 1 .. c
         const uint32_t wv[4] = {v.x, v.y, v.z, v.w};
-        unsigned char sj[8];
+        uint32_t out[4];
 #pragma unroll
-        for (int t = 0; t < 8; ++t) sj[t] = s_rd[(pm >> t) & 1u ? (wv[t >> 1] >> ((t & 1) * 16)) & 0xFFFFu : 0u];
-        bool blocked = false;
-#pragma unroll
-        for (int t = 0; t < 8; ++t) {
-            blocked |= ((pm >> t) & 1u) && sj[t] == ST_CENTER;
-            if (sj[t] == ST_NOT) pm &= ~(1u << t);
+        for (int t = 0; t < 4; ++t) {
+            const int k = 8 * sub + 2 * t;
+            out[t] = (k >= 1 && k <= c ? wv[t] & 0xFFFFu : (uint32_t)qpad) | (k + 1 <= c ? wv[t] & 0xFFFF0000u : (uint32_t)qpad << 16);
         }
-        const bool b8 = ((__ballot(blocked) >> (lane & 56)) & 0xFFull) != 0, p8 = ((__ballot(pm != 0) >> (lane & 56)) & 0xFFull) != 0;
-        if (p >= 0 && sub == 0) decide(p, b8, p8);
+        return make_uint4(out[0], out[1], out[2], out[3]);
+    };
+    auto look_long = [&](const uint4& v, int p) __attribute__((always_inline)) {
+        const uint32_t wv[4] = {v.x, v.y, v.z, v.w};
+        uint32_t seen = 0;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) seen |= (uint32_t)s_rd[wv[t] & 0xFFFFu] | s_rd[wv[t] >> 16];
+        const bool b8 = ((__ballot((seen & CENTRE) != 0) >> (lane & 56)) & 0xFFull) != 0, p8 = ((__ballot((seen & OPEN) != 0) >> (lane & 56)) & 0xFFull) != 0;
+        if (p >= 0 && sub == 0) decide(p, b8 ? CENTRE : p8 ? OPEN : NONE);
         return !b8 && p8;
     };
     // A token whose list overflowed the record, by the whole wavefront.
@@ -685,31 +685,33 @@ __device__ __forceinline__ void run_rounds(const Batch& bt, const CentresArgs& a
                 const int j = (w << 6) + bit;
                 if (j < q && precedes(r[j], j, rp, p)) {
                     const unsigned char sj = s_st[j];
-                    blocked |= (sj == ST_CENTER);
-                    pending |= (sj == ST_UNKNOWN);
+                    blocked |= sj == CENTRE;
+                    pending |= sj == OPEN;
                 }
             }
         }
         blocked = __any(blocked);
         pending = __any(pending);
-        if (lane == 0 && (blocked || !pending)) s_st[p] = blocked ? ST_NOT : ST_CENTER;
+        if (lane == 0 && (blocked || !pending)) s_st[p] = blocked ? NONE : CENTRE;
         return !blocked && pending;
     };
     // (tokens are dealt out to all wavefronts)
     const int mine = lane * 16 + wave, mine8 = (lane >> 3) * 16 + wave;
-    int sp = -1, lp[2] = {-1, -1};                               // this thread's short-list token, its group's long-list tokens
-    bool over[2] = {false, false};                               // (one whose list overflowed)
+    constexpr int HELD = 4;                                      // long-list tokens a group keeps in its registers
+    int sp = -1, lp[HELD];                                       // this thread's short-list token, its group's long-list tokens
+    bool over[HELD];                                             // (one whose list overflowed)
     head_t sh = {0, 0};
-    uint4 lv[2];
-    uint32_t pm[2] = {0, 0};
+    uint4 lv[HELD];
 #pragma unroll
-    for (int k = 0; k < 2; ++k) {
+    for (int k = 0; k < HELD; ++k) {
+        lp[k] = -1;
+        over[k] = false;
         if (mine8 + 128 * k < nlong) {
             lp[k] = s_list[qpad - 1 - (mine8 + 128 * k)];
             lv[k] = rec[(size_t)lp[k] * 8 + sub];
             const int c = head_of(lp[k]).x & 0xFFFF;
             over[k] = c > KP;
-            pm[k] = over[k] ? 0u : piece_mask(c);
+            lv[k] = piece_of(lv[k], over[k] ? 0 : c);
         }
     }
     if (mine < nshort) {
@@ -717,31 +719,32 @@ __device__ __forceinline__ void run_rounds(const Batch& bt, const CentresArgs& a
         sh = head_of(sp);
     }
     int looks = 2;
-    bool more_short = nshort > 1024, more_long = nlong > 256;
-    while (__any(sp >= 0 || lp[0] >= 0 || lp[1] >= 0 || more_short || more_long)) {
+    bool more_short = nshort > 1024, more_long = nlong > 128 * HELD;
+    auto held = [&]() __attribute__((always_inline)) {
+        int any = -1;
+#pragma unroll
+        for (int k = 0; k < HELD; ++k) any = max(any, lp[k]);
+        return any >= 0;
+    };
+    while (__any(sp >= 0 || held() || more_short || more_long)) {
         asm volatile("" ::: "memory");                           // (the statuses are read again)
         ++looks;
         if (sp >= 0) {
-            bool blocked, pending;
-            look(sh, sh.x & 0xFFFF, blocked, pending);
-            if (!decide(sp, blocked, pending)) sp = -1;
+            if (!decide(sp, look(sh))) sp = -1;
         }
         if (more_short) {
             more_short = false;
 #pragma unroll 1
             for (int i = tid + 1024; i < nshort; i += 1024) {
                 const int p = s_list[i];
-                if (s_st[p] != ST_UNKNOWN) continue;
-                const head_t hv = head_of(p);
-                bool blocked, pending;
-                look(hv, hv.x & 0xFFFF, blocked, pending);
-                more_short |= decide(p, blocked, pending);
+                if (s_st[p] != OPEN) continue;
+                more_short |= decide(p, look(head_of(p)));
             }
         }
 #pragma unroll
-        for (int k = 0; k < 2; ++k) {
+        for (int k = 0; k < HELD; ++k) {
             if (__any(lp[k] >= 0)) {
-                const bool stays = look_long(lv[k], over[k] ? -1 : lp[k], pm[k]);
+                const bool stays = look_long(lv[k], over[k] ? -1 : lp[k]);
                 if (!over[k] && !stays) lp[k] = -1;
                 uint64_t mo = __ballot(lp[k] >= 0 && over[k] && sub == 0);
                 while (mo) {
@@ -754,15 +757,14 @@ __device__ __forceinline__ void run_rounds(const Batch& bt, const CentresArgs& a
         if (__any(more_long)) {                                  // more of them than groups hold
             more_long = false;
 #pragma unroll 1
-            for (int i0 = 256; i0 < nlong; i0 += 128) {          // (wave-uniform trip count)
+            for (int i0 = 128 * HELD; i0 < nlong; i0 += 128) {          // (wave-uniform trip count)
                 const int i = i0 + mine8, p = i < nlong ? s_list[qpad - 1 - i] : 0;
-                const bool on = i < nlong && s_st[p] == ST_UNKNOWN;
+                const bool on = i < nlong && s_st[p] == OPEN;
                 if (!__any(on)) continue;
                 const uint4 v = rec[(size_t)p * 8 + sub];
                 const int c = on ? (int)(head_of(p).x & 0xFFFF) : 0;
                 const bool ov = c > KP;
-                uint32_t m = ov ? 0u : piece_mask(c);
-                const bool stays = look_long(v, on && !ov ? p : -1, m);
+                const bool stays = look_long(piece_of(v, ov ? 0 : c), on && !ov ? p : -1);
                 more_long |= on && !ov && stays;
                 uint64_t mo = __ballot(ov && sub == 0);
                 while (mo) {
@@ -781,7 +783,7 @@ __device__ __forceinline__ void run_rounds(const Batch& bt, const CentresArgs& a
 #pragma unroll 1
     for (int w = wave; w < Wq; w += 16) {
         const int p = (w << 6) + lane;
-        const uint64_t m = __ballot(p < q && s_st[p] == ST_CENTER);
+        const uint64_t m = __ballot(p < q && s_rd[p] == CENTRE);
         if (lane == 0) { cm[w] = m; s_wcnt[w] = __popcll(m); }
     }
     __syncthreads();
@@ -807,12 +809,11 @@ __device__ __forceinline__ void run_rounds(const Batch& bt, const CentresArgs& a
 #pragma unroll 1
     for (int p0 = 0; p0 < q; p0 += 1024) {                       // (64 consecutive positions per wavefront)
         const int p = p0 + tid;
-        const unsigned char sv = p < q ? s_st[p] : (unsigned char)ST_NOT;
-        const bool isc = sv == ST_CENTER;
+        const bool isc = p < q && s_rd[p] == CENTRE;
         const uint64_t m = __ballot(isc);
         if (p < q) {
             const int c = s_wcnt[p >> 6] + lanes_below(m, lane);
-            st[p] = sv;
+            st[p] = isc ? ST_CENTER : ST_NOT;
             cn[p] = isc ? c : -1;
             if (isc) co[c] = tok_lds ? s_ix[p] : ix[p];
         }
@@ -826,14 +827,16 @@ __device__ __forceinline__ void run_rounds(const Batch& bt, const CentresArgs& a
 // supplies row l % 16 of either operand, the l / 16-th 16-byte chunk of the piece, and receives the products of listed
 // tokens 4 v + l / 16 with kept token l % 16.  (The order of the summands of a dot product is the same for every pair: equal rows give
 // equal dot products.)  The parts meet in LDS; a thread per pair takes them from there.  The next item's first rows are requested
-// before that.  Four tiles; two or one where a wavefront would have more than eight steps of 32 multiplications (bf16) to
-// do and the items are so few that every workgroup still gets at most one (3584-wide rows, 6 listed tokens: 40 -> 25 us; rows
-// of 1 KB are not worth the additional workgroups to count in).
+// before that.  Four tiles; two or one where a wavefront would have more than two steps of 32 multiplications (bf16) to
+// do and the items are so few that every workgroup still gets at most one (3584-wide rows, 6 listed tokens: 40 -> 25 us) - up to eight steps only if
+// they are for three quarters of the workgroups, all of which have to be counted in: 4010 rows of 1 KB with two / eight listed tokens, 126 items instead of 63,
+// the launch 20.0 -> 18.4 / 18.9 us, 27 samples of up to 1649 with a few 20.1 -> 17.7; 7586 rows, 238 items, 22.3 -> 23.2; one tile 20.4.
 // The sums are exact, hence the same in any order and for any two tokens with the same terms (two tokens at
 // equal distances from everything else tie exactly, as they do for a correctly rounded sum, and the index
 // decides): every term t in (0, 1] is split into hi = t rounded to a multiple of 2^-30 and lo = t - hi; sums of at
 // most 32768 such hi, and of such lo as long as t >= 2^-17 (d_n >= 0.17), fit the 53 bits of an fp64 whatever
 // their order, and the density is hi_total + lo_total, rounded once.
+__device__ __forceinline__ int items_wanted(int workers, int nchunk, int tiles) { return nchunk * tiles > 8 * 64 ? workers : workers - workers / 4; }
 typedef double f64x4_t __attribute__((ext_vector_type(4)));
 constexpr int RECHECK_LDS = 4 * 16 * 64 * 8;
 template <int DT>
@@ -1020,7 +1023,7 @@ __device__ __forceinline__ void replace_densities(const Batch& bt, const Centres
     const int n_lists = all ? q : T;
     for (int t = wave; t < n_lists; t += 16) {
         const int p = all ? t : min(list[t] & 0xFFFF, q - 1);
-        preds_of_row<false, 64>(p, q, rho_b, a.adj + ((size_t)b * bt.n_max + p) * bt.W, a.preds + ((size_t)b * bt.n_max + p) * PRED_CAP,
+        preds_of_row<false, 64>(p, q, positions(bt.n_max), rho_b, a.adj + ((size_t)b * bt.n_max + p) * bt.W, a.preds + ((size_t)b * bt.n_max + p) * PRED_CAP,
                                 (uint16_t*)(a.heads + (size_t)b * bt.n_max + p), s_nb + wave * PREDS_SPREAD, lane, 0.0);
     }
     __syncthreads();
@@ -1033,14 +1036,15 @@ __device__ __forceinline__ void replace_densities(const Batch& bt, const Centres
 // densities in place and runs the rounds again.  Nobody waits for anybody: counters say who is last.
 // As two launches, rounds with barriers after the re-evaluation (event brackets, of which either launch has 2.5 us): 4010-token
 // image 29 -> 20 us, 8 videos of 3450 tokens 48 -> 42 us, 16 ragged images 34 -> 21 us, 7290 rows of 7 KB 96 -> 36 us, 16384 tokens with fp32
-// keys 151 -> 77 us (the fp64 products of 70 listed tokens).  Bound by the selection of a sample on one CU, for the videos and the long
-// rows by the fp64 matrix products of the listed tokens.
+// keys 151 -> 77 us (the fp64 products of 70 listed tokens).  Bound by the selection of a sample on one CU, and where tokens are listed by their chain
+// (an image with two: first rows at 4 us, the products of an item 2, counted in at 12.7, looked at 15, 15.9), for the videos and the long
+// rows by the products themselves (four wavefronts per SIMD, 9 us an item of four tiles).
 // tie_cnt[4b]: listed tokens; [4b + 1]: work items done; [4b + 2]: 1 looked at, ORDER_PAIRS, ORDER_BAND, 4 rounds run.
 // grid (B + workers), block 1024, dynamic LDS: what run_rounds takes, at least RECHECK_LDS.
 template <int DT>
 __global__ __launch_bounds__(1024) void centres_kernel(Batch bt, CentresArgs a) {
     extern __shared__ double s_dyn[];
-    __shared__ int s_flag[2], s_nshort, s_nlong, s_looks, s_got, s_tiles;
+    __shared__ int s_flag[2], s_count, s_looks, s_got, s_tiles;
     __shared__ int s_T[PACT_MAX_BATCH], s_q[PACT_MAX_BATCH], s_items[PACT_MAX_BATCH + 1];
     static_assert(PACT_MAX_BATCH <= 64, "a sample per lane");
     const bool resolver = (int)blockIdx.x < bt.B;
@@ -1060,9 +1064,9 @@ __global__ __launch_bounds__(1024) void centres_kernel(Batch bt, CentresArgs a) 
             // tiles of kept tokens per item; the room for partial sums is that of four tiles, for the most listed tokens
             const int nchunk = a.dk * Elem<DT>::BYTES / 16;
             int tiles = 4, inc = wave_scan_incl_i32(((Tk + 15) >> 4) * ((qk + 63) >> 6));
-            while (tiles > 1 && nchunk * tiles > 8 * 64) {
+            while (tiles > 1 && nchunk * tiles > 2 * 64) {
                 const int half = 8 * tiles, inc2 = wave_scan_incl_i32(((Tk + 15) >> 4) * ((qk + half - 1) / half));
-                if (lane63_of(inc2) > workers || __any(Tk * (64 / half) > rho_fix_tokens(bt.n_max))) break;
+                if (lane63_of(inc2) > items_wanted(workers, nchunk, tiles) || __any(Tk * (64 / half) > rho_fix_tokens(bt.n_max))) break;
                 tiles >>= 1;
                 inc = inc2;
             }
@@ -1096,7 +1100,7 @@ __global__ __launch_bounds__(1024) void centres_kernel(Batch bt, CentresArgs a) 
         }
         const int bs = fresh_s(b);
         if (again) replace_densities(bt, a, bs, T, q, changed, (uint16_t*)s_dyn);
-        if (!again || changed) run_rounds(bt, a, bs, (unsigned char*)s_dyn, s_nshort, s_nlong, s_looks);
+        if (!again || changed) run_rounds(bt, a, bs, (unsigned char*)s_dyn, s_count, s_looks);
         if (!resolver) continue;
         if (again) return;
         T = a.tie_cnt[4 * bs];
@@ -1471,9 +1475,9 @@ __global__ __launch_bounds__(1024) void select_small_kernel(Batch bt, CentresArg
         const int q = clamp_count(a.rep[b].n_kept, bt.s[b].n);
         const int nchunk = a.dk * Elem<DT>::BYTES / 16, rows = (T + 15) >> 4;
         int tiles = 4;                                           // (see centres_kernel)
-        while (tiles > 1 && nchunk * tiles > 8 * 64) {
+        while (tiles > 1 && nchunk * tiles > 2 * 64) {
             const int half = 8 * tiles;
-            if (rows * ((q + half - 1) / half) > workers / bt.B || T * (64 / half) > rho_fix_tokens(bt.n_max)) break;
+            if (rows * ((q + half - 1) / half) > items_wanted(workers / bt.B, nchunk, tiles) || T * (64 / half) > rho_fix_tokens(bt.n_max)) break;
             tiles >>= 1;
         }
         const int total = rows * ((q + 16 * tiles - 1) / (16 * tiles)), per = total < 128 ? 1 : 4;       // items; of a ticket
