@@ -12,6 +12,7 @@
 // change meanwhile.  The lists come from one order of the tokens, so the densest undecided token can always
 // be decided and the looks end; what a token becomes does not depend on how stale the statuses are that were read.
 #include <cstring>
+#include <type_traits>
 
 #include "pact_internal.h"
 
@@ -32,6 +33,50 @@ __device__ __forceinline__ void note_odd_norm(pact_report* rp, double nn) {
 
 __device__ __forceinline__ bool precedes(double rho_j, int j, double rho_i, int i) {
     return rho_j > rho_i || (rho_j == rho_i && j < i);
+}
+
+// Eq. 5 in fp64 (as wave_dot64 computes it) between the token's row `mine` and the rows of its na candidates (tokens in ctok), by one
+// wavefront, two candidates and CH 16-byte chunks of each row at a time.
+template <int DT, int CH>
+__device__ __forceinline__ void nearest_fp64(const lds_i32* cand, const lds_i32* ctok, int na, const char* mine, double nnp,
+                                             const char* kb, size_t row_bytes, const double* nnb, int dk, int lane, double thr,
+                                             double& best, int& bestc) {
+    constexpr int EPL = Elem<DT>::EPL, STEP = 64 * EPL;
+    for (int k = 0; k < na; k += 2) {
+        const int k1 = min(k + 1, na - 1);
+        const int c0 = cand[k], c1 = cand[k1];
+        const int t0 = ctok[k], t1 = ctok[k1];
+        const char* r0 = kb + (size_t)t0 * row_bytes;
+        const char* r1 = kb + (size_t)t1 * row_bytes;
+        const double n0 = nnb[t0], n1 = nnb[t1];
+        double a0 = 0.0, a1 = 0.0;
+        for (int e0 = lane * EPL; e0 < dk; e0 += CH * STEP) {
+            uint4 va[CH], v0[CH], v1[CH];
+#pragma unroll
+            for (int u = 0; u < CH; ++u) {
+                const size_t o = (size_t)(u == 0 || e0 + u * STEP < dk ? e0 + u * STEP : e0) * Elem<DT>::BYTES;
+                va[u] = *(const uint4*)(mine + o);
+                v0[u] = *(const uint4*)(r0 + o);
+                v1[u] = *(const uint4*)(r1 + o);
+            }
+#pragma unroll
+            for (int u = 0; u < CH; ++u) {
+                if (u > 0 && e0 + u * STEP >= dk) break;
+                double a[8], x[8];
+                Elem<DT>::widen(va[u], a);
+                Elem<DT>::widen(v0[u], x);
+#pragma unroll
+                for (int i = 0; i < EPL; ++i) a0 = fma(a[i], x[i], a0);
+                Elem<DT>::widen(v1[u], x);
+#pragma unroll
+                for (int i = 0; i < EPL; ++i) a1 = fma(a[i], x[i], a1);
+            }
+        }
+        const double d0 = cos_dist64(wave_sum_f64(a0), nnp, n0);
+        const double d1 = cos_dist64(wave_sum_f64(a1), nnp, n1);
+        if (d0 < thr && (d0 < best || (d0 == best && c0 < bestc))) { best = d0; bestc = c0; }
+        if (k1 != k && d1 < thr && (d1 < best || (d1 == best && c1 < bestc))) { best = d1; bestc = c1; }
+    }
 }
 
 // Nearest of `ncand` candidates (ids in LDS) of one token, by one wavefront; only distances
@@ -119,34 +164,7 @@ __device__ __forceinline__ void nearest_candidate(lds_i32* cand, lds_i32* ctok, 
         return;
     }
     if ((double)top < cthr - (double)margin) return;   // nothing can pass the threshold
-    // fp64 for the rest, two candidates in flight
-    for (int k = 0; k < na; k += 2) {
-        const int k1 = min(k + 1, na - 1);
-        const int c0 = cand[k], c1 = cand[k1];
-        const int t0 = ctok[k], t1 = ctok[k1];
-        const char* r0 = kb + (size_t)t0 * row_bytes;
-        const char* r1 = kb + (size_t)t1 * row_bytes;
-        const double n0 = nnb[t0], n1 = nnb[t1];
-        double a0 = 0.0, a1 = 0.0;
-        for (int e = lane * EPL; e < dk; e += 64 * EPL) {
-            const size_t o = (size_t)e * Elem<DT>::BYTES;
-            const uint4 va = *(const uint4*)(mine + o);
-            const uint4 v0 = *(const uint4*)(r0 + o);
-            const uint4 v1 = *(const uint4*)(r1 + o);
-            double a[8], x[8];
-            Elem<DT>::widen(va, a);
-            Elem<DT>::widen(v0, x);
-#pragma unroll
-            for (int i = 0; i < EPL; ++i) a0 = fma(a[i], x[i], a0);
-            Elem<DT>::widen(v1, x);
-#pragma unroll
-            for (int i = 0; i < EPL; ++i) a1 = fma(a[i], x[i], a1);
-        }
-        const double d0 = cos_dist64(wave_sum_f64(a0), nnp, n0);
-        const double d1 = cos_dist64(wave_sum_f64(a1), nnp, n1);
-        if (d0 < thr && (d0 < best || (d0 == best && c0 < bestc))) { best = d0; bestc = c0; }
-        if (k1 != k && d1 < thr && (d1 < best || (d1 == best && c1 < bestc))) { best = d1; bestc = c1; }
-    }
+    nearest_fp64<DT, 1>(cand, ctok, na, mine, nnp, kb, row_bytes, nnb, dk, lane, thr, best, bestc);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1644,6 +1662,40 @@ __device__ __forceinline__ void nearest_listed(const lds_i32* list, int n, int l
     }
 }
 
+// The candidates of one token, listed by a wavefront from words of bits (a word per lane) and compared as the buffer fills.
+template <int DT> struct CandidateList {
+    lds_i32 *cand, *ctok;
+    lds_f32* ccos;
+    const char* mine; double nnp;
+    const char* kb; size_t row_bytes; const double* nnb;
+    const int32_t* ix;
+    int dk, lane; float margin;
+    int nbuf = 0, ntot = 0;
+    __device__ __forceinline__ void compare(bool complete, double& best, int& bestj) {
+        const int32_t* ixl = ix;
+        nearest_candidate<DT>(cand, ctok, ccos, nbuf, complete, mine, nnp, kb, row_bytes, nnb, dk, lane, INFINITY, margin,
+                              [ixl](int j) { return ixl[j]; }, best, bestj);
+    }
+    __device__ __forceinline__ void add(uint64_t word, int w, double& best, int& bestj) {      // bits of word w
+        BitPop bp{word};
+        while (bp.any()) {
+            int bit;
+            const bool ok = bp.pop(bit);
+            const uint64_t m = __ballot(ok);
+            if (ok) cand[nbuf + lanes_below(m, lane)] = (w << 6) + bit;
+            nbuf += __popcll(m);
+            ntot += __popcll(m);
+            if (nbuf > CAND_BUF - 64) {
+                compare(false, best, bestj);
+                nbuf = 0;
+            }
+        }
+    }
+    __device__ __forceinline__ void finish(double& best, int& bestj) {
+        if (nbuf) compare(nbuf == ntot, best, bestj);
+    }
+};
+
 // Alg. 2 last loop: every kept token joins the nearest centre.  Candidates are the centres
 // its bitmap row reaches (the nearest centre is within d_c, hence one of them; it need not
 // precede the token); with one candidate no distance is needed, otherwise Eq. 5 is
@@ -1749,27 +1801,10 @@ __device__ __forceinline__ void assign_body(const Batch& bt, const NearArgs& a, 
         const double nnp = nnb[toka];
         double best = INFINITY;
         int bestj = 0x7FFFFFFF;
-        auto tok_of = [&](int j) { return ix[j]; };
-        int nbuf = 0, ntot = 0;
-        auto list = [&](uint64_t word, int w) __attribute__((always_inline)) {
-            BitPop bp{word};
-            while (bp.any()) {
-                int bit;
-                const bool ok = bp.pop(bit);
-                const uint64_t m = __ballot(ok);
-                if (ok) cand[nbuf + lanes_below(m, lane)] = (w << 6) + bit;
-                nbuf += __popcll(m);
-                ntot += __popcll(m);
-                if (nbuf > CAND_BUF - 64) {
-                    nearest_candidate<DT>(cand, ctok, ccos, nbuf, false, mine, nnp, kb, row_bytes, nnb, dk,
-                                          lane, INFINITY, a.margin, tok_of, best, bestj);
-                    nbuf = 0;
-                }
-            }
-        };
+        CandidateList<DT> list{cand, ctok, ccos, mine, nnp, kb, row_bytes, nnb, ix, dk, lane, a.margin};
 #pragma unroll 1
         for (int u = 0; u < WPL; ++u) {
-            list(mine_g ? first[0] : 0ull, gl + GL * u);
+            list.add(mine_g ? first[0] : 0ull, gl + GL * u, best, bestj);
 #pragma unroll
             for (int v = 0; v + 1 < WPL; ++v) if (mine_g) first[v] = first[v + 1];
         }
@@ -1778,10 +1813,9 @@ __device__ __forceinline__ void assign_body(const Batch& bt, const NearArgs& a, 
             const int w = w0 + lane;
             uint64_t word = w < Wq ? rowa[w] & cm[w] : 0ull;
             if (w == Wq - 1 && (q & 63)) word &= (1ull << (q & 63)) - 1ull;
-            list(word, w);
+            list.add(word, w, best, bestj);
         }
-        if (nbuf) nearest_candidate<DT>(cand, ctok, ccos, nbuf, nbuf == ntot, mine, nnp, kb, row_bytes, nnb,
-                                        dk, lane, INFINITY, a.margin, tok_of, best, bestj);
+        list.finish(best, bestj);
         if (mine_g) cid = bestj;                           // (a position; its cluster below, for all tokens at once)
     }
     if (several && on) cid = cid >= 0 && cid != 0x7FFFFFFF ? cn[cid] : -1;
@@ -1792,16 +1826,253 @@ __device__ __forceinline__ void assign_body(const Batch& bt, const NearArgs& a, 
     }
 }
 
+typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+typedef int i32x4_t __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) f32x4_t lds_f32x4;
+// The assignment for wide bf16 rows: 16 kept tokens per workgroup, all centres that any of them reaches (the neighbours of tokens that are close in the
+// sequence are mostly the same) as 16 x 16 products on v_mfma_f32_16x16x32_bf16, 32 of them a turn, an eighth of the row's width per wavefront,
+// straight from the rows.  A token per wavefront (assign_body) reads every candidate's row for every token, eight candidates in 14 dependent trips.
+// 7290 rows of 7 KB with five centres each in reach: bracket 63 us -> 31, 20 to 24 of a workgroup's, of which 5 to the words of its tokens, 3 the list, 6 to 14
+// the rows (72 MB in all, at the rate of the last-level cache), 5 fp64 where it is needed.
+// Products are summed in chains of 224 elements, so the margin of the screen is a twelfth of the long chain's and few tokens
+// are left with more than one candidate; those take fp64, a wavefront per token.  A token of which more than ASSIGN_KEEP candidates stay, or all tokens
+// where more than ASSIGN_LIST centres are reached, are compared as assign_body does it.
+// grid (16 tokens each, rounded up to a multiple of 8; an eighth of the sequence per XCD, whose L2 then holds the rows that are read again; B), block 512.
+constexpr int ASSIGN_LIST = 1024, ASSIGN_KEEP = 8, ASSIGN_CHAIN = 7;
+static float assign_tile_margin(int dk) { return (float)((ASSIGN_CHAIN * 32 + dk / 1024 + 24.0) * (1.0 / 8388608.0) + 2.5e-6); }
+__global__ __launch_bounds__(512, 4) void assign_tile_kernel(Batch bt, NearArgs a, float tile_margin) {
+    constexpr int DT = PACT_BF16, WAVES = 8;
+    __shared__ uint64_t s_union[PACT_MAX_TOKENS / 64];
+    __shared__ uint16_t s_j[ASSIGN_LIST];
+    __shared__ int s_ct[ASSIGN_LIST];
+    __shared__ float s_rc[ASSIGN_LIST], s_part[2][WAVES][16][17], s_keepc[16][ASSIGN_KEEP];
+    __shared__ int s_keepj[16][ASSIGN_KEEP], s_keept[16][ASSIGN_KEEP], s_tok[16], s_count, s_best[16], s_todo[16], s_ntodo;
+    __shared__ int s_cand[WAVES][CAND_BUF], s_ctok[WAVES][CAND_BUF];
+    __shared__ float s_ccos[WAVES][CAND_BUF];
+    const int b = blockIdx.y;
+    const Seg sg = bt.s[b];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), t = (tid >> 4) & 15, gl = tid & 15;
+    const bool owner = tid < 256;                                            // 16 lanes per token; the other wavefronts help with the products and in fp64
+    const int p0 = (int)((blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3)) * 16;
+    if (p0 >= sg.n) return;
+    // (the first 64 words of the token's row and of the mask of centres, and its status, go out ahead of the number of kept tokens: they lie inside the workspace)
+    const uint64_t* cm = a.cmask + (size_t)b * bt.W;
+    uint64_t ahead[4];
+    {
+        const uint64_t* r = a.adj + ((size_t)b * bt.n_max + min(p0 + t, sg.n - 1)) * bt.W;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) ahead[u] = gl + 16 * u < bt.W ? r[gl + 16 * u] & cm[gl + 16 * u] : 0ull;
+    }
+    const int q = clamp_count(a.rep[b].n_kept, sg.n);
+    if (p0 >= q) return;
+    const int p = min(p0 + t, q - 1), Wq = (q + 63) >> 6;
+    const bool on = owner && p0 + t < q;
+    const int32_t* ix = a.idx + sg.base;
+    const int32_t* cn = a.cnum + (size_t)b * bt.n_max;
+    const double* nnb = a.nn + sg.base;
+    const float* rinv = a.rinv + sg.base;
+    const uint64_t* row = a.adj + ((size_t)b * bt.n_max + p) * bt.W;
+    const int tok = ix[p];
+    const bool centre = (a.status + (size_t)b * bt.n_max)[p] == ST_CENTER;
+    const float rt = rinv[tok];
+    for (int w = tid; w < Wq; w += 512) s_union[w] = 0ull;
+    if (tid == 0) s_ntodo = 0;
+    // the token's centres in reach: how many (at most one per lane counts), and the first
+    auto inside = [&](uint64_t word, int w) __attribute__((always_inline)) {
+        if (w == Wq - 1 && (q & 63)) word &= (1ull << (q & 63)) - 1ull;
+        return w < Wq && on && !centre ? word : 0ull;
+    };
+    auto reached = [&](int w) __attribute__((always_inline)) { return inside(w < Wq ? row[w] & cm[w] : 0ull, w); };
+    int some = 0, j1 = -1;
+    auto note = [&](uint64_t word, int w) __attribute__((always_inline)) {
+        if (word && j1 < 0) j1 = (w << 6) + __builtin_ctzll(word);
+        some += __popcll(word);
+    };
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        ahead[u] = inside(ahead[u], gl + 16 * u);
+        note(ahead[u], gl + 16 * u);
+    }
+#pragma unroll 4
+    for (int w = 64 + gl; w < Wq; w += 16) note(reached(w), w);
+    const int gbase = lane & 48;
+    auto group_bits = [&](bool v) __attribute__((always_inline)) { return (uint32_t)(__ballot(v) >> gbase) & 0xFFFFu; };
+    const uint32_t have = group_bits(some > 0), many = group_bits(some > 1);
+    const bool several = on && !centre && (many != 0 || (have & (have - 1)) != 0);
+    int bestj = have ? __shfl(j1, gbase + __builtin_ctz(have), 64) : -1;      // (a single centre in reach: no distance needed)
+    if (gl == 0 && owner) s_tok[t] = several ? tok : -1;
+    const size_t row_bytes = (size_t)a.dk * 2;
+    const char* kb = a.keys + (size_t)sg.base * row_bytes;
+    if (__syncthreads_or(several)) {
+        if (several) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (ahead[u]) atomicOr((unsigned long long*)&s_union[gl + 16 * u], (unsigned long long)ahead[u]);
+            for (int w = 64 + gl; w < Wq; w += 16) {
+                const uint64_t word = reached(w);
+                if (word) atomicOr((unsigned long long*)&s_union[w], (unsigned long long)word);
+            }
+        }
+        __syncthreads();
+        if (wave == 0) {
+            int run = 0;
+            for (int w0 = 0; w0 < Wq; w0 += 64) {
+                uint64_t word = w0 + lane < Wq ? s_union[w0 + lane] : 0ull;
+                const int cnt = __popcll(word), inc = wave_scan_incl_i32(cnt);
+                for (int at = run + inc - cnt; word && at < ASSIGN_LIST; ++at) {
+                    s_j[at] = (uint16_t)(((w0 + lane) << 6) + __builtin_ctzll(word));
+                    word &= word - 1;
+                }
+                run += lane63_of(inc);
+            }
+            if (lane == 0) s_count = run;
+        }
+        __syncthreads();
+        const int U = lane0_of(s_count);
+        bool over = U > ASSIGN_LIST;
+        int kept = 0;
+        if (!over) {
+            for (int k = tid; k < U; k += 512) {
+                const int c = ix[s_j[k]];
+                s_ct[k] = c;
+                s_rc[k] = rinv[c];
+            }
+            __syncthreads();
+            const int l16 = lane & 15, kg = lane >> 4, nchunk = a.dk / 8, steps = (nchunk + 3) / 4;
+            const int from = steps * wave / WAVES, to = steps * (wave + 1) / WAVES;
+            // (a token that needs no distance stands in with the row of one that does; the exchange is outside the choice, for all lanes)
+            const int own = s_tok[l16], other = __shfl(own, __builtin_ctz((uint32_t)__ballot(own >= 0) | 0x10000u) & 15, 64);
+            const char* rowA = kb + (size_t)max(own >= 0 ? own : other, 0) * row_bytes;
+            float top = -INFINITY;
+#pragma unroll 1
+            for (int k0 = 0; k0 < U; k0 += 32) {
+                const char* rowB[2];
+                bool reach[2];
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    rowB[i] = kb + (size_t)s_ct[min(k0 + 16 * i + l16, U - 1)] * row_bytes;
+                    const int k = k0 + 16 * i + gl, j = s_j[min(k, U - 1)];
+                    reach[i] = several && k < U && ((row[j >> 6] >> (j & 63)) & 1ull);
+                }
+                f32x4_t sum[2] = {{0.0f, 0.0f, 0.0f, 0.0f}, {0.0f, 0.0f, 0.0f, 0.0f}};
+                // (two loops and no branch around the second sixteen's products: behind such a branch the compiler left the wait states between a product and the
+                //  addition that reads it out, and every fourth token had a stale sum)
+                auto products = [&](auto tiles) __attribute__((always_inline)) {
+                    constexpr int NT = decltype(tiles)::value;
+#pragma unroll 1
+                    for (int s0 = from; s0 < to; s0 += ASSIGN_CHAIN) {
+                        uint4 va[ASSIGN_CHAIN], vb[NT][ASSIGN_CHAIN];
+#pragma unroll
+                        for (int u = 0; u < ASSIGN_CHAIN; ++u) {
+                            const int e = min(s0 + u, to - 1) * 4 + kg;
+                            const size_t o = e < nchunk ? (size_t)e * 16 : 0;
+                            va[u] = *(const uint4*)(rowA + o);
+#pragma unroll
+                            for (int i = 0; i < NT; ++i) vb[i][u] = *(const uint4*)(rowB[i] + o);
+                        }
+                        f32x4_t acc[NT];
+#pragma unroll
+                        for (int i = 0; i < NT; ++i) acc[i] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+                        for (int u = 0; u < ASSIGN_CHAIN; ++u) {
+                            const bool in = s0 + u < to && (s0 + u) * 4 + kg < nchunk;
+                            const uint4 none = make_uint4(0, 0, 0, 0);
+                            const bf16x8_t x = __builtin_bit_cast(bf16x8_t, in ? va[u] : none);
+#pragma unroll
+                            for (int i = 0; i < NT; ++i)
+                                acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x, __builtin_bit_cast(bf16x8_t, in ? vb[i][u] : none), acc[i], 0, 0, 0);
+                        }
+#pragma unroll
+                        for (int i = 0; i < NT; ++i) sum[i] += acc[i];
+                    }
+                };
+                if (k0 + 16 < U) products(std::integral_constant<int, 2>{});
+                else products(std::integral_constant<int, 1>{});
+                // sum[i][r]: token 4 kg + r of the sixteen, candidate k0 + 16 i + l16; this wavefront's part of the row
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) s_part[i][wave][4 * kg + r][l16] = sum[i][r];
+                __syncthreads();
+                float v[2];
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    const int k = min(k0 + 16 * i + gl, U - 1);
+                    float dot = 0.0f;
+#pragma unroll
+                    for (int w = 0; w < WAVES; ++w) dot += s_part[i][w][t][gl];
+                    v[i] = dot * rt * s_rc[k];
+                }
+                __syncthreads();
+                // the candidates that can still be the nearest: those before, then this turn's, by the token's 16 lanes
+                top = fmaxf(top, group_max_f32<16>(fmaxf(reach[0] ? v[0] : -INFINITY, reach[1] ? v[1] : -INFINITY)));
+                const float floor32 = top - 2.0f * tile_margin;
+                const float oldc = gl < kept ? s_keepc[t][gl & (ASSIGN_KEEP - 1)] : 0.0f;
+                const int oldj = gl < kept ? s_keepj[t][gl & (ASSIGN_KEEP - 1)] : 0;
+                uint32_t m = group_bits(gl < kept && !(oldc < floor32));
+                __builtin_amdgcn_wave_barrier();
+                auto keep = [&](uint32_t m, int base, float c, int j) __attribute__((always_inline)) {
+                    const int at = base + __popc(m & ((1u << gl) - 1u));
+                    if (((m >> gl) & 1u) && at < ASSIGN_KEEP) { s_keepc[t][at] = c; s_keepj[t][at] = j; }
+                    return base + __popc(m);
+                };
+                kept = keep(m, 0, oldc, oldj);
+#pragma unroll
+                for (int i = 0; i < 2; ++i) kept = keep(group_bits(reach[i] && !(v[i] < floor32)), kept, v[i], s_j[min(k0 + 16 * i + gl, U - 1)]);
+                over = over || kept > ASSIGN_KEEP;
+                kept = min(kept, ASSIGN_KEEP);
+                __builtin_amdgcn_wave_barrier();
+            }
+            if (several) {
+                bestj = s_keepj[t][0];
+                if (gl < kept) s_keept[t][gl & (ASSIGN_KEEP - 1)] = ix[s_keepj[t][gl & (ASSIGN_KEEP - 1)]];
+            }
+        }
+        // what is left for fp64 (and for the long way), a wavefront per token
+        const bool left = several && (over || kept > 1);
+        if (left && gl == 0) s_todo[atomicAdd(&s_ntodo, 1)] = t | kept << 8 | (over ? 1 << 16 : 0);
+        __syncthreads();
+        const int n = lane0_of(s_ntodo);
+        for (int k = wave; k < n; k += WAVES) {
+            const int what = lane0_of(s_todo[k]), ta = what & 15, toka = lane0_of(s_tok[ta]);
+            const char* mine = kb + (size_t)toka * row_bytes;
+            double best = INFINITY;
+            int bj = 0x7FFFFFFF;
+            if (!(what >> 16)) {
+                nearest_fp64<DT, 7>((lds_i32*)s_keepj[ta], (lds_i32*)s_keept[ta], what >> 8 & 0xFF, mine, nnb[toka], kb, row_bytes, nnb, a.dk, lane,
+                                    INFINITY, best, bj);
+            } else {
+                const uint64_t* rowa = a.adj + ((size_t)b * bt.n_max + p0 + ta) * bt.W;
+                CandidateList<DT> list{(lds_i32*)s_cand[wave], (lds_i32*)s_ctok[wave], (lds_f32*)s_ccos[wave], mine, nnb[toka], kb, row_bytes, nnb, ix, a.dk, lane, a.margin};
+#pragma unroll 1
+                for (int w0 = 0; w0 < Wq; w0 += 64) {
+                    const int w = w0 + lane;
+                    uint64_t word = w < Wq ? rowa[w] & cm[w] : 0ull;
+                    if (w == Wq - 1 && (q & 63)) word &= (1ull << (q & 63)) - 1ull;
+                    list.add(word, w, best, bj);
+                }
+                list.finish(best, bj);
+            }
+            if (lane == 0) s_best[ta] = bj;
+        }
+        __syncthreads();
+        if (left) bestj = s_best[t];
+    }
+    if (gl == 0 && on) {
+        const int cid = centre ? cn[p] : bestj >= 0 && bestj != 0x7FFFFFFF ? cn[bestj] : -1;
+        a.cluster_id[sg.base + tok] = cid;
+        if (cid >= 0 && a.cluster_counts) join_cluster(a, a.rep + b, sg.base, cid, tok);
+        note_odd_norm(a.rep + b, nnb[tok]);
+    }
+}
+
 // What the matrix-core pass over centres x pruned tokens leaves (MODE_CAND of gram_kernel: the same byte products, cut and margin), for 16
 // pruned tokens and in LDS: a wavefront per group of 64 centres and turn, v_mfma 16x16 straight from the key rows, 16 (fp32 keys: 12)
 // 16-byte chunks of centres in flight per lane.  Bound by its chain: lists, rows and norms, products, 100 instructions of one wavefront.  (The lists were
 // requested once their lengths were known at first: 3 us longer.)
 // tokB: this lane's token (lanes 16 apart the same), first: the centre 64 wavefront + lane, if there is such a one.
 // s_cb, s_cw: [group][16]; s_rs: [4 wavefronts][64].
-typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
-typedef float f32x4_t __attribute__((ext_vector_type(4)));
-typedef int i32x4_t __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) f32x4_t lds_f32x4;
 template <int DT>
 __device__ __forceinline__ void candidates_16(const NearArgs& a, const Seg& sg, int tokB, int first, int C, lds_f32* s_cb, lds_u64* s_cw,
                                               lds_f32* s_rs) {
@@ -2089,6 +2360,15 @@ static int launch_nearest(const Batch& bt, NearArgs a, int recover_blocks, pact_
                 : launch_nearest_part<NEAREST_BOTH, 1>(bt, a, blocks, k_dt, name, st);
 }
 
+// Which rows: event brackets of the assignment, a token per wavefront -> tiles, clustering alone, 300 / 1000 / 2000 / 4000 / 7290 tokens: 3584 wide 26 -> 19, 39 -> 19, 54 -> 27,
+// 70 -> 26, 63 -> 31; 2048: 14 -> 12, 21 -> 16, 21 -> 15, 27 -> 17, 22 -> 20; 1024: 6.5 -> 6.6, 7.8 -> 9.2, 7.9 -> 9.2, 9.2 -> 9.6, 11.2 -> 12.8; 512: 10 -> 16 to 17 -> 24.
+static bool assigns_by_tiles(int dk, int k_dt) { return k_dt == PACT_BF16 && dk * 2 > 2048; }
+static int launch_assign_tiles(const Batch& bt, NearArgs a, const float* rinv, hipStream_t st) {
+    a.rinv = rinv;
+    PACT_LAUNCH("assign", assign_tile_kernel, dim3((bt.n_max + 127) / 128 * 8, bt.B), dim3(512), st, bt, a, assign_tile_margin(a.dk));
+    return PACT_OK;
+}
+
 // Stand-alone pact_reincorporate: totals of recovered / dropped tokens (the fused path gets
 // them from the cluster sizes).  grid (B), block 1024.
 __global__ __launch_bounds__(1024) void count_recovered_kernel(Batch bt, pact_report* rep,
@@ -2183,6 +2463,7 @@ int launch_centres(const Batch& bt, const Ws& w, const void* keys, pact_dtype k_
     a.rep = rep; a.keys = k; a.dk = dk; a.nn = w.nn; a.adj = w.adj; a.margin = (float)cos_margin(dk, k_dt);
     a.cluster_id = cluster_id; a.cluster_counts = cluster_counts;
     a.idx = idx; a.cmask = w.cmask; a.status = w.status; a.cnum = w.cnum;
+    if (assigns_by_tiles(dk, k_dt)) return launch_assign_tiles(bt, a, w.rinv, st);
     a.assign_blocks = 1;
     return launch_nearest(bt, a, 0, k_dt, "assign", st);
 }
