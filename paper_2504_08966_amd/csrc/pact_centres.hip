@@ -172,10 +172,14 @@ __device__ __forceinline__ void nearest_candidate(lds_i32* cand, lds_i32* ctok, 
 // cleared where the distance exceeds d_c.  One wavefront per listed pair and turn, so that the pairs are
 // spread evenly (near d_c the pairs of a row come in clumps: settled by the wavefronts that build the rows'
 // lists, or by workgroups of 32 rows, they took 3 to 13 us longer); a wavefront's pairs, tokens and norms arrive in three
-// trips, then one trip per pair brings both rows (up to eight chunks of either per lane in flight: rows of
-// 7 KB took 57 us for 23 700 pairs when every chunk was a trip of its own, 52 to 55 us now: they are 340 MB).
+// trips, then one trip per pair brings both rows (up to eight chunks of either per lane in flight).
+// Rows of more than 2 KB are screened in fp32 (bf16 on v_dot2_f32_bf16): a lane's chain is a 64th of the row, so its error is a fortieth of the margin that
+// listed the pair and nearly all are decided by it, without the conversions to fp64.  And they are bound by what their rows take to come (340 MB for 23 700 pairs of 7 KB
+// rows), so the pairs of a tile of the density pass, which share rows, stay on one XCD.  7290 rows of 7 KB, bracket 51.6 us, by XCD 41, with the screen 36.6,
+// on the dot instruction 32.6, 1024 workgroups (what the chip holds) instead of 768 31; 2000 rows 27 -> 21; 7290 fp32 rows 69.5 -> 44.5.  Short
+// rows: 16 ragged images 10.2 -> 10.9 by XCD, 11.6 with 1024.
 // grid (settle_blocks(), B), block 256.
-static int settle_blocks(int n_max) { return n_max >= 6144 ? 768 : n_max < 512 ? 64 : n_max / 8; }   // (the benchmark image: a pair per wavefront)
+static int settle_blocks(int n_max, bool wide) { return n_max >= 6144 ? (wide ? 1024 : 768) : n_max < 512 ? 64 : n_max / 64 * 8; }   // (the benchmark image: a pair per wavefront)
 
 template <int DT, int CH>
 __global__ __launch_bounds__(256) void settle_kernel(Batch bt, const char* __restrict__ keys, int dk,
@@ -191,12 +195,17 @@ __global__ __launch_bounds__(256) void settle_kernel(Batch bt, const char* __res
     if (sg.d_n < EXACT_SUMS_D_N)                               // densities that came in two parts (add_density)
         for (int p = blockIdx.x * 256 + threadIdx.x; p < sg.n; p += gridDim.x * 256)
             rho[(size_t)b * bt.n_max + p] += rho_lo[(size_t)b * bt.n_max + p];
+    constexpr bool SCREEN = CH > 2;                            // wide rows
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
     const int gw = blockIdx.x * 4 + wave;
-    const int nw = gridDim.x * 4;
     const uint32_t raw = (uint32_t)near_cnt[2 * b];
-    const int cnt = (int)min(raw, (uint32_t)NEAR_CAP);
+    const int cnt_all = (int)min(raw, (uint32_t)NEAR_CAP);
+    // wide rows: an eighth of the list per XCD (workgroups are dealt to them round-robin; the grid is a multiple of 8): neighbouring pairs are of one tile of the
+    // density pass and share rows, which its L2 then holds
+    const int xcd = blockIdx.x & 7;
+    const int from = SCREEN ? (int)((long)cnt_all * xcd >> 3) : 0, cnt = SCREEN ? (int)((long)cnt_all * (xcd + 1) >> 3) : cnt_all;
+    const int first = SCREEN ? from + (int)(blockIdx.x >> 3) * 4 + wave : gw, nw = SCREEN ? (int)(gridDim.x >> 3) * 4 : (int)gridDim.x * 4;
     if (gw == 0) {
         // largest key distance: the wavefronts of the density pass each left theirs
         uint32_t fb = 0u;
@@ -217,8 +226,10 @@ __global__ __launch_bounds__(256) void settle_kernel(Batch bt, const char* __res
     const int32_t* ix = idx + sg.base;
     const double* nnb = nn + sg.base;
     const double d_c = (double)sg.d_c;
+    // error of a lane's chain of dk / 64 fp32 additions, with a near-tie's 1e-6 on top
+    const double screen = ((double)dk / 64.0 + 24.0) * (1.0 / 8388608.0) + 1.1e-6;
     int ties = 0;
-    for (int e0 = gw; e0 < cnt; e0 += 64 * nw) {
+    for (int e0 = first; e0 < cnt; e0 += 64 * nw) {
         // lane l takes this wavefront's l-th pair (e0 + l * nw)
         const int my_e = e0 + lane * nw;
         uint32_t my_pi = 0, my_pj = 0;
@@ -240,26 +251,55 @@ __global__ __launch_bounds__(256) void settle_kernel(Batch bt, const char* __res
             if (pi != pj) {
                 const char* ri = kb + (size_t)__builtin_amdgcn_readlane(my_ti, k) * row_bytes;
                 const char* rj = kb + (size_t)__builtin_amdgcn_readlane(my_tj, k) * row_bytes;
-                double acc = 0.0;                        // (the order of operations of wave_dot64)
-                for (int c0 = lane * EPL; c0 < dk; c0 += CH * 64 * EPL) {
-                    uint4 va[CH], vb[CH];
+                const double ni = __shfl(my_ni, k, 64), nj = __shfl(my_nj, k, 64);
+                // both rows, CH chunks of either per lane and trip
+                auto over_rows = [&](auto&& use) __attribute__((always_inline)) {
+#pragma unroll 1
+                    for (int c0 = lane * EPL; c0 < dk; c0 += CH * 64 * EPL) {
+                        uint4 va[CH], vb[CH];
 #pragma unroll
-                    for (int u = 0; u < CH; ++u) {
-                        const size_t o = (size_t)(c0 + u * 64 * EPL < dk ? c0 + u * 64 * EPL : c0) * Elem<DT>::BYTES;
-                        va[u] = *(const uint4*)(ri + o);
-                        vb[u] = *(const uint4*)(rj + o);
-                    }
-#pragma unroll
-                    for (int u = 0; u < CH; ++u)
-                        if (c0 + u * 64 * EPL < dk) {
-                            double a[8], x[8];
-                            Elem<DT>::widen(va[u], a);
-                            Elem<DT>::widen(vb[u], x);
-#pragma unroll
-                            for (int i = 0; i < EPL; ++i) acc = fma(a[i], x[i], acc);
+                        for (int u = 0; u < CH; ++u) {
+                            const size_t o = (size_t)(c0 + u * 64 * EPL < dk ? c0 + u * 64 * EPL : c0) * Elem<DT>::BYTES;
+                            va[u] = *(const uint4*)(ri + o);
+                            vb[u] = *(const uint4*)(rj + o);
                         }
+#pragma unroll
+                        for (int u = 0; u < CH; ++u)
+                            if (c0 + u * 64 * EPL < dk) use(va[u], vb[u]);
+                    }
+                };
+                bool decided = false;
+                if constexpr (SCREEN) {
+                    float acc = 0.0f;
+                    over_rows([&](const uint4& va, const uint4& vb) __attribute__((always_inline)) {
+                        if constexpr (DT == PACT_BF16) {
+                            typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+                            const uint32_t a[4] = {va.x, va.y, va.z, va.w}, x[4] = {vb.x, vb.y, vb.z, vb.w};
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) acc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, a[i]), __builtin_bit_cast(bf16x2_t, x[i]), acc, false);
+                        } else {
+                            float a[8], x[8];
+                            Elem<DT>::widenf(va, a);
+                            Elem<DT>::widenf(vb, x);
+#pragma unroll
+                            for (int i = 0; i < EPL; ++i) acc = fmaf(a[i], x[i], acc);
+                        }
+                    });
+                    d = cos_dist64(wave_sum_f64((double)acc), ni, nj);
+                    const double len = sqrt(ni * nj);        // (products that overflow or vanish in fp32: fp64)
+                    decided = len > 1e-15 && len < 1e30 && fabs(d - d_c) > screen;
                 }
-                d = cos_dist64(wave_sum_f64(acc), __shfl(my_ni, k, 64), __shfl(my_nj, k, 64));
+                if (!decided) {                              // (the same in every lane)
+                    double acc = 0.0;                        // (the order of operations of wave_dot64)
+                    over_rows([&](const uint4& va, const uint4& vb) __attribute__((always_inline)) {
+                        double a[8], x[8];
+                        Elem<DT>::widen(va, a);
+                        Elem<DT>::widen(vb, x);
+#pragma unroll
+                        for (int i = 0; i < EPL; ++i) acc = fma(a[i], x[i], acc);
+                    });
+                    d = cos_dist64(wave_sum_f64(acc), ni, nj);
+                }
             }
             if (lane == 0) {
                 if (beyond_cutoff(d, d_c)) {
@@ -2416,8 +2456,8 @@ int launch_centres(const Batch& bt, const Ws& w, const void* keys, pact_dtype k_
     static size_t raised[4] = {};
     const bool narrow = dk * (k_dt == PACT_BF16 ? 2 : 4) <= SMALL_SETTLE_CHUNKS * 16, small = selects_in_one(bt, narrow);
     if (!small || !narrow) {
-        dim3 gset(settle_blocks(bt.n_max), bt.B);
         const bool wide = (size_t)dk * (k_dt == PACT_BF16 ? 2 : 4) > 2048;
+        dim3 gset(settle_blocks(bt.n_max, wide), bt.B);
 #define PACT_SETTLE(DT, CH)                                                                                           \
         PACT_LAUNCH("settle", (settle_kernel<DT, CH>), gset, dim3(256), st, bt, k, dk, idx, w.nn, w.near_list, w.near_cnt, \
                     w.stat, stat_words, w.rho, w.rho_lo, w.adj, rep)
