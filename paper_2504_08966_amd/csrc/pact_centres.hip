@@ -251,10 +251,8 @@ __global__ __launch_bounds__(256) void settle_kernel(Batch bt, const char* __res
             if (pi != pj) {
                 const char* ri = kb + (size_t)__builtin_amdgcn_readlane(my_ti, k) * row_bytes;
                 const char* rj = kb + (size_t)__builtin_amdgcn_readlane(my_tj, k) * row_bytes;
-                const double ni = __shfl(my_ni, k, 64), nj = __shfl(my_nj, k, 64);
                 // both rows, CH chunks of either per lane and trip
                 auto over_rows = [&](auto&& use) __attribute__((always_inline)) {
-#pragma unroll 1
                     for (int c0 = lane * EPL; c0 < dk; c0 += CH * 64 * EPL) {
                         uint4 va[CH], vb[CH];
 #pragma unroll
@@ -285,6 +283,7 @@ __global__ __launch_bounds__(256) void settle_kernel(Batch bt, const char* __res
                             for (int i = 0; i < EPL; ++i) acc = fmaf(a[i], x[i], acc);
                         }
                     });
+                    const double ni = __shfl(my_ni, k, 64), nj = __shfl(my_nj, k, 64);
                     d = cos_dist64(wave_sum_f64((double)acc), ni, nj);
                     const double len = sqrt(ni * nj);        // (products that overflow or vanish in fp32: fp64)
                     decided = len > 1e-15 && len < 1e30 && fabs(d - d_c) > screen;
@@ -298,7 +297,7 @@ __global__ __launch_bounds__(256) void settle_kernel(Batch bt, const char* __res
 #pragma unroll
                         for (int i = 0; i < EPL; ++i) acc = fma(a[i], x[i], acc);
                     });
-                    d = cos_dist64(wave_sum_f64(acc), ni, nj);
+                    d = cos_dist64(wave_sum_f64(acc), __shfl(my_ni, k, 64), __shfl(my_nj, k, 64));
                 }
             }
             if (lane == 0) {
@@ -392,7 +391,7 @@ __device__ __forceinline__ double recheck_band2(float d_n) {
 // have at most three preceding neighbours, and the kernel that runs the rounds - a single
 // workgroup - then has 8 bytes per token to fetch instead of 32.  The head of a longer list starts with the densest
 // neighbour instead (the first of the list as it is ordered by position): it is a centre more often than not, and
-// the token is then decided without its record.  Slots of a head that nothing names hold `pad`, the position behind the last one (see run_rounds).
+// the token is then decided without its record.
 // GL lanes of a wavefront per token (16: four tokens per wavefront, most tokens have fewer
 // neighbours than that; 64: one).  Every lane of the wavefront takes part, with p < 0 for no token.
 // `odd` counts, per token, the neighbours whose density is too close to this token's: DETECT:
@@ -402,7 +401,7 @@ constexpr int HEAD_PREDS = 3;
 __host__ __device__ inline int positions(int n_max) { return (n_max + 63) / 64 * 64; }
 constexpr int PREDS_SPREAD = 256;      // set bits of a wavefront's row words that are spread over the lanes through LDS
 template <bool DETECT, int GL>
-__device__ __forceinline__ int preds_of_row(int p, int q, int pad, const double* r, const uint64_t* row, uint16_t* out,
+__device__ __forceinline__ int preds_of_row(int p, int q, const double* r, const uint64_t* row, uint16_t* out,
                                             uint16_t* head, volatile uint16_t* nb_wave, int lane, double band2) {
     static_assert(GL == 16 || GL == 64, "a row of lanes or the wavefront");
     constexpr int WPL = 64 / GL;                       // words per lane and turn
@@ -502,7 +501,6 @@ __device__ __forceinline__ int preds_of_row(int p, int q, int pad, const double*
         const uint64_t m = group_bits(best == top);
         if (total > HEAD_PREDS && gl == __builtin_ctzll(m)) head[1] = (uint16_t)best_j;
     }
-    if (on && gl < HEAD_PREDS && gl >= total) head[1 + gl] = (uint16_t)pad;
     if (gl == 0 && on) {
         const uint16_t c = (uint16_t)(total > KP ? KP + 1 : total);
         out[0] = c;
@@ -533,7 +531,7 @@ __global__ __launch_bounds__(256) void build_preds_kernel(Batch bt, const pact_r
     if (pw >= q) return;
     const int p = pw + lane / GL < q ? pw + lane / GL : -1, pr = p < 0 ? pw : p;
     const double* r = rho + (size_t)b * bt.n_max;
-    const int odd = preds_of_row<true, GL>(p, q, positions(bt.n_max), r, adj + ((size_t)b * bt.n_max + pr) * bt.W,
+    const int odd = preds_of_row<true, GL>(p, q, r, adj + ((size_t)b * bt.n_max + pr) * bt.W,
                                            preds + ((size_t)b * bt.n_max + pr) * PRED_CAP,
                                            (uint16_t*)(heads + (size_t)b * bt.n_max + pr), s_nb[wave], lane,
                                            recheck_band2(sg.d_n));
@@ -634,6 +632,12 @@ __device__ __forceinline__ void run_rounds(const Batch& bt, const CentresArgs& a
     const lds_u8* s_rd = (const lds_u8*)s_st;                    // plain reads: independent look-ups go out together
     const uint4* rec = (const uint4*)(a.preds + (size_t)b * bt.n_max * PRED_CAP);   // 8 pieces per token
     if (tid == 0) { s_count = 0; s_looks = 0; s_st[qpad] = NONE; }
+    // a head with the position behind the last in the slots that name nobody
+    auto padded = [&](const uint2& v) __attribute__((always_inline)) {
+        const uint32_t c = v.x & 0xFFFFu, none = (uint32_t)qpad;
+        const uint32_t y = c > 1 ? v.y : none;
+        return head_t{c > 0 ? v.x : none << 16, c > 2 ? y : (y & 0xFFFFu) | none << 16};
+    };
     // round 1.  (The first heads are requested before the number of kept tokens is known: they lie inside the workspace.  So are the token
     // numbers, and again where the list may end with the last kept one.)
     for (int p0 = 0; p0 < sg.n; p0 += 4096) {
@@ -648,7 +652,7 @@ __device__ __forceinline__ void run_rounds(const Batch& bt, const CentresArgs& a
             const int p = p0 + 1024 * u + tid;
             if (p < q) {
                 s_st[p] = (hv[u].x & 0xFFFFu) == 0 ? CENTRE : OPEN;
-                if (p < n_heads) s_head[p] = head_t{hv[u].x, hv[u].y};
+                if (p < n_heads) s_head[p] = padded(hv[u]);
             }
         }
         if (a.idx_ahead != a.idx) {
@@ -662,8 +666,7 @@ __device__ __forceinline__ void run_rounds(const Batch& bt, const CentresArgs& a
     __syncthreads();
     auto head_of = [&](int p) __attribute__((always_inline)) {
         if (p < n_heads) return (head_t)s_head[p];
-        const uint2 v = hd[p];
-        return head_t{v.x, v.y};
+        return padded(hd[p]);
     };
     // one look at the up to three predecessors that a token's head names
     auto look = [&](head_t hv) __attribute__((always_inline)) {
@@ -676,17 +679,23 @@ __device__ __forceinline__ void run_rounds(const Batch& bt, const CentresArgs& a
     // the second, and the two token lists (a wavefront's entries at once)
 #pragma unroll 1
     for (int p0 = 0; p0 < q; p0 += 2048) {                       // (wave-uniform trip count)
+        head_t hv[2];
+        int c[2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int p = p0 + 1024 * u + tid;
+            hv[u] = head_of(min(p, q - 1));
+            c[u] = p < q ? hv[u].x & 0xFFFF : 0;
+        }
+        if (!__any(c[0] + c[1] > 0)) continue;                   // (centres already, or past the last)
         uint64_t ms[2], ml[2];
         int n = 0;                                               // short ones, long ones << 16
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
-            const int p = p0 + 1024 * u + tid;
-            const head_t hv = head_of(min(p, q - 1));
-            const int c = p < q ? hv.x & 0xFFFF : 0;
-            const uint32_t seen = look(hv);
-            const bool lng = c > HEAD_PREDS && !(seen & CENTRE);
+            const uint32_t seen = look(hv[u]);
+            const bool lng = c[u] > HEAD_PREDS && !(seen & CENTRE);
             bool shrt = false;
-            if (c > 0 && !lng) shrt = decide(p, seen);
+            if (c[u] > 0 && !lng) shrt = decide(p0 + 1024 * u + tid, seen);
             ms[u] = __ballot(shrt);
             ml[u] = __ballot(lng);
             n += __popcll(ms[u]) + (__popcll(ml[u]) << 16);
@@ -1081,7 +1090,7 @@ __device__ __forceinline__ void replace_densities(const Batch& bt, const Centres
     const int n_lists = all ? q : T;
     for (int t = wave; t < n_lists; t += 16) {
         const int p = all ? t : min(list[t] & 0xFFFF, q - 1);
-        preds_of_row<false, 64>(p, q, positions(bt.n_max), rho_b, a.adj + ((size_t)b * bt.n_max + p) * bt.W, a.preds + ((size_t)b * bt.n_max + p) * PRED_CAP,
+        preds_of_row<false, 64>(p, q, rho_b, a.adj + ((size_t)b * bt.n_max + p) * bt.W, a.preds + ((size_t)b * bt.n_max + p) * PRED_CAP,
                                 (uint16_t*)(a.heads + (size_t)b * bt.n_max + p), s_nb + wave * PREDS_SPREAD, lane, 0.0);
     }
     __syncthreads();

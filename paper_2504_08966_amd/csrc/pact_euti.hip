@@ -20,8 +20,8 @@ namespace pact {
 //                                       4 KB, several tokens per wavefront (eight loads in flight per lane).
 // Keys and hidden states are walked by token of the whole batch (no blocks for the tokens that
 // shorter samples do not have).  Bound by HBM, and nearly by the vector units (conversions to fp64): 7290 tokens of 3584 bf16 with 4 / 28 query
-// heads 67 / 112 MB, 14.7 -> 12.7 / 25.2 -> 22.9 us; 16 x 2688 tokens 396 MB in 64 us, 8 x 6272 462 MB, 89.5 -> 81 (a plain read of as much: 71); 32 x 729 of 896
-// 90 MB, 19.4 -> 18.2; 16384 of 3584 with fp32 keys 185 MB, 54.4 -> 44.8 (before: a key row at a time, longer query chunks).
+// heads 67 / 112 MB, 14.7 -> 13.2 / 25.2 -> 23 us; 16 x 2688 tokens 396 MB in 64 us, 8 x 6272 462 MB, 89.5 -> 81 (a plain read of as much: 71); 32 x 729 of 896
+// 90 MB, 19.4 -> 18.2; 16384 of 3584 with fp32 keys 185 MB, 54.4 -> 44 (before: a key row at a time, longer query chunks).
 // grid (blocks), block 256.
 struct FrontArgs {
     const char* keys; int32_t dk;
@@ -39,15 +39,15 @@ struct FrontArgs {
 // Row chunks of the query sum: 8, or 4 for wide queries, which have blocks enough (every workgroup of the logits
 // kernel reads its columns of all chunks, 32 KB); fewer for short samples (128 rows a chunk); more for long ones with narrow queries, whose few
 // blocks would each be a chain of trips of 256 rows (16384 tokens, 512 fp32 columns: 8 chunks of 2048 rows were 128 blocks of 8 trips, 22 us for 34 MB
-// and the end of a launch of 54 us; 32 chunks: 45 us; 7290 tokens 13.2 -> 12.7).
+// and the end of a launch of 53 us; 16 chunks: 41.  512 rows a chunk cost the logits what they gave here: 1.1 us, 14823 tokens with 14 query heads 2.4).
 static int query_chunks(int n_max, int qcols) {
-    if (qcols <= 1024 && n_max > 512 * QG_CHUNKS) return (n_max + 511) / 512;
+    if (qcols <= 1024 && n_max > 1024 * QG_CHUNKS) return (n_max + 1023) / 1024;
     const int most = qcols > 1024 ? QG_CHUNKS / 2 : QG_CHUNKS, want = (n_max + 127) / 128;
     return want < most ? want : most;
 }
 // Where the chunks' sums are: more than QG_CHUNKS of them in the place of the predecessor lists, which are made after the sums' last use.
 static double* query_sums(const Ws& w, int chunks) {
-    static_assert(8 * 1024 / 512 <= 2 * PRED_CAP, "the sums of 512 tokens of 1024 columns take less than the tokens' lists");
+    static_assert(8 * 1024 / 1024 <= PRED_CAP, "the sums of 1024 tokens of 1024 columns take less than the tokens' lists");
     return chunks > QG_CHUNKS ? (double*)w.preds : w.qg_part;
 }
 

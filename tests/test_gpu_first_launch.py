@@ -37,7 +37,7 @@ def test_rows_by_fours_as_one_at_a_time(dk, n_b, d_n):
 
 
 # one token more than eight chunks take, a last chunk of a few rows, and the widest queries that come in more chunks
-@pytest.mark.parametrize("n,n_kv,n_q,d_h,dtype", [(4097, 1, 1, 64, "bf16"), (4097, 2, 2, 64, "f32"), (5121, 1, 8, 128, "bf16"), (8200, 1, 4, 32, "f32")])
+@pytest.mark.parametrize("n,n_kv,n_q,d_h,dtype", [(8193, 1, 1, 64, "bf16"), (8193, 2, 2, 64, "f32"), (9217, 1, 8, 128, "bf16"), (12300, 1, 4, 32, "f32")])
 def test_query_sums_of_long_samples(n, n_kv, n_q, d_h, dtype):
     s = _random_sample(31, n, n_kv, n_q, d_h, 64, 0.4, dtype)
     hid, ks, qs = (gu.dev(x.reshape(n, -1), dtype) for x in (s.hidden, s.keys, s.queries))
