@@ -773,6 +773,7 @@ __device__ __forceinline__ void run_rounds(const Batch& bt, const CentresArgs& a
     for (int k = 0; k < HELD; ++k) {
         lp[k] = -1;
         over[k] = false;
+        lv[k] = piece_of(make_uint4(0, 0, 0, 0), 0);             // (no predecessors: a group without a token looks with the others of its wavefront)
         if (mine8 + 128 * k < nlong) {
             lp[k] = s_list[qpad - 1 - (mine8 + 128 * k)];
             lv[k] = rec[(size_t)lp[k] * 8 + sub];
