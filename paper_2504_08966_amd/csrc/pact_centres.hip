@@ -2009,8 +2009,8 @@ __global__ __launch_bounds__(512, 4) void assign_tile_kernel(Batch bt, NearArgs 
                     reach[i] = several && k < U && ((row[j >> 6] >> (j & 63)) & 1ull);
                 }
                 f32x4_t sum[2] = {{0.0f, 0.0f, 0.0f, 0.0f}, {0.0f, 0.0f, 0.0f, 0.0f}};
-                // (two loops and no branch around the second sixteen's products: behind such a branch the compiler left the wait states between a product and the
-                //  addition that reads it out, and every fourth token had a stale sum)
+                // (two loops and no branch around the second sixteen's products: across such a branch the compiler left three of the eight wait states between the last
+                //  product and the addition that reads it out, and every fourth token had a stale sum.  A test follows all products of all kernels to their readers)
                 auto products = [&](auto tiles) __attribute__((always_inline)) {
                     constexpr int NT = decltype(tiles)::value;
 #pragma unroll 1
