@@ -1605,11 +1605,8 @@ struct NearArgs {
     const int32_t* idx; const uint64_t* cmask; const uint32_t* status; const int32_t* cnum; int assign_blocks;
     // recovery of pruned tokens (Eq. 8/9): the blocks before the assignment ones
     const int32_t* pruned_idx; const int32_t* center_idx; const float* cbest;
-    const float* rinv;                          // small samples, which look for their candidates here: reciprocal norms
-    union {
-        const char* planes;                     // (there) fp32 keys' byte planes
-        const float* cand;                      // candidates found by two bytes of fp32 keys: see Ws
-    };
+    // small samples, which look for their candidates here: reciprocal norms, fp32 keys' byte planes
+    const float* rinv; const char* planes;
 };
 
 // Token `tok` joins cluster c (both local to the sample): the cluster's size goes up and, where
@@ -2240,9 +2237,8 @@ __device__ __forceinline__ void candidates_16(const NearArgs& a, const Seg& sg, 
 // (16 tokens per block and turn): the values and words of 64 groups arrive in one trip and are
 // kept for the listing, a candidate row in another.  Blocks blk = 0 .. nblk-1, 256 threads.
 // s_c: [16][LIST_TURN] candidate ids per token slot.
-// HERE: the candidates are found by candidates_16 (SMALL_TOKENS at most).  BESIDE: in one kernel with the assignment.  OWN: every group of centres has a margin of its
-// own (cand_margin: fp32 keys, candidates by two of their bytes).
-template <int DT, bool HERE, bool BESIDE, bool OWN>
+// HERE: the candidates are found by candidates_16 (SMALL_TOKENS at most).  BESIDE: in one kernel with the assignment.
+template <int DT, bool HERE, bool BESIDE>
 __device__ __forceinline__ void recover_body(const Batch& bt, const NearArgs& a, int blk, int nblk, lds_i32* s_c, lds_f32* s_cb = nullptr,
                                              lds_u64* s_cw = nullptr, lds_f32* s_rs = nullptr) {
     pact_report* rep = a.rep;
@@ -2291,18 +2287,10 @@ __device__ __forceinline__ void recover_body(const Batch& bt, const NearArgs& a,
         if (thr > 0.0 && C > 0) {
             // groups part, part + 16, .. of the first 64 with their candidate words (a word is
             // only meaningful where the group's largest cosine is within reach); further
-            // groups, if any, for the maximum only.  OWN: of each group, where it is within reach, the largest that its cosines can be in exact arithmetic, and
-            // the maximum is that of what they are at least.
+            // groups, if any, for the maximum only
             float v[4];
             uint64_t word[4];
-            const float col = OWN ? a.cand[2 * (sg.base + t) + 1] : 0.0f;
-            auto bounds = [&](int w, float c, float& most) __attribute__((always_inline)) {
-                const float m = cand_margin(a.cand[2 * (sg.base + w)], col);
-                most = c >= recovery_reach(sg, m) ? c + m : -INFINITY;
-                return c - m;
-            };
             auto load_batch = [&](int wb) __attribute__((always_inline)) {
-                float low[4];
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
                     const int w = wb + part + 16 * u;
@@ -2313,22 +2301,16 @@ __device__ __forceinline__ void recover_body(const Batch& bt, const NearArgs& a,
                         v[u] = w < Wc ? cb[(size_t)w * bt.n_max + t] : -INFINITY;
                         word[u] = w < Wc ? cw[(size_t)w * np + t] : 0ull;
                     }
-                    low[u] = v[u];
-                    if constexpr (OWN) low[u] = bounds(min(w, Wc - 1), v[u], v[u]);
                 }
-                return fmaxf(fmaxf(low[0], low[1]), fmaxf(low[2], low[3]));
             };
-            float gm = load_batch(0), top = OWN ? fmaxf(fmaxf(v[0], v[1]), fmaxf(v[2], v[3])) : 0.0f;
-            for (int w = 64 + part; w < Wc; w += 16) {
-                float c = cb[(size_t)w * bt.n_max + t], most;
-                if constexpr (OWN) { c = bounds(w, c, most); top = fmaxf(top, most); }
-                gm = fmaxf(gm, c);
-            }
+            load_batch(0);
+            float gm = fmaxf(fmaxf(v[0], v[1]), fmaxf(v[2], v[3]));
+            for (int w = 64 + part; w < Wc; w += 16) gm = fmaxf(gm, cb[(size_t)w * bt.n_max + t]);
             gm = group_max_f32<16>(gm);
-            if (OWN ? group_max_f32<16>(top) > -INFINITY : gm >= t_lo) {
-                const float floor32 = OWN ? gm : fmaxf(gm - 2.0f * margin, t_lo);
+            if (gm >= t_lo) {
+                const float floor32 = fmaxf(gm - 2.0f * margin, t_lo);
                 double thr_here = thr;                                   // (BESIDE: what follows of it and of the margin stays here; kept since the start it was spilled)
-                float margin_here = OWN ? 0.0f : margin;
+                float margin_here = margin;
                 if constexpr (BESIDE && HERE) asm volatile("" : "+v"(thr_here), "+v"(margin_here));
                 const bool clear = (double)gm - (1.0 - thr_here) > (double)margin_here;   // d < thr  <=>  cosine > 1 - thr: the nearest is certainly within alpha*d_c
                 const char* mine = kb + (size_t)tok * row_bytes;
@@ -2377,7 +2359,7 @@ __device__ __forceinline__ void recover_body(const Batch& bt, const NearArgs& a,
 // PART: NEAREST_BOTH, or a build that holds one of the two searches only (the assignment alone
 // needs fewer registers and runs four wavefronts per SIMD instead of three).  _HERE: the recovery finds its candidates itself (three per SIMD).
 enum { NEAREST_BOTH = 0, NEAREST_ASSIGN = 1, NEAREST_RECOVER = 2, NEAREST_BOTH_HERE = 3, NEAREST_RECOVER_HERE = 4 };
-template <int DT, int PART, int TPW, bool OWN>
+template <int DT, int PART, int TPW>
 __global__ __launch_bounds__(256, PART >= NEAREST_BOTH_HERE ? 3 : 4) void nearest_centre_kernel(Batch bt, NearArgs a) {
     __shared__ int s_cand[4][CAND_BUF], s_ctok[4][CAND_BUF];
     __shared__ float s_ccos[4][CAND_BUF];
@@ -2392,26 +2374,18 @@ __global__ __launch_bounds__(256, PART >= NEAREST_BOTH_HERE ? 3 : 4) void neares
     __shared__ f32x4_t s_rs[HERE ? 64 : 1];
     if constexpr (PART == NEAREST_ASSIGN) assign_body<DT, TPW>(bt, a, blockIdx.x, cand, ctok, ccos, (lds_i32*)s_list);
     else if constexpr (PART == NEAREST_RECOVER || PART == NEAREST_RECOVER_HERE)
-        recover_body<DT, HERE, false, OWN>(bt, a, blockIdx.x, gridDim.x, (lds_i32*)s_list, (lds_f32*)s_cb, (lds_u64*)s_cw, (lds_f32*)s_rs);
+        recover_body<DT, HERE, false>(bt, a, blockIdx.x, gridDim.x, (lds_i32*)s_list, (lds_f32*)s_cb, (lds_u64*)s_cw, (lds_f32*)s_rs);
     else if ((int)blockIdx.x >= (int)gridDim.x - a.assign_blocks)
         assign_body<DT, TPW>(bt, a, blockIdx.x - (gridDim.x - a.assign_blocks), cand, ctok, ccos, (lds_i32*)s_list);
-    else recover_body<DT, HERE, true, OWN>(bt, a, blockIdx.x, gridDim.x - a.assign_blocks, (lds_i32*)s_list, (lds_f32*)s_cb, (lds_u64*)s_cw, (lds_f32*)s_rs);
+    else recover_body<DT, HERE, true>(bt, a, blockIdx.x, gridDim.x - a.assign_blocks, (lds_i32*)s_list, (lds_f32*)s_cb, (lds_u64*)s_cw, (lds_f32*)s_rs);
 }
 
 template <int PART, int TPW>
 static int launch_nearest_part(const Batch& bt, const NearArgs& a, int blocks, pact_dtype k_dt, const char* name,
                                hipStream_t st) {
     dim3 grid(blocks, bt.B);
-    if (k_dt == PACT_BF16) PACT_LAUNCH(name, (nearest_centre_kernel<PACT_BF16, PART, TPW, false>), grid, dim3(256), st, bt, a);
-    else {
-        if constexpr (PART == NEAREST_BOTH || PART == NEAREST_RECOVER) {
-            if (a.cand) {
-                PACT_LAUNCH(name, (nearest_centre_kernel<PACT_F32, PART, TPW, true>), grid, dim3(256), st, bt, a);
-                return PACT_OK;
-            }
-        }
-        PACT_LAUNCH(name, (nearest_centre_kernel<PACT_F32, PART, TPW, false>), grid, dim3(256), st, bt, a);
-    }
+    if (k_dt == PACT_BF16) PACT_LAUNCH(name, (nearest_centre_kernel<PACT_BF16, PART, TPW>), grid, dim3(256), st, bt, a);
+    else PACT_LAUNCH(name, (nearest_centre_kernel<PACT_F32, PART, TPW>), grid, dim3(256), st, bt, a);
     return PACT_OK;
 }
 // a.assign_blocks: whether the assignment takes part.  Four tokens per wavefront in it from 8192 kept ones on (see assign_body), beside the recovery
@@ -2585,7 +2559,6 @@ int launch_reincorporate(const Batch& bt, const Ws& w, const void* keys, pact_dt
     a.cluster_id = cluster_id; a.cluster_counts = cluster_counts;
     a.pruned_idx = pruned_idx; a.center_idx = center_idx; a.cbest = w.cbest;
     if (here) { a.rinv = w.rinv; a.planes = w.ksplit; }
-    if (!here && two_byte_candidates(bt, k_dt)) a.cand = w.cand;
     if (kept_idx) {
         a.idx = kept_idx; a.cmask = w.cmask; a.status = w.status; a.cnum = w.cnum;
         a.assign_blocks = 1;

@@ -125,7 +125,7 @@ struct Ws {
     uint64_t* adj; float* cbest; double* rho; uint32_t* status;
     int32_t* cnum; uint64_t* cmask; uint16_t* preds; uint2* heads; double* rho_lo; uint32_t* near_list; int32_t* near_cnt; uint32_t* stat;
     int32_t* tie_list; int32_t* tie_cnt; double* rho_fix;
-    int32_t* offsets; int32_t* members; int32_t* big; int32_t* slots; uint32_t* zeros; char* ksplit; float* cand;
+    int32_t* offsets; int32_t* members; int32_t* big; int32_t* slots; uint32_t* zeros; char* ksplit;
 };
 
 inline Ws resolve(void* base, const WsLayout& L) {
@@ -146,9 +146,6 @@ inline Ws resolve(void* base, const WsLayout& L) {
     w.offsets = (int32_t*)(p + L.offsets); w.big = (int32_t*)(p + L.big);
     w.members = (int32_t*)(p + L.members); w.slots = (int32_t*)(p + L.slots); w.zeros = (uint32_t*)(p + L.zeros);
     w.ksplit = p + L.ksplit;
-    // Candidates by two bytes of fp32 keys, [total][2]: what cand_margin() takes of the sample's i-th group of 64 centres (the largest) and of its i-th pruned token.
-    // (In the place of offsets and, behind them, members, which only a merge by itself has use for.)
-    w.cand = (float*)(p + L.offsets);
     return w;
 }
 
@@ -195,8 +192,6 @@ int launch_gram_density(const Batch& bt, const Ws& w, const void* keys, pact_dty
                         const int32_t* idx, pact_report* rep, bool want_stat, int* stat_words, hipStream_t st);
 // (diagnostic) the map of workgroup slots to samples that the Gram passes of a batch use
 int plan_gram_workgroups(const int32_t* tiles, int32_t batch, uint16_t* wg_map, uint16_t* wg_count);
-// fp32 keys: whether the candidate pass takes the upper two bytes of each element, so that every group of 64 centres has its own margin (cand_margin).
-bool two_byte_candidates(const Batch& bt, int k_dt);
 int launch_centres(const Batch& bt, const Ws& w, const void* keys, pact_dtype k_dt, int32_t dk,
                    const int32_t* idx, int32_t* center_idx, int32_t* cluster_id,
                    int32_t* cluster_counts, pact_report* rep, double* rho_opt, int32_t* rank_opt,
@@ -242,7 +237,7 @@ inline double cos_margin(int dk, int k_dt) {
 }
 
 // Internal element type of the Gram kernel for fp32 keys: each row as 32-bit integers in four int8 planes.
-enum { PACT_I8X4 = 2, PACT_I8X2 = 3 };       // (density pass; candidate pass, which takes the upper two planes)
+enum { PACT_I8X4 = 2 };
 
 }  // namespace pact
 
@@ -443,13 +438,6 @@ __device__ __forceinline__ double cos_dist64(double dot, double nna, double nnb)
     const double c = den > 0.0 ? dot / den : 0.0;
     return fmin(fmax(1.0 - c, 0.0), 2.0);
 }
-
-// fp32 keys in the candidate pass: of a row X = a + 2^16 s + r (a: its highest bytes, s: the second ones, r: the rest) the products a a', a s' and s a' are
-// summed, exactly.  What is left out is 2^32 s.s' + (X - r).r' + r.X', at most s s' + (1 + r) r' + r of |X| |X'| with s, r <= sqrt(dk) 2^23, sqrt(dk) 32896 over |X|.
-// rinv is 4096 / |X|, so s <= 2^11 sqrt(dk) rinv = cand_scale() rinv and r is 0.0039216 of that.  (512 elements, the largest 3.5 and 4.5 times the rms: 3.7e-4; one element that is
-// all of both rows: 8.6e-3.)  The constant is for the fp32 steps that follow, as in cos_margin().
-inline float cand_scale(int dk) { return (float)(2048.0 * sqrt((double)dk) * (1.0 + 1e-6)); }
-__device__ __forceinline__ float cand_margin(float row, float col) { return fmaf(row * 1.0001f, col, (row + col) * 0.003922f) + 5e-6f; }
 
 // Recovery (Eq. 8/9): the smallest fp32 cosine of a centre that may be within alpha d_c.
 __device__ __forceinline__ float recovery_reach(const Seg& sg, float margin) { return (1.0f - sg.alpha * sg.d_c) - margin; }

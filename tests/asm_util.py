@@ -11,8 +11,7 @@ from paper_2504_08966_amd import build as B
 
 
 @functools.lru_cache(maxsize=None)
-def kernels(source):
-    """[(name, body)] of the kernels that `source` (a file of csrc/) compiles to."""
+def _assembly(source):
     with tempfile.TemporaryDirectory() as tmp:
         out = os.path.join(tmp, "out.s")
         cmd = [B._hipcc(), *B.FLAGS, "--cuda-device-only", "-S", os.path.join(B.CSRC, source), "-o", out]
@@ -22,7 +21,21 @@ def kernels(source):
             pytest.skip("no hipcc")
         assert r.returncode == 0, r.stderr
         with open(out) as f:
-            return re.findall(r"^(_ZN4pact\w+):(.*?)^\.Lfunc_end", f.read(), re.S | re.M)
+            return f.read()
+
+
+def kernels(source):
+    """[(name, body)] of the kernels that `source` (a file of csrc/) compiles to."""
+    return re.findall(r"^(_ZN4pact\w+):(.*?)^\.Lfunc_end", _assembly(source), re.S | re.M)
+
+
+def spills(source):
+    """{name: (vector registers spilled, bytes of scratch, scalar registers spilled)} of its kernels."""
+    out = {}
+    for m in re.finditer(r"- \.agpr_count:.*?\.wavefront_size", _assembly(source), re.S):
+        of = lambda field: int(re.search(r"\." + field + r":\s+(\d+)", m.group(0)).group(1))
+        out[re.search(r"\.name:\s+(\w+)", m.group(0)).group(1)] = (of("vgpr_spill_count"), of("private_segment_fixed_size"), of("sgpr_spill_count"))
+    return out
 
 
 def registers(text):
