@@ -2,6 +2,8 @@
 // plus the per-token preparation of the clustering keys (norms, cleared bitmap rows).
 // All arithmetic of the score is fp64 (the stage is bound by reading H from HBM, the ALU work
 // is free), rounded once to fp32; the split then compares fp32 bit patterns exactly.
+#include <type_traits>
+
 #include "pact_internal.h"
 
 namespace pact {
@@ -40,9 +42,10 @@ struct FrontArgs {
 // kernel reads its columns of all chunks, 32 KB); fewer for short samples (128 rows a chunk); more for long ones with narrow queries, whose few
 // blocks would each be a chain of trips of 256 rows (16384 tokens, 512 fp32 columns: 8 chunks of 2048 rows were 128 blocks of 8 trips, 22 us for 34 MB
 // and the end of a launch of 53 us; 16 chunks: 41.  512 rows a chunk cost the logits what they gave here: 1.1 us, 14823 tokens with 14 query heads 2.4).
+constexpr int QG_NARROW = 1024;          // columns
 static int query_chunks(int n_max, int qcols) {
-    if (qcols <= 1024 && n_max > 1024 * QG_CHUNKS) return (n_max + 1023) / 1024;
-    const int most = qcols > 1024 ? QG_CHUNKS / 2 : QG_CHUNKS, want = (n_max + 127) / 128;
+    if (qcols <= QG_NARROW && n_max > 1024 * QG_CHUNKS) return (n_max + 1023) / 1024;
+    const int most = qcols > QG_NARROW ? QG_CHUNKS / 2 : QG_CHUNKS, want = (n_max + 127) / 128;
     return want < most ? want : most;
 }
 // Where the chunks' sums are: more than QG_CHUNKS of them in the place of the predecessor lists, which are made after the sums' last use.
@@ -416,10 +419,12 @@ __global__ __launch_bounds__(256) void front_kernel(Batch bt, FrontArgs a) {
 // BY_LANES (one query head per key head, a power-of-two number of 16-byte chunks per head, at most 64): the
 // lanes that hold a token's keys of the group multiply by elements of the global query in their registers; 64 / LT tokens at a time.
 // BY_HEAD: any shape; a token per wavefront, one head after the other (and if a key head's columns do not fit
-// the LDS, the chunk sums are added up where they are used).
+// the LDS, the chunk sums are added up where they are used: columns that many come in few chunks; a loop over more of them there cost
+// all of BY_HEAD 97 spilled scalar registers, 729 tokens, four heads of 72 with 28 query heads, 271 -> 289 us).
 // A launch of its own that added the chunk sums up cost 2.3 us and hid the norms' stream from the keys'.
 // grid (ceil(n_max / SCORE_TOK) x groups, B), block 256.
 constexpr int LOGITS_COLS_ANY = 15360;   // columns of the global query that fit the LDS
+static_assert(LOGITS_COLS_ANY >= QG_NARROW, "columns that do not fit the LDS come in QG_CHUNKS chunks at most");
 constexpr int LOGITS_HEADS = 16;         // query heads of a workgroup, but for BY_HEAD
 enum { BY_HEAD = 0, BY_LANES = 1, BY_MFMA = 2 };
 struct LogitsArgs {
@@ -489,22 +494,25 @@ __global__ __launch_bounds__(256) void score_logits_kernel(Batch bt, LogitsArgs 
         }
     };
     fetch(0);
-    // column j0 d_h + c of the global query
-    auto query = [&](int c) __attribute__((always_inline)) {
+    // column j0 d_h + c of the global query; `further`: there may be more than QG_CHUNKS chunks
+    auto query = [&](int c, auto further) __attribute__((always_inline)) {
         if (a.q_given) {
             const size_t at = (size_t)b * qcols + j0 * a.d_h + c;
             return a.q_bf16 ? (double)__uint_as_float((uint32_t)((const uint16_t*)a.q_given)[at] << 16) : (double)((const float*)a.q_given)[at];
         }
         const double* in = a.qg_part + (size_t)b * a.q_chunks * qcols + j0 * a.d_h + c;
         double v = 0.0;
-#pragma unroll 1
-        for (int k0 = 0; k0 < a.q_chunks; k0 += QG_CHUNKS) {
+        auto add = [&](int k0) __attribute__((always_inline)) {
             double p[QG_CHUNKS];
 #pragma unroll
             for (int k = 0; k < QG_CHUNKS; ++k) p[k] = k0 + k < a.q_chunks ? in[(size_t)(k0 + k) * qcols] : 0.0;
 #pragma unroll
             for (int k = 0; k < QG_CHUNKS; ++k) v += p[k];
-        }
+        };
+        if constexpr (decltype(further)::value) {
+#pragma unroll 1
+            for (int k0 = 0; k0 < a.q_chunks; k0 += QG_CHUNKS) add(k0);
+        } else add(0);
         return v / (double)sg.n;
     };
     // (a head's quarters one word apart from whole multiples of the LDS banks, the heads another: 64 different banks)
@@ -512,7 +520,7 @@ __global__ __launch_bounds__(256) void score_logits_kernel(Batch bt, LogitsArgs 
     if (WAY != BY_HEAD || a.qg_lds) {
 #pragma unroll 2
         for (int c = threadIdx.x; c < cols; c += 256) {
-            const double v = query(c);
+            const double v = query(c, std::true_type{});
             if constexpr (WAY == BY_MFMA) {
                 const int r = c / a.d_h, e = c - r * a.d_h, qt = e / qlen;
                 s_qg[r * hpitch + qt * qpitch + (e - qt * qlen)] = v;
@@ -573,7 +581,7 @@ __global__ __launch_bounds__(256) void score_logits_kernel(Batch bt, LogitsArgs 
 #pragma unroll
                     for (int k = 0; k < EPL; ++k) {
                         const int c = jl * a.d_h + e + k;
-                        acc = fma(x[k], a.qg_lds ? s_qg[c] : query(c), acc);
+                        acc = fma(x[k], a.qg_lds ? s_qg[c] : query(c, std::false_type{}), acc);
                     }
                 }
                 acc = wave_sum_f64(acc);
