@@ -38,14 +38,17 @@ struct FrontArgs {
     uint32_t key_share;                      // key blocks among the blocks behind the query's, in units of 2^-32, rounded up; 0: all of them first
 };
 
-// Row chunks of the query sum: 8, or 4 for wide queries, which have blocks enough (every workgroup of the logits
+// Row chunks of a sample's query sum: 8, or 4 for wide queries, which have blocks enough (every workgroup of the logits
 // kernel reads its columns of all chunks, 32 KB); fewer for short samples (128 rows a chunk); more for long ones with narrow queries, whose few
 // blocks would each be a chain of trips of 256 rows (16384 tokens, 512 fp32 columns: 8 chunks of 2048 rows were 128 blocks of 8 trips, 22 us for 34 MB
 // and the end of a launch of 53 us; 16 chunks: 41.  512 rows a chunk cost the logits what they gave here: 1.1 us, 14823 tokens with 14 query heads 2.4).
+// 16 at most, and each sample's own: with the longest one's 32 for all, 32768 tokens beside 31 of 729, 14 query heads, this launch took 62.6 us and the logits 36.2
+// (8 for all 47.4 and 30.0, so 48.6 and 31.3); 32768 tokens alone, 4 heads, logits 17.8 with 32, 15.4 with 16, 14.8 with 8, this launch 59 whatever.
 constexpr int QG_NARROW = 1024;          // columns
-static int query_chunks(int n_max, int qcols) {
-    if (qcols <= QG_NARROW && n_max > 1024 * QG_CHUNKS) return (n_max + 1023) / 1024;
-    const int most = qcols > QG_NARROW ? QG_CHUNKS / 2 : QG_CHUNKS, want = (n_max + 127) / 128;
+constexpr int QG_LONG_CHUNKS = 16;
+__host__ __device__ inline int query_chunks(int n, int qcols) {
+    const int most = qcols > QG_NARROW ? QG_CHUNKS / 2 : QG_CHUNKS, want = (n + 127) / 128;
+    if (qcols <= QG_NARROW && n > 1024 * QG_CHUNKS) return n > 1024 * QG_LONG_CHUNKS ? QG_LONG_CHUNKS : (n + 1023) / 1024;
     return want < most ? want : most;
 }
 // Where the chunks' sums are: more than QG_CHUNKS of them in the place of the predecessor lists, which are made after the sums' last use.
@@ -372,7 +375,9 @@ __global__ __launch_bounds__(256) void front_kernel(Batch bt, FrontArgs a) {
     const int cgroup = blk % ngroups, bc = blk / ngroups;
     const int b = bc / a.q_chunks, chunk = bc % a.q_chunks;
     const Seg sg = bt.s[b];
-    const int rows_per = (sg.n + a.q_chunks - 1) / a.q_chunks;
+    const int own = query_chunks(sg.n, a.qcols);
+    if (chunk >= own) return;                                    // (q_chunks: those of the longest sample)
+    const int rows_per = (sg.n + own - 1) / own;
     const int r0 = chunk * rows_per, r1 = min(sg.n, r0 + rows_per);
     const int rl = threadIdx.x >> 3, cl = threadIdx.x & 7;
     const int c = cgroup * CW + cl * EPL;
@@ -501,17 +506,18 @@ __global__ __launch_bounds__(256) void score_logits_kernel(Batch bt, LogitsArgs 
             return a.q_bf16 ? (double)__uint_as_float((uint32_t)((const uint16_t*)a.q_given)[at] << 16) : (double)((const float*)a.q_given)[at];
         }
         const double* in = a.qg_part + (size_t)b * a.q_chunks * qcols + j0 * a.d_h + c;
+        const int own = query_chunks(sg.n, qcols);
         double v = 0.0;
         auto add = [&](int k0) __attribute__((always_inline)) {
             double p[QG_CHUNKS];
 #pragma unroll
-            for (int k = 0; k < QG_CHUNKS; ++k) p[k] = k0 + k < a.q_chunks ? in[(size_t)(k0 + k) * qcols] : 0.0;
+            for (int k = 0; k < QG_CHUNKS; ++k) p[k] = k0 + k < own ? in[(size_t)(k0 + k) * qcols] : 0.0;
 #pragma unroll
             for (int k = 0; k < QG_CHUNKS; ++k) v += p[k];
         };
         if constexpr (decltype(further)::value) {
 #pragma unroll 1
-            for (int k0 = 0; k0 < a.q_chunks; k0 += QG_CHUNKS) add(k0);
+            for (int k0 = 0; k0 < own; k0 += QG_CHUNKS) add(k0);
         } else add(0);
         return v / (double)sg.n;
     };

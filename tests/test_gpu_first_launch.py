@@ -45,3 +45,21 @@ def test_query_sums_of_long_samples(n, n_kv, n_q, d_h, dtype):
     torch.cuda.synchronize()
     want = O.euti_scores(s.hidden, s.keys, s.queries)
     np.testing.assert_allclose(got[:n].cpu().numpy(), want, rtol=2e-7)          # one rounding to fp32: 6e-8, and the sums in fp64
+
+
+# samples of one batch with 16, 10, 8, 6 and 1 chunks: each has its own number, that of a call of its own
+@pytest.mark.parametrize("n_kv,n_q,d_h,dtype", [(1, 2, 32, "f32"), (2, 14, 64, "bf16"), (1, 3, 24, "f32")])
+def test_query_sums_of_a_long_sample_beside_short_ones(n_kv, n_q, d_h, dtype):
+    lens = [729, 17000, 100, 9500, 1024, 1]
+    ss = [_random_sample(700 + k, n, n_kv, n_q, d_h, 64, 0.4, dtype) for k, n in enumerate(lens)]
+    hid, ks, qs = (gu.dev(np.concatenate([x(s).reshape(s.n, -1) for s in ss]), dtype) for x in (lambda s: s.hidden, lambda s: s.keys, lambda s: s.queries))
+    off = np.concatenate([[0], np.cumsum(lens)]).astype(int)
+    o = P.pact_reduce_varlen(hid, ks, ks, qs, n_kv, d_h, n_q, off.tolist(), [P.PactParams(0.4, 0.02, 2.0, 1.5) for _ in lens])
+    torch.cuda.synchronize()
+    for k, s in enumerate(ss):
+        a, b = off[k], off[k + 1]
+        got = o["scores"][a:b]
+        one = P.pact_score(hid[a:b], ks[a:b], qs[a:b], n_kv, d_h, n_q)
+        torch.cuda.synchronize()
+        assert torch.equal(got, one[:s.n]), k
+        np.testing.assert_allclose(got.cpu().numpy(), O.euti_scores(s.hidden, s.keys, s.queries), rtol=2e-7)
