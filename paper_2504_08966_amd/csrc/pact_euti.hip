@@ -44,18 +44,13 @@ struct FrontArgs {
 // and the end of a launch of 53 us; 16 chunks: 41.  512 rows a chunk cost the logits what they gave here: 1.1 us, 14823 tokens with 14 query heads 2.4).
 // 16 at most, and each sample's own: with the longest one's 32 for all, 32768 tokens beside 31 of 729, 14 query heads, this launch took 62.6 us and the logits 36.2
 // (8 for all 47.4 and 30.0, so 48.6 and 31.3); 32768 tokens alone, 4 heads, logits 17.8 with 32, 15.4 with 16, 14.8 with 8, this launch 59 whatever.
-constexpr int QG_NARROW = 1024;          // columns
-constexpr int QG_LONG_CHUNKS = 16;
 __host__ __device__ inline int query_chunks(int n, int qcols) {
     const int most = qcols > QG_NARROW ? QG_CHUNKS / 2 : QG_CHUNKS, want = (n + 127) / 128;
     if (qcols <= QG_NARROW && n > 1024 * QG_CHUNKS) return n > 1024 * QG_LONG_CHUNKS ? QG_LONG_CHUNKS : (n + 1023) / 1024;
     return want < most ? want : most;
 }
-// Where the chunks' sums are: more than QG_CHUNKS of them in the place of the predecessor lists, which are made after the sums' last use.
-static double* query_sums(const Ws& w, int chunks) {
-    static_assert(8 * 1024 / 1024 <= PRED_CAP, "the sums of 1024 tokens of 1024 columns take less than the tokens' lists");
-    return chunks > QG_CHUNKS ? (double*)w.preds : w.qg_part;
-}
+// Where the chunks' sums are.
+static double* query_sums(const Ws& w, int chunks) { return chunks > QG_CHUNKS ? w.qg_long : w.qg_part; }
 
 // |h_g|_2 in fp64 of TPW consecutive tokens by one wavefront, 8 / TPW independent 16-byte loads in flight per
 // lane and token.

@@ -32,7 +32,9 @@ struct Batch {
 
 // ---------------------------------------------------------------------------------------
 // Workspace layout.  Offsets in bytes from the 256-aligned workspace base.
-constexpr int QG_CHUNKS = 8;          // row chunks of the global-query column sum, at most
+constexpr int QG_CHUNKS = 8;          // row chunks of the global-query column sum, at most; but of queries of
+constexpr int QG_NARROW = 1024;       // columns or fewer, in samples of more than 1024 QG_CHUNKS tokens,
+constexpr int QG_LONG_CHUNKS = 16;    // at most
 constexpr int SCORE_TOK = 64;         // tokens per workgroup in the logits kernel
 constexpr int PRED_CAP = 64;          // 16-bit slots per kept token: slot 0 = count, then up to 63 preceding neighbours
 constexpr int GRAM_MAX_WORKGROUPS = 256; // workgroups of 8 wavefronts per sample in a Gram pass (one per CU)
@@ -56,6 +58,7 @@ struct WsLayout {
     size_t adj;                                        // [B][n_max][W] u64: rows < q adjacency; from row q on: candidate words [Wc][n_pruned]
     size_t cbest;                                      // [B][W][n_max] f32: largest cosine per (group of 64 centres, pruned token)
     size_t rho, status, cnum, cmask;                   // per sample, pitch n_max (cmask: W)
+    size_t qg_long;                                    // [B][chunks][qcols] f64: more chunk sums than QG_CHUNKS (in the place of preds)
     size_t preds, heads;                               // [B][n_max][PRED_CAP] u16, [B][n_max] 4 x u16 (count + first 3; until those are
                                                        // built, the low parts of the densities: see add_density)
     size_t ksplit;                                     // [total]: fp32 clustering keys as int8 planes, [dk/64 rounded up][3][64] and [dk/64 rounded up][64]
@@ -99,6 +102,10 @@ inline WsLayout make_layout(int64_t n_max, int64_t B, int64_t total, int64_t qco
     L.cnum = take(sizeof(int32_t) * B * n_max);
     L.cmask = take(sizeof(uint64_t) * B * W);
     L.preds = take(sizeof(uint16_t) * B * n_max * PRED_CAP);
+    // (the sums are used up by the logits, before the lists are made)
+    static_assert(sizeof(double) * QG_LONG_CHUNKS * QG_NARROW <= sizeof(uint16_t) * PRED_CAP * 1024 * QG_CHUNKS,
+                  "the sums of a sample of that many tokens take no more room than its lists");
+    L.qg_long = L.preds;
     L.heads = take(sizeof(uint16_t) * 4 * B * n_max);
     L.near_list = take(sizeof(uint32_t) * 2 * B * NEAR_CAP);
     L.near_cnt = take(sizeof(int32_t) * 2 * B);   // per sample: list slots taken, ordered pairs they stand for
@@ -120,7 +127,7 @@ inline WsLayout make_layout(int64_t n_max, int64_t B, int64_t total, int64_t qco
 
 // Resolved device pointers for one call.
 struct Ws {
-    double* qg_part; double* logits; double* hnorm; double* sm_part;
+    double* qg_part; double* qg_long; double* logits; double* hnorm; double* sm_part;
     double* nn; float* rinv; int32_t* ident;
     uint64_t* adj; float* cbest; double* rho; uint32_t* status;
     int32_t* cnum; uint64_t* cmask; uint16_t* preds; uint2* heads; double* rho_lo; uint32_t* near_list; int32_t* near_cnt; uint32_t* stat;
@@ -131,7 +138,7 @@ struct Ws {
 inline Ws resolve(void* base, const WsLayout& L) {
     char* p = (char*)base;
     Ws w;
-    w.qg_part = (double*)(p + L.qg_part);
+    w.qg_part = (double*)(p + L.qg_part); w.qg_long = (double*)(p + L.qg_long);
     w.logits = (double*)(p + L.logits); w.hnorm = (double*)(p + L.hnorm);
     w.sm_part = (double*)(p + L.sm_part);
     w.nn = (double*)(p + L.nn); w.rinv = (float*)(p + L.rinv); w.ident = (int32_t*)(p + L.ident);
