@@ -983,10 +983,13 @@ int launch_front(const Batch& bt, const Ws& w, const void* keys, pact_dtype k_dt
     if (keys) {
         const int chunks = dk * (k_dt == PACT_BF16 ? 2 : 4) / 16;
         a.key_lanes = chunks <= 16 ? 16 : chunks <= 32 ? 32 : 64;
-        // Four rows per group of lanes: beside hidden states but for the smallest calls (512 wide, a row at a time / by fours: 230 tokens 4.0 / 4.4 us, 1458:
-        // 5.3 / 5.1; 2000 128 wide 4.5 / 4.1), and where one row each is more wavefronts than the chip holds (keys alone, 512 wide, 4655 tokens: 4.8 / 5.7;
-        // 7290: 6.7 / 6.2; 16384: 11.7 / 10.3).
-        a.four_keys = k_dt == PACT_BF16 && chunks <= 128 && (long)bt.total * a.key_lanes / 64 >= (score ? 400 : 6144);
+        // Four rows per group of lanes, where there are rows enough.  Beside hidden states it is their number that counts, not that of wavefronts: of fewer than 1200 the
+        // launch is one wavefront's chain, which four rows make longer (a row at a time / by fours, hidden states 3584 wide: 400 tokens 512 wide 3.9 / 4.6 us, 860 4.4 / 4.7, 1200
+        // 4.8 / 4.9, 1458 5.4 / 5.2, 9000 16.8 / 15.2; 860 128 wide 4.1 / 4.6, 1458 4.8 / 5.0, 2500 7.2 / 6.6), and rows above 1 KB are even or longer up to 5000 (1024 wide: 1020 5.0 / 5.9,
+        // 3200 8.8 / 9.2, 5000 12.5 / 12.2, 9000 18.3 / 17.5).  Keys alone: where one row each is nearly the wavefronts that the chip holds (512 wide, 6272 tokens 6.6 / 7.5,
+        // 7290 6.7 / 6.2, 16384 13.0 / 10.0; 128 wide, 16384 8.2 / 15.4, 32768 22.3 / 20.8).
+        a.four_keys = k_dt == PACT_BF16 && chunks <= 128 &&
+                      (score ? bt.total >= (chunks <= 64 ? 1200 : 5000) : (long)bt.total * a.key_lanes / 64 >= 7000);
         const int per_block = 4 * (64 / a.key_lanes) * (a.four_keys ? 4 : 1);
         a.n_key_blocks = (bt.total + per_block - 1) / per_block;
     }
