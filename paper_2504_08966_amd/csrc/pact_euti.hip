@@ -368,10 +368,15 @@ __global__ __launch_bounds__(256) void front_kernel(Batch bt, FrontArgs a) {
     __shared__ double s_part[32][CW];
     const int ngroups = (a.qcols + CW - 1) / CW;
     const int cgroup = blk % ngroups, bc = blk / ngroups;
-    const int b = bc / a.q_chunks, chunk = bc % a.q_chunks;
+    // (q_chunks: those of the longest sample.  A single one has them; its blocks are the launch's longest chains, and this is ahead of their first loads)
+    int b = 0, chunk = bc, own = a.q_chunks;
+    if (bt.B > 1) {
+        b = bc / a.q_chunks;
+        chunk = bc - b * a.q_chunks;
+        own = query_chunks(bt.s[b].n, a.qcols);
+        if (chunk >= own) return;
+    }
     const Seg sg = bt.s[b];
-    const int own = query_chunks(sg.n, a.qcols);
-    if (chunk >= own) return;                                    // (q_chunks: those of the longest sample)
     const int rows_per = (sg.n + own - 1) / own;
     const int r0 = chunk * rows_per, r1 = min(sg.n, r0 + rows_per);
     const int rl = threadIdx.x >> 3, cl = threadIdx.x & 7;
