@@ -18,6 +18,7 @@ against the HBM peak, and the CPU oracle timed on this machine's host cores on the s
 from __future__ import annotations
 
 import argparse
+import gc
 import hashlib
 import json
 import os
@@ -118,6 +119,24 @@ def kernel_times(P, torch, fn, steps):
     return {k: v / steps * 1e3 for k, v in tot.items()}, {k: c // steps for k, c in cnt.items()}
 
 
+def time_calls(torch, fn, steps):
+    """us per call, warm and back to back.  Python's cycle collector waits until after: a full collection of a process that has torch loaded takes 30 to 35 ms,
+    and one that fell into 50 calls of 320 us was once printed as 940 us each."""
+    gc.collect()
+    gc.disable()
+    try:
+        for _ in range(5):
+            fn()
+        torch.cuda.synchronize()
+        t0 = time.perf_counter()
+        for _ in range(steps):
+            fn()
+        torch.cuda.synchronize()
+        return (time.perf_counter() - t0) / steps * 1e6
+    finally:
+        gc.enable()
+
+
 def other_configs(P, gen, torch, np, only=None, steps_override=None):
     """us per call of the other workload shapes (warm, back to back), with their counts, the
     algorithmic matrix-core fraction of their density pass and HBM fraction of their merge.
@@ -133,16 +152,6 @@ def other_configs(P, gen, torch, np, only=None, steps_override=None):
         grids = sm.n // (sm.config.gh * sm.config.gw)
         heads = "" if sm.queries.shape[1] == sm.config.n_kv else f":q{sm.queries.shape[1]}"
         return man[f"{sm.config.name}:s{sm.seed}:g{grids}:l{sm.lam:.2f}{heads}"]
-
-    def timeit(fn, steps):
-        for _ in range(5):
-            fn()
-        torch.cuda.synchronize()
-        t0 = time.perf_counter()
-        for _ in range(steps):
-            fn()
-        torch.cuda.synchronize()
-        return (time.perf_counter() - t0) / steps * 1e6
 
     def fractions(kus, reps, ns, h, dk):
         """density pass: unique pairs of all samples against the bf16 matrix-core peak (fp32 keys run on the int8
@@ -178,7 +187,7 @@ def other_configs(P, gen, torch, np, only=None, steps_override=None):
         ws = P.alloc_workspace(sm.n, 1, cfg.dk, n_q, cfg.d_h, key_dtype=ks.dtype)
         o = P.pact_reduce(hid, ks, ks, qs, cfg.n_kv, cfg.d_h, n_q, prm, ws=ws)
         call = lambda: P.pact_reduce(hid, ks, ks, qs, cfg.n_kv, cfg.d_h, n_q, prm, ws=ws, out=o)
-        us = timeit(call, steps)
+        us = time_calls(torch, call, steps)
         r = P.read_report(o["rep"])
         assert r["n_kept"] == m["q"] and r["n_centers"] == m["C"], (name, r, m)
         kus, _ = kernel_times(P, torch, call, min(steps, 10))
@@ -196,7 +205,7 @@ def other_configs(P, gen, torch, np, only=None, steps_override=None):
         ws = P.alloc_workspace(sm.n, 1, sm.config.hidden, 1, 1, key_dtype=hid.dtype)
         o = P.dbdpc_cluster(hid, m["d_c"], 2.0, ws=ws)
         call = lambda: P.dbdpc_cluster(hid, m["d_c"], 2.0, ws=ws)
-        us = timeit(call, steps_override or 50)
+        us = time_calls(torch, call, steps_override or 50)
         r = P.read_report(o["rep"])
         assert r["n_centers"] == m["C"], (r, m)
         kus, _ = kernel_times(P, torch, call, 10)
@@ -226,7 +235,7 @@ def other_configs(P, gen, torch, np, only=None, steps_override=None):
         ws = P.alloc_workspace(n_max, len(samples), cfg0.dk, cfg0.n_kv, cfg0.d_h, key_dtype=ks.dtype)
         o = P.pact_reduce_varlen(hid, ks, ks, qs, cfg0.n_kv, cfg0.d_h, cfg0.n_kv, cu, prms, ws=ws)
         call = lambda: P.pact_reduce_varlen(hid, ks, ks, qs, cfg0.n_kv, cfg0.d_h, cfg0.n_kv, cu, prms, ws=ws, out=o)
-        us = timeit(call, steps)
+        us = time_calls(torch, call, steps)
         reps = P.read_report(o["rep"])
         assert [(r["n_kept"], r["n_centers"]) for r in reps] == exp, (name, reps, exp)
         kus, _ = kernel_times(P, torch, call, min(steps, 10))

@@ -1,5 +1,7 @@
 """What bench.py prints from committed measurements belongs to the sources it runs.  CPU only."""
+import gc
 import os
+import types
 
 import bench
 
@@ -39,3 +41,20 @@ def test_the_digest_is_of_the_code(tmp_path):
     assert bench.source_digest(str(tmp_path)) == first
     (tmp_path / "a.hip").write_text("int f(int x) { return 3 * x; }\n")
     assert bench.source_digest(str(tmp_path)) != first
+
+
+def test_no_full_collection_while_calls_are_timed():
+    torch = types.SimpleNamespace(cuda=types.SimpleNamespace(synchronize=lambda: None))
+    kept, seen = [], []
+
+    def collection(phase, info):
+        if phase == "start" and kept:                    # (one before the first call is wanted)
+            seen.append(info["generation"])
+
+    gc.callbacks.append(collection)
+    try:
+        bench.time_calls(torch, lambda: kept.extend([] for _ in range(20000)), 10)
+        during = list(seen)
+    finally:
+        gc.callbacks.remove(collection)
+    assert not during and gc.isenabled()
