@@ -43,18 +43,20 @@ def test_the_digest_is_of_the_code(tmp_path):
     assert bench.source_digest(str(tmp_path)) != first
 
 
-def test_no_full_collection_while_calls_are_timed():
+def test_no_collection_while_calls_are_timed():
     torch = types.SimpleNamespace(cuda=types.SimpleNamespace(synchronize=lambda: None))
-    kept, seen = [], []
+    kept, seen, at = [], [], []
 
     def collection(phase, info):
-        if phase == "start" and kept:                    # (one before the first call is wanted)
-            seen.append(info["generation"])
+        seen.append(info["generation"])
+
+    def call():
+        at.append(len(seen))
+        kept.extend([] for _ in range(20000))
 
     gc.callbacks.append(collection)
     try:
-        bench.time_calls(torch, lambda: kept.extend([] for _ in range(20000)), 10)
-        during = list(seen)
+        bench.time_calls(torch, call, 10)
     finally:
         gc.callbacks.remove(collection)
-    assert not during and gc.isenabled()
+    assert seen and at[0] == at[-1] and gc.isenabled()    # (one before the first call)
