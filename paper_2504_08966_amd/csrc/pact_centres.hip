@@ -1928,7 +1928,7 @@ __global__ __launch_bounds__(512, 4) void assign_tile_kernel(Batch bt, NearArgs 
     const float rt = rinv[tok];
     for (int w = tid; w < Wq; w += 512) s_union[w] = 0ull;
     if (tid == 0) s_ntodo = 0;
-    // the token's centres in reach: how many (at most one per lane counts), and the first
+    // the lane's part of the centres in reach: how many, and the first
     auto inside = [&](uint64_t word, int w) __attribute__((always_inline)) {
         if (w == Wq - 1 && (q & 63)) word &= (1ull << (q & 63)) - 1ull;
         return w < Wq && on && !centre ? word : 0ull;

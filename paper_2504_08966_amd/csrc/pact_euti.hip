@@ -13,7 +13,7 @@ namespace pact {
 // independent jobs share one launch, so that the small ones hide behind the stream of hidden states:
 //   blocks [0, n_q_blocks)            : Eq. 1 pass 1, column sums of one row chunk of Q and 128 bytes of
 //                                       its columns (32 row lanes x 8 lanes of 16 bytes; eight rows in
-//                                       flight per lane).  QG_CHUNKS chunks at most: the logits kernel
+//                                       flight per lane).  Few chunks (query_chunks()): the logits kernel
 //                                       adds them up again in every workgroup;
 //   blocks [.., + n_key_blocks)       : squared key norm (fp64), reciprocal norm (fp32), fp32 keys' int8
 //                                       planes, cleared bitmap row, per-token initial state (status,
