@@ -12,9 +12,9 @@ from tests.test_gpu_parity import _random_sample
 pytestmark = pytest.mark.gpu
 
 
-# more than one turn of whole tiles: rows of more than 512 elements take those (2945: a last tile of one token), shorter ones halves, 5800 tokens of 64 (eight
-# turns and more) too
-@pytest.mark.parametrize("n,dk", [(2945, 520), (3000, 576), (2945, 512), (5800, 64), (5801, 128)])
+# more than one turn of whole tiles: rows of more than 512 elements take those where their last turn is as full as that of the halves (2945, 3457: a last tile of one token; whole
+# tiles: the last two), shorter ones halves, 5800 tokens of 64 (eight turns and more) too
+@pytest.mark.parametrize("n,dk", [(2945, 520), (3000, 576), (2945, 512), (5800, 64), (5801, 128), (3457, 1032), (3500, 1600)])
 def test_clustering(n, dk):
     _check_clustering(n, dk, "f32")
 
