@@ -2412,7 +2412,12 @@ static int launch_nearest(const Batch& bt, NearArgs a, int recover_blocks, pact_
 
 // Which rows: event brackets of the assignment, a token per wavefront -> tiles, clustering alone, 300 / 1000 / 2000 / 4000 / 7290 tokens: 3584 wide 26 -> 19, 39 -> 19, 54 -> 27,
 // 70 -> 26, 63 -> 31; 2048: 14 -> 12, 21 -> 16, 21 -> 15, 27 -> 17, 22 -> 20; 1024: 6.5 -> 6.6, 7.8 -> 9.2, 7.9 -> 9.2, 9.2 -> 9.6, 11.2 -> 12.8; 512: 10 -> 16 to 17 -> 24.
-static bool assigns_by_tiles(int dk, int k_dt) { return k_dt == PACT_BF16 && dk * 2 > 2048; }
+// Between 2 and 3.5 KB only where all rows together are 1.5 times what an XCD's L2 holds: a token per wavefront reads them again from there.  200 / 729 / 2000 / 3000 / 6000 tokens: 1032 wide
+// 12.0 -> 14.6, 13.6 -> 14.0, 14.0 -> 16.0, 20.2 -> 20.2, 25.0 -> 21.9; 1280: 14.8 -> 15.3, 16.2 -> 18.1, 19.4 -> 21.2, 23.0 -> 20.4, 27.4 -> 26.2; 1536: 13.1 -> 14.7, 15.3 -> 17.3,
+// 21.7 -> 20.1, 23.9 -> 20.7, 33.2 -> 25.7; 1792: 18.4 -> 15.6, 18.5 -> 15.4, 27.0 -> 22.2, 25.0 -> 20.0, 37.6 -> 26.4.
+static bool assigns_by_tiles(const Batch& bt, int dk, int k_dt) {
+    return k_dt == PACT_BF16 && dk * 2 > 2048 && (dk * 2 >= 3584 || (long)bt.n_max * dk * 2 >= 6000000);
+}
 static int launch_assign_tiles(const Batch& bt, NearArgs a, const float* rinv, hipStream_t st) {
     a.rinv = rinv;
     PACT_LAUNCH("assign", assign_tile_kernel, dim3((bt.n_max + 127) / 128 * 8, bt.B), dim3(512), st, bt, a, assign_tile_margin(a.dk));
@@ -2513,7 +2518,7 @@ int launch_centres(const Batch& bt, const Ws& w, const void* keys, pact_dtype k_
     a.rep = rep; a.keys = k; a.dk = dk; a.nn = w.nn; a.adj = w.adj; a.margin = (float)cos_margin(dk, k_dt);
     a.cluster_id = cluster_id; a.cluster_counts = cluster_counts;
     a.idx = idx; a.cmask = w.cmask; a.status = w.status; a.cnum = w.cnum;
-    if (assigns_by_tiles(dk, k_dt)) return launch_assign_tiles(bt, a, w.rinv, st);
+    if (assigns_by_tiles(bt, dk, k_dt)) return launch_assign_tiles(bt, a, w.rinv, st);
     a.assign_blocks = 1;
     return launch_nearest(bt, a, 0, k_dt, "assign", st);
 }

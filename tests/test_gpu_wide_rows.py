@@ -22,9 +22,11 @@ def _check(u, dtype, d_c, d_n=2.0):
     return rep, ref
 
 
+# bf16 rows below 3.5 KB take the products from 6 MB of them on (the last size; the first three are compared by wavefronts);
 # widths of whole and broken 64-byte steps and wavefronts' parts; a last sixteen of one token; one, two and more turns of 32 centres in reach
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
-@pytest.mark.parametrize("n,dk,blob", [(2, 1032, 1), (17, 1032, 6), (300, 1544, 24), (1009, 2048, 24), (700, 3584, 100), (1201, 4104, 40)])
+@pytest.mark.parametrize("n,dk,blob", [(2, 1032, 1), (17, 1032, 6), (300, 1544, 24), (1009, 2048, 24), (700, 3584, 100), (1201, 4104, 40),
+                                       (2, 1800, 1), (17, 1800, 6), (300, 2056, 24), (3001, 1032, 24)])
 def test_neighbours_near_the_cutoff(n, dk, blob, dtype):
     r = np.random.default_rng(n + dk)
     cen = r.normal(size=(n // blob + 1, dk))
