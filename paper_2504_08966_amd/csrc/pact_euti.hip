@@ -988,13 +988,14 @@ int launch_front(const Batch& bt, const Ws& w, const void* keys, pact_dtype k_dt
     if (keys) {
         const int chunks = dk * (k_dt == PACT_BF16 ? 2 : 4) / 16;
         a.key_lanes = chunks <= 16 ? 16 : chunks <= 32 ? 32 : 64;
-        // Four rows per group of lanes, where there are rows enough.  Beside hidden states it is their number that counts, not that of wavefronts: of fewer than 1200 the
-        // launch is one wavefront's chain, which four rows make longer (a row at a time / by fours, hidden states 3584 wide: 400 tokens 512 wide 3.9 / 4.6 us, 860 4.4 / 4.7, 1200
-        // 4.8 / 4.9, 1458 5.4 / 5.2, 9000 16.8 / 15.2; 860 128 wide 4.1 / 4.6, 1458 4.8 / 5.0, 2500 7.2 / 6.6), and rows above 1 KB are even or longer up to 5000 (1024 wide: 1020 5.0 / 5.9,
-        // 3200 8.8 / 9.2, 5000 12.5 / 12.2, 9000 18.3 / 17.5).  Keys alone: where one row each is nearly the wavefronts that the chip holds (512 wide, 6272 tokens 6.6 / 7.5,
-        // 7290 6.7 / 6.2, 16384 13.0 / 10.0; 128 wide, 16384 8.2 / 15.4, 32768 22.3 / 20.8).
-        a.four_keys = k_dt == PACT_BF16 && chunks <= 128 &&
-                      (score ? bt.total >= (chunks <= 64 ? 1200 : 5000) : (long)bt.total * a.key_lanes / 64 >= 7000);
+        // Four rows per group of lanes, where there are rows enough.  Beside hidden states it is their number that counts: of few the launch is one wavefront's chain, which four rows make longer (event
+        // brackets, a row at a time / by fours, hidden states 896 wide; 128 wide 1200 tokens 7.6 / 8.2 us, 3000 8.5 / 7.7, 6500 10.4 / 9.4; 512 wide 860 4.4 / 4.7 and 1458 5.4 / 5.2 of the kernel itself;
+        // 1024 wide, 3584 beside, 3000 10.3 / 10.7, 4500 13.1 / 12.5).  In batches more so, as rows of four in two samples, which look for their samples one by one, are likely the last ones (1 us: 16
+        // samples, 128 wide 2000 tokens 7.2 / 8.0, 3000 6.8 / 8.3, 4500 7.7 / 8.0, 6500 8.0 / 8.2, 20000 14.3 / 13.6; 256 wide 4500 8.6 / 8.3, 6500 9.1 / 8.8; 512 wide 1200 6.8 / 7.4, 3000
+        // 8.3 / 7.5, 6500 11.7 / 9.8).  Keys alone: where one row each is nearly the wavefronts that the chip holds (512 wide, 6272 tokens 6.6 / 7.5, 7290 6.7 / 6.2, 16384 13.0 / 10.0; 128 wide,
+        // 16384 8.2 / 15.4, 32768 22.3 / 20.8).
+        const int rows_enough = chunks > 64 ? 5000 : chunks > 32 ? (bt.B > 1 ? 3000 : 1200) : bt.B > 1 ? 5000 : 2500;
+        a.four_keys = k_dt == PACT_BF16 && chunks <= 128 && (score ? bt.total >= rows_enough : (long)bt.total * a.key_lanes / 64 >= 7000);
         const int per_block = 4 * (64 / a.key_lanes) * (a.four_keys ? 4 : 1);
         a.n_key_blocks = (bt.total + per_block - 1) / per_block;
     }
