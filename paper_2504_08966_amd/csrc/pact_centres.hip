@@ -199,8 +199,18 @@ __global__ __launch_bounds__(256) void settle_kernel(Batch bt, const char* __res
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
     const int gw = blockIdx.x * 4 + wave;
-    const uint32_t raw = (uint32_t)near_cnt[2 * b];
-    const int cnt_all = (int)min(raw, (uint32_t)NEAR_CAP);
+    // the parts' counters, a lane each, and where in the list as a whole each part begins
+    const int parts = near_parts(bt.n_max, bt.B), room = NEAR_CAP / parts;
+    const uint2 taken = lane < parts ? *(const uint2*)(near_cnt + (b * NEAR_PARTS + lane) * NEAR_COUNTER) : make_uint2(0u, 0u);
+    const int in_part = (int)min(taken.x, (uint32_t)room), ends = parts > 1 ? wave_scan_incl_i32(in_part) : in_part;
+    const int cnt_all = __builtin_amdgcn_readlane(ends, parts > 1 ? 63 : 0);
+    auto place = [&](int e) __attribute__((always_inline)) {         // of entry e of the list as a whole
+        if (parts == 1) return e;
+        int part = 0;
+#pragma unroll
+        for (int k = 0; k < NEAR_PARTS - 1; ++k) part += e >= __builtin_amdgcn_readlane(ends, k) ? 1 : 0;
+        return part * room + e - __shfl(ends - in_part, part, 64);
+    };
     // wide rows: an eighth of the list per XCD (workgroups are dealt to them round-robin; the grid is a multiple of 8): neighbouring pairs are of one tile of the
     // density pass and share rows, which its L2 then holds
     const int xcd = blockIdx.x & 7;
@@ -218,7 +228,11 @@ __global__ __launch_bounds__(256) void settle_kernel(Batch bt, const char* __res
         }
 #pragma unroll
         for (int sft = 32; sft >= 1; sft >>= 1) fb = max(fb, (uint32_t)__shfl_xor((int)fb, sft, 64));
-        if (lane == 0) report_settled(rep + b, raw, near_cnt[2 * b + 1], fb, sg.d_n);
+        const bool overflow = __ballot(lane < parts && taken.x <= (uint32_t)room) == 0;
+        int ordered = (int)taken.y;
+#pragma unroll
+        for (int sft = 32; sft >= 1; sft >>= 1) ordered += __shfl_xor(ordered, sft, 64);
+        if (lane == 0) report_settled(rep + b, overflow, ordered, fb, sg.d_n);
     }
     constexpr int EPL = Elem<DT>::EPL;
     const size_t row_bytes = (size_t)dk * Elem<DT>::BYTES;
@@ -236,8 +250,9 @@ __global__ __launch_bounds__(256) void settle_kernel(Batch bt, const char* __res
         uint32_t my_pi = 0, my_pj = 0;
         int my_ti = 0, my_tj = 0;
         double my_ni = 0.0, my_nj = 0.0;
+        const int at = place(min(my_e, cnt - 1));
         if (my_e < cnt) {
-            const uint2 pr = *(const uint2*)(near_list + ((size_t)b * NEAR_CAP + my_e) * 2);
+            const uint2 pr = *(const uint2*)(near_list + ((size_t)b * NEAR_CAP + at) * 2);
             my_pi = pr.x; my_pj = pr.y;
             my_ti = ix[my_pi & ~NEAR_MIRROR]; my_tj = ix[my_pj];
             my_ni = nnb[my_ti]; my_nj = nnb[my_tj];
@@ -1279,8 +1294,9 @@ __device__ __forceinline__ int select_sample(const Batch& bt, const CentresArgs&
     uint2 pr[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) pr[u] = settle ? pairs[u * ng + g] : make_uint2(0, 0);      // (garbage beyond the count, never used)
-    const uint32_t raw = settle ? (uint32_t)sa.near_cnt[2 * b] : 0u;
-    const int checked = settle ? sa.near_cnt[2 * b + 1] : 0;
+    static_assert(SMALL_TOKENS <= 1024, "one part (near_parts)");
+    const uint32_t raw = settle ? (uint32_t)sa.near_cnt[b * NEAR_PARTS * NEAR_COUNTER] : 0u;
+    const int checked = settle ? sa.near_cnt[b * NEAR_PARTS * NEAR_COUNTER + 1] : 0;
     const int q = clamp_count(rep->n_kept, sg.n), Wq = (q + 63) >> 6;
     const int cnt = (int)min(raw, (uint32_t)NEAR_CAP);
     if (a.idx_ahead != a.idx && tid < q) tok = ix[tid];
@@ -1440,7 +1456,7 @@ __device__ __forceinline__ int select_sample(const Batch& bt, const CentresArgs&
                 uint32_t fb = 0u;
                 if (sa.far_words > 0)
                     for (int k = 0; k < 16; ++k) fb = max(fb, sh.far[k]);
-                report_settled(rep, raw, checked, fb, sg.d_n);
+                report_settled(rep, raw > (uint32_t)NEAR_CAP, checked, fb, sg.d_n);
             }
         }
     }

@@ -327,9 +327,9 @@ __global__ __launch_bounds__(256) void front_kernel(Batch bt, FrontArgs a) {
         blk = (int)key_no;
         if (blk == 0) {
             if (threadIdx.x < 64) a.zeros[threadIdx.x] = 0u;
+            for (int k = (int)threadIdx.x; k < bt.B * NEAR_PARTS; k += 256) *(int2*)(a.near_cnt + k * NEAR_COUNTER) = make_int2(0, 0);
             const int b = (int)threadIdx.x;
             if (b < bt.B) {
-                a.near_cnt[2 * b] = 0; a.near_cnt[2 * b + 1] = 0;
 #pragma unroll
                 for (int k = 0; k < 4; ++k) a.tie_cnt[4 * b + k] = 0;
                 pact_report* rp = a.rep + b;

@@ -39,6 +39,11 @@ constexpr int SCORE_TOK = 64;         // tokens per workgroup in the logits kern
 constexpr int PRED_CAP = 64;          // 16-bit slots per kept token: slot 0 = count, then up to 63 preceding neighbours
 constexpr int GRAM_MAX_WORKGROUPS = 256; // workgroups of 8 wavefronts per sample in a Gram pass (one per CU)
 constexpr int NEAR_CAP = 1 << 16;     // near-threshold pairs kept for fp64 re-evaluation, per sample
+// The list of a sample is in parts of equal size, each with a counter on a cache line of its own.  (One counter answers a hundred atomics a microsecond: an image's density
+// pass, 700 wavefronts with undecided pairs, waited 4 us for it at its end.)  Samples of up to 1024 tokens, whose workgroups are few, have one, and those of
+// batches, whose workgroups are fewer and at it at other times (finding a pair's part took 16 ragged images' settling 3 us, their density pass gained 2 without).
+constexpr int NEAR_PARTS = 16, NEAR_COUNTER = 32;      // (words of a counter: places taken, ordered pairs they stand for, unused)
+__host__ __device__ inline int near_parts(int n_max, int batch) { return n_max > 1024 && batch <= 3 ? NEAR_PARTS : 1; }
 constexpr uint32_t NEAR_MIRROR = 0x80000000u;   // flag in a listed pair's row: the pair (col, row) is meant as well
 constexpr float EXACT_SUMS_D_N = 0.21f;      // from this d_n on the density sums are exact in any order (see add_density)
 constexpr uint32_t ST_UNKNOWN = 0, ST_CENTER = 1, ST_NOT = 2;
@@ -108,7 +113,7 @@ inline WsLayout make_layout(int64_t n_max, int64_t B, int64_t total, int64_t qco
     L.qg_long = L.preds;
     L.heads = take(sizeof(uint16_t) * 4 * B * n_max);
     L.near_list = take(sizeof(uint32_t) * 2 * B * NEAR_CAP);
-    L.near_cnt = take(sizeof(int32_t) * 2 * B);   // per sample: list slots taken, ordered pairs they stand for
+    L.near_cnt = take(sizeof(int32_t) * NEAR_COUNTER * NEAR_PARTS * B);
     L.stat = take(sizeof(uint32_t) * B * GRAM_MAX_WORKGROUPS * 8);   // Shape::STAT_WORDS of each workgroup of the density pass
     L.tie_list = take(sizeof(int32_t) * B * RHO_RECHECK_MAX);
     L.tie_cnt = take(sizeof(int32_t) * 4 * B);
@@ -458,12 +463,12 @@ __device__ __forceinline__ float candidate_cut(float& top, float rj, float margi
     return fabsf(cutv) < INFINITY ? cutv : -INFINITY;          // (a zero vector, or nearly infinite ones: all are candidates)
 }
 
-// What settling a sample's undecided pairs reports.  listed: list slots asked for, ordered: ordered pairs they stand for (a pair that stands for
+// What settling a sample's undecided pairs reports.  overflow: the list held not all of them, ordered: ordered pairs they stand for (a pair that stands for
 // both orders counts twice).  far_bits: of the most negative exponent -(d / d_n) log2(e) that the density pass saw (negative floats order
 // like their bits), 0 where it was not asked to look.
-__device__ __forceinline__ void report_settled(pact_report* rep, uint32_t listed, int ordered, uint32_t far_bits, float d_n) {
-    rep->dc_checked_pairs = listed > (uint32_t)NEAR_CAP ? NEAR_CAP : ordered;
-    rep->refine_overflow = listed > (uint32_t)NEAR_CAP ? OVERFLOW_NEAR_LIST : 0;
+__device__ __forceinline__ void report_settled(pact_report* rep, bool overflow, int ordered, uint32_t far_bits, float d_n) {
+    rep->dc_checked_pairs = overflow ? NEAR_CAP : ordered;
+    rep->refine_overflow = overflow ? OVERFLOW_NEAR_LIST : 0;
     rep->max_key_distance = far_bits ? fminf(-__uint_as_float(far_bits) * d_n * 0.6931471805599453f, 2.0f) : 0.0f;
 }
 // ... and what a pair's fp64 distance decides: no neighbours beyond d_c; how many near-ties to count.
