@@ -126,10 +126,10 @@ static int run_reduce(const Batch& bt, const Ws& w, const ReduceIO& io, hipStrea
     const int32_t dk = io.n_kv * io.d_h;
     ScoreIn si{io.hidden, io.h_dt, io.h, io.keys_pre, io.k_dt, io.n_kv, io.d_h, io.q, io.q_dt,
                io.q_per_token, io.n_q};
-    int rc = launch_front(bt, w, io.keys, io.k_dt, dk, &si, io.rep, io.cluster_id, io.cluster_counts, INIT_REDUCE, nullptr, st);
+    const ReductionIn red{{io.keys, io.k_dt, dk}, io.rep, io.cluster_id, io.cluster_counts};
+    int rc = launch_score(bt, w, si, io.scores, &red, st);
     if (rc) return rc;
-    if ((rc = launch_score(bt, w, si, io.scores, true, st))) return rc;
-    if ((rc = launch_score_prune(bt, &w, io.n_q, io.scores, w.adj, io.kept_idx, io.pruned_idx, io.rep, st))) return rc;
+    if ((rc = launch_score_prune(bt, &w, &si, io.scores, &red, io.kept_idx, io.pruned_idx, io.rep, st))) return rc;
     bool want_stat = false;                  // the key-distance statistic: only if a sample asks for it
     for (int b = 0; b < bt.B; ++b) want_stat = want_stat || (bt.s[b].flags & PACT_FLAG_KEY_STATS);
     int stat_words = 0;
@@ -188,8 +188,7 @@ int pact_score(const void* hidden, pact_dtype h_dt, int32_t n, int32_t h,
     const Ws w = resolve(ws, L);
     hipStream_t st = (hipStream_t)stream;
     ScoreIn si{hidden, h_dt, h, keys_pre, k_dt, n_kv, d_h, q, q_dt, q_rows == n ? 1 : 0, n_q};
-    if ((rc = launch_front(bt, w, nullptr, k_dt, 0, &si, nullptr, nullptr, nullptr, INIT_SCORE, nullptr, st))) return rc;
-    return launch_score(bt, w, si, scores, false, st);
+    return launch_score(bt, w, si, scores, nullptr, st);
 }
 
 int pact_prune(const float* scores, int32_t n, float lambda,
@@ -205,7 +204,7 @@ int pact_prune(const float* scores, int32_t n, float lambda,
     p.lambda = lambda;
     Batch bt;
     fill_single(bt, n, p);
-    return launch_score_prune(bt, nullptr, 0, const_cast<float*>(scores), nullptr, kept_idx, pruned_idx, rep, (hipStream_t)stream);
+    return launch_score_prune(bt, nullptr, nullptr, const_cast<float*>(scores), nullptr, kept_idx, pruned_idx, rep, (hipStream_t)stream);
 }
 
 int dbdpc_cluster(const void* keys, pact_dtype k_dt, int32_t n, int32_t dk,
@@ -231,8 +230,7 @@ int dbdpc_cluster(const void* keys, pact_dtype k_dt, int32_t n, int32_t dk,
     fill_single(bt, n, p);
     const Ws w = resolve(ws, L);
     hipStream_t st = (hipStream_t)stream;
-    if ((rc = launch_front(bt, w, keys, k_dt, dk, nullptr, rep, cluster_id, nullptr,
-                           idx ? INIT_DBDPC_SUBSET : INIT_DBDPC_ALL, n_idx_dev, st))) return rc;
+    if ((rc = launch_front(bt, w, KeysIn{keys, k_dt, dk}, rep, cluster_id, idx ? INIT_DBDPC_SUBSET : INIT_DBDPC_ALL, n_idx_dev, st))) return rc;
     const int32_t* use_idx = idx ? idx : w.ident;
     int stat_words = 0;
     if ((rc = launch_gram_density(bt, w, keys, k_dt, dk, use_idx, rep, true, &stat_words, st))) return rc;
@@ -259,7 +257,7 @@ int pact_reincorporate(const void* keys, pact_dtype k_dt, int32_t n, int32_t dk,
     fill_single(bt, n, p);
     const Ws w = resolve(ws, L);
     hipStream_t st = (hipStream_t)stream;
-    if ((rc = launch_front(bt, w, keys, k_dt, dk, nullptr, rep, cluster_id, nullptr, INIT_REINC, nullptr, st))) return rc;
+    if ((rc = launch_front(bt, w, KeysIn{keys, k_dt, dk}, rep, cluster_id, INIT_REINC, nullptr, st))) return rc;
     return launch_reincorporate(bt, w, keys, k_dt, dk, pruned_idx, center_idx, cluster_id, nullptr, rep, true,
                                 nullptr, st);
 }

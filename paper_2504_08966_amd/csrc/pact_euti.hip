@@ -9,44 +9,36 @@
 namespace pact {
 
 // ------------------------------------------------------------------------------------------
-// First kernel of a call: everything that reads the inputs once and depends on nothing else.  Three
-// independent jobs share one launch, so that the small ones hide behind the stream of hidden states:
-//   blocks [0, n_q_blocks)            : Eq. 1 pass 1, column sums of one row chunk of Q and 128 bytes of
-//                                       its columns (32 row lanes x 8 lanes of 16 bytes; eight rows in
-//                                       flight per lane).  Few chunks (query_chunks()): the logits kernel
-//                                       adds them up again in every workgroup;
-//   blocks [.., + n_key_blocks)       : squared key norm (fp64), reciprocal norm (fp32), fp32 keys' int8
-//                                       planes, cleared bitmap row, per-token initial state (status,
-//                                       cluster id, counts); 16 to 64 lanes per token by the row's width;
-//   the other blocks                  : |h_i|_2 in fp64, one wavefront per token or, for rows of at most
-//                                       4 KB, several tokens per wavefront (eight loads in flight per lane).
-// Keys and hidden states are walked by token of the whole batch (no blocks for the tokens that
-// shorter samples do not have).  Bound by HBM, and nearly by the vector units (conversions to fp64): 7290 tokens of 3584 bf16 with 4 / 28 query
-// heads 67 / 112 MB, 14.7 -> 13.2 / 25.2 -> 23 us; 16 x 2688 tokens 396 MB in 64 us, 8 x 6272 462 MB, 89.5 -> 81 (a plain read of as much: 71); 32 x 729 of 896
-// 90 MB, 19.4 -> 18.2; 16384 of 3584 with fp32 keys 185 MB, 54.4 -> 44 (before: a key row at a time, longer query chunks).
-// grid (blocks), block 256.
-struct FrontArgs {
+// What depends on the inputs alone:
+//   query sums    : Eq. 1 pass 1, column sums of one row chunk of Q and 128 bytes of
+//                   its columns (32 row lanes x 8 lanes of 16 bytes; eight rows in
+//                   flight per lane).  Few chunks (query_chunks()): the logits kernel
+//                   adds them up again in every workgroup;
+//   clustering keys: squared norm (fp64), reciprocal norm (fp32), fp32 keys' int8
+//                   planes, cleared bitmap row, per-token initial state (status,
+//                   cluster id, counts); 16 to 64 lanes per token by the row's width;
+//   |h_i|_2 in fp64: one wavefront per token or, for rows of at most 4 KB, several tokens per wavefront (eight loads in flight per lane).
+// Keys and hidden states are walked by token of the whole batch (no blocks for the tokens that shorter samples do not have).
+// The first launch of a reduction is the query sums, the second the logits, both short of work: the hidden states' norms, most of a
+// call's bytes, are dealt to both, and the keys are in the second or beside the percentile split (launch_score()).  A clustering alone has its keys in a launch of their own.
+constexpr int FRONT_THREADS = 256;
+struct KeyArgs {
     const char* keys; int32_t dk;
-    const char* q; int32_t qcols;            // q == nullptr: no query pass
-    const char* hidden; int32_t h; int32_t h_bf16; int32_t stream;   // hidden == nullptr: no norms
-    double* nn; float* rinv; uint64_t* adj; double* rho; double* rho_lo; double* qg_part; double* hnorm;
+    double* nn; float* rinv; uint64_t* adj; double* rho; double* rho_lo;
     uint32_t* status; int32_t* ident; int32_t* near_cnt; int32_t* tie_cnt;
     pact_report* rep; int32_t* cluster_id; int32_t* cluster_counts;
     const int32_t* n_idx_dev; uint32_t* zeros;
     char* ksplit;                            // fp32 keys only: the int8 planes for the Gram passes
-    int32_t mode; int32_t n_q_blocks, n_key_blocks, q_chunks, key_lanes, four_keys;
-    uint32_t key_share;                      // key blocks among the blocks behind the query's, in units of 2^-32, rounded up; 0: all of them first
+    int32_t mode, key_lanes, rows_each;      // lanes per row; rows per group of them
 };
-
-// Row chunks of a sample's query sum: 8, or 4 for wide queries, which have blocks enough (every workgroup of the logits
-// kernel reads its columns of all chunks, 32 KB); fewer for short samples (128 rows a chunk); more for long ones with narrow queries, whose few
-// blocks would each be a chain of trips of 256 rows (16384 tokens, 512 fp32 columns: 8 chunks of 2048 rows were 128 blocks of 8 trips, 22 us for 34 MB
-// and the end of a launch of 53 us; 16 chunks: 41.  512 rows a chunk cost the logits what they gave here: 1.1 us, 14823 tokens with 14 query heads 2.4).
-// 16 at most, and each sample's own: with the longest one's 32 for all, 32768 tokens beside 31 of 729, 14 query heads, this launch took 62.6 us and the logits 36.2
-// (8 for all 47.4 and 30.0, so 48.6 and 31.3); 32768 tokens alone, 4 heads, logits 17.8 with 32, 15.4 with 16, 14.8 with 8, this launch 59 whatever.
+// Row chunks of a sample's query sum: of 128 rows, 8 at most, of wide queries, which have strips enough, 4 up to 4096 tokens (every workgroup of the logits
+// kernel reads its columns of all chunks, 32 KB); 16 at most of long ones with narrow queries, whose few
+// blocks would each be a chain of trips of 256 rows (16384 tokens, 512 fp32 columns: 8 chunks of 2048 rows were 128 blocks of 8 trips, 22 us for 34 MB).  Each sample its own number: with the longest
+// one's for all, 32768 tokens beside 31 of 729, 14 query heads, both launches were a third longer.
 __host__ __device__ inline int query_chunks(int n, int qcols) {
-    const int most = qcols > QG_NARROW ? QG_CHUNKS / 2 : QG_CHUNKS, want = (n + 127) / 128;
-    if (qcols <= QG_NARROW && n > 1024 * QG_CHUNKS) return n > 1024 * QG_LONG_CHUNKS ? QG_LONG_CHUNKS : (n + 1023) / 1024;
+    const bool wide = qcols > QG_NARROW;
+    if (!wide && n > 1024 * QG_CHUNKS) return n > 1024 * QG_LONG_CHUNKS ? QG_LONG_CHUNKS : (n + 1023) / 1024;
+    const int most = wide && n <= 4096 ? QG_CHUNKS / 2 : QG_CHUNKS, want = (n + 127) / 128;
     return want < most ? want : most;
 }
 // Where the chunks' sums are.
@@ -97,13 +89,18 @@ __host__ __device__ inline int hnorm_tokens(int h, int elem_bytes) {
     const int loads = (h * elem_bytes + 1023) / 1024;      // 16-byte loads per lane and row
     return loads <= 2 ? 4 : loads <= 4 ? 2 : 1;
 }
+struct NormArgs { const char* hidden; double* hnorm; int32_t h, h_bf16, stream, from, to; };      // tokens [from, to) of the batch
 template <int HDT>
-__device__ __forceinline__ void hnorm_job(const FrontArgs& a, int wave_no, int total, int lane) {
-    const int tpw = hnorm_tokens(a.h, Elem<HDT>::BYTES), g0 = wave_no * tpw;
-    if (g0 >= total) return;
-    if (tpw == 4) hnorm_rows<HDT, 4>(a.hidden, a.h, g0, total, lane, a.hnorm, a.stream != 0);
-    else if (tpw == 2) hnorm_rows<HDT, 2>(a.hidden, a.h, g0, total, lane, a.hnorm, a.stream != 0);
-    else hnorm_rows<HDT, 1>(a.hidden, a.h, g0, total, lane, a.hnorm, a.stream != 0);
+__device__ __forceinline__ void hnorm_job(const NormArgs& a, int wave_no, int lane) {
+    const int tpw = hnorm_tokens(a.h, Elem<HDT>::BYTES), g0 = a.from + wave_no * tpw;
+    if (g0 >= a.to) return;
+    if (tpw == 4) hnorm_rows<HDT, 4>(a.hidden, a.h, g0, a.to, lane, a.hnorm, a.stream != 0);
+    else if (tpw == 2) hnorm_rows<HDT, 2>(a.hidden, a.h, g0, a.to, lane, a.hnorm, a.stream != 0);
+    else hnorm_rows<HDT, 1>(a.hidden, a.h, g0, a.to, lane, a.hnorm, a.stream != 0);
+}
+__device__ __forceinline__ void norm_block(const NormArgs& a, int wave_no, int lane) {
+    if (a.h_bf16) hnorm_job<PACT_BF16>(a, wave_no, lane);
+    else hnorm_job<PACT_F32>(a, wave_no, lane);
 }
 
 // Sample that token g of the batch belongs to (g the same for the wavefront: scalar loads, a vector load of an argument is a trip to memory).
@@ -119,13 +116,13 @@ __device__ __forceinline__ int sample_of(const Batch& bt, int g) {
 // n - m rows and columns unless scores tie at the threshold (Eq. 3 / 4); the split
 // clears the rest itself in that case.  Token i of sample b, by KL lanes.
 template <int KL>
-__device__ __forceinline__ void clear_bits(const Batch& bt, const FrontArgs& a, int b, const Seg& sg, int i, int kl) {
+__device__ __forceinline__ void clear_bits(const Batch& bt, const KeyArgs& a, int b, const Seg& sg, int i, int kl) {
     uint64_t* arow = a.adj + ((size_t)b * bt.n_max + i) * bt.W;
     const int side = (a.mode == INIT_REDUCE) ? sg.n - prune_rank(sg.lambda, sg.n) : sg.n;
     const int Wn = (i < side) ? (side + 63) >> 6 : 0;
     for (int k = kl; k < Wn; k += KL) arow[k] = 0ull;
 }
-__device__ __forceinline__ void start_token(const Batch& bt, const FrontArgs& a, int b, const Seg& sg, int i, double v, float rinv) {
+__device__ __forceinline__ void start_token(const Batch& bt, const KeyArgs& a, int b, const Seg& sg, int i, double v, float rinv) {
     const size_t g = (size_t)sg.base + i;
     a.nn[g] = v;
     a.rinv[g] = rinv;
@@ -139,10 +136,41 @@ __device__ __forceinline__ void start_token(const Batch& bt, const FrontArgs& a,
     }
 }
 
+// A row of fp32 keys as 32-bit integers X = rint(x S) (S: its largest element becomes 2139062143 = 0x7F7F7F7F, or a power of
+// four less for rows of more than 2^17 elements, whose order-0 sums would not fit an int32), split
+// into four signed bytes: the upper three in turn, 64 elements of each, then all of the lowest; padded with zeros.
+// The Gram passes' products are in units of 2^24, so that the reciprocal norm is 4096 / |X|.  It is rounded up to fp32 and S is
+// taken from what that is the reciprocal of: it is then exact.  v: squared norm, top: largest element.
+__device__ __forceinline__ double bytes_scale(double v, float top, int dk, float& rinv) {
+    double most = 2139062143.0;
+    for (int64_t d = dk; d > 131072; d >>= 2) most *= 0.5;
+    double S = top > 0.0f ? most / (double)top : 0.0;
+    if (v > 0.0) {
+        const double len = sqrt(v);
+        rinv = __double2float_ru(4096.0 / (S * len));
+        if (v < INFINITY) S = 4096.0 / ((double)rinv * len);
+    }
+    return S;
+}
+// Four elements from element e on, to the planes at sp.  X + 0x80808080 has the signed bytes of X, each 128 more, as its
+// unsigned ones (|X| <= 0x7F7F7F7F); then bytes of four words to four words of a byte each.
+__device__ __forceinline__ void store_bytes(char* sp, int groups, int e, const float (&x)[8], double S) {
+    uint32_t w[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) w[k] = ((uint32_t)(int)rint((double)x[k] * S) + 0x80808080u) ^ 0x80808080u;
+    const uint32_t a01 = __builtin_amdgcn_perm(w[1], w[0], 0x05010400u), b01 = __builtin_amdgcn_perm(w[1], w[0], 0x07030602u);
+    const uint32_t a23 = __builtin_amdgcn_perm(w[3], w[2], 0x05010400u), b23 = __builtin_amdgcn_perm(w[3], w[2], 0x07030602u);
+    char* at = sp + (size_t)(e >> 6) * 192 + (e & 63);
+    *(uint32_t*)at = __builtin_amdgcn_perm(b23, b01, 0x07060302u);
+    *(uint32_t*)(at + 64) = __builtin_amdgcn_perm(b23, b01, 0x05040100u);
+    *(uint32_t*)(at + 128) = __builtin_amdgcn_perm(a23, a01, 0x07060302u);
+    *(uint32_t*)(sp + (size_t)groups * 192 + e) = __builtin_amdgcn_perm(a23, a01, 0x05040100u);
+}
+
 // One clustering key by KL lanes (16, 32 or 64; a row of at most KL 16-byte chunks for KL < 64): the
 // values are those of wave_dot64 whatever KL (the lanes it leaves out would add zeros).
 template <int KDT, int KL>
-__device__ __forceinline__ void key_job(const Batch& bt, const FrontArgs& a, int wave_no, int lane) {
+__device__ __forceinline__ void key_job(const Batch& bt, const KeyArgs& a, int wave_no, int lane) {
     constexpr int EPL = Elem<KDT>::EPL;
     const int kl = lane & (KL - 1);
     const int g0 = wave_no * (64 / KL);
@@ -174,11 +202,6 @@ __device__ __forceinline__ void key_job(const Batch& bt, const FrontArgs& a, int
     const double v = group_sum_f64(acc, KL);
     float rinv = v > 0.0 ? (float)(1.0 / sqrt(v)) : 0.0f;
     if constexpr (KDT == PACT_F32) {
-        // The row as 32-bit integers X = rint(x S) (S: its largest element becomes 2139062143 = 0x7F7F7F7F, or a power of
-        // four less for rows of more than 2^17 elements, whose order-0 sums would not fit an int32), split
-        // into four signed bytes: the upper three in turn, 64 elements of each, then all of the lowest; padded with zeros.
-        // The Gram passes' products are in units of 2^24, so that the reciprocal norm is 4096 / |X|.  It is rounded up to fp32 and S is
-        // taken from what that is the reciprocal of: it is then exact.
         float top = 0.0f;
         for (int e = kl * 4; e < a.dk; e += 4 * KL) {
             float x[8];
@@ -188,101 +211,113 @@ __device__ __forceinline__ void key_job(const Batch& bt, const FrontArgs& a, int
         top = group_max_f32<16>(top);
 #pragma unroll
         for (int sft = 16; sft < KL; sft <<= 1) top = fmaxf(top, __shfl_xor(top, sft, 64));
-        double most = 2139062143.0;
-        for (int64_t d = a.dk; d > 131072; d >>= 2) most *= 0.5;
-        double S = top > 0.0f ? most / (double)top : 0.0;
-        if (v > 0.0) {
-            const double len = sqrt(v);
-            rinv = __double2float_ru(4096.0 / (S * len));
-            if (v < INFINITY) S = 4096.0 / ((double)rinv * len);
-        }
+        const double S = bytes_scale(v, top, a.dk, rinv);
         const int groups = (a.dk + 63) / 64;
         char* sp = a.ksplit + g * (size_t)groups * 256;
         for (int e = kl * 4; e < groups * 64; e += 4 * KL) {
             float x[8];
             Elem<KDT>::widenf(chunk(e), x);                            // (zeros past the row's end)
-            uint32_t part[4] = {0u, 0u, 0u, 0u};
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                int X = (int)rint((double)x[k] * S);
-#pragma unroll
-                for (int pl = 3; pl >= 0; --pl) {
-                    const int byte = (int)(int8_t)(X & 255);
-                    part[pl] |= (uint32_t)(byte & 255) << (8 * k);
-                    X = (X - byte) >> 8;
-                }
-            }
-#pragma unroll
-            for (int pl = 0; pl < 3; ++pl) *(uint32_t*)(sp + (size_t)(e >> 6) * 192 + pl * 64 + (e & 63)) = part[pl];
-            *(uint32_t*)(sp + (size_t)groups * 192 + e) = part[3];
+            store_bytes(sp, groups, e, x, S);
         }
     }
     clear_bits<KL>(bt, a, b, sg, i, kl);
     if (kl == 0) start_token(bt, a, b, sg, i, v, rinv);
 }
 
-// Values of four rows per lane (v[t]: row t), each summed over KL lanes as group_sum_f64 does it (neighbours, then pairs 2, 4, 8, 16 and 32
-// apart; the same pairs, so the same bits): a lane gives up half of its rows at each of the first two steps and is left with row
-// lane & 3.  Half the instructions of four sums.
-template <int KL> __device__ __forceinline__ double four_sums(const double (&v)[4], int lane) {
-    auto halve = [&](double a, double b, bool low, auto other) __attribute__((always_inline)) {
-        const double own = low ? a : b;
-        return own + other(low ? b : a);
-    };
-    const bool e1 = (lane & 1) == 0, e2 = (lane & 2) == 0;
-    auto x1 = [](double d) __attribute__((always_inline)) { return dpp_f64<DPP_XOR1>(d); };
-    auto x2 = [](double d) __attribute__((always_inline)) { return dpp_f64<DPP_XOR2>(d); };
-    const double s0 = halve(v[0], v[1], e1, x1), s1 = halve(v[2], v[3], e1, x1);
-    double s = halve(s0, s1, e2, x2);
-    s += dpp_xor4_f64(s);
-    s += dpp_f64<0x128>(s);                                          // row_ror:8
+// Values of T rows per lane (v[t]: row t), each combined over KL lanes as group_sum_f64 does it (neighbours, then pairs 2, 4, 8, 16 and 32
+// apart; the same pairs, so the same bits): a lane gives up half of its rows at each step until it is left with row
+// lane % T.  T = 4: half the instructions of four sums.
+template <int T, int KL, class V, class F, class X> __device__ __forceinline__ V over_lanes(V (&v)[T], int lane, F&& join, X&& from) {
+    static_assert(T == 2 || T == 4 || T == 8 || T == 16, "a row per lane in the end, inside a row of 16 lanes");
 #pragma unroll
-    for (int sft = 16; sft < KL; sft <<= 1) s += __shfl_xor(s, sft, 64);
-    return s;
+    for (int s = 0, left = T; (1 << s) < KL; ++s) {
+        if (left > 1) {
+            const bool low = ((lane >> s) & 1) == 0;
+            left >>= 1;
+#pragma unroll
+            for (int k = 0; k < left; ++k) {
+                const V own = low ? v[2 * k] : v[2 * k + 1], give = low ? v[2 * k + 1] : v[2 * k];
+                v[k] = join(own, from(give, s));
+            }
+        } else v[0] = join(v[0], from(v[0], s));
+    }
+    return v[0];
+}
+__device__ __forceinline__ double apart_f64(double d, int s) {
+    return s == 0 ? dpp_f64<DPP_XOR1>(d) : s == 1 ? dpp_f64<DPP_XOR2>(d) : s == 2 ? dpp_xor4_f64(d) : s == 3 ? dpp_f64<0x128>(d) : __shfl_xor(d, 1 << s, 64);      // (row_ror:8)
 }
 
-// bf16 keys of up to two 16-byte chunks a lane: four rows per group of KL lanes, whose chunks are requested together, and what is one value per row -
-// the square root, the reciprocal, the stores - is done for all of them at once, a row per lane.  (Row by row that is 150
-// instructions of a whole wavefront for each token, as much as the hidden states' part of the wavefronts beside it: 8 x 6272 tokens 512 wide, keys and hidden states
-// 77.5 -> 65 us, one image 13.8 -> 11.7.  fp32 keys, whose split into bytes is most of the work, and wide rows are the shorter a row at a time.)
-template <int KL>
-__device__ __forceinline__ void four_keys_job(const Batch& bt, const FrontArgs& a, int wave_no, int lane) {
-    constexpr int EPL = 8, ROWS = 64 / KL;
+// T rows per group of KL lanes, U 16-byte chunks a lane, which are requested together; what is one value per row -
+// the square root, the reciprocals, the stores - is done for all of them at once, a row per lane.  (Row by row that is 150
+// instructions of a whole wavefront for each token, as much as the hidden states' part was: 8 x 6272 tokens 512 wide, keys and hidden states
+// 77.5 -> 65 us, one image 13.8 -> 11.7.)
+template <int KDT, int KL, int T, int U>
+__device__ __forceinline__ void many_keys_job(const Batch& bt, const KeyArgs& a, int wave_no, int lane) {
+    constexpr int EPL = Elem<KDT>::EPL, ROWS = 64 / KL;
     const int kl = lane & (KL - 1);
-    const int g0 = wave_no * (ROWS * 4);
+    const int g0 = wave_no * (ROWS * T);
     if (g0 >= bt.total) return;
     const int grp = KL < 64 ? lane / KL : 0;                         // this group's rows: g0 + grp + ROWS t
     const uint4 none = make_uint4(0, 0, 0, 0);
-    uint4 c[4][2];
+    const size_t row_bytes = (size_t)a.dk * Elem<KDT>::BYTES;
+    uint4 c[T][U];
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
-        const char* row = a.keys + (size_t)min(g0 + grp + ROWS * t, bt.total - 1) * (size_t)a.dk * 2;
+    for (int t = 0; t < T; ++t) {
+        const char* row = a.keys + (size_t)min(g0 + grp + ROWS * t, bt.total - 1) * row_bytes;
 #pragma unroll
-        for (int u = 0; u < 2; ++u) c[t][u] = (u * KL + kl) * EPL < a.dk ? *(const uint4*)(row + (size_t)(u * KL + kl) * 16) : none;
+        for (int u = 0; u < U; ++u) c[t][u] = (u * KL + kl) * EPL < a.dk ? *(const uint4*)(row + (size_t)(u * KL + kl) * 16) : none;
     }
     const int b0 = sample_of(bt, g0);
-    double acc[4];
+    double acc[T];
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
+    for (int t = 0; t < T; ++t) {
         acc[t] = 0.0;
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            if (u * KL * EPL >= a.dk) break;                         // (uniform)
+        for (int u = 0; u < U; ++u) {
             double x[8];
-            Elem<PACT_BF16>::widen(c[t][u], x);
+            Elem<KDT>::widen(c[t][u], x);
 #pragma unroll
             for (int k = 0; k < EPL; ++k) acc[t] = fma(x[k], x[k], acc[t]);
         }
     }
-    const double v = four_sums<KL>(acc, lane);                       // from here on a lane has row lane & 3 of its group's
-    const float rinv = v > 0.0 ? (float)(1.0 / sqrt(v)) : 0.0f;
-    const int mine = g0 + grp + ROWS * (lane & 3);
-    const int end = b0 + 1 < bt.B ? bt.s[b0 + 1].base : bt.total;
-    if (g0 + ROWS * 4 <= end) {                                      // all of one sample (uniform)
-        const Seg sg = bt.s[b0];
+    const double v = over_lanes<T, KL>(acc, lane, [](double x, double y) { return x + y; }, apart_f64);    // from here on a lane has row lane % T of its group's
+    float rinv = v > 0.0 ? (float)(1.0 / sqrt(v)) : 0.0f;
+    if constexpr (KDT == PACT_F32) {
+        float tops[T];
 #pragma unroll
-        for (int t = 0; t < 4; ++t) clear_bits<KL>(bt, a, b0, sg, g0 + grp + ROWS * t - sg.base, kl);
-        if (kl < 4) start_token(bt, a, b0, sg, mine - sg.base, v, rinv);
+        for (int t = 0; t < T; ++t) {
+            tops[t] = 0.0f;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                float x[8];
+                Elem<KDT>::widenf(c[t][u], x);
+                tops[t] = fmaxf(fmaxf(tops[t], fmaxf(fabsf(x[0]), fabsf(x[1]))), fmaxf(fabsf(x[2]), fabsf(x[3])));
+            }
+        }
+        const float top = over_lanes<T, KL>(tops, lane, [](float x, float y) { return fmaxf(x, y); },
+                                            [](float d, int s) { return __shfl_xor(d, 1 << s, 64); });
+        const double S = bytes_scale(v, top, a.dk, rinv);
+        const int groups = (a.dk + 63) / 64;
+#pragma unroll
+        for (int t = 0; t < T; ++t) {
+            const int g = g0 + grp + ROWS * t;
+            const double St = __shfl(S, (lane & ~(KL - 1)) | t, 64);
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int e = (u * KL + kl) * 4;
+                float x[8];
+                Elem<KDT>::widenf(c[t][u], x);
+                if (g < bt.total && e < groups * 64) store_bytes(a.ksplit + (size_t)g * groups * 256, groups, e, x, St);
+            }
+        }
+    }
+    const int mine = g0 + grp + ROWS * (lane & (T - 1));
+    const int end = b0 + 1 < bt.B ? bt.s[b0 + 1].base : bt.total;
+    if (g0 + ROWS * T <= end) {                                      // all of one sample (uniform)
+        const Seg sg = bt.s[b0];
+#pragma unroll 4
+        for (int t = 0; t < T; ++t) clear_bits<KL>(bt, a, b0, sg, g0 + grp + ROWS * t - sg.base, kl);
+        if (kl < T) start_token(bt, a, b0, sg, mine - sg.base, v, rinv);
         return;
     }
     auto sample_from = [&](int g) __attribute__((always_inline)) {
@@ -291,81 +326,83 @@ __device__ __forceinline__ void four_keys_job(const Batch& bt, const FrontArgs& 
         return b;
     };
 #pragma unroll 1
-    for (int t = 0; t < 4; ++t) {
+    for (int t = 0; t < T; ++t) {
         const int g = g0 + grp + ROWS * t;
         if (g < bt.total) {
             const int b = sample_from(g);
             clear_bits<KL>(bt, a, b, bt.s[b], g - bt.s[b].base, kl);
         }
     }
-    if (kl < 4 && mine < bt.total) {
+    if (kl < T && mine < bt.total) {
         const int b = sample_from(mine);
         start_token(bt, a, b, bt.s[b], mine - bt.s[b].base, v, rinv);
     }
 }
 
+// Block `blk` of those of the clustering keys (WAVES wavefronts each), of which the first also clears counters and starts the reports.
+template <int KDT, int WAVES>
+__device__ __forceinline__ void key_block(const Batch& bt, const KeyArgs& a, int blk, int wave, int lane) {
+    if (blk == 0) {
+        if (threadIdx.x < 64) a.zeros[threadIdx.x] = 0u;
+        for (int k = (int)threadIdx.x; k < bt.B * NEAR_PARTS; k += 64 * WAVES) *(int2*)(a.near_cnt + k * NEAR_COUNTER) = make_int2(0, 0);
+        const int b = (int)threadIdx.x;
+        if (b < bt.B) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) a.tie_cnt[4 * b + k] = 0;
+            pact_report* rp = a.rep + b;
+            const int mode = a.mode, n = bt.s[b].n;
+            if (mode == INIT_REDUCE || mode == INIT_DBDPC_ALL || mode == INIT_DBDPC_SUBSET) {
+                if (mode != INIT_REDUCE) {
+                    const int k = (mode == INIT_DBDPC_ALL) ? n : min(max(*a.n_idx_dev, 0), n);
+                    rp->n_kept = k;
+                    rp->n_pruned = (mode == INIT_DBDPC_ALL) ? 0 : n - k;
+                }
+                rp->n_centers = 0; rp->rounds = 0; rp->dc_checked_pairs = 0; rp->dc_near_ties = 0;
+                rp->refine_overflow = 0; rp->n_reincorporated = 0; rp->n_dropped = 0;
+                rp->zero_norm_seen = 0;     // counted by the assignment kernels, which run later
+                rp->max_key_distance = 0.0f;
+                rp->rho_rechecked = 0; rp->rho_near_ties = 0;
+                // (the split's two counters: a clustering call on a subset adds to them, in a reduction the split writes them, in this launch)
+                if (mode == INIT_DBDPC_ALL) { rp->score_near_ties = 0; rp->nonfinite_seen = 0; }
+                rp->reserved[0] = 0;
+            }
+            if (mode == INIT_REINC) { rp->n_reincorporated = 0; rp->n_dropped = 0; }
+        }
+    }
+    const int wave_no = blk * WAVES + wave;
+    if (a.rows_each > 1) {
+        constexpr int T = KDT == PACT_BF16 ? 4 : 2;
+        if (a.key_lanes == 16) many_keys_job<KDT, 16, T, 1>(bt, a, wave_no, lane);
+        else if (a.key_lanes == 32) many_keys_job<KDT, 32, T, 1>(bt, a, wave_no, lane);
+        else if (KDT == PACT_BF16 && a.rows_each == 8) many_keys_job<PACT_BF16, 64, 8, 1>(bt, a, wave_no, lane);
+        else many_keys_job<KDT, 64, T, 2>(bt, a, wave_no, lane);
+    }
+    else if (a.key_lanes == 16) key_job<KDT, 16>(bt, a, wave_no, lane);
+    else if (a.key_lanes == 32) key_job<KDT, 32>(bt, a, wave_no, lane);
+    else key_job<KDT, 64>(bt, a, wave_no, lane);
+}
+
+// The keys of a clustering or recovery that is called alone.  grid (blocks), block 256.
+template <int KDT>
+__global__ __launch_bounds__(256) void front_kernel(Batch bt, KeyArgs a) {
+    key_block<KDT, 4>(bt, a, blockIdx.x, __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), threadIdx.x & 63);
+}
+
+// The query sums: first launch of a reduction with per-token queries; and, behind their blocks, keys and hidden states' norms.
+// grid (strips of columns x chunks x B + keys' + norms'), block FRONT_THREADS.
+struct QueryArgs { const char* q; double* qg_part; int32_t qcols, q_chunks, blocks, key_blocks; NormArgs norm; KeyArgs key; };
 template <int KDT, int QDT>
-__global__ __launch_bounds__(256) void front_kernel(Batch bt, FrontArgs a) {
+__global__ __launch_bounds__(FRONT_THREADS) void query_sums_kernel(Batch bt, QueryArgs a) {
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    int blk = blockIdx.x;
-    if (blk >= a.n_q_blocks) {
-        // key blocks: ahead of those of the hidden states, or evenly among them (see launch_front)
-        const uint32_t at = (uint32_t)(blk - a.n_q_blocks);
-        uint32_t key_no = min(at, (uint32_t)a.n_key_blocks);
-        bool keys_here = at < (uint32_t)a.n_key_blocks;
-        if (a.key_share) {
-            key_no = __umulhi(at, a.key_share);
-            keys_here = __umulhi(at + 1, a.key_share) != key_no;
-        }
-        if (!keys_here) {
-            const int wave_no = (int)(at - key_no) * 4 + wave;
-            if (a.h_bf16) hnorm_job<PACT_BF16>(a, wave_no, bt.total, lane);
-            else hnorm_job<PACT_F32>(a, wave_no, bt.total, lane);
-            return;
-        }
-        blk = (int)key_no;
-        if (blk == 0) {
-            if (threadIdx.x < 64) a.zeros[threadIdx.x] = 0u;
-            for (int k = (int)threadIdx.x; k < bt.B * NEAR_PARTS; k += 256) *(int2*)(a.near_cnt + k * NEAR_COUNTER) = make_int2(0, 0);
-            const int b = (int)threadIdx.x;
-            if (b < bt.B) {
-#pragma unroll
-                for (int k = 0; k < 4; ++k) a.tie_cnt[4 * b + k] = 0;
-                pact_report* rp = a.rep + b;
-                const int mode = a.mode, n = bt.s[b].n;
-                if (mode == INIT_REDUCE || mode == INIT_DBDPC_ALL || mode == INIT_DBDPC_SUBSET) {
-                    if (mode != INIT_REDUCE) {
-                        const int k = (mode == INIT_DBDPC_ALL) ? n : min(max(*a.n_idx_dev, 0), n);
-                        rp->n_kept = k;
-                        rp->n_pruned = (mode == INIT_DBDPC_ALL) ? 0 : n - k;
-                    }
-                    rp->n_centers = 0; rp->rounds = 0; rp->dc_checked_pairs = 0; rp->dc_near_ties = 0;
-                    rp->refine_overflow = 0; rp->n_reincorporated = 0; rp->n_dropped = 0;
-                    rp->zero_norm_seen = 0;     // counted by the assignment kernels, which run later
-                    rp->max_key_distance = 0.0f;
-                    rp->rho_rechecked = 0; rp->rho_near_ties = 0;
-                    // (a clustering call on a subset follows a split, whose two counters it adds to)
-                    if (mode != INIT_DBDPC_SUBSET) { rp->score_near_ties = 0; rp->nonfinite_seen = 0; }
-                    rp->reserved[0] = 0;
-                }
-                if (mode == INIT_REINC) { rp->n_reincorporated = 0; rp->n_dropped = 0; }
-            }
-        }
-        const int wave_no = blk * 4 + wave;
-        if (KDT == PACT_BF16 && a.four_keys) {
-            if (a.key_lanes == 16) four_keys_job<16>(bt, a, wave_no, lane);
-            else if (a.key_lanes == 32) four_keys_job<32>(bt, a, wave_no, lane);
-            else four_keys_job<64>(bt, a, wave_no, lane);
-        }
-        else if (a.key_lanes == 16) key_job<KDT, 16>(bt, a, wave_no, lane);
-        else if (a.key_lanes == 32) key_job<KDT, 32>(bt, a, wave_no, lane);
-        else key_job<KDT, 64>(bt, a, wave_no, lane);
-        return;
+    const int blk = blockIdx.x;
+    if (blk >= a.blocks) {
+        const int at = blk - a.blocks;
+        if (at < a.key_blocks) return key_block<KDT, FRONT_THREADS / 64>(bt, a.key, at, wave, lane);
+        return norm_block(a.norm, (at - a.key_blocks) * (FRONT_THREADS / 64) + wave, lane);
     }
-    // ---- Eq. 1, pass 1
-    constexpr int EPL = Elem<QDT>::EPL, CW = 8 * EPL;            // columns of a block
-    __shared__ double s_part[32][CW];
+    constexpr int EPL = Elem<QDT>::EPL, CW = 8 * EPL, RL = FRONT_THREADS / 8, U = 8;      // columns of a block, rows in a step, steps in flight
+    __shared__ double s_part[FRONT_THREADS / 64][CW];
     const int ngroups = (a.qcols + CW - 1) / CW;
     const int cgroup = blk % ngroups, bc = blk / ngroups;
     // (q_chunks: those of the longest sample.  A single one has them; its blocks are the launch's longest chains, and this is ahead of their first loads)
@@ -387,26 +424,44 @@ __global__ __launch_bounds__(256) void front_kernel(Batch bt, FrontArgs a) {
     double acc[EPL];
 #pragma unroll
     for (int k = 0; k < EPL; ++k) acc[k] = 0.0;
-    for (int r = r0 + rl; r < r1; r += 32 * 8) {
-        uint4 v[8];
+    for (int rb = r0; rb < r1; rb += RL * U) {
+        uint4 v[U];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = r + 32 * u < r1 ? *(const uint4*)(base + (size_t)(r + 32 * u) * row_bytes) : make_uint4(0, 0, 0, 0);
+        for (int u = 0; u < U; ++u) {
+            if (rb + RL * u >= r1) break;                        // (uniform)
+            v[u] = rb + RL * u + rl < r1 ? *(const uint4*)(base + (size_t)(rb + RL * u + rl) * row_bytes) : make_uint4(0, 0, 0, 0);
+        }
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
+        for (int u = 0; u < U; ++u) {
+            if (rb + RL * u >= r1) break;
             double x[8];
             Elem<QDT>::widen(v[u], x);
 #pragma unroll
             for (int k = 0; k < EPL; ++k) acc[k] += x[k];
         }
     }
+    // over the wavefront's eight row lanes (lane bits 3 to 5): a lane gives up half of its columns at each step, as long as it has two
+    int own_c = 0;
 #pragma unroll
-    for (int k = 0; k < EPL; ++k) s_part[rl][cl * EPL + k] = acc[k];
+    for (int s = 0; s < 3; ++s) {
+        const int left = EPL >> s;
+        const bool up = ((lane >> (3 + s)) & 1) != 0;
+        if (left >= 2) {
+#pragma unroll
+            for (int k = 0; k < left / 2; ++k) {
+                const double keep = up ? acc[k + left / 2] : acc[k], give = up ? acc[k] : acc[k + left / 2];
+                acc[k] = keep + __shfl_xor(give, 8 << s, 64);
+            }
+            own_c += up ? left / 2 : 0;
+        } else acc[0] += __shfl_xor(acc[0], 8 << s, 64);
+    }
+    s_part[wave][cl * EPL + own_c] = acc[0];
     __syncthreads();
     const int oc = cgroup * CW + (int)threadIdx.x;
     if ((int)threadIdx.x < CW && oc < a.qcols) {
         double t = 0.0;
 #pragma unroll
-        for (int k = 0; k < 32; ++k) t += s_part[k][threadIdx.x];
+        for (int k = 0; k < FRONT_THREADS / 64; ++k) t += s_part[k][threadIdx.x];
         a.qg_part[((size_t)b * a.q_chunks + chunk) * a.qcols + oc] = t;
     }
 }
@@ -427,7 +482,8 @@ __global__ __launch_bounds__(256) void front_kernel(Batch bt, FrontArgs a) {
 // the LDS, the chunk sums are added up where they are used: columns that many come in few chunks; a loop over more of them there cost
 // all of BY_HEAD 97 spilled scalar registers, 729 tokens, four heads of 72 with 28 query heads, 271 -> 289 us).
 // A launch of its own that added the chunk sums up cost 2.3 us and hid the norms' stream from the keys'.
-// grid (ceil(n_max / SCORE_TOK) x groups, B), block 256.
+// Behind the workgroups of the logits, which are bound by latency, those of hidden states' norms, bound by HBM, and of the clustering keys.
+// grid (ceil(n_max / SCORE_TOK) x groups x B + norms' + keys'), block 256.
 constexpr int LOGITS_COLS_ANY = 15360;   // columns of the global query that fit the LDS
 static_assert(LOGITS_COLS_ANY >= QG_NARROW, "columns that do not fit the LDS come in QG_CHUNKS chunks at most");
 constexpr int LOGITS_HEADS = 16;         // query heads of a workgroup, but for BY_HEAD
@@ -437,6 +493,12 @@ struct LogitsArgs {
     const double* qg_part; const char* q_given; int32_t q_bf16, q_chunks;     // q_given: the caller's global query
     double* expl; double* sm_part;
     int32_t kv_heads, qg_lds;            // key heads per group; whether their columns are in LDS
+    int32_t blocks, logits_blocks;       // workgroups of a sample; of all samples
+};
+struct LogitsMoreArgs {
+    NormArgs norm;
+    KeyArgs key; int32_t key_blocks;
+    uint32_t key_share;                  // key blocks among those behind the logits', in units of 2^-32, rounded up; 0: all of them first
 };
 // Key heads per workgroup of BY_HEAD.
 static int logits_kv_heads_any(int n_kv, int n_q, int d_h) {
@@ -462,19 +524,23 @@ static int logits_kv_heads_lanes(const Batch& bt, int n_kv, int lph) {
 }
 
 template <int KDT, int WAY>
-__global__ __launch_bounds__(256) void score_logits_kernel(Batch bt, LogitsArgs a) {
+__device__ __forceinline__ void logits_block(const Batch& bt, const LogitsArgs& a) {
     constexpr int EPL = Elem<KDT>::EPL;
     constexpr int HEADS = WAY == BY_HEAD ? PACT_MAX_QHEADS : LOGITS_HEADS;
     extern __shared__ double s_qg[];     // BY_MFMA: [rep][4 quarters, padded]; otherwise [columns]
     __shared__ double s_l[HEADS][SCORE_TOK + 1];
-    const int b = blockIdx.y;
-    const Seg sg = bt.s[b];
-    const int n_groups = a.n_kv / a.kv_heads;
-    const int tb = blockIdx.x / n_groups, kv0 = (blockIdx.x - tb * n_groups) * a.kv_heads;
-    const int t0 = tb * SCORE_TOK;
-    if (t0 >= sg.n) return;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    int b = 0, blk = blockIdx.x;
+    if (bt.B > 1) {
+        b = (uint32_t)blk / (uint32_t)a.blocks;
+        blk -= b * a.blocks;
+    }
+    const Seg sg = bt.s[b];
+    const int n_groups = a.n_kv / a.kv_heads;
+    const int tb = (uint32_t)blk / (uint32_t)n_groups, kv0 = (blk - tb * n_groups) * a.kv_heads;
+    const int t0 = tb * SCORE_TOK;
+    if (t0 >= sg.n) return;
     const int rep = a.n_q / a.n_kv, qcols = a.n_q * a.d_h;
     const int j0 = kv0 * rep, heads = a.kv_heads * rep, cols = heads * a.d_h;     // this workgroup's query heads and columns
     const size_t krow = (size_t)a.n_kv * a.d_h * Elem<KDT>::BYTES;
@@ -615,6 +681,28 @@ __global__ __launch_bounds__(256) void score_logits_kernel(Batch bt, LogitsArgs 
     }
 }
 
+template <int KDT, int WAY>
+__global__ __launch_bounds__(256) void score_logits_kernel(Batch bt, LogitsArgs a) {
+    logits_block<KDT, WAY>(bt, a);
+}
+// With keys or hidden states behind them.
+template <int KDT, int WAY>
+__global__ __launch_bounds__(256) void score_logits_more_kernel(Batch bt, LogitsArgs a, LogitsMoreArgs m) {
+    if ((int)blockIdx.x < a.logits_blocks) return logits_block<KDT, WAY>(bt, a);
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    // key blocks: ahead of those of the hidden states, or evenly among them (see launch_logits)
+    const uint32_t at = blockIdx.x - (uint32_t)a.logits_blocks;
+    uint32_t key_no = min(at, (uint32_t)m.key_blocks);
+    bool keys_here = at < (uint32_t)m.key_blocks;
+    if (m.key_share) {
+        key_no = __umulhi(at, m.key_share);
+        keys_here = __umulhi(at + 1, m.key_share) != key_no;
+    }
+    if (keys_here) key_block<KDT, 4>(bt, m.key, (int)key_no, wave, lane);
+    else norm_block(m.norm, (int)(at - key_no) * 4 + wave, lane);
+}
+
 // ------------------------------------------------------------------------------------------
 // Eq. 2, pass 2: the softmax statistics of every head from the token blocks' partials, and from them the
 // factor exp(m_block - M) / Z of each (block, head); then s_i = |h_i| (1/n_q) sum_j e_ij factor_j.
@@ -741,11 +829,11 @@ __device__ __forceinline__ int counts_before(const int* s_cnt, int lane, int wav
 }
 
 template <bool FINISH, int KREG>
-__global__ __launch_bounds__(1024) void score_prune_kernel(Batch bt, FinishArgs fin, float* scores,
-                                                           uint64_t* __restrict__ adj,
-                                                           int32_t* __restrict__ kept_idx,
-                                                           int32_t* __restrict__ pruned_idx,
-                                                           pact_report* __restrict__ rep) {
+__device__ __forceinline__ void prune_block(const Batch& bt, const FinishArgs& fin, float* scores,
+                                            uint64_t* __restrict__ adj,
+                                            int32_t* __restrict__ kept_idx,
+                                            int32_t* __restrict__ pruned_idx,
+                                            pact_report* __restrict__ rep) {
     __shared__ __align__(16) int s_hist[256 * 16];           // (cleared and scanned four bins at a time)
     __shared__ int s_bin[256];
     __shared__ int s_sel[2][2];
@@ -961,72 +1049,82 @@ __global__ __launch_bounds__(1024) void score_prune_kernel(Batch bt, FinishArgs 
     }
 }
 
+struct PruneArgs { FinishArgs fin; float* scores; uint64_t* adj; int32_t *kept_idx, *pruned_idx; pact_report* rep; };
+template <bool FINISH, int KREG>
+__global__ __launch_bounds__(1024) void score_prune_kernel(Batch bt, PruneArgs a) {
+    prune_block<FINISH, KREG>(bt, a.fin, a.scores, a.adj, a.kept_idx, a.pruned_idx, a.rep);
+}
+// With the clustering keys of the call (KDT: their type) behind the samples' workgroups.  (The split alone is half a microsecond longer with their code.)
+template <bool FINISH, int KREG, int KDT>
+__global__ __launch_bounds__(1024) void score_prune_keys_kernel(Batch bt, PruneArgs a, KeyArgs key) {
+    if ((int)blockIdx.x < bt.B) prune_block<FINISH, KREG>(bt, a.fin, a.scores, a.adj, a.kept_idx, a.pruned_idx, a.rep);
+    else key_block<KDT, 16>(bt, key, (int)blockIdx.x - bt.B, __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), threadIdx.x & 63);
+}
+
 // ------------------------------------------------------------------------------------------
 static hipError_t raise_lds_limit(const void* fn, size_t bytes) {
     return hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
 }
 
-template <int KDT>
-static int launch_front_q(const Batch& bt, const FrontArgs& a, pact_dtype q_dt, dim3 grid, hipStream_t st) {
-    if (q_dt == PACT_BF16)
-        PACT_LAUNCH("front", (front_kernel<KDT, PACT_BF16>), grid, dim3(256), st, bt, a);
-    else
-        PACT_LAUNCH("front", (front_kernel<KDT, PACT_F32>), grid, dim3(256), st, bt, a);
+// What the workgroups of a call's clustering keys need, `waves` wavefronts each; their number.
+static int key_args(KeyArgs& a, const Batch& bt, const Ws& w, const ReductionIn& red, int mode, const int32_t* n_idx_dev, int waves) {
+    const KeysIn& in = red.keys;
+    a.keys = (const char*)in.keys; a.dk = in.dk;
+    a.nn = w.nn; a.rinv = w.rinv; a.adj = w.adj; a.rho = w.rho; a.rho_lo = w.rho_lo;
+    a.status = w.status; a.ident = w.ident; a.near_cnt = w.near_cnt; a.tie_cnt = w.tie_cnt;
+    a.rep = red.rep; a.cluster_id = red.cluster_id; a.cluster_counts = red.cluster_counts; a.n_idx_dev = n_idx_dev;
+    a.zeros = w.zeros; a.ksplit = w.ksplit;
+    a.mode = mode;
+    const int chunks = in.dk * (in.k_dt == PACT_BF16 ? 2 : 4) / 16;
+    a.key_lanes = chunks <= 16 ? 16 : chunks <= 32 ? 32 : 64;
+    // Four rows per group of lanes, where there are rows enough.  Beside the split it is their number that counts: of few the launch is one wavefront's chain, which four rows make longer (event
+    // brackets, a row at a time / by fours, beside hidden states 896 wide; 128 wide 1200 tokens 7.6 / 8.2 us, 3000 8.5 / 7.7, 6500 10.4 / 9.4; 512 wide 860 4.4 / 4.7 and 1458 5.4 / 5.2 of the kernel itself;
+    // 1024 wide, 3584 beside, 3000 10.3 / 10.7, 4500 13.1 / 12.5).  In batches more so, as rows of four in two samples, which look for their samples one by one, are likely the last ones (1 us: 16
+    // samples, 128 wide 2000 tokens 7.2 / 8.0, 3000 6.8 / 8.3, 4500 7.7 / 8.0, 6500 8.0 / 8.2, 20000 14.3 / 13.6; 256 wide 4500 8.6 / 8.3, 6500 9.1 / 8.8; 512 wide 1200 6.8 / 7.4, 3000
+    // 8.3 / 7.5, 6500 11.7 / 9.8).  Keys alone: where one row each is nearly the wavefronts that the chip holds (512 wide, 6272 tokens 6.6 / 7.5, 7290 6.7 / 6.2, 16384 13.0 / 10.0; 128 wide,
+    // 16384 8.2 / 15.4, 32768 22.3 / 20.8).
+    const int rows_enough = chunks > 64 ? 5000 : chunks > 32 ? (bt.B > 1 ? 3000 : 1200) : bt.B > 1 ? 5000 : 2500;
+    const bool many = chunks <= 128 && (mode == INIT_REDUCE ? bt.total >= rows_enough : in.k_dt == PACT_BF16 && (long)bt.total * a.key_lanes / 64 >= 7000);
+    a.rows_each = !many ? 1 : in.k_dt == PACT_F32 ? 2 : chunks > 32 && chunks <= 64 && bt.total >= 12000 ? 8 : 4;
+    const int per_block = waves * (64 / a.key_lanes) * a.rows_each;
+    return (bt.total + per_block - 1) / per_block;
+}
+
+int launch_front(const Batch& bt, const Ws& w, const KeysIn& keys, pact_report* rep, int32_t* cluster_id, int mode,
+                 const int32_t* n_idx_dev, hipStream_t st) {
+    KeyArgs a = {};
+    const dim3 grid(key_args(a, bt, w, ReductionIn{keys, rep, cluster_id, nullptr}, mode, n_idx_dev, 4));
+    if (keys.k_dt == PACT_BF16) PACT_LAUNCH("front", front_kernel<PACT_BF16>, grid, dim3(256), st, bt, a);
+    else PACT_LAUNCH("front", front_kernel<PACT_F32>, grid, dim3(256), st, bt, a);
     return PACT_OK;
 }
 
-int launch_front(const Batch& bt, const Ws& w, const void* keys, pact_dtype k_dt, int32_t dk,
-                 const ScoreIn* score, pact_report* rep, int32_t* cluster_id,
-                 int32_t* cluster_counts, int mode, const int32_t* n_idx_dev, hipStream_t st) {
-    FrontArgs a = {};
-    a.keys = (const char*)keys; a.dk = dk;
-    a.nn = w.nn; a.rinv = w.rinv; a.adj = w.adj; a.rho = w.rho; a.rho_lo = w.rho_lo; a.hnorm = w.hnorm;
-    a.status = w.status; a.ident = w.ident; a.near_cnt = w.near_cnt; a.tie_cnt = w.tie_cnt;
-    a.rep = rep; a.cluster_id = cluster_id; a.cluster_counts = cluster_counts; a.n_idx_dev = n_idx_dev;
-    a.zeros = w.zeros; a.ksplit = w.ksplit;
-    a.mode = mode;
-    if (keys) {
-        const int chunks = dk * (k_dt == PACT_BF16 ? 2 : 4) / 16;
-        a.key_lanes = chunks <= 16 ? 16 : chunks <= 32 ? 32 : 64;
-        // Four rows per group of lanes, where there are rows enough.  Beside hidden states it is their number that counts: of few the launch is one wavefront's chain, which four rows make longer (event
-        // brackets, a row at a time / by fours, hidden states 896 wide; 128 wide 1200 tokens 7.6 / 8.2 us, 3000 8.5 / 7.7, 6500 10.4 / 9.4; 512 wide 860 4.4 / 4.7 and 1458 5.4 / 5.2 of the kernel itself;
-        // 1024 wide, 3584 beside, 3000 10.3 / 10.7, 4500 13.1 / 12.5).  In batches more so, as rows of four in two samples, which look for their samples one by one, are likely the last ones (1 us: 16
-        // samples, 128 wide 2000 tokens 7.2 / 8.0, 3000 6.8 / 8.3, 4500 7.7 / 8.0, 6500 8.0 / 8.2, 20000 14.3 / 13.6; 256 wide 4500 8.6 / 8.3, 6500 9.1 / 8.8; 512 wide 1200 6.8 / 7.4, 3000
-        // 8.3 / 7.5, 6500 11.7 / 9.8).  Keys alone: where one row each is nearly the wavefronts that the chip holds (512 wide, 6272 tokens 6.6 / 7.5, 7290 6.7 / 6.2, 16384 13.0 / 10.0; 128 wide,
-        // 16384 8.2 / 15.4, 32768 22.3 / 20.8).
-        const int rows_enough = chunks > 64 ? 5000 : chunks > 32 ? (bt.B > 1 ? 3000 : 1200) : bt.B > 1 ? 5000 : 2500;
-        a.four_keys = k_dt == PACT_BF16 && chunks <= 128 && (score ? bt.total >= rows_enough : (long)bt.total * a.key_lanes / 64 >= 7000);
-        const int per_block = 4 * (64 / a.key_lanes) * (a.four_keys ? 4 : 1);
-        a.n_key_blocks = (bt.total + per_block - 1) / per_block;
+static int launch_query_sums(const Batch& bt, const Ws& w, const ScoreIn& in, const NormArgs& norm, const KeyArgs* key, int key_blocks, hipStream_t st) {
+    QueryArgs a = {};
+    a.q = (const char*)in.q; a.qcols = in.n_q * in.d_h;
+    const int cw = 128 / (in.q_dt == PACT_BF16 ? 2 : 4), strips = (a.qcols + cw - 1) / cw;
+    a.q_chunks = query_chunks(bt.n_max, a.qcols);
+    a.qg_part = query_sums(w, a.q_chunks);
+    a.blocks = strips * a.q_chunks * bt.B;
+    a.norm = norm;
+    const int per_block = FRONT_THREADS / 64 * hnorm_tokens(norm.h, norm.h_bf16 ? 2 : 4);
+    if (key) { a.key = *key; a.key_blocks = key_blocks; }
+    const dim3 grid(a.blocks + a.key_blocks + (norm.to - norm.from + per_block - 1) / per_block);
+#define PACT_QUERY(KDT, QDT) PACT_LAUNCH("front", (query_sums_kernel<KDT, QDT>), grid, dim3(FRONT_THREADS), st, bt, a)
+    if (in.k_dt == PACT_BF16) {
+        if (in.q_dt == PACT_BF16) PACT_QUERY(PACT_BF16, PACT_BF16);
+        else PACT_QUERY(PACT_BF16, PACT_F32);
+    } else {
+        if (in.q_dt == PACT_BF16) PACT_QUERY(PACT_F32, PACT_BF16);
+        else PACT_QUERY(PACT_F32, PACT_F32);
     }
-    int h_blocks = 0;
-    pact_dtype q_dt = PACT_BF16;
-    if (score) {
-        const int hb = score->h_dt == PACT_BF16 ? 2 : 4, per_block = 4 * hnorm_tokens(score->h, hb);
-        a.hidden = (const char*)score->hidden; a.h = score->h; a.h_bf16 = score->h_dt == PACT_BF16;
-        a.stream = hidden_streams(bt.total, score->h, hb) ? 1 : 0;
-        h_blocks = (bt.total + per_block - 1) / per_block;
-        if (score->q_per_token) {
-            q_dt = score->q_dt;
-            a.q = (const char*)score->q; a.qcols = score->n_q * score->d_h;
-            a.q_chunks = query_chunks(bt.n_max, a.qcols);
-            a.qg_part = query_sums(w, a.q_chunks);
-            const int cw = 128 / (q_dt == PACT_BF16 ? 2 : 4);
-            a.n_q_blocks = (a.qcols + cw - 1) / cw * a.q_chunks * bt.B;
-        }
-    }
-    // Long streams of hidden states: bf16 keys' blocks evenly among theirs, whose loads keep the memory busy beside the keys' arithmetic (16 x 2688 tokens 67.0 ->
-    // 64.1 us, 4 x 6272 40.9 -> 39.7); otherwise first, since their chains would be the launch's end (7290 tokens 13.2 -> 13.8, 16384 with fp32 keys 44.9 -> 46.5).
-    const uint64_t rest = (uint64_t)a.n_key_blocks + h_blocks;
-    a.key_share = k_dt == PACT_BF16 && h_blocks > 5000 ? (uint32_t)((((uint64_t)a.n_key_blocks << 32) + rest - 1) / rest) : 0u;
-    dim3 grid(a.n_q_blocks + a.n_key_blocks + h_blocks);
-    return (k_dt == PACT_BF16) ? launch_front_q<PACT_BF16>(bt, a, q_dt, grid, st)
-                               : launch_front_q<PACT_F32>(bt, a, q_dt, grid, st);
+#undef PACT_QUERY
+    return PACT_OK;
 }
 
-// Scores of every sample, up to the token blocks' softmax partials.  The first kernel (launch_front with `in`)
-// must have run.
-static int launch_logits(const Batch& bt, const Ws& w, const ScoreIn& in, hipStream_t st) {
+// Scores of every sample, up to the token blocks' softmax partials, and the norms of the hidden states `norm` names.  The query sums must be there.
+// key: the call's clustering keys, if they are in this launch, or nullptr.
+static int launch_logits(const Batch& bt, const Ws& w, const ScoreIn& in, const NormArgs& norm, const KeyArgs* key, int key_blocks, hipStream_t st) {
     LogitsArgs a = {};
     a.keys = (const char*)in.keys_pre; a.n_kv = in.n_kv; a.d_h = in.d_h; a.n_q = in.n_q;
     a.q_given = in.q_per_token ? nullptr : (const char*)in.q; a.q_bf16 = in.q_dt == PACT_BF16;
@@ -1038,20 +1136,37 @@ static int launch_logits(const Batch& bt, const Ws& w, const ScoreIn& in, hipStr
                                        : logits_kv_heads_any(in.n_kv, in.n_q, in.d_h);
     const int cols = way == BY_MFMA ? r * (4 * (in.d_h / 4 + 1) + 1) : a.kv_heads * r * in.d_h;
     a.qg_lds = cols <= LOGITS_COLS_ANY;
-    dim3 grid((bt.n_max + SCORE_TOK - 1) / SCORE_TOK * (in.n_kv / a.kv_heads), bt.B);
+    a.blocks = (bt.n_max + SCORE_TOK - 1) / SCORE_TOK * (in.n_kv / a.kv_heads);
+    a.logits_blocks = a.blocks * bt.B;
+    LogitsMoreArgs m = {};
+    m.norm = norm;
+    if (key) { m.key = *key; m.key_blocks = key_blocks; }
+    const int per_block = 4 * hnorm_tokens(norm.h, norm.h_bf16 ? 2 : 4), h_blocks = (norm.to - norm.from + per_block - 1) / per_block;
+    // Long streams of hidden states: bf16 keys' blocks evenly among theirs, whose loads keep the memory busy beside the keys' arithmetic (16 x 2688 tokens 67.0 ->
+    // 64.1 us, 4 x 6272 40.9 -> 39.7); otherwise first, since their chains would be the launch's end (7290 tokens 13.2 -> 13.8, 16384 with fp32 keys 44.9 -> 46.5).
+    const uint64_t rest = (uint64_t)m.key_blocks + h_blocks;
+    m.key_share = key && in.k_dt == PACT_BF16 && h_blocks > 5000 ? (uint32_t)((((uint64_t)m.key_blocks << 32) + rest - 1) / rest) : 0u;
+    const bool more = rest > 0;
+    dim3 grid(a.logits_blocks + (unsigned)rest);
     const size_t lds = a.qg_lds ? sizeof(double) * cols : 0;
     if (lds > 24 * 1024) {
-        static size_t raised[6] = {};
-        const int di = (in.k_dt == PACT_BF16 ? 1 : 0) + 2 * way;
-        const void* fns[6] = {(const void*)score_logits_kernel<PACT_F32, BY_HEAD>, (const void*)score_logits_kernel<PACT_BF16, BY_HEAD>,
-                              (const void*)score_logits_kernel<PACT_F32, BY_LANES>, (const void*)score_logits_kernel<PACT_BF16, BY_LANES>,
-                              (const void*)score_logits_kernel<PACT_F32, BY_MFMA>, (const void*)score_logits_kernel<PACT_BF16, BY_MFMA>};
+        static size_t raised[12] = {};
+        const int di = (in.k_dt == PACT_BF16 ? 1 : 0) + 2 * way + (more ? 6 : 0);
+#define PACT_LOGITS_OF(KERNEL)                                                                                                \
+    (const void*)KERNEL<PACT_F32, BY_HEAD>, (const void*)KERNEL<PACT_BF16, BY_HEAD>, (const void*)KERNEL<PACT_F32, BY_LANES>, \
+        (const void*)KERNEL<PACT_BF16, BY_LANES>, (const void*)KERNEL<PACT_F32, BY_MFMA>, (const void*)KERNEL<PACT_BF16, BY_MFMA>
+        const void* fns[12] = {PACT_LOGITS_OF(score_logits_kernel), PACT_LOGITS_OF(score_logits_more_kernel)};
+#undef PACT_LOGITS_OF
         if (lds > raised[di]) {
             if (raise_lds_limit(fns[di], lds) != hipSuccess) return PACT_ERR_HIP;
             raised[di] = lds;
         }
     }
-#define PACT_LOGITS(KDT, WAY) PACT_LAUNCH_SHMEM("score_logits", (score_logits_kernel<KDT, WAY>), grid, dim3(256), lds, st, bt, a)
+#define PACT_LOGITS(KDT, WAY)                                                                                                     \
+    do {                                                                                                                          \
+        if (more) PACT_LAUNCH_SHMEM("score_logits", (score_logits_more_kernel<KDT, WAY>), grid, dim3(256), lds, st, bt, a, m);    \
+        else PACT_LAUNCH_SHMEM("score_logits", (score_logits_kernel<KDT, WAY>), grid, dim3(256), lds, st, bt, a);                 \
+    } while (0)
     if (in.k_dt == PACT_BF16) {
         if (way == BY_MFMA) PACT_LOGITS(PACT_BF16, BY_MFMA);
         else if (way == BY_LANES) PACT_LOGITS(PACT_BF16, BY_LANES);
@@ -1069,10 +1184,47 @@ static bool finish_in_prune(const Batch& bt, int n_q) {
     return bt.n_max <= FUSE_TOKENS && (long)bt.n_max * n_q <= FUSE_VALUES;
 }
 
-// The scores themselves; with `prune_follows` small samples leave them to launch_score_prune.
-int launch_score(const Batch& bt, const Ws& w, const ScoreIn& in, float* scores, bool prune_follows, hipStream_t st) {
-    if (const int rc = launch_logits(bt, w, in, st)) return rc;
-    if (prune_follows && finish_in_prune(bt, in.n_q)) return PACT_OK;
+// Calls whose inputs are little to read: all of it in the first launch, whose chains are then the longest part of it anyway.  (us up to the split, so / as below: 2915 tokens, 28 query heads 27.8 /
+// 29.6, 7290 with four, 67 MB, 31.7 / 32.5, with 28, 112 MB, 42.6 / 39.5.)
+static bool inputs_first(const Batch& bt, const ScoreIn& in) {
+    const int64_t kb = in.k_dt == PACT_BF16 ? 2 : 4, qb = in.q_dt == PACT_BF16 ? 2 : 4, hb = in.h_dt == PACT_BF16 ? 2 : 4;
+    return bt.B == 1 && in.q_per_token && bt.total * (in.h * hb + (int64_t)in.n_q * in.d_h * qb + (int64_t)in.n_kv * in.d_h * kb) < (int64_t)90e6;
+}
+// Which launch prepares a reduction's keys: the first, or the split's of long single samples and of batches of small ones, whose scores
+// are finished there too, otherwise that of the logits.  (us up to the split, beside the logits / beside the split: 16384 with fp32 keys about 66 / 62 (70 with the first),
+// 16 ragged images 89 / 96 (92): the split's workgroups have 1024 threads, each turn of them a launch's time; 8 x 6272 98 / 105 (103), 32 of 729 - / 35.6 (36.9).)
+enum { KEYS_FIRST, KEYS_LOGITS, KEYS_SPLIT };
+static int keys_launch(const Batch& bt, const ScoreIn& in) {
+    if (inputs_first(bt, in)) return KEYS_FIRST;
+    return bt.B == 1 ? (bt.n_max > 4096 ? KEYS_SPLIT : KEYS_LOGITS) : finish_in_prune(bt, in.n_q) ? KEYS_SPLIT : KEYS_LOGITS;
+}
+// Hidden states, of the whole batch, whose norms are in the first launch: otherwise of single samples none (7290 tokens, 28 query heads: of both launches the first is as long without them), of batches such that both launches
+// read as much (16 ragged images 74.6 us with none, 74.9, 8 x 6272 87.4 and 85.8).
+static int norms_first(const Batch& bt, const ScoreIn& in, bool keys_there) {
+    if (inputs_first(bt, in)) return bt.total;
+    if (bt.B == 1) return 0;
+    const int kb = in.k_dt == PACT_BF16 ? 2 : 4;
+    const int64_t keys = (int64_t)in.n_kv * in.d_h * kb * (keys_there ? 2 : 1), queries = (int64_t)in.n_q * in.d_h * (in.q_dt == PACT_BF16 ? 2 : 4);
+    const int64_t row = (int64_t)in.h * (in.h_dt == PACT_BF16 ? 2 : 4), share = (row + keys - queries) / 2;      // (bytes of each token's that the first launch has yet to read)
+    return share <= 0 ? 0 : share >= row ? bt.total : (int)(bt.total * share / row) & ~15;
+}
+
+// The scores themselves; with `red` (what a reduction has beside them) small samples leave them to launch_score_prune.
+int launch_score(const Batch& bt, const Ws& w, const ScoreIn& in, float* scores, const ReductionIn* red, hipStream_t st) {
+    KeyArgs key = {};
+    const int where = red ? keys_launch(bt, in) : KEYS_SPLIT;
+    const int key_blocks = where == KEYS_SPLIT ? 0 : key_args(key, bt, w, *red, INIT_REDUCE, nullptr, where == KEYS_FIRST ? FRONT_THREADS / 64 : 4);
+    const int hb = in.h_dt == PACT_BF16 ? 2 : 4;
+    NormArgs norm{(const char*)in.hidden, w.hnorm, in.h, in.h_dt == PACT_BF16, hidden_streams(bt.total, in.h, hb) ? 1 : 0, 0, bt.total};
+    if (in.q_per_token) {
+        const int first = norms_first(bt, in, where == KEYS_LOGITS);
+        norm.to = first;
+        if (const int rc = launch_query_sums(bt, w, in, norm, where == KEYS_FIRST ? &key : nullptr, key_blocks, st)) return rc;
+        norm.from = first;
+        norm.to = bt.total;
+    }
+    if (const int rc = launch_logits(bt, w, in, norm, where == KEYS_LOGITS ? &key : nullptr, key_blocks, st)) return rc;
+    if (red && finish_in_prune(bt, in.n_q)) return PACT_OK;
     if (in.n_q > 8)
         PACT_LAUNCH("score_final", score_final_kernel<128>, dim3((bt.n_max + 127) / 128, bt.B), dim3(1024), st, bt,
                     in.n_q, w.logits, w.hnorm, w.sm_part, scores);
@@ -1082,25 +1234,30 @@ int launch_score(const Batch& bt, const Ws& w, const ScoreIn& in, float* scores,
     return PACT_OK;
 }
 
-// Splits the scores of every sample (Eq. 3 / 4).  unfinished: what launch_score(prune_follows) left, or nullptr.
-// adj: the samples' neighbour bitmaps as launch_front(INIT_REDUCE) left them, or nullptr when no
-// clustering follows.
-int launch_score_prune(const Batch& bt, const Ws* unfinished, int n_q, float* scores, uint64_t* adj, int32_t* kept_idx,
-                       int32_t* pruned_idx, pact_report* rep, hipStream_t st) {
-#define PACT_PRUNE(FINISH, KREG, fin)                                                                                          \
-    PACT_LAUNCH("score_prune", (score_prune_kernel<FINISH, KREG>), dim3(bt.B), dim3(1024), st, bt, fin, scores, adj, kept_idx, \
-                pruned_idx, rep)
-    if (unfinished && finish_in_prune(bt, n_q)) {
-        const FinishArgs fin{unfinished->logits, unfinished->hnorm, unfinished->sm_part, n_q};
-        PACT_PRUNE(true, 1, fin);
-        return PACT_OK;
-    }
-    const FinishArgs none{};
+// Splits the scores of every sample (Eq. 3 / 4).  red: what a reduction has beside them, or nullptr (the split alone): small samples' scores are
+// then finished here, and its keys prepared for their clustering, if they are not yet.
+int launch_score_prune(const Batch& bt, const Ws* w, const ScoreIn* in, float* scores, const ReductionIn* red, int32_t* kept_idx, int32_t* pruned_idx,
+                       pact_report* rep, hipStream_t st) {
+    KeyArgs key = {};
+    uint64_t* adj = red ? w->adj : nullptr;
+    const bool f32 = red && red->keys.k_dt == PACT_F32, keys_here = red && keys_launch(bt, *in) == KEYS_SPLIT;
+    const dim3 grid(bt.B + (keys_here ? key_args(key, bt, *w, *red, INIT_REDUCE, nullptr, 16) : 0));
+    PruneArgs a{{}, scores, adj, kept_idx, pruned_idx, rep};
+#define PACT_PRUNE(FINISH, KREG)                                                                                                                \
+    do {                                                                                                                                        \
+        if (!keys_here) PACT_LAUNCH("score_prune", (score_prune_kernel<FINISH, KREG>), grid, dim3(1024), st, bt, a);                            \
+        else if (f32) PACT_LAUNCH("score_prune", (score_prune_keys_kernel<FINISH, KREG, PACT_F32>), grid, dim3(1024), st, bt, a, key);          \
+        else PACT_LAUNCH("score_prune", (score_prune_keys_kernel<FINISH, KREG, PACT_BF16>), grid, dim3(1024), st, bt, a, key);                  \
+    } while (0)
     static_assert(PACT_MAX_TOKENS <= 1024 * 32, "a sample's keys in the registers of one workgroup");
-    if (bt.n_max <= 1024 * 4) PACT_PRUNE(false, 4, none);
-    else if (bt.n_max <= 1024 * 8) PACT_PRUNE(false, 8, none);
-    else if (bt.n_max <= 1024 * 16) PACT_PRUNE(false, 16, none);
-    else PACT_PRUNE(false, 32, none);
+    if (red && finish_in_prune(bt, in->n_q)) {
+        a.fin = FinishArgs{w->logits, w->hnorm, w->sm_part, in->n_q};
+        PACT_PRUNE(true, 1);
+    }
+    else if (bt.n_max <= 1024 * 4) PACT_LAUNCH("score_prune", (score_prune_kernel<false, 4>), grid, dim3(1024), st, bt, a);       // (no keys here: see keys_launch)
+    else if (bt.n_max <= 1024 * 8) PACT_PRUNE(false, 8);
+    else if (bt.n_max <= 1024 * 16) PACT_PRUNE(false, 16);
+    else PACT_PRUNE(false, 32);
 #undef PACT_PRUNE
     return PACT_OK;
 }

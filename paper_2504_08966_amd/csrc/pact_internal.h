@@ -190,14 +190,16 @@ struct ScoreIn {
     const void* q; pact_dtype q_dt; int32_t q_per_token; int32_t n_q;   // q_per_token: 1 = [total, ..], 0 = [B, ..]
 };
 
-// First kernel of every call: key norms, cleared bitmap rows, per-token initial state and (score !=
-// nullptr) hidden-state norms and the first pass of Eq. 1.
-int launch_front(const Batch& bt, const Ws& w, const void* keys, pact_dtype k_dt, int32_t dk,
-                 const ScoreIn* score, pact_report* rep, int32_t* cluster_id,
-                 int32_t* cluster_counts, int mode, const int32_t* n_idx_dev, hipStream_t st);
-int launch_score(const Batch& bt, const Ws& w, const ScoreIn& in, float* scores, bool prune_follows, hipStream_t st);
-int launch_score_prune(const Batch& bt, const Ws* unfinished, int n_q, float* scores, uint64_t* adj, int32_t* kept_idx,
-                       int32_t* pruned_idx, pact_report* rep, hipStream_t st);
+struct KeysIn { const void* keys; pact_dtype k_dt; int32_t dk; };      // clustering keys
+struct ReductionIn { KeysIn keys; pact_report* rep; int32_t *cluster_id, *cluster_counts; };
+
+// First kernel of a clustering or recovery called alone: key norms, cleared bitmap rows, per-token initial state.  (In a reduction launch_score or
+// launch_score_prune does it.)
+int launch_front(const Batch& bt, const Ws& w, const KeysIn& keys, pact_report* rep, int32_t* cluster_id, int mode,
+                 const int32_t* n_idx_dev, hipStream_t st);
+int launch_score(const Batch& bt, const Ws& w, const ScoreIn& in, float* scores, const ReductionIn* red, hipStream_t st);
+int launch_score_prune(const Batch& bt, const Ws* w, const ScoreIn* in, float* scores, const ReductionIn* red, int32_t* kept_idx, int32_t* pruned_idx,
+                       pact_report* rep, hipStream_t st);
 // want_stat: also record the largest key distance; *stat_words = words per sample the kernel
 // wrote to w.stat (0 if not wanted), to be handed to launch_centres.
 int launch_gram_density(const Batch& bt, const Ws& w, const void* keys, pact_dtype k_dt, int32_t dk,
@@ -237,7 +239,7 @@ inline long kept_estimate(const Batch& bt) {
     return n;
 }
 
-enum { INIT_REDUCE = 0, INIT_DBDPC_ALL = 1, INIT_DBDPC_SUBSET = 2, INIT_REINC = 3, INIT_SCORE = 4 };
+enum { INIT_REDUCE = 0, INIT_DBDPC_ALL = 1, INIT_DBDPC_SUBSET = 2, INIT_REINC = 3 };
 
 // Worst-case error of a cosine from the matrix passes.  bf16 keys: rounding of the fp32 accumulation of
 // dk products, plus slack for the scaling multiplies.  fp32 keys: bytes left out of the elements (at most

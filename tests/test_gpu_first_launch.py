@@ -1,5 +1,6 @@
-"""The first launch of a call: norms of four bf16 key rows per group of lanes (calls of enough rows, samples that start inside such a group), and
-the query sums of long samples, which come in more chunks.  Against a call of one sample, whose rows are taken one at a time, and the oracle."""
+"""What depends on the inputs alone: norms of several key rows per group of lanes (calls of enough rows, samples that start inside such a group), in each of the launches
+that prepare keys; the query sums of long samples, which come in more chunks; hidden states' norms in two launches.  Against a call of one sample, whose rows are
+taken one at a time, and the oracle."""
 import numpy as np
 import pytest
 import torch
@@ -13,13 +14,14 @@ pytestmark = pytest.mark.gpu
 
 
 # 16, 32 and 64 lanes a row, one and two chunks a lane; the batches have tokens enough for four rows at a time, a sample of its own never has
-@pytest.mark.parametrize("dk,n_b", [(8, 165), (128, 165), (136, 165), (256, 165), (264, 100), (512, 100), (1024, 165)])
+@pytest.mark.parametrize("dk,n_b,dtype", [(8, 165, "bf16"), (128, 165, "bf16"), (136, 165, "bf16"), (256, 165, "bf16"), (264, 100, "bf16"), (512, 100, "bf16"), (512, 400, "bf16"),
+                                          (1024, 165, "bf16"), (4, 165, "f32"), (64, 165, "f32"), (68, 165, "f32"), (128, 165, "f32"), (132, 100, "f32"), (260, 165, "f32"), (512, 165, "f32")])
 @pytest.mark.parametrize("d_n", [2.0, 0.1])
-def test_rows_by_fours_as_one_at_a_time(dk, n_b, d_n):
+def test_several_rows_as_one_at_a_time(dk, n_b, dtype, d_n):
     lens = [n_b + k % 5 for k in range(31)] + [1, 2, 3]
-    assert sum(lens) >= (3000 if 256 < dk <= 512 else 5000) and max(lens) < 1200
-    ss = [_random_sample(9100 + k, n, 1, 1, dk, 64, 0.3, "bf16") for k, n in enumerate(lens)]
-    hid, ks, qs = (gu.dev(np.concatenate([x(s).reshape(s.n, -1) for s in ss]), "bf16") for x in (lambda s: s.hidden, lambda s: s.keys, lambda s: s.queries))
+    assert sum(lens) >= (3000 if n_b == 100 else 12000 if n_b == 400 else 5000) and max(lens) < 1200
+    ss = [_random_sample(9100 + k, n, 1, 1, dk, 64, 0.3, dtype) for k, n in enumerate(lens)]
+    hid, ks, qs = (gu.dev(np.concatenate([x(s).reshape(s.n, -1) for s in ss]), dtype) for x in (lambda s: s.hidden, lambda s: s.keys, lambda s: s.queries))
     ks[5] = 0                                              # a zero vector
     off = np.concatenate([[0], np.cumsum(lens)]).astype(int)
     prm = [P.PactParams(0.3, 0.06, d_n, 1.5) for _ in lens]
@@ -63,3 +65,35 @@ def test_query_sums_of_a_long_sample_beside_short_ones(n_kv, n_q, d_h, dtype):
         torch.cuda.synchronize()
         assert torch.equal(got, one[:s.n]), k
         np.testing.assert_allclose(got.cpu().numpy(), O.euti_scores(s.hidden, s.keys, s.queries), rtol=2e-7)
+
+
+# keys prepared beside the query sums (single samples up to 4096 tokens), beside the split (longer ones, samples of up to 1024) and beside the logits (batches, a query
+# given as its mean); norms of the hidden states in the first launch, the second, part in either, with rows of one to four at a time
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("h,n_q,d_h", [(64, 1, 64), (1032, 1, 72), (3584, 2, 128), (256, 7, 64)])
+@pytest.mark.parametrize("mean", [False, True])
+def test_inputs_in_any_launch(h, n_q, d_h, dtype, mean):
+    lens = [1100, 4099, 17, 4097]
+    rng = np.random.default_rng(77)
+    hid, ks = (gu.dev(rng.normal(size=(sum(lens), c)), dtype) for c in (h, d_h))
+    ks[1000:1040] = ks[0]
+    qs = gu.dev(rng.normal(size=(len(lens) if mean else sum(lens), n_q * d_h)), dtype)
+    off = np.concatenate([[0], np.cumsum(lens)]).astype(int)
+    prm = [P.PactParams(0.5, 0.1, 2.0, 1.5) for _ in lens]
+    o = P.pact_reduce_varlen(hid, ks, ks, qs, 1, d_h, n_q, off.tolist(), prm)
+    torch.cuda.synchronize()
+    reps = P.read_report(o["rep"])
+    norm = hid.double().cpu().norm(dim=1)
+    for k in range(len(lens)):
+        a, b = off[k], off[k + 1]
+        q = qs[k:k + 1] if mean else qs[a:b]
+        g = P.pact_reduce(hid[a:b], ks[a:b], ks[a:b], q, 1, d_h, n_q, prm[k])
+        torch.cuda.synchronize()
+        rep = P.read_report(g["rep"])
+        assert all(reps[k][f] == rep[f] for f in ("n_kept", "n_centers", "n_reincorporated", "zero_norm_seen", "nonfinite_seen", "score_near_ties")), k
+        for name, m in (("scores", b - a), ("cluster_id", b - a), ("center_idx", rep["n_centers"]), ("merged", rep["n_centers"]), ("cluster_counts", rep["n_centers"])):
+            assert torch.equal(o[name][a:a + m], g[name][:m]), (k, name)
+        # the scores in fp64, on the CPU
+        Q = q.double().cpu().mean(0).reshape(n_q, d_h)
+        want = norm[a:b] * torch.softmax(ks[a:b].double().cpu() @ Q.T, dim=0).mean(1)
+        np.testing.assert_allclose(g["scores"][: b - a].cpu().numpy(), want.numpy(), rtol=2e-7)
