@@ -2387,6 +2387,7 @@ __global__ __launch_bounds__(256, PART >= NEAREST_BOTH_HERE ? 3 : 4) void neares
     lds_i32* ctok = (lds_i32*)s_ctok[wave];
     lds_f32* ccos = (lds_f32*)s_ccos[wave];
     constexpr bool HERE = PART == NEAREST_BOTH_HERE || PART == NEAREST_RECOVER_HERE;
+    if constexpr (HERE) touch_args<sizeof(NearArgs)>(blockIdx.y);
     __shared__ uint64_t s_cw[HERE ? SMALL_TOKENS / 4 : 1];
     __shared__ float s_cb[HERE ? SMALL_TOKENS / 4 : 1];
     __shared__ f32x4_t s_rs[HERE ? 64 : 1];

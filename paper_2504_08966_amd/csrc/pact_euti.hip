@@ -683,6 +683,7 @@ __device__ __forceinline__ void logits_block(const Batch& bt, const LogitsArgs& 
 
 template <int KDT, int WAY>
 __global__ __launch_bounds__(256) void score_logits_kernel(Batch bt, LogitsArgs a) {
+    touch_args<sizeof(LogitsArgs)>(0);
     logits_block<KDT, WAY>(bt, a);
 }
 // With keys or hidden states behind them.
@@ -766,6 +767,7 @@ __global__ __launch_bounds__(1024) void score_final_kernel(Batch bt, int n_q, co
     __shared__ double s_f[NBLK * PACT_MAX_QHEADS];
     __shared__ double s_acc[FINAL_PARTS - 1][FINAL_TOK];
     const int b = blockIdx.y;
+    touch_args<40>(b);
     const Seg sg = bt.s[b];
     if ((int)blockIdx.x * FINAL_TOK >= sg.n) return;
     const int tid = threadIdx.x, tok = tid & (FINAL_TOK - 1), part = tid / FINAL_TOK;
@@ -1052,11 +1054,13 @@ __device__ __forceinline__ void prune_block(const Batch& bt, const FinishArgs& f
 struct PruneArgs { FinishArgs fin; float* scores; uint64_t* adj; int32_t *kept_idx, *pruned_idx; pact_report* rep; };
 template <bool FINISH, int KREG>
 __global__ __launch_bounds__(1024) void score_prune_kernel(Batch bt, PruneArgs a) {
+    touch_args<sizeof(PruneArgs)>(blockIdx.x);
     prune_block<FINISH, KREG>(bt, a.fin, a.scores, a.adj, a.kept_idx, a.pruned_idx, a.rep);
 }
 // With the clustering keys of the call (KDT: their type) behind the samples' workgroups.  (The split alone is half a microsecond longer with their code.)
 template <bool FINISH, int KREG, int KDT>
 __global__ __launch_bounds__(1024) void score_prune_keys_kernel(Batch bt, PruneArgs a, KeyArgs key) {
+    touch_args<sizeof(PruneArgs) + sizeof(KeyArgs)>(min((int)blockIdx.x, PACT_MAX_BATCH - 1));
     if ((int)blockIdx.x < bt.B) prune_block<FINISH, KREG>(bt, a.fin, a.scores, a.adj, a.kept_idx, a.pruned_idx, a.rep);
     else key_block<KDT, 16>(bt, key, (int)blockIdx.x - bt.B, __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), threadIdx.x & 63);
 }

@@ -357,6 +357,7 @@ __global__ __launch_bounds__(256, U > 4 ? 6 : 8) void merge_kernel(Batch bt, Mer
     constexpr int EPL = Elem<HDT>::EPL, WAVES = 4, TEAMS = WAVES / TW, TT = 64 * TW;
     __shared__ uint16_t s_list[TEAMS == 1 ? 1 : WAVES][MERGE_LIST + 64];
     __shared__ int s_sum[WAVES];
+    touch_args<sizeof(MergeArgs)>(0);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), tl = tid & (TT - 1);
     int blk, nblk;
