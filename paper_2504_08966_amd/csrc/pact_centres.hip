@@ -178,10 +178,12 @@ __device__ __forceinline__ void nearest_candidate(lds_i32* cand, lds_i32* ctok, 
 // rows), so the pairs of a tile of the density pass, which share rows, stay on one XCD.  7290 rows of 7 KB, bracket 51.6 us, by XCD 41, with the screen 36.6,
 // on the dot instruction 32.6, 1024 workgroups (what the chip holds) instead of 768 31; 2000 rows 27 -> 21; 7290 fp32 rows 69.5 -> 44.5.  Short
 // rows: 16 ragged images 10.2 -> 10.9 by XCD, 11.6 with 1024.
+// PARTS: parts of the pairs' list (near_parts).  A list in one part has a build of its own: with the search for a pair's part and a vector load of the counter in it, 16 ragged images took 10.3 us
+// instead of 8.7, 8 videos 7.1 instead of 6.1.
 // grid (settle_blocks(), B), block 256.
 static int settle_blocks(int n_max, bool wide) { return n_max >= 6144 ? (wide ? 1024 : 768) : n_max < 512 ? 64 : n_max / 64 * 8; }   // (the benchmark image: a pair per wavefront)
 
-template <int DT, int CH>
+template <int DT, int CH, int PARTS>
 __global__ __launch_bounds__(256) void settle_kernel(Batch bt, const char* __restrict__ keys, int dk,
                                                      const int32_t* __restrict__ idx,
                                                      const double* __restrict__ nn,
@@ -199,16 +201,25 @@ __global__ __launch_bounds__(256) void settle_kernel(Batch bt, const char* __res
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
     const int gw = blockIdx.x * 4 + wave;
-    // the parts' counters, a lane each, and where in the list as a whole each part begins
-    const int parts = near_parts(bt.n_max, bt.B), room = NEAR_CAP / parts;
-    const uint2 taken = lane < parts ? *(const uint2*)(near_cnt + (b * NEAR_PARTS + lane) * NEAR_COUNTER) : make_uint2(0u, 0u);
-    const int in_part = (int)min(taken.x, (uint32_t)room), ends = parts > 1 ? wave_scan_incl_i32(in_part) : in_part;
-    const int cnt_all = __builtin_amdgcn_readlane(ends, parts > 1 ? 63 : 0);
+    // the parts' counters, a lane each, and where in the list as a whole each part begins; the only one of a list in one part by a scalar load
+    constexpr int room = NEAR_CAP / PARTS;
+    const int32_t* counters = near_cnt + b * NEAR_PARTS * NEAR_COUNTER;
+    uint2 taken = make_uint2(0u, 0u);
+    int in_part, ends, cnt_all;
+    if constexpr (PARTS == 1) {
+        taken = make_uint2((uint32_t)counters[0], (uint32_t)counters[1]);
+        in_part = ends = cnt_all = (int)min(taken.x, (uint32_t)room);
+    } else {
+        if (lane < PARTS) taken = *(const uint2*)(counters + lane * NEAR_COUNTER);
+        in_part = (int)min(taken.x, (uint32_t)room);
+        ends = wave_scan_incl_i32(in_part);
+        cnt_all = __builtin_amdgcn_readlane(ends, 63);
+    }
     auto place = [&](int e) __attribute__((always_inline)) {         // of entry e of the list as a whole
-        if (parts == 1) return e;
+        if constexpr (PARTS == 1) return e;
         int part = 0;
 #pragma unroll
-        for (int k = 0; k < NEAR_PARTS - 1; ++k) part += e >= __builtin_amdgcn_readlane(ends, k) ? 1 : 0;
+        for (int k = 0; k < PARTS - 1; ++k) part += e >= __builtin_amdgcn_readlane(ends, k) ? 1 : 0;
         return part * room + e - __shfl(ends - in_part, part, 64);
     };
     // wide rows: an eighth of the list per XCD (workgroups are dealt to them round-robin; the grid is a multiple of 8): neighbouring pairs are of one tile of the
@@ -228,10 +239,12 @@ __global__ __launch_bounds__(256) void settle_kernel(Batch bt, const char* __res
         }
 #pragma unroll
         for (int sft = 32; sft >= 1; sft >>= 1) fb = max(fb, (uint32_t)__shfl_xor((int)fb, sft, 64));
-        const bool overflow = __ballot(lane < parts && taken.x <= (uint32_t)room) == 0;
+        const bool overflow = __ballot(lane < PARTS && taken.x <= (uint32_t)room) == 0;
         int ordered = (int)taken.y;
+        if constexpr (PARTS > 1) {
 #pragma unroll
-        for (int sft = 32; sft >= 1; sft >>= 1) ordered += __shfl_xor(ordered, sft, 64);
+            for (int sft = 32; sft >= 1; sft >>= 1) ordered += __shfl_xor(ordered, sft, 64);
+        }
         if (lane == 0) report_settled(rep + b, overflow, ordered, fb, sg.d_n);
     }
     constexpr int EPL = Elem<DT>::EPL;
@@ -2492,9 +2505,10 @@ int launch_centres(const Batch& bt, const Ws& w, const void* keys, pact_dtype k_
     if (!small || !narrow) {
         const bool wide = (size_t)dk * (k_dt == PACT_BF16 ? 2 : 4) > 2048;
         dim3 gset(settle_blocks(bt.n_max, wide), bt.B);
+        const bool one = near_parts(bt.n_max, bt.B) == 1;
 #define PACT_SETTLE(DT, CH)                                                                                           \
-        PACT_LAUNCH("settle", (settle_kernel<DT, CH>), gset, dim3(256), st, bt, k, dk, idx, w.nn, w.near_list, w.near_cnt, \
-                    w.stat, stat_words, w.rho, w.rho_lo, w.adj, rep)
+        PACT_LAUNCH("settle", (one ? settle_kernel<DT, CH, 1> : settle_kernel<DT, CH, NEAR_PARTS>), gset, dim3(256), st, bt, k, dk, idx, \
+                    w.nn, w.near_list, w.near_cnt, w.stat, stat_words, w.rho, w.rho_lo, w.adj, rep)
         if (k_dt == PACT_BF16) { if (wide) PACT_SETTLE(PACT_BF16, 8); else PACT_SETTLE(PACT_BF16, 2); }
         else { if (wide) PACT_SETTLE(PACT_F32, 8); else PACT_SETTLE(PACT_F32, 2); }
 #undef PACT_SETTLE
