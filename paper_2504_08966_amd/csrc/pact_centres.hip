@@ -1540,6 +1540,7 @@ __device__ __forceinline__ int select_sample(const Batch& bt, const CentresArgs&
 // grid (B + workers), block 1024, dynamic LDS: small_lds, at least RECHECK_LDS.
 template <int DT>
 __global__ __launch_bounds__(1024) void select_small_kernel(Batch bt, CentresArgs a, SmallArgs sa) {
+    touch_args<sizeof(CentresArgs) + sizeof(SmallArgs)>(min((int)blockIdx.x, PACT_MAX_BATCH - 1));
     extern __shared__ double s_dyn[];
     __shared__ SmallShared sh;
     auto meet = [&](int* counter, int add) __attribute__((always_inline)) { return count_in(counter, add, sh.got); };
