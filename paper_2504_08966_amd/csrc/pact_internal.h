@@ -44,6 +44,7 @@ constexpr int NEAR_CAP = 1 << 16;     // near-threshold pairs kept for fp64 re-e
 // batches, whose workgroups are fewer and at it at other times (finding a pair's part took 16 ragged images' settling 3 us, their density pass gained 2 without).
 constexpr int NEAR_PARTS = 16, NEAR_COUNTER = 32;      // (words of a counter: places taken, ordered pairs they stand for, unused)
 __host__ __device__ inline int near_parts(int n_max, int batch) { return n_max > 1024 && batch <= 3 ? NEAR_PARTS : 1; }
+constexpr uint32_t NEAR_MARK = 0x80000000u;     // in the places taken of all parts of a list: some pair had no place in any
 constexpr uint32_t NEAR_MIRROR = 0x80000000u;   // flag in a listed pair's row: the pair (col, row) is meant as well
 constexpr float EXACT_SUMS_D_N = 0.21f;      // from this d_n on the density sums are exact in any order (see add_density)
 constexpr uint32_t ST_UNKNOWN = 0, ST_CENTER = 1, ST_NOT = 2;
