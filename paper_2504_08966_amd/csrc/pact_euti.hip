@@ -1146,10 +1146,13 @@ static int launch_logits(const Batch& bt, const Ws& w, const ScoreIn& in, const 
     m.norm = norm;
     if (key) { m.key = *key; m.key_blocks = key_blocks; }
     const int per_block = 4 * hnorm_tokens(norm.h, norm.h_bf16 ? 2 : 4), h_blocks = (norm.to - norm.from + per_block - 1) / per_block;
-    // Long streams of hidden states: bf16 keys' blocks evenly among theirs, whose loads keep the memory busy beside the keys' arithmetic (16 x 2688 tokens 67.0 ->
-    // 64.1 us, 4 x 6272 40.9 -> 39.7); otherwise first, since their chains would be the launch's end (7290 tokens 13.2 -> 13.8, 16384 with fp32 keys 44.9 -> 46.5).
+    // Key blocks ahead of those of the hidden states, but evenly among them in large batches whose clustering keys are the tensor that the logits read, as bf16: its rows, read
+    // a second time, are then spread over the launch.  (Whole call, first / among, us.  One tensor: 16 x 2688 tokens 301.3 / 299.1, 8 x 6272 385.7 / 382.1, 16 ragged images 357.0 / 355.9 and with
+    // 28 query heads 439.6 / 437.9, 16 x 4095 514.1 / 510.8, 12 x 2688 257.4 / 256.3, 8 x 3645 269.6 / 269.0; 4 x 6272 238.5 / 239.1, 2 x 2915 106.1 / 106.7, 5 x 1458 109.9 / 110.8.  Two tensors: 16 x 2688 299.2 / 300.6 and with 28 query
+    // heads 385.0 / 388.7, 8 x 6272 390.6 / 392.7, ragged 360.7 / 362.4, 3 x 7290 256.2 / 258.3.)
     const uint64_t rest = (uint64_t)m.key_blocks + h_blocks;
-    m.key_share = key && in.k_dt == PACT_BF16 && h_blocks > 5000 ? (uint32_t)((((uint64_t)m.key_blocks << 32) + rest - 1) / rest) : 0u;
+    const bool among = key && in.k_dt == PACT_BF16 && key->keys == (const char*)in.keys_pre && bt.total > 26000;
+    m.key_share = among ? (uint32_t)((((uint64_t)m.key_blocks << 32) + rest - 1) / rest) : 0u;       // (no hidden states here: 2^32, which is 0)
     const bool more = rest > 0;
     dim3 grid(a.logits_blocks + (unsigned)rest);
     const size_t lds = a.qg_lds ? sizeof(double) * cols : 0;

@@ -97,3 +97,31 @@ def test_inputs_in_any_launch(h, n_q, d_h, dtype, mean):
         Q = q.double().cpu().mean(0).reshape(n_q, d_h)
         want = norm[a:b] * torch.softmax(ks[a:b].double().cpu() @ Q.T, dim=0).mean(1)
         np.testing.assert_allclose(g["scores"][: b - a].cpu().numpy(), want.numpy(), rtol=2e-7)
+
+
+# large batches, keys prepared beside the logits: their blocks evenly among those of the hidden states (one tensor as both keys) or ahead of them (two); one to four norms a wavefront, key blocks
+# the more and the fewer; a query given as its mean leaves all norms to that launch
+@pytest.mark.parametrize("h,n_q,d_h", [(64, 1, 64), (1032, 1, 8), (1032, 14, 64), (2560, 1, 128)])
+@pytest.mark.parametrize("two", [False, True])
+@pytest.mark.parametrize("mean", [False, True])
+def test_keys_among_hidden_states(h, n_q, d_h, two, mean):
+    lens = [2500, 1, 4096, 1025, 3001, 2999] * 2 + [5900, 63]
+    assert sum(lens) > 32768
+    g = torch.Generator("cuda").manual_seed(11)
+    rand = lambda *s: torch.randn(*s, device="cuda", generator=g).bfloat16()
+    hid, ks, qs = rand(sum(lens), h), rand(sum(lens), d_h), rand(len(lens) if mean else sum(lens), n_q * d_h)
+    ks[::7] = ks[3]
+    pre = ks.clone() if two else ks
+    off = np.concatenate([[0], np.cumsum(lens)]).astype(int)
+    prm = [P.PactParams(0.5, 0.05, 2.0, 1.5) for _ in lens]
+    o = P.pact_reduce_varlen(hid, pre, ks, qs, 1, d_h, n_q, off.tolist(), prm)
+    torch.cuda.synchronize()
+    reps = P.read_report(o["rep"])
+    for k in range(len(lens)):
+        a, b = off[k], off[k + 1]
+        one = P.pact_reduce(hid[a:b], pre[a:b], ks[a:b], qs[k:k + 1] if mean else qs[a:b], 1, d_h, n_q, prm[k])
+        torch.cuda.synchronize()
+        rep = P.read_report(one["rep"])
+        assert all(reps[k][f] == rep[f] for f in ("n_kept", "n_centers", "n_reincorporated", "zero_norm_seen", "nonfinite_seen", "score_near_ties")), k
+        for name, m in (("scores", b - a), ("cluster_id", b - a), ("center_idx", rep["n_centers"]), ("merged", rep["n_centers"]), ("cluster_counts", rep["n_centers"])):
+            assert torch.equal(o[name][a:a + m], one[name][:m]), (k, name)
