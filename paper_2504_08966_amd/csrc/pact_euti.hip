@@ -1191,19 +1191,25 @@ static bool finish_in_prune(const Batch& bt, int n_q) {
     return bt.n_max <= FUSE_TOKENS && (long)bt.n_max * n_q <= FUSE_VALUES;
 }
 
-// Calls whose inputs are little to read: all of it in the first launch, whose chains are then the longest part of it anyway.  (us up to the split, so / as below: 2915 tokens, 28 query heads 27.8 /
-// 29.6, 7290 with four, 67 MB, 31.7 / 32.5, with 28, 112 MB, 42.6 / 39.5.)
+constexpr int KEYS_SHORT = 4096;         // tokens of a single sample whose keys are never beside the split
+// Single samples of more than 4096 tokens with narrow queries and little to read otherwise have all of it in the first launch.  (Whole call, all first / as below, us.  Four query heads, hidden states 3584 wide: 4374
+// tokens 94.5 / 93.7, 5832 110.9 / 110.7, 6561 116.0 / 117.6, 7290 123.0 / 124.9, 8748, 81 MB, 150.2 / 151.5; 9701, 89 MB, 164.9 / 165.0; 10501, 97 MB, 171.3 / 169.4, 14001 232.7 / 229.4.  fp32 keys 4200
+// 110.3 / 111.9, 5001 127.4 / 129.4, 7290, 82 MB, 174.7 / 175.1, 9001, 101 MB, 220.2 / 220.1.  896 wide: 4200 82.1 / 83.5, 7290 96.6 / 97.2.  Wide queries, 28 heads: 2915 89.6 / 89.5, 5001 112.4 / 111.4, 7290, 112 MB, 138.1 /
+// 134.8.  Up to 4096 tokens, where the keys would be beside the logits and not the split: 729 50.9 / 50.2 and 75.3 / 74.5 with fp32 keys, 2187 83.3 / 82.7, 3645 90.1 / 89.5.)
 static bool inputs_first(const Batch& bt, const ScoreIn& in) {
     const int64_t kb = in.k_dt == PACT_BF16 ? 2 : 4, qb = in.q_dt == PACT_BF16 ? 2 : 4, hb = in.h_dt == PACT_BF16 ? 2 : 4;
-    return bt.B == 1 && in.q_per_token && bt.total * (in.h * hb + (int64_t)in.n_q * in.d_h * qb + (int64_t)in.n_kv * in.d_h * kb) < (int64_t)90e6;
+    return bt.B == 1 && in.q_per_token && bt.n_max > KEYS_SHORT && in.n_q * in.d_h <= QG_NARROW &&
+           bt.total * (in.h * hb + (int64_t)in.n_q * in.d_h * qb + (int64_t)in.n_kv * in.d_h * kb) < (int64_t)90e6;
 }
 // Which launch prepares a reduction's keys: the first, or the split's of long single samples and of batches of small ones, whose scores
-// are finished there too, otherwise that of the logits.  (us up to the split, beside the logits / beside the split: 16384 with fp32 keys about 66 / 62 (70 with the first),
-// 16 ragged images 89 / 96 (92): the split's workgroups have 1024 threads, each turn of them a launch's time; 8 x 6272 98 / 105 (103), 32 of 729 - / 35.6 (36.9).)
+// are finished there too, otherwise that of the logits.  (Batches, us up to the split, beside the logits / beside the split: 16 ragged images 89 / 96 (92 with the first launch): the split's workgroups have 1024
+// threads, each turn of them a launch's time; 8 x 6272 98 / 105 (103), 32 of 729 - / 35.6 (36.9).  Single samples, whole call, beside the logits / beside the split: a query given as its mean 1500 tokens 72.1 / 74.4, 2915 82.5 / 83.8, 4095 91.4 /
+// 92.6, 5001 97.4 / 98.0, 7290 117.8 / 115.6, 16384 280.9 / 275.5, with fp32 keys 7290 174.7 / 169.6 and 16384 477.0 / 479.1; 28 query heads 4500 110.5 / 109.4, 7290 137.4 / 134.9, 16384 311.8 / 308.0; four
+// 10001 168.3 / 166.4, 32768 690.0 / 682.0.)
 enum { KEYS_FIRST, KEYS_LOGITS, KEYS_SPLIT };
 static int keys_launch(const Batch& bt, const ScoreIn& in) {
     if (inputs_first(bt, in)) return KEYS_FIRST;
-    return bt.B == 1 ? (bt.n_max > 4096 ? KEYS_SPLIT : KEYS_LOGITS) : finish_in_prune(bt, in.n_q) ? KEYS_SPLIT : KEYS_LOGITS;
+    return bt.B == 1 ? (bt.n_max > KEYS_SHORT ? KEYS_SPLIT : KEYS_LOGITS) : finish_in_prune(bt, in.n_q) ? KEYS_SPLIT : KEYS_LOGITS;
 }
 // Hidden states, of the whole batch, whose norms are in the first launch: otherwise of single samples none (7290 tokens, 28 query heads: of both launches the first is as long without them), of batches such that both launches
 // read as much (16 ragged images 74.6 us with none, 74.9, 8 x 6272 87.4 and 85.8).

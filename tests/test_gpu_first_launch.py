@@ -67,10 +67,10 @@ def test_query_sums_of_a_long_sample_beside_short_ones(n_kv, n_q, d_h, dtype):
         np.testing.assert_allclose(got.cpu().numpy(), O.euti_scores(s.hidden, s.keys, s.queries), rtol=2e-7)
 
 
-# keys prepared beside the query sums (single samples up to 4096 tokens), beside the split (longer ones, samples of up to 1024) and beside the logits (batches, a query
-# given as its mean); norms of the hidden states in the first launch, the second, part in either, with rows of one to four at a time
+# keys prepared beside the query sums (single samples of more than 4096 tokens with narrow queries), beside the split (with wide ones, or a query given as its mean) and beside the logits (shorter
+# ones, batches); norms of the hidden states in the first launch, the second, part in either, with rows of one to four at a time
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
-@pytest.mark.parametrize("h,n_q,d_h", [(64, 1, 64), (1032, 1, 72), (3584, 2, 128), (256, 7, 64)])
+@pytest.mark.parametrize("h,n_q,d_h", [(64, 1, 64), (1032, 1, 72), (3584, 2, 128), (256, 7, 64), (64, 9, 128)])
 @pytest.mark.parametrize("mean", [False, True])
 def test_inputs_in_any_launch(h, n_q, d_h, dtype, mean):
     lens = [1100, 4099, 17, 4097]
