@@ -1267,7 +1267,11 @@ int launch_score_prune(const Batch& bt, const Ws* w, const ScoreIn* in, float* s
         a.fin = FinishArgs{w->logits, w->hnorm, w->sm_part, in->n_q};
         PACT_PRUNE(true, 1);
     }
-    else if (bt.n_max <= 1024 * 4) PACT_LAUNCH("score_prune", (score_prune_kernel<false, 4>), grid, dim3(1024), st, bt, a);       // (no keys here: see keys_launch)
+    else if (bt.n_max <= 1024 * 4) {
+        static_assert(KEYS_SHORT == 1024 * 4, "keys_launch gives the split of such samples no keys: there is no build for it");
+        if (keys_here) return PACT_ERR_HIP;
+        PACT_LAUNCH("score_prune", (score_prune_kernel<false, 4>), grid, dim3(1024), st, bt, a);
+    }
     else if (bt.n_max <= 1024 * 8) PACT_PRUNE(false, 8);
     else if (bt.n_max <= 1024 * 16) PACT_PRUNE(false, 16);
     else PACT_PRUNE(false, 32);
