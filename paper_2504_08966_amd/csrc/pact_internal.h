@@ -276,15 +276,16 @@ __device__ __forceinline__ float bf16_bits_to_f32(uint32_t hi16) { return __uint
 // The cache lines of a kernel's arguments (a Batch, then `bytes` of others; up to the last of them, no kernel's segment need go on behind it), and that of sample b,
 // are asked for together, ahead of everything else.  A scalar load comes where the compiler first needs it, behind the branches that decide on it, and each new line was a
 // trip of its own to memory the first time: four to eight in turn ahead of a kernel's first vector load.
-template <int BYTES> __device__ __forceinline__ void touch_args(int b) {
+template <int BYTES> __device__ __forceinline__ uint32_t args_asked_for(int b) {
     const __attribute__((address_space(4))) char* args = (const __attribute__((address_space(4))) char*)__builtin_amdgcn_kernarg_segment_ptr();
-    asm volatile("" : "+s"(args));
+    asm("" : "+s"(args));
     auto word = [&](int at) __attribute__((always_inline)) { return *(const __attribute__((address_space(4))) uint32_t*)(args + at); };
     uint32_t t = word(0) ^ word(16 + (int)sizeof(Seg) * b);
 #pragma unroll
     for (int at = 0; at < BYTES + 64; at += 64) t ^= word((int)sizeof(Batch) + (at < BYTES ? at : BYTES - 4));
-    asm volatile("" :: "s"(t));
+    return t;
 }
+template <int BYTES> __device__ __forceinline__ void touch_args(int b) { asm volatile("" :: "s"(args_asked_for<BYTES>(b))); }
 // Counts read back from a device-side report are clamped to the sample size, so that a report
 // the caller never initialised cannot send a kernel out of bounds.
 __device__ __forceinline__ int clamp_count(int v, int n) { return v < 0 ? 0 : (v > n ? n : v); }

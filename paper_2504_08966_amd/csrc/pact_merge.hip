@@ -293,11 +293,11 @@ struct MergeArgs {
     int32_t first[PACT_MAX_BATCH + 1];                    // first workgroup of each sample
 };
 // The sample that this workgroup works for; its number within the sample's, -1 for the one that adds up the sizes (if any does).
-__device__ __forceinline__ int merge_sample(const Batch& bt, const MergeArgs& a, int& blk, int& nblk) {
+__device__ __forceinline__ int merge_sample(const Batch& bt, const MergeArgs& a, int block, int& blk, int& nblk) {
     int b = 0;
     for (int step = PACT_MAX_BATCH / 2; step; step >>= 1)            // (scalar loads: a vector load of an argument is a trip to memory)
-        if (b + step < bt.B && a.first[b + step] <= (int)blockIdx.x) b += step;
-    blk = (int)blockIdx.x - a.first[b] - (a.slots ? 1 : 0);
+        if (b + step < bt.B && a.first[b + step] <= block) b += step;
+    blk = block - a.first[b] - (a.slots ? 1 : 0);
     nblk = a.first[b + 1] - a.first[b] - (a.slots ? 1 : 0);
     return b;
 }
@@ -357,11 +357,12 @@ __global__ __launch_bounds__(256, U > 4 ? 6 : 8) void merge_kernel(Batch bt, Mer
     constexpr int EPL = Elem<HDT>::EPL, WAVES = 4, TEAMS = WAVES / TW, TT = 64 * TW;
     __shared__ uint16_t s_list[TEAMS == 1 ? 1 : WAVES][MERGE_LIST + 64];
     __shared__ int s_sum[WAVES];
-    touch_args<sizeof(MergeArgs)>(0);
+    int block = blockIdx.x;
+    asm("" : "+s"(block) : "s"(args_asked_for<sizeof(MergeArgs)>(0)));       // (not volatile: behind such a statement counts come by vector loads)
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), tl = tid & (TT - 1);
     int blk, nblk;
-    const int b = merge_sample(bt, a, blk, nblk);
+    const int b = merge_sample(bt, a, block, blk, nblk);
     const Seg sg = bt.s[b];
     if (blk < 0) {
         merge_totals<256>(a, b, sg, s_sum);
