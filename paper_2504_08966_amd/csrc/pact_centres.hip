@@ -2401,16 +2401,17 @@ __global__ __launch_bounds__(256, PART >= NEAREST_BOTH_HERE ? 3 : 4) void neares
     lds_i32* ctok = (lds_i32*)s_ctok[wave];
     lds_f32* ccos = (lds_f32*)s_ccos[wave];
     constexpr bool HERE = PART == NEAREST_BOTH_HERE || PART == NEAREST_RECOVER_HERE;
-    if constexpr (HERE) touch_args<sizeof(NearArgs)>(blockIdx.y);
+    int block = blockIdx.x;
+    if constexpr (HERE) asm("" : "+s"(block) : "s"(args_asked_for<sizeof(NearArgs)>(blockIdx.y)));       // (not volatile: see there)
     __shared__ uint64_t s_cw[HERE ? SMALL_TOKENS / 4 : 1];
     __shared__ float s_cb[HERE ? SMALL_TOKENS / 4 : 1];
     __shared__ f32x4_t s_rs[HERE ? 64 : 1];
-    if constexpr (PART == NEAREST_ASSIGN) assign_body<DT, TPW>(bt, a, blockIdx.x, cand, ctok, ccos, (lds_i32*)s_list);
+    if constexpr (PART == NEAREST_ASSIGN) assign_body<DT, TPW>(bt, a, block, cand, ctok, ccos, (lds_i32*)s_list);
     else if constexpr (PART == NEAREST_RECOVER || PART == NEAREST_RECOVER_HERE)
-        recover_body<DT, HERE, false>(bt, a, blockIdx.x, gridDim.x, (lds_i32*)s_list, (lds_f32*)s_cb, (lds_u64*)s_cw, (lds_f32*)s_rs);
-    else if ((int)blockIdx.x >= (int)gridDim.x - a.assign_blocks)
-        assign_body<DT, TPW>(bt, a, blockIdx.x - (gridDim.x - a.assign_blocks), cand, ctok, ccos, (lds_i32*)s_list);
-    else recover_body<DT, HERE, true>(bt, a, blockIdx.x, gridDim.x - a.assign_blocks, (lds_i32*)s_list, (lds_f32*)s_cb, (lds_u64*)s_cw, (lds_f32*)s_rs);
+        recover_body<DT, HERE, false>(bt, a, block, gridDim.x, (lds_i32*)s_list, (lds_f32*)s_cb, (lds_u64*)s_cw, (lds_f32*)s_rs);
+    else if (block >= (int)gridDim.x - a.assign_blocks)
+        assign_body<DT, TPW>(bt, a, block - (gridDim.x - a.assign_blocks), cand, ctok, ccos, (lds_i32*)s_list);
+    else recover_body<DT, HERE, true>(bt, a, block, gridDim.x - a.assign_blocks, (lds_i32*)s_list, (lds_f32*)s_cb, (lds_u64*)s_cw, (lds_f32*)s_rs);
 }
 
 template <int PART, int TPW>

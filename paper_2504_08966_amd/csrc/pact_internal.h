@@ -275,7 +275,9 @@ __device__ __forceinline__ float bf16_bits_to_f32(uint32_t hi16) { return __uint
 
 // The cache lines of a kernel's arguments (a Batch, then `bytes` of others; up to the last of them, no kernel's segment need go on behind it), and that of sample b,
 // are asked for together, ahead of everything else.  A scalar load comes where the compiler first needs it, behind the branches that decide on it, and each new line was a
-// trip of its own to memory the first time: four to eight in turn ahead of a kernel's first vector load.
+// trip of its own to memory the first time: four to eight in turn ahead of a kernel's first vector load.  What is returned has to be waited for: in kernels whose counts and list heads, written
+// by kernels before, come by scalar loads, by a statement that is not volatile, as an input beside the workgroup's number (behind a volatile one the compiler takes memory as written and uses vector
+// loads: merge of 64 x 1458 tokens 896 wide 294.6 -> 298.6 us a call, searches of 64 x 196 97.4 -> 98.7); elsewhere by touch_args.
 template <int BYTES> __device__ __forceinline__ uint32_t args_asked_for(int b) {
     const __attribute__((address_space(4))) char* args = (const __attribute__((address_space(4))) char*)__builtin_amdgcn_kernarg_segment_ptr();
     asm("" : "+s"(args));

@@ -358,7 +358,7 @@ __global__ __launch_bounds__(256, U > 4 ? 6 : 8) void merge_kernel(Batch bt, Mer
     __shared__ uint16_t s_list[TEAMS == 1 ? 1 : WAVES][MERGE_LIST + 64];
     __shared__ int s_sum[WAVES];
     int block = blockIdx.x;
-    asm("" : "+s"(block) : "s"(args_asked_for<sizeof(MergeArgs)>(0)));       // (not volatile: behind such a statement counts come by vector loads)
+    asm("" : "+s"(block) : "s"(args_asked_for<sizeof(MergeArgs)>(0)));       // (not volatile: see there)
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), tl = tid & (TT - 1);
     int blk, nblk;
