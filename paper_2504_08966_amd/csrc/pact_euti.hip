@@ -1070,8 +1070,39 @@ static hipError_t raise_lds_limit(const void* fn, size_t bytes) {
     return hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
 }
 
-// What the workgroups of a call's clustering keys need, `waves` wavefronts each; their number.
-static int key_args(KeyArgs& a, const Batch& bt, const Ws& w, const ReductionIn& red, int mode, const int32_t* n_idx_dev, int waves) {
+// The launch that prepares the clustering keys: the query sums', the logits' or the split's of a reduction, or one of their own.
+enum { KEYS_FIRST, KEYS_LOGITS, KEYS_SPLIT, KEYS_ALONE };
+constexpr int CUS = 256;
+
+// How they are dealt there: lanes per row, rows per group of lanes, workgroups (of 1024 threads beside the split, otherwise of 256).
+struct KeyPlan { int lanes, rows, blocks; };
+static KeyPlan key_plan(const Batch& bt, pact_dtype k_dt, int32_t dk, int where) {
+    static_assert(FRONT_THREADS == 256, "four wavefronts");
+    const bool bf16 = k_dt == PACT_BF16, among_splits = where == KEYS_SPLIT && bt.B > 1;
+    const int chunks = dk * (bf16 ? 2 : 4) / 16, lanes = chunks <= 16 ? 16 : chunks <= 32 ? 32 : 64;
+    auto blocks = [&](int rows) { const int each = (where == KEYS_SPLIT ? 16 : 4) * (64 / lanes) * rows; return (bt.total + each - 1) / each; };
+    // Several rows per group of lanes, where there are rows enough: of few the launch is one wavefront's chain, which more rows make longer.  Whole calls, a row at a time / four (fp32 keys: two), us:
+    // * Single samples: hardly a difference (128 wide 2500 tokens 71.2 / 70.7, 6500 87.3 / 87.2; 512 wide 860 69.5 / 69.4, 2000 81.7 / 81.7; fp32 keys 128 wide 2500 76.1 / 75.8, 512 wide 5001 127.3 / 126.7).
+    // * Batches, beside the logits (rows of four in two samples, which look for their samples one by one, are likely the last ones): 512 wide 2 of 1500 86.5 / 86.2, of 3250 113.3 / 110.7, 128 wide
+    //   2 of 1500 72.9 / 73.3, of 2250 76.2 / 76.3, 1024 wide 4 of 1125 124.1 / 122.5, of 1625 143.5 / 140.4; fp32 keys 512 wide 4 of 1458 123.3 / 121.2, 8 of 2688 286.7 / 283.2.
+    // * Batches, beside the splits, whose workgroups are one to a CU (that many, a row at a time): 512 wide 16 of 190 (204) 94.8 / 96.1, of 400 (422) 105.8 / 106.4, of 560 (578) 117.7 / 116.2; 1024 wide 8 of
+    //   750 (383) 133.1 / 135.9, 16 of 560 (578) 148.2 / 146.9; 128 wide 32 of 440 (251) 90.5 / 91.9, 16 of 1000 (266) 97.3 / 98.1, 32 of 720 (391) 110.5 / 110.7 and with 14 query heads 121.5 / 120.1, of 1000 (532) 132.5 / 130.2; fp32 keys
+    //   128 wide 16 of 400 (219) 78.9 / 79.7, of 560 (297) 89.3 / 86.8, 512 wide 4 of 750 (192) 95.1 / 97.1, 8 of 750 (383) 118.6 / 116.3.
+    // * Keys alone (the kernel itself): where one row each is nearly the wavefronts that the chip holds (512 wide, 6272 tokens 6.6 / 7.5, 7290 6.7 / 6.2, 16384 13.0 / 10.0; 128 wide, 16384 8.2 / 15.4,
+    //   32768 22.3 / 20.8).
+    const int rows_enough = chunks > 64 ? 5000 : chunks > 32 ? (bt.B > 1 ? 3000 : 1200) : bt.B > 1 ? 5000 : 2500;
+    const bool many = chunks > 128           ? false
+                    : where == KEYS_ALONE    ? bf16 && (long)bt.total * lanes / 64 >= 7000
+                    : among_splits           ? blocks(1) + bt.B > (!bf16 ? CUS : lanes == 16 ? CUS * 3 / 2 : CUS * 7 / 4)
+                                             : bt.total >= rows_enough;
+    // (bf16, eight rows / four: 2 x 6272 tokens 512 wide 189.5 / 191.4, 9 x 1458 149.5 / 151.2, 32 x 720 200.5 / 201.9, 8 x 6272 436.2 / 435.0; alone beside the split 12001 198.7 / 198.1, 14001 228.9 / 230.2, 16384
+    // 276.3 / 279.0; beside the splits of a batch 16 x 875 162.3 / 158.1)
+    const int rows = !many ? 1 : !bf16 ? 2 : chunks > 32 && chunks <= 64 && bt.total >= 12000 && !among_splits ? 8 : 4;
+    return {lanes, rows, blocks(rows)};
+}
+
+// What their workgroups need; the number of those.
+static int key_args(KeyArgs& a, const Batch& bt, const Ws& w, const ReductionIn& red, int mode, const int32_t* n_idx_dev, int where) {
     const KeysIn& in = red.keys;
     a.keys = (const char*)in.keys; a.dk = in.dk;
     a.nn = w.nn; a.rinv = w.rinv; a.adj = w.adj; a.rho = w.rho; a.rho_lo = w.rho_lo;
@@ -1079,25 +1110,15 @@ static int key_args(KeyArgs& a, const Batch& bt, const Ws& w, const ReductionIn&
     a.rep = red.rep; a.cluster_id = red.cluster_id; a.cluster_counts = red.cluster_counts; a.n_idx_dev = n_idx_dev;
     a.zeros = w.zeros; a.ksplit = w.ksplit;
     a.mode = mode;
-    const int chunks = in.dk * (in.k_dt == PACT_BF16 ? 2 : 4) / 16;
-    a.key_lanes = chunks <= 16 ? 16 : chunks <= 32 ? 32 : 64;
-    // Four rows per group of lanes, where there are rows enough.  Beside the split it is their number that counts: of few the launch is one wavefront's chain, which four rows make longer (event
-    // brackets, a row at a time / by fours, beside hidden states 896 wide; 128 wide 1200 tokens 7.6 / 8.2 us, 3000 8.5 / 7.7, 6500 10.4 / 9.4; 512 wide 860 4.4 / 4.7 and 1458 5.4 / 5.2 of the kernel itself;
-    // 1024 wide, 3584 beside, 3000 10.3 / 10.7, 4500 13.1 / 12.5).  In batches more so, as rows of four in two samples, which look for their samples one by one, are likely the last ones (1 us: 16
-    // samples, 128 wide 2000 tokens 7.2 / 8.0, 3000 6.8 / 8.3, 4500 7.7 / 8.0, 6500 8.0 / 8.2, 20000 14.3 / 13.6; 256 wide 4500 8.6 / 8.3, 6500 9.1 / 8.8; 512 wide 1200 6.8 / 7.4, 3000
-    // 8.3 / 7.5, 6500 11.7 / 9.8).  Keys alone: where one row each is nearly the wavefronts that the chip holds (512 wide, 6272 tokens 6.6 / 7.5, 7290 6.7 / 6.2, 16384 13.0 / 10.0; 128 wide,
-    // 16384 8.2 / 15.4, 32768 22.3 / 20.8).
-    const int rows_enough = chunks > 64 ? 5000 : chunks > 32 ? (bt.B > 1 ? 3000 : 1200) : bt.B > 1 ? 5000 : 2500;
-    const bool many = chunks <= 128 && (mode == INIT_REDUCE ? bt.total >= rows_enough : in.k_dt == PACT_BF16 && (long)bt.total * a.key_lanes / 64 >= 7000);
-    a.rows_each = !many ? 1 : in.k_dt == PACT_F32 ? 2 : chunks > 32 && chunks <= 64 && bt.total >= 12000 ? 8 : 4;
-    const int per_block = waves * (64 / a.key_lanes) * a.rows_each;
-    return (bt.total + per_block - 1) / per_block;
+    const KeyPlan plan = key_plan(bt, in.k_dt, in.dk, where);
+    a.key_lanes = plan.lanes; a.rows_each = plan.rows;
+    return plan.blocks;
 }
 
 int launch_front(const Batch& bt, const Ws& w, const KeysIn& keys, pact_report* rep, int32_t* cluster_id, int mode,
                  const int32_t* n_idx_dev, hipStream_t st) {
     KeyArgs a = {};
-    const dim3 grid(key_args(a, bt, w, ReductionIn{keys, rep, cluster_id, nullptr}, mode, n_idx_dev, 4));
+    const dim3 grid(key_args(a, bt, w, ReductionIn{keys, rep, cluster_id, nullptr}, mode, n_idx_dev, KEYS_ALONE));
     if (keys.k_dt == PACT_BF16) PACT_LAUNCH("front", front_kernel<PACT_BF16>, grid, dim3(256), st, bt, a);
     else PACT_LAUNCH("front", front_kernel<PACT_F32>, grid, dim3(256), st, bt, a);
     return PACT_OK;
@@ -1201,15 +1222,16 @@ static bool inputs_first(const Batch& bt, const ScoreIn& in) {
     return bt.B == 1 && in.q_per_token && bt.n_max > KEYS_SHORT && in.n_q * in.d_h <= QG_NARROW &&
            bt.total * (in.h * hb + (int64_t)in.n_q * in.d_h * qb + (int64_t)in.n_kv * in.d_h * kb) < (int64_t)90e6;
 }
-// Which launch prepares a reduction's keys: the first, or the split's of long single samples and of batches of small ones, whose scores
-// are finished there too, otherwise that of the logits.  (Batches, us up to the split, beside the logits / beside the split: 16 ragged images 89 / 96 (92 with the first launch): the split's workgroups have 1024
-// threads, each turn of them a launch's time; 8 x 6272 98 / 105 (103), 32 of 729 - / 35.6 (36.9).  Single samples, whole call, beside the logits / beside the split: a query given as its mean 1500 tokens 72.1 / 74.4, 2915 82.5 / 83.8, 4095 91.4 /
-// 92.6, 5001 97.4 / 98.0, 7290 117.8 / 115.6, 16384 280.9 / 275.5, with fp32 keys 7290 174.7 / 169.6 and 16384 477.0 / 479.1; 28 query heads 4500 110.5 / 109.4, 7290 137.4 / 134.9, 16384 311.8 / 308.0; four
-// 10001 168.3 / 166.4, 32768 690.0 / 682.0.)
-enum { KEYS_FIRST, KEYS_LOGITS, KEYS_SPLIT };
+// Which launch prepares a reduction's keys: the first; the split's of long single samples, and of batches whose scores are finished there too as long as its workgroups, one to a CU, are one turn; otherwise that of the
+// logits.  (Whole calls, beside the logits / beside the split, us.  Single samples: a query given as its mean 1500 tokens 72.1 / 74.4, 2915 82.5 / 83.8, 4095 91.4 / 92.6, 5001 97.4 / 98.0, 7290 117.8 / 115.6, 16384 280.9 / 275.5,
+// with fp32 keys 7290 174.7 / 169.6 and 16384 477.0 / 479.1; 28 query heads 4500 110.5 / 109.4, 7290 137.4 / 134.9, 16384 311.8 / 308.0; four 10001 168.3 / 166.4, 32768 690.0 / 682.0.  Batches, with the workgroups
+// that the split then has: 512 wide 16 of 875 (235) 161.1 / 157.7, 16 of 1000 (266) 163.9 / 167.2, 32 of 720 (392) 201.9 / 203.5, 64 of 220 (283) 163.4 / 167.5, of 470 (533) 237.9 / 244.2; 256 wide 32 of 720 (212)
+// 174.7 / 173.4, 64 of 470 (299) 211.7 / 214.2; 128 wide, 14 query heads, 32 of 720 (122) 123.7 / 122.2, 64 of 720 (244) 174.7 / 172.2, two heads 64 of 940 (299) 188.9 / 191.7; 1024 wide 16 of 875 (235) 186.5 / 184.4, 32 of
+// 720 (392) 238.7 / 242.0; fp32 keys 512 wide 16 of 400 (219) 121.9 / 120.0, of 560 (298) 138.1 / 142.2, 128 wide 32 of 440 (251) 100.1 / 98.2, 64 of 220 (283) 101.8 / 104.1.)
 static int keys_launch(const Batch& bt, const ScoreIn& in) {
     if (inputs_first(bt, in)) return KEYS_FIRST;
-    return bt.B == 1 ? (bt.n_max > KEYS_SHORT ? KEYS_SPLIT : KEYS_LOGITS) : finish_in_prune(bt, in.n_q) ? KEYS_SPLIT : KEYS_LOGITS;
+    if (bt.B == 1) return bt.n_max > KEYS_SHORT ? KEYS_SPLIT : KEYS_LOGITS;
+    return finish_in_prune(bt, in.n_q) && key_plan(bt, in.k_dt, in.n_kv * in.d_h, KEYS_SPLIT).blocks + bt.B <= CUS ? KEYS_SPLIT : KEYS_LOGITS;
 }
 // Hidden states, of the whole batch, whose norms are in the first launch: otherwise of single samples none (7290 tokens, 28 query heads: of both launches the first is as long without them), of batches such that both launches
 // read as much (16 ragged images 74.6 us with none, 74.9, 8 x 6272 87.4 and 85.8).
@@ -1226,7 +1248,7 @@ static int norms_first(const Batch& bt, const ScoreIn& in, bool keys_there) {
 int launch_score(const Batch& bt, const Ws& w, const ScoreIn& in, float* scores, const ReductionIn* red, hipStream_t st) {
     KeyArgs key = {};
     const int where = red ? keys_launch(bt, in) : KEYS_SPLIT;
-    const int key_blocks = where == KEYS_SPLIT ? 0 : key_args(key, bt, w, *red, INIT_REDUCE, nullptr, where == KEYS_FIRST ? FRONT_THREADS / 64 : 4);
+    const int key_blocks = where == KEYS_SPLIT ? 0 : key_args(key, bt, w, *red, INIT_REDUCE, nullptr, where);
     const int hb = in.h_dt == PACT_BF16 ? 2 : 4;
     NormArgs norm{(const char*)in.hidden, w.hnorm, in.h, in.h_dt == PACT_BF16, hidden_streams(bt.total, in.h, hb) ? 1 : 0, 0, bt.total};
     if (in.q_per_token) {
@@ -1254,7 +1276,7 @@ int launch_score_prune(const Batch& bt, const Ws* w, const ScoreIn* in, float* s
     KeyArgs key = {};
     uint64_t* adj = red ? w->adj : nullptr;
     const bool f32 = red && red->keys.k_dt == PACT_F32, keys_here = red && keys_launch(bt, *in) == KEYS_SPLIT;
-    const dim3 grid(bt.B + (keys_here ? key_args(key, bt, *w, *red, INIT_REDUCE, nullptr, 16) : 0));
+    const dim3 grid(bt.B + (keys_here ? key_args(key, bt, *w, *red, INIT_REDUCE, nullptr, KEYS_SPLIT) : 0));
     PruneArgs a{{}, scores, adj, kept_idx, pruned_idx, rep};
 #define PACT_PRUNE(FINISH, KREG)                                                                                                                \
     do {                                                                                                                                        \
