@@ -40,9 +40,11 @@ constexpr int PRED_CAP = 64;          // 16-bit slots per kept token: slot 0 = c
 constexpr int GRAM_MAX_WORKGROUPS = 256; // workgroups of 8 wavefronts per sample in a Gram pass (one per CU)
 constexpr int NEAR_CAP = 1 << 16;     // near-threshold pairs kept for fp64 re-evaluation, per sample
 // The list of a sample is in parts of equal size, each with a counter on a cache line of its own.  (One counter answers a hundred atomics a microsecond: an image's density
-// pass, 700 wavefronts with undecided pairs, waited 4 us for it at its end.)  Samples of up to 1024 tokens, whose workgroups are few, have one, and those of
-// batches, whose workgroups are fewer and at it at other times (finding a pair's part took 16 ragged images' settling 3 us, their density pass gained 2 without).
-constexpr int NEAR_PARTS = 16, NEAR_COUNTER = 32;      // (words of a counter: places taken, ordered pairs they stand for, unused)
+// pass, 700 wavefronts with undecided pairs, waited 4 us for it at its end.  Whole calls with one part / 4 / 8 / 16, us: images 1500 tokens 76.2 / 75.5 / 75.4 / 75.7, 2500 82.4 / 80.6 / 79.7 / 80.4, 4500 97.5 / 94.7 / 94.3 /
+// 95.0, 7290 119.8 / 117.6 / 116.9 / 117.1; with few such pairs 128-wide images 3093 73.1 / 73.4 / 73.3 / 73.4, videos 3093 78.8 / 78.9 / 79.5 / 79.1, 6272 103.0 / 103.6 / 102.8 / 103.1.)  Samples of up to 1024 tokens, whose workgroups
+// are few, have one, and those of batches, whose workgroups are fewer and at it at other times.  (One / sixteen: 2 x 2916 106.5 / 107.0, 2 x 7290 197.4 / 196.9, 3 x 4374 168.7 / 169.5, 7290 beside 729 134.7 / 132.0; 4 x 2916 148.4 / 149.1,
+// 5 x 2916 159.9 / 161.0, 16 ragged images 356.5 / 358.9: finding a pair's part is 1.6 us of their settling.)
+constexpr int NEAR_PARTS = 8, NEAR_COUNTER = 32;      // (words of a counter: places taken, ordered pairs they stand for, unused)
 __host__ __device__ inline int near_parts(int n_max, int batch) { return n_max > 1024 && batch <= 3 ? NEAR_PARTS : 1; }
 constexpr uint32_t NEAR_MARK = 0x80000000u;     // in the places taken of all parts of a list: some pair had no place in any
 constexpr uint32_t NEAR_MIRROR = 0x80000000u;   // flag in a listed pair's row: the pair (col, row) is meant as well

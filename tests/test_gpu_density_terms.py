@@ -37,9 +37,9 @@ def test_densities(n, dk, angles, d_n, dtype):
     assert np.array_equal(out["center_idx"][: rep["n_centers"]].cpu().numpy(), ref["centers"])
 
 
-@pytest.mark.parametrize("n,half", [(1025, 70), (1300, 100), (2600, 128)])
+@pytest.mark.parametrize("n,half", [(1025, 70), (1025, 95), (1300, 100), (2600, 128)])
 def test_undecided_pairs_of_few_workgroups(n, half):
-    # two blocks of identical keys at a distance of d_c to within fp32 rounding: of one tile come more pairs than a part of the list holds (4096)
+    # two blocks of identical keys at a distance of d_c to within fp32 rounding: of one tile come more pairs than a part of the list holds (8192)
     k = np.zeros((n, 1, 16), dtype=np.float32)
     k[:half, 0, 0] = 1.0
     k[half:2 * half, 0, 0] = 0.9
