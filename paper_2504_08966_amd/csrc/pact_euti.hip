@@ -19,8 +19,8 @@ namespace pact {
 //                   cluster id, counts); 16 to 64 lanes per token by the row's width;
 //   |h_i|_2 in fp64: one wavefront per token or, for rows of at most 4 KB, several tokens per wavefront (eight loads in flight per lane).
 // Keys and hidden states are walked by token of the whole batch (no blocks for the tokens that shorter samples do not have).
-// The first launch of a reduction is the query sums, the second the logits, both short of work: the hidden states' norms, most of a
-// call's bytes, are dealt to both, and the keys are in the second or beside the percentile split (launch_score()).  A clustering alone has its keys in a launch of their own.
+// The first launch of a reduction is the query sums (none if the query is given as its mean), the second the logits, both short of work: the hidden states' norms, most of a
+// call's bytes, are in either or dealt to both (norms_first()), and the keys in one of these or beside the percentile split (keys_launch()).  A clustering alone has its keys in a launch of their own.
 constexpr int FRONT_THREADS = 256;
 struct KeyArgs {
     const char* keys; int32_t dk;
@@ -34,7 +34,8 @@ struct KeyArgs {
 // Row chunks of a sample's query sum: of 128 rows, 8 at most, of wide queries, which have strips enough, 4 up to 4096 tokens (every workgroup of the logits
 // kernel reads its columns of all chunks, 32 KB); 16 at most of long ones with narrow queries, whose few
 // blocks would each be a chain of trips of 256 rows (16384 tokens, 512 fp32 columns: 8 chunks of 2048 rows were 128 blocks of 8 trips, 22 us for 34 MB).  Each sample its own number: with the longest
-// one's for all, 32768 tokens beside 31 of 729, 14 query heads, both launches were a third longer.
+// one's for all, 32768 tokens beside 31 of 729, 14 query heads, both launches were a third longer.  And the number of a call of its own, so that its sums are the same there.  (28 query heads, whole calls with four chunks / eight, us: 4500 tokens
+// 110.4 / 109.9, 7290 136.1 / 134.6, 10001 181.8 / 179.4, 32768 727 / 722, 4 x 5001 248.8 / 246.4, 3 x 7290 285.1 / 285.1; 2 x 4500 145.0 / 146.7, 8 x 6272 488.8 / 492.9, 7290 with fp32 keys 196.6 / 197.7.)
 __host__ __device__ inline int query_chunks(int n, int qcols) {
     const bool wide = qcols > QG_NARROW;
     if (!wide && n > 1024 * QG_CHUNKS) return n > 1024 * QG_LONG_CHUNKS ? QG_LONG_CHUNKS : (n + 1023) / 1024;
@@ -1234,7 +1235,8 @@ static int keys_launch(const Batch& bt, const ScoreIn& in) {
     return finish_in_prune(bt, in.n_q) && key_plan(bt, in.k_dt, in.n_kv * in.d_h, KEYS_SPLIT).blocks + bt.B <= CUS ? KEYS_SPLIT : KEYS_LOGITS;
 }
 // Hidden states, of the whole batch, whose norms are in the first launch: otherwise of single samples none (7290 tokens, 28 query heads: of both launches the first is as long without them), of batches such that both launches
-// read as much (16 ragged images 74.6 us with none, 74.9, 8 x 6272 87.4 and 85.8).
+// read as much (16 ragged images 74.6 us with none, 74.9, 8 x 6272 87.4 and 85.8).  So also beside BY_HEAD, whose LDS leaves a CU room for two to four of their workgroups: four heads of 72 with 28 query heads, whole calls, all
+// in the first launch / as here, 16384 tokens 484.7 / 474.6, 8 x 1458 368.8 / 362.4, 16 x 2688 608.0 / 577.5, 8 x 6272 898.2 / 870.3, 64 query heads over two of 96 7290 654.0 / 647.0.
 static int norms_first(const Batch& bt, const ScoreIn& in, bool keys_there) {
     if (inputs_first(bt, in)) return bt.total;
     if (bt.B == 1) return 0;
