@@ -1229,8 +1229,11 @@ static bool inputs_first(const Batch& bt, const ScoreIn& in) {
 // that the split then has: 512 wide 16 of 875 (235) 161.1 / 157.7, 16 of 1000 (266) 163.9 / 167.2, 32 of 720 (392) 201.9 / 203.5, 64 of 220 (283) 163.4 / 167.5, of 470 (533) 237.9 / 244.2; 256 wide 32 of 720 (212)
 // 174.7 / 173.4, 64 of 470 (299) 211.7 / 214.2; 128 wide, 14 query heads, 32 of 720 (122) 123.7 / 122.2, 64 of 720 (244) 174.7 / 172.2, two heads 64 of 940 (299) 188.9 / 191.7; 1024 wide 16 of 875 (235) 186.5 / 184.4, 32 of
 // 720 (392) 238.7 / 242.0; fp32 keys 512 wide 16 of 400 (219) 121.9 / 120.0, of 560 (298) 138.1 / 142.2, 128 wide 32 of 440 (251) 100.1 / 98.2, 64 of 220 (283) 101.8 / 104.1.)
+// (Where the logits go head by head their launch is a call's longest, and the keys belong there whatever the size, up to the first rule: beside the logits / beside the split, 8 heads of 72, one query head each, 32 of 406 tokens
+// 203.3 / 221.9, 32 of 812 281.0 / 287.4; seven each, 6000 568.4 / 595.2; 8 of 80, two each, 32 of 406 268.3 / 286.0, 6000 244.2 / 256.8; 4 of 72, one each, 32 of 812 221.8 / 227.5.)
 static int keys_launch(const Batch& bt, const ScoreIn& in) {
     if (inputs_first(bt, in)) return KEYS_FIRST;
+    if (logits_way(in.n_kv, in.n_q, in.d_h, in.k_dt == PACT_BF16 ? 2 : 4) == BY_HEAD) return KEYS_LOGITS;
     if (bt.B == 1) return bt.n_max > KEYS_SHORT ? KEYS_SPLIT : KEYS_LOGITS;
     return finish_in_prune(bt, in.n_q) && key_plan(bt, in.k_dt, in.n_kv * in.d_h, KEYS_SPLIT).blocks + bt.B <= CUS ? KEYS_SPLIT : KEYS_LOGITS;
 }

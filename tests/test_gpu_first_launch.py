@@ -13,7 +13,7 @@ from tests.test_gpu_parity import _random_sample
 pytestmark = pytest.mark.gpu
 
 
-# 16, 32 and 64 lanes a row, one and two chunks a lane; batches with tokens enough for two, four or eight rows at a time, beside the splits as long as those are one turn of the chip (the first of each width) and
+# 16, 32 and 64 lanes a row, one and two chunks a lane; batches with tokens enough for two, four or eight rows at a time, beside the splits as long as those are one turn of the chip (and the logits do not go head by head) and
 # beside the logits, and with too few; a sample of its own never has enough
 @pytest.mark.parametrize("dk,n_b,dtype", [(8, 165, "bf16"), (128, 165, "bf16"), (136, 165, "bf16"), (256, 165, "bf16"), (264, 100, "bf16"), (512, 100, "bf16"), (512, 400, "bf16"),
                                           (1024, 165, "bf16"), (4, 165, "f32"), (64, 165, "f32"), (68, 165, "f32"), (128, 165, "f32"), (132, 100, "f32"), (260, 165, "f32"), (512, 165, "f32"),
