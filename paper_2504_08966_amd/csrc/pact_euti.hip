@@ -1237,15 +1237,18 @@ static int keys_launch(const Batch& bt, const ScoreIn& in) {
     if (bt.B == 1) return bt.n_max > KEYS_SHORT ? KEYS_SPLIT : KEYS_LOGITS;
     return finish_in_prune(bt, in.n_q) && key_plan(bt, in.k_dt, in.n_kv * in.d_h, KEYS_SPLIT).blocks + bt.B <= CUS ? KEYS_SPLIT : KEYS_LOGITS;
 }
-// Hidden states, of the whole batch, whose norms are in the first launch: otherwise of single samples none (7290 tokens, 28 query heads: of both launches the first is as long without them), of batches such that both launches
-// read as much (16 ragged images 74.6 us with none, 74.9, 8 x 6272 87.4 and 85.8).  So also beside BY_HEAD, whose LDS leaves a CU room for two to four of their workgroups: four heads of 72 with 28 query heads, whole calls, all
-// in the first launch / as here, 16384 tokens 484.7 / 474.6, 8 x 1458 368.8 / 362.4, 16 x 2688 608.0 / 577.5, 8 x 6272 898.2 / 870.3, 64 query heads over two of 96 7290 654.0 / 647.0.
-static int norms_first(const Batch& bt, const ScoreIn& in, bool keys_there) {
+// Hidden states, of the whole batch, whose norms are in the first launch.  Of batches such that both launches read as much (16 ragged images 74.6 us with none, 74.9, 8 x 6272 87.4 and 85.8), also beside BY_HEAD, whose LDS leaves a CU room for two
+// to four of their workgroups: four heads of 72 with 28 query heads, whole calls, all in the first launch / as here, 16384 tokens 484.7 / 474.6, 8 x 1458 368.8 / 362.4, 16 x 2688 608.0 / 577.5, 8 x 6272 898.2 / 870.3, 64 query heads over two of 96
+// 7290 654.0 / 647.0.  Of single samples of more than 4096 tokens too where the queries are little beside them, of others none.  (Whole calls, none / half, us: four query heads 10501 tokens 167.1 / 165.0, 12001 197.1 / 195.2, 32768 645.2 / 639.5;
+// fp32 hidden states 8124 163.0 / 161.7, 16384 302.8 / 301.0, 7000 and two heads of 64 119.0 / 116.2, 13001 188.0 / 185.7.  fp32 queries 16384 466.7 / 468.6; 28 heads 7290 132.9 / 133.8, 12001 213.2 / 212.6, with fp32 hidden states
+// 7290 146.6 / 148.2; up to 4096 tokens 3000 92.8 / 93.0, 1458 83.2 / 83.6.)
+static int norms_first(const Batch& bt, const ScoreIn& in, int keys_launch) {
     if (inputs_first(bt, in)) return bt.total;
-    if (bt.B == 1) return 0;
     const int kb = in.k_dt == PACT_BF16 ? 2 : 4;
-    const int64_t keys = (int64_t)in.n_kv * in.d_h * kb * (keys_there ? 2 : 1), queries = (int64_t)in.n_q * in.d_h * (in.q_dt == PACT_BF16 ? 2 : 4);
-    const int64_t row = (int64_t)in.h * (in.h_dt == PACT_BF16 ? 2 : 4), share = (row + keys - queries) / 2;      // (bytes of each token's that the first launch has yet to read)
+    const int64_t row = (int64_t)in.h * (in.h_dt == PACT_BF16 ? 2 : 4), queries = (int64_t)in.n_q * in.d_h * (in.q_dt == PACT_BF16 ? 2 : 4);
+    if (bt.B == 1 && (bt.n_max <= KEYS_SHORT || 4 * queries > row)) return 0;
+    const int64_t keys = (int64_t)in.n_kv * in.d_h * kb * (keys_launch == KEYS_LOGITS ? 2 : keys_launch == KEYS_FIRST ? 0 : 1);     // (the logits' read, and that of their preparation)
+    const int64_t share = (row + keys - queries) / 2;      // (bytes of each token's that the first launch has yet to read)
     return share <= 0 ? 0 : share >= row ? bt.total : (int)(bt.total * share / row) & ~15;
 }
 
@@ -1257,7 +1260,7 @@ int launch_score(const Batch& bt, const Ws& w, const ScoreIn& in, float* scores,
     const int hb = in.h_dt == PACT_BF16 ? 2 : 4;
     NormArgs norm{(const char*)in.hidden, w.hnorm, in.h, in.h_dt == PACT_BF16, hidden_streams(bt.total, in.h, hb) ? 1 : 0, 0, bt.total};
     if (in.q_per_token) {
-        const int first = norms_first(bt, in, where == KEYS_LOGITS);
+        const int first = norms_first(bt, in, where);
         norm.to = first;
         if (const int rc = launch_query_sums(bt, w, in, norm, where == KEYS_FIRST ? &key : nullptr, key_blocks, st)) return rc;
         norm.from = first;

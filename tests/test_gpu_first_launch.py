@@ -128,3 +128,16 @@ def test_keys_among_hidden_states(h, n_q, d_h, two, mean):
         assert all(reps[k][f] == rep[f] for f in ("n_kept", "n_centers", "n_reincorporated", "zero_norm_seen", "nonfinite_seen", "score_near_ties")), k
         for name, m in (("scores", b - a), ("cluster_id", b - a), ("center_idx", rep["n_centers"]), ("merged", rep["n_centers"]), ("cluster_counts", rep["n_centers"])):
             assert torch.equal(o[name][a:a + m], one[name][:m]), (k, name)
+
+
+# single samples of more than 90 MB, part of whose norms are in the first launch: hidden states of one and of two launches' rows, rows of a part's end
+@pytest.mark.parametrize("n,h,dtype", [(4101, 5600, "f32"), (6403, 3584, "f32"), (11009, 4100, "f32"), (12001, 4096, "bf16")])
+def test_norms_in_both_launches(n, h, dtype):
+    g = torch.Generator("cuda").manual_seed(n)
+    hid = torch.randn(n, h, device="cuda", generator=g).to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+    ks, qs = (torch.randn(n, 64, device="cuda", generator=g).bfloat16() for _ in range(2))
+    assert n * (hid.element_size() * h + 256) > 90e6
+    want = hid.double().norm(dim=1) * torch.softmax(ks.double() @ qs.double().mean(0), dim=0)
+    for o in (P.pact_score(hid, ks, qs, 1, 64, 1), P.pact_reduce(hid, ks, ks, qs, 1, 64, 1, P.PactParams(0.5, 0.02, 2.0, 1.5))["scores"]):
+        torch.cuda.synchronize()
+        np.testing.assert_allclose(o[:n].cpu().numpy(), want.cpu().numpy(), rtol=2e-7)
